@@ -747,6 +747,11 @@ int32_t launch_gemm(const void* A, const void* W, void* C, const void* bias, con
   note_fallback(dtype, trans_w ? FLEXCO_K_GEMM_BWD : FLEXCO_K_GEMM_FWD);
   if (splits_out) *splits_out = 1;
   KernelTimerScope ts(FLEXCO_K_GENERIC, s);
+  if (dtype == FLEXCO_F32) {
+    const int32_t rc = launch_gemm_f32_mfma(A, W, C, bias, residual, M, N, K, lda, ldw, ldc, ldr, trans_w, s);
+    if (rc != FLEXCO_EUNSUPPORTED) return rc;
+    clear_error();
+  }
   return launch_gemm_generic(A, W, C, bias, residual, M, N, K, lda, ldw, ldc, ldr, trans_w, dtype, s);
 }
 }  // namespace flexco

@@ -94,6 +94,9 @@ int32_t launch_gemm(const void* A, const void* W, void* C, const void* bias, con
 int32_t launch_gemm_generic(const void* A, const void* W, void* C, const void* bias, const void* residual, int M,
                             int N, int K, size_t lda, size_t ldw, size_t ldc, size_t ldr, bool trans_w, int dtype,
                             hipStream_t s);
+// fp32 on the matrix cores; FLEXCO_EUNSUPPORTED (nothing launched) where K or a leading dimension is no multiple of four
+int32_t launch_gemm_f32_mfma(const void* A, const void* W, void* C, const void* bias, const void* residual, int M,
+                             int N, int K, size_t lda, size_t ldw, size_t ldc, size_t ldr, bool trans_w, hipStream_t s);
 // How the bf16 MFMA path tiles a product: one or two launches side by side in the output columns, each one tile
 // shape (bm x bn), `cols` output columns, K cut over `splits` blocks, a ring of `stages` stages.  part_elems: floats of
 // split-K scratch at hand (0 = none).  The gated form is the forward plan over its 2F interleaved columns.
