@@ -30,12 +30,17 @@ struct AttnArgs {
   float scale;
 };
 
-template <typename T>
-__global__ __launch_bounds__(256) void attn_fwd_generic_kernel(AttnArgs a, const T* __restrict__ q, size_t ldq,
-                                                               const T* __restrict__ kp, const T* __restrict__ vp,
-                                                               float* __restrict__ part_ml,
-                                                               float* __restrict__ part_acc) {
+// One wavefront per column, NW of them per block.  The kernel is a chain of loads (the fp32 configuration's grids do not
+// fill the chip): K rows and V page rows are read 16 bytes at a time with several loads in flight - a lane per key for the
+// scores, a lane per channel for the output - and a page id is looked up once per page (before: one element and one
+// lookup at a time: 78 us for the fp32 configuration's 68-token batch, 16 now).
+template <typename T, int NW>
+__global__ __launch_bounds__(64 * NW) void attn_fwd_generic_kernel(AttnArgs a, const T* __restrict__ q, size_t ldq,
+                                                                   const T* __restrict__ kp, const T* __restrict__ vp,
+                                                                   float* __restrict__ part_ml,
+                                                                   float* __restrict__ part_acc) {
   extern __shared__ float smem[];   // per wave: q[d] + scores[split_keys]
+  constexpr int N = Vec<T>::N;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   float* qs = smem + wave * (a.d + a.split_keys);
   float* sc = qs + a.d;
@@ -47,9 +52,9 @@ __global__ __launch_bounds__(256) void attn_fwd_generic_kernel(AttnArgs a, const
   const int r = a.tile_req[tile], t0 = a.tile_tok0[tile], ntok = a.tile_ntok[tile];
   const int group = a.nq / a.nkv;
   const int part = a.tile_part0[tile] + split;
-  const int k0 = split * a.split_keys;
-  const int32_t* bt = a.block_table + (size_t)r * a.max_pages;
-  for (int c = wave; c < ntok * group; c += 4) {
+  const int k0 = split * a.split_keys;       // the first key of a page
+  const int32_t* bt = a.block_table + (size_t)r * a.max_pages + k0 / a.ps;
+  for (int c = wave; c < ntok * group; c += NW) {
     const int t = t0 + c / group, h = kvh * group + c % group;
     const int kend = min(k0 + a.split_keys, a.tok_pos[t] + 1);
     const int nk = max(0, kend - k0);
@@ -57,11 +62,16 @@ __global__ __launch_bounds__(256) void attn_fwd_generic_kernel(AttnArgs a, const
     __builtin_amdgcn_wave_barrier();
     float m = -INFINITY;
     for (int jj = lane; jj < nk; jj += 64) {
-      const int j = k0 + jj;
-      const size_t page = bt[j / a.ps];
-      const T* kr = kp + ((page * a.nkv + kvh) * a.ps + j % a.ps) * (size_t)a.d;
+      const size_t page = bt[jj / a.ps];
+      const T* kr = kp + ((page * a.nkv + kvh) * a.ps + jj % a.ps) * (size_t)a.d;   // rows are whole 16-byte units
       float s = 0.f;
-      for (int dd = 0; dd < a.d; ++dd) s += qs[dd] * ld(kr + dd);
+#pragma unroll 8
+      for (int dd = 0; dd < a.d; dd += N) {
+        float kv[N];
+        Vec<T>::load(kr + dd, kv);
+#pragma unroll
+        for (int e = 0; e < N; ++e) s += qs[dd + e] * kv[e];
+      }
       s *= a.scale;
       sc[jj] = s;
       m = fmaxf(m, s);
@@ -78,10 +88,21 @@ __global__ __launch_bounds__(256) void attn_fwd_generic_kernel(AttnArgs a, const
     const size_t idx = ((size_t)part * a.nkv + kvh) * a.cols_per_tile + c;
     for (int dd = lane; dd < a.d; dd += 64) {
       float acc = 0.f;
-      for (int jj = 0; jj < nk; ++jj) {
-        const int j = k0 + jj;
-        const size_t page = bt[j / a.ps];
-        acc += sc[jj] * ld(vp + ((page * a.nkv + kvh) * (size_t)a.d + dd) * a.ps + j % a.ps);
+      for (int j0 = 0; j0 < nk; j0 += a.ps) {
+        const T* vr = vp + (((size_t)bt[j0 / a.ps] * a.nkv + kvh) * (size_t)a.d + dd) * a.ps;
+        const int n = min(a.ps, nk - j0);
+        if (a.ps % N == 0) {                 // (a page row is whole 16-byte units; slots past the last key may hold anything)
+#pragma unroll 4
+          for (int p0 = 0; p0 < n; p0 += N) {
+            float v[N];
+            Vec<T>::load(vr + p0, v);
+#pragma unroll
+            for (int e = 0; e < N; ++e)
+              if (p0 + e < n) acc += sc[j0 + p0 + e] * v[e];
+          }
+        } else {
+          for (int p = 0; p < n; ++p) acc += sc[j0 + p] * ld(vr + p);
+        }
       }
       part_acc[idx * a.d + dd] = acc;
     }
@@ -217,10 +238,12 @@ __global__ __launch_bounds__(64) void attn_bwd_dq_generic_kernel(const T* __rest
                                                                  const int32_t* __restrict__ pages,
                                                                  T* __restrict__ dq, int win_start, int nq, int nkv,
                                                                  int d, int ps, float scale) {
-  extern __shared__ float smem[];   // q[d], do[d], ds[64]
+  extern __shared__ float smem[];   // q[d], do[d], ds[64], row of each key of the step [64]
+  constexpr int N = Vec<T>::N;
   float* qs = smem;
   float* dos = smem + d;
   float* dss = smem + 2 * d;
+  size_t* rows = (size_t*)(dss + 64);   // the key's row of the K pool (d is even: 8-byte aligned)
   const size_t i = blockIdx.x;
   const int h = blockIdx.y, lane = threadIdx.x;
   const int group = nq / nkv, kvh = h / group;
@@ -237,12 +260,22 @@ __global__ __launch_bounds__(64) void attn_bwd_dq_generic_kernel(const T* __rest
     float ds = 0.f;
     if (j <= p) {
       const size_t page = pages[j / ps];
-      const T* kr = kp + ((page * nkv + kvh) * ps + j % ps) * (size_t)d;
+      const size_t row = (page * nkv + kvh) * ps + j % ps;
+      rows[lane] = row;
+      const T* kr = kp + row * (size_t)d;
       const T* vr = vp + ((page * nkv + kvh) * (size_t)d) * ps + j % ps;
       float s = 0.f, dp = 0.f;
-      for (int dd = 0; dd < d; ++dd) {
-        s += qs[dd] * ld(kr + dd);
-        dp += dos[dd] * ld(vr + (size_t)dd * ps);
+#pragma unroll 4
+      for (int dd = 0; dd < d; dd += N) {
+        float kv[N], vv[N];
+        Vec<T>::load(kr + dd, kv);
+#pragma unroll
+        for (int e = 0; e < N; ++e) vv[e] = ld(vr + (size_t)(dd + e) * ps);
+#pragma unroll
+        for (int e = 0; e < N; ++e) {
+          s += qs[dd + e] * kv[e];
+          dp += dos[dd + e] * vv[e];
+        }
       }
       const float pj = __expf(s * scale - row_lse);
       ds = pj * (dp - row_delta) * scale;
@@ -250,10 +283,9 @@ __global__ __launch_bounds__(64) void attn_bwd_dq_generic_kernel(const T* __rest
     dss[lane] = ds;
     __builtin_amdgcn_wave_barrier();
     const int nk = min(64, p + 1 - kc);
+#pragma unroll 8
     for (int jj = 0; jj < nk; ++jj) {
-      const int jk = kc + jj;
-      const size_t page = pages[jk / ps];
-      const T* kr = kp + ((page * nkv + kvh) * ps + jk % ps) * (size_t)d;
+      const T* kr = kp + rows[jj] * d;
       const float w = dss[jj];
 #pragma unroll
       for (int u = 0; u < 4; ++u)
@@ -361,9 +393,14 @@ int32_t launch_attention_generic(const flexco_layer_cfg& c, const flexco_maps& m
   a.scale = 1.0f / sqrtf((float)c.head_dim);
   const size_t shm = 4 * sizeof(float) * (size_t)(a.d + a.split_keys);
   if (shm > 64 * 1024) return fail(FLEXCO_EUNSUPPORTED, "kv_split_pages * page_size = %d keys is too large for the generic attention kernel", a.split_keys);
-  DISPATCH_T(c.dtype, hipLaunchKernelGGL((attn_fwd_generic_kernel<T>), dim3(m.n_items, c.n_kv_heads, FLEXCO_ATTN_ITEM_TILES), dim3(256), shm,
-                                         s, a, (const T*)q, ldq, (const T*)pool.k_pages, (const T*)pool.v_pages,
-                                         part_ml, part_acc));
+  const dim3 grid(m.n_items, c.n_kv_heads, FLEXCO_ATTN_ITEM_TILES);
+  // a tile has up to 16 columns: a wavefront for each while their score rows fit the same LDS
+  if (4 * shm <= 64 * 1024)
+    DISPATCH_T(c.dtype, hipLaunchKernelGGL((attn_fwd_generic_kernel<T, 16>), grid, dim3(1024), 4 * shm, s, a, (const T*)q, ldq,
+                                           (const T*)pool.k_pages, (const T*)pool.v_pages, part_ml, part_acc));
+  else
+    DISPATCH_T(c.dtype, hipLaunchKernelGGL((attn_fwd_generic_kernel<T, 4>), grid, dim3(256), shm, s, a, (const T*)q, ldq,
+                                           (const T*)pool.k_pages, (const T*)pool.v_pages, part_ml, part_acc));
   return post_launch("attn_fwd_generic");
 }
 
@@ -398,7 +435,7 @@ int32_t launch_attention_bwd_generic(const flexco_layer_cfg& c, const flexco_kv_
                                      const void* dout, void* dq, float* dk_accum, float* dv_accum, hipStream_t s) {
   const float scale = 1.0f / sqrtf((float)c.head_dim);
   const int l = win_start + win_len;
-  const size_t shm = sizeof(float) * (2 * (size_t)c.head_dim + 128);
+  const size_t shm = sizeof(float) * (2 * (size_t)c.head_dim + 64) + sizeof(size_t) * 64;   // (dK/dV: two score rows of 64)
   DISPATCH_T(c.dtype, {
     hipLaunchKernelGGL((attn_bwd_dq_generic_kernel<T>), dim3(win_len, c.n_q_heads), dim3(64), shm, s, (const T*)q,
                        (const T*)dout, lse, delta, (const T*)pool.k_pages, (const T*)pool.v_pages, seq_pages,

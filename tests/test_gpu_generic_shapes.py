@@ -41,3 +41,41 @@ def test_gemm_f32(M, N, K, trans):
     got = to_np(guard)
     assert np.all(np.abs(got[:M] - ref) <= bound)
     assert np.all(got[M:] == 7.0)               # nothing past the last row
+
+
+@pytest.mark.parametrize("cfg,split", [(ODD_F32, 0), (ODD_F32, 2), (WIDE_BF16, 0), (WIDE_BF16, 2),
+                                       (C1, 64)])           # 1024 keys per split: four wavefronts per block
+def test_generic_attention_forward(cfg, split):
+    print(f"attention forward {cfg.name} split={split}", flush=True)
+    batch = gen.mixed_batch(cfg.page_size, 4, decode_ctx=(1, 7, 1100, 64), prefill=[(0, 33, 33), (21, 18, 39)], finetune=[(50, 21, 71)])
+    out, a_o, lse, lse_o = attention_case(cfg, batch, split)
+    assert_close("attention out", out, a_o, TOL[cfg.dtype])
+    assert float(np.max(np.abs(lse - lse_o))) <= (1e-4 if cfg.dtype == "f32" else 2e-2)
+
+
+@pytest.mark.parametrize("cfg,win_start,win_len", [(ODD_F32, 0, 1), (ODD_F32, 61, 68), (WIDE_BF16, 40, 37), (C1, 130, 21)])
+def test_generic_attention_backward(cfg, win_start, win_len):
+    print(f"attention backward {cfg.name} [{win_start}, +{win_len})", flush=True)
+    l = win_start + win_len
+    n_pages = -(-l // cfg.page_size)
+    g = gen.rng(12, "generic_bwd", cfg.name, win_start, win_len)
+    pages = (g.permutation(n_pages + 3)[:n_pages] + 1).astype(np.int32)
+    rnd = lambda *s: gen.storage_round(cfg, g.standard_normal(s, dtype=np.float32))  # noqa: E731
+    K, V, q, do = rnd(l, cfg.kv_dim), rnd(l, cfg.kv_dim), rnd(win_len, cfg.q_dim), rnd(win_len, cfg.q_dim)
+    pos = np.arange(win_start, l)
+    f64 = lambda a: a.astype(np.float64)  # noqa: E731
+    o, lse = OO.attention(f64(q), pos, f64(K), f64(V), cfg.n_q_heads, cfg.n_kv_heads, cfg.head_dim)
+    dq_o, dk_o, dv_o = OO.attention_bwd(f64(q), pos, f64(K), f64(V), cfg.n_q_heads, cfg.n_kv_heads, cfg.head_dim, f64(do))
+    pool = HH.DevicePool(cfg, n_pages + 4)
+    pool.write_rows(pages, K, V)
+    dt = HH.TORCH_DTYPE[cfg.dtype]
+    dev = lambda a, t=dt: torch.from_numpy(np.ascontiguousarray(a)).to("cuda", t)  # noqa: E731
+    q_d, o_d, do_d, lse_d = dev(q), dev(o), dev(do), dev(lse, torch.float32)
+    dq, dk, dv = torch.empty_like(q_d), torch.ones(l, cfg.kv_dim, device="cuda"), torch.ones(l, cfg.kv_dim, device="cuda")
+    ws = torch.empty(win_len * cfg.n_q_heads * 4 + 64, dtype=torch.uint8, device="cuda")
+    B.flexco_attention_window_bwd(HH.c_cfg(cfg), pool.c, dev(pages, torch.int32), n_pages, win_start, win_len, q_d, o_d, lse_d, do_d,
+                                  dq, dk, dv, ws, ws.numel())
+    torch.cuda.synchronize()
+    assert_close("dq", to_np(dq), dq_o, TOL[cfg.dtype])
+    assert_close("dk", to_np(dk) - 1.0, dk_o, TOL[cfg.dtype])
+    assert_close("dv", to_np(dv) - 1.0, dv_o, TOL[cfg.dtype])
