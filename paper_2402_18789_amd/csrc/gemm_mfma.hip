@@ -1,4 +1,4 @@
-// bf16 projections on the matrix cores (v_mfma_f32_32x32x16_bf16), LDS-staged.
+// bf16 projections on the matrix cores (v_mfma_f32_16x16x32_bf16), LDS-staged.
 //
 //   TRANS = false:  C[M, N] = A[M, K] W[N, K]^T (+ bias[N]) (+ residual[M, N])   forward form
 //   TRANS = true :  C[M, N] = A[M, K] W[K, N]                                      input-gradient form
@@ -10,11 +10,11 @@
 // dX = dY W remains.
 //
 // Tiling: block tile BM x BN, 256 threads = 4 wavefronts in a 2 x 2 grid, each owning
-// (BM/2) x (BN/2) as 32 x 32 MFMA tiles with fp32 accumulators.
+// (BM/2) x (BN/2) as 16 x 16 MFMA tiles with fp32 accumulators (the 256 x 256 tile has a kernel of its own, below).
 //   * Forward form: operand tiles go from global memory straight into LDS
-//     (global_load_lds_dwordx4: one wavefront instruction fills 1 KB; lane l lands at
+//     (buffer_load_dwordx4 ... lds: one wavefront instruction fills 1 KB; lane l lands at
 //     base + 16 l), no staging registers and no LDS write instructions.  LDS is a ring of stages
-//     (four of 32 KB for the 128 tile, two of 64 KB for the 256 tile) whose loads are in flight
+//     (four of 32 KB for the 128 tile, two of 56 KB for the 256 x 192 tile) whose loads are in flight
 //     while another stage is multiplied; the per-stage barrier carries no memory fence, the wait
 //     in front of it names exactly the loads that must have landed.  Rows are XOR-swizzled in 16-byte chunks (applied to the
 //     global address a lane fetches) so that the ds_read_b128 operand fetches of 16 consecutive
@@ -41,7 +41,152 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 #define FLEXCO_GP(p) ((const __attribute__((address_space(1))) void*)(p))
 #define FLEXCO_LP(p) ((__attribute__((address_space(3))) void*)(p))
 
-__device__ inline int swz(int row, int chunk) { return chunk ^ ((row >> 1) & 7); }
+
+// c += w a^T on a 16 x 16 block over 32 of K.  The W fragment is the first operand: a lane then holds, for ONE output
+// row (lane % 16), 4 consecutive output columns.
+// 16 x 16 x 32 products rather than 32 x 32 x 16: both have the same peak, but on real data the chip's power limit sets
+// the rate, and the larger form moves every accumulator through the register file twice as often (back to back from
+// registers, N(0, 1) operands: 2.04 against 1.78 PFLOP/s; on zeros 2.43 and 2.45).
+// In assembly: accumulators of four registers left to the compiler wander between the two register files (64 - 330 moves
+// per pass of the loop below; 0 this way).  The compiler does not see a product in it, hence FLEXCO_ACC_FENCE before
+// anything else touches the accumulators (32 wait states, the products need 18) and the order of a loop's instructions
+// is the one they are written in.  Operands come from LDS reads, whose waits the compiler places for any use.
+#define FLEXCO_MFMA(c_, w_, a_) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c_) : "v"(w_), "v"(a_));
+#define FLEXCO_ACC_FENCE                                                                              \
+  {                                                                                                   \
+    __builtin_amdgcn_sched_barrier(0);                                                                \
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");                                                \
+    _Pragma("unroll") for (int i = 0; i < MT; ++i)                                                    \
+      _Pragma("unroll") for (int j = 0; j < NT; ++j) asm volatile("" : "+a"(acc[i][j]));              \
+    __builtin_amdgcn_sched_barrier(0);                                                                \
+  }
+
+// ---- epilogue: register e of acc[i][j] is row lane % 16, column 4 (lane / 16) + e of
+// the 16 x 16 block.  Stored as they lie, an instruction would touch 16 rows with 32 (bf16) or 64 (fp32)
+// bytes each; measured (with 32 x 32 blocks), such stores run at about 1 TB/s where whole 128-byte lines reach 3.5.  So every
+// wavefront turns its rows through a piece of the (now free) ring that only it touches (stg): accumulators in,
+// 16 bytes per lane along a row out, 128 contiguous bytes or more per row and instruction.
+// row0, col0 / ac_w: first row and column (act column) of this wavefront's tile. ------------
+template <int MT, int NT>
+__device__ __forceinline__ void store_tile_glu(const f32x4 (&acc)[MT][NT], bf16_t* stg, bf16_t* __restrict__ C, size_t ldc,
+                                               const GemmGlu& glu, int M, int N, int row0, int ac_w, int lane) {
+  // acc[i][2 f] (gate) and acc[i][2 f + 1] (up) belong to act columns 16 f .. + 16
+  constexpr int AW = NT * 8;                       // act columns of a wavefront's tile
+  constexpr int PITCH = AW + 8;                    // staged row in elements (16 bytes of padding)
+  constexpr int LPR = AW / 8;                      // lanes that cover a row, 16 bytes each
+  constexpr int LPRP = LPR <= 4 ? 4 : 8;           // ... rounded up to a power of two (the others idle)
+  constexpr int RPI = 64 / LPRP;                   // rows per instruction
+  const int l16 = lane & 15, q4 = lane >> 4;
+  const int ac_end = min(glu.col0 + N / 2, glu.F);
+  const int rl = lane / LPRP, cl = (lane % LPRP) * 8;
+  const bool lane_on = (lane % LPRP) < LPR && ac_w + cl < ac_end;   // F % 8 == 0: a run of 8 is in or out as a whole
+#pragma unroll
+  for (int i = 0; i < MT; i += 2) {
+    const int rb = row0 + i * 16;
+    const bool band_saves = glu.save_gate && rb + 32 > glu.save_row0 && rb < glu.save_row0 + glu.save_rows;   // uniform
+#pragma unroll
+    for (int what = 0; what < 3; ++what) {         // 0: act, 1: gate, 2: up (the last two for finetune rows only)
+      if (what > 0 && !band_saves) break;
+#pragma unroll
+      for (int ii = 0; ii < 2; ++ii)
+#pragma unroll
+        for (int f = 0; f < NT / 2; ++f) {
+          bf16x4 o;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            // gate and up pass through the storage type first (they are what the backward pass reads back)
+            const bf16_t gs = (bf16_t)acc[i + ii][2 * f][e], us = (bf16_t)acc[i + ii][2 * f + 1][e];
+            const float gv = (float)gs, uv = (float)us;
+            // (reciprocal instruction, 1 ulp, instead of the ten-instruction IEEE division: the tile's 64 K sigmoids are on
+            // the critical path of a launch whose blocks all end together)
+            o[e] = what == 0 ? (bf16_t)(gv * __builtin_amdgcn_rcpf(1.0f + __expf(-gv)) * uv) : (what == 1 ? gs : us);
+          }
+          *reinterpret_cast<bf16x4*>(stg + (ii * 16 + l16) * PITCH + f * 16 + 4 * q4) = o;
+        }
+      bf16_t* dst = what == 0 ? C : (what == 1 ? glu.save_gate : glu.save_up);
+      const size_t ldd = what == 0 ? ldc : glu.ld_save;
+#pragma unroll
+      for (int p = 0; p < 32 / RPI; ++p) {
+        const int r = p * RPI + rl, row = rb + r;
+        const int drow = what == 0 ? row : row - glu.save_row0;
+        const bool ok = lane_on && row < M && (what == 0 || (drow >= 0 && drow < glu.save_rows));
+        if (ok) *reinterpret_cast<bf16x8*>(dst + (size_t)drow * ldd + ac_w + cl) = *reinterpret_cast<const bf16x8*>(stg + r * PITCH + cl);
+      }
+      if (MT * NT > 16) __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+}
+
+// fp32 staging (what is added to the accumulators - bias, residual - is added in fp32 before the one rounding):
+// 32 rows x 64 columns at a time (32 columns where the wavefront's tile has that many left), rows 272 bytes apart.
+// P: this K split's partial sums, else NULL.  PRE: bias and residual were fetched ahead (bpre, rpre).
+constexpr int STORE_PITCH32 = 64 + 4;
+template <int MT, int NT, bool PRE, int PM, int PG>
+__device__ __forceinline__ void store_tile(const f32x4 (&acc)[MT][NT], float* stg, float* __restrict__ P, bf16_t* __restrict__ C,
+                                           size_t ldc, const bf16_t* __restrict__ bias, const bf16_t* __restrict__ res, size_t ldr,
+                                           const bf16x8 (&bpre)[PG], const bf16x8 (&rpre)[PM][PG][4], int M, int N, int row0,
+                                           int col0, int lane) {
+  const int l16 = lane & 15, q4 = lane >> 4;
+#pragma unroll
+  for (int i = 0; i < MT; i += 2) {
+    const int rb = row0 + i * 16;
+#pragma unroll
+    for (int j0 = 0; j0 < NT; j0 += 4) {
+      const int nj = (j0 + 2 < NT) ? 2 : 1;          // 32-column halves in this group (compile-time after unrolling)
+#pragma unroll
+      for (int ii = 0; ii < 2; ++ii)
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) {
+          if (jj >= 2 * nj) break;
+          *reinterpret_cast<f32x4*>(stg + (ii * 16 + l16) * STORE_PITCH32 + jj * 16 + 4 * q4) = acc[i + ii][j0 + jj];
+        }
+      const int cb = col0 + j0 * 16;                 // first column of the group
+      if (P) {
+        // 16 lanes x 4 columns per row, 4 rows per instruction
+        const int rl = lane >> 4, cl = (lane & 15) * 4;
+#pragma unroll
+        for (int p = 0; p < 8; ++p) {
+          const int r = p * 4 + rl, row = rb + r, col = cb + cl;
+          if (cl < nj * 32 && row < M && col < N)    // N % 8 == 0: a run of 4 is inside or outside as a whole
+            *reinterpret_cast<f32x4*>(P + (size_t)row * N + col) = *reinterpret_cast<const f32x4*>(stg + r * STORE_PITCH32 + cl);
+        }
+      } else {
+        // 8 lanes x 8 columns per row, 8 rows per instruction
+        const int rl = lane >> 3, cl = (lane & 7) * 8;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+          const int r = p * 8 + rl, row = rb + r, col = cb + cl;
+          if (cl < nj * 32 && row < M && col < N) {  // N % 8 == 0: a run of 8 is inside or outside as a whole
+            const f32x4 lo = *reinterpret_cast<const f32x4*>(stg + r * STORE_PITCH32 + cl);
+            const f32x4 hi = *reinterpret_cast<const f32x4*>(stg + r * STORE_PITCH32 + cl + 4);
+            float v[8];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { v[e] = lo[e]; v[4 + e] = hi[e]; }
+            if (bias) {
+              bf16x8 b8;
+              if constexpr (PRE) b8 = bpre[j0 / 4]; else b8 = *reinterpret_cast<const bf16x8*>(bias + col);
+#pragma unroll
+              for (int e = 0; e < 8; ++e) v[e] += (float)b8[e];
+            }
+            if (res) {
+              bf16x8 r8;
+              if constexpr (PRE) r8 = rpre[i / 2][j0 / 4][p]; else r8 = *reinterpret_cast<const bf16x8*>(res + (size_t)row * ldr + col);
+#pragma unroll
+              for (int e = 0; e < 8; ++e) v[e] += (float)r8[e];
+            }
+            bf16x8 o;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) o[e] = (bf16_t)v[e];
+            *reinterpret_cast<bf16x8*>(C + (size_t)row * ldc + col) = o;
+          }
+        }
+      }
+      // (keeps the scheduler from gathering the stores of the whole tile up front, which costs more
+      // registers than the large tile has left)
+      if (MT * NT > 16) __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+}
 
 template <int BM, int BN, bool TRANS, bool GLU = false, int NSTAGES = 0>
 __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W,
@@ -50,7 +195,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
                                                         size_t lda, size_t ldw, size_t ldc, size_t ldr, int tiles_m,
                                                         int tiles_n, GemmExt ext, float* __restrict__ part,
                                                         int k_chunk, GemmGlu glu) {
-  constexpr int WM = BM / 2, WN = BN / 2, MT = WM / 32, NT = WN / 32;
+#ifdef __HIP_DEVICE_COMPILE__      // (the host pass knows no such assembly)
+  constexpr int WM = BM / 2, WN = BN / 2, MT = WM / 16, NT = WN / 16;
 
   // ---- work-group id -> tile, XCD-aware ------------------------------------------------
   int lid = blockIdx.x;
@@ -63,37 +209,25 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wavefront-uniform: LDS bases of the tile loads stay scalar
   const int wm0 = (wave >> 1) * WM, wn0 = (wave & 1) * WN;
 
-  f32x16 acc[MT][NT];
+  f32x4 acc[MT][NT];
 #pragma unroll
   for (int i = 0; i < MT; ++i)
 #pragma unroll
     for (int j = 0; j < NT; ++j)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+      for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
 
   // split-K: blockIdx.y owns k in [kbeg, kbeg + k_chunk) and writes fp32 partial sums to `part`
   const int kbeg = blockIdx.y * k_chunk;
-  const int l32 = lane & 31, kg = lane >> 5;
-
-  // The W fragment is the MFMA's first operand: a lane then holds, for ONE output row (lane % 32), runs
-  // of 4 consecutive output columns, so the epilogue moves 8 bytes per lane and instruction.
-  // (the pipelines are macros on purpose: register arrays captured by lambdas were left in
-  // scratch memory)
-#define FLEXCO_MFMAS(af_, bf_)                                                                        \
-  {                                                                                                   \
-    _Pragma("unroll") for (int i = 0; i < MT; ++i)                                                    \
-      _Pragma("unroll") for (int j = 0; j < NT; ++j)                                                  \
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf_[j], af_[i], acc[i][j], 0, 0, 0);      \
-  }
+  const int l16 = lane & 15, q4 = lane >> 4;
 
   // ===================== operand tiles: global memory -> LDS directly ==========================
   // A ring of stages of 64 k-columns; a stage holds the A tile [BM][64] and the W tile ([BN][64]
   // in the forward form, [64][BN] in the input-gradient form), A first.  The 128-row forward
   // tiles use four stages (32 KB each at 128 columns, 40 KB - all of the LDS - at 192): up to
   // three in flight or waiting while one is multiplied.
-  // The 256-row tiles use two stages (64 KB at 256 columns, 56 KB at 192): half as many barriers, and a stage's buffer is
-  // handed to the loads of the stage after next as soon as its last fragments are in registers
-  // (measured equal at T = 1024 and 4-7 % faster than four 32 KB stages at T >= 2048).  The
+  // The 256 x 192 tile uses two stages (56 KB): half as many barriers, and a stage's buffer is
+  // handed to the loads of the stage after next as soon as its last fragments are in registers.  The
   // input-gradient form uses two stages of 32 KB, so that two blocks share a CU (its grids are
   // K-split into more blocks than CUs).  The stages are separate arrays, not one indexed
   // buffer: the compiler then sees that loads in flight target an array no ds_read of that
@@ -102,10 +236,10 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
   // faster than one four-stage block per CU in two rounds (one block's waits are the other's products); with one
   // tile per CU the four stages win.
   constexpr int NST = NSTAGES ? NSTAGES : (TRANS ? 2 : ((BM + BN) * BK * 2 * 4 <= 160 * 1024 ? 4 : 2));   // stages in the ring
-  constexpr int SL = BK / 16;                                       // MFMA k-slices per stage
+  constexpr int SL = BK / 32;                                       // MFMA k-slices per stage
   constexpr int PA = BM / 32, PB = BN / 32;                         // 1 KB load instructions per wavefront and stage
   constexpr int ST_ELEMS = (BM + BN) * BK;
-  static_assert(!TRANS || BN == 128 || BN == 256, "the input-gradient form's W tile swizzle assumes 256- or 512-byte rows");
+  static_assert(!TRANS || BN == 128, "the input-gradient form's W tile swizzle assumes 256-byte rows");
   __shared__ __attribute__((aligned(1024))) bf16_t ring0[ST_ELEMS];
   __shared__ __attribute__((aligned(1024))) bf16_t ring1[ST_ELEMS];
   __shared__ __attribute__((aligned(1024))) bf16_t ring2[NST == 4 ? ST_ELEMS : 8];
@@ -113,9 +247,9 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
   // [rows][64] tiles (128-byte rows): chunk c of row r is stored at chunk c ^ ((r >> 1) & 7) (the
   // variant measured fastest for the ds_read_b128 operand fetches: 85 % of the LDS peak).
   // [64][BN] W tile of the input-gradient form (256- or 512-byte rows, read by transposing LDS reads of
-  // 4 consecutive rows x 64 bytes per pass): chunk c of row r is stored at chunk c ^ (4 (r & 3)),
-  // which puts the four rows of a pass on the four 64-byte quarters of the banks (the exchange stays
-  // inside a 256-byte half of a 512-byte row).
+  // 4 consecutive rows x 32 bytes, two such blocks 8 rows apart per pass): chunk c of row r is stored at
+  // chunk c ^ (4 (r & 3)) ^ (2 (r / 8 & 1)), which puts the four rows on the four 64-byte quarters of the banks
+  // and the two blocks on the halves of a quarter.
 #define FLEXCO_KEY(r_) (((r_) >> 1) & 7)
   // Load instruction p of wavefront w fills 1 KB = rows 8 (4 p + w) .. + 8 of a [rows][64] tile (rows
   // TR (4 p + w) .. + TR of the [64][BN] tile, TR = 512 / BN); lane l lands at base + 16 l, so it fetches from
@@ -124,66 +258,79 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
   const int d_c = (lane & 7) ^ FLEXCO_KEY(wave * 8 + d_row);
   constexpr int TCH = BN / 8, TR = 64 / TCH;      // 16-byte chunks of a W-tile row, rows per load instruction
   const int t_row = lane / TCH;
-  const int t_c = (lane % TCH) ^ (((wave * TR + t_row) & 3) << 2);
-  const bf16_t* ga[PA];
-  const bf16_t* gw[PB];
+  const int t_k = wave * TR + t_row;              // its row, up to a multiple of 16
+  const int t_c = (lane % TCH) ^ ((t_k & 3) << 2) ^ (((t_k >> 3) & 1) << 1);
+  // byte offsets from the tile's own corner: 32 bits (the launcher refuses what would not fit)
+  unsigned oa[PA], ow[PB];
 #pragma unroll
-  for (int p = 0; p < PA; ++p)
-    ga[p] = A + (size_t)min(m0 + (p * 4 + wave) * 8 + d_row, M - 1) * lda + kbeg + d_c * 8;
+  for (int p = 0; p < PA; ++p) oa[p] = (unsigned)((size_t)min((p * 4 + wave) * 8 + d_row, M - 1 - m0) * lda * 2 + d_c * 16);
 #pragma unroll
   for (int p = 0; p < PB; ++p) {
     if (GLU) {
       // W-tile rows alternate between the two halves of W in runs of 16: rows 32 f .. + 16 are gate rows
       // (act columns tile + 16 f .. + 16), rows 32 f + 16 .. + 16 the up rows of the same columns, so that
-      // a lane's accumulators of one fragment hold gate and up of the same 4 + 4 act columns
+      // a lane holds gate and up of the same 4 act columns in neighbouring accumulators
       const int rr = (p * 4 + wave) * 8 + d_row;
       const int ac = glu.col0 + tn * (BN / 2) + (rr >> 5) * 16 + (rr & 15);
-      gw[p] = W + ((size_t)((rr >> 4) & 1) * glu.F + min(ac, glu.F - 1)) * ldw + kbeg + d_c * 8;
+      ow[p] = (unsigned)(((size_t)((rr >> 4) & 1) * glu.F + min(ac, glu.F - 1)) * ldw * 2 + d_c * 16);
     } else if (!TRANS) {
-      gw[p] = W + (size_t)min(n0 + (p * 4 + wave) * 8 + d_row, N - 1) * ldw + kbeg + d_c * 8;
+      ow[p] = (unsigned)((size_t)min((p * 4 + wave) * 8 + d_row, N - 1 - n0) * ldw * 2 + d_c * 16);
     } else {
-      int col = n0 + t_c * 8;
-      if (col >= N) col = 0;   // masked at the store
-      gw[p] = W + (size_t)(kbeg + (p * 4 + wave) * TR + t_row) * ldw + col;
+      int col = t_c * 8;
+      if (n0 + col >= N) col = 0;   // masked at the store
+      ow[p] = (unsigned)((size_t)((p * 4 + wave) * TR + t_row) * ldw * 2 + col * 2);
     }
   }
+  const char* const pa = (const char*)(A + (size_t)m0 * lda + kbeg);
+  const char* const pw = (const char*)(GLU ? W + kbeg : (TRANS ? W + (size_t)kbeg * ldw + n0 : W + (size_t)n0 * ldw + kbeg));
+  const size_t wstep = TRANS ? (size_t)BK * ldw * 2 : (size_t)BK * 2;
   const int ns = k_chunk / BK;                   // stages of this block
 
   // stage index past the end: clamped, the loads repeat the last stage into a free buffer
+#define GEMM_SRC_A(s_) __builtin_amdgcn_make_buffer_rsrc((void*)(pa + (size_t)min((s_), ns - 1) * (BK * 2)), 0, -1, 0x00027000)
+#define GEMM_SRC_W(s_) __builtin_amdgcn_make_buffer_rsrc((void*)(pw + (size_t)min((s_), ns - 1) * wstep), 0, -1, 0x00027000)
+  // load instruction q of a stage's PA + PB
+#define FLEXCO_LOAD(ring_, q_)                                                                        \
+  {                                                                                                   \
+    if ((q_) < PA)                                                                                    \
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(sa_, FLEXCO_LP(ring_ + ((q_) * 4 + wave) * 512), 16, oa[(q_) < PA ? (q_) : 0], 0, 0, 0); \
+    else                                                                                              \
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(sw_, FLEXCO_LP(ring_ + BM * BK + (((q_) - PA) * 4 + wave) * 512), 16, ow[(q_) < PA ? 0 : (q_) - PA], 0, 0, 0); \
+  }
 #define FLEXCO_DMA(ring_, s_)                                                                         \
   {                                                                                                   \
-    const int koff_ = min((s_), ns - 1) * BK;                                                         \
-    _Pragma("unroll") for (int p = 0; p < PA; ++p)                                                    \
-      __builtin_amdgcn_global_load_lds(FLEXCO_GP(ga[p] + koff_),                                      \
-                                       FLEXCO_LP(ring_ + (p * 4 + wave) * 512), 16, 0, 0);            \
-    _Pragma("unroll") for (int p = 0; p < PB; ++p)                                                    \
-      __builtin_amdgcn_global_load_lds(FLEXCO_GP(gw[p] + (TRANS ? (size_t)koff_ * ldw : (size_t)koff_)), \
-                                       FLEXCO_LP(ring_ + BM * BK + (p * 4 + wave) * 512), 16, 0, 0);  \
+    const __amdgpu_buffer_rsrc_t sa_ = GEMM_SRC_A(s_), sw_ = GEMM_SRC_W(s_);                      \
+    _Pragma("unroll") for (int q = 0; q < PA + PB; ++q) FLEXCO_LOAD(ring_, q)                         \
   }
   // Operand fragments of W in the input-gradient form come from transposing LDS reads
   // (ds_read_b64_tr_b16): within a group of 16 lanes, lane s hands in the address of 4 consecutive
   // columns, 4 (s % 4) .., of row s / 4, and lane i receives column i of those 4 rows - i.e. 4
-  // consecutive k for one column, the MFMA operand order.  Group g of the wavefront covers columns
-  // 16 (g % 2) .. + 16 and the k-half g / 2; two reads (rows 0..3 and 4..7) make the 8 k of a fragment.
-  const int tr_k = 8 * (lane >> 5) + ((lane & 15) >> 2);
-  const int tr_n = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-  const int tr_sw = ((lane & 15) >> 2) << 2;     // 4 (row & 3): the fragment's rows are tr_k + multiples of 4
-#define FLEXCO_FRAGS(ring_, kk_, af_, bf_)                                                            \
+  // consecutive k for one column, the MFMA operand order.  Group g of the wavefront covers k rows
+  // 8 g .. + 8 of a slice's 32; two reads (rows 0..3 and 4..7) make the 8 k of a fragment.
+  // (element offset of a read inside the W tile; one index expression from the array on: behind a longer chain of pointer
+  // steps the compiler loses which array a read is from and waits for every load in flight, and did: the input-gradient
+  // products took 1.2 - 1.4 times as long)
+  int tr_off[NT];
+#pragma unroll
+  for (int j = 0; j < NT; ++j) {
+    const int col = wn0 + j * 16 + 4 * (lane & 3);
+    tr_off[j] = (8 * q4 + (l16 >> 2)) * BN + (((col >> 3) ^ ((l16 >> 2) << 2) ^ ((q4 & 1) << 1)) * 8) + (col & 7);
+  }
+  // fragment q of a slice's MT + NT: rows of A first, then columns of W
+#define FLEXCO_FRAG(ring_, kk_, af_, bf_, q_)                                                         \
   {                                                                                                   \
-    _Pragma("unroll") for (int i = 0; i < MT; ++i) {                                                  \
-      const int r_ = wm0 + i * 32 + l32;                                                              \
-      af_[i] = *reinterpret_cast<const bf16x8*>(ring_ + r_ * BK + (((kk_) * 2 + kg) ^ FLEXCO_KEY(r_)) * 8); \
-    }                                                                                                 \
-    _Pragma("unroll") for (int j = 0; j < NT; ++j) {                                                  \
+    if ((q_) < MT) {                                                                                  \
+      const int r_ = wm0 + (q_) * 16 + l16;                                                           \
+      af_[(q_) < MT ? (q_) : 0] = *reinterpret_cast<const bf16x8*>(ring_ + r_ * BK + (((kk_) * 4 + q4) ^ FLEXCO_KEY(r_)) * 8); \
+    } else {                                                                                          \
+      const int j_ = (q_) < MT ? 0 : (q_) - MT;                                                       \
       if (!TRANS) {                                                                                   \
-        const int r_ = wn0 + j * 32 + l32;                                                            \
-        bf_[j] = *reinterpret_cast<const bf16x8*>(ring_ + (BM + r_) * BK + (((kk_) * 2 + kg) ^ FLEXCO_KEY(r_)) * 8); \
+        const int r_ = wn0 + j_ * 16 + l16;                                                           \
+        bf_[j_] = *reinterpret_cast<const bf16x8*>(ring_ + (BM + r_) * BK + (((kk_) * 4 + q4) ^ FLEXCO_KEY(r_)) * 8); \
       } else {                                                                                        \
-        const int col_ = wn0 + j * 32 + tr_n;                                                         \
-        const bf16_t* blk_ = ring_ + BM * BK + ((kk_) * 16 + tr_k) * BN + (((col_ >> 3) ^ tr_sw) * 8) + (col_ & 7); \
-        const s16x4 lo_ = __builtin_amdgcn_ds_read_tr16_b64_v4i16((FLEXCO_LDS s16x4*)blk_);           \
-        const s16x4 hi_ = __builtin_amdgcn_ds_read_tr16_b64_v4i16((FLEXCO_LDS s16x4*)(blk_ + 4 * BN)); \
-        bf_[j] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo_, hi_, 0, 1, 2, 3, 4, 5, 6, 7)); \
+        const s16x4 lo_ = __builtin_amdgcn_ds_read_tr16_b64_v4i16((FLEXCO_LDS s16x4*)(ring_ + (tr_off[j_] + (BM * BK + (kk_) * 32 * BN)))); \
+        const s16x4 hi_ = __builtin_amdgcn_ds_read_tr16_b64_v4i16((FLEXCO_LDS s16x4*)(ring_ + (tr_off[j_] + (BM * BK + ((kk_) * 32 + 4) * BN)))); \
+        bf_[j_] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo_, hi_, 0, 1, 2, 3, 4, 5, 6, 7)); \
       }                                                                                               \
     }                                                                                                 \
   }
@@ -206,49 +353,25 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
   //   everyone has the last fragments of stage s in registers; start the loads of the stage
   //   that takes over the freed buffer; fetch slice 0 of stage s + 1; then the last slice's
   //   MFMAs cover those latencies.
+  // A read (and, in the stage's last slice, a load) goes behind each product until they are used up.
+#define FLEXCO_SLICE(af_, bf_, ring_, kk_, raf_, rbf_, load_)                                         \
+  {                                                                                                   \
+    _Pragma("unroll") for (int n = 0; n < MT * NT; ++n) {                                             \
+      FLEXCO_MFMA(acc[n / NT][n % NT], bf_[n % NT], af_[n / NT])                                      \
+      load_                                                                                           \
+      if (n < MT + NT) FLEXCO_FRAG(ring_, kk_, raf_, rbf_, n)                                         \
+      __builtin_amdgcn_sched_barrier(0);                                                              \
+    }                                                                                                 \
+  }
 #define FLEXCO_STAGE(cur_, nxt_, free_, s_)                                                           \
   {                                                                                                   \
-    _Pragma("unroll") for (int kk = 0; kk < SL; kk += 2) {                                            \
-      FLEXCO_FRAGS(cur_, kk + 1, af1, bf1)                                                            \
-      FLEXCO_MFMAS(af0, bf0)                                                                          \
-      FLEXCO_ORDER_READS_FIRST                                                                        \
-      __builtin_amdgcn_sched_barrier(0);                                                              \
-      if (kk + 2 < SL) {                                                                              \
-        FLEXCO_FRAGS(cur_, kk + 2, af0, bf0)                                                          \
-        FLEXCO_MFMAS(af1, bf1)                                                                        \
-        FLEXCO_ORDER_READS_FIRST                                                                      \
-      } else {                                                                                        \
-        FLEXCO_WAIT_BARRIER(WAIT_NEXT_STAGE)                                                          \
-        FLEXCO_DMA(free_, (s_) + AHEAD)                                                               \
-        FLEXCO_FRAGS(nxt_, 0, af0, bf0)                                                               \
-        FLEXCO_MFMAS(af1, bf1)                                                                        \
-        FLEXCO_ORDER_LOADS_READS_FIRST                                                                \
-      }                                                                                               \
-      __builtin_amdgcn_sched_barrier(0);                                                              \
-    }                                                                                                 \
+    FLEXCO_SLICE(af0, bf0, cur_, 1, af1, bf1, )                                                       \
+    FLEXCO_WAIT_BARRIER(WAIT_NEXT_STAGE)                                                              \
+    const __amdgpu_buffer_rsrc_t sa_ = GEMM_SRC_A((s_) + AHEAD), sw_ = GEMM_SRC_W((s_) + AHEAD);  \
+    FLEXCO_SLICE(af1, bf1, nxt_, 0, af0, bf0, if (n < NLD) FLEXCO_LOAD(free_, n))                     \
   }
-  // Instruction order inside a slice, imposed on the scheduler (it otherwise sinks the fragment
-  // reads behind the MFMAs, right in front of their first use): LDS reads - or global loads and
-  // LDS reads - ahead of each MFMA until they are used up, the remaining MFMAs after.
-  // Masks: 0x008 MFMA, 0x020 VMEM read, 0x100 DS read.
-  constexpr int NRD = MT + (TRANS ? 2 * NT : NT);                  // LDS reads of one slice
-  constexpr int NMF = MT * NT;                                     // its MFMAs
+  static_assert(SL == 2 && MT * NT >= MT + NT && MT * NT >= PA + PB, "a slice's products outnumber its reads and a stage's loads");
   constexpr int NLD = PA + PB;                                     // loads of one stage
-#define FLEXCO_ORDER_READS_FIRST                                                                      \
-  {                                                                                                   \
-    _Pragma("unroll") for (int q = 0; q < NMF; ++q) {                                                 \
-      __builtin_amdgcn_sched_group_barrier(0x100, (NRD + NMF - 1) / NMF, 0);                          \
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                              \
-    }                                                                                                 \
-  }
-#define FLEXCO_ORDER_LOADS_READS_FIRST                                                                \
-  {                                                                                                   \
-    _Pragma("unroll") for (int q = 0; q < NMF; ++q) {                                                 \
-      __builtin_amdgcn_sched_group_barrier(0x020, (NLD + NMF - 1) / NMF, 0);                          \
-      __builtin_amdgcn_sched_group_barrier(0x100, (NRD + NMF - 1) / NMF, 0);                          \
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                              \
-    }                                                                                                 \
-  }
   // s_waitcnt immediates: vmcnt in bits 3:0 and 15:14, expcnt 6:4 and lgkmcnt 11:8 left at
   // their maxima (no wait)
 #define FLEXCO_VMCNT(n_) (0x0F70 | ((n_) & 15) | (((n_) >> 4) << 14))
@@ -259,44 +382,51 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
   // ---- operands of the rank-r extension's first step and the residual / bias of the epilogue, fetched ahead of the
   // main loop (128-row tiles: the registers are there; their round trips - one or two per block, all blocks
   // ending together - otherwise lie open at the end of the launch) --------------------------------------------
-  // forward form: an entry covers a column range whose ends are multiples of 32, so each 32-column
+  // forward form: an entry covers a column range whose ends are multiples of 32, so each 16-column
   // fragment of the tile belongs to at most one entry; fragments outside this entry multiply zeros
+  // (16 x 16 x 16 products: lane l holds k = 4 (l / 16) .. + 4 of row or column l % 16)
 #define FLEXCO_EXT_SKIPS(e_) (!TRANS && !GLU && (n0 + BN <= ext.col0[e_] || n0 >= ext.col1[e_]))
 #define FLEXCO_EXT_LOAD(e_, k2_, af_, bfr_)                                                           \
   {                                                                                                   \
     const bf16_t* A2_ = ext.A2[e_];                                                                   \
     const bf16_t* W2_ = ext.W2[e_];                                                                   \
     _Pragma("unroll") for (int i = 0; i < MT; ++i) {                                                  \
-      const int r_ = min(m0 + wm0 + i * 32 + l32, M - 1);                                             \
-      af_[i] = *reinterpret_cast<const bf16x8*>(A2_ + (size_t)r_ * ext.r + (k2_) + kg * 8);           \
+      const int r_ = min(m0 + wm0 + i * 16 + l16, M - 1);                                             \
+      af_[i] = *reinterpret_cast<const bf16x4*>(A2_ + (size_t)r_ * ext.r + (k2_) + q4 * 4);           \
     }                                                                                                 \
     _Pragma("unroll") for (int j = 0; j < NT; ++j) {                                                  \
       if (GLU) {                                                                                      \
-        /* this lane's W-tile row is a gate or an up row: column of the [gate | up] range the entries address */ \
-        const int ac_ = glu.col0 + tn * (BN / 2) + ((wn0 + j * 32) >> 1) + (l32 & 15);                \
-        const int lc_ = (l32 >> 4) * glu.F + ac_;                                                     \
+        /* even fragments are gate, odd ones up rows: column of the [gate | up] range the entries address */ \
+        const int ac_ = glu.col0 + tn * (BN / 2) + ((wn0 + (j & ~1) * 16) >> 1) + l16;                \
+        const int lc_ = (j & 1) * glu.F + ac_;                                                        \
         if (ac_ < glu.F && lc_ >= ext.col0[e_] && lc_ < ext.col1[e_]) {                               \
-          bfr_[j] = *reinterpret_cast<const bf16x8*>(W2_ + (size_t)(lc_ - ext.col0[e_]) * ext.ldw2[e_] + (k2_) + kg * 8); \
+          bfr_[j] = *reinterpret_cast<const bf16x4*>(W2_ + (size_t)(lc_ - ext.col0[e_]) * ext.ldw2[e_] + (k2_) + q4 * 4); \
         } else {                                                                                      \
-          _Pragma("unroll") for (int q = 0; q < 8; ++q) bfr_[j][q] = (bf16_t)0.f;                     \
+          _Pragma("unroll") for (int q = 0; q < 4; ++q) bfr_[j][q] = (bf16_t)0.f;                     \
         }                                                                                             \
       } else if (!TRANS) {                                                                            \
-        const int cj_ = n0 + wn0 + j * 32;                                                            \
+        const int cj_ = n0 + wn0 + j * 16;                                                            \
         if (cj_ >= ext.col0[e_] && cj_ < ext.col1[e_]) {                                              \
-          const int c_ = min(cj_ + l32, ext.col1[e_] - 1) - ext.col0[e_];                             \
-          bfr_[j] = *reinterpret_cast<const bf16x8*>(W2_ + (size_t)c_ * ext.ldw2[e_] + (k2_) + kg * 8); \
+          const int c_ = min(cj_ + l16, ext.col1[e_] - 1) - ext.col0[e_];                             \
+          bfr_[j] = *reinterpret_cast<const bf16x4*>(W2_ + (size_t)c_ * ext.ldw2[e_] + (k2_) + q4 * 4); \
         } else {                                                                                      \
-          _Pragma("unroll") for (int q = 0; q < 8; ++q) bfr_[j][q] = (bf16_t)0.f;                     \
+          _Pragma("unroll") for (int q = 0; q < 4; ++q) bfr_[j][q] = (bf16_t)0.f;                     \
         }                                                                                             \
       } else {                                                                                        \
-        const int c_ = min(n0 + wn0 + j * 32 + l32, N - 1);                                           \
-        _Pragma("unroll") for (int q = 0; q < 8; ++q) bfr_[j][q] = W2_[(size_t)((k2_) + kg * 8 + q) * ext.ldw2[e_] + c_]; \
+        const int c_ = min(n0 + wn0 + j * 16 + l16, N - 1);                                           \
+        _Pragma("unroll") for (int q = 0; q < 4; ++q) bfr_[j][q] = W2_[(size_t)((k2_) + q4 * 4 + q) * ext.ldw2[e_] + c_]; \
       }                                                                                               \
     }                                                                                                 \
   }
-  constexpr bool PF = MT * NT <= 4;
+#define FLEXCO_EXT_MFMAS(af_, bfr_)                                                                   \
+  {                                                                                                   \
+    _Pragma("unroll") for (int i = 0; i < MT; ++i)                                                    \
+      _Pragma("unroll") for (int j = 0; j < NT; ++j)                                                  \
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, bfr_[j]), __builtin_bit_cast(s16x4, af_[i]), acc[i][j], 0, 0, 0); \
+  }
+  constexpr bool PF = MT * NT <= 16;
   int e_first = -1;
-  bf16x8 paf[PF ? MT : 1], pbf[PF ? NT : 1];
+  bf16x4 paf[PF ? MT : 1], pbf[PF ? NT : 1];
   if constexpr (PF) {
     if (blockIdx.y == 0) {
       for (int e = 0; e < ext.n; ++e)
@@ -305,35 +435,38 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
     }
   }
   // residual and bias in the layout the epilogue stores in: 8 lanes x 8 columns per row, 8 rows per instruction,
-  // 32 rows x 64 columns per group of two fragments
-  constexpr int NG = (NT + 1) / 2;
-  constexpr bool PF_RES = !GLU && MT * NT <= 6;
-  bf16x8 rpre[PF_RES ? MT : 1][PF_RES ? NG : 1][4];
+  // 32 rows x 64 columns per group of 2 x 4 fragments
+  constexpr int NG = (NT + 3) / 4;
+  constexpr bool PF_RES = !GLU && MT * NT <= 24;
+  bf16x8 rpre[PF_RES ? MT / 2 : 1][PF_RES ? NG : 1][4];
   bf16x8 bpre[PF_RES ? NG : 1];
   if constexpr (PF_RES) if (!part) {
 #pragma unroll
-    for (int j0 = 0; j0 < NT; j0 += 2) {
-      const int col = n0 + wn0 + j0 * 32 + (lane & 7) * 8;
-      const bool col_ok = (lane & 7) * 8 < ((j0 + 1 < NT) ? 64 : 32) && col < N;
-      if (bias && col_ok) bpre[j0 / 2] = *reinterpret_cast<const bf16x8*>(bias + col);
+    for (int j0 = 0; j0 < NT; j0 += 4) {
+      const int col = n0 + wn0 + j0 * 16 + (lane & 7) * 8;
+      const bool col_ok = (lane & 7) * 8 < ((j0 + 2 < NT) ? 64 : 32) && col < N;
+      if (bias && col_ok) bpre[j0 / 4] = *reinterpret_cast<const bf16x8*>(bias + col);
       if (res) {
 #pragma unroll
-        for (int i = 0; i < MT; ++i)
+        for (int i = 0; i < MT / 2; ++i)
 #pragma unroll
           for (int p = 0; p < 4; ++p) {
             const int row = m0 + wm0 + i * 32 + p * 8 + (lane >> 3);
-            if (col_ok && row < M) rpre[i][j0 / 2][p] = *reinterpret_cast<const bf16x8*>(res + (size_t)row * ldr + col);
+            if (col_ok && row < M) rpre[i][j0 / 4][p] = *reinterpret_cast<const bf16x8*>(res + (size_t)row * ldr + col);
           }
       }
     }
   }
   bf16x8 af0[MT], bf0[NT], af1[MT], bf1[NT];
+  FLEXCO_ACC_FENCE
+#define FLEXCO_FIRST_FRAGS                                                                            \
+  { _Pragma("unroll") for (int q = 0; q < MT + NT; ++q) FLEXCO_FRAG(ring0, 0, af0, bf0, q) }
   if constexpr (NST == 4) {
     FLEXCO_DMA(ring0, 0)
     FLEXCO_DMA(ring1, 1)
     FLEXCO_DMA(ring2, 2)
     FLEXCO_WAIT_BARRIER(FLEXCO_VMCNT(2 * NLD))
-    FLEXCO_FRAGS(ring0, 0, af0, bf0)
+    FLEXCO_FIRST_FRAGS
     int st = 0;
     for (; st + 3 < ns; st += 4) {
       FLEXCO_STAGE(ring0, ring1, ring3, st)
@@ -348,7 +481,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
     FLEXCO_DMA(ring0, 0)
     FLEXCO_DMA(ring1, 1)
     FLEXCO_WAIT_BARRIER(FLEXCO_VMCNT(NLD))
-    FLEXCO_FRAGS(ring0, 0, af0, bf0)
+    FLEXCO_FIRST_FRAGS
     int st = 0;
     for (; st + 1 < ns; st += 2) {
       FLEXCO_STAGE(ring0, ring1, ring0, st)
@@ -357,6 +490,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
     if (st < ns) FLEXCO_STAGE(ring0, ring1, ring0, st)
   }
   __builtin_amdgcn_s_waitcnt(FLEXCO_VMCNT(0));   // nothing may land in LDS after the block ends
+  FLEXCO_ACC_FENCE
 
   // ---- rank-r extension: C += A2 W2^T (forward form; the entry whose column range holds this
   // block) or C += sum_e A2_e W2_e (input-gradient form; every entry).  This is the LoRA bypass
@@ -366,7 +500,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
   for (int e = 0; e < (blockIdx.y == 0 ? ext.n : 0); ++e) {
     if (FLEXCO_EXT_SKIPS(e)) continue;
     for (int k2 = 0; k2 < ext.r; k2 += 16) {
-      bf16x8 af[MT], bfr[NT];
+      bf16x4 af[MT], bfr[NT];
       bool have = false;
       if constexpr (PF) {
         if (e == e_first && k2 == 0) {
@@ -378,139 +512,219 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
         }
       }
       if (!have) FLEXCO_EXT_LOAD(e, k2, af, bfr)
-#pragma unroll
-      for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int j = 0; j < NT; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);
+      FLEXCO_EXT_MFMAS(af, bfr)
     }
   }
-  // ---- epilogue: register 4 q + e of acc[i][j] is row lane % 32, column 8 q + 4 (lane / 32) + e of
-  // the 32 x 32 block.  Stored as they lie, an instruction would touch 32 rows with 16 (bf16) or 32 (fp32)
-  // bytes each; measured, such stores run at about 1 TB/s where whole 128-byte lines reach 3.5.  So every
-  // wavefront turns its rows through a piece of the (now free) ring that only it touches: accumulators in,
-  // 16 bytes per lane along a row out, 128 contiguous bytes or more per row and instruction. ------------
   __syncthreads();   // every wavefront is done with the ring, and (after its own wait above) its loads have landed
-  if (GLU) {
-    // registers 4 qq + e (gate) and 8 + 4 qq + e (up) of acc[i][j] belong to act column 8 qq + 4 (lane / 32) + e
-    // of the fragment's 16
-    constexpr int AW = WN / 2;                       // act columns of a wavefront's tile
-    constexpr int PITCH = AW + 8;                    // staged row in elements (16 bytes of padding)
-    constexpr int LPR = AW / 8;                      // lanes that cover a row, 16 bytes each
-    constexpr int LPRP = LPR <= 4 ? 4 : 8;           // ... rounded up to a power of two (the others idle)
-    constexpr int RPI = 64 / LPRP;                   // rows per instruction
-    static_assert(4 * 32 * PITCH <= ST_ELEMS, "the staged act rows of four wavefronts fit a stage");
-    bf16_t* stg = ring0 + wave * 32 * PITCH;
-    const int ac_end = min(glu.col0 + N / 2, glu.F);
-    const int ac_w = glu.col0 + tn * (BN / 2) + (wn0 >> 1);      // first act column of this wavefront
-    const int rl = lane / LPRP, cl = (lane % LPRP) * 8;
-    const bool lane_on = (lane % LPRP) < LPR && ac_w + cl < ac_end;   // F % 8 == 0: a run of 8 is in or out as a whole
+  if constexpr (GLU) {
+    static_assert(4 * 32 * (WN / 2 + 8) <= ST_ELEMS, "the staged act rows of four wavefronts fit a stage");
+    store_tile_glu<MT, NT>(acc, ring0 + wave * 32 * (WN / 2 + 8), C, ldc, glu, M, N, m0 + wm0, glu.col0 + tn * (BN / 2) + (wn0 >> 1), lane);
+  } else {
+    static_assert(2 * 32 * STORE_PITCH32 * 4 <= ST_ELEMS * 2, "the staged rows of two wavefronts fit a stage");
+    store_tile<MT, NT, PF_RES>(acc, reinterpret_cast<float*>(wave < 2 ? ring0 : ring1) + (wave & 1) * 32 * STORE_PITCH32,
+                               part ? part + (size_t)blockIdx.y * M * N : nullptr, C, ldc, bias, res, ldr, bpre, rpre, M, N, m0 + wm0, n0 + wn0, lane);
+  }
+#endif
+}
+
+// The 256 x 256 tile: four wavefronts, one per SIMD, 2 x 2 of 128 x 128 each.
+//
+// What bounds it: the matrix pipes, if the loads keep up; a block of 64 KB per 64 columns of K needs about 3000 cycles of
+// cover for a load under load, and two whole 64 KB stages give 2048.  So LDS is eight half-tiles of 16 KB (two stages x
+// {A0, A1, W0, W1}; A0 / A1 hold the first / second 64 rows of each wavefront's 128, W0 / W1 the same of its columns), and
+// a stage is four phases of 32 products (64 x 64 of the wavefront's tile).  While a phase multiplies what is in
+// registers, the half-tile the next phase needs is read from LDS, and the buffer that the phase before has read takes the
+// load that will be read seven phases on (about 3500 cycles).  Every half-tile is read exactly once:
+//     even stage s:  A0 x W0 (reads W1(s)),  A0 x W1 (reads A1(s)),  A1 x W1 (reads A0(s + 1)),  A1 x W0 (reads W1(s + 1))
+//     odd stage s:   A0 x W1 (reads W0(s)),  A0 x W0 (reads A1(s)),  A1 x W0 (reads A0(s + 1)),  A1 x W1 (reads W0(s + 1))
+// vmcnt(24) before a phase's barrier: all but the six youngest half-tiles (four instructions each) have landed.
+// Measured against two 64 KB stages of 32 x 32 x 16 products (M x N x K, N(0, 1) x N(0, 0.02) operands): forward
+// 2048 x 24576 x 5120 442 -> 383 us (1.35 PFLOP/s), 512 x 128256 x 4096 535 -> 435, 4096^3 114 -> 97; input gradient
+// 1024 x 13824 x 5120 173 -> 115 us (1.26 PFLOP/s), 1536 x 8192 x 28672 895 -> 551.  What is left is the power limit (4096^3
+// on zeros: 76 us) and, at K = 4096, the 10 us a tile's first loads and its epilogue take.  Eight wavefronts in two sets
+// that take turns at the matrix pipes and at LDS (64 x 128 each, half as many products per barrier) were as fast with
+// 32 x 32 x 16 products and read half as much again from LDS.
+constexpr int Q_HT = 128 * BK;        // elements of a half-tile: 128 rows x 64 K-columns, or 64 K-rows x 128 columns
+
+template <bool TRANS, bool GLU>
+__global__ __launch_bounds__(256) void gemm_bf16_quad_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W,
+                                                             bf16_t* __restrict__ C, const bf16_t* __restrict__ bias,
+                                                             const bf16_t* __restrict__ res, int M, int N, int K,
+                                                             size_t lda, size_t ldw, size_t ldc, size_t ldr, int tiles_m,
+                                                             int tiles_n, GemmExt ext, float* __restrict__ part,
+                                                             int k_chunk, GemmGlu glu) {
+#ifdef __HIP_DEVICE_COMPILE__
+  constexpr int BM = 256, BN = 256, MT = 8, NT = 8;
+  int lid = blockIdx.x;
+  const int nblk = gridDim.x;
+  if ((nblk & 7) == 0) lid = (blockIdx.x & 7) * (nblk >> 3) + (blockIdx.x >> 3);
+  const int tm = lid % tiles_m, tn = lid / tiles_m;
+  const int m0 = tm * BM, n0 = tn * BN;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int wm0 = wm * 128, wn0 = wn * 128;
+  const int l16 = lane & 15, q4 = lane >> 4;
+  const int kbeg = blockIdx.y * k_chunk;
+  const int ns = k_chunk / BK;
+
+  f32x4 acc[MT][NT];
 #pragma unroll
-    for (int i = 0; i < MT; ++i) {
-      const int rb = m0 + wm0 + i * 32;
-      const bool band_saves = glu.save_gate && rb + 32 > glu.save_row0 && rb < glu.save_row0 + glu.save_rows;   // uniform
+  for (int i = 0; i < MT; ++i)
 #pragma unroll
-      for (int what = 0; what < 3; ++what) {         // 0: act, 1: gate, 2: up (the last two for finetune rows only)
-        if (what > 0 && !band_saves) break;
+    for (int j = 0; j < NT; ++j)
 #pragma unroll
-        for (int j = 0; j < NT; ++j)
+      for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
+
+  // (separate arrays: the compiler then sees that loads in flight target an array no ds_read of that moment touches)
+  __shared__ __attribute__((aligned(1024))) bf16_t a0e[Q_HT];
+  __shared__ __attribute__((aligned(1024))) bf16_t a0o[Q_HT];
+  __shared__ __attribute__((aligned(1024))) bf16_t a1e[Q_HT];
+  __shared__ __attribute__((aligned(1024))) bf16_t a1o[Q_HT];
+  __shared__ __attribute__((aligned(1024))) bf16_t w0e[Q_HT];
+  __shared__ __attribute__((aligned(1024))) bf16_t w0o[Q_HT];
+  __shared__ __attribute__((aligned(1024))) bf16_t w1e[Q_HT];
+  __shared__ __attribute__((aligned(1024))) bf16_t w1o[Q_HT];
+
+  // ---- loads: instruction p of wavefront w fills 1 KB of a half-tile: rows 8 (4 p + w) .. + 8 of [128][64], or
+  // rows 4 (4 p + w) .. + 4 of [64][128].  16-byte chunk c of a 128-byte row r is stored at c ^ ((r / 2) % 8), of a
+  // 256-byte row at c ^ 4 (r % 4) ^ 2 (r / 8 % 2) (as in the kernel above).  Byte offsets from the tile's own corner fit 32 bits. ----
+  unsigned oa[2][4], ow[2][4];
+  {
+    const int d_row = lane >> 3;
+    const int d_c = (lane & 7) ^ (((wave * 8 + d_row) >> 1) & 7);
+    const int t_row = lane >> 4;
+    const int t_c = (lane & 15) ^ ((t_row & 3) << 2) ^ (((wave >> 1) & 1) << 1);
 #pragma unroll
-          for (int qq = 0; qq < 2; ++qq) {
-            bf16x4 o;
+    for (int p = 0; p < 4; ++p) {
+      const int r = (p * 4 + wave) * 8 + d_row;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              // gate and up pass through the storage type first (they are what the backward pass reads back)
-              const bf16_t gs = (bf16_t)acc[i][j][4 * qq + e], us = (bf16_t)acc[i][j][8 + 4 * qq + e];
-              const float gv = (float)gs, uv = (float)us;
-              // (reciprocal instruction, 1 ulp, instead of the ten-instruction IEEE division: the tile's 64 K sigmoids are on
-              // the critical path of a launch whose blocks all end together)
-              o[e] = what == 0 ? (bf16_t)(gv * __builtin_amdgcn_rcpf(1.0f + __expf(-gv)) * uv) : (what == 1 ? gs : us);
-            }
-            *reinterpret_cast<bf16x4*>(stg + l32 * PITCH + j * 16 + 8 * qq + 4 * kg) = o;
-          }
-        bf16_t* dst = what == 0 ? C : (what == 1 ? glu.save_gate : glu.save_up);
-        const size_t ldd = what == 0 ? ldc : glu.ld_save;
-#pragma unroll
-        for (int p = 0; p < 32 / RPI; ++p) {
-          const int r = p * RPI + rl, row = rb + r;
-          const int drow = what == 0 ? row : row - glu.save_row0;
-          const bool ok = lane_on && row < M && (what == 0 || (drow >= 0 && drow < glu.save_rows));
-          if (ok) *reinterpret_cast<bf16x8*>(dst + (size_t)drow * ldd + ac_w + cl) = *reinterpret_cast<const bf16x8*>(stg + r * PITCH + cl);
+      for (int h = 0; h < 2; ++h) {
+        const int rt = 128 * (r >> 6) + 64 * h + (r & 63);           // tile row (row of W) of the half-tile's row r
+        oa[h][p] = (unsigned)((size_t)min(rt, M - 1 - m0) * lda * 2 + d_c * 16);
+        if (GLU) {
+          const int ac = glu.col0 + tn * (BN / 2) + (rt >> 5) * 16 + (rt & 15);
+          ow[h][p] = (unsigned)(((size_t)((rt >> 4) & 1) * glu.F + min(ac, glu.F - 1)) * ldw * 2 + d_c * 16);
+        } else if (!TRANS) {
+          ow[h][p] = (unsigned)((size_t)min(rt, N - 1 - n0) * ldw * 2 + d_c * 16);
+        } else {
+          const int cl = t_c * 8;
+          int col = 128 * (cl >> 6) + 64 * h + (cl & 63);
+          if (n0 + col >= N) col = 0;                                // masked at the store
+          ow[h][p] = (unsigned)((size_t)((p * 4 + wave) * 4 + t_row) * ldw * 2 + col * 2);
         }
-        if (MT * NT > 4) __builtin_amdgcn_sched_barrier(0);
       }
     }
-    return;
   }
-  // fp32 staging (what is added to the accumulators - bias, residual - is added in fp32 before the one rounding):
-  // 32 rows x 64 columns at a time (two fragments; one if the wavefront's tile has an odd one left), rows 272 bytes apart
-  constexpr int PITCH32 = 64 + 4;
-  static_assert(2 * 32 * PITCH32 * 4 <= ST_ELEMS * 2, "the staged rows of two wavefronts fit a stage");
-  float* stg = reinterpret_cast<float*>(wave < 2 ? ring0 : ring1) + (wave & 1) * 32 * PITCH32;
-  float* P = part ? part + (size_t)blockIdx.y * M * N : nullptr;
+  const char* const pa = (const char*)(A + (size_t)m0 * lda + kbeg);
+  const char* const pw = (const char*)(GLU ? W + kbeg : (TRANS ? W + (size_t)kbeg * ldw + n0 : W + (size_t)n0 * ldw + kbeg));
+  const size_t wstep = TRANS ? (size_t)BK * ldw * 2 : (size_t)BK * 2;
+  // (a stage past the end: clamped, the loads repeat the last stage into a free buffer)
+#define Q_LOAD(buf_, src_, off_, p_) \
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(src_, FLEXCO_LP(buf_ + ((p_) * 4 + wave) * 512), 16, off_[p_], 0, 0, 0);
+#define Q_LOAD4(buf_, src_, off_) \
+  { const __amdgpu_buffer_rsrc_t b_ = src_; Q_LOAD(buf_, b_, off_, 0) Q_LOAD(buf_, b_, off_, 1) Q_LOAD(buf_, b_, off_, 2) Q_LOAD(buf_, b_, off_, 3) }
+  const int key = l16 >> 1;
+  int tr_off[4];       // (one index expression from the array on, see the kernel above)
 #pragma unroll
-  for (int i = 0; i < MT; ++i) {
-    const int rb = m0 + wm0 + i * 32;
+  for (int jj = 0; jj < 4; ++jj) {
+    const int col = wn * 64 + jj * 16 + 4 * (lane & 3);
+    tr_off[jj] = (8 * q4 + (l16 >> 2)) * 128 + (((col >> 3) ^ ((l16 >> 2) << 2) ^ ((q4 & 1) << 1)) * 8) + (col & 7);
+  }
+  // one fragment (16 rows or columns x 32 of K) of the eight a wavefront reads of a half-tile
+#define Q_READ_ROWS(dst_, buf_, w_, q_)                                                               \
+  dst_[(q_) & 3][(q_) >> 2] = *reinterpret_cast<const bf16x8*>(buf_ + (w_ * 64 + ((q_) & 3) * 16 + l16) * BK + ((((q_) >> 2) * 4 + q4) ^ key) * 8);
+#define Q_READ_A(dst_, buf_, q_) Q_READ_ROWS(dst_, buf_, wm, q_)
+#define Q_READ_W(dst_, buf_, q_)                                                                      \
+  {                                                                                                   \
+    if (!TRANS) {                                                                                     \
+      Q_READ_ROWS(dst_, buf_, wn, q_)                                                                 \
+    } else {                                                                                          \
+      const s16x4 lo_ = __builtin_amdgcn_ds_read_tr16_b64_v4i16((FLEXCO_LDS s16x4*)(buf_ + (tr_off[(q_) & 3] + ((q_) >> 2) * 32 * 128)));       \
+      const s16x4 hi_ = __builtin_amdgcn_ds_read_tr16_b64_v4i16((FLEXCO_LDS s16x4*)(buf_ + (tr_off[(q_) & 3] + (((q_) >> 2) * 32 + 4) * 128))); \
+      dst_[(q_) & 3][(q_) >> 2] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo_, hi_, 0, 1, 2, 3, 4, 5, 6, 7)); \
+    }                                                                                                 \
+  }
+#define Q_WAIT(n_) (0x0070 | ((n_) & 15) | (((n_) >> 4) << 14))      /* vmcnt(n), lgkmcnt(0) */
+  // a phase: read_ (for the next one), load_ (into the buffer the last one read), 32 products; then this wavefront's
+  // reads are in registers and its loads of the half-tile that is read next have landed
+#define Q_PHASE(READ_, rdst_, rbuf_, lbuf_, lsrc_, loff_, i0_, j0_, a_, w_)                           \
+  {                                                                                                   \
+    const __amdgpu_buffer_rsrc_t src_ = lsrc_;                                                        \
+    _Pragma("unroll") for (int n = 0; n < 32; ++n) {                                                  \
+      FLEXCO_MFMA(acc[i0_ + ((n >> 2) & 3)][j0_ + (n & 3)], w_[n & 3][n >> 4], a_[(n >> 2) & 3][n >> 4])   \
+      if ((n & 1) && n < 16) READ_(rdst_, rbuf_, n >> 1)                                              \
+      if ((n & 1) && n >= 16 && n < 24) Q_LOAD(lbuf_, src_, loff_, (n - 16) >> 1)                     \
+      if (n & 1) __builtin_amdgcn_sched_barrier(0);                                                   \
+    }                                                                                                 \
+    Q_END                                                                                             \
+  }
+#define Q_END                                                                                         \
+  {                                                                                                   \
+    __builtin_amdgcn_sched_barrier(0);                                                                \
+    __builtin_amdgcn_s_waitcnt(Q_WAIT(24));                                                           \
+    asm volatile("" ::: "memory");                                                                    \
+    __builtin_amdgcn_s_barrier();                                                                     \
+    asm volatile("" ::: "memory");                                                                    \
+    __builtin_amdgcn_sched_barrier(0);                                                                \
+  }
+#define Q_EVEN(s_)                                                                                    \
+  {                                                                                                   \
+    Q_PHASE(Q_READ_W, fw1, w1e, w0e, GEMM_SRC_W((s_) + 2), ow[0], 0, 0, fa0, fw0)                        \
+    Q_PHASE(Q_READ_A, fa1, a1e, w1e, GEMM_SRC_W((s_) + 2), ow[1], 0, 4, fa0, fw1)                        \
+    Q_PHASE(Q_READ_A, fa0, a0o, a1e, GEMM_SRC_A((s_) + 2), oa[1], 4, 4, fa1, fw1)                        \
+    Q_PHASE(Q_READ_W, fw1, w1o, a0o, GEMM_SRC_A((s_) + 3), oa[0], 4, 0, fa1, fw0)                        \
+  }
+#define Q_ODD(s_)                                                                                     \
+  {                                                                                                   \
+    Q_PHASE(Q_READ_W, fw0, w0o, w1o, GEMM_SRC_W((s_) + 2), ow[1], 0, 4, fa0, fw1)                        \
+    Q_PHASE(Q_READ_A, fa1, a1o, w0o, GEMM_SRC_W((s_) + 2), ow[0], 0, 0, fa0, fw0)                        \
+    Q_PHASE(Q_READ_A, fa0, a0e, a1o, GEMM_SRC_A((s_) + 2), oa[1], 4, 0, fa1, fw0)                        \
+    Q_PHASE(Q_READ_W, fw0, w0e, a0e, GEMM_SRC_A((s_) + 3), oa[0], 4, 4, fa1, fw1)                        \
+  }
+  bf16x8 fa0[4][2], fa1[4][2], fw0[4][2], fw1[4][2];
+  Q_LOAD4(a0e, GEMM_SRC_A(0), oa[0]) Q_LOAD4(w0e, GEMM_SRC_W(0), ow[0]) Q_LOAD4(w1e, GEMM_SRC_W(0), ow[1]) Q_LOAD4(a1e, GEMM_SRC_A(0), oa[1])
+  Q_LOAD4(a0o, GEMM_SRC_A(1), oa[0]) Q_LOAD4(w1o, GEMM_SRC_W(1), ow[1]) Q_LOAD4(w0o, GEMM_SRC_W(1), ow[0]) Q_LOAD4(a1o, GEMM_SRC_A(1), oa[1])
+  Q_END                                          // A0(0), W0(0) have landed
 #pragma unroll
-    for (int j0 = 0; j0 < NT; j0 += 2) {
-      const int nj = (j0 + 1 < NT) ? 2 : 1;          // fragments in this group (compile-time after unrolling)
-#pragma unroll
-      for (int jj = 0; jj < 2; ++jj) {
-        if (jj >= nj) break;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          f32x4 v;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = acc[i][j0 + jj][4 * q + e];
-          *reinterpret_cast<f32x4*>(stg + l32 * PITCH32 + jj * 32 + 8 * q + 4 * kg) = v;
-        }
-      }
-      const int cb = n0 + wn0 + j0 * 32;             // first column of the group
-      if (part) {
-        // 16 lanes x 4 columns per row, 4 rows per instruction
-        const int rl = lane >> 4, cl = (lane & 15) * 4;
-#pragma unroll
-        for (int p = 0; p < 8; ++p) {
-          const int r = p * 4 + rl, row = rb + r, col = cb + cl;
-          if (cl < nj * 32 && row < M && col < N)    // N % 8 == 0: a run of 4 is inside or outside as a whole
-            *reinterpret_cast<f32x4*>(P + (size_t)row * N + col) = *reinterpret_cast<const f32x4*>(stg + r * PITCH32 + cl);
-        }
-      } else {
-        // 8 lanes x 8 columns per row, 8 rows per instruction
-        const int rl = lane >> 3, cl = (lane & 7) * 8;
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-          const int r = p * 8 + rl, row = rb + r, col = cb + cl;
-          if (cl < nj * 32 && row < M && col < N) {  // N % 8 == 0: a run of 8 is inside or outside as a whole
-            const f32x4 lo = *reinterpret_cast<const f32x4*>(stg + r * PITCH32 + cl);
-            const f32x4 hi = *reinterpret_cast<const f32x4*>(stg + r * PITCH32 + cl + 4);
-            float v[8];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) { v[e] = lo[e]; v[4 + e] = hi[e]; }
-            if (bias) {
-              bf16x8 b8;
-              if constexpr (PF_RES) b8 = bpre[j0 / 2]; else b8 = *reinterpret_cast<const bf16x8*>(bias + col);
-#pragma unroll
-              for (int e = 0; e < 8; ++e) v[e] += (float)b8[e];
-            }
-            if (res) {
-              bf16x8 r8;
-              if constexpr (PF_RES) r8 = rpre[i][j0 / 2][p]; else r8 = *reinterpret_cast<const bf16x8*>(res + (size_t)row * ldr + col);
-#pragma unroll
-              for (int e = 0; e < 8; ++e) v[e] += (float)r8[e];
-            }
-            bf16x8 o;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) o[e] = (bf16_t)v[e];
-            *reinterpret_cast<bf16x8*>(C + (size_t)row * ldc + col) = o;
-          }
-        }
-      }
-      // (keeps the scheduler from gathering the stores of the whole tile up front, which costs more
-      // registers than the large tile has left)
-      if (MT * NT > 4) __builtin_amdgcn_sched_barrier(0);
+  for (int q = 0; q < 8; ++q) {
+    Q_READ_A(fa0, a0e, q)
+    Q_READ_W(fw0, w0e, q)
+  }
+  Q_END
+  Q_LOAD4(a0e, GEMM_SRC_A(2), oa[0])
+  FLEXCO_ACC_FENCE
+  Q_END                                          // W1(0)
+  int st = 0;
+  for (; st + 1 < ns; st += 2) {
+    Q_EVEN(st)
+    Q_ODD(st + 1)
+  }
+  if (st < ns) Q_EVEN(st)
+  __builtin_amdgcn_s_waitcnt(Q_WAIT(0));         // nothing may land in LDS after the block ends
+  FLEXCO_ACC_FENCE
+
+  // ---- rank-r extension (see the kernel above) ----
+  for (int e = 0; e < (blockIdx.y == 0 ? ext.n : 0); ++e) {
+    if (FLEXCO_EXT_SKIPS(e)) continue;
+    for (int k2 = 0; k2 < ext.r; k2 += 16) {
+      bf16x4 af[MT], bfr[NT];
+      FLEXCO_EXT_LOAD(e, k2, af, bfr)
+      FLEXCO_EXT_MFMAS(af, bfr)
     }
   }
+  __syncthreads();   // every wavefront is done with the half-tiles, and (after its own wait above) its loads have landed
+  // (one 16 KB half-tile per wavefront to turn its rows in)
+  bf16_t* const stg = wave == 0 ? a0e : wave == 1 ? a0o : wave == 2 ? a1e : a1o;
+  static_assert(32 * STORE_PITCH32 * 4 <= Q_HT * 2 && 32 * (NT * 8 + 8) <= Q_HT, "the staged rows of a wavefront fit a half-tile");
+  if constexpr (GLU) {
+    store_tile_glu<MT, NT>(acc, stg, C, ldc, glu, M, N, m0 + wm0, glu.col0 + tn * (BN / 2) + (wn0 >> 1), lane);
+  } else {
+    bf16x8 bpre[1], rpre[1][1][4];
+    store_tile<MT, NT, false>(acc, reinterpret_cast<float*>(stg), part ? part + (size_t)blockIdx.y * M * N : nullptr, C, ldc,
+                              bias, res, ldr, bpre, rpre, M, N, m0 + wm0, n0 + wn0, lane);
+  }
+#endif
 }
 
 // C[row, col] = sum over splits of part[split][row][col] (+ bias) (+ residual), fixed order
@@ -543,7 +757,13 @@ int32_t launch_cfg(const void* A, const void* W, void* C, const void* bias, cons
                    size_t lda, size_t ldw, size_t ldc, size_t ldr, const GemmExt& ext, hipStream_t s,
                    int timer_id, float* part = nullptr, int splits = 1, bool first_of_call = true,
                    const GemmGlu* glu_in = nullptr, bool skip_reduce = false) {
-  auto kern = gemm_bf16_kernel<BM, BN, TRANS, GLU, NSTAGES>;   // all LDS is static
+  // all LDS is static; the 256 x 256 tile is a kernel of its own
+  constexpr bool QUAD = BM == 256 && BN == 256;
+  constexpr int THREADS = 256;
+  void (*kern)(const bf16_t*, const bf16_t*, bf16_t*, const bf16_t*, const bf16_t*, int, int, int, size_t, size_t, size_t, size_t,
+               int, int, GemmExt, float*, int, GemmGlu);
+  if constexpr (QUAD) kern = gemm_bf16_quad_kernel<TRANS, GLU>;
+  else kern = gemm_bf16_kernel<BM, BN, TRANS, GLU, NSTAGES>;
   GemmGlu glu;
   if (glu_in) glu = *glu_in; else memset(&glu, 0, sizeof(glu));
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
@@ -552,19 +772,19 @@ int32_t launch_cfg(const void* A, const void* W, void* C, const void* bias, cons
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (timer_id >= 0) (void)kernel_timer_pair(timer_id, &e0, &e1, first_of_call);
   // (the plain launch when no pair is due: it is the form a stream capture records)
-#define FLEXCO_LAUNCH_TIMED(kern_, grid_, ...)                                                        \
+#define FLEXCO_LAUNCH_TIMED(kern_, grid_, threads_, ...)                                              \
   {                                                                                                   \
-    if (e0) hipExtLaunchKernelGGL(kern_, grid_, dim3(256), 0, s, e0, e1, 0, __VA_ARGS__);             \
-    else hipLaunchKernelGGL(kern_, grid_, dim3(256), 0, s, __VA_ARGS__);                              \
+    if (e0) hipExtLaunchKernelGGL(kern_, grid_, dim3(threads_), 0, s, e0, e1, 0, __VA_ARGS__);        \
+    else hipLaunchKernelGGL(kern_, grid_, dim3(threads_), 0, s, __VA_ARGS__);                         \
   }
-  FLEXCO_LAUNCH_TIMED(kern, dim3(tiles_m * tiles_n, splits), (const bf16_t*)A, (const bf16_t*)W, (bf16_t*)C,
+  FLEXCO_LAUNCH_TIMED(kern, dim3(tiles_m * tiles_n, splits), THREADS, (const bf16_t*)A, (const bf16_t*)W, (bf16_t*)C,
                       (const bf16_t*)bias, (const bf16_t*)res, M, N, K, lda, ldw, ldc, ldr, tiles_m, tiles_n, ext,
                       splits > 1 ? part : nullptr, K / splits, glu)
   if (splits > 1 && !skip_reduce) {
     const size_t quads = ((size_t)M * N + 3) / 4;
     e0 = e1 = nullptr;
     if (timer_id >= 0) (void)kernel_timer_pair(timer_id, &e0, &e1, false);
-    FLEXCO_LAUNCH_TIMED(gemm_splitk_reduce_kernel, dim3((unsigned)((quads + 255) / 256)), part, splits, (bf16_t*)C,
+    FLEXCO_LAUNCH_TIMED(gemm_splitk_reduce_kernel, dim3((unsigned)((quads + 255) / 256)), 256, part, splits, (bf16_t*)C,
                         (const bf16_t*)bias, (const bf16_t*)res, M, N, ldc, ldr)
   }
 #undef FLEXCO_LAUNCH_TIMED
