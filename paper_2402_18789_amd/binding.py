@@ -141,6 +141,7 @@ def _load():
         "flexco_attention_window_bwd": [P(LayerCfg), P(KVPool), vp, i32, i32, i32, vp, vp, vp, vp, vp, vp, vp, vp, sz, vp],
         "flexco_gemm": [vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, vp],
         "flexco_gemm_plan": [i32, i32, i32, i32, C.c_int64, P(i32)],
+        "flexco_gemm_k_ranges": [i32, i32, i32, i32, C.c_int64, P(i32)],
         "flexco_prune_graph": [P(Graph), vp],
         "flexco_kernel_timer_start": [i32, i32],
         "flexco_kernel_timer_stop": [i32, P(C.c_double), P(C.c_int64)],
@@ -177,7 +178,7 @@ def _load():
 _lib = _load()
 EXPORTS = ("flexco_last_error", "flexco_abi_version", "flexco_maps_blob_ints", "flexco_build_maps",
            "flexco_maps_rebase", "flexco_workspace_bytes", "flexco_layer_forward", "flexco_layer_forward_multi", "flexco_attention_mixed",
-           "flexco_lora_fwd", "flexco_lora_fwd_static", "flexco_lora_bwd", "flexco_attention_window_bwd", "flexco_gemm", "flexco_gemm_plan",
+           "flexco_lora_fwd", "flexco_lora_fwd_static", "flexco_lora_bwd", "flexco_attention_window_bwd", "flexco_gemm", "flexco_gemm_plan", "flexco_gemm_k_ranges",
            "flexco_kernel_timer_start", "flexco_kernel_timer_stop", "flexco_kernel_timer_sample", "flexco_kernel_timer_read", "flexco_probe_mfma", "flexco_probe_mfma_lds", "flexco_probe_read",
            "flexco_latency_estimate", "flexco_sched_window", "flexco_sched_inference", "flexco_sched_advance",
            "flexco_lm_loss_workspace_bytes", "flexco_lm_loss", "flexco_adam_step", "flexco_prune_graph",
@@ -375,6 +376,13 @@ def flexco_gemm_plan(M, N, K, trans_w, part_elems=0):
     out = (C.c_int32 * 11)()
     _check(_lib.flexco_gemm_plan(M, N, K, int(trans_w), int(part_elems), out))
     return [tuple(out[1 + 5 * i:6 + 5 * i]) for i in range(out[0])]
+
+
+def flexco_gemm_k_ranges(M, N, K, trans_w, part_elems=0):
+    """-> ranges of K the product runs in on 256 x 256 tiles, 0: it follows flexco_gemm_plan"""
+    out = C.c_int32()
+    _check(_lib.flexco_gemm_k_ranges(M, N, K, int(trans_w), int(part_elems), C.byref(out)))
+    return out.value
 
 
 def flexco_probe_mfma(blocks, iters, sink, stream=None):

@@ -197,6 +197,8 @@ extern "C" int32_t flexco_bf16_fallbacks(int64_t* counts, int32_t reset) {
 namespace {
 
 constexpr size_t SPLITK_COLS = 32768;   // split-K scratch of the backward GEMMs: rows x this many floats
+// windows of up to 256 rows twice that (one row of 256 x 256 tiles: K in up to sixteen ranges to fill the chip)
+inline size_t bwd_splitk_cols(int n) { return n <= 256 ? 2 * SPLITK_COLS : SPLITK_COLS; }
 constexpr int FWD_SPLITK_MAX_T = 256;   // forward batches up to this many tokens get split-K scratch too
 constexpr int ROW_T_MAX_ROWS = 512;     // windows up to this many rows take t = dy B inside the row kernels
 
@@ -308,7 +310,7 @@ BwdWs carve_bwd(const flexco_layer_cfg& c, int n, void* base) {
   const int r = c.lora_rank > 0 ? c.lora_rank : 1;
   w.u = (float*)cv.take(sizeof(float) * n * r);
   w.t = (float*)cv.take(sizeof(float) * n * r);
-  w.gemm_part_elems = c.dtype == FLEXCO_BF16 ? (size_t)n * SPLITK_COLS : 0;
+  w.gemm_part_elems = c.dtype == FLEXCO_BF16 ? (size_t)n * bwd_splitk_cols(n) : 0;
   w.gemm_part = (float*)cv.take(sizeof(float) * w.gemm_part_elems);
   w.colsum_part = (float*)cv.take(sizeof(float) * (size_t)((n + 7) / 8) *
                                   std::max<size_t>(c.ffn, (size_t)c.n_kv_heads * c.head_dim));
@@ -765,7 +767,7 @@ extern "C" int32_t flexco_workspace_bytes(const flexco_layer_cfg* cfg, int32_t T
   // (a batch of at most FWD_SPLITK_MAX_T tokens also asks for split-K scratch: cover the largest such batch)
   const size_t f = std::max(carve_fwd(*cfg, T_max, n_parts_max, nullptr).bytes,
                             carve_fwd(*cfg, std::min(T_max, FWD_SPLITK_MAX_T), n_parts_max, nullptr).bytes);
-  const size_t b = carve_bwd(*cfg, win_max, nullptr).bytes;
+  const size_t b = std::max(carve_bwd(*cfg, win_max, nullptr).bytes, carve_bwd(*cfg, std::min(win_max, 256), nullptr).bytes);
   *out_bytes = f > b ? f : b;
   return FLEXCO_OK;
 }
@@ -782,11 +784,23 @@ extern "C" int32_t flexco_gemm(const void* A, const void* W, void* C, const void
                      (hipStream_t)stream);
 }
 
-extern "C" int32_t flexco_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t trans_w, int64_t part_elems, int32_t* out) {
-  clear_error();
+static int32_t check_plan_args(int32_t M, int32_t N, int32_t K, int64_t part_elems, const int32_t* out) {
   FLEXCO_CHECK(out != nullptr, FLEXCO_EINVAL, "out is NULL");
   FLEXCO_CHECK(M > 0 && N > 0 && K > 0 && part_elems >= 0, FLEXCO_EINVAL, "M, N, K must be positive, part_elems not negative");
   FLEXCO_CHECK(K % 64 == 0 && N % 8 == 0, FLEXCO_ESHAPE, "the matrix-core path takes K in multiples of 64 and N in multiples of 8");
+  return FLEXCO_OK;
+}
+
+extern "C" int32_t flexco_gemm_k_ranges(int32_t M, int32_t N, int32_t K, int32_t trans_w, int64_t part_elems, int32_t* out) {
+  clear_error();
+  FLEXCO_TRY(check_plan_args(M, N, K, part_elems, out));
+  *out = plan_gemm_k_ranges(M, N, K, trans_w != 0, (size_t)part_elems);
+  return FLEXCO_OK;
+}
+
+extern "C" int32_t flexco_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t trans_w, int64_t part_elems, int32_t* out) {
+  clear_error();
+  FLEXCO_TRY(check_plan_args(M, N, K, part_elems, out));
   const GemmLaunchPlan pl = plan_gemm_mfma(M, N, K, trans_w != 0, (size_t)part_elems);
   for (int i = 0; i < 11; ++i) out[i] = 0;
   out[0] = pl.n;
@@ -955,8 +969,17 @@ static int32_t layer_forward_impl(const flexco_layer_cfg* cfg, const flexco_base
   const int T = m.T, H = c.hidden, F = c.ffn, dt = c.dtype;
   const size_t e = esize(dt);
   const int qd = c.n_q_heads * c.head_dim, kd = c.n_kv_heads * c.head_dim, qkvd = qd + 2 * kd;
+  // Batches of more tokens have no split-K scratch of their own: the [T, 2F] buffer serves while it holds nothing, i.e.
+  // before the gate/up projection, and after it where the gated form left gate and up to the epilogue.
+  const bool gu_part = dt == FLEXCO_BF16 && T > FWD_SPLITK_MAX_T;
+  auto lend_gu = [&](bool free) {
+    if (!gu_part) return;
+    k.gemm_part = free ? (float*)k.gu : nullptr;
+    k.gemm_part_elems = free ? (size_t)T * F : 0;
+  };
 
   // attention side
+  lend_gu(true);
   // (the finetune window's rows of x, x2, the attention output and its log-sum-exp - what graph pruning keeps,
   // Alg. 1 - are written to the sequence's state by the kernels that read or produce them anyway)
   const size_t p0 = m.ft_pos0;
@@ -988,10 +1011,12 @@ static int32_t layer_forward_impl(const flexco_layer_cfg* cfg, const flexco_base
   EW(launch_rmsnorm(k.x2, w->g2, k.h, T, H, c.rms_eps, dt, s, ft ? (void*)boff(ft->saved_x2, p0 * H, e) : nullptr, m.ft_tok0,
                     m.n_ft));
   GluOut glu{k.act, (size_t)F, false};
+  lend_gu(false);
   {
     const int tg[2] = {FLEXCO_T_GATE, FLEXCO_T_UP}, c0[2] = {0, F};
     FLEXCO_TRY(forward_projection(c, ad, m, k.h, H, w->wgu, nullptr, nullptr, 0, k.gu, 2 * F, tg, c0, 2, k, ft, s, &glu));
   }
+  lend_gu(glu.done);
   if (!glu.done) EW(launch_swiglu(k.gu, k.act, T, F, dt, s));
   if (ia3 && m.n_lora > 0) {   // the SwiGLU product of the adapter's rows
     Ia3ScaleArgs sa;

@@ -527,7 +527,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
 #endif
 }
 
-// The 256 x 256 tile: four wavefronts, one per SIMD, 2 x 2 of 128 x 128 each.
+// The 256-row tiles (256 x 256, and 256 x 192 in the forward form): four wavefronts, one per SIMD, 2 x 2 of 128 x 128 (96) each.
+// (Written below for 256 columns; at 192 a W half-tile has 96 columns and a phase 64 x 48 of the wavefront's tile.)
 //
 // What bounds it: the matrix pipes, if the loads keep up; a block of 64 KB per 64 columns of K needs about 3000 cycles of
 // cover for a load under load, and two whole 64 KB stages give 2048.  So LDS is eight half-tiles of 16 KB (two stages x
@@ -537,7 +538,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
 // load that will be read seven phases on (about 3500 cycles).  Every half-tile is read exactly once:
 //     even stage s:  A0 x W0 (reads W1(s)),  A0 x W1 (reads A1(s)),  A1 x W1 (reads A0(s + 1)),  A1 x W0 (reads W1(s + 1))
 //     odd stage s:   A0 x W1 (reads W0(s)),  A0 x W0 (reads A1(s)),  A1 x W0 (reads A0(s + 1)),  A1 x W1 (reads W0(s + 1))
-// vmcnt(24) before a phase's barrier: all but the six youngest half-tiles (four instructions each) have landed.
+// The vmcnt before a phase's barrier: all but the six youngest half-tiles (NA = 4 or NW = 4 (3) instructions each) have landed.
+// K is cut over gridDim.y blocks in whole stages, in ranges that differ by a stage at most.
 // Measured against two 64 KB stages of 32 x 32 x 16 products (M x N x K, N(0, 1) x N(0, 0.02) operands): forward
 // 2048 x 24576 x 5120 442 -> 383 us (1.35 PFLOP/s), 512 x 128256 x 4096 535 -> 435, 4096^3 114 -> 97; input gradient
 // 1024 x 13824 x 5120 173 -> 115 us (1.26 PFLOP/s), 1536 x 8192 x 28672 895 -> 551.  What is left is the power limit (4096^3
@@ -546,15 +548,17 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
 // 32 x 32 x 16 products and read half as much again from LDS.
 constexpr int Q_HT = 128 * BK;        // elements of a half-tile: 128 rows x 64 K-columns, or 64 K-rows x 128 columns
 
-template <bool TRANS, bool GLU>
+template <int BN, bool TRANS, bool GLU>
 __global__ __launch_bounds__(256) void gemm_bf16_quad_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W,
                                                              bf16_t* __restrict__ C, const bf16_t* __restrict__ bias,
                                                              const bf16_t* __restrict__ res, int M, int N, int K,
                                                              size_t lda, size_t ldw, size_t ldc, size_t ldr, int tiles_m,
                                                              int tiles_n, GemmExt ext, float* __restrict__ part,
-                                                             int k_chunk, GemmGlu glu) {
+                                                             int /*k_chunk*/, GemmGlu glu) {
 #ifdef __HIP_DEVICE_COMPILE__
-  constexpr int BM = 256, BN = 256, MT = 8, NT = 8;
+  constexpr int BM = 256, MT = 8, NT = BN / 32, HN = NT / 2;      // HN: 16-column fragments of a phase
+  constexpr int NA = 4, NW = BN / 64;                             // load instructions of a half-tile
+  static_assert(BN == 256 || (BN == 192 && !TRANS), "the input-gradient form's W tile swizzle assumes 256-byte rows");
   int lid = blockIdx.x;
   const int nblk = gridDim.x;
   if ((nblk & 7) == 0) lid = (blockIdx.x & 7) * (nblk >> 3) + (blockIdx.x >> 3);
@@ -563,10 +567,12 @@ __global__ __launch_bounds__(256) void gemm_bf16_quad_kernel(const bf16_t* __res
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
-  const int wm0 = wm * 128, wn0 = wn * 128;
+  const int wm0 = wm * 128, wn0 = wn * (BN / 2);
   const int l16 = lane & 15, q4 = lane >> 4;
-  const int kbeg = blockIdx.y * k_chunk;
-  const int ns = k_chunk / BK;
+  const int st_all = K / BK;
+  const int st_beg = (int)((long)st_all * blockIdx.y / gridDim.y);
+  const int ns = (int)((long)st_all * (blockIdx.y + 1) / gridDim.y) - st_beg;      // stages of this block (at least one)
+  const int kbeg = st_beg * BK;
 
   f32x4 acc[MT][NT];
 #pragma unroll
@@ -581,15 +587,15 @@ __global__ __launch_bounds__(256) void gemm_bf16_quad_kernel(const bf16_t* __res
   __shared__ __attribute__((aligned(1024))) bf16_t a0o[Q_HT];
   __shared__ __attribute__((aligned(1024))) bf16_t a1e[Q_HT];
   __shared__ __attribute__((aligned(1024))) bf16_t a1o[Q_HT];
-  __shared__ __attribute__((aligned(1024))) bf16_t w0e[Q_HT];
-  __shared__ __attribute__((aligned(1024))) bf16_t w0o[Q_HT];
-  __shared__ __attribute__((aligned(1024))) bf16_t w1e[Q_HT];
-  __shared__ __attribute__((aligned(1024))) bf16_t w1o[Q_HT];
+  __shared__ __attribute__((aligned(1024))) bf16_t w0e[HN * 32 * BK];
+  __shared__ __attribute__((aligned(1024))) bf16_t w0o[HN * 32 * BK];
+  __shared__ __attribute__((aligned(1024))) bf16_t w1e[HN * 32 * BK];
+  __shared__ __attribute__((aligned(1024))) bf16_t w1o[HN * 32 * BK];
 
   // ---- loads: instruction p of wavefront w fills 1 KB of a half-tile: rows 8 (4 p + w) .. + 8 of [128][64], or
   // rows 4 (4 p + w) .. + 4 of [64][128].  16-byte chunk c of a 128-byte row r is stored at c ^ ((r / 2) % 8), of a
   // 256-byte row at c ^ 4 (r % 4) ^ 2 (r / 8 % 2) (as in the kernel above).  Byte offsets from the tile's own corner fit 32 bits. ----
-  unsigned oa[2][4], ow[2][4];
+  unsigned oa[2][NA], ow[2][NW];
   {
     const int d_row = lane >> 3;
     const int d_c = (lane & 7) ^ (((wave * 8 + d_row) >> 1) & 7);
@@ -600,8 +606,10 @@ __global__ __launch_bounds__(256) void gemm_bf16_quad_kernel(const bf16_t* __res
       const int r = (p * 4 + wave) * 8 + d_row;
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const int rt = 128 * (r >> 6) + 64 * h + (r & 63);           // tile row (row of W) of the half-tile's row r
-        oa[h][p] = (unsigned)((size_t)min(rt, M - 1 - m0) * lda * 2 + d_c * 16);
+        const int ra = 128 * (r >> 6) + 64 * h + (r & 63);           // tile row of the half-tile's row r
+        oa[h][p] = (unsigned)((size_t)min(ra, M - 1 - m0) * lda * 2 + d_c * 16);
+        if (p >= NW) continue;
+        const int rt = (BN / 2) * (r / (BN / 4)) + (BN / 4) * h + r % (BN / 4);      // the same for rows of W
         if (GLU) {
           const int ac = glu.col0 + tn * (BN / 2) + (rt >> 5) * 16 + (rt & 15);
           ow[h][p] = (unsigned)(((size_t)((rt >> 4) & 1) * glu.F + min(ac, glu.F - 1)) * ldw * 2 + d_c * 16);
@@ -622,79 +630,84 @@ __global__ __launch_bounds__(256) void gemm_bf16_quad_kernel(const bf16_t* __res
   // (a stage past the end: clamped, the loads repeat the last stage into a free buffer)
 #define Q_LOAD(buf_, src_, off_, p_) \
   __builtin_amdgcn_raw_ptr_buffer_load_lds(src_, FLEXCO_LP(buf_ + ((p_) * 4 + wave) * 512), 16, off_[p_], 0, 0, 0);
-#define Q_LOAD4(buf_, src_, off_) \
-  { const __amdgpu_buffer_rsrc_t b_ = src_; Q_LOAD(buf_, b_, off_, 0) Q_LOAD(buf_, b_, off_, 1) Q_LOAD(buf_, b_, off_, 2) Q_LOAD(buf_, b_, off_, 3) }
+#define Q_LOAD_A(buf_, h_, s_) \
+  { const __amdgpu_buffer_rsrc_t b_ = GEMM_SRC_A(s_); _Pragma("unroll") for (int p = 0; p < NA; ++p) Q_LOAD(buf_, b_, oa[h_], p) }
+#define Q_LOAD_W(buf_, g_, s_) \
+  { const __amdgpu_buffer_rsrc_t b_ = GEMM_SRC_W(s_); _Pragma("unroll") for (int p = 0; p < NW; ++p) Q_LOAD(buf_, b_, ow[g_], p) }
   const int key = l16 >> 1;
-  int tr_off[4];       // (one index expression from the array on, see the kernel above)
+  int tr_off[HN];       // (one index expression from the array on, see the kernel above)
 #pragma unroll
-  for (int jj = 0; jj < 4; ++jj) {
+  for (int jj = 0; jj < HN; ++jj) {
     const int col = wn * 64 + jj * 16 + 4 * (lane & 3);
     tr_off[jj] = (8 * q4 + (l16 >> 2)) * 128 + (((col >> 3) ^ ((l16 >> 2) << 2) ^ ((q4 & 1) << 1)) * 8) + (col & 7);
   }
-  // one fragment (16 rows or columns x 32 of K) of the eight a wavefront reads of a half-tile
-#define Q_READ_ROWS(dst_, buf_, w_, q_)                                                               \
-  dst_[(q_) & 3][(q_) >> 2] = *reinterpret_cast<const bf16x8*>(buf_ + (w_ * 64 + ((q_) & 3) * 16 + l16) * BK + ((((q_) >> 2) * 4 + q4) ^ key) * 8);
-#define Q_READ_A(dst_, buf_, q_) Q_READ_ROWS(dst_, buf_, wm, q_)
+  // fragment q_ (16 rows or columns x 32 of K) of the eight (six) a wavefront reads of a half-tile
+#define Q_READ_ROWS(dst_, buf_, rows_, n_, q_)                                                        \
+  dst_[(q_) % n_][(q_) / n_] = *reinterpret_cast<const bf16x8*>(buf_ + (rows_ + ((q_) % n_) * 16 + l16) * BK + ((((q_) / n_) * 4 + q4) ^ key) * 8);
+#define Q_READ_A(dst_, buf_, q_) if ((q_) < 8) Q_READ_ROWS(dst_, buf_, wm * 64, 4, (q_) & 7)
 #define Q_READ_W(dst_, buf_, q_)                                                                      \
-  {                                                                                                   \
+  if ((q_) < 2 * HN) {                                                                                \
     if (!TRANS) {                                                                                     \
-      Q_READ_ROWS(dst_, buf_, wn, q_)                                                                 \
+      Q_READ_ROWS(dst_, buf_, wn * (BN / 4), HN, (q_) % (2 * HN))                                     \
     } else {                                                                                          \
-      const s16x4 lo_ = __builtin_amdgcn_ds_read_tr16_b64_v4i16((FLEXCO_LDS s16x4*)(buf_ + (tr_off[(q_) & 3] + ((q_) >> 2) * 32 * 128)));       \
-      const s16x4 hi_ = __builtin_amdgcn_ds_read_tr16_b64_v4i16((FLEXCO_LDS s16x4*)(buf_ + (tr_off[(q_) & 3] + (((q_) >> 2) * 32 + 4) * 128))); \
-      dst_[(q_) & 3][(q_) >> 2] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo_, hi_, 0, 1, 2, 3, 4, 5, 6, 7)); \
+      const s16x4 lo_ = __builtin_amdgcn_ds_read_tr16_b64_v4i16((FLEXCO_LDS s16x4*)(buf_ + (tr_off[(q_) % HN] + (((q_) / HN) & 1) * 32 * 128)));       \
+      const s16x4 hi_ = __builtin_amdgcn_ds_read_tr16_b64_v4i16((FLEXCO_LDS s16x4*)(buf_ + (tr_off[(q_) % HN] + ((((q_) / HN) & 1) * 32 + 4) * 128))); \
+      dst_[(q_) % HN][((q_) / HN) & 1] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo_, hi_, 0, 1, 2, 3, 4, 5, 6, 7)); \
     }                                                                                                 \
   }
 #define Q_WAIT(n_) (0x0070 | ((n_) & 15) | (((n_) >> 4) << 14))      /* vmcnt(n), lgkmcnt(0) */
-  // a phase: read_ (for the next one), load_ (into the buffer the last one read), 32 products; then this wavefront's
-  // reads are in registers and its loads of the half-tile that is read next have landed
-#define Q_PHASE(READ_, rdst_, rbuf_, lbuf_, lsrc_, loff_, i0_, j0_, a_, w_)                           \
+  // a phase: 32 (24) products; behind each second one goes a read for the next phase, then the loads into the buffer the
+  // last phase has read.  At its end this wavefront's reads are in registers and its loads of the half-tile that is read
+  // next have landed (vm_: instructions of the six younger ones)
+#define Q_PHASE(READ_, rdst_, rbuf_, lbuf_, lsrc_, loff_, nl_, i0_, j0_, a_, w_, vm_)                 \
   {                                                                                                   \
     const __amdgpu_buffer_rsrc_t src_ = lsrc_;                                                        \
-    _Pragma("unroll") for (int n = 0; n < 32; ++n) {                                                  \
-      FLEXCO_MFMA(acc[i0_ + ((n >> 2) & 3)][j0_ + (n & 3)], w_[n & 3][n >> 4], a_[(n >> 2) & 3][n >> 4])   \
+    _Pragma("unroll") for (int n = 0; n < 8 * HN; ++n) {                                              \
+      FLEXCO_MFMA(acc[i0_ + (n / HN) % 4][j0_ + n % HN], w_[n % HN][n / (4 * HN)], a_[(n / HN) % 4][n / (4 * HN)]) \
       if ((n & 1) && n < 16) READ_(rdst_, rbuf_, n >> 1)                                              \
-      if ((n & 1) && n >= 16 && n < 24) Q_LOAD(lbuf_, src_, loff_, (n - 16) >> 1)                     \
+      if ((n & 1) && n >= 16 && n < 16 + 2 * nl_) Q_LOAD(lbuf_, src_, loff_, ((n - 16) >> 1) % nl_)   \
       if (n & 1) __builtin_amdgcn_sched_barrier(0);                                                   \
     }                                                                                                 \
-    Q_END                                                                                             \
+    Q_END(vm_)                                                                                        \
   }
-#define Q_END                                                                                         \
+#define Q_END(vm_)                                                                                    \
   {                                                                                                   \
     __builtin_amdgcn_sched_barrier(0);                                                                \
-    __builtin_amdgcn_s_waitcnt(Q_WAIT(24));                                                           \
+    __builtin_amdgcn_s_waitcnt(Q_WAIT(vm_));                                                          \
     asm volatile("" ::: "memory");                                                                    \
     __builtin_amdgcn_s_barrier();                                                                     \
     asm volatile("" ::: "memory");                                                                    \
     __builtin_amdgcn_sched_barrier(0);                                                                \
   }
+  // half-tiles in the order they are read: W A A W per stage
+  constexpr int VM0 = 3 * NA + 3 * NW, VM1 = 2 * NA + 4 * NW, VM2 = 3 * NA + 3 * NW, VM3 = 4 * NA + 2 * NW;
 #define Q_EVEN(s_)                                                                                    \
   {                                                                                                   \
-    Q_PHASE(Q_READ_W, fw1, w1e, w0e, GEMM_SRC_W((s_) + 2), ow[0], 0, 0, fa0, fw0)                        \
-    Q_PHASE(Q_READ_A, fa1, a1e, w1e, GEMM_SRC_W((s_) + 2), ow[1], 0, 4, fa0, fw1)                        \
-    Q_PHASE(Q_READ_A, fa0, a0o, a1e, GEMM_SRC_A((s_) + 2), oa[1], 4, 4, fa1, fw1)                        \
-    Q_PHASE(Q_READ_W, fw1, w1o, a0o, GEMM_SRC_A((s_) + 3), oa[0], 4, 0, fa1, fw0)                        \
+    Q_PHASE(Q_READ_W, fw1, w1e, w0e, GEMM_SRC_W((s_) + 2), ow[0], NW, 0, 0, fa0, fw0, VM0)            \
+    Q_PHASE(Q_READ_A, fa1, a1e, w1e, GEMM_SRC_W((s_) + 2), ow[1], NW, 0, HN, fa0, fw1, VM1)           \
+    Q_PHASE(Q_READ_A, fa0, a0o, a1e, GEMM_SRC_A((s_) + 2), oa[1], NA, 4, HN, fa1, fw1, VM2)           \
+    Q_PHASE(Q_READ_W, fw1, w1o, a0o, GEMM_SRC_A((s_) + 3), oa[0], NA, 4, 0, fa1, fw0, VM3)            \
   }
 #define Q_ODD(s_)                                                                                     \
   {                                                                                                   \
-    Q_PHASE(Q_READ_W, fw0, w0o, w1o, GEMM_SRC_W((s_) + 2), ow[1], 0, 4, fa0, fw1)                        \
-    Q_PHASE(Q_READ_A, fa1, a1o, w0o, GEMM_SRC_W((s_) + 2), ow[0], 0, 0, fa0, fw0)                        \
-    Q_PHASE(Q_READ_A, fa0, a0e, a1o, GEMM_SRC_A((s_) + 2), oa[1], 4, 0, fa1, fw0)                        \
-    Q_PHASE(Q_READ_W, fw0, w0e, a0e, GEMM_SRC_A((s_) + 3), oa[0], 4, 4, fa1, fw1)                        \
+    Q_PHASE(Q_READ_W, fw0, w0o, w1o, GEMM_SRC_W((s_) + 2), ow[1], NW, 0, HN, fa0, fw1, VM0)           \
+    Q_PHASE(Q_READ_A, fa1, a1o, w0o, GEMM_SRC_W((s_) + 2), ow[0], NW, 0, 0, fa0, fw0, VM1)            \
+    Q_PHASE(Q_READ_A, fa0, a0e, a1o, GEMM_SRC_A((s_) + 2), oa[1], NA, 4, 0, fa1, fw0, VM2)            \
+    Q_PHASE(Q_READ_W, fw0, w0e, a0e, GEMM_SRC_A((s_) + 3), oa[0], NA, 4, HN, fa1, fw1, VM3)           \
   }
-  bf16x8 fa0[4][2], fa1[4][2], fw0[4][2], fw1[4][2];
-  Q_LOAD4(a0e, GEMM_SRC_A(0), oa[0]) Q_LOAD4(w0e, GEMM_SRC_W(0), ow[0]) Q_LOAD4(w1e, GEMM_SRC_W(0), ow[1]) Q_LOAD4(a1e, GEMM_SRC_A(0), oa[1])
-  Q_LOAD4(a0o, GEMM_SRC_A(1), oa[0]) Q_LOAD4(w1o, GEMM_SRC_W(1), ow[1]) Q_LOAD4(w0o, GEMM_SRC_W(1), ow[0]) Q_LOAD4(a1o, GEMM_SRC_A(1), oa[1])
-  Q_END                                          // A0(0), W0(0) have landed
+  bf16x8 fa0[4][2], fa1[4][2], fw0[HN][2], fw1[HN][2];
+  Q_LOAD_A(a0e, 0, 0) Q_LOAD_W(w0e, 0, 0) Q_LOAD_W(w1e, 1, 0) Q_LOAD_A(a1e, 1, 0)
+  Q_LOAD_A(a0o, 0, 1) Q_LOAD_W(w1o, 1, 1) Q_LOAD_W(w0o, 0, 1) Q_LOAD_A(a1o, 1, 1)
+  Q_END(VM0)                                     // A0(0), W0(0) have landed
 #pragma unroll
   for (int q = 0; q < 8; ++q) {
     Q_READ_A(fa0, a0e, q)
     Q_READ_W(fw0, w0e, q)
   }
-  Q_END
-  Q_LOAD4(a0e, GEMM_SRC_A(2), oa[0])
+  Q_END(VM0)
+  Q_LOAD_A(a0e, 0, 2)
   FLEXCO_ACC_FENCE
-  Q_END                                          // W1(0)
+  Q_END(VM3)                                     // W1(0)
   int st = 0;
   for (; st + 1 < ns; st += 2) {
     Q_EVEN(st)
@@ -735,9 +748,20 @@ __global__ __launch_bounds__(256) void gemm_splitk_reduce_kernel(const float* __
   const size_t idx = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;
   if (idx >= (size_t)M * N) return;
   const int row = (int)(idx / N), col = (int)(idx % N);     // N % 8 == 0: the 4 elements share a row
+  const size_t mn = (size_t)M * N;
   f32x4 v = *reinterpret_cast<const f32x4*>(part + idx);
-  for (int sp = 1; sp < splits; ++sp) {
-    const f32x4 w = *reinterpret_cast<const f32x4*>(part + (size_t)sp * M * N + idx);
+  int sp = 1;
+  for (; sp + 3 <= splits; sp += 3) {        // three loads in flight, added in split order
+    f32x4 w[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) w[q] = *reinterpret_cast<const f32x4*>(part + (sp + q) * mn + idx);
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] += w[q][j];
+  }
+  for (; sp < splits; ++sp) {
+    const f32x4 w = *reinterpret_cast<const f32x4*>(part + sp * mn + idx);
 #pragma unroll
     for (int j = 0; j < 4; ++j) v[j] += w[j];
   }
@@ -757,12 +781,12 @@ int32_t launch_cfg(const void* A, const void* W, void* C, const void* bias, cons
                    size_t lda, size_t ldw, size_t ldc, size_t ldr, const GemmExt& ext, hipStream_t s,
                    int timer_id, float* part = nullptr, int splits = 1, bool first_of_call = true,
                    const GemmGlu* glu_in = nullptr, bool skip_reduce = false) {
-  // all LDS is static; the 256 x 256 tile is a kernel of its own
-  constexpr bool QUAD = BM == 256 && BN == 256;
+  // all LDS is static; the 256-row tiles have a kernel of their own
+  constexpr bool QUAD = BM == 256;
   constexpr int THREADS = 256;
   void (*kern)(const bf16_t*, const bf16_t*, bf16_t*, const bf16_t*, const bf16_t*, int, int, int, size_t, size_t, size_t, size_t,
                int, int, GemmExt, float*, int, GemmGlu);
-  if constexpr (QUAD) kern = gemm_bf16_quad_kernel<TRANS, GLU>;
+  if constexpr (QUAD) kern = gemm_bf16_quad_kernel<BN, TRANS, GLU>;
   else kern = gemm_bf16_kernel<BM, BN, TRANS, GLU, NSTAGES>;
   GemmGlu glu;
   if (glu_in) glu = *glu_in; else memset(&glu, 0, sizeof(glu));
@@ -846,38 +870,82 @@ static int pick_splits(int M, int N, int K, int tiles, size_t part_elems, int wa
 // 512 to 1536 rows at the 8B, 14B and 32B shapes; with them the estimate picks the faster shape in each).
 constexpr double TRANS_RATE_128 = 0.94, TRANS_RATE_256 = 1.05;
 
-// Tile shapes of a forward-form product by estimated time.  A launch runs in rounds of one block per CU; a
-// round costs the tile's area over the rate its kernel sustains with the chip full (measured, relative:
-// 256 x 256 tiles 1.24, 256 x 192 1.09, 128 x 192 1.0, 128 x 128 0.875).  Candidates: columns [0, 256 a) in
-// 256-wide tiles and the rest in ONE of the three narrower shapes, as two launches (a partial last round of
-// wide tiles is what the narrower ones avoid); a = 0 is a single shape for the whole matrix.
+// ---- estimated times, us, of launches of `blocks` blocks over `stages` 64-wide stages of K each.  Fitted to products of
+// 256 to 2048 rows at the 8B, 14B and 32B shapes with N(0, 1) x N(0, 0.02) operands, weights not in a cache; within 10 % of
+// each of some 150 measurements but for windows of 256 rows, which wait for HBM (up to 20 % above the estimate, all shapes
+// alike).  A launch runs in rounds over the CUs; a stage of the 256-row tiles takes longer the more CUs multiply at the
+// same time (the chip's power limit: 256 x 256 tiles 1.03 us at up to 128 blocks, 1.31 at 256).
+static double us_tile256(long blocks, double stages, int bn) {
+  const long rounds = (blocks + 255) / 256;
+  const double over = std::max(0.0, (double)blocks / rounds - 128);
+  return rounds * (9 + stages * (bn == 256 ? 1.03 + 0.0022 * over : 0.85 + 0.0013 * over));
+}
+static double us_tile128x192(long blocks, double stages) { return ((blocks + 255) / 256) * (4 + 0.76 * stages); }
+// 128 x 128: one four-stage block per CU, or with more blocks than CUs two two-stage blocks
+static double us_tile128(long blocks, double stages) {
+  if (blocks <= 256) return 3 + 0.6 * stages;
+  const long rounds = (blocks + 511) / 512;
+  return rounds * (3 + (blocks / rounds <= 460 ? 0.95 : 1.1) * stages);
+}
+// partial sums out and back in, and the launch that adds them
+static double us_partial_sums(int splits, int M, int N) { return splits > 1 ? 4 + (double)splits * M * N * 1e-6 : 0.0; }
+
+// Tile shapes of a forward-form product by estimated time: columns [0, 256 a) in 256-wide tiles and the rest in ONE of
+// the three narrower shapes, as two launches (a partial last round of wide tiles is what the narrower ones avoid);
+// a = 0 is a single shape for the whole matrix.
 struct GemmPlan {
   int a256;    // number of 256-wide column tiles
   int rest;    // shape of the remaining columns: 0 = 128 x 128, 1 = 128 x 192, 2 = 256 x 192
+  double us;
 };
-static GemmPlan plan_forward(int M, int N) {
-  const int CU = 256;
-  auto rounds = [&](long tiles) { return (double)((tiles + CU - 1) / CU); };
+static GemmPlan plan_forward(int M, int N, int K) {
+  const double ns = K / BK;
   const long tm256 = (M + 255) / 256, tm128 = (M + 127) / 128;
-  const double c256 = 256.0 * 256 / 1.24;
-  const long tm_rest[3] = {tm128, tm128, tm256};
-  const int bn_rest[3] = {128, 192, 192};
-  const double c_rest[3] = {128.0 * 128 / 0.875, 128.0 * 192 / 1.0, 256.0 * 192 / 1.09};
-  GemmPlan best{0, 0};
-  double best_t = 1e300;
+  GemmPlan best{0, 0, 1e300};
   const int n256 = (N + 255) / 256;
   for (int a = n256; a >= 0; --a) {
     const int rest = N - 256 * a;                   // columns left for the narrower tiles
     if (rest < 0 && a != n256) continue;
-    const double t_a = a ? rounds(tm256 * a) * c256 : 0.0;
+    const double t_a = a ? us_tile256(tm256 * a, ns, 256) : 0.0;
     if (rest <= 0) {
-      if (t_a < best_t - 1e-9) { best_t = t_a; best = GemmPlan{a, 0}; }
+      if (t_a < best.us - 1e-9) best = GemmPlan{a, 0, t_a};
       continue;
     }
-    for (int sh = 2; sh >= 0; --sh) {
-      const double t = t_a + rounds(tm_rest[sh] * ((rest + bn_rest[sh] - 1) / bn_rest[sh])) * c_rest[sh];
-      if (t < best_t - 1e-9) { best_t = t; best = GemmPlan{a, sh}; }
-    }
+    const long c192 = (rest + 191) / 192;
+    const double t_rest[3] = {us_tile128(tm128 * ((rest + 127) / 128), ns), us_tile128x192(tm128 * c192, ns), us_tile256(tm256 * c192, ns, 192)};
+    for (int sh = 2; sh >= 0; --sh)
+      if (t_a + t_rest[sh] < best.us - 1e-9) best = GemmPlan{a, sh, t_a + t_rest[sh]};
+  }
+  return best;
+}
+
+// Ranges of K in whole stages, equal to within one, to run a product on 256 x 256 tiles with, or 0: the launch plan
+// below is as good.  For products whose 256 x 256 tiles leave CUs idle (or whose last round does), at the price of partial
+// sums.  1: the tiles as they are, input-gradient form only (the forward plan has that choice).
+// Measured (us, plan -> ranges): forward 1024 x 4096 x 14336 135 -> 99 (4), 2048 x 4096 x 14336 210 -> 172 (2),
+// 1405 x 5120 x 27648 400 -> 312 (2); input gradient 512 x 4096 x 128256 625 -> 419 (8), 512 x 4096 x 28672 152 -> 103 (8),
+// 1024 x 5120 x 7168 126 -> 74 (3), 1024 x 5120 x 5120 100 -> 60 (3), 256 x 4096 x 28672 91 -> 77 (12).
+int plan_gemm_k_ranges(int M, int N, int K, bool trans_w, size_t part_elems) {
+  const int ns = K / BK;
+  const long tiles = (long)((M + 255) / 256) * ((N + 255) / 256);
+  const GemmLaunchPlan pl = plan_gemm_mfma(M, N, K, trans_w, part_elems);
+  const GemmLaunchStep& st = pl.step[0];
+  double us;
+  if (!trans_w && st.splits == 1) {
+    us = plan_forward(M, N, K).us;
+  } else {
+    const long blocks = (long)((M + st.bm - 1) / st.bm) * ((N + st.bn - 1) / st.bn) * st.splits;
+    const double s = (double)ns / st.splits;
+    // (the input-gradient form's 128 x 128 blocks have two stages whatever their number)
+    us = (st.bm == 256 ? us_tile256(blocks, s, 256) : !trans_w ? us_tile128(blocks, s)
+          : blocks <= 256 ? 3 + 0.85 * s : ((blocks + 511) / 512) * (3 + 1.1 * s)) + us_partial_sums(st.splits, M, N);
+  }
+  int best = 0;
+  us *= 0.95;                                       // (the large tiles have to win clearly)
+  for (int r = trans_w ? 1 : 2; r <= 16 && ns / r >= 4; ++r) {
+    if (r > 1 && (size_t)r * M * N > part_elems) break;
+    const double t = us_tile256(tiles * r, (double)((ns + r - 1) / r), 256) + us_partial_sums(r, M, N);
+    if (t < us) { us = t; best = r; }
   }
   return best;
 }
@@ -928,7 +996,7 @@ GemmLaunchPlan plan_gemm_mfma(int M, int N, int K, bool trans_w, size_t part_ele
       return pl;
     }
   }
-  const GemmPlan fp = plan_forward(M, N);
+  const GemmPlan fp = plan_forward(M, N, K);
   const int n1 = std::min(N, 256 * fp.a256);
   if (n1 > 0) add(256, 256, n1, 1, 2);
   if (n1 < N) {
@@ -942,6 +1010,9 @@ GemmLaunchPlan plan_gemm_mfma(int M, int N, int K, bool trans_w, size_t part_ele
   return pl;
 }
 
+// The kernels address a tile's rows by 32-bit byte offsets from its first.
+static bool offsets_fit(size_t ld, size_t rows) { return ld <= 0xffff0000u / 2 / rows; }
+
 int32_t launch_gemm_mfma(const void* A, const void* W, void* C, const void* bias, const void* residual, int M, int N,
                          int K, size_t lda, size_t ldw, size_t ldc, size_t ldr, bool trans_w, const GemmExt* ext_in,
                          hipStream_t s, float* part, size_t part_elems, int timer_id, int* splits_out) {
@@ -951,14 +1022,23 @@ int32_t launch_gemm_mfma(const void* A, const void* W, void* C, const void* bias
   if (K % BK != 0 || lda % 8 != 0 || ldw % 8 != 0 || N % 8 != 0 || ldc % 4 != 0 || (residual && ldr % 4 != 0) ||
       ((uintptr_t)C & 7) || ((uintptr_t)bias & 7) || ((uintptr_t)residual & 7))
     return FLEXCO_EUNSUPPORTED;
+  if (!offsets_fit(lda, 256) || !offsets_fit(ldw, 256)) return FLEXCO_EUNSUPPORTED;
   GemmExt ext;
   if (ext_in) ext = *ext_in; else ext.n = 0;
   if (!ext_fits(ext, trans_w, N)) return FLEXCO_EUNSUPPORTED;
+  // splits_out: the caller's next kernel adds the partial sums itself (part[split][M][N], in split order) and
+  // the reduction launch is left out; bias and residual are then not applied
+  const int ranges = plan_gemm_k_ranges(M, N, K, trans_w, part ? part_elems : 0);
+  if (ranges) {
+    const bool leave = splits_out && ranges > 1 && !bias && !residual;
+    if (leave) *splits_out = ranges;
+    if (trans_w)
+      return launch_cfg<256, 256, true>(A, W, C, bias, residual, M, N, K, lda, ldw, ldc, ldr, ext, s, timer_id, part, ranges, true, nullptr, leave);
+    return launch_cfg<256, 256, false>(A, W, C, bias, residual, M, N, K, lda, ldw, ldc, ldr, ext, s, timer_id, part, ranges, true, nullptr, leave);
+  }
   const GemmLaunchPlan pl = plan_gemm_mfma(M, N, K, trans_w, part ? part_elems : 0);
   if (trans_w) {
     const GemmLaunchStep& st = pl.step[0];
-    // splits_out: the caller's next kernel adds the partial sums itself (part[split][M][N], in split order) and
-    // the reduction launch is left out; bias and residual are then not applied
     const bool leave = splits_out && st.splits > 1 && !bias && !residual;
     if (leave) *splits_out = st.splits;
     if (st.bm == 256)
@@ -1004,6 +1084,7 @@ int32_t launch_gemm_glu_mfma(const void* A, const void* W, void* act, int M, int
   if (K % BK != 0 || lda % 8 != 0 || ldw % 8 != 0 || F % 8 != 0 || ld_act % 4 != 0 || ld_save % 4 != 0 ||
       ((uintptr_t)act & 7) || ((uintptr_t)save_gate & 7) || ((uintptr_t)save_up & 7))
     return FLEXCO_EUNSUPPORTED;
+  if (!offsets_fit(lda, 256) || !offsets_fit(ldw, (size_t)F + 256)) return FLEXCO_EUNSUPPORTED;   // (gate and up rows of W in one tile)
   GemmExt ext;
   if (ext_in) ext = *ext_in; else ext.n = 0;
   if (ext.n > 0 && ext.r % 16 != 0) return FLEXCO_EUNSUPPORTED;
