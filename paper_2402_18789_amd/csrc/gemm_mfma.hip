@@ -194,7 +194,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
                                                         const bf16_t* __restrict__ res, int M, int N, int K,
                                                         size_t lda, size_t ldw, size_t ldc, size_t ldr, int tiles_m,
                                                         int tiles_n, GemmExt ext, float* __restrict__ part,
-                                                        int k_chunk, GemmGlu glu) {
+                                                        GemmGlu glu) {
 #ifdef __HIP_DEVICE_COMPILE__      // (the host pass knows no such assembly)
   constexpr int WM = BM / 2, WN = BN / 2, MT = WM / 16, NT = WN / 16;
 
@@ -217,8 +217,11 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
 #pragma unroll
       for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
 
-  // split-K: blockIdx.y owns k in [kbeg, kbeg + k_chunk) and writes fp32 partial sums to `part`
-  const int kbeg = blockIdx.y * k_chunk;
+  // split-K: blockIdx.y owns whole stages of K, in ranges that differ by one at most, and writes fp32 partial sums to `part`
+  const int st_all = K / BK;
+  const int st_beg = (int)((long)st_all * blockIdx.y / gridDim.y);
+  const int ns = (int)((long)st_all * (blockIdx.y + 1) / gridDim.y) - st_beg;      // stages of this block (at least one)
+  const int kbeg = st_beg * BK;
   const int l16 = lane & 15, q4 = lane >> 4;
 
   // ===================== operand tiles: global memory -> LDS directly ==========================
@@ -232,6 +235,12 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
   // K-split into more blocks than CUs).  The stages are separate arrays, not one indexed
   // buffer: the compiler then sees that loads in flight target an array no ds_read of that
   // moment touches, and inserts no wait of its own.
+  // NSTAGES = 6 for the 64-row tile (24 KB a stage, 144 KB): batches of few tokens, whose time is the weights' way out of
+  // HBM.  A block has 80 KB of weights on their way (128-row tiles, half of whose loads repeat the last row: 48 KB).  With
+  // a 48-token batch at the 14B shape, reduction launches included: qkv 36 -> 21 us, down 40 -> 32 us; 8 tokens, 8B shape: o
+  // 16.7 -> 12.3, down 27.7 -> 26, gate/up 4.5 TB/s either way.  (Fragments of W straight from global memory into
+  // registers, a block's wavefronts cutting K, no partial sums: 5.3 TB/s for one row, but the blocks' reads of A
+  // compete: 16 rows 3.8, 64 rows 1.7 TB/s.)
   // NSTAGES = 2 for a 128-row forward tile: two such blocks share a CU.  With more tiles than CUs that is 15-30 %
   // faster than one four-stage block per CU in two rounds (one block's waits are the other's products); with one
   // tile per CU the four stages win.
@@ -242,8 +251,10 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
   static_assert(!TRANS || BN == 128, "the input-gradient form's W tile swizzle assumes 256-byte rows");
   __shared__ __attribute__((aligned(1024))) bf16_t ring0[ST_ELEMS];
   __shared__ __attribute__((aligned(1024))) bf16_t ring1[ST_ELEMS];
-  __shared__ __attribute__((aligned(1024))) bf16_t ring2[NST == 4 ? ST_ELEMS : 8];
-  __shared__ __attribute__((aligned(1024))) bf16_t ring3[NST == 4 ? ST_ELEMS : 8];
+  __shared__ __attribute__((aligned(1024))) bf16_t ring2[NST >= 4 ? ST_ELEMS : 8];
+  __shared__ __attribute__((aligned(1024))) bf16_t ring3[NST >= 4 ? ST_ELEMS : 8];
+  __shared__ __attribute__((aligned(1024))) bf16_t ring4[NST == 6 ? ST_ELEMS : 8];
+  __shared__ __attribute__((aligned(1024))) bf16_t ring5[NST == 6 ? ST_ELEMS : 8];
   // [rows][64] tiles (128-byte rows): chunk c of row r is stored at chunk c ^ ((r >> 1) & 7) (the
   // variant measured fastest for the ds_read_b128 operand fetches: 85 % of the LDS peak).
   // [64][BN] W tile of the input-gradient form (256- or 512-byte rows, read by transposing LDS reads of
@@ -284,7 +295,6 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
   const char* const pa = (const char*)(A + (size_t)m0 * lda + kbeg);
   const char* const pw = (const char*)(GLU ? W + kbeg : (TRANS ? W + (size_t)kbeg * ldw + n0 : W + (size_t)n0 * ldw + kbeg));
   const size_t wstep = TRANS ? (size_t)BK * ldw * 2 : (size_t)BK * 2;
-  const int ns = k_chunk / BK;                   // stages of this block
 
   // stage index past the end: clamped, the loads repeat the last stage into a free buffer
 #define GEMM_SRC_A(s_) __builtin_amdgcn_make_buffer_rsrc((void*)(pa + (size_t)min((s_), ns - 1) * (BK * 2)), 0, -1, 0x00027000)
@@ -375,10 +385,10 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
   // s_waitcnt immediates: vmcnt in bits 3:0 and 15:14, expcnt 6:4 and lgkmcnt 11:8 left at
   // their maxima (no wait)
 #define FLEXCO_VMCNT(n_) (0x0F70 | ((n_) & 15) | (((n_) >> 4) << 14))
-  // before a stage's barrier: the next stage has landed; with four stages one more may stay in flight
-  constexpr int WAIT_NEXT_STAGE = NST == 4 ? FLEXCO_VMCNT(NLD) : FLEXCO_VMCNT(0);
-  // the buffer freed at stage s's barrier held stage s - 1 (four stages) or stage s itself (two)
-  constexpr int AHEAD = NST == 4 ? 3 : 2;
+  // before a stage's barrier: the next stage has landed, the ones after it (up to s + 2 of four, s + 4 of six) may stay in flight
+  constexpr int WAIT_NEXT_STAGE = FLEXCO_VMCNT(NST > 2 ? (NST - 3) * NLD : 0);
+  // the buffer freed at stage s's barrier held stage s - 1 (four stages, six) or stage s itself (two)
+  constexpr int AHEAD = NST > 2 ? NST - 1 : 2;
   // ---- operands of the rank-r extension's first step and the residual / bias of the epilogue, fetched ahead of the
   // main loop (128-row tiles: the registers are there; their round trips - one or two per block, all blocks
   // ending together - otherwise lie open at the end of the launch) --------------------------------------------
@@ -461,7 +471,29 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
   FLEXCO_ACC_FENCE
 #define FLEXCO_FIRST_FRAGS                                                                            \
   { _Pragma("unroll") for (int q = 0; q < MT + NT; ++q) FLEXCO_FRAG(ring0, 0, af0, bf0, q) }
-  if constexpr (NST == 4) {
+  if constexpr (NST == 6) {
+    FLEXCO_DMA(ring0, 0)
+    FLEXCO_DMA(ring1, 1)
+    FLEXCO_DMA(ring2, 2)
+    FLEXCO_DMA(ring3, 3)
+    FLEXCO_DMA(ring4, 4)
+    FLEXCO_WAIT_BARRIER(FLEXCO_VMCNT(4 * NLD))
+    FLEXCO_FIRST_FRAGS
+    int st = 0;
+    for (; st + 5 < ns; st += 6) {
+      FLEXCO_STAGE(ring0, ring1, ring5, st)
+      FLEXCO_STAGE(ring1, ring2, ring0, st + 1)
+      FLEXCO_STAGE(ring2, ring3, ring1, st + 2)
+      FLEXCO_STAGE(ring3, ring4, ring2, st + 3)
+      FLEXCO_STAGE(ring4, ring5, ring3, st + 4)
+      FLEXCO_STAGE(ring5, ring0, ring4, st + 5)
+    }
+    if (st < ns) FLEXCO_STAGE(ring0, ring1, ring5, st)
+    if (st + 1 < ns) FLEXCO_STAGE(ring1, ring2, ring0, st + 1)
+    if (st + 2 < ns) FLEXCO_STAGE(ring2, ring3, ring1, st + 2)
+    if (st + 3 < ns) FLEXCO_STAGE(ring3, ring4, ring2, st + 3)
+    if (st + 4 < ns) FLEXCO_STAGE(ring4, ring5, ring3, st + 4)
+  } else if constexpr (NST == 4) {
     FLEXCO_DMA(ring0, 0)
     FLEXCO_DMA(ring1, 1)
     FLEXCO_DMA(ring2, 2)
@@ -554,7 +586,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_quad_kernel(const bf16_t* __res
                                                              const bf16_t* __restrict__ res, int M, int N, int K,
                                                              size_t lda, size_t ldw, size_t ldc, size_t ldr, int tiles_m,
                                                              int tiles_n, GemmExt ext, float* __restrict__ part,
-                                                             int /*k_chunk*/, GemmGlu glu) {
+                                                             GemmGlu glu) {
 #ifdef __HIP_DEVICE_COMPILE__
   constexpr int BM = 256, MT = 8, NT = BN / 32, HN = NT / 2;      // HN: 16-column fragments of a phase
   constexpr int NA = 4, NW = BN / 64;                             // load instructions of a half-tile
@@ -785,7 +817,7 @@ int32_t launch_cfg(const void* A, const void* W, void* C, const void* bias, cons
   constexpr bool QUAD = BM == 256;
   constexpr int THREADS = 256;
   void (*kern)(const bf16_t*, const bf16_t*, bf16_t*, const bf16_t*, const bf16_t*, int, int, int, size_t, size_t, size_t, size_t,
-               int, int, GemmExt, float*, int, GemmGlu);
+               int, int, GemmExt, float*, GemmGlu);
   if constexpr (QUAD) kern = gemm_bf16_quad_kernel<BN, TRANS, GLU>;
   else kern = gemm_bf16_kernel<BM, BN, TRANS, GLU, NSTAGES>;
   GemmGlu glu;
@@ -803,7 +835,7 @@ int32_t launch_cfg(const void* A, const void* W, void* C, const void* bias, cons
   }
   FLEXCO_LAUNCH_TIMED(kern, dim3(tiles_m * tiles_n, splits), THREADS, (const bf16_t*)A, (const bf16_t*)W, (bf16_t*)C,
                       (const bf16_t*)bias, (const bf16_t*)res, M, N, K, lda, ldw, ldc, ldr, tiles_m, tiles_n, ext,
-                      splits > 1 ? part : nullptr, K / splits, glu)
+                      splits > 1 ? part : nullptr, glu)
   if (splits > 1 && !skip_reduce) {
     const size_t quads = ((size_t)M * N + 3) / 4;
     e0 = e1 = nullptr;
@@ -950,6 +982,15 @@ int plan_gemm_k_ranges(int M, int N, int K, bool trans_w, size_t part_elems) {
   return best;
 }
 
+// Forward products of at most THIN_ROWS rows run on 64 x 128 tiles, K cut until the tiles cover the chip, ten stages or
+// more to a block (4096 columns, K = 4096: 11.8 - 12.6 us with 4 to 8 ranges, 15.9 with 12; K = 14336: 35, 29, 26 us with 4, 5, 8).
+constexpr int THIN_ROWS = 64;
+static int thin_splits(int M, int N, int K, size_t part_elems) {
+  int sp = std::min(256 / ((N + 127) / 128), K / BK / 10);
+  if (sp > 1) sp = (int)std::min<size_t>(sp, part_elems / ((size_t)M * N));
+  return std::max(sp, 1);
+}
+
 // What launch_gemm_mfma does for a shape: one or two launches, each a tile shape over a range of output columns,
 // possibly with K cut across blocks.  A pure function of the arguments (host arithmetic only).
 GemmLaunchPlan plan_gemm_mfma(int M, int N, int K, bool trans_w, size_t part_elems) {
@@ -1026,6 +1067,9 @@ int32_t launch_gemm_mfma(const void* A, const void* W, void* C, const void* bias
   GemmExt ext;
   if (ext_in) ext = *ext_in; else ext.n = 0;
   if (!ext_fits(ext, trans_w, N)) return FLEXCO_EUNSUPPORTED;
+  if (!trans_w && M <= THIN_ROWS)
+    return launch_cfg<THIN_ROWS, 128, false, false, 6>(A, W, C, bias, residual, M, N, K, lda, ldw, ldc, ldr, ext, s, timer_id, part,
+                                                       thin_splits(M, N, K, part ? part_elems : 0));
   // splits_out: the caller's next kernel adds the partial sums itself (part[split][M][N], in split order) and
   // the reduction launch is left out; bias and residual are then not applied
   const int ranges = plan_gemm_k_ranges(M, N, K, trans_w, part ? part_elems : 0);
@@ -1092,6 +1136,9 @@ int32_t launch_gemm_glu_mfma(const void* A, const void* W, void* act, int M, int
   glu.F = F; glu.col0 = 0; glu.save_gate = (bf16_t*)save_gate; glu.save_up = (bf16_t*)save_up;
   glu.save_row0 = save_row0; glu.save_rows = save_gate ? save_rows : 0; glu.ld_save = ld_save;
   const int N = 2 * F;
+  if (M <= THIN_ROWS)
+    return launch_cfg<THIN_ROWS, 128, false, true, 6>(A, W, act, nullptr, nullptr, M, N, K, lda, ldw, ld_act, 0, ext, s, timer_id,
+                                                      nullptr, 1, true, &glu);
   const GemmLaunchPlan pl = plan_gemm_mfma(M, N, K, false, 0);
   int c0 = 0;                                       // interleaved columns done = 2 x the act columns done
   for (int i = 0; i < pl.n; ++i) {

@@ -38,6 +38,14 @@ def test_forward_tiles(tile, M, N, K):
     run_gemm(M, N, K, 0)
 
 
+# at most 64 rows: 64 x 128 tiles with a ring of six stages
+@pytest.mark.parametrize("K", [64, 192, 384, 448, 704])
+@pytest.mark.parametrize("M,N", [(1, 8), (63, 136), (64, 1000)])
+def test_forward_tiles_of_few_rows(M, N, K):
+    print(f"forward M={M} N={N} K={K}", flush=True)
+    run_gemm(M, N, K, 0)
+
+
 @pytest.mark.parametrize("K", [64, 128, 192, 448])
 @pytest.mark.parametrize("M,N", [(1030, 13832), (130, 136), (64, 40)])
 def test_input_gradient_tiles_128(M, N, K):
