@@ -277,7 +277,7 @@ FwdWs carve_fwd(const flexco_layer_cfg& c, int T, int n_parts, void* base) {
   w.gu = cv.take(e * T * 2 * c.ffn);
   w.act = cv.take(e * T * c.ffn);
   w.lse = (float*)cv.take(sizeof(float) * T * c.n_q_heads);
-  w.u = (float*)cv.take(sizeof(float) * T * (c.lora_rank > 0 ? c.lora_rank : 1));
+  w.u = (float*)cv.take(sizeof(float) * LORA_GROUP * T * (c.lora_rank > 0 ? c.lora_rank : 1));
   const size_t prow = (size_t)n_parts * c.n_kv_heads * cols_per_tile(c);
   w.part_ml = (float*)cv.take(sizeof(float) * prow * 2);
   w.part_acc = (float*)cv.take(sizeof(float) * prow * c.head_dim);
@@ -308,8 +308,8 @@ BwdWs carve_bwd(const flexco_layer_cfg& c, int n, void* base) {
   w.dqkv = cv.take(e * n * qkvd);
   w.delta = (float*)cv.take(sizeof(float) * n * c.n_q_heads);
   const int r = c.lora_rank > 0 ? c.lora_rank : 1;
-  w.u = (float*)cv.take(sizeof(float) * n * r);
-  w.t = (float*)cv.take(sizeof(float) * n * r);
+  w.u = (float*)cv.take(sizeof(float) * LORA_GROUP * n * r);
+  w.t = (float*)cv.take(sizeof(float) * LORA_GROUP * n * r);
   w.gemm_part_elems = c.dtype == FLEXCO_BF16 ? (size_t)n * bwd_splitk_cols(n) : 0;
   w.gemm_part = (float*)cv.take(sizeof(float) * w.gemm_part_elems);
   w.colsum_part = (float*)cv.take(sizeof(float) * (size_t)((n + 7) / 8) *
@@ -419,17 +419,6 @@ void target_dims(const flexco_layer_cfg& c, int t, int* in, int* out) {
 inline char* boff(void* p, size_t elems, size_t e) { return (char*)p + elems * e; }
 inline const char* boff(const void* p, size_t elems, size_t e) { return (const char*)p + elems * e; }
 inline bool has_target(const flexco_layer_cfg& c, int t) { return (c.lora_targets >> t & 1) != 0; }
-
-// unfused fallback: y[rows, col0 : col0 + out] += scale (x[rows] A^T) B^T for the n rows listed in row_idx
-int32_t lora_apply(const flexco_layer_cfg& c, const flexco_lora* l, int t, const int32_t* row_idx, int n, const void* x,
-                   size_t ldx, void* y, size_t ldy, size_t col0, float* u, hipStream_t s) {
-  if (!has_target(c, t) || n == 0) return FLEXCO_OK;
-  int in, out;
-  target_dims(c, t, &in, &out);
-  FLEXCO_TRY(launch_lora_shrink(x, ldx, l->A[t], u, n, in, c.lora_rank, c.dtype, row_idx, s));
-  return launch_lora_expand(u, l->B[t], boff(y, col0, esize(c.dtype)), ldy, n, out, c.lora_rank, c.lora_scale, c.dtype,
-                            row_idx, s);
-}
 
 // the bf16 LoRA path needs whole MFMA k-steps in the rank and in the contracted dimensions
 bool lora_mfma_ok(const flexco_layer_cfg& c, int k_dim) {
@@ -556,13 +545,21 @@ int32_t forward_projection(const flexco_layer_cfg& c, const Adapters& ad, const 
     }
     LR(launch_lora_shrink_mfma(sa, nact, s));
   }
-  for (int ia = 0; ia < nact; ++ia)
-    for (int iu = 0; iu < nused; ++iu) {
-      const int a = used[iu];
-      const int32_t* rows = ad.any_id ? m.lora_tok : m.lora_tok + m.adapter_tok_off[a];
-      const int n = ad.any_id ? m.n_lora : m.adapter_tok_off[a + 1] - m.adapter_tok_off[a];
-      LR(lora_apply(c, &ad.ads[a], targets[act[ia]], rows, n, x, K, y, N, col0[act[ia]], k.u, s));
+  // unfused fallback: y[rows, col0_t : col0_t + out_t] += scale (x[rows] A_t^T) B_t^T, adapter by adapter
+  for (int iu = 0; iu < nused && nact > 0; ++iu) {
+    const int a = used[iu];
+    const int32_t* rows = ad.any_id ? m.lora_tok : m.lora_tok + m.adapter_tok_off[a];
+    const int n = ad.any_id ? m.n_lora : m.adapter_tok_off[a + 1] - m.adapter_tok_off[a];
+    LoraTarget tg[LORA_GROUP];
+    for (int ia = 0; ia < nact; ++ia) {
+      const int t = targets[act[ia]];
+      int in, out;
+      target_dims(c, t, &in, &out);
+      tg[ia] = {x, (size_t)K, boff(y, col0[act[ia]], esize(dt)), (size_t)N, ad.ads[a].A[t], ad.ads[a].B[t], in, out,
+                k.u + (size_t)ia * T * r, nullptr, nullptr, nullptr};
     }
+    LR(launch_lora_apply(tg, nact, n, r, c.lora_scale, dt, rows, s));
+  }
   return FLEXCO_OK;
 }
 
@@ -672,13 +669,15 @@ int32_t backward_projection(const flexco_layer_cfg& c, const flexco_lora* lora, 
   // (the unfused LoRA kernels below add into dx: they need it complete)
   if (dx) FLEXCO_TRY(launch_gemm(dy, W, dx, nullptr, nullptr, n, N_dx, K_dy, K_dy, N_dx, N_dx, 0, true, dt, s, nullptr,
                                  k.gemm_part, k.gemm_part_elems, g.nact == 0 ? splits_out : nullptr));
+  LoraTarget tg[LORA_GROUP];
   for (int z = 0; z < g.nact; ++z) {
     const int t = g.targets[g.act[z]];
     int in, out;
     target_dims(c, t, &in, &out);
-    LR(launch_lora_bwd(g.xs[g.act[z]], in, boff(dy, g.col0[g.act[z]], e), K_dy, lora->A[t], lora->B[t], lora->dA[t],
-                       lora->dB[t], dx, N_dx, k.u, k.t, n, in, out, r, c.lora_scale, dt, s));
+    tg[z] = {g.xs[g.act[z]], (size_t)in, const_cast<char*>(boff(dy, g.col0[g.act[z]], e)), (size_t)K_dy, lora->A[t], lora->B[t],
+             in, out, k.u + (size_t)z * n * r, k.t + (size_t)z * n * r, lora->dA[t], lora->dB[t]};
   }
+  if (g.nact > 0) LR(launch_lora_bwd(tg, g.nact, dx, N_dx, n, r, c.lora_scale, dt, s));
   return FLEXCO_OK;
 }
 
@@ -1410,8 +1409,8 @@ extern "C" int32_t flexco_adapter_bwd(int32_t dtype, int32_t hidden, const flexc
   }
   KernelTimerScope ts(FLEXCO_K_LORA, s);
   // u = relu(x W_down^T); t = (dY W_up) masked; dW_up += dY^T u; dW_down += t^T x; dY += t W_down
-  return launch_lora_bwd(x_w, hidden, dY, hidden, ad->w_down, ad->w_up, ad->dw_down, ad->dw_up, dY, hidden, u, t, n, hidden,
-                         hidden, b, 1.f, dtype, s, true);
+  const LoraTarget tg = {x_w, (size_t)hidden, dY, (size_t)hidden, ad->w_down, ad->w_up, hidden, hidden, u, t, ad->dw_down, ad->dw_up};
+  return launch_lora_bwd(&tg, 1, dY, hidden, n, b, 1.f, dtype, s, true);
 }
 
 // ---- all layers of a model in one call ---------------------------------------------------------------

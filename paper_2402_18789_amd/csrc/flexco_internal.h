@@ -179,9 +179,29 @@ int32_t launch_lora_shrink(const void* x, size_t ldx, const void* A, float* u, i
                            const int32_t* row_idx, hipStream_t s);
 int32_t launch_lora_expand(const float* u, const void* B, void* y, size_t ldy, int n, int out, int r, float scale,
                            int dtype, const int32_t* row_idx, hipStream_t s);
-int32_t launch_lora_bwd(const void* x, size_t ldx, const void* dy, size_t lddy, const void* A, const void* B,
-                        float* dA, float* dB, void* dx, size_t lddx, float* u_ws, float* t_ws, int n, int in,
-                        int out, int r, float scale, int dtype, hipStream_t s, bool relu = false);
+// One target of the type-generic LoRA kernels: x [n, in], A [r, in], B [out, r], u [n, r] scratch; y: its columns of the
+// output (forward) or of the output's gradient (backward, read only); backward: t [n, r] scratch, dA and dB.
+struct LoraTarget {
+  const void* x; size_t ldx;
+  void* y; size_t ldy;
+  const void *A, *B;
+  int in, out;
+  float *u, *t, *dA, *dB;
+};
+constexpr int LORA_GROUP = 3;      // targets that share a projection
+// one product of those kernels' batches: out / G / Y of a long index i < n_long and a rank index (see kernels_generic.hip)
+struct LoraProduct {
+  const void* X; size_t ldx;
+  const void* S; size_t s_i, s_j;
+  float* U;
+  void* Y; size_t ldy;
+  float* G; size_t g_i, g_j;
+  int n_long;
+};
+struct LoraBatch { LoraProduct p[2 * LORA_GROUP]; int count; };
+int32_t launch_lora_apply(const LoraTarget* tg, int count, int n, int r, float scale, int dtype, const int32_t* row_idx, hipStream_t s);
+int32_t launch_lora_bwd(const LoraTarget* tg, int count, void* dx, size_t lddx, int n, int r, float scale, int dtype,
+                        hipStream_t s, bool relu = false);
 int32_t launch_relu_mask(float* u, float* t, size_t count, hipStream_t s);
 
 int32_t launch_attention_generic(const flexco_layer_cfg& c, const flexco_maps& m, const void* q, size_t ldq,
