@@ -186,19 +186,35 @@ __global__ __launch_bounds__(256) void attn_merge128_kernel(const int32_t* __res
   const int c = (t - tile_tok0[tile]) * group + h % group;
   const size_t idx0 = ((size_t)tile_part0[tile] * nkv + kvh) * cols_per_tile + c;
   const size_t step = (size_t)nkv * cols_per_tile;         // from one split's row to the next
+  // The chain of loads is what this kernel's time is: U splits' at once (past the last one they repeat it), added in
+  // split order.  The first U splits' maxima are kept for the second pass.
+  constexpr int U = 8;
   float M = -INFINITY;
-  for (int s = 0; s < nsplit; ++s) M = fmaxf(M, part_ml[(idx0 + s * step) * 2]);
+  float2 first[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) first[u] = *reinterpret_cast<const float2*>(part_ml + (idx0 + min(u, nsplit - 1) * step) * 2);
+#pragma unroll
+  for (int u = 0; u < U; ++u) M = fmaxf(M, first[u].x);
+  for (int s = U; s < nsplit; ++s) M = fmaxf(M, part_ml[(idx0 + s * step) * 2]);
   float L = 0.f;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  for (int s = 0; s < nsplit; ++s) {
-    const size_t idx = idx0 + s * step;
-    const float ms = part_ml[idx * 2];
-    if (ms > -INFINITY) {
-      const float w = __expf(ms - M);
-      L += part_ml[idx * 2 + 1] * w;
-      const f32x4 a = *reinterpret_cast<const f32x4*>(part_acc + idx * d + 4 * ln);
+  for (int s = 0; s < nsplit; s += U) {
+    float2 ml[U];
+    f32x4 a[U];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[j] += a[j] * w;
+    for (int u = 0; u < U; ++u) {
+      const size_t idx = idx0 + min(s + u, nsplit - 1) * step;
+      ml[u] = s == 0 ? first[u] : *reinterpret_cast<const float2*>(part_ml + idx * 2);
+      a[u] = *reinterpret_cast<const f32x4*>(part_acc + idx * d + 4 * ln);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (s + u < nsplit && ml[u].x > -INFINITY) {        // (the sums of a split without a visible key are not written)
+        const float w = __expf(ml[u].x - M);
+        L += ml[u].y * w;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[j] += a[u][j] * w;
+      }
     }
   }
   const float inv = 1.0f / L;

@@ -474,7 +474,17 @@ struct Adapters {
 int32_t forward_projection(const flexco_layer_cfg& c, const Adapters& ad, const flexco_maps& m, const void* x,
                            int K, const void* W, const void* bias, const void* res, size_t ldr, void* y, int N,
                            const int* targets, const int* col0, int n_targets, FwdWs& k,
-                           const flexco_ft_state* ft, hipStream_t s, GluOut* glu = nullptr) {
+                           const flexco_ft_state* ft, hipStream_t s, GluOut* glu = nullptr, SplitSums* left = nullptr) {
+  // left: the caller's next kernel can add the product's partial sums, bias and residual itself; where the product is cut
+  // over K (left->splits > 1) they stay in k.gemm_part for it and y is not written
+  if (left) *left = SplitSums{nullptr, 1};
+  const bool leave = left && c.dtype == FLEXCO_BF16 && k.gemm_part && gemm_forward_splits(m.T, N, K, k.gemm_part_elems) > 1;
+  auto cut_gemm = [&](const GemmExt* ext) {
+    const int32_t rc = launch_gemm(x, W, y, nullptr, nullptr, m.T, N, K, K, K, N, ldr, false, c.dtype, s, ext, k.gemm_part,
+                                   k.gemm_part_elems, &left->splits);
+    left->part = k.gemm_part;
+    return rc != FLEXCO_OK || left->splits > 1 ? rc : fail(FLEXCO_EINVAL, "forward projection: planned cut over K not taken");
+  };
   int act[3], nact = 0;
   for (int i = 0; i < n_targets; ++i)
     if (m.n_lora > 0 && has_target(c, targets[i])) act[nact++] = i;
@@ -519,14 +529,22 @@ int32_t forward_projection(const flexco_layer_cfg& c, const Adapters& ad, const 
       if (rc != FLEXCO_EUNSUPPORTED) return rc;
       clear_error();
     }
-    int32_t rc = launch_gemm(x, W, y, bias, res, T, N, K, K, K, N, ldr, false, dt, s, &ext, k.gemm_part, k.gemm_part_elems);
+    int32_t rc = leave ? cut_gemm(&ext)
+                       : launch_gemm(x, W, y, bias, res, T, N, K, K, K, N, ldr, false, dt, s, &ext, k.gemm_part, k.gemm_part_elems);
     if (rc != FLEXCO_EUNSUPPORTED) return rc;
     clear_error();   // e.g. a target boundary inside a 32-column fragment: run the bypass as separate kernels
+    if (left) *left = SplitSums{nullptr, 1};
   }
   if (glu && nact == 0) {
     const int32_t rc = gated_gemm(c, m, x, K, W, N / 2, nullptr, ft, *glu, s);
     if (rc != FLEXCO_EUNSUPPORTED) return rc;
     clear_error();
+  }
+  if (leave && nact == 0) {
+    const int32_t rc = cut_gemm(nullptr);
+    if (rc != FLEXCO_EUNSUPPORTED) return rc;
+    clear_error();
+    *left = SplitSums{nullptr, 1};
   }
   FLEXCO_TRY(launch_gemm(x, W, y, bias, res, T, N, K, K, K, N, ldr, false, dt, s, nullptr, k.gemm_part, k.gemm_part_elems));
   // more adapters than the folded path takes: the backward pass (which folds whenever it can) still
@@ -979,6 +997,7 @@ static int32_t layer_forward_impl(const flexco_layer_cfg* cfg, const flexco_base
 
   // attention side
   lend_gu(true);
+  SplitSums qkv_sums{nullptr, 1}, o_sums{nullptr, 1};
   // (the finetune window's rows of x, x2, the attention output and its log-sum-exp - what graph pruning keeps,
   // Alg. 1 - are written to the sequence's state by the kernels that read or produce them anyway)
   const size_t p0 = m.ft_pos0;
@@ -986,7 +1005,10 @@ static int32_t layer_forward_impl(const flexco_layer_cfg* cfg, const flexco_base
                     m.n_ft));
   {
     const int tg[3] = {FLEXCO_T_Q, FLEXCO_T_K, FLEXCO_T_V}, c0[3] = {0, qd, qd + kd};
-    FLEXCO_TRY(forward_projection(c, ad, m, k.h, H, w->wqkv, w->bqkv, nullptr, 0, k.qkv, qkvd, tg, c0, 3, k, ft, s));
+    // (few tokens: the rotation adds the projection's partial sums; (IA)^3 scales the rows in between)
+    const bool sums_ok = dt == FLEXCO_BF16 && !ia3 && aligned16(w->bqkv) && rope_append_vec(c, k.qkv, *pool, ft ? ft->q_cache : nullptr);
+    FLEXCO_TRY(forward_projection(c, ad, m, k.h, H, w->wqkv, w->bqkv, nullptr, 0, k.qkv, qkvd, tg, c0, 3, k, ft, s, nullptr,
+                                  sums_ok ? &qkv_sums : nullptr));
   }
   if (ia3 && m.n_lora > 0) {   // keys and values of the adapter's rows, scaled before the rotation and the append
     Ia3ScaleArgs sa;
@@ -998,17 +1020,23 @@ static int32_t layer_forward_impl(const flexco_layer_cfg* cfg, const flexco_base
     EW(launch_ia3_scale_rows(k.qkv, qkvd, m.lora_tok, m.n_lora, sa, dt, s));
   }
   EW(launch_rope_append(c, k.qkv, m.tok_pos, m.slot, *pool, T, m.ft_tok0, m.n_ft, m.ft_pos0,
-                        ft ? ft->q_cache : nullptr, s));
+                        ft ? ft->q_cache : nullptr, s, &qkv_sums, w->bqkv));
   const AttnKeep keep{ft ? (void*)boff(ft->saved_attn, p0 * qd, e) : nullptr, ft ? ft->lse + p0 * c.n_q_heads : nullptr,
                       m.ft_tok0, ft ? m.n_ft : 0};
   FLEXCO_TRY(run_attention(c, m, k.qkv, qkvd, *pool, k.attn, qd, nullptr, k.part_ml, k.part_acc, s, &keep));
   {
     const int tg[1] = {FLEXCO_T_O}, c0[1] = {0};
-    FLEXCO_TRY(forward_projection(c, ad, m, k.attn, qd, w->wo, nullptr, x_in, H, k.x2, H, tg, c0, 1, k, ft, s));
+    // (its partial sums and the residual are added by the norm that reads it next)
+    const bool sums_ok = dt == FLEXCO_BF16 && H % 8 == 0 && H <= 8192 && aligned16(w->g2) && aligned16(ft ? ft->saved_x2 : nullptr);
+    FLEXCO_TRY(forward_projection(c, ad, m, k.attn, qd, w->wo, nullptr, x_in, H, k.x2, H, tg, c0, 1, k, ft, s, nullptr,
+                                  sums_ok ? &o_sums : nullptr));
   }
   // MLP side
-  EW(launch_rmsnorm(k.x2, w->g2, k.h, T, H, c.rms_eps, dt, s, ft ? (void*)boff(ft->saved_x2, p0 * H, e) : nullptr, m.ft_tok0,
-                    m.n_ft));
+  void* const keep_x2 = ft ? (void*)boff(ft->saved_x2, p0 * H, e) : nullptr;
+  if (o_sums.splits > 1)
+    EW(launch_rmsnorm_sums(o_sums, x_in, k.x2, w->g2, k.h, T, H, c.rms_eps, s, keep_x2, m.ft_tok0, m.n_ft));
+  else
+    EW(launch_rmsnorm(k.x2, w->g2, k.h, T, H, c.rms_eps, dt, s, keep_x2, m.ft_tok0, m.n_ft));
   GluOut glu{k.act, (size_t)F, false};
   lend_gu(false);
   {

@@ -103,6 +103,8 @@ int32_t launch_gemm_f32_mfma(const void* A, const void* W, void* C, const void* 
 struct GemmLaunchStep { int bm, bn, cols, splits, stages; };
 struct GemmLaunchPlan { int n; GemmLaunchStep step[2]; };
 GemmLaunchPlan plan_gemm_mfma(int M, int N, int K, bool trans_w, size_t part_elems);
+// ranges K is cut into for a forward product, whatever its tiles
+int gemm_forward_splits(int M, int N, int K, size_t part_elems);
 // > 0: the product runs on 256 x 256 tiles with K in that many ranges of whole stages instead of by the plan
 int plan_gemm_k_ranges(int M, int N, int K, bool trans_w, size_t part_elems);
 // bf16 MFMA path; returns FLEXCO_EUNSUPPORTED (without launching) for shapes it does not cover
@@ -121,6 +123,12 @@ int32_t launch_lora_outer_batch(const LoraOuterArgs& a, hipStream_t s);
 int32_t launch_lora_outer_bf16(const void* X, size_t ldx, const float* U, float* G, size_t g_i, size_t g_j, int n,
                                int n_long, int r, float scale, hipStream_t s);
 
+// Partial sums a forward product leaves for the kernel that reads it next: part[split][rows][width], fp32.  That kernel
+// adds them in split order, then the bias or residual row, and rounds once, as the reduction launch would have.
+struct SplitSums { const float* part; int splits; };
+// x = sums + res (width H), h = rmsnorm(x); bf16, H a multiple of 8, 16-byte aligned pointers
+int32_t launch_rmsnorm_sums(const SplitSums& sums, const void* res, void* x, const void* g, void* h, int T, int H, float eps,
+                            hipStream_t s, void* save, int save_row0, int save_rows);
 int32_t launch_rmsnorm(const void* x, const void* g, void* h, int T, int H, float eps, int dtype, hipStream_t s,
                        void* save = nullptr, int save_row0 = 0, int save_rows = 0);
 // The LoRA backward's rank-r products t_z = dy_z B_z (Sec. 4.1 bypass form) of up to three targets whose dy_z are
@@ -143,7 +151,9 @@ int32_t launch_rmsnorm_bwd(const void* x, const void* g, const void* dh, const v
 int32_t launch_lora_row_t(const void* dy, size_t lddy, int n, int width, const RowLoraT& lt, hipStream_t s);
 int32_t launch_rope_append(const flexco_layer_cfg& c, void* qkv, const int32_t* tok_pos, const int32_t* slot,
                            const flexco_kv_pool& pool, int T, int ft_tok0, int n_ft, int ft_pos0, void* q_cache,
-                           hipStream_t s);
+                           hipStream_t s, const SplitSums* sums = nullptr, const void* bias = nullptr);
+// sums: the qkv rows still lie as partial sums (bf16, rope_append_vec); q is then written to qkv, k and v to the pool only
+bool rope_append_vec(const flexco_layer_cfg& c, const void* qkv, const flexco_kv_pool& pool, const void* q_cache);
 int32_t launch_rope_bwd_pack(const flexco_layer_cfg& c, const void* dq, const float* dk_rows, const float* dv_rows,
                              void* dqkv, int win_start, int n, hipStream_t s, const RowLoraT* lt = nullptr);
 int32_t launch_swiglu(const void* gu, void* act, int T, int F, int dtype, hipStream_t s);

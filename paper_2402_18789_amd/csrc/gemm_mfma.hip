@@ -1051,6 +1051,12 @@ GemmLaunchPlan plan_gemm_mfma(int M, int N, int K, bool trans_w, size_t part_ele
   return pl;
 }
 
+int gemm_forward_splits(int M, int N, int K, size_t part_elems) {
+  if (M <= THIN_ROWS) return thin_splits(M, N, K, part_elems);
+  const int ranges = plan_gemm_k_ranges(M, N, K, false, part_elems);
+  return ranges ? ranges : plan_gemm_mfma(M, N, K, false, part_elems).step[0].splits;
+}
+
 // The kernels address a tile's rows by 32-bit byte offsets from its first.
 static bool offsets_fit(size_t ld, size_t rows) { return ld <= 0xffff0000u / 2 / rows; }
 
@@ -1067,11 +1073,15 @@ int32_t launch_gemm_mfma(const void* A, const void* W, void* C, const void* bias
   GemmExt ext;
   if (ext_in) ext = *ext_in; else ext.n = 0;
   if (!ext_fits(ext, trans_w, N)) return FLEXCO_EUNSUPPORTED;
-  if (!trans_w && M <= THIN_ROWS)
-    return launch_cfg<THIN_ROWS, 128, false, false, 6>(A, W, C, bias, residual, M, N, K, lda, ldw, ldc, ldr, ext, s, timer_id, part,
-                                                       thin_splits(M, N, K, part ? part_elems : 0));
   // splits_out: the caller's next kernel adds the partial sums itself (part[split][M][N], in split order) and
   // the reduction launch is left out; bias and residual are then not applied
+  if (!trans_w && M <= THIN_ROWS) {
+    const int sp = thin_splits(M, N, K, part ? part_elems : 0);
+    const bool leave = splits_out && sp > 1 && !bias && !residual;
+    if (leave) *splits_out = sp;
+    return launch_cfg<THIN_ROWS, 128, false, false, 6>(A, W, C, bias, residual, M, N, K, lda, ldw, ldc, ldr, ext, s, timer_id, part, sp,
+                                                       true, nullptr, leave);
+  }
   const int ranges = plan_gemm_k_ranges(M, N, K, trans_w, part ? part_elems : 0);
   if (ranges) {
     const bool leave = splits_out && ranges > 1 && !bias && !residual;
@@ -1091,9 +1101,12 @@ int32_t launch_gemm_mfma(const void* A, const void* W, void* C, const void* bias
     return launch_cfg<128, 128, true>(A, W, C, bias, residual, M, N, K, lda, ldw, ldc, ldr, ext, s, timer_id, part, st.splits, true,
                                       nullptr, leave);
   }
-  if (pl.step[0].splits > 1)
+  if (pl.step[0].splits > 1) {
+    const bool leave = splits_out && !bias && !residual;
+    if (leave) *splits_out = pl.step[0].splits;
     return launch_cfg<128, 128, false>(A, W, C, bias, residual, M, N, K, lda, ldw, ldc, ldr, ext, s, timer_id, part,
-                                       pl.step[0].splits);
+                                       pl.step[0].splits, true, nullptr, leave);
+  }
   int c0 = 0;
   for (int i = 0; i < pl.n; ++i) {
     const GemmLaunchStep& st = pl.step[i];

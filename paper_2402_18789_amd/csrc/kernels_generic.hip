@@ -188,6 +188,77 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const T* __restrict__ x, c
   }
 }
 
+// x = sums + res, h = rmsnorm(x), bf16: the output projection's partial sums added by the norm that reads the product next
+// (a launch of its own cost 4.7 us, as much as this kernel).  Eight wavefronts per row, everything a thread needs - the
+// partial sums, the residual, the gain - on its way at once, the row in registers between the two passes.
+constexpr int NORM_SUMS_VECS = 4;                 // 16-byte pieces per thread: rows of up to 512 x 8 x 4 elements
+__global__ __launch_bounds__(512) void rmsnorm_sums_kernel(SplitSums sums, const bf16_t* __restrict__ res, bf16_t* __restrict__ x,
+                                                           const bf16_t* __restrict__ g, bf16_t* __restrict__ h, int H, float eps,
+                                                           bf16_t* __restrict__ save, int save_row0, int save_rows) {
+  __shared__ float red[8];
+  const size_t row = blockIdx.x, stride = (size_t)gridDim.x * H;
+  bf16_t* sv = (save && (int)row >= save_row0 && (int)row < save_row0 + save_rows) ? save + (row - save_row0) * H : nullptr;
+  bf16x8 v[NORM_SUMS_VECS];
+  float ss = 0.f;
+#pragma unroll
+  for (int q = 0; q < NORM_SUMS_VECS; ++q) {
+    const int i = (q * 512 + threadIdx.x) * 8;
+    if (i < H) {
+      const float* p = sums.part + row * H + i;
+      const bf16x8 r8 = *reinterpret_cast<const bf16x8*>(res + row * H + i);
+      float t[8];
+      {
+        const f32x4 a = *reinterpret_cast<const f32x4*>(p), b = *reinterpret_cast<const f32x4*>(p + 4);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { t[j] = a[j]; t[4 + j] = b[j]; }
+      }
+      int sp = 1;
+      for (; sp + 3 <= sums.splits; sp += 3) {      // three splits in flight, added in split order
+        f32x4 a[3], b[3];
+#pragma unroll
+        for (int u = 0; u < 3; ++u) {
+          a[u] = *reinterpret_cast<const f32x4*>(p + (sp + u) * stride);
+          b[u] = *reinterpret_cast<const f32x4*>(p + (sp + u) * stride + 4);
+        }
+#pragma unroll
+        for (int u = 0; u < 3; ++u)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) { t[j] += a[u][j]; t[4 + j] += b[u][j]; }
+      }
+      for (; sp < sums.splits; ++sp) {
+        const f32x4 a = *reinterpret_cast<const f32x4*>(p + sp * stride), b = *reinterpret_cast<const f32x4*>(p + sp * stride + 4);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { t[j] += a[j]; t[4 + j] += b[j]; }
+      }
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        v[q][j] = (bf16_t)(t[j] + (float)r8[j]);
+        ss += (float)v[q][j] * (float)v[q][j];
+      }
+      *reinterpret_cast<bf16x8*>(x + row * H + i) = v[q];
+      if (sv) *reinterpret_cast<bf16x8*>(sv + i) = v[q];
+    }
+  }
+  ss = wave_sum(ss);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
+  __syncthreads();
+  ss = 0.f;
+#pragma unroll
+  for (int w = 0; w < 8; ++w) ss += red[w];
+  const float rstd = 1.0f / sqrtf(ss / H + eps);
+#pragma unroll
+  for (int q = 0; q < NORM_SUMS_VECS; ++q) {
+    const int i = (q * 512 + threadIdx.x) * 8;
+    if (i < H) {
+      const bf16x8 g8 = *reinterpret_cast<const bf16x8*>(g + i);
+      bf16x8 o;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) o[j] = (bf16_t)((float)v[q][j] * rstd * (float)g8[j]);
+      *reinterpret_cast<bf16x8*>(h + row * H + i) = o;
+    }
+  }
+}
+
 // v[0..N) = the N consecutive elements at `idx` of a product whose split-K partial sums still lie in
 // part[split][stride]: added in split order and rounded to the storage type, exactly as the reduction
 // kernel would have written them.
@@ -437,17 +508,19 @@ __device__ inline void rope_cos_sin(const RopeFreq& f, int i, int pos, float* c,
 // --------------------------------------------------------------------------------------
 // VEC: a thread rotates Vec<T>::N neighbouring pairs of one head with 16-byte accesses (head_dim / 2 a
 // multiple of the vector width, every pointer 16-byte aligned); same arithmetic, same results.
-template <typename T, bool VEC>
-__global__ __launch_bounds__(256) void rope_append_kernel(T* __restrict__ qkv, const int32_t* __restrict__ tok_pos,
+// SUMS (with VEC): the rows lie as the projection's partial sums; q is written to qkv, k and v go to the pool only.
+template <typename T, bool VEC, bool SUMS = false>
+__global__ __launch_bounds__(SUMS ? 512 : 256) void rope_append_kernel(T* __restrict__ qkv, const int32_t* __restrict__ tok_pos,
                                                           const int32_t* __restrict__ slot, T* __restrict__ kp,
                                                           T* __restrict__ vp, int nq, int nkv, int d, int ps,
                                                           RopeFreq freq, int ft_tok0, int n_ft, int ft_pos0,
-                                                          T* __restrict__ q_cache) {
+                                                          T* __restrict__ q_cache, SplitSums sums, const T* __restrict__ bias) {
   extern __shared__ float cs[];   // cos[d/2], sin[d/2]
+  constexpr int THREADS = SUMS ? 512 : 256;
   const int t = blockIdx.x;
   const int pos = tok_pos[t];
   const int half = d >> 1;
-  for (int i = threadIdx.x; i < half; i += 256) rope_cos_sin(freq, i, pos, &cs[i], &cs[half + i]);
+  for (int i = threadIdx.x; i < half; i += THREADS) rope_cos_sin(freq, i, pos, &cs[i], &cs[half + i]);
   // the run of tokens this token's v row is written with (below): its first token and its length.  One lane per
   // neighbouring token looks at that token's slot and its predecessor's, all at once (a chain of dependent loads
   // along the run would cost more than the kernel's whole run time)
@@ -486,12 +559,54 @@ __global__ __launch_bounds__(256) void rope_append_kernel(T* __restrict__ qkv, c
   if constexpr (VEC) {
     constexpr int N = Vec<T>::N;
     const int hv = half / N;
-    for (int idx = threadIdx.x; idx < (nq + nkv) * hv; idx += 256) {
+    // P pieces of N elements of a token's row, `gap` elements apart.  Partial sums: those of four splits at a time are on
+    // their way together (past the last split it is read again and left out), added in split order.
+    auto load = [&](int token, int col, auto& v, int gap) {
+      constexpr int P = sizeof(v) / (N * sizeof(float));
+      if constexpr (SUMS) {
+        constexpr int U = 4;
+        const size_t stride = (size_t)gridDim.x * qkv_dim;
+        const float* p = sums.part + (size_t)token * qkv_dim + col;
+        float b[P][N] = {};
+        if (bias)
+#pragma unroll
+          for (int q = 0; q < P; ++q) Vec<T>::load(bias + col + q * gap, b[q]);
+#pragma unroll
+        for (int q = 0; q < P; ++q)
+#pragma unroll
+          for (int e = 0; e < N; ++e) v[q][e] = 0.f;
+        for (int sp = 0; sp < sums.splits; sp += U) {
+          f32x4 t4[U][P][N / 4];
+#pragma unroll
+          for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int q = 0; q < P; ++q)
+#pragma unroll
+              for (int e4 = 0; e4 < N / 4; ++e4)
+                t4[u][q][e4] = *reinterpret_cast<const f32x4*>(p + min(sp + u, sums.splits - 1) * stride + q * gap + 4 * e4);
+#pragma unroll
+          for (int u = 0; u < U; ++u)
+            if (sp + u < sums.splits)
+#pragma unroll
+              for (int q = 0; q < P; ++q)
+#pragma unroll
+                for (int e = 0; e < N; ++e) v[q][e] += t4[u][q][e / 4][e % 4];
+        }
+#pragma unroll
+        for (int q = 0; q < P; ++q)
+#pragma unroll
+          for (int e = 0; e < N; ++e) v[q][e] = (float)(T)(v[q][e] + b[q][e]);
+      } else {
+#pragma unroll
+        for (int q = 0; q < P; ++q) Vec<T>::load(qkv + (size_t)token * qkv_dim + col + q * gap, v[q]);
+      }
+    };
+    for (int idx = threadIdx.x; idx < (nq + nkv) * hv; idx += THREADS) {
       const int head = idx / hv, i = (idx % hv) * N;
       T* hp = row + head * d;
-      float lo[N], hi[N], rlo[N], rhi[N];
-      Vec<T>::load(hp + i, lo);
-      Vec<T>::load(hp + half + i, hi);
+      float x[2][N], rlo[N], rhi[N];
+      load(t, head * d + i, x, half);
+      const float (&lo)[N] = x[0], (&hi)[N] = x[1];
 #pragma unroll
       for (int j = 0; j < N; ++j) {
         const float c = cs[i + j], sn = cs[half + i + j];
@@ -525,14 +640,19 @@ __global__ __launch_bounds__(256) void rope_append_kernel(T* __restrict__ qkv, c
     const int nv = nkv * d / N;                       // 16-byte pieces of a v row
     const int v_lo = (int)((long)nv * j / len), v_hi = (int)((long)nv * (j + 1) / len);
     const bool whole = len == RUN && ps % N == 0;
-    const T* vrow0 = qkv + (size_t)t0 * qkv_dim + (nq + nkv) * d;
-    for (int vi = v_lo + threadIdx.x; vi < v_hi; vi += 256) {
+    const int v0 = (nq + nkv) * d;
+    for (int vi = v_lo + THREADS - 1 - threadIdx.x; vi < v_hi; vi += THREADS) {      // (the threads with the least to rotate first)
       const int idx = vi * N, kh = idx / d, i = idx % d;
       T* dst = vp + ((page * nkv + kh) * (size_t)d + i) * ps + pip0;
       if (whole) {        // (all sixteen loads in flight before the first store)
         float rows[RUN][N];
 #pragma unroll
-        for (int jj = 0; jj < RUN; ++jj) Vec<T>::load(vrow0 + (size_t)jj * qkv_dim + idx, rows[jj]);
+        for (int jj = 0; jj < RUN; ++jj) {
+          float v[1][N];
+          load(t0 + jj, v0 + idx, v, 0);
+#pragma unroll
+          for (int c = 0; c < N; ++c) rows[jj][c] = v[0][c];
+        }
 #pragma unroll
         for (int c = 0; c < N; ++c) {
           float col[RUN];
@@ -543,10 +663,10 @@ __global__ __launch_bounds__(256) void rope_append_kernel(T* __restrict__ qkv, c
         }
       } else {
         for (int jj = 0; jj < len; ++jj) {
-          float v[N];
-          Vec<T>::load(vrow0 + (size_t)jj * qkv_dim + idx, v);
+          float v[1][N];
+          load(t0 + jj, v0 + idx, v, 0);
 #pragma unroll
-          for (int c = 0; c < N; ++c) dst[(size_t)c * ps + jj] = (T)v[c];
+          for (int c = 0; c < N; ++c) dst[(size_t)c * ps + jj] = (T)v[0][c];
         }
       }
     }
@@ -1104,6 +1224,16 @@ int32_t launch_rmsnorm(const void* x, const void* g, void* h, int T_, int H, flo
   return post_launch("rmsnorm");
 }
 
+int32_t launch_rmsnorm_sums(const SplitSums& sums, const void* res, void* x, const void* g, void* h, int T_, int H, float eps,
+                            hipStream_t s, void* save, int save_row0, int save_rows) {
+  if (T_ == 0) return FLEXCO_OK;
+  if (H > 512 * 8 * NORM_SUMS_VECS || !vec_ok(FLEXCO_BF16, H, {sums.part, res, x, g, h, save}))
+    return fail(FLEXCO_EUNSUPPORTED, "rmsnorm_sums: not covered");
+  hipLaunchKernelGGL(rmsnorm_sums_kernel, dim3(T_), dim3(512), 0, s, sums, (const bf16_t*)res, (bf16_t*)x, (const bf16_t*)g, (bf16_t*)h,
+                     H, eps, (bf16_t*)save, save_row0, save ? save_rows : 0);
+  return post_launch("rmsnorm_sums");
+}
+
 int32_t launch_rmsnorm_bwd(const void* x, const void* g, const void* dh, const void* add, void* dx, int T_, int H,
                            float eps, int dtype, hipStream_t s, void* hn, const float* dh_part, int splits,
                            const RowLoraT* lt_in) {
@@ -1166,18 +1296,29 @@ static int32_t rope_freq(const flexco_layer_cfg& c, RopeFreq* out) {
   return FLEXCO_OK;
 }
 
+bool rope_append_vec(const flexco_layer_cfg& c, const void* qkv, const flexco_kv_pool& pool, const void* q_cache) {
+  return c.head_dim % 2 == 0 && vec_ok(c.dtype, c.head_dim / 2, {qkv, pool.k_pages, pool.v_pages, q_cache});
+}
+
 int32_t launch_rope_append(const flexco_layer_cfg& c, void* qkv, const int32_t* tok_pos, const int32_t* slot,
                            const flexco_kv_pool& pool, int T_, int ft_tok0, int n_ft, int ft_pos0, void* q_cache,
-                           hipStream_t s) {
+                           hipStream_t s, const SplitSums* sums, const void* bias) {
   if (T_ == 0) return FLEXCO_OK;
   const size_t shm = sizeof(float) * c.head_dim;
   RopeFreq freq;
   FLEXCO_TRY(rope_freq(c, &freq));
-  const bool vec = c.head_dim % 2 == 0 && vec_ok(c.dtype, c.head_dim / 2, {qkv, pool.k_pages, pool.v_pages, q_cache});
+  const bool vec = rope_append_vec(c, qkv, pool, q_cache);
+  if (sums && sums->splits > 1) {
+    if (!vec || c.dtype != FLEXCO_BF16 || !aligned16(bias)) return fail(FLEXCO_EUNSUPPORTED, "rope_append: partial sums not covered");
+    hipLaunchKernelGGL((rope_append_kernel<bf16_t, true, true>), dim3(T_), dim3(512), shm, s, (bf16_t*)qkv, tok_pos, slot,
+                       (bf16_t*)pool.k_pages, (bf16_t*)pool.v_pages, c.n_q_heads, c.n_kv_heads, c.head_dim, c.page_size, freq,
+                       ft_tok0, n_ft, ft_pos0, (bf16_t*)q_cache, *sums, (const bf16_t*)bias);
+    return post_launch("rope_append");
+  }
   DISPATCH_TV(c.dtype, vec, hipLaunchKernelGGL((rope_append_kernel<T, VEC>), dim3(T_), dim3(256), shm, s, (T*)qkv, tok_pos,
                                                slot, (T*)pool.k_pages, (T*)pool.v_pages, c.n_q_heads, c.n_kv_heads,
                                                c.head_dim, c.page_size, freq, ft_tok0, n_ft, ft_pos0,
-                                               (T*)q_cache));
+                                               (T*)q_cache, SplitSums{}, (const T*)nullptr));
   return post_launch("rope_append");
 }
 

@@ -1,0 +1,38 @@
+"""Layers on few tokens, where a projection leaves its partial sums to the kernel that reads it next (the rotation, the
+second norm), and the merge of many key splits (run with -m gpu on an MI355X)."""
+import numpy as np
+import pytest
+import torch
+
+from workload import gen, CONFIGS
+
+pytestmark = pytest.mark.gpu
+
+if torch.cuda.is_available():
+    import paper_2402_18789_amd.binding as B
+    from gpu_common import TOL, assert_close
+    from test_gpu_parity import attention_case, run_layer_case
+
+# K of 32 stages: three ranges of it per projection at up to 64 tokens
+WIDE = CONFIGS["c2_llama8b_layer"].with_(name="wide_bf16", hidden=2048, n_q_heads=16, n_kv_heads=4, head_dim=128, ffn=2816,
+                                         qkv_bias=True, lora_targets=("q", "v", "o", "gate", "down"))
+
+
+# 30 tokens a pass (64-row tiles), then 130 (128-row tiles)
+@pytest.mark.parametrize("chunk,window", [(12, 14), (60, 66)])
+def test_layer_partial_sums_left_to_the_next_kernel(chunk, window):
+    print(f"layer of few tokens: prefill chunk {chunk}, window {window}", flush=True)
+    b = gen.batch_scaled(17, 4, 3, 90, [(0, chunk, 2 * chunk)], [(0, window, 2 * window)])
+    assert b.n_tokens <= 256
+    run_layer_case(WIDE, b, ft_window=window, prefill_chunk=chunk, bwd_windows=[window, window], seed=17)
+
+
+# (split: pages of 16 keys) contexts of one split, then of up to six, then of 1, 2, 8, 9 and 12
+@pytest.mark.parametrize("split", [24, 4, 2])
+def test_attention_merge_of_many_splits(split):
+    print(f"attention, key splits of {split} pages", flush=True)
+    cfg = WIDE
+    batch = gen.mixed_batch(cfg.page_size, 4, decode_ctx=(1, 17, 256, 270, 384), prefill=[(0, 33, 33), (270, 18, 288)], finetune=[(50, 21, 71)])
+    out, a_o, lse, lse_o = attention_case(cfg, batch, split)
+    assert_close("attention out", out, a_o, TOL[cfg.dtype])
+    assert float(np.max(np.abs(lse - lse_o))) <= 2e-2
