@@ -155,11 +155,15 @@ __global__ __launch_bounds__(64 * SP) void attn_bwd_dq_mfma_kernel(BwdArgs a) {
   //    transposing read then sit 128 bytes apart (mod 256).
   const int k_rin = lane >> 4, k_pc = lane & 15;
   const int v_lc = lane ^ (((lane >> 4) & 1) << 3);
-  int page_nxt;
+  // The next step's page id is asked for a step ahead and read when that step's loads are issued.  It is the same for all
+  // lanes, and told so the compiler turns it into a scalar at once, i.e. waits for it - and with it for the eight tile
+  // loads issued before it - right behind the request.  So its address goes through a register it knows nothing about.
+  int page_nxt, lane_zero;
+  asm volatile("v_mov_b32 %0, 0" : "=v"(lane_zero));
 #define FLEXCO_ISSUE(kb_, vb_, it_, page_)                                                            \
   {                                                                                                   \
     const int slot_ = SP * (it_) + wave;                                                              \
-    const size_t pb_ = ((size_t)(page_) * a.nkv + kvh);                                               \
+    const size_t pb_ = ((size_t)__builtin_amdgcn_readfirstlane(page_) * a.nkv + kvh);                 \
     _Pragma("unroll") for (int q = 0; q < 4; ++q) {                                                   \
       const int key_ = 4 * q + k_rin;                                                                 \
       const int keff_ = slot_ * PS + key_ < a.l ? key_ : last_key;                                    \
@@ -228,7 +232,7 @@ __global__ __launch_bounds__(64 * SP) void attn_bwd_dq_mfma_kernel(BwdArgs a) {
     FLEXCO_WAIT_ALL_BARRIER                                                                           \
     if ((it_) + 1 < nit) {                                                                            \
       FLEXCO_ISSUE(kn_, vn_, (it_) + 1, page_nxt)                                                     \
-      page_nxt = a.pages[min(SP * ((it_) + 2) + wave, last_page)];                                    \
+      page_nxt = a.pages[min(SP * ((it_) + 2) + wave, last_page) + lane_zero];                        \
     }                                                                                                 \
     FLEXCO_DQ_COMPUTE(kb_, vb_, it_, MASKED_)                                                         \
   }
@@ -236,7 +240,7 @@ __global__ __launch_bounds__(64 * SP) void attn_bwd_dq_mfma_kernel(BwdArgs a) {
   {
     const int page0 = a.pages[min(wave, last_page)];
     FLEXCO_ISSUE(kb0, vb0, 0, page0)
-    page_nxt = a.pages[min(SP + wave, last_page)];
+    page_nxt = a.pages[min(SP + wave, last_page) + lane_zero];
   }
   // leading steps whose two pages of this wavefront (2 kh, 2 kh + 1 of the step's SP) end at or before the position
   // of the wavefront's first row, in pairs (the two buffer sets); every form of a step has the one barrier, so the
