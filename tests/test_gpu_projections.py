@@ -67,3 +67,11 @@ def test_input_gradient_in_unequal_ranges(n, H, V):
     print(f"loss head n={n} H={H} V={V}: {r} ranges", flush=True)
     assert r > 1 and (V // 64) % r != 0
     run_loss("bf16", n, H, V, seed=3)
+
+
+# rows of logits that a block holds in registers: 3 and 8, 9 and 16, 17 and 19 pieces of 8192 (the last ragged or whole),
+# and the first length past them
+@pytest.mark.parametrize("V", [16392, 65536, 65544, 131072, 131080, 155648, 155656])
+def test_loss_rows(V):
+    print(f"loss head V={V}", flush=True)
+    run_loss("bf16", 5, 256, V, seed=4, ignore=(1, 4))
