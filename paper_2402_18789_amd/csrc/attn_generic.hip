@@ -234,22 +234,12 @@ __global__ __launch_bounds__(256) void attn_merge128_kernel(const int32_t* __res
 // window backward (Sec. 6.1): queries = window rows at positions win_start + i, keys/values
 // = cached rows [0, l).  P is recomputed from Q, K and the stored log-sum-exp.
 // ------------------------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(64) void attn_delta_kernel(const T* __restrict__ out, const T* __restrict__ dout,
-                                                        float* __restrict__ delta, int nq, int d) {
-  const size_t i = blockIdx.x;
-  const int h = blockIdx.y;
-  float s = 0.f;
-  for (int dd = threadIdx.x; dd < d; dd += 64)
-    s += ld(out + (i * nq + h) * d + dd) * ld(dout + (i * nq + h) * d + dd);
-  s = wsum(s);
-  if (threadIdx.x == 0) delta[i * nq + h] = s;
-}
-
+// (delta = rowsum(dO (.) O) of a row is computed here and left for the dK / dV kernel)
 template <typename T>
 __global__ __launch_bounds__(64) void attn_bwd_dq_generic_kernel(const T* __restrict__ q, const T* __restrict__ dout,
+                                                                 const T* __restrict__ out,
                                                                  const float* __restrict__ lse,
-                                                                 const float* __restrict__ delta,
+                                                                 float* __restrict__ delta,
                                                                  const T* __restrict__ kp, const T* __restrict__ vp,
                                                                  const int32_t* __restrict__ pages,
                                                                  T* __restrict__ dq, int win_start, int nq, int nkv,
@@ -264,11 +254,16 @@ __global__ __launch_bounds__(64) void attn_bwd_dq_generic_kernel(const T* __rest
   const int h = blockIdx.y, lane = threadIdx.x;
   const int group = nq / nkv, kvh = h / group;
   const int p = win_start + (int)i;
+  float row_delta = 0.f;
   for (int dd = lane; dd < d; dd += 64) {
     qs[dd] = ld(q + (i * nq + h) * d + dd);
-    dos[dd] = ld(dout + (i * nq + h) * d + dd);
+    const float o = ld(dout + (i * nq + h) * d + dd);
+    dos[dd] = o;
+    row_delta += ld(out + (i * nq + h) * d + dd) * o;
   }
-  const float row_lse = lse[i * nq + h], row_delta = delta[i * nq + h];
+  row_delta = wsum(row_delta);
+  if (lane == 0) delta[i * nq + h] = row_delta;
+  const float row_lse = lse[i * nq + h];
   float acc[4] = {0.f, 0.f, 0.f, 0.f};   // d <= 256
   for (int kc = 0; kc <= p; kc += 64) {
     __builtin_amdgcn_wave_barrier();
@@ -439,22 +434,15 @@ int32_t launch_attention_merge(const flexco_layer_cfg& c, const flexco_maps& m, 
   return post_launch("attn_merge");
 }
 
-int32_t launch_attention_delta(const flexco_layer_cfg& c, const void* out, const void* dout, float* delta, int n,
-                               hipStream_t s) {
-  DISPATCH_T(c.dtype, hipLaunchKernelGGL((attn_delta_kernel<T>), dim3(n, c.n_q_heads), dim3(64), 0, s, (const T*)out,
-                                         (const T*)dout, delta, c.n_q_heads, c.head_dim));
-  return post_launch("attn_delta");
-}
-
 int32_t launch_attention_bwd_generic(const flexco_layer_cfg& c, const flexco_kv_pool& pool, const int32_t* seq_pages,
-                                     int win_start, int win_len, const void* q, const float* lse, const float* delta,
+                                     int win_start, int win_len, const void* q, const void* out, const float* lse, float* delta,
                                      const void* dout, void* dq, float* dk_accum, float* dv_accum, hipStream_t s) {
   const float scale = 1.0f / sqrtf((float)c.head_dim);
   const int l = win_start + win_len;
   const size_t shm = sizeof(float) * (2 * (size_t)c.head_dim + 64) + sizeof(size_t) * 64;   // (dK/dV: two score rows of 64)
   DISPATCH_T(c.dtype, {
     hipLaunchKernelGGL((attn_bwd_dq_generic_kernel<T>), dim3(win_len, c.n_q_heads), dim3(64), shm, s, (const T*)q,
-                       (const T*)dout, lse, delta, (const T*)pool.k_pages, (const T*)pool.v_pages, seq_pages,
+                       (const T*)dout, (const T*)out, lse, delta, (const T*)pool.k_pages, (const T*)pool.v_pages, seq_pages,
                        (T*)dq, win_start, c.n_q_heads, c.n_kv_heads, c.head_dim, c.page_size, scale);
     hipLaunchKernelGGL((attn_bwd_dkv_generic_kernel<T>), dim3(l, c.n_kv_heads), dim3(64), shm, s, (const T*)q,
                        (const T*)dout, lse, delta, (const T*)pool.k_pages, (const T*)pool.v_pages, seq_pages,

@@ -987,7 +987,7 @@ static int32_t layer_forward_impl(const flexco_layer_cfg* cfg, const flexco_base
   const size_t e = esize(dt);
   const int qd = c.n_q_heads * c.head_dim, kd = c.n_kv_heads * c.head_dim, qkvd = qd + 2 * kd;
   // Batches of more tokens have no split-K scratch of their own: the [T, 2F] buffer serves while it holds nothing, i.e.
-  // before the gate/up projection, and after it where the gated form left gate and up to the epilogue.
+  // before the gate/up projection and after SwiGLU.
   const bool gu_part = dt == FLEXCO_BF16 && T > FWD_SPLITK_MAX_T;
   auto lend_gu = [&](bool free) {
     if (!gu_part) return;
@@ -1043,8 +1043,11 @@ static int32_t layer_forward_impl(const flexco_layer_cfg* cfg, const flexco_base
     const int tg[2] = {FLEXCO_T_GATE, FLEXCO_T_UP}, c0[2] = {0, F};
     FLEXCO_TRY(forward_projection(c, ad, m, k.h, H, w->wgu, nullptr, nullptr, 0, k.gu, 2 * F, tg, c0, 2, k, ft, s, &glu));
   }
-  lend_gu(glu.done);
-  if (!glu.done) EW(launch_swiglu(k.gu, k.act, T, F, dt, s));
+  // (the gated projection has written the window's rows of gate and up to the sequence's state)
+  if (!glu.done)
+    EW(launch_swiglu(k.gu, k.act, T, F, dt, s, ft ? (void*)boff(ft->saved_gate, p0 * F, e) : nullptr,
+                     ft ? (void*)boff(ft->saved_up, p0 * F, e) : nullptr, m.ft_tok0, ft ? m.n_ft : 0));
+  lend_gu(true);
   if (ia3 && m.n_lora > 0) {   // the SwiGLU product of the adapter's rows
     Ia3ScaleArgs sa;
     memset(&sa, 0, sizeof(sa));
@@ -1054,22 +1057,6 @@ static int32_t layer_forward_impl(const flexco_layer_cfg* cfg, const flexco_base
   {
     const int tg[1] = {FLEXCO_T_DOWN}, c0[1] = {0};
     FLEXCO_TRY(forward_projection(c, ad, m, k.act, F, w->wd, nullptr, k.x2, H, x_out, H, tg, c0, 1, k, ft, s));
-  }
-  // where the gated projection did not run (fp32), gate and up are still in the workspace: copy the window's rows
-  if (ft && !glu.done) {
-    const int n = m.n_ft;
-    const size_t t0 = m.ft_tok0;
-    CopyRowsBatch cb;
-    size_t wb[8];
-    memset(&cb, 0, sizeof(cb));
-    auto add = [&](const void* src, size_t ld_src, void* dst, size_t ld_dst, size_t width) {
-      const int q = cb.count++;
-      cb.src[q] = (const char*)src; cb.ld_src[q] = ld_src; cb.dst[q] = (char*)dst; cb.ld_dst[q] = ld_dst;
-      cb.width16[q] = (int)(width / 16); wb[q] = width;
-    };
-    add(boff(k.gu, t0 * 2 * F, e), 2 * F * e, boff(ft->saved_gate, p0 * F, e), F * e, F * e);
-    add(boff(k.gu, t0 * 2 * F + F, e), 2 * F * e, boff(ft->saved_up, p0 * F, e), F * e, F * e);
-    EW(launch_copy_rows_batch(cb, n, wb, s));
   }
   return FLEXCO_OK;
 }
@@ -1117,8 +1104,7 @@ static int32_t attention_window_bwd_impl(const flexco_layer_cfg& c, const flexco
   if (rc != FLEXCO_EUNSUPPORTED) return rc;
   clear_error();
   note_fallback(c.dtype, FLEXCO_K_ATTN_BWD);
-  FLEXCO_TRY(launch_attention_delta(c, out, dout, delta, win_len, s));
-  return launch_attention_bwd_generic(c, pool, seq_pages, win_start, win_len, q, lse, delta, dout, dq, dk_accum,
+  return launch_attention_bwd_generic(c, pool, seq_pages, win_start, win_len, q, out, lse, delta, dout, dq, dk_accum,
                                       dv_accum, s);
 }
 

@@ -156,7 +156,9 @@ int32_t launch_rope_append(const flexco_layer_cfg& c, void* qkv, const int32_t* 
 bool rope_append_vec(const flexco_layer_cfg& c, const void* qkv, const flexco_kv_pool& pool, const void* q_cache);
 int32_t launch_rope_bwd_pack(const flexco_layer_cfg& c, const void* dq, const float* dk_rows, const float* dv_rows,
                              void* dqkv, int win_start, int n, hipStream_t s, const RowLoraT* lt = nullptr);
-int32_t launch_swiglu(const void* gu, void* act, int T, int F, int dtype, hipStream_t s);
+// rows [save_row0, save_row0 + save_rows) of gate and up are also written to save_gate / save_up (NULL: none)
+int32_t launch_swiglu(const void* gu, void* act, int T, int F, int dtype, hipStream_t s, void* save_gate, void* save_up,
+                      int save_row0, int save_rows);
 int32_t launch_swiglu_bwd(const void* gate, const void* up, const void* dact, void* dgu, int n, int F, int dtype,
                           hipStream_t s, void* act = nullptr,
                           const float* dact_part = nullptr, int splits = 1);
@@ -175,13 +177,6 @@ int32_t launch_ia3_scale_rows(void* buf, size_t ld, const int32_t* tok, int n_to
 // dl[c] += sum_r G[r, c] X[r, c];  G[r, c] *= l[c];  part: float [ceil(n / 8)][C] scratch
 int32_t launch_ia3_colgrad(void* G, size_t ldg, const void* X, size_t ldx, const void* l, float* part, float* dl, int n,
                            int C, int dtype, hipStream_t s);
-struct CopyRowsBatch {
-  const char* src[8]; size_t ld_src[8];
-  char* dst[8]; size_t ld_dst[8];
-  int width16[8];       // row width in 16-byte units
-  int count;
-};
-int32_t launch_copy_rows_batch(const CopyRowsBatch& b, int n_rows, size_t const* width_bytes, hipStream_t s);
 int32_t launch_copy_rows(const void* src, size_t ld_src_bytes, void* dst, size_t ld_dst_bytes, int n_rows,
                          size_t width_bytes, hipStream_t s);
 
@@ -240,10 +235,8 @@ int32_t launch_attention_bwd_mfma(const flexco_layer_cfg& c, const flexco_kv_poo
 int32_t launch_attention_merge(const flexco_layer_cfg& c, const flexco_maps& m, const float* part_ml,
                                const float* part_acc, void* out, size_t ldo, float* lse, hipStream_t s, bool skip_single_split = false,
                                const AttnKeep* keep = nullptr);
-int32_t launch_attention_delta(const flexco_layer_cfg& c, const void* out, const void* dout, float* delta, int n,
-                               hipStream_t s);
 int32_t launch_attention_bwd_generic(const flexco_layer_cfg& c, const flexco_kv_pool& pool, const int32_t* seq_pages,
-                                     int win_start, int win_len, const void* q, const float* lse, const float* delta,
+                                     int win_start, int win_len, const void* q, const void* out, const float* lse, float* delta,
                                      const void* dout, void* dq, float* dk_accum, float* dv_accum, hipStream_t s);
 
 }  // namespace flexco

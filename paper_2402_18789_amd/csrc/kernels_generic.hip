@@ -924,7 +924,8 @@ __global__ __launch_bounds__(256) void ia3_colgrad_finalize_kernel(const float* 
 // SwiGLU forward / backward
 // --------------------------------------------------------------------------------------
 template <typename T, bool VEC>
-__global__ __launch_bounds__(256) void swiglu_kernel(const T* __restrict__ gu, T* __restrict__ act, int F) {
+__global__ __launch_bounds__(256) void swiglu_kernel(const T* __restrict__ gu, T* __restrict__ act, int F,
+                                                     T* __restrict__ save_gate, T* __restrict__ save_up, int save_row0, int save_rows) {
   constexpr int N = VEC ? Vec<T>::N : 1;
   const size_t row = blockIdx.y;
   const int i = (blockIdx.x * 256 + threadIdx.x) * N;
@@ -932,6 +933,11 @@ __global__ __launch_bounds__(256) void swiglu_kernel(const T* __restrict__ gu, T
   float g[N], u[N];
   if (VEC) { Vec<T>::load(gu + row * 2 * F + i, g); Vec<T>::load(gu + row * 2 * F + F + i, u); }
   else { g[0] = ld(gu + row * 2 * F + i); u[0] = ld(gu + row * 2 * F + F + i); }
+  if (save_gate && (int)row >= save_row0 && (int)row < save_row0 + save_rows) {      // (values of T: stored as they are)
+    const size_t o = (row - save_row0) * F + i;
+    if (VEC) { Vec<T>::store(save_gate + o, g); Vec<T>::store(save_up + o, u); }
+    else { st(save_gate + o, g[0]); st(save_up + o, u[0]); }
+  }
 #pragma unroll
   for (int j = 0; j < N; ++j) g[j] = g[j] / (1.0f + __expf(-g[j])) * u[j];
   if (VEC) Vec<T>::store(act + row * F + i, g); else st(act + row * F + i, g[0]);
@@ -988,15 +994,6 @@ __global__ __launch_bounds__(256) void swiglu_remat_kernel(const T* __restrict__
 // --------------------------------------------------------------------------------------
 // strided row copy: dst row i = src row i, `width` units of V (uint4 = 16 bytes, or 4-byte words)
 // --------------------------------------------------------------------------------------
-// several strided row copies in one launch (blockIdx.z picks the copy); widths in 16-byte units
-__global__ __launch_bounds__(256) void copy_rows_batch_kernel(CopyRowsBatch b) {
-  const int e = blockIdx.z;
-  const size_t row = blockIdx.y;
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= b.width16[e]) return;
-  reinterpret_cast<uint4*>(b.dst[e] + row * b.ld_dst[e])[i] = reinterpret_cast<const uint4*>(b.src[e] + row * b.ld_src[e])[i];
-}
-
 template <typename V>
 __global__ __launch_bounds__(256) void copy_rows_kernel(const char* __restrict__ src, size_t ld_src,
                                                         char* __restrict__ dst, size_t ld_dst, int width) {
@@ -1011,7 +1008,7 @@ __global__ __launch_bounds__(256) void copy_rows_kernel(const char* __restrict__
 // of a LoRA matrix, addressed as S[i * s_i + j * s_j], so that the same kernels serve
 // A [r, in] (s_i = 1, s_j = in) and B [out, r] (s_i = r, s_j = 1).
 // A launch takes a batch of products (the targets of one projection, u and t, dA and dB): they are small, and a launch
-// costs 4 - 6 us whatever it does (the fp32 configuration's co-served iteration: 51 -> 41 launches, 311 -> 254 us).
+// costs 4 - 6 us whatever it does (the fp32 configuration's co-served iteration: 51 -> 41 launches, 311 -> 255 us).
 // --------------------------------------------------------------------------------------
 // out[m, j] = sum_i X[m, i] * S(i, j)        one block per row m; R = rank bound
 template <typename T, int R>
@@ -1071,6 +1068,55 @@ __global__ __launch_bounds__(256) void lora_expand_kernel(LoraBatch b, int n, in
       for (int j = 0; j < R; ++j) a += us[mm][j] * sv[j];
       const size_t yr = row_idx ? (size_t)row_idx[m0 + mm] : (size_t)(m0 + mm);
       T* y = (T*)p.Y + yr * p.ldy + i;
+      st(y, ld(y) + scale * a);
+    }
+  }
+}
+
+// Both of a few rows in one launch: a block per row (and product) that keeps u between them.
+//   FWD:  u = x A^T;  y += scale u B^T               (down.p[z]: x, A, u;  up.p[z]: B, y)
+//   else: the gradients' sums of one row, u_z = x_z A_z^T and t_z = dy_z B_z (down.p[2 z], down.p[2 z + 1]), and
+//         dx += scale sum_z t_z A_z (up.p[z], one dx for all of them)
+template <typename T, int R, bool FWD>
+__global__ __launch_bounds__(256) void lora_rows_kernel(LoraBatch down, LoraBatch up, int r, float scale,
+                                                        const int32_t* __restrict__ row_idx) {
+  __shared__ float red[4][R], us[R];
+  const size_t mo = blockIdx.x;
+  const size_t m = row_idx ? (size_t)row_idx[mo] : mo;
+  for (int z = FWD ? blockIdx.y : 0; z < (FWD ? (int)blockIdx.y + 1 : down.count); ++z) {
+    const LoraProduct& p = down.p[z];
+    const T* __restrict__ X = (const T*)p.X + m * p.ldx;
+    const T* __restrict__ S = (const T*)p.S;
+    float acc[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j) acc[j] = 0.f;
+    for (int i = threadIdx.x; i < p.n_long; i += 256) {
+      const float xv = ld(X + i);
+#pragma unroll
+      for (int j = 0; j < R; ++j)
+        if (j < r) acc[j] += xv * ld(S + (size_t)i * p.s_i + (size_t)j * p.s_j);
+    }
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      const float v = wave_sum(acc[j]);
+      if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][j] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x < R) {
+      const float v = red[0][threadIdx.x] + red[1][threadIdx.x] + red[2][threadIdx.x] + red[3][threadIdx.x];
+      us[threadIdx.x] = v;                          // (ranks past r: zero)
+      if ((int)threadIdx.x < r) p.U[mo * r + threadIdx.x] = v;
+    }
+    __syncthreads();
+    if (!FWD && (z & 1) == 0) continue;             // (a u: nothing to add anywhere)
+    const LoraProduct& o = up.p[FWD ? z : z >> 1];
+    const T* __restrict__ B = (const T*)o.S;
+    for (int i = threadIdx.x; i < o.n_long; i += 256) {
+      float a = 0.f;
+#pragma unroll
+      for (int j = 0; j < R; ++j)
+        if (j < r) a += us[j] * ld(B + (size_t)i * o.s_i + (size_t)j * o.s_j);
+      T* y = (T*)o.Y + m * o.ldy + i;
       st(y, ld(y) + scale * a);
     }
   }
@@ -1385,12 +1431,13 @@ int32_t launch_ia3_colgrad(void* G, size_t ldg, const void* X, size_t ldx, const
   return post_launch("ia3_colgrad");
 }
 
-int32_t launch_swiglu(const void* gu, void* act, int T_, int F, int dtype, hipStream_t s) {
+int32_t launch_swiglu(const void* gu, void* act, int T_, int F, int dtype, hipStream_t s, void* save_gate, void* save_up,
+                      int save_row0, int save_rows) {
   if (T_ == 0) return FLEXCO_OK;
-  const bool vec = vec_ok(dtype, F, {gu, act});
+  const bool vec = vec_ok(dtype, F, {gu, act, save_gate, save_up});
   const int per = 256 * (vec ? (dtype == FLEXCO_BF16 ? 8 : 4) : 1);
   DISPATCH_TV(dtype, vec, hipLaunchKernelGGL((swiglu_kernel<T, VEC>), dim3((F + per - 1) / per, T_), dim3(256), 0, s,
-                                             (const T*)gu, (T*)act, F));
+                                             (const T*)gu, (T*)act, F, (T*)save_gate, (T*)save_up, save_row0, save_rows));
   return post_launch("swiglu");
 }
 
@@ -1412,26 +1459,6 @@ int32_t launch_swiglu_remat(const void* gate, const void* up, void* act, int n, 
   DISPATCH_TV(dtype, vec, hipLaunchKernelGGL((swiglu_remat_kernel<T, VEC>), dim3((F + per - 1) / per, n), dim3(256), 0,
                                              s, (const T*)gate, (const T*)up, (T*)act, F));
   return post_launch("swiglu_remat");
-}
-
-// Several row copies with the same row count in one launch; falls back to one launch per copy when
-// a copy is not made of aligned 16-byte pieces.
-int32_t launch_copy_rows_batch(const CopyRowsBatch& b, int n_rows, size_t const* width_bytes, hipStream_t s) {
-  if (n_rows == 0 || b.count == 0) return FLEXCO_OK;
-  bool v16 = true;
-  int wmax = 0;
-  for (int e = 0; e < b.count; ++e) {
-    v16 = v16 && width_bytes[e] % 16 == 0 && b.ld_src[e] % 16 == 0 && b.ld_dst[e] % 16 == 0 && aligned16(b.src[e]) &&
-          aligned16(b.dst[e]);
-    wmax = b.width16[e] > wmax ? b.width16[e] : wmax;
-  }
-  if (!v16) {
-    for (int e = 0; e < b.count; ++e)
-      FLEXCO_TRY(launch_copy_rows(b.src[e], b.ld_src[e], b.dst[e], b.ld_dst[e], n_rows, width_bytes[e], s));
-    return FLEXCO_OK;
-  }
-  hipLaunchKernelGGL(copy_rows_batch_kernel, dim3((wmax + 255) / 256, n_rows, b.count), dim3(256), 0, s, b);
-  return post_launch("copy_rows_batch");
 }
 
 int32_t launch_copy_rows(const void* src, size_t ld_src_bytes, void* dst, size_t ld_dst_bytes, int n_rows,
@@ -1469,6 +1496,23 @@ static int32_t lora_ops(int op, const LoraBatch& b, bool shared_y, int n, int r,
   return post_launch("lora kernel");
 }
 
+// Up to this many rows the two launches' cost is that they are two (4 - 5 us of host and queue each), and the matrices are
+// read once per row from L2; beyond, the row blocks of the separate expand kernel read them a sixteenth as often.
+constexpr int LORA_ROWS_MAX = 256;
+template <bool FWD>
+static int32_t lora_rows(const LoraBatch& down, const LoraBatch& up, int n, int r, float scale, int dtype, const int32_t* row_idx,
+                         hipStream_t s) {
+  const dim3 grid(n, FWD ? down.count : 1);
+#define FLEXCO_LORA_ROWS(R_) \
+  DISPATCH_T(dtype, hipLaunchKernelGGL((lora_rows_kernel<T, R_, FWD>), grid, dim3(256), 0, s, down, up, r, scale, row_idx))
+  if (r <= 8) FLEXCO_LORA_ROWS(8);
+  else if (r <= 16) FLEXCO_LORA_ROWS(16);
+  else if (r <= 32) FLEXCO_LORA_ROWS(32);
+  else FLEXCO_LORA_ROWS(64);
+#undef FLEXCO_LORA_ROWS
+  return post_launch("lora_rows");
+}
+
 static int32_t lora_dispatch(int op, const LoraBatch& b, bool shared_y, int n, int r, float scale, int dtype, hipStream_t s,
                              const int32_t* row_idx = nullptr) {
   if (n == 0 || b.count == 0) return FLEXCO_OK;
@@ -1504,6 +1548,8 @@ int32_t launch_lora_apply(const LoraTarget* tg, int count, int n, int r, float s
     down.p[z] = {t.x, t.ldx, t.A, 1, (size_t)t.in, t.u, nullptr, 0, nullptr, 0, 0, t.in};
     up.p[z] = {nullptr, 0, t.B, (size_t)r, 1, t.u, t.y, t.ldy, nullptr, 0, 0, t.out};
   }
+  if (n == 0 || count == 0) return FLEXCO_OK;
+  if (n <= LORA_ROWS_MAX) return lora_rows<true>(down, up, n, r, scale, dtype, row_idx, s);
   const int32_t rc = lora_dispatch(0, down, false, n, r, 0.f, dtype, s, row_idx);
   return rc ? rc : lora_dispatch(1, up, count == 1, n, r, scale, dtype, s, row_idx);
 }
@@ -1540,6 +1586,12 @@ int32_t launch_lora_bwd(const LoraTarget* tg, int count, void* dx, size_t lddx, 
     back.p[z] = {nullptr, 0, t.A, 1, (size_t)t.in, t.t, dx, lddx, nullptr, 0, 0, t.in};
   }
   int32_t rc;
+  // (few rows with a dx to add to: u, t and dx in one launch.  The outer products read dy and x, which may be dx itself -
+  // the adapter's in-place call, which has relu - so they cannot come first there.)
+  if (dx && !relu && n > 0 && n <= LORA_ROWS_MAX) {
+    if ((rc = lora_rows<false>(long_sums, back, n, r, scale, dtype, nullptr, s))) return rc;
+    return lora_dispatch(2, outer, false, n, r, scale, dtype, s);
+  }
   if ((rc = lora_dispatch(0, long_sums, false, n, r, 0.f, dtype, s))) return rc;
   if (relu && (rc = launch_relu_mask(tg[0].u, tg[0].t, (size_t)n * r, s))) return rc;
   if ((rc = lora_dispatch(2, outer, false, n, r, scale, dtype, s))) return rc;

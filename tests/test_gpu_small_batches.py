@@ -36,3 +36,13 @@ def test_attention_merge_of_many_splits(split):
     out, a_o, lse, lse_o = attention_case(cfg, batch, split)
     assert_close("attention out", out, a_o, TOL[cfg.dtype])
     assert float(np.max(np.abs(lse - lse_o))) <= 2e-2
+
+
+# the type-generic LoRA kernels: up to 256 rows in one launch with the products' sums kept in LDS, more in two
+@pytest.mark.parametrize("window", [256, 257])
+@pytest.mark.parametrize("rank", [5, 24])
+def test_generic_lora_rows(window, rank):
+    print(f"type-generic LoRA of rank {rank}, windows of {window}", flush=True)
+    cfg = CONFIGS["c1_tiny_f32"].with_(name="tiny_r%d" % rank, lora_rank=rank, lora_targets=("q", "v", "o", "gate", "up", "down"))
+    b = gen.mixed_batch(cfg.page_size, 19, decode_ctx=(1, 40), finetune=[(0, window, 2 * window)])
+    run_layer_case(cfg, b, ft_window=window, prefill_chunk=32, bwd_windows=[window, window], seed=19)
