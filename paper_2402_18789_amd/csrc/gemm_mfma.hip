@@ -732,6 +732,23 @@ __global__ __launch_bounds__(256) void gemm_bf16_quad_kernel(const bf16_t* __res
     Q_PHASE(Q_READ_A, fa0, a0e, a1o, GEMM_SRC_A((s_) + 2), oa[1], NA, 4, 0, fa1, fw0, VM2)            \
     Q_PHASE(Q_READ_W, fw0, w0e, a0e, GEMM_SRC_A((s_) + 3), oa[0], NA, 4, HN, fa1, fw1, VM3)           \
   }
+  // The rank-r extension's steps (entry, 16 of its rank) in turn, entries that miss the tile left out.  The operands of the
+  // first step are fetched here: their round trip lies open behind the main loop otherwise, every tile (1 % of a 1024-row
+  // window's backward; two steps' operands, where there are registers for them, were no faster).
+#define Q_EXT_NEXT(e_, k2_)                                                                           \
+  {                                                                                                   \
+    k2_ += 16;                                                                                        \
+    if (k2_ >= ext.r) {                                                                               \
+      k2_ = 0;                                                                                        \
+      do ++e_; while (e_ < ext.n && FLEXCO_EXT_SKIPS(e_));                                            \
+    }                                                                                                 \
+  }
+  const int ext_n = blockIdx.y == 0 ? ext.n : 0;
+  int ext_e = -1, ext_k = ext.r;
+  bf16x4 xa[MT], xw[NT];
+  if (ext_n > 0) Q_EXT_NEXT(ext_e, ext_k)
+  const bool ext_on = ext_n > 0 && ext_e < ext_n;
+  if (ext_on) FLEXCO_EXT_LOAD(ext_e, ext_k, xa, xw)
   bf16x8 fa0[4][2], fa1[4][2], fw0[HN][2], fw1[HN][2];
   Q_LOAD_A(a0e, 0, 0) Q_LOAD_W(w0e, 0, 0) Q_LOAD_W(w1e, 1, 0) Q_LOAD_A(a1e, 1, 0)
   Q_LOAD_A(a0o, 0, 1) Q_LOAD_W(w1o, 1, 1) Q_LOAD_W(w0o, 0, 1) Q_LOAD_A(a1o, 1, 1)
@@ -755,12 +772,14 @@ __global__ __launch_bounds__(256) void gemm_bf16_quad_kernel(const bf16_t* __res
   FLEXCO_ACC_FENCE
 
   // ---- rank-r extension (see the kernel above) ----
-  for (int e = 0; e < (blockIdx.y == 0 ? ext.n : 0); ++e) {
-    if (FLEXCO_EXT_SKIPS(e)) continue;
-    for (int k2 = 0; k2 < ext.r; k2 += 16) {
+  if (ext_on) {
+    FLEXCO_EXT_MFMAS(xa, xw)
+    Q_EXT_NEXT(ext_e, ext_k)
+    while (ext_e < ext_n) {
       bf16x4 af[MT], bfr[NT];
-      FLEXCO_EXT_LOAD(e, k2, af, bfr)
+      FLEXCO_EXT_LOAD(ext_e, ext_k, af, bfr)
       FLEXCO_EXT_MFMAS(af, bfr)
+      Q_EXT_NEXT(ext_e, ext_k)
     }
   }
   __syncthreads();   // every wavefront is done with the half-tiles, and (after its own wait above) its loads have landed
