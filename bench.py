@@ -293,13 +293,16 @@ def per_projection(B, torch, step_serial, cfg, T):
     names = [("qkv", (qd + 2 * kd) * H), ("o", qd * H), ("gate_up", 2 * F * H), ("down", F * H)]
     if calls != 4 * steps or per_step < 4 or len(each) != per_step * steps:
         return {"note": "unexpected launch pattern: %d pairs for %d calls" % (len(each), calls)}
-    # the calls come in the order qkv, o, gate/up, down; extra pairs of a step belong to the widest projection
-    # (gate/up), whose plan is the one that splits into two launches at this size
-    extra = per_step - 4
+    # the calls come in the order qkv, o, gate/up, down; a product in ranges of K has a second pair, its sum's, and
+    # the rest belong to the widest projection (gate/up), whose plan is the one with two tile shapes at this size
+    pairs = [1 + (k != 2 and B.flexco_gemm_k_ranges(T, p // K, K, False, 1 << 30) > 1)
+             for k, (p, K) in enumerate(zip((p for _, p in names), (H, qd, H, F)))]
+    pairs[2] += per_step - sum(pairs)
+    if pairs[2] < 1:
+        return {"note": "unexpected launch pattern: %d pairs for %d calls" % (len(each), calls)}
     out = {}
     for k, (name, p) in enumerate(names):
-        lo = k if k < 2 else (2 if k == 2 else 3 + extra)
-        hi = lo + (1 + extra if k == 2 else 1)
+        lo, hi = sum(pairs[:k]), sum(pairs[:k + 1])
         ms = sum(sum(each[st * per_step + j] for j in range(lo, hi)) for st in range(steps)) / steps
         tf = 2.0 * p * T / (ms * 1e-3) / 1e12
         out[name] = {"ms": round(ms, 4), "launches": hi - lo, "achieved": tf, "unit": "TFLOP/s", "frac": tf / MFMA_BF16_PEAK_TFLOPS}
