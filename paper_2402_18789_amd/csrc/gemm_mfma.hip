@@ -365,9 +365,11 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
   // between the two fragment sets, each fetched one slice ahead.  In the last slice:
   //   wait until this wavefront's loads of stage s + 1 have landed (with four stages those of
   //   stage s + 2 may stay in flight), barrier -> stage s + 1 is complete for everyone, and
-  //   everyone has the last fragments of stage s in registers; start the loads of the stage
-  //   that takes over the freed buffer; fetch slice 0 of stage s + 1; then the last slice's
-  //   MFMAs cover those latencies.
+  //   nobody reads the freed buffer any more; start the loads of the stage that takes it over;
+  //   fetch slice 0 of stage s + 1; then the last slice's MFMAs cover those latencies.
+  // Why nobody does: with four or six stages it held stage s - 1, whose last fragments the products before this barrier
+  // have used.  With two it held stage s itself, whose last fragments were asked for in the slice before and are used
+  // behind the barrier only: there the wait in front of it names the LDS reads too (lgkmcnt(0)).
   // A read (and, in the stage's last slice, a load) goes behind each product until they are used up.
 #define FLEXCO_SLICE(af_, bf_, ring_, kk_, raf_, rbf_, load_)                                         \
   {                                                                                                   \
@@ -391,7 +393,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
   // their maxima (no wait)
 #define FLEXCO_VMCNT(n_) (0x0F70 | ((n_) & 15) | (((n_) >> 4) << 14))
   // before a stage's barrier: the next stage has landed, the ones after it (up to s + 2 of four, s + 4 of six) may stay in flight
-  constexpr int WAIT_NEXT_STAGE = FLEXCO_VMCNT(NST > 2 ? (NST - 3) * NLD : 0);
+  // (two stages: and this wavefront's LDS reads have returned, see above)
+  constexpr int WAIT_NEXT_STAGE = NST > 2 ? FLEXCO_VMCNT((NST - 3) * NLD) : 0x0070;
   // the buffer freed at stage s's barrier held stage s - 1 (four stages, six) or stage s itself (two)
   constexpr int AHEAD = NST > 2 ? NST - 1 : 2;
   // ---- operands of the rank-r extension's first step and the residual / bias of the epilogue, fetched ahead of the

@@ -1,0 +1,44 @@
+"""What the built gfx950 code of the LDS-staged kernels does, on every path of it (no GPU): a buffer is handed to new loads
+only when its readers have their data."""
+import os
+import re
+
+import pytest
+
+import gfx_code
+import paper_2402_18789_amd.binding as B
+
+pytestmark = [pytest.mark.skipif(B.HOST_ONLY, reason="needs the whole library, this is a host-only build"),
+              pytest.mark.skipif(not os.path.exists(gfx_code.OBJDUMP), reason="needs llvm-objdump")]
+
+
+@pytest.fixture(scope="module")
+def code(tmp_path_factory):
+    return gfx_code.kernels(B.LIB_PATH, str(tmp_path_factory.mktemp("code")))
+
+
+def barriers_of(code, name):
+    """{kernel's template arguments: reads on their way at each of its barriers}"""
+    out = {}
+    for mangled, ins in code.items():
+        m = re.search(r"\d%sI((?:L[ib]\d+E)+)E" % name, mangled)
+        if m and not mangled.endswith(".kd"):
+            out[tuple(int(v) for v in re.findall(r"L[ib](\d+)E", m.group(1)))] = gfx_code.lds_reads_at_barriers(ins)
+    assert out, name
+    return out
+
+
+# Rings of two stages (the input-gradient form, and the forward form built with two): the buffer freed at a stage's barrier
+# is the stage's own, so no wavefront may have a read on its way there.  Rings of four and six free the stage before:
+# reads issued since the last barrier may be on their way, older ones may not.
+def test_projection_rings_are_not_overwritten_under_a_read(code):
+    two = 0
+    for (bm, bn, trans, glu, stages), reads in barriers_of(code, "gemm_bf16_kernel").items():
+        assert len(reads) > 2
+        assert all(old == 0 for _, old in reads), (bm, bn, trans, glu, stages, reads)
+        if trans or stages == 2:
+            two += 1
+            assert all(young == 0 for young, _ in reads), (bm, bn, trans, glu, stages, reads)
+    assert two == 3
+    for args, reads in barriers_of(code, "gemm_bf16_quad_kernel").items():
+        assert all(r == (0, 0) for r in reads), (args, reads)
