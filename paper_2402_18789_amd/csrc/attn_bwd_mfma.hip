@@ -63,11 +63,13 @@ struct BwdArgs {
 //     0-3 and 12-15 own the same four chunk pairs, one chunk of each, so the 16 lanes cover 16 different chunks.
 __device__ inline int rsw(int r) { return (((r + ((r >> 3) << 2)) & 7) << 1) | ((r >> 3) & 1); }
 
-// wait for this wavefront's loads, then a barrier without memory fences (those would also drain
-// loads issued after the wait); the empty asm statements keep LDS accesses on their side of it
+// wait for this wavefront's loads and LDS reads, then a barrier without memory fences (those would also drain
+// loads issued after the wait); the empty asm statements keep LDS accesses on their side of it.  The reads: the next
+// loads overwrite the buffers that the step before has read, and its last products, which wait for them, may come
+// behind the barrier.
 #define FLEXCO_WAIT_ALL_BARRIER                  \
   {                                              \
-    __builtin_amdgcn_s_waitcnt(0x0F70);          \
+    __builtin_amdgcn_s_waitcnt(0x0070);          \
     asm volatile("" ::: "memory");               \
     __builtin_amdgcn_s_barrier();                \
     asm volatile("" ::: "memory");               \

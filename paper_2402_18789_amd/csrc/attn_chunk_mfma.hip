@@ -130,11 +130,12 @@ __global__ __launch_bounds__(256, RING == 3 ? 3 : 2) void attn_fwd_chunk_kernel(
       __builtin_amdgcn_global_load_lds(FLEXCO_GP(vb_ + v_src), FLEXCO_LP(ring_ + (2 + x) * PAGE_EL + wave * 512), 16, 0, 0); \
     }                                                                                                 \
   }
-  // wait until this wavefront's loads of all stages but the last LATEST_ issued have landed (4 loads each), then a
-  // barrier without memory fences
+  // wait until this wavefront's loads of all stages but the last LATEST_ issued have landed (4 loads each) and its LDS
+  // reads have returned (the V of the stage whose buffer is handed over: the products that use it may come behind the
+  // barrier), then a barrier without memory fences
 #define FLEXCO_CH_WAIT_BARRIER(LATEST_)                     \
   {                                                         \
-    __builtin_amdgcn_s_waitcnt(0x0F70 | (4 * (LATEST_)));   \
+    __builtin_amdgcn_s_waitcnt(0x0070 | (4 * (LATEST_)));   \
     asm volatile("" ::: "memory");                          \
     __builtin_amdgcn_s_barrier();                           \
     asm volatile("" ::: "memory");                          \

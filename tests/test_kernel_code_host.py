@@ -42,3 +42,12 @@ def test_projection_rings_are_not_overwritten_under_a_read(code):
     assert two == 3
     for args, reads in barriers_of(code, "gemm_bf16_quad_kernel").items():
         assert all(r == (0, 0) for r in reads), (args, reads)
+
+
+# Attention: the buffer freed at a step's barrier is the one the step before has read (backward: two buffer sets; chunk
+# items: rings of three and four, whose V is read in the step that ends at the barrier).
+@pytest.mark.parametrize("name", ["attn_bwd_dq_mfma_kernel", "attn_bwd_dkv_mfma_kernel", "attn_fwd_chunk_kernel"])
+def test_attention_buffers_are_not_overwritten_under_a_read(code, name):
+    for args, reads in barriers_of(code, name).items():
+        assert len(reads) > 2
+        assert all(r == (0, 0) for r in reads), (args, reads)
