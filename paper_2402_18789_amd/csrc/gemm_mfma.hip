@@ -34,7 +34,8 @@ namespace flexco {
 namespace {
 
 constexpr int BK = 64;
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned int frag_t __attribute__((ext_vector_type(4), may_alias));   // 8 bf16 of one row or column: an operand of a product
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 #define FLEXCO_LDS __attribute__((address_space(3)))
 
@@ -50,8 +51,15 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 // In assembly: accumulators of four registers left to the compiler wander between the two register files (64 - 330 moves
 // per pass of the loop below; 0 this way).  The compiler does not see a product in it, hence FLEXCO_ACC_FENCE before
 // anything else touches the accumulators (32 wait states, the products need 18) and the order of a loop's instructions
-// is the one they are written in.  Operands come from LDS reads, whose waits the compiler places for any use.
-#define FLEXCO_MFMA(c_, w_, a_) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c_) : "v"(w_), "v"(a_));
+// is the one they are written in.
+// Operands come from LDS reads, whose waits the compiler places for any use.  A vector instruction that writes one
+// would have to be two wait states ahead of the product, which the compiler does not see to here either: fragments are
+// held as whole registers (as 16-bit elements the stages behind a main loop had them reassembled, right in front
+// of 11 products of the 128 x 192 tile), those stages, where paths join and copies may arise,
+// carry the wait states themselves (FLEXCO_PAD), and a test reads the built code of all of them.  (Wait states in front of
+// every product: 2048 x 24576 x 5120 362 -> 378 us, 1024 x 28672 x 4096 179 -> 192; behind the main loops alone: no difference.)
+#define FLEXCO_PAD "s_nop 1\n\t"
+#define FLEXCO_MFMA(c_, w_, a_, pad_) asm volatile(pad_ "v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c_) : "v"(w_), "v"(a_));
 #define FLEXCO_ACC_FENCE                                                                              \
   {                                                                                                   \
     __builtin_amdgcn_sched_barrier(0);                                                                \
@@ -336,16 +344,16 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
   {                                                                                                   \
     if ((q_) < MT) {                                                                                  \
       const int r_ = wm0 + (q_) * 16 + l16;                                                           \
-      af_[(q_) < MT ? (q_) : 0] = *reinterpret_cast<const bf16x8*>(ring_ + r_ * BK + (((kk_) * 4 + q4) ^ FLEXCO_KEY(r_)) * 8); \
+      af_[(q_) < MT ? (q_) : 0] = *reinterpret_cast<const frag_t*>(ring_ + r_ * BK + (((kk_) * 4 + q4) ^ FLEXCO_KEY(r_)) * 8); \
     } else {                                                                                          \
       const int j_ = (q_) < MT ? 0 : (q_) - MT;                                                       \
       if (!TRANS) {                                                                                   \
         const int r_ = wn0 + j_ * 16 + l16;                                                           \
-        bf_[j_] = *reinterpret_cast<const bf16x8*>(ring_ + (BM + r_) * BK + (((kk_) * 4 + q4) ^ FLEXCO_KEY(r_)) * 8); \
+        bf_[j_] = *reinterpret_cast<const frag_t*>(ring_ + (BM + r_) * BK + (((kk_) * 4 + q4) ^ FLEXCO_KEY(r_)) * 8); \
       } else {                                                                                        \
         const s16x4 lo_ = __builtin_amdgcn_ds_read_tr16_b64_v4i16((FLEXCO_LDS s16x4*)(ring_ + (tr_off[j_] + (BM * BK + (kk_) * 32 * BN)))); \
         const s16x4 hi_ = __builtin_amdgcn_ds_read_tr16_b64_v4i16((FLEXCO_LDS s16x4*)(ring_ + (tr_off[j_] + (BM * BK + ((kk_) * 32 + 4) * BN)))); \
-        bf_[j_] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo_, hi_, 0, 1, 2, 3, 4, 5, 6, 7)); \
+        bf_[j_] = __builtin_shufflevector(__builtin_bit_cast(u32x2, lo_), __builtin_bit_cast(u32x2, hi_), 0, 1, 2, 3); \
       }                                                                                               \
     }                                                                                                 \
   }
@@ -371,22 +379,23 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
   // have used.  With two it held stage s itself, whose last fragments were asked for in the slice before and are used
   // behind the barrier only: there the wait in front of it names the LDS reads too (lgkmcnt(0)).
   // A read (and, in the stage's last slice, a load) goes behind each product until they are used up.
-#define FLEXCO_SLICE(af_, bf_, ring_, kk_, raf_, rbf_, load_)                                         \
+#define FLEXCO_SLICE(af_, bf_, ring_, kk_, raf_, rbf_, load_, pad_)                                   \
   {                                                                                                   \
     _Pragma("unroll") for (int n = 0; n < MT * NT; ++n) {                                             \
-      FLEXCO_MFMA(acc[n / NT][n % NT], bf_[n % NT], af_[n / NT])                                      \
+      FLEXCO_MFMA(acc[n / NT][n % NT], bf_[n % NT], af_[n / NT], pad_)                                \
       load_                                                                                           \
       if (n < MT + NT) FLEXCO_FRAG(ring_, kk_, raf_, rbf_, n)                                         \
       __builtin_amdgcn_sched_barrier(0);                                                              \
     }                                                                                                 \
   }
-#define FLEXCO_STAGE(cur_, nxt_, free_, s_)                                                           \
+#define FLEXCO_STAGE_PAD(cur_, nxt_, free_, s_, pad_)                                                 \
   {                                                                                                   \
-    FLEXCO_SLICE(af0, bf0, cur_, 1, af1, bf1, )                                                       \
+    FLEXCO_SLICE(af0, bf0, cur_, 1, af1, bf1, , pad_)                                                 \
     FLEXCO_WAIT_BARRIER(WAIT_NEXT_STAGE)                                                              \
     const __amdgpu_buffer_rsrc_t sa_ = GEMM_SRC_A((s_) + AHEAD), sw_ = GEMM_SRC_W((s_) + AHEAD);  \
-    FLEXCO_SLICE(af1, bf1, nxt_, 0, af0, bf0, if (n < NLD) FLEXCO_LOAD(free_, n))                     \
+    FLEXCO_SLICE(af1, bf1, nxt_, 0, af0, bf0, if (n < NLD) FLEXCO_LOAD(free_, n), pad_)               \
   }
+#define FLEXCO_STAGE(cur_, nxt_, free_, s_) FLEXCO_STAGE_PAD(cur_, nxt_, free_, s_, "")
   static_assert(SL == 2 && MT * NT >= MT + NT && MT * NT >= PA + PB, "a slice's products outnumber its reads and a stage's loads");
   constexpr int NLD = PA + PB;                                     // loads of one stage
   // s_waitcnt immediates: vmcnt in bits 3:0 and 15:14, expcnt 6:4 and lgkmcnt 11:8 left at
@@ -475,7 +484,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
       }
     }
   }
-  bf16x8 af0[MT], bf0[NT], af1[MT], bf1[NT];
+  frag_t af0[MT], bf0[NT], af1[MT], bf1[NT];
   FLEXCO_ACC_FENCE
 #define FLEXCO_FIRST_FRAGS                                                                            \
   { _Pragma("unroll") for (int q = 0; q < MT + NT; ++q) FLEXCO_FRAG(ring0, 0, af0, bf0, q) }
@@ -496,11 +505,11 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
       FLEXCO_STAGE(ring4, ring5, ring3, st + 4)
       FLEXCO_STAGE(ring5, ring0, ring4, st + 5)
     }
-    if (st < ns) FLEXCO_STAGE(ring0, ring1, ring5, st)
-    if (st + 1 < ns) FLEXCO_STAGE(ring1, ring2, ring0, st + 1)
-    if (st + 2 < ns) FLEXCO_STAGE(ring2, ring3, ring1, st + 2)
-    if (st + 3 < ns) FLEXCO_STAGE(ring3, ring4, ring2, st + 3)
-    if (st + 4 < ns) FLEXCO_STAGE(ring4, ring5, ring3, st + 4)
+    if (st < ns) FLEXCO_STAGE_PAD(ring0, ring1, ring5, st, FLEXCO_PAD)
+    if (st + 1 < ns) FLEXCO_STAGE_PAD(ring1, ring2, ring0, st + 1, FLEXCO_PAD)
+    if (st + 2 < ns) FLEXCO_STAGE_PAD(ring2, ring3, ring1, st + 2, FLEXCO_PAD)
+    if (st + 3 < ns) FLEXCO_STAGE_PAD(ring3, ring4, ring2, st + 3, FLEXCO_PAD)
+    if (st + 4 < ns) FLEXCO_STAGE_PAD(ring4, ring5, ring3, st + 4, FLEXCO_PAD)
   } else if constexpr (NST == 4) {
     FLEXCO_DMA(ring0, 0)
     FLEXCO_DMA(ring1, 1)
@@ -514,9 +523,9 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
       FLEXCO_STAGE(ring2, ring3, ring1, st + 2)
       FLEXCO_STAGE(ring3, ring0, ring2, st + 3)
     }
-    if (st < ns) FLEXCO_STAGE(ring0, ring1, ring3, st)
-    if (st + 1 < ns) FLEXCO_STAGE(ring1, ring2, ring0, st + 1)
-    if (st + 2 < ns) FLEXCO_STAGE(ring2, ring3, ring1, st + 2)
+    if (st < ns) FLEXCO_STAGE_PAD(ring0, ring1, ring3, st, FLEXCO_PAD)
+    if (st + 1 < ns) FLEXCO_STAGE_PAD(ring1, ring2, ring0, st + 1, FLEXCO_PAD)
+    if (st + 2 < ns) FLEXCO_STAGE_PAD(ring2, ring3, ring1, st + 2, FLEXCO_PAD)
   } else {
     FLEXCO_DMA(ring0, 0)
     FLEXCO_DMA(ring1, 1)
@@ -527,7 +536,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
       FLEXCO_STAGE(ring0, ring1, ring0, st)
       FLEXCO_STAGE(ring1, ring0, ring1, st + 1)
     }
-    if (st < ns) FLEXCO_STAGE(ring0, ring1, ring0, st)
+    if (st < ns) FLEXCO_STAGE_PAD(ring0, ring1, ring0, st, FLEXCO_PAD)
   }
   __builtin_amdgcn_s_waitcnt(FLEXCO_VMCNT(0));   // nothing may land in LDS after the block ends
   FLEXCO_ACC_FENCE
@@ -683,7 +692,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_quad_kernel(const bf16_t* __res
   }
   // fragment q_ (16 rows or columns x 32 of K) of the eight (six) a wavefront reads of a half-tile
 #define Q_READ_ROWS(dst_, buf_, rows_, n_, q_)                                                        \
-  dst_[(q_) % n_][(q_) / n_] = *reinterpret_cast<const bf16x8*>(buf_ + (rows_ + ((q_) % n_) * 16 + l16) * BK + ((((q_) / n_) * 4 + q4) ^ key) * 8);
+  dst_[(q_) % n_][(q_) / n_] = *reinterpret_cast<const frag_t*>(buf_ + (rows_ + ((q_) % n_) * 16 + l16) * BK + ((((q_) / n_) * 4 + q4) ^ key) * 8);
 #define Q_READ_A(dst_, buf_, q_) if ((q_) < 8) Q_READ_ROWS(dst_, buf_, wm * 64, 4, (q_) & 7)
 #define Q_READ_W(dst_, buf_, q_)                                                                      \
   if ((q_) < 2 * HN) {                                                                                \
@@ -692,18 +701,18 @@ __global__ __launch_bounds__(256) void gemm_bf16_quad_kernel(const bf16_t* __res
     } else {                                                                                          \
       const s16x4 lo_ = __builtin_amdgcn_ds_read_tr16_b64_v4i16((FLEXCO_LDS s16x4*)(buf_ + (tr_off[(q_) % HN] + (((q_) / HN) & 1) * 32 * 128)));       \
       const s16x4 hi_ = __builtin_amdgcn_ds_read_tr16_b64_v4i16((FLEXCO_LDS s16x4*)(buf_ + (tr_off[(q_) % HN] + ((((q_) / HN) & 1) * 32 + 4) * 128))); \
-      dst_[(q_) % HN][((q_) / HN) & 1] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo_, hi_, 0, 1, 2, 3, 4, 5, 6, 7)); \
+      dst_[(q_) % HN][((q_) / HN) & 1] = __builtin_shufflevector(__builtin_bit_cast(u32x2, lo_), __builtin_bit_cast(u32x2, hi_), 0, 1, 2, 3); \
     }                                                                                                 \
   }
 #define Q_WAIT(n_) (0x0070 | ((n_) & 15) | (((n_) >> 4) << 14))      /* vmcnt(n), lgkmcnt(0) */
   // a phase: 32 (24) products; behind each second one goes a read for the next phase, then the loads into the buffer the
   // last phase has read.  At its end this wavefront's reads are in registers and its loads of the half-tile that is read
   // next have landed (vm_: instructions of the six younger ones)
-#define Q_PHASE(READ_, rdst_, rbuf_, lbuf_, lsrc_, loff_, nl_, i0_, j0_, a_, w_, vm_)                 \
+#define Q_PHASE(READ_, rdst_, rbuf_, lbuf_, lsrc_, loff_, nl_, i0_, j0_, a_, w_, vm_, pad_)           \
   {                                                                                                   \
     const __amdgpu_buffer_rsrc_t src_ = lsrc_;                                                        \
     _Pragma("unroll") for (int n = 0; n < 8 * HN; ++n) {                                              \
-      FLEXCO_MFMA(acc[i0_ + (n / HN) % 4][j0_ + n % HN], w_[n % HN][n / (4 * HN)], a_[(n / HN) % 4][n / (4 * HN)]) \
+      FLEXCO_MFMA(acc[i0_ + (n / HN) % 4][j0_ + n % HN], w_[n % HN][n / (4 * HN)], a_[(n / HN) % 4][n / (4 * HN)], pad_) \
       if ((n & 1) && n < 16) READ_(rdst_, rbuf_, n >> 1)                                              \
       if ((n & 1) && n >= 16 && n < 16 + 2 * nl_) Q_LOAD(lbuf_, src_, loff_, ((n - 16) >> 1) % nl_)   \
       if (n & 1) __builtin_amdgcn_sched_barrier(0);                                                   \
@@ -721,19 +730,19 @@ __global__ __launch_bounds__(256) void gemm_bf16_quad_kernel(const bf16_t* __res
   }
   // half-tiles in the order they are read: W A A W per stage
   constexpr int VM0 = 3 * NA + 3 * NW, VM1 = 2 * NA + 4 * NW, VM2 = 3 * NA + 3 * NW, VM3 = 4 * NA + 2 * NW;
-#define Q_EVEN(s_)                                                                                    \
+#define Q_EVEN(s_, pad_)                                                                              \
   {                                                                                                   \
-    Q_PHASE(Q_READ_W, fw1, w1e, w0e, GEMM_SRC_W((s_) + 2), ow[0], NW, 0, 0, fa0, fw0, VM0)            \
-    Q_PHASE(Q_READ_A, fa1, a1e, w1e, GEMM_SRC_W((s_) + 2), ow[1], NW, 0, HN, fa0, fw1, VM1)           \
-    Q_PHASE(Q_READ_A, fa0, a0o, a1e, GEMM_SRC_A((s_) + 2), oa[1], NA, 4, HN, fa1, fw1, VM2)           \
-    Q_PHASE(Q_READ_W, fw1, w1o, a0o, GEMM_SRC_A((s_) + 3), oa[0], NA, 4, 0, fa1, fw0, VM3)            \
+    Q_PHASE(Q_READ_W, fw1, w1e, w0e, GEMM_SRC_W((s_) + 2), ow[0], NW, 0, 0, fa0, fw0, VM0, pad_)          \
+    Q_PHASE(Q_READ_A, fa1, a1e, w1e, GEMM_SRC_W((s_) + 2), ow[1], NW, 0, HN, fa0, fw1, VM1, pad_)         \
+    Q_PHASE(Q_READ_A, fa0, a0o, a1e, GEMM_SRC_A((s_) + 2), oa[1], NA, 4, HN, fa1, fw1, VM2, pad_)         \
+    Q_PHASE(Q_READ_W, fw1, w1o, a0o, GEMM_SRC_A((s_) + 3), oa[0], NA, 4, 0, fa1, fw0, VM3, pad_)          \
   }
-#define Q_ODD(s_)                                                                                     \
+#define Q_ODD(s_, pad_)                                                                               \
   {                                                                                                   \
-    Q_PHASE(Q_READ_W, fw0, w0o, w1o, GEMM_SRC_W((s_) + 2), ow[1], NW, 0, HN, fa0, fw1, VM0)           \
-    Q_PHASE(Q_READ_A, fa1, a1o, w0o, GEMM_SRC_W((s_) + 2), ow[0], NW, 0, 0, fa0, fw0, VM1)            \
-    Q_PHASE(Q_READ_A, fa0, a0e, a1o, GEMM_SRC_A((s_) + 2), oa[1], NA, 4, 0, fa1, fw0, VM2)            \
-    Q_PHASE(Q_READ_W, fw0, w0e, a0e, GEMM_SRC_A((s_) + 3), oa[0], NA, 4, HN, fa1, fw1, VM3)           \
+    Q_PHASE(Q_READ_W, fw0, w0o, w1o, GEMM_SRC_W((s_) + 2), ow[1], NW, 0, HN, fa0, fw1, VM0, pad_)         \
+    Q_PHASE(Q_READ_A, fa1, a1o, w0o, GEMM_SRC_W((s_) + 2), ow[0], NW, 0, 0, fa0, fw0, VM1, pad_)          \
+    Q_PHASE(Q_READ_A, fa0, a0e, a1o, GEMM_SRC_A((s_) + 2), oa[1], NA, 4, 0, fa1, fw0, VM2, pad_)          \
+    Q_PHASE(Q_READ_W, fw0, w0e, a0e, GEMM_SRC_A((s_) + 3), oa[0], NA, 4, HN, fa1, fw1, VM3, pad_)         \
   }
   // The rank-r extension's steps (entry, 16 of its rank) in turn, entries that miss the tile left out.  The operands of the
   // first step are fetched here: their round trip lies open behind the main loop otherwise, every tile (1 % of a 1024-row
@@ -752,7 +761,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_quad_kernel(const bf16_t* __res
   if (ext_n > 0) Q_EXT_NEXT(ext_e, ext_k)
   const bool ext_on = ext_n > 0 && ext_e < ext_n;
   if (ext_on) FLEXCO_EXT_LOAD(ext_e, ext_k, xa, xw)
-  bf16x8 fa0[4][2], fa1[4][2], fw0[HN][2], fw1[HN][2];
+  frag_t fa0[4][2], fa1[4][2], fw0[HN][2], fw1[HN][2];
   Q_LOAD_A(a0e, 0, 0) Q_LOAD_W(w0e, 0, 0) Q_LOAD_W(w1e, 1, 0) Q_LOAD_A(a1e, 1, 0)
   Q_LOAD_A(a0o, 0, 1) Q_LOAD_W(w1o, 1, 1) Q_LOAD_W(w0o, 0, 1) Q_LOAD_A(a1o, 1, 1)
   Q_END(VM0)                                     // A0(0), W0(0) have landed
@@ -767,10 +776,10 @@ __global__ __launch_bounds__(256) void gemm_bf16_quad_kernel(const bf16_t* __res
   Q_END(VM3)                                     // W1(0)
   int st = 0;
   for (; st + 1 < ns; st += 2) {
-    Q_EVEN(st)
-    Q_ODD(st + 1)
+    Q_EVEN(st, "")
+    Q_ODD(st + 1, "")
   }
-  if (st < ns) Q_EVEN(st)
+  if (st < ns) Q_EVEN(st, FLEXCO_PAD)
   __builtin_amdgcn_s_waitcnt(Q_WAIT(0));         // nothing may land in LDS after the block ends
   FLEXCO_ACC_FENCE
 

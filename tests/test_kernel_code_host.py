@@ -1,5 +1,5 @@
 """What the built gfx950 code of the LDS-staged kernels does, on every path of it (no GPU): a buffer is handed to new loads
-only when its readers have their data."""
+only when its readers have their data, and the operands of a matrix product are there when it reads them."""
 import os
 import re
 
@@ -51,3 +51,13 @@ def test_attention_buffers_are_not_overwritten_under_a_read(code, name):
     for args, reads in barriers_of(code, name).items():
         assert len(reads) > 2
         assert all(r == (0, 0) for r in reads), (args, reads)
+
+
+# The projections' products are inline assembly, whose operands the compiler's hazard handling does not cover: none may be
+# written by a vector instruction in the two wait states before.
+def test_operands_of_the_products_are_not_written_just_before(code):
+    products = 0
+    for name, ins in code.items():
+        products += sum(op.startswith("v_mfma") for _, op, _ in ins)
+        assert gfx_code.operands_written_too_late(ins, 2) == [], name
+    assert products > 1000
