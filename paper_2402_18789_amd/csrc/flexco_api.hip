@@ -478,12 +478,15 @@ int32_t forward_projection(const flexco_layer_cfg& c, const Adapters& ad, const 
   // left: the caller's next kernel can add the product's partial sums, bias and residual itself; where the product is cut
   // over K (left->splits > 1) they stay in k.gemm_part for it and y is not written
   if (left) *left = SplitSums{nullptr, 1};
-  const bool leave = left && c.dtype == FLEXCO_BF16 && k.gemm_part && gemm_forward_splits(m.T, N, K, k.gemm_part_elems) > 1;
-  auto cut_gemm = [&](const GemmExt* ext) {
-    const int32_t rc = launch_gemm(x, W, y, nullptr, nullptr, m.T, N, K, K, K, N, ldr, false, c.dtype, s, ext, k.gemm_part,
-                                   k.gemm_part_elems, &left->splits);
-    left->part = k.gemm_part;
-    return rc != FLEXCO_OK || left->splits > 1 ? rc : fail(FLEXCO_EINVAL, "forward projection: planned cut over K not taken");
+  auto product = [&](const GemmExt* ext) -> int32_t {
+    if (left && c.dtype == FLEXCO_BF16 && k.gemm_part && gemm_forward_splits(y, m.T, N, K, K, K, N, ext, k.gemm_part_elems) > 1) {
+      const int32_t rc = launch_gemm(x, W, y, nullptr, nullptr, m.T, N, K, K, K, N, 0, false, c.dtype, s, ext, k.gemm_part,
+                                     k.gemm_part_elems, &left->splits);
+      left->part = k.gemm_part;
+      if (rc != FLEXCO_OK || left->splits > 1) return rc;
+      // (came out whole all the same, without bias and residual: once more with them)
+    }
+    return launch_gemm(x, W, y, bias, res, m.T, N, K, K, K, N, ldr, false, c.dtype, s, ext, k.gemm_part, k.gemm_part_elems);
   };
   int act[3], nact = 0;
   for (int i = 0; i < n_targets; ++i)
@@ -529,27 +532,20 @@ int32_t forward_projection(const flexco_layer_cfg& c, const Adapters& ad, const 
       if (rc != FLEXCO_EUNSUPPORTED) return rc;
       clear_error();
     }
-    int32_t rc = leave ? cut_gemm(&ext)
-                       : launch_gemm(x, W, y, bias, res, T, N, K, K, K, N, ldr, false, dt, s, &ext, k.gemm_part, k.gemm_part_elems);
+    const int32_t rc = product(&ext);
     if (rc != FLEXCO_EUNSUPPORTED) return rc;
     clear_error();   // e.g. a target boundary inside a 32-column fragment: run the bypass as separate kernels
-    if (left) *left = SplitSums{nullptr, 1};
   }
   if (glu && nact == 0) {
     const int32_t rc = gated_gemm(c, m, x, K, W, N / 2, nullptr, ft, *glu, s);
     if (rc != FLEXCO_EUNSUPPORTED) return rc;
     clear_error();
   }
-  if (leave && nact == 0) {
-    const int32_t rc = cut_gemm(nullptr);
-    if (rc != FLEXCO_EUNSUPPORTED) return rc;
-    clear_error();
-    *left = SplitSums{nullptr, 1};
-  }
+  if (nact == 0) return product(nullptr);
   FLEXCO_TRY(launch_gemm(x, W, y, bias, res, T, N, K, K, K, N, ldr, false, dt, s, nullptr, k.gemm_part, k.gemm_part_elems));
   // more adapters than the folded path takes: the backward pass (which folds whenever it can) still
   // expects the finetune rows' rank-r products where the state keeps them
-  if (nact > 0 && nused > FUSED_ADAPTERS && lora_mfma_ok(c, K) && ft && m.n_ft > 0 && ft->saved_u[targets[act[0]]]) {
+  if (nused > FUSED_ADAPTERS && lora_mfma_ok(c, K) && ft && m.n_ft > 0 && ft->saved_u[targets[act[0]]]) {
     LoraShrinkArgs sa;
     memset(&sa, 0, sizeof(sa));
     const int a = ad.any_id ? 0 : m.ft_adapter;
@@ -564,7 +560,7 @@ int32_t forward_projection(const flexco_layer_cfg& c, const Adapters& ad, const 
     LR(launch_lora_shrink_mfma(sa, nact, s));
   }
   // unfused fallback: y[rows, col0_t : col0_t + out_t] += scale (x[rows] A_t^T) B_t^T, adapter by adapter
-  for (int iu = 0; iu < nused && nact > 0; ++iu) {
+  for (int iu = 0; iu < nused; ++iu) {
     const int a = used[iu];
     const int32_t* rows = ad.any_id ? m.lora_tok : m.lora_tok + m.adapter_tok_off[a];
     const int n = ad.any_id ? m.n_lora : m.adapter_tok_off[a + 1] - m.adapter_tok_off[a];

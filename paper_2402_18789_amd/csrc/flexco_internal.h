@@ -103,8 +103,9 @@ int32_t launch_gemm_f32_mfma(const void* A, const void* W, void* C, const void* 
 struct GemmLaunchStep { int bm, bn, cols, splits, stages; };
 struct GemmLaunchPlan { int n; GemmLaunchStep step[2]; };
 GemmLaunchPlan plan_gemm_mfma(int M, int N, int K, bool trans_w, size_t part_elems);
-// ranges K is cut into for a forward product, whatever its tiles
-int gemm_forward_splits(int M, int N, int K, size_t part_elems);
+// ranges K is cut into for a forward product without bias and residual, whatever its tiles; 1 where the MFMA path does not
+// take it
+int gemm_forward_splits(const void* C, int M, int N, int K, size_t lda, size_t ldw, size_t ldc, const GemmExt* ext, size_t part_elems);
 // > 0: the product runs on 256 x 256 tiles with K in that many ranges of whole stages instead of by the plan
 int plan_gemm_k_ranges(int M, int N, int K, bool trans_w, size_t part_elems);
 // bf16 MFMA path; returns FLEXCO_EUNSUPPORTED (without launching) for shapes it does not cover

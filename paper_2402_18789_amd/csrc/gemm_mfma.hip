@@ -1087,28 +1087,33 @@ GemmLaunchPlan plan_gemm_mfma(int M, int N, int K, bool trans_w, size_t part_ele
   return pl;
 }
 
-int gemm_forward_splits(int M, int N, int K, size_t part_elems) {
+// The kernels address a tile's rows by 32-bit byte offsets from its first.
+static bool offsets_fit(size_t ld, size_t rows) { return ld <= 0xffff0000u / 2 / rows; }
+
+// Whether the tiled kernels take a product: K in whole 64-wide steps, 16-byte aligned rows (and 8-byte aligned runs of 4
+// output columns in C, bias and residual), tile rows in reach, a rank-r extension of whole steps.
+static bool takes_product(const void* C, const void* bias, const void* residual, int N, int K, size_t lda, size_t ldw,
+                          size_t ldc, size_t ldr, bool trans_w, const GemmExt* ext) {
+  if (K % BK != 0 || lda % 8 != 0 || ldw % 8 != 0 || N % 8 != 0 || ldc % 4 != 0 || (residual && ldr % 4 != 0) ||
+      ((uintptr_t)C & 7) || ((uintptr_t)bias & 7) || ((uintptr_t)residual & 7))
+    return false;
+  return offsets_fit(lda, 256) && offsets_fit(ldw, 256) && (!ext || ext_fits(*ext, trans_w, N));
+}
+
+int gemm_forward_splits(const void* C, int M, int N, int K, size_t lda, size_t ldw, size_t ldc, const GemmExt* ext, size_t part_elems) {
+  if (!takes_product(C, nullptr, nullptr, N, K, lda, ldw, ldc, 0, false, ext)) return 1;
   if (M <= THIN_ROWS) return thin_splits(M, N, K, part_elems);
   const int ranges = plan_gemm_k_ranges(M, N, K, false, part_elems);
   return ranges ? ranges : plan_gemm_mfma(M, N, K, false, part_elems).step[0].splits;
 }
 
-// The kernels address a tile's rows by 32-bit byte offsets from its first.
-static bool offsets_fit(size_t ld, size_t rows) { return ld <= 0xffff0000u / 2 / rows; }
-
 int32_t launch_gemm_mfma(const void* A, const void* W, void* C, const void* bias, const void* residual, int M, int N,
                          int K, size_t lda, size_t ldw, size_t ldc, size_t ldr, bool trans_w, const GemmExt* ext_in,
                          hipStream_t s, float* part, size_t part_elems, int timer_id, int* splits_out) {
   if (splits_out) *splits_out = 1;
-  // shapes the tiled kernel covers: K in whole 64-wide steps, 16-byte aligned rows
-  // (and 8-byte aligned runs of 4 output columns in C, bias and residual)
-  if (K % BK != 0 || lda % 8 != 0 || ldw % 8 != 0 || N % 8 != 0 || ldc % 4 != 0 || (residual && ldr % 4 != 0) ||
-      ((uintptr_t)C & 7) || ((uintptr_t)bias & 7) || ((uintptr_t)residual & 7))
-    return FLEXCO_EUNSUPPORTED;
-  if (!offsets_fit(lda, 256) || !offsets_fit(ldw, 256)) return FLEXCO_EUNSUPPORTED;
+  if (!takes_product(C, bias, residual, N, K, lda, ldw, ldc, ldr, trans_w, ext_in)) return FLEXCO_EUNSUPPORTED;
   GemmExt ext;
   if (ext_in) ext = *ext_in; else ext.n = 0;
-  if (!ext_fits(ext, trans_w, N)) return FLEXCO_EUNSUPPORTED;
   // splits_out: the caller's next kernel adds the partial sums itself (part[split][M][N], in split order) and
   // the reduction launch is left out; bias and residual are then not applied
   if (!trans_w && M <= THIN_ROWS) {

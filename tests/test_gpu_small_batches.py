@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 
 if torch.cuda.is_available():
     import paper_2402_18789_amd.binding as B
-    from gpu_common import TOL, assert_close
+    from gpu_common import Case, TOL, assert_close
     from test_gpu_parity import attention_case, run_layer_case
 
 # K of 32 stages: three ranges of it per projection at up to 64 tokens
@@ -25,6 +25,19 @@ def test_layer_partial_sums_left_to_the_next_kernel(chunk, window):
     b = gen.batch_scaled(17, 4, 3, 90, [(0, chunk, 2 * chunk)], [(0, window, 2 * window)])
     assert b.n_tokens <= 256
     run_layer_case(WIDE, b, ft_window=window, prefill_chunk=chunk, bwd_windows=[window, window], seed=17)
+
+
+# K that is no multiple of 64 runs on the type-generic kernel, uncut, whatever the planner of the matrix-core path would
+# do with it: the qkv and down products (hidden, ffn), then o (q_dim = 27 x 48); few tokens, no adapter rows, a bias
+@pytest.mark.parametrize("hidden,heads,kv,d", [(2056, 16, 4, 128), (2048, 27, 9, 48), (1352, 11, 11, 128)])
+def test_layer_of_a_width_the_matrix_cores_do_not_take(hidden, heads, kv, d):
+    cfg = WIDE.with_(name=f"odd_{hidden}_{heads * d}", hidden=hidden, n_q_heads=heads, n_kv_heads=kv, head_dim=d, ffn=1400, lora_targets=())
+    for n_decode, chunk in ((8, 0), (40, 8), (64, 36), (64, 236)):
+        print(f"{cfg.name}: {n_decode} decode tokens, a chunk of {chunk}", flush=True)
+        b = gen.mixed_batch(cfg.page_size, 23, decode_ctx=tuple(range(3, 3 + n_decode)), prefill=[(5, chunk, 5 + chunk)] if chunk else [])
+        case = Case(cfg, b, seed=23)
+        got, ref, _ = case.forward(b, gen.layer_input(cfg, 23, b.n_tokens))
+        assert_close("y", got, ref, TOL["bf16"])
 
 
 # (split: pages of 16 keys) contexts of one split, then of up to six, then of 1, 2, 8, 9 and 12
