@@ -220,7 +220,7 @@ typedef struct flexco_ft_state {
 /* Message for the last failing call on this thread ("" if none). */
 const char* flexco_last_error(void);
 
-/* Library ABI version (increases when a struct above changes). */
+/* Library ABI version (increases when a struct above changes or an entry point is added; 9: flexco_gemm_k_ranges). */
 int32_t flexco_abi_version(void);
 
 /* Upper bound of the int32 words flexco_build_maps needs for `desc` (host only). */

@@ -34,6 +34,18 @@ def test_library_exports_every_declared_symbol():
     assert B.flexco_abi_version() == B.ABI_VERSION
 
 
+# the version an entry point came with: a library without it then fails on the version, not on the missing name
+ADDED_IN = {"flexco_gemm_plan": 8, "flexco_gemm_k_ranges": 9}
+EXPORTS_UP_TO = {9: 42}                       # entry points of the present version
+
+
+@full_library
+def test_a_new_entry_point_raises_the_version():
+    for name, version in ADDED_IN.items():
+        assert name in B.EXPORTS and B.flexco_abi_version() >= version, name
+    assert len(B.EXPORTS) == EXPORTS_UP_TO[B.flexco_abi_version()], "an entry point came or went: raise the ABI version"
+
+
 def c_maps(batch, nq, nkv, split=0):
     desc, keep = B.make_batch_desc([r.kind for r in batch.requests], [r.start_pos for r in batch.requests],
                                    [r.n_new for r in batch.requests], [r.adapter for r in batch.requests],
