@@ -430,12 +430,13 @@ int32_t flexco_gemm(const void* A, const void* W, void* C, const void* bias, con
 /* How the bf16 matrix-core path would tile a product of these sizes (host arithmetic only: no GPU is touched, nothing
  * is launched) - the plan flexco_gemm, the frozen base projections over all tokens of the batch (Sec. 6.2; the gated
  * gate/up projection with N = 2 ffn) and the window backward's input-gradient products (Alg. 2; trans_w = 1) follow,
- * but for the products flexco_gemm_k_ranges names and forward products of at most 64 rows (64 x 128 tiles).
+ * but for the products flexco_gemm_k_ranges names.
  * part_elems: floats of split-K scratch the caller has (0 = none: flexco_gemm; the layer calls bring rows x 65536 for
  * windows of at most 256 rows and rows x 32768 for longer ones and for forward batches of at most 256 tokens; larger
  * forward batches bring rows x ffn for all but the gate/up projection).  out (host, 11 ints): out[0] = launches (1 or 2,
  * side by side in the output columns), then per launch: tile rows, tile columns, output columns covered, blocks K is
- * cut over, stages of the LDS ring; unused entries 0.  Errors: EINVAL (NULL, non-positive sizes), ESHAPE (K not a
+ * cut over (in whole 64-wide stages, equal but for the 64-row tiles, whose ranges differ by one at most), stages of the
+ * LDS ring; unused entries 0.  Errors: EINVAL (NULL, non-positive sizes), ESHAPE (K not a
  * multiple of 64 or N not a multiple of 8: such products run on the type-generic kernels). */
 int32_t flexco_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t trans_w, int64_t part_elems, int32_t* out);
 /* Into how many ranges of whole 64-wide stages, equal to within one, the matrix-core path cuts K to run the same product

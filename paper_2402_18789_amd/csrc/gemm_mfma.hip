@@ -987,6 +987,15 @@ static GemmPlan plan_forward(int M, int N, int K) {
   return best;
 }
 
+// Forward products of at most THIN_ROWS rows run on 64 x 128 tiles, K cut until the tiles cover the chip, ten stages or
+// more to a block (4096 columns, K = 4096: 11.8 - 12.6 us with 4 to 8 ranges, 15.9 with 12; K = 14336: 35, 29, 26 us with 4, 5, 8).
+constexpr int THIN_ROWS = 64;
+static int thin_splits(int M, int N, int K, size_t part_elems) {
+  int sp = std::min(256 / ((N + 127) / 128), K / BK / 10);
+  if (sp > 1) sp = (int)std::min<size_t>(sp, part_elems / ((size_t)M * N));
+  return std::max(sp, 1);
+}
+
 // Ranges of K in whole stages, equal to within one, to run a product on 256 x 256 tiles with, or 0: the launch plan
 // below is as good.  For products whose 256 x 256 tiles leave CUs idle (or whose last round does), at the price of partial
 // sums.  1: the tiles as they are, input-gradient form only (the forward plan has that choice).
@@ -994,6 +1003,7 @@ static GemmPlan plan_forward(int M, int N, int K) {
 // 1405 x 5120 x 27648 400 -> 312 (2); input gradient 512 x 4096 x 128256 625 -> 419 (8), 512 x 4096 x 28672 152 -> 103 (8),
 // 1024 x 5120 x 7168 126 -> 74 (3), 1024 x 5120 x 5120 100 -> 60 (3), 256 x 4096 x 28672 91 -> 77 (12).
 int plan_gemm_k_ranges(int M, int N, int K, bool trans_w, size_t part_elems) {
+  if (!trans_w && M <= THIN_ROWS) return 0;         // the plan's 64 x 128 tiles
   const int ns = K / BK;
   const long tiles = (long)((M + 255) / 256) * ((N + 255) / 256);
   const GemmLaunchPlan pl = plan_gemm_mfma(M, N, K, trans_w, part_elems);
@@ -1016,15 +1026,6 @@ int plan_gemm_k_ranges(int M, int N, int K, bool trans_w, size_t part_elems) {
     if (t < us) { us = t; best = r; }
   }
   return best;
-}
-
-// Forward products of at most THIN_ROWS rows run on 64 x 128 tiles, K cut until the tiles cover the chip, ten stages or
-// more to a block (4096 columns, K = 4096: 11.8 - 12.6 us with 4 to 8 ranges, 15.9 with 12; K = 14336: 35, 29, 26 us with 4, 5, 8).
-constexpr int THIN_ROWS = 64;
-static int thin_splits(int M, int N, int K, size_t part_elems) {
-  int sp = std::min(256 / ((N + 127) / 128), K / BK / 10);
-  if (sp > 1) sp = (int)std::min<size_t>(sp, part_elems / ((size_t)M * N));
-  return std::max(sp, 1);
 }
 
 // What launch_gemm_mfma does for a shape: one or two launches, each a tile shape over a range of output columns,
@@ -1061,6 +1062,10 @@ GemmLaunchPlan plan_gemm_mfma(int M, int N, int K, bool trans_w, size_t part_ele
     }
     if (sp256) add(256, 256, N, sp256, 2);
     else add(128, 128, N, sp, 2);
+    return pl;
+  }
+  if (M <= THIN_ROWS) {
+    add(THIN_ROWS, 128, N, thin_splits(M, N, K, part_elems), 6);
     return pl;
   }
   // A batch of few tokens (decode-only iterations) has one or two row tiles and far fewer output tiles
@@ -1102,7 +1107,6 @@ static bool takes_product(const void* C, const void* bias, const void* residual,
 
 int gemm_forward_splits(const void* C, int M, int N, int K, size_t lda, size_t ldw, size_t ldc, const GemmExt* ext, size_t part_elems) {
   if (!takes_product(C, nullptr, nullptr, N, K, lda, ldw, ldc, 0, false, ext)) return 1;
-  if (M <= THIN_ROWS) return thin_splits(M, N, K, part_elems);
   const int ranges = plan_gemm_k_ranges(M, N, K, false, part_elems);
   return ranges ? ranges : plan_gemm_mfma(M, N, K, false, part_elems).step[0].splits;
 }
@@ -1116,13 +1120,6 @@ int32_t launch_gemm_mfma(const void* A, const void* W, void* C, const void* bias
   if (ext_in) ext = *ext_in; else ext.n = 0;
   // splits_out: the caller's next kernel adds the partial sums itself (part[split][M][N], in split order) and
   // the reduction launch is left out; bias and residual are then not applied
-  if (!trans_w && M <= THIN_ROWS) {
-    const int sp = thin_splits(M, N, K, part ? part_elems : 0);
-    const bool leave = splits_out && sp > 1 && !bias && !residual;
-    if (leave) *splits_out = sp;
-    return launch_cfg<THIN_ROWS, 128, false, false, 6>(A, W, C, bias, residual, M, N, K, lda, ldw, ldc, ldr, ext, s, timer_id, part, sp,
-                                                       true, nullptr, leave);
-  }
   const int ranges = plan_gemm_k_ranges(M, N, K, trans_w, part ? part_elems : 0);
   if (ranges) {
     const bool leave = splits_out && ranges > 1 && !bias && !residual;
@@ -1141,6 +1138,13 @@ int32_t launch_gemm_mfma(const void* A, const void* W, void* C, const void* bias
                                         true, nullptr, leave);
     return launch_cfg<128, 128, true>(A, W, C, bias, residual, M, N, K, lda, ldw, ldc, ldr, ext, s, timer_id, part, st.splits, true,
                                       nullptr, leave);
+  }
+  if (pl.step[0].bm == THIN_ROWS) {
+    const int sp = pl.step[0].splits;
+    const bool leave = splits_out && sp > 1 && !bias && !residual;
+    if (leave) *splits_out = sp;
+    return launch_cfg<THIN_ROWS, 128, false, false, 6>(A, W, C, bias, residual, M, N, K, lda, ldw, ldc, ldr, ext, s, timer_id, part, sp,
+                                                       true, nullptr, leave);
   }
   if (pl.step[0].splits > 1) {
     const bool leave = splits_out && !bias && !residual;
@@ -1190,10 +1194,10 @@ int32_t launch_gemm_glu_mfma(const void* A, const void* W, void* act, int M, int
   glu.F = F; glu.col0 = 0; glu.save_gate = (bf16_t*)save_gate; glu.save_up = (bf16_t*)save_up;
   glu.save_row0 = save_row0; glu.save_rows = save_gate ? save_rows : 0; glu.ld_save = ld_save;
   const int N = 2 * F;
-  if (M <= THIN_ROWS)
+  const GemmLaunchPlan pl = plan_gemm_mfma(M, N, K, false, 0);
+  if (pl.step[0].bm == THIN_ROWS)
     return launch_cfg<THIN_ROWS, 128, false, true, 6>(A, W, act, nullptr, nullptr, M, N, K, lda, ldw, ld_act, 0, ext, s, timer_id,
                                                       nullptr, 1, true, &glu);
-  const GemmLaunchPlan pl = plan_gemm_mfma(M, N, K, false, 0);
   int c0 = 0;                                       // interleaved columns done = 2 x the act columns done
   for (int i = 0; i < pl.n; ++i) {
     const GemmLaunchStep& st = pl.step[i];

@@ -48,16 +48,19 @@ def test_input_gradient_plans_by_window_length():
 
 def test_decode_only_batches_cut_k():
     c2 = CONFIGS["c2_llama8b_layer"]
-    (bm, bn, cols, splits, stages), = B.flexco_gemm_plan(16, c2.q_dim + 2 * c2.kv_dim, c2.hidden, 0, 16 * SPLITK_COLS)
-    assert (bm, bn, cols) == (128, 128, 6144) and splits > 1
-    assert B.flexco_gemm_plan(16, 6144, c2.hidden, 0, 0) == [(128, 128, 6144, 1, 4)]   # no scratch, no cut
+    # up to 64 rows: the 64-row tile; up to 256: the 128-row tile
+    for M, tile in ((16, (64, 128)), (64, (64, 128)), (65, (128, 128)), (256, (128, 128))):
+        (bm, bn, cols, splits, stages), = B.flexco_gemm_plan(M, c2.q_dim + 2 * c2.kv_dim, c2.hidden, 0, M * SPLITK_COLS)
+        assert (bm, bn, cols) == tile + (6144,) and splits > 1
+    assert B.flexco_gemm_plan(16, 6144, c2.hidden, 0, 0) == [(64, 128, 6144, 1, 6)]    # no scratch, no cut
+    assert B.flexco_gemm_plan(100, 6144, c2.hidden, 0, 0) == [(128, 128, 6144, 1, 4)]
 
 
 def test_any_plan_is_well_formed():
     g = np.random.default_rng(7)
-    shapes = {(128, 128), (128, 192), (256, 192), (256, 256)}
-    for _ in range(3000):
-        M = int(g.integers(1, 5000))
+    shapes = {(64, 128), (128, 128), (128, 192), (256, 192), (256, 256)}
+    for n in range(3000):
+        M = int(g.integers(1, 5000 if n % 10 else 70))
         N = 8 * int(g.integers(1, 8000))
         K = 64 * int(g.integers(1, 900))
         trans = int(g.integers(0, 2))
@@ -66,12 +69,13 @@ def test_any_plan_is_well_formed():
         assert 1 <= len(plan) <= 2, (M, N, K, trans, pe, plan)
         assert sum(p[2] for p in plan) == N
         for i, (bm, bn, cols, splits, stages) in enumerate(plan):
-            assert (bm, bn) in shapes and cols > 0 and stages in (2, 4)
+            assert (bm, bn) in shapes and cols > 0 and stages in ((6,) if bm == 64 else (2, 4))
+            assert (bm == 64) == (M <= 64 and not trans)
             if trans:
                 assert (bm, bn) in ((128, 128), (256, 256)) and len(plan) == 1
             if i + 1 < len(plan):
                 assert cols % bn == 0                       # the next launch starts at a tile boundary
-            assert splits >= 1 and K % (64 * splits) == 0
+            assert splits >= 1 and (bm == 64 or K % (64 * splits) == 0)
             if splits > 1:
                 assert splits * M * N <= pe and len(plan) == 1
                 assert K // splits >= 4 * 64
