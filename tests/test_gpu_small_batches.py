@@ -40,6 +40,30 @@ def test_layer_of_a_width_the_matrix_cores_do_not_take(hidden, heads, kv, d):
         assert_close("y", got, ref, TOL["bf16"])
 
 
+# More than 256 tokens: the [T, 2 ffn] buffer of gate and up is lent to the other projections, whose sums of unequal ranges
+# of K lie in it until the norm (o) or the rotation (qkv) has read them; with the finetune window's adapter rows folded
+# in, and without adapters
+O_CUT = CONFIGS["c2_llama8b_layer"].with_(name="o_cut", hidden=512, n_q_heads=64, n_kv_heads=8, head_dim=128, ffn=2816, qkv_bias=True,
+                                          lora_targets=("q", "v", "o", "gate", "down"))
+QKV_CUT = O_CUT.with_(name="qkv_cut", hidden=4096, n_q_heads=4, n_kv_heads=1)
+
+
+@pytest.mark.parametrize("adapter", [True, False])
+@pytest.mark.parametrize("cfg", [O_CUT, QKV_CUT])
+def test_layer_partial_sums_in_the_lent_buffer(cfg, adapter):
+    b = gen.batch_scaled(29, 5, 3, 90, [(0, 131, 262)], [(0, 141, 282)])
+    T = b.n_tokens
+    assert T == 277
+    cuts = {"qkv": B.flexco_gemm_k_ranges(T, cfg.q_dim + 2 * cfg.kv_dim, cfg.hidden, 0, T * cfg.ffn),
+            "o": B.flexco_gemm_k_ranges(T, cfg.hidden, cfg.q_dim, 0, T * cfg.ffn)}
+    print(f"layer of {T} tokens, {cfg.name}, cuts {cuts}, adapter {adapter}", flush=True)
+    r, K = (cuts["o"], cfg.q_dim) if cfg is O_CUT else (cuts["qkv"], cfg.hidden)
+    assert r > 1 and (K // 64) % r != 0
+    if not adapter:
+        cfg = cfg.with_(name=cfg.name + "_base", lora_targets=())
+    run_layer_case(cfg, b, ft_window=141, prefill_chunk=131, bwd_windows=[141, 141], seed=29)
+
+
 # (split: pages of 16 keys) contexts of one split, then of up to six, then of 1, 2, 8, 9 and 12
 @pytest.mark.parametrize("split", [24, 4, 2])
 def test_attention_merge_of_many_splits(split):
