@@ -1073,52 +1073,47 @@ __global__ __launch_bounds__(256) void lora_expand_kernel(LoraBatch b, int n, in
   }
 }
 
-// Both of a few rows in one launch: a block per row (and product) that keeps u between them.
-//   FWD:  u = x A^T;  y += scale u B^T               (down.p[z]: x, A, u;  up.p[z]: B, y)
-//   else: the gradients' sums of one row, u_z = x_z A_z^T and t_z = dy_z B_z (down.p[2 z], down.p[2 z + 1]), and
-//         dx += scale sum_z t_z A_z (up.p[z], one dx for all of them)
-template <typename T, int R, bool FWD>
+// Both of a few rows in one launch: u = x A^T, then y += scale u B^T, a block per row and product (down.p[z]: x, A, u;
+// up.p[z]: B, y) that keeps u between them.
+template <typename T, int R>
 __global__ __launch_bounds__(256) void lora_rows_kernel(LoraBatch down, LoraBatch up, int r, float scale,
                                                         const int32_t* __restrict__ row_idx) {
   __shared__ float red[4][R], us[R];
   const size_t mo = blockIdx.x;
   const size_t m = row_idx ? (size_t)row_idx[mo] : mo;
-  for (int z = FWD ? blockIdx.y : 0; z < (FWD ? (int)blockIdx.y + 1 : down.count); ++z) {
-    const LoraProduct& p = down.p[z];
-    const T* __restrict__ X = (const T*)p.X + m * p.ldx;
-    const T* __restrict__ S = (const T*)p.S;
-    float acc[R];
+  const LoraProduct& p = down.p[blockIdx.y];
+  const T* __restrict__ X = (const T*)p.X + m * p.ldx;
+  const T* __restrict__ S = (const T*)p.S;
+  float acc[R];
 #pragma unroll
-    for (int j = 0; j < R; ++j) acc[j] = 0.f;
-    for (int i = threadIdx.x; i < p.n_long; i += 256) {
-      const float xv = ld(X + i);
+  for (int j = 0; j < R; ++j) acc[j] = 0.f;
+  for (int i = threadIdx.x; i < p.n_long; i += 256) {
+    const float xv = ld(X + i);
 #pragma unroll
-      for (int j = 0; j < R; ++j)
-        if (j < r) acc[j] += xv * ld(S + (size_t)i * p.s_i + (size_t)j * p.s_j);
-    }
+    for (int j = 0; j < R; ++j)
+      if (j < r) acc[j] += xv * ld(S + (size_t)i * p.s_i + (size_t)j * p.s_j);
+  }
 #pragma unroll
-    for (int j = 0; j < R; ++j) {
-      const float v = wave_sum(acc[j]);
-      if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][j] = v;
-    }
-    __syncthreads();
-    if (threadIdx.x < R) {
-      const float v = red[0][threadIdx.x] + red[1][threadIdx.x] + red[2][threadIdx.x] + red[3][threadIdx.x];
-      us[threadIdx.x] = v;                          // (ranks past r: zero)
-      if ((int)threadIdx.x < r) p.U[mo * r + threadIdx.x] = v;
-    }
-    __syncthreads();
-    if (!FWD && (z & 1) == 0) continue;             // (a u: nothing to add anywhere)
-    const LoraProduct& o = up.p[FWD ? z : z >> 1];
-    const T* __restrict__ B = (const T*)o.S;
-    for (int i = threadIdx.x; i < o.n_long; i += 256) {
-      float a = 0.f;
+  for (int j = 0; j < R; ++j) {
+    const float v = wave_sum(acc[j]);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][j] = v;
+  }
+  __syncthreads();
+  if (threadIdx.x < R) {
+    const float v = red[0][threadIdx.x] + red[1][threadIdx.x] + red[2][threadIdx.x] + red[3][threadIdx.x];
+    us[threadIdx.x] = v;                          // (ranks past r: zero)
+    if ((int)threadIdx.x < r) p.U[mo * r + threadIdx.x] = v;
+  }
+  __syncthreads();
+  const LoraProduct& o = up.p[blockIdx.y];
+  const T* __restrict__ B = (const T*)o.S;
+  for (int i = threadIdx.x; i < o.n_long; i += 256) {
+    float a = 0.f;
 #pragma unroll
-      for (int j = 0; j < R; ++j)
-        if (j < r) a += us[j] * ld(B + (size_t)i * o.s_i + (size_t)j * o.s_j);
-      T* y = (T*)o.Y + m * o.ldy + i;
-      st(y, ld(y) + scale * a);
-    }
+    for (int j = 0; j < R; ++j)
+      if (j < r) a += us[j] * ld(B + (size_t)i * o.s_i + (size_t)j * o.s_j);
+    T* y = (T*)o.Y + m * o.ldy + i;
+    st(y, ld(y) + scale * a);
   }
 }
 
@@ -1499,16 +1494,23 @@ static int32_t lora_ops(int op, const LoraBatch& b, bool shared_y, int n, int r,
 // Up to this many rows the two launches' cost is that they are two (4 - 5 us of host and queue each), and the matrices are
 // read once per row from L2; beyond, the row blocks of the separate expand kernel read them a sixteenth as often.
 constexpr int LORA_ROWS_MAX = 256;
-template <bool FWD>
+// A row's block walks both products alone, and wide or high-rank ones take longer that way than the launch they save: up
+// to this many passes of 256 elements x ranks (rounded up as the kernels do).  Layer forward of 4 / 32 / 128 / 250 rows,
+// one launch against two, us: width 256, rank 8 (32) 73 / 105 / 122 / 140 against 85 / 122 / 143 / 158; width 512, ffn 1376,
+// rank 8 (64) 88 / 130 / 175 / 194 against 83 / 135 / 185 / 199; the same, rank 64 (512) 302 / 450 / 509 / 677 against
+// 211 / 373 / 426 / 446; 8 rows at the 8B shape, rank 8 (576) 643 against 471.
+constexpr int LORA_ROWS_WORK = 64;
+static int lora_rows_work(int in, int out, int r) {
+  return ((in + 255) / 256 + (out + 255) / 256) * (r <= 8 ? 8 : r <= 16 ? 16 : r <= 32 ? 32 : 64);
+}
 static int32_t lora_rows(const LoraBatch& down, const LoraBatch& up, int n, int r, float scale, int dtype, const int32_t* row_idx,
                          hipStream_t s) {
-  const dim3 grid(n, FWD ? down.count : 1);
+  const dim3 grid(n, down.count);
 #define FLEXCO_LORA_ROWS(R_) \
-  DISPATCH_T(dtype, hipLaunchKernelGGL((lora_rows_kernel<T, R_, FWD>), grid, dim3(256), 0, s, down, up, r, scale, row_idx))
+  DISPATCH_T(dtype, hipLaunchKernelGGL((lora_rows_kernel<T, R_>), grid, dim3(256), 0, s, down, up, r, scale, row_idx))
   if (r <= 8) FLEXCO_LORA_ROWS(8);
   else if (r <= 16) FLEXCO_LORA_ROWS(16);
-  else if (r <= 32) FLEXCO_LORA_ROWS(32);
-  else FLEXCO_LORA_ROWS(64);
+  else FLEXCO_LORA_ROWS(32);                     // (ranks past 32 have too much work at any width)
 #undef FLEXCO_LORA_ROWS
   return post_launch("lora_rows");
 }
@@ -1549,10 +1551,13 @@ int32_t launch_lora_apply(const LoraTarget* tg, int count, int n, int r, float s
     up.p[z] = {nullptr, 0, t.B, (size_t)r, 1, t.u, t.y, t.ldy, nullptr, 0, 0, t.out};
   }
   if (n == 0 || count == 0) return FLEXCO_OK;
-  if (n <= LORA_ROWS_MAX) return lora_rows<true>(down, up, n, r, scale, dtype, row_idx, s);
+  int work = 0;      // (the targets' blocks run side by side)
+  for (int z = 0; z < count; ++z) work = std::max(work, lora_rows_work(tg[z].in, tg[z].out, r));
+  if (n <= LORA_ROWS_MAX && work <= LORA_ROWS_WORK) return lora_rows(down, up, n, r, scale, dtype, row_idx, s);
   const int32_t rc = lora_dispatch(0, down, false, n, r, 0.f, dtype, s, row_idx);
   return rc ? rc : lora_dispatch(1, up, count == 1, n, r, scale, dtype, s, row_idx);
 }
+
 int32_t launch_lora_shrink(const void* x, size_t ldx, const void* A, float* u, int n, int in, int r, int dtype,
                            const int32_t* row_idx, hipStream_t s) {
   LoraBatch b;
@@ -1586,12 +1591,9 @@ int32_t launch_lora_bwd(const LoraTarget* tg, int count, void* dx, size_t lddx, 
     back.p[z] = {nullptr, 0, t.A, 1, (size_t)t.in, t.t, dx, lddx, nullptr, 0, 0, t.in};
   }
   int32_t rc;
-  // (few rows with a dx to add to: u, t and dx in one launch.  The outer products read dy and x, which may be dx itself -
-  // the adapter's in-place call, which has relu - so they cannot come first there.)
-  if (dx && !relu && n > 0 && n <= LORA_ROWS_MAX) {
-    if ((rc = lora_rows<false>(long_sums, back, n, r, scale, dtype, nullptr, s))) return rc;
-    return lora_dispatch(2, outer, false, n, r, scale, dtype, s);
-  }
+  // (u, t and dx of a row in one launch, as the forward pass does: no faster at width 256, rank 8, and everywhere else
+  // slower, a window of 64 rows at the 8B shape, rank 8, 895 us against 549.  The outer products read dy and x, which may be dx
+  // itself - the adapter's in-place call.)
   if ((rc = lora_dispatch(0, long_sums, false, n, r, 0.f, dtype, s))) return rc;
   if (relu && (rc = launch_relu_mask(tg[0].u, tg[0].t, (size_t)n * r, s))) return rc;
   if ((rc = lora_dispatch(2, outer, false, n, r, scale, dtype, s))) return rc;

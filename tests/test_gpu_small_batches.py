@@ -75,9 +75,10 @@ def test_attention_merge_of_many_splits(split):
     assert float(np.max(np.abs(lse - lse_o))) <= 2e-2
 
 
-# the type-generic LoRA kernels: up to 256 rows in one launch with the products' sums kept in LDS, more in two
+# the type-generic LoRA kernels: up to 256 rows of narrow products of a low rank (at these widths: every target at ranks of
+# up to 16, q, v and o at ranks of up to 32) in one launch with the products' sums kept in LDS, others in two
 @pytest.mark.parametrize("window", [256, 257])
-@pytest.mark.parametrize("rank", [5, 24])
+@pytest.mark.parametrize("rank", [5, 16, 24, 40])
 def test_generic_lora_rows(window, rank):
     print(f"type-generic LoRA of rank {rank}, windows of {window}", flush=True)
     cfg = CONFIGS["c1_tiny_f32"].with_(name="tiny_r%d" % rank, lora_rank=rank, lora_targets=("q", "v", "o", "gate", "up", "down"))
