@@ -246,8 +246,12 @@ extern "C" int32_t flexco_lm_loss(const flexco_lm_head* head, const void* x, con
     KernelTimerScope ts(FLEXCO_K_ELEMWISE, s);
     const bool vec = V % (dt == FLEXCO_BF16 ? 8 : 4) == 0;   // rows of z then start 16-byte aligned
     const int regs = (V + CE_REG_THREADS * 8 - 1) / (CE_REG_THREADS * 8);      // 16-byte pieces of a row per thread
-    if (dt == FLEXCO_BF16 && vec && regs > 2 && regs <= 19) {
-      // (shorter rows would leave most of a block's threads idle, longer ones do not fit the registers)
+    // Rows in registers: from 65537 logits on, up to what fits; down to 24577 if there are no more rows than CUs.  (More rows
+    // are better off with blocks of 512 threads, which share a CU.  Loss head of hidden size 1024, with against without, us: 1024 rows
+    // of 24000 161 / 150, 32000 194 / 186, 65536 345 / 343, 131072 639 / 645; 256 rows of 24000 82 / 81, 50304 119 / 120,
+    // 131072 275 / 286; 16 rows of 32000 76 / 78.)
+    const bool in_regs = dt == FLEXCO_BF16 && vec && regs <= 19 && (regs > 8 || (regs > 3 && n <= 256));
+    if (in_regs) {
       if (regs <= 8) hipLaunchKernelGGL(ce_rows_reg_kernel<8>, dim3(n), dim3(CE_REG_THREADS), 0, s, (bf16_t*)k.z, targets, k.row_loss, V, scale);
       else if (regs <= 16) hipLaunchKernelGGL(ce_rows_reg_kernel<16>, dim3(n), dim3(CE_REG_THREADS), 0, s, (bf16_t*)k.z, targets, k.row_loss, V, scale);
       else hipLaunchKernelGGL(ce_rows_reg_kernel<19>, dim3(n), dim3(CE_REG_THREADS), 0, s, (bf16_t*)k.z, targets, k.row_loss, V, scale);

@@ -69,9 +69,10 @@ def test_input_gradient_in_unequal_ranges(n, H, V):
     run_loss("bf16", n, H, V, seed=3)
 
 
-# rows of logits that a block holds in registers: 3 and 8, 9 and 16, 17 and 19 pieces of 8192 (the last ragged or whole),
-# and the first length past them
-@pytest.mark.parametrize("V", [16392, 65536, 65544, 131072, 131080, 155648, 155656])
-def test_loss_rows(V):
-    print(f"loss head V={V}", flush=True)
-    run_loss("bf16", 5, 256, V, seed=4, ignore=(1, 4))
+# rows of logits that a block holds in registers: 4 and 8, 9 and 16, 17 and 19 pieces of 8192 (the last ragged or whole),
+# and the first lengths and the first number of rows past them
+@pytest.mark.parametrize("n,V", [(5, V) for V in (16392, 24576, 24584, 65536, 65544, 131072, 131080, 155648, 155656)]
+                         + [(256, 24584), (257, 24584), (257, 65544)])
+def test_loss_rows(n, V):
+    print(f"loss head n={n} V={V}", flush=True)
+    run_loss("bf16", n, 256, V, seed=4, ignore=(1, 4))
