@@ -362,7 +362,7 @@ def measured_ceilings(B, torch):
             "k_loop_without_memory_wait_tile128_tflops": best_lds[(128, True)],
             "k_loop_without_memory_wait_tile256_tflops": best_lds[(256, True)], "hbm_read_stream_gbs": best_read,
             "device_copy_gbs": best_copy,
-            "what": "probe kernels of the library: 256 blocks x 4 wavefronts of back-to-back v_mfma_f32_32x32x16_bf16 on "
+            "what": "probe kernels of the library: 256 blocks x 4 wavefronts of back-to-back v_mfma_f32_16x16x32_bf16 on "
                     "register operands in [-1, 1); the same products with operands read from LDS in the projection "
                     "kernels' pattern for a 128 x 128 and a 256 x 256 block tile, one slice ahead (no global traffic, no "
                     "barriers), and with a stage of tile loads into LDS from cache-resident memory plus a barrier per "

@@ -648,12 +648,12 @@ int32_t flexco_model_backward(const flexco_layer_cfg* cfg, const flexco_model_la
  * sustains for the two resources the rooflines are quoted against.  Both only enqueue one kernel
  * on `stream`; the caller times it with events.  sink: device, >= 4 bytes, never written in
  * practice (it keeps the compiler from removing the work).
- *   flexco_probe_mfma: `blocks` blocks of 4 wavefronts, each `iters` x 16 back-to-back
- *     v_mfma_f32_32x32x16_bf16 on register operands with values in [-1, 1); *flops = work enqueued.
+ *   flexco_probe_mfma: `blocks` blocks of 4 wavefronts, each `iters` x 32 back-to-back
+ *     v_mfma_f32_16x16x32_bf16 on register operands with values in [-1, 1); *flops = work enqueued.
  *   flexco_probe_read: `blocks` blocks each stream their own contiguous piece of src[0, bytes) with
  *     16-byte loads; *bytes_read = bytes actually read (bytes rounded down to whole rounds).
  *   flexco_probe_mfma_lds: the same products with the operands fetched from LDS as the projection kernels fetch
- *     them, one 16-column slice ahead of the products (tile = 128: 2 x 2 wavefronts on a 128 x 128 tile, where the
+ *     them, one 32-column slice ahead of the products (tile = 128: 2 x 2 wavefronts on a 128 x 128 tile, where the
  *     LDS reads take as long as the products; tile = 256: a 256 x 256 tile, half as long); `iters` 64-column
  *     stages per wavefront.  src == NULL: no global memory traffic and no barriers.  src != NULL (device, 16-byte
  *     aligned, at least 8 x 2 x tile x 64 x 2 bytes of finite bf16 values): every stage also loads a stage of tile
