@@ -252,7 +252,7 @@ def main():
     if per_step:
         out["ms_per_step_median"] = float(np.median(per_step))
         out["ms_per_step_min"] = float(np.min(per_step))
-    out["forward_projections"] = per_projection(B, torch, step_serial, cfg, T)
+    out["forward_projections"] = per_projection(B, torch, step_serial, cfg, T, use_ia3)
     # bf16 launches that missed the matrix-core kernels and ran type-generic ones (all zero at this configuration)
     out["bf16_generic_fallbacks"] = {k: v for k, v in B.flexco_bf16_fallbacks().items() if k in ("gemm_fwd", "gemm_bwd", "attn_fwd", "attn_bwd")}
     out["measured_ceilings"] = measured_ceilings(B, torch)
@@ -276,9 +276,24 @@ def main():
     print(json.dumps(out), flush=True)
 
 
-def per_projection(B, torch, step_serial, cfg, T):
+def forward_launches(B, cfg, T, use_ia3=False):
+    """[(projection, weight elements, launches of the class)] in the order the layer's forward pass makes them.  A product
+    cut over K has a second launch, its sum's, unless the next kernel adds the partial sums itself (the norm behind o,
+    the rotation behind qkv unless (IA)^3 scales the rows in between); one that is not may be two tile shapes."""
+    H, F, qd, kd = cfg.hidden, cfg.ffn, cfg.q_dim, cfg.kv_dim
+    scratch = T * (32768 if T <= 256 else F)          # what the layer has: its own, or the gate/up buffer while that is free
+    out = []
+    for name, N, K, part, left in (("qkv", qd + 2 * kd, H, scratch, not use_ia3), ("o", H, qd, scratch, True),
+                                   ("gate_up", 2 * F, H, 0, False), ("down", H, F, scratch, False)):
+        plan = B.flexco_gemm_plan(T, N, K, False, part)
+        cut = max(plan[0][3], B.flexco_gemm_k_ranges(T, N, K, False, part) if part else 0)
+        out.append((name, N * K, len(plan) if cut == 1 else 1 if left else 2))
+    return out
+
+
+def per_projection(B, torch, step_serial, cfg, T, use_ia3):
     """The four forward projections one by one (three extra steps with an event pair on every launch of the class;
-    a projection whose tile plan is two launches is the sum of both)."""
+    a projection of several launches is their sum)."""
     kid = B.KERNEL_IDS["gemm_fwd"]
     steps = 3
     B.flexco_kernel_timer_sample(kid, 1)
@@ -288,24 +303,16 @@ def per_projection(B, torch, step_serial, cfg, T):
     torch.cuda.synchronize()
     each = B.flexco_kernel_timer_read(kid)
     _, calls = B.flexco_kernel_timer_stop(kid)
-    per_step = len(each) // steps
-    H, F, qd, kd = cfg.hidden, cfg.ffn, cfg.q_dim, cfg.kv_dim
-    names = [("qkv", (qd + 2 * kd) * H), ("o", qd * H), ("gate_up", 2 * F * H), ("down", F * H)]
-    if calls != 4 * steps or per_step < 4 or len(each) != per_step * steps:
+    launches = forward_launches(B, cfg, T, use_ia3)
+    per_step = sum(n for _, _, n in launches)
+    if calls != 4 * steps or len(each) != per_step * steps:
         return {"note": "unexpected launch pattern: %d pairs for %d calls" % (len(each), calls)}
-    # the calls come in the order qkv, o, gate/up, down; a product in ranges of K has a second pair, its sum's, and
-    # the rest belong to the widest projection (gate/up), whose plan is the one with two tile shapes at this size
-    pairs = [1 + (k != 2 and B.flexco_gemm_k_ranges(T, p // K, K, False, 1 << 30) > 1)
-             for k, (p, K) in enumerate(zip((p for _, p in names), (H, qd, H, F)))]
-    pairs[2] += per_step - sum(pairs)
-    if pairs[2] < 1:
-        return {"note": "unexpected launch pattern: %d pairs for %d calls" % (len(each), calls)}
-    out = {}
-    for k, (name, p) in enumerate(names):
-        lo, hi = sum(pairs[:k]), sum(pairs[:k + 1])
-        ms = sum(sum(each[st * per_step + j] for j in range(lo, hi)) for st in range(steps)) / steps
+    out, lo = {}, 0
+    for name, p, n in launches:
+        ms = sum(sum(each[st * per_step + j] for j in range(lo, lo + n)) for st in range(steps)) / steps
         tf = 2.0 * p * T / (ms * 1e-3) / 1e12
-        out[name] = {"ms": round(ms, 4), "launches": hi - lo, "achieved": tf, "unit": "TFLOP/s", "frac": tf / MFMA_BF16_PEAK_TFLOPS}
+        out[name] = {"ms": round(ms, 4), "launches": n, "achieved": tf, "unit": "TFLOP/s", "frac": tf / MFMA_BF16_PEAK_TFLOPS}
+        lo += n
     return out
 
 

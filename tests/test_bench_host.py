@@ -1,0 +1,35 @@
+"""bench.py's account of the forward projections' launches (host arithmetic, no GPU): a second launch only where a product
+is cut over K with the scratch the layer has and nothing else adds its sums."""
+import pytest
+
+import bench
+import paper_2402_18789_amd.binding as B
+from workload import CONFIGS
+
+pytestmark = pytest.mark.skipif(B.HOST_ONLY, reason="needs the whole library, this is a host-only build")
+
+C2, C4, C5 = (CONFIGS[n] for n in ("c2_llama8b_layer", "c4_qwen14b_full", "c5_qwen32b_full"))
+
+
+def launches(cfg, T, **kw):
+    return [n for _, _, n in bench.forward_launches(B, cfg, T, **kw)]
+
+
+def test_launches_of_the_benchmark_step():
+    assert launches(C2, 1024) == [1, 1, 2, 2]         # gate/up in two tile shapes, down in ranges and their sum
+
+
+def test_sums_left_to_the_next_kernel_are_no_launch():
+    assert B.flexco_gemm_k_ranges(280, C2.hidden, C2.q_dim, 0, 280 * C2.ffn) > 1
+    assert launches(C2, 280)[1] == 1                  # o: the norm adds them
+    qkv = (C5.q_dim + 2 * C5.kv_dim, C5.hidden)
+    assert B.flexco_gemm_k_ranges(600, *qkv, 0, 600 * C5.ffn) > 1
+    assert launches(C5, 600)[0] == 1 and launches(C5, 600, use_ia3=True)[0] == 2      # the rotation, unless (IA)^3 comes between
+    assert launches(C2, 16)[:2] == [1, 1] and launches(C2, 16)[3] == 2
+
+
+def test_cuts_are_asked_for_with_the_layers_own_scratch():
+    # tokens at which more scratch than the gate/up buffer would cut a product that the layer leaves whole
+    more = [T for T in range(257, 2049) if B.flexco_gemm_k_ranges(T, C4.hidden, C4.ffn, 0, 1 << 30) > 1
+            and B.flexco_gemm_k_ranges(T, C4.hidden, C4.ffn, 0, T * C4.ffn) <= 1]
+    assert more and all(launches(C4, T)[3] == len(B.flexco_gemm_plan(T, C4.hidden, C4.ffn, 0, T * C4.ffn)) for T in more)
