@@ -14,9 +14,9 @@
 //   * Forward form: operand tiles go from global memory straight into LDS
 //     (buffer_load_dwordx4 ... lds: one wavefront instruction fills 1 KB; lane l lands at
 //     base + 16 l), no staging registers and no LDS write instructions.  LDS is a ring of stages
-//     (four of 32 KB for the 128 tile, two of 56 KB for the 256 x 192 tile) whose loads are in flight
-//     while another stage is multiplied; the per-stage barrier carries no memory fence, the wait
-//     in front of it names exactly the loads that must have landed.  Rows are XOR-swizzled in 16-byte chunks (applied to the
+//     (four of 32 or 40 KB for the 128-row tiles, two of 32 KB where two blocks share a CU, six of 24 KB for the
+//     64-row tile) whose loads are in flight while another stage is multiplied; the per-stage barrier carries no
+//     memory fence, the wait in front of it names exactly the loads that must have landed.  Rows are XOR-swizzled in 16-byte chunks (applied to the
 //     global address a lane fetches) so that the ds_read_b128 operand fetches of 16 consecutive
 //     rows hit 64 distinct banks.
 //   * Input-gradient form: the same ring; the W tile is [64][BN] (k-major as in memory), loaded
@@ -237,10 +237,9 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
   // in the forward form, [64][BN] in the input-gradient form), A first.  The 128-row forward
   // tiles use four stages (32 KB each at 128 columns, 40 KB - all of the LDS - at 192): up to
   // three in flight or waiting while one is multiplied.
-  // The 256 x 192 tile uses two stages (56 KB): half as many barriers, and a stage's buffer is
-  // handed to the loads of the stage after next as soon as its last fragments are in registers.  The
-  // input-gradient form uses two stages of 32 KB, so that two blocks share a CU (its grids are
-  // K-split into more blocks than CUs).  The stages are separate arrays, not one indexed
+  // The input-gradient form uses two stages of 32 KB, so that two blocks share a CU (its grids are
+  // K-split into more blocks than CUs); a stage's buffer is handed to the loads of the stage after next as
+  // soon as its last fragments are in registers.  The stages are separate arrays, not one indexed
   // buffer: the compiler then sees that loads in flight target an array no ds_read of that
   // moment touches, and inserts no wait of its own.
   // NSTAGES = 6 for the 64-row tile (24 KB a stage, 144 KB): batches of few tokens, whose time is the weights' way out of
@@ -252,7 +251,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
   // NSTAGES = 2 for a 128-row forward tile: two such blocks share a CU.  With more tiles than CUs that is 15-30 %
   // faster than one four-stage block per CU in two rounds (one block's waits are the other's products); with one
   // tile per CU the four stages win.
-  constexpr int NST = NSTAGES ? NSTAGES : (TRANS ? 2 : ((BM + BN) * BK * 2 * 4 <= 160 * 1024 ? 4 : 2));   // stages in the ring
+  constexpr int NST = NSTAGES ? NSTAGES : TRANS ? 2 : 4;            // stages in the ring
+  static_assert((BM + BN) * BK * 2 * NST <= 160 * 1024, "the ring fits the LDS of a CU");
   constexpr int SL = BK / 32;                                       // MFMA k-slices per stage
   constexpr int PA = BM / 32, PB = BN / 32;                         // 1 KB load instructions per wavefront and stage
   constexpr int ST_ELEMS = (BM + BN) * BK;
@@ -308,8 +308,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
 #define GEMM_SRC_A(s_) __builtin_amdgcn_make_buffer_rsrc((void*)(pa + (size_t)min((s_), ns - 1) * (BK * 2)), 0, -1, 0x00027000)
 #define GEMM_SRC_W(s_) __builtin_amdgcn_make_buffer_rsrc((void*)(pw + (size_t)min((s_), ns - 1) * wstep), 0, -1, 0x00027000)
   // The 64-row tile's weights are read by one block and once: non-temporal loads (cache policy bit 1), which leave the
-  // caches to what is read again.  8 x 28672 x 4096 with weights in no cache 50.6 -> 47.2 us (5.0 TB/s), a layer of 48
-  // tokens at the 14B shape 253 -> 229, of 8 at the 8B shape 135 -> 128.  Tiles whose weights meet several row tiles lose
+  // caches to what is read again.  8 x 28672 x 4096 with weights in no cache 50.6 -> 47.2 us (5.0 TB/s), calls back to
+  // back, a layer of 48 tokens at the 14B shape 253 -> 229, of 8 at the 8B shape 135 -> 128 (among other work 257 -> 252 and 131 -> 122).  Tiles whose weights meet several row tiles lose
   // up to 5 % with it.
   constexpr int W_AUX = BM == 64 ? 2 : 0;
   // load instruction q of a stage's PA + PB
@@ -934,8 +934,10 @@ static int pick_splits(int M, int N, int K, int tiles, size_t part_elems, int wa
   return best;
 }
 
-// Rates of the input-gradient form's two tile shapes with every block slot taken, PFLOP/s (fitted to twelve products of
-// 512 to 1536 rows at the 8B, 14B and 32B shapes; with them the estimate picks the faster shape in each).
+// Rates of the input-gradient form's two tile shapes with every block slot taken, PFLOP/s: fitted to twelve products of
+// 512 to 1536 rows at the 8B, 14B and 32B shapes with the 32 x 32 x 16 kernels (the 256 x 256 tile reaches 1.26 now).  What they
+// decide is the plan's tile and equal cut; plan_gemm_k_ranges prices that choice with the present kernels' times and
+// takes the 256 x 256 tile, at the number of ranges that suits it, where that is estimated 5 % better.
 constexpr double TRANS_RATE_128 = 0.94, TRANS_RATE_256 = 1.05;
 
 // ---- estimated times, us, of launches of `blocks` blocks over `stages` 64-wide stages of K each.  Fitted to products of
@@ -955,7 +957,8 @@ static double us_tile128(long blocks, double stages) {
   const long rounds = (blocks + 511) / 512;
   return rounds * (3 + (blocks / rounds <= 460 ? 0.95 : 1.1) * stages);
 }
-// partial sums out and back in, and the launch that adds them
+// partial sums out and back in, and the launch that adds them (also where the next kernel will add them: who comes next is not
+// known here)
 static double us_partial_sums(int splits, int M, int N) { return splits > 1 ? 4 + (double)splits * M * N * 1e-6 : 0.0; }
 
 // Tile shapes of a forward-form product by estimated time: columns [0, 256 a) in 256-wide tiles and the rest in ONE of
