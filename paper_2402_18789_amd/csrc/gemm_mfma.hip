@@ -279,7 +279,9 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
   const int t_row = lane / TCH;
   const int t_k = wave * TR + t_row;              // its row, up to a multiple of 16
   const int t_c = (lane % TCH) ^ ((t_k & 3) << 2) ^ (((t_k >> 3) & 1) << 1);
-  // byte offsets from the tile's own corner: 32 bits (the launcher refuses what would not fit)
+  // byte offsets from the tile's own corner - gated form: from its first gate row, the up rows F further on - in 32 bits
+  // (the launcher refuses what would not fit)
+  const int ac0 = GLU ? glu.col0 + tn * (BN / 2) : 0;
   unsigned oa[PA], ow[PB];
 #pragma unroll
   for (int p = 0; p < PA; ++p) oa[p] = (unsigned)((size_t)min((p * 4 + wave) * 8 + d_row, M - 1 - m0) * lda * 2 + d_c * 16);
@@ -290,8 +292,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
       // (act columns tile + 16 f .. + 16), rows 32 f + 16 .. + 16 the up rows of the same columns, so that
       // a lane holds gate and up of the same 4 act columns in neighbouring accumulators
       const int rr = (p * 4 + wave) * 8 + d_row;
-      const int ac = glu.col0 + tn * (BN / 2) + (rr >> 5) * 16 + (rr & 15);
-      ow[p] = (unsigned)(((size_t)((rr >> 4) & 1) * glu.F + min(ac, glu.F - 1)) * ldw * 2 + d_c * 16);
+      const int ac = ac0 + (rr >> 5) * 16 + (rr & 15);
+      ow[p] = (unsigned)(((size_t)((rr >> 4) & 1) * glu.F + (min(ac, glu.F - 1) - ac0)) * ldw * 2 + d_c * 16);
     } else if (!TRANS) {
       ow[p] = (unsigned)((size_t)min((p * 4 + wave) * 8 + d_row, N - 1 - n0) * ldw * 2 + d_c * 16);
     } else {
@@ -301,7 +303,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
     }
   }
   const char* const pa = (const char*)(A + (size_t)m0 * lda + kbeg);
-  const char* const pw = (const char*)(GLU ? W + kbeg : (TRANS ? W + (size_t)kbeg * ldw + n0 : W + (size_t)n0 * ldw + kbeg));
+  const char* const pw = (const char*)(GLU ? W + (size_t)ac0 * ldw + kbeg : (TRANS ? W + (size_t)kbeg * ldw + n0 : W + (size_t)n0 * ldw + kbeg));
   const size_t wstep = TRANS ? (size_t)BK * ldw * 2 : (size_t)BK * 2;
 
   // stage index past the end: clamped, the loads repeat the last stage into a free buffer
@@ -644,6 +646,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_quad_kernel(const bf16_t* __res
   // ---- loads: instruction p of wavefront w fills 1 KB of a half-tile: rows 8 (4 p + w) .. + 8 of [128][64], or
   // rows 4 (4 p + w) .. + 4 of [64][128].  16-byte chunk c of a 128-byte row r is stored at c ^ ((r / 2) % 8), of a
   // 256-byte row at c ^ 4 (r % 4) ^ 2 (r / 8 % 2) (as in the kernel above).  Byte offsets from the tile's own corner fit 32 bits. ----
+  const int ac0 = GLU ? glu.col0 + tn * (BN / 2) : 0;
   unsigned oa[2][NA], ow[2][NW];
   {
     const int d_row = lane >> 3;
@@ -660,8 +663,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_quad_kernel(const bf16_t* __res
         if (p >= NW) continue;
         const int rt = (BN / 2) * (r / (BN / 4)) + (BN / 4) * h + r % (BN / 4);      // the same for rows of W
         if (GLU) {
-          const int ac = glu.col0 + tn * (BN / 2) + (rt >> 5) * 16 + (rt & 15);
-          ow[h][p] = (unsigned)(((size_t)((rt >> 4) & 1) * glu.F + min(ac, glu.F - 1)) * ldw * 2 + d_c * 16);
+          const int ac = ac0 + (rt >> 5) * 16 + (rt & 15);
+          ow[h][p] = (unsigned)(((size_t)((rt >> 4) & 1) * glu.F + (min(ac, glu.F - 1) - ac0)) * ldw * 2 + d_c * 16);
         } else if (!TRANS) {
           ow[h][p] = (unsigned)((size_t)min(rt, N - 1 - n0) * ldw * 2 + d_c * 16);
         } else {
@@ -674,7 +677,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_quad_kernel(const bf16_t* __res
     }
   }
   const char* const pa = (const char*)(A + (size_t)m0 * lda + kbeg);
-  const char* const pw = (const char*)(GLU ? W + kbeg : (TRANS ? W + (size_t)kbeg * ldw + n0 : W + (size_t)n0 * ldw + kbeg));
+  const char* const pw = (const char*)(GLU ? W + (size_t)ac0 * ldw + kbeg : (TRANS ? W + (size_t)kbeg * ldw + n0 : W + (size_t)n0 * ldw + kbeg));
   const size_t wstep = TRANS ? (size_t)BK * ldw * 2 : (size_t)BK * 2;
   // (a stage past the end: clamped, the loads repeat the last stage into a free buffer)
 #define Q_LOAD(buf_, src_, off_, p_) \

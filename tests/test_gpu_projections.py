@@ -1,12 +1,18 @@
 """The bf16 projections' tile kernels at the sizes where they can go wrong: each tile shape with ragged last rows and
-columns, one, two and three 64-wide stages of K, K in unequal ranges (run with -m gpu on an MI355X)."""
+columns, one, two and three 64-wide stages of K, K in unequal ranges, weights past 4 GiB (run with -m gpu on an MI355X)."""
+from types import SimpleNamespace
+
 import pytest
 import torch
+
+from workload import CONFIGS
 
 pytestmark = pytest.mark.gpu
 
 if torch.cuda.is_available():
     import paper_2402_18789_amd.binding as B
+    from paper_2402_18789_amd import host as HH
+    from gpu_common import TOL, assert_close, to_np
     from test_gpu_train import run_loss
 
 
@@ -76,3 +82,36 @@ def test_input_gradient_in_unequal_ranges(n, H, V):
 def test_loss_rows(n, V):
     print(f"loss head n={n} V={V}", flush=True)
     run_loss("bf16", n, 256, V, seed=4, ignore=(1, 4))
+
+
+# gate and up rows of one weight matrix of more than 4 GiB, on the 64-, 128- and 256-row tiles.  One-token sequences: the
+# attention output of a token is its value row.
+def test_gated_projection_of_weights_past_4_gib():
+    H, F, nq, nkv, d = 1024, 64 * 16448, 8, 2, 128
+    assert 2 * F * H * 2 > 1 << 32
+    cfg = CONFIGS["c2_llama8b_layer"].with_(name="wide_ffn", hidden=H, n_q_heads=nq, n_kv_heads=nkv, head_dim=d, ffn=F, lora_targets=())
+    g = torch.Generator(device="cuda").manual_seed(31)
+    rnd = lambda *shape: torch.randn(shape, generator=g, device="cuda", dtype=torch.bfloat16)  # noqa: E731
+    wqkv, wo, wgu, wd = (rnd(*s).mul_(0.02) for s in ((cfg.q_dim + 2 * cfg.kv_dim, H), (H, cfg.q_dim), (2 * F, H), (H, F)))
+    g1, g2 = (1 + 0.02 * rnd(H).float()).bfloat16(), (1 + 0.02 * rnd(H).float()).bfloat16()
+    w = B.BaseWeights(*[t.data_ptr() if t is not None else None for t in (wqkv, None, wo, wgu, wd, g1, g2)])
+    c = HH.c_cfg(cfg)
+    norm = lambda x, gain: x * torch.rsqrt(x.square().mean(-1, keepdim=True) + cfg.rms_eps) * gain.double()  # noqa: E731
+    for T in (8, 130, 520):
+        print(f"gated projection, {wgu.numel() * 2 / 2 ** 30:.2f} GiB of weights, {T} tokens, {B.flexco_gemm_plan(T, 2 * F, H, 0, 0)}", flush=True)
+        reqs = [SimpleNamespace(kind=B.FLEXCO_DECODE, seq_id=i, start_pos=0, n_new=1, adapter=-1) for i in range(T)]
+        pool = HH.DevicePool(cfg, T + 1)
+        db = HH.DeviceBatch(cfg, reqs, [[i] for i in range(T)], T + 1)
+        ws = HH.Workspace(c, T, db.host_maps.n_parts)
+        x, y = rnd(T, H), torch.empty(T, H, device="cuda", dtype=torch.bfloat16)
+        B.flexco_layer_forward(c, w, None, db.maps, x, y, pool.c, None, ws.ptr, ws.bytes)
+        torch.cuda.synchronize()
+        v = (norm(x.double(), g1) @ wqkv[cfg.q_dim + cfg.kv_dim:].double().t()).view(T, nkv, 1, d).expand(T, nkv, nq // nkv, d).reshape(T, -1)
+        ref = x.double() + v @ wo.double().t()
+        h = norm(ref, g2)
+        for f0 in range(0, F, 1 << 16):
+            f1 = min(F, f0 + (1 << 16))
+            gate, up = h @ wgu[f0:f1].double().t(), h @ wgu[F + f0:F + f1].double().t()
+            ref = ref + (gate * torch.sigmoid(gate) * up) @ wd[:, f0:f1].double().t()
+        assert_close(f"y of {T} tokens", to_np(y), to_np(ref), TOL["bf16"])
+        del ws
