@@ -276,7 +276,11 @@ __global__ __launch_bounds__(64) void attn_bwd_dq_generic_kernel(const T* __rest
       const T* kr = kp + row * (size_t)d;
       const T* vr = vp + ((page * nkv + kvh) * (size_t)d) * ps + j % ps;
       float s = 0.f, dp = 0.f;
-#pragma unroll 4
+      // eight rows of V on their way per lane (a V element is a load of its own; 32 for bf16, 16 for fp32 had too few wavefronts
+      // on a CU: window of 256 rows in 2048, head_dim 256 2524 -> 1819 us of the layer's backward, 64 2466 -> 2303, fp32 of
+      // head_dim 64 2195 -> 2092)
+      constexpr int U = 8 / N;
+#pragma unroll U
       for (int dd = 0; dd < d; dd += N) {
         float kv[N], vv[N];
         Vec<T>::load(kr + dd, kv);

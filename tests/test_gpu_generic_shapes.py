@@ -18,6 +18,7 @@ if torch.cuda.is_available():
 C1 = CONFIGS["c1_tiny_f32"]
 ODD_F32 = C1.with_(name="odd_f32", n_q_heads=6, n_kv_heads=2, head_dim=20, page_size=5)          # V page rows: no whole 16 bytes
 WIDE_BF16 = C1.with_(name="wide_bf16", dtype="bf16", n_q_heads=4, n_kv_heads=2, head_dim=72, page_size=24)
+D256_BF16 = C1.with_(name="d256_bf16", dtype="bf16", n_q_heads=4, n_kv_heads=2, head_dim=256)
 
 
 # one tile; ragged tiles; K not a multiple of a step of 16; more steps than wavefronts x loads in flight; more than 1024 tiles of
@@ -43,7 +44,7 @@ def test_gemm_f32(M, N, K, trans):
     assert np.all(got[M:] == 7.0)               # nothing past the last row
 
 
-@pytest.mark.parametrize("cfg,split", [(ODD_F32, 0), (ODD_F32, 2), (WIDE_BF16, 0), (WIDE_BF16, 2),
+@pytest.mark.parametrize("cfg,split", [(ODD_F32, 0), (ODD_F32, 2), (WIDE_BF16, 0), (WIDE_BF16, 2), (D256_BF16, 4),
                                        (C1, 64)])           # 1024 keys per split: four wavefronts per block
 def test_generic_attention_forward(cfg, split):
     print(f"attention forward {cfg.name} split={split}", flush=True)
@@ -53,7 +54,8 @@ def test_generic_attention_forward(cfg, split):
     assert float(np.max(np.abs(lse - lse_o))) <= (1e-4 if cfg.dtype == "f32" else 2e-2)
 
 
-@pytest.mark.parametrize("cfg,win_start,win_len", [(ODD_F32, 0, 1), (ODD_F32, 61, 68), (WIDE_BF16, 40, 37), (C1, 130, 21)])
+@pytest.mark.parametrize("cfg,win_start,win_len", [(ODD_F32, 0, 1), (ODD_F32, 61, 68), (WIDE_BF16, 40, 37), (C1, 130, 21),
+                                                   (D256_BF16, 70, 33)])
 def test_generic_attention_backward(cfg, win_start, win_len):
     print(f"attention backward {cfg.name} [{win_start}, +{win_len})", flush=True)
     l = win_start + win_len
