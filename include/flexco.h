@@ -488,9 +488,9 @@ int32_t flexco_bf16_fallbacks(int64_t* counts, int32_t reset);
  * stream of the library's own (default priority; created on the device's first such call, which therefore must not
  * fall inside a stream capture) that leaves the caller's stream before the attention and rejoins it after: to the
  * caller's stream the call behaves as before, also under capture; -1 = chosen by batch, the default: the kernel of
- * their own alone when the work list has no single-token item, beside the decode stream when the chunks' products
- * outweigh it (flexco_maps.chunk_tile_pages >= stream_pages), else the one kernel for everything (a light chunk load
- * hides in the decode stream's waits).  Both kernels take the same products per column tile; their results agree to
+ * four wavefronts for the whole work list, decode tokens included, in one launch, with neighbouring key splits taken together
+ * where the list is cut finer than it needs; the one-wavefront kernel for batches of nothing but decode tokens whose contexts
+ * are many and short or cut into about as many items as the chip has wavefronts.  Both kernels take the same products per column tile; their results agree to
  * rounding (the kernels scale their running sums at different steps).  Process-wide; returns FLEXCO_EINVAL for other
  * values. */
 int32_t flexco_attention_chunk_path(int32_t mode);

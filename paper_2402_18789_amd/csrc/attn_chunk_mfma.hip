@@ -37,6 +37,10 @@ struct ChunkArgs {
   size_t ldo;
   float* lse;         // or NULL
   AttnKeep keep;
+  int singles;        // single tokens too (else they are the one-launch kernel's)
+  int fold;           // key splits of the work list that the block of a request of one token takes as one
+  const int32_t* req_tok_off;
+  float lag;          // LAZY, or 0: the reference points follow the maxima as in the one-wavefront kernel
 };
 
 // K rows in LDS ([16 keys][128] bf16, 256-byte rows): chunk cc of row r is stored at chunk cc ^ rsw(r), so that the
@@ -53,10 +57,10 @@ __device__ inline bf16x4 lds_read_8(const bf16_t* p) {
   return __builtin_bit_cast(bf16x4, v);
 }
 
-// RING = stages of the K / V ring.  4: 65 KB of LDS, two blocks per CU, two stages of loads in flight - the form that
-// runs beside the decode tokens' kernel.  3: 49 KB and at most 168 registers, three blocks per CU, one stage in flight -
-// 7 - 10 % faster when the kernel has the chip to itself (three wavefronts per SIMD fill each other's waits), no
-// better beside the decode stream, which it crowds out of the CUs.
+// RING = stages of the K / V ring.  4: 65 KB of LDS, two blocks per CU, two stages of loads in flight - the form for work
+// lists with decode tokens, whose pages stream from HBM (the benchmark batch 420 us, 437 with three stages; a 14B batch 568 and
+// 588), and beside the one-wavefront kernel.  3: 49 KB and at most 168 registers, three blocks per CU, one stage in flight -
+// 3 - 10 % faster where only chunks are left (three wavefronts per SIMD fill each other's waits).
 template <int RING>
 __global__ __launch_bounds__(256, RING == 3 ? 3 : 2) void attn_fwd_chunk_kernel(ChunkArgs a, const bf16_t* __restrict__ q, size_t ldq,
                                                                 const bf16_t* __restrict__ kp,
@@ -71,23 +75,35 @@ __global__ __launch_bounds__(256, RING == 3 ? 3 : 2) void attn_fwd_chunk_kernel(
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int item = blockIdx.x / a.nkv, kvh = blockIdx.x % a.nkv;
-  const int tile0 = a.item_tile[item], split = a.item_split[item];
-  const int ntl = a.item_ntiles[item];
-  if (ntl == 1 && a.tile_ntok[tile0] == 1) return;   // a decode token: the one-launch kernel's (whole block, before any barrier)
+  // (a block's start is a chain of lookups in front of its first load of K: each step asks for all it can)
+  const int tile0 = a.item_tile[item], split = a.item_split[item], ntl = a.item_ntiles[item];
+  const int tl = tile0 + ntl - 1;
   const int r = a.tile_req[tile0];
+  const int tok_first = a.tile_tok0[tile0], ntok_first = a.tile_ntok[tile0];
+  const int tok_last = a.tile_tok0[tl] + a.tile_ntok[tl] - 1;
+  const bool lone = ntl == 1 && ntok_first == 1;
+  if (!a.singles && lone) return;                          // the one-launch kernel's (whole block, before any barrier)
+  const int fold = a.fold > 1 && a.req_tok_off[r + 1] - a.req_tok_off[r] == 1 ? a.fold : 1;
+  if (split % fold != 0) return;                           // the block of an earlier split takes this one's keys (whole block)
   const int group = a.nq / a.nkv;
   const int c = lane & 15, g = lane >> 4;
-  // the item's keys: up to the last position of its last tile
-  const int tl = tile0 + ntl - 1;
-  const int last_pos = a.tok_pos[a.tile_tok0[tl] + a.tile_ntok[tl] - 1];
-  const int vis_pages = last_pos / PS + 1;
-  const int first_pos = a.tok_pos[a.tile_tok0[tile0]];   // the item's first column sees the fewest keys
   const int pb = split * a.split_pages;
-  const int pe = min(pb + a.split_pages, vis_pages);
+  // the page ids of the range, and what may follow them in the request's row of the table (never used)
+  page_tab[tid] = a.block_table[(size_t)r * a.max_pages + min(pb + tid, a.max_pages - 1)];   // MAXSP = block size
+  // the item's keys: up to the last position of its last tile
+  const int last_pos = a.tok_pos[tok_last];
+  const int first_pos = a.tok_pos[tok_first];            // the item's first column sees the fewest keys
+  const int vis_pages = last_pos / PS + 1;
+  const int pe = min(pb + fold * a.split_pages, vis_pages);
   const int npg = pe - pb;                               // >= 1: an item exists for splits inside the visible range only
-  page_tab[tid] = a.block_table[(size_t)r * a.max_pages + (tid < npg ? pb + tid : pb)];   // MAXSP = block size
   __syncthreads();
 
+  // (A lone token's block leaves three wavefronts without a tile.  Having all four fetch page pairs of their own into
+  // registers, without barriers, and add up at the end was slower - benchmark batch 422 us against 417, 14B batch 594 against 557: the
+  // stream is not short of arithmetic, and whole 1 KB loads into LDS move it better than 64-byte pieces of rows.)
+  // how far the reference point of a column's exponentials may lag its maximum (below): where it may at all, the odd last token of a
+  // chunk, which the one-wavefront kernel used to take, excepted
+  const float lag = lone ? 0.f : a.lag;
   // this wavefront's tile (wavefronts past the item's last tile only help with the loads and the barriers)
   const bool have = wave < ntl;
   const int tile = tile0 + (have ? wave : 0);
@@ -191,20 +207,21 @@ __global__ __launch_bounds__(256, RING == 3 ? 3 : 2) void attn_fwd_chunk_kernel(
     mx = max_xor32(mx);                                                                               \
     /* The reference point m of a column's exponentials need not be its running maximum: any m gives the same */ \
     /* row after the final division by l.  It follows the maximum only when that has moved up by more than    */ \
-    /* LAZY (exponentials then stay below 2^LAZY: no overflow, same relative rounding in bf16), so that the    */ \
+    /* lag = LAZY (exponentials then stay below 2^LAZY: no overflow, same relative rounding in bf16), so that the */ \
     /* accumulators are rescaled in few steps - in place, inside a branch the wavefront takes as one - instead */ \
     /* of in every step (32 of a step's 80 vector instructions).                                              */ \
-    if (__builtin_amdgcn_ballot_w64(mx > m + LAZY) != 0) {                                            \
-      const float m_upd = mx > m + LAZY ? mx : m;                                                     \
+    if (__builtin_amdgcn_ballot_w64(mx > m + lag) != 0) {                                             \
+      const float m_upd = mx > m + lag ? mx : m;                                                      \
       const float alpha = __builtin_amdgcn_exp2f(m - m_upd);                                          \
       l *= alpha;                                                                                     \
       m = m_upd;                                                                                      \
       _Pragma("unroll") for (int mt = 0; mt < 8; ++mt)                                                \
         _Pragma("unroll") for (int j = 0; j < 4; ++j) o[mt][j] *= alpha;                              \
     }                                                                                                 \
+    const float m_use = (m == -INFINITY) ? 0.f : m;                                                   \
     float p[8], psum = 0.f;                                                                           \
     _Pragma("unroll") for (int j = 0; j < 8; ++j) {                                                   \
-      p[j] = __builtin_amdgcn_exp2f(s[j] - m);                                                        \
+      p[j] = __builtin_amdgcn_exp2f(s[j] - m_use);                                                    \
       psum += p[j];                                                                                   \
     }                                                                                                 \
     l += psum;                                                                                        \
@@ -363,7 +380,7 @@ __global__ __launch_bounds__(256, RING == 3 ? 3 : 2) void attn_fwd_chunk_kernel(
   lsum = sum_xor16(lsum);
   lsum = sum_xor32(lsum);
   if (c >= a.tile_ntok[tile] * group) return;
-  if (a.tile_nsplit[tile] == 1) {
+  if (a.tile_nsplit[tile] <= fold) {
     const int t = a.tile_tok0[tile] + c / group, h = kvh * group + c % group;
     const float inv = 1.0f / lsum;
     bf16_t* po = a.out + (size_t)t * a.ldo + h * D + 4 * g;
@@ -400,15 +417,14 @@ __global__ __launch_bounds__(256, RING == 3 ? 3 : 2) void attn_fwd_chunk_kernel(
 
 }  // namespace
 
-// The chunk items of the work list (everything but single decode tokens) on the four-wavefront kernel; the caller
-// has the one-launch kernel skip them.  Same support test as launch_attention_mfma.  alone: no other kernel of the
-// call runs beside this one (the work list has no decode token).
+// The chunk items of the work list (everything but single tokens) on the four-wavefront kernel; the caller
+// has the one-launch kernel skip them.  Same support test as launch_attention_mfma.  alone: the single tokens too.
 int32_t launch_attention_chunk_mfma(const flexco_layer_cfg& c, const flexco_maps& m, const void* q, size_t ldq,
                                     const flexco_kv_pool& pool, float* part_ml, float* part_acc, void* out, size_t ldo,
-                                    float* lse, hipStream_t s, const AttnKeep* keep, bool alone) {
+                                    float* lse, hipStream_t s, const AttnKeep* keep, bool alone, int fold, bool lag) {
   const int group = c.n_q_heads / c.n_kv_heads;
   if (c.dtype != FLEXCO_BF16 || c.head_dim != D || c.page_size != PS || group > 16 || ldq % 8 != 0 ||
-      m.kv_split_pages > MAXSP || ldo % 4 != 0 || ((uintptr_t)out & 7))
+      m.kv_split_pages * fold > MAXSP || ldo % 4 != 0 || ((uintptr_t)out & 7))
     return FLEXCO_EUNSUPPORTED;
   if (m.n_items == 0) return FLEXCO_OK;
   ChunkArgs a;
@@ -420,14 +436,13 @@ int32_t launch_attention_chunk_mfma(const flexco_layer_cfg& c, const flexco_maps
   a.scale_log2 = 1.4426950408889634f / sqrtf((float)D);
   a.out = (bf16_t*)out; a.ldo = ldo; a.lse = lse;
   a.keep = keep ? *keep : AttnKeep{nullptr, nullptr, 0, 0};
-  if (alone)
-    hipLaunchKernelGGL(attn_fwd_chunk_kernel<3>, dim3((unsigned)m.n_items * c.n_kv_heads), dim3(256), 0, s, a,
-                       (const bf16_t*)q, ldq, (const bf16_t*)pool.k_pages, (const bf16_t*)pool.v_pages, part_ml,
-                       part_acc);
-  else
-    hipLaunchKernelGGL(attn_fwd_chunk_kernel<4>, dim3((unsigned)m.n_items * c.n_kv_heads), dim3(256), 0, s, a,
-                       (const bf16_t*)q, ldq, (const bf16_t*)pool.k_pages, (const bf16_t*)pool.v_pages, part_ml,
-                       part_acc);
+  a.singles = alone;
+  a.fold = fold;
+  a.req_tok_off = m.req_tok_off;
+  a.lag = lag ? LAZY : 0.f;
+  const auto kern = m.n_single == 0 ? attn_fwd_chunk_kernel<3> : attn_fwd_chunk_kernel<4>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)m.n_items * c.n_kv_heads), dim3(256), 0, s, a, (const bf16_t*)q, ldq,
+                     (const bf16_t*)pool.k_pages, (const bf16_t*)pool.v_pages, part_ml, part_acc);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(FLEXCO_EHIP, "launch of attn_fwd_chunk failed: %s", hipGetErrorString(e));
   return FLEXCO_OK;

@@ -111,7 +111,14 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_generic_kernel(AttnArgs a, c
   }
 }
 
-// One wave per (token, query head): combine the tile's splits.
+// key splits that share a partial row: fold for a request of one token, else 1
+__device__ inline int token_fold(int t, int fold, const int32_t* tok_req, const int32_t* req_tok_off) {
+  if (fold == 1) return 1;
+  const int r = tok_req[t];
+  return req_tok_off[r + 1] - req_tok_off[r] == 1 ? fold : 1;
+}
+
+// One wave per (token, query head): combine the tile's splits (every fold-th has a partial row).
 template <typename T>
 __global__ __launch_bounds__(64) void attn_merge_kernel(const int32_t* __restrict__ tok_tile,
                                                         const int32_t* __restrict__ tile_tok0,
@@ -120,20 +127,22 @@ __global__ __launch_bounds__(64) void attn_merge_kernel(const int32_t* __restric
                                                         const float* __restrict__ part_ml,
                                                         const float* __restrict__ part_acc, T* __restrict__ out,
                                                         size_t ldo, float* __restrict__ lse, int nq, int nkv, int d,
-                                                        int cols_per_tile, int skip_single_split, AttnKeep keep) {
+                                                        int cols_per_tile, int direct, int fold_in, const int32_t* __restrict__ req_tok_off,
+                                                        const int32_t* __restrict__ tok_req, AttnKeep keep) {
   const int t = blockIdx.x, h = blockIdx.y;
   const int group = nq / nkv, kvh = h / group;
   const int tile = tok_tile[t];
   const int c = (t - tile_tok0[tile]) * group + h % group;
   const int nsplit = tile_nsplit[tile], part0 = tile_part0[tile];
-  if (skip_single_split && nsplit == 1) return;   // the attention kernel has written these rows itself
+  const int fold = token_fold(t, fold_in, tok_req, req_tok_off);
+  if (direct && nsplit <= fold) return;   // the attention kernel has written these rows itself
   float M = -INFINITY;
-  for (int s = 0; s < nsplit; ++s) {
+  for (int s = 0; s < nsplit; s += fold) {
     const size_t idx = ((size_t)(part0 + s) * nkv + kvh) * cols_per_tile + c;
     M = fmaxf(M, part_ml[idx * 2]);
   }
   float L = 0.f;
-  for (int s = 0; s < nsplit; ++s) {
+  for (int s = 0; s < nsplit; s += fold) {
     const size_t idx = ((size_t)(part0 + s) * nkv + kvh) * cols_per_tile + c;
     const float ms = part_ml[idx * 2];
     if (ms > -INFINITY) L += part_ml[idx * 2 + 1] * __expf(ms - M);
@@ -142,7 +151,7 @@ __global__ __launch_bounds__(64) void attn_merge_kernel(const int32_t* __restric
   const bool kept = keep.lse2 && t >= keep.tok0 && t < keep.tok0 + keep.n;
   for (int dd = threadIdx.x; dd < d; dd += 64) {
     float acc = 0.f;
-    for (int s = 0; s < nsplit; ++s) {
+    for (int s = 0; s < nsplit; s += fold) {
       const size_t idx = ((size_t)(part0 + s) * nkv + kvh) * cols_per_tile + c;
       const float ms = part_ml[idx * 2];
       if (ms > -INFINITY) acc += part_acc[idx * d + dd] * __expf(ms - M);
@@ -175,17 +184,19 @@ __global__ __launch_bounds__(256) void attn_merge128_kernel(const int32_t* __res
                                                             const float* __restrict__ part_ml,
                                                             const float* __restrict__ part_acc, T* __restrict__ out,
                                                             size_t ldo, float* __restrict__ lse, int nq, int nkv,
-                                                            int cols_per_tile, int skip_single_split, AttnKeep keep) {
+                                                            int cols_per_tile, int direct, int fold_in, const int32_t* __restrict__ req_tok_off,
+                                                        const int32_t* __restrict__ tok_req, AttnKeep keep) {
   constexpr int d = 128;
   const int t = blockIdx.x, h = blockIdx.y * 8 + (threadIdx.x >> 5), ln = threadIdx.x & 31;
   if (h >= nq) return;
   const int group = nq / nkv, kvh = h / group;
   const int tile = tok_tile[t];
-  const int nsplit = tile_nsplit[tile];
-  if (skip_single_split && nsplit == 1) return;   // the attention kernel has written these rows itself
+  const int fold = token_fold(t, fold_in, tok_req, req_tok_off);
+  const int nsplit = (tile_nsplit[tile] + fold - 1) / fold;     // partial rows
+  if (direct && nsplit == 1) return;   // the attention kernel has written these rows itself
   const int c = (t - tile_tok0[tile]) * group + h % group;
   const size_t idx0 = ((size_t)tile_part0[tile] * nkv + kvh) * cols_per_tile + c;
-  const size_t step = (size_t)nkv * cols_per_tile;         // from one split's row to the next
+  const size_t step = (size_t)fold * nkv * cols_per_tile;         // from one partial row to the next
   // The chain of loads is what this kernel's time is: U splits' at once (past the last one they repeat it), added in
   // split order.  The first U splits' maxima are kept for the second pass.
   constexpr int U = 8;
@@ -421,7 +432,7 @@ int32_t launch_attention_generic(const flexco_layer_cfg& c, const flexco_maps& m
 
 int32_t launch_attention_merge(const flexco_layer_cfg& c, const flexco_maps& m, const float* part_ml,
                                const float* part_acc, void* out, size_t ldo, float* lse, hipStream_t s,
-                               bool skip_single_split, const AttnKeep* keep_in) {
+                               bool direct, int fold, const AttnKeep* keep_in) {
   AttnKeep keep{nullptr, nullptr, 0, 0};
   if (keep_in) keep = *keep_in;
   const int cpt = m.tile_tokens * (c.n_q_heads / c.n_kv_heads);
@@ -429,12 +440,12 @@ int32_t launch_attention_merge(const flexco_layer_cfg& c, const flexco_maps& m, 
       ((uintptr_t)keep.out2 & 15) == 0) {
     DISPATCH_T(c.dtype, hipLaunchKernelGGL((attn_merge128_kernel<T>), dim3(m.T, (c.n_q_heads + 7) / 8), dim3(256), 0, s,
                                            m.tok_tile, m.tile_tok0, m.tile_nsplit, m.tile_part0, part_ml, part_acc, (T*)out,
-                                           ldo, lse, c.n_q_heads, c.n_kv_heads, cpt, skip_single_split ? 1 : 0, keep));
+                                           ldo, lse, c.n_q_heads, c.n_kv_heads, cpt, direct ? 1 : 0, fold, m.req_tok_off, m.tok_req, keep));
     return post_launch("attn_merge");
   }
   DISPATCH_T(c.dtype, hipLaunchKernelGGL((attn_merge_kernel<T>), dim3(m.T, c.n_q_heads), dim3(64), 0, s, m.tok_tile,
                                          m.tile_tok0, m.tile_nsplit, m.tile_part0, part_ml, part_acc, (T*)out, ldo,
-                                         lse, c.n_q_heads, c.n_kv_heads, c.head_dim, cpt, skip_single_split ? 1 : 0, keep));
+                                         lse, c.n_q_heads, c.n_kv_heads, c.head_dim, cpt, direct ? 1 : 0, fold, m.req_tok_off, m.tok_req, keep));
   return post_launch("attn_merge");
 }
 

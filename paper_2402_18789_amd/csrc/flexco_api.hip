@@ -1,6 +1,7 @@
 // Entry points of the C ABI: validation on the host, workspace carving, and the launch
 // sequences of one forward iteration (Sec. 6.2) and one token-window backward step
 // (Alg. 2) of a decoder layer.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <atomic>
@@ -695,22 +696,62 @@ int32_t backward_projection(const flexco_layer_cfg& c, const flexco_lora* lora, 
   return FLEXCO_OK;
 }
 
+// The default choice of attention kernel and key ranges, from the sums the map builder leaves.
+//
+// alone: the four-wavefront kernel takes the whole work list in one launch: its blocks, two or three per CU, keep as many
+// bytes on their way as the one-wavefront kernel's items did, and share a CU between streaming and multiplying blocks.  Measured
+// against what was done before (one kernel for everything, or the two beside each other on two streams; us): the 14B shape's 512 decode
+// tokens with 512 + 1024 chunk rows 641 -> 608, the 8B shape's 96 decode tokens beside 211 + 205 rows 122 -> 99, 217 decode
+// tokens beside 279 + 40 rows 294 -> 108, 105 beside 74 + 73 166 -> 112, chunks of 713 + 487 + 205 rows without a decode token
+// 144 -> 67 (a last tile of one token had sent them to the pair of kernels), the benchmark batch 428 -> 419.
+// The one-wavefront kernel stays for batches of nothing but decode tokens in two ranges: many short contexts, none of them cut, where
+// a block's fixed chain (tables, first stages) outweighs its few pages (256 requests of 16 - 100 keys 24 against 31 us, of
+// 100 - 600 keys 72 against 76; 128 of 200 - 2000 keys, 70 pages each, 125 against 105), and lists cut into about as many items as
+// the chip has wavefronts of that kernel, 1024 (48 requests of 200 - 2048 keys 49 against 51, 48 of 2000 - 8000 175 against 180; with
+// 1184 items 88 against 81).
+//
+// fold: the work list is cut for one wavefront per item and head, i.e. into more pieces than blocks of four need; the block of a
+// request of one token takes that many neighbouring key splits as one while that leaves 400 blocks, up to the 256 pages of its
+// table (96 requests of 200 - 2000 keys 89 -> 81 from 64 to 128) - 32 where the products of chunks are the work, which a long
+// chain of one wavefront would outlast (24 decode tokens beside 150 and 343 rows 65, with 128 pages 83).
+// 8 pages are too few for a block's fixed chain with 40 items or more (72 items: 22 -> 16; 44: 13.3 against 13.7).
+//
+// Rows of chunks keep their key ranges, and the reference point of their exponentials lags its maximum exactly where
+// the four-wavefront kernel took them before (no single token, or products that outweigh the stream): the probabilities'
+// rounding to bf16 depends on both, and the window's saved rows and gradients with it.
+struct AttnPlan { bool alone; int fold; bool lag; };
+AttnPlan plan_attention(const flexco_maps& m, int nkv) {
+  const int64_t blocks = (int64_t)m.n_items * nkv;
+  const bool lag = m.n_single == 0 || m.chunk_tile_pages >= m.stream_pages;
+  if (m.n_single == m.n_items && blocks >= 768 &&
+      (m.n_parts == m.n_tiles ? m.stream_pages < 24 * (int64_t)m.n_items : blocks <= 1152))
+    return {false, 1, lag};
+  int fold = 1;
+  const int most = 4 * (int64_t)m.stream_pages > m.chunk_tile_pages ? 256 : 32;
+  if (m.req_tok_off && m.kv_split_pages > 0)
+    while (2 * fold * m.kv_split_pages <= most && blocks >= (2 * fold * m.kv_split_pages <= 16 ? 320 : 800) * (int64_t)fold) fold *= 2;
+  return {m.n_single == 0 || m.req_tok_off != nullptr, fold, lag};
+}
+
 int32_t run_attention(const flexco_layer_cfg& c, const flexco_maps& m, const void* q, size_t ldq,
                       const flexco_kv_pool& pool, void* out, size_t ldo, float* lse, float* part_ml, float* part_acc,
                       hipStream_t s, const AttnKeep* keep = nullptr) {
   int32_t rc;
   bool direct = true;    // the matrix-core kernel writes the rows of single-split tiles itself
+  int fold = 1;          // key splits of the work list taken as one
   {
     KernelTimerScope ts(FLEXCO_K_ATTN_FWD, s);
     const int mode = g_chunk_path.load();
-    const bool mixed = m.n_single > 0 && m.n_single < m.n_items;
-    const bool beside = mixed && (mode == 2 || (mode < 0 && m.chunk_tile_pages >= m.stream_pages));
-    const bool chunk = mode > 0 || (mode < 0 && m.n_single == 0) || beside;
+    const AttnPlan plan = mode < 0 ? plan_attention(m, c.n_kv_heads) : AttnPlan{mode > 0 && m.n_single == 0, 1, true};
+    const bool alone = plan.alone;
+    fold = plan.fold;
+    const bool beside = mode == 2 && m.n_single > 0 && m.n_single < m.n_items;
+    const bool chunk = mode > 0 || alone;
     if (!beside) {
-      // (with no single-token item the one-launch kernel has nothing left to do; its support test still decides)
-      rc = launch_attention_mfma(c, m, q, ldq, pool, part_ml, part_acc, out, ldo, lse, s, keep, chunk, chunk && m.n_single == 0);
+      // (with no item of its own the one-launch kernel has nothing left to do; its support test still decides)
+      rc = launch_attention_mfma(c, m, q, ldq, pool, part_ml, part_acc, out, ldo, lse, s, keep, chunk, chunk && alone);
       if (rc == FLEXCO_OK && chunk)
-        rc = launch_attention_chunk_mfma(c, m, q, ldq, pool, part_ml, part_acc, out, ldo, lse, s, keep, m.n_single == 0);
+        rc = launch_attention_chunk_mfma(c, m, q, ldq, pool, part_ml, part_acc, out, ldo, lse, s, keep, alone, fold, plan.lag);
     } else {
       // the decode tokens' kernel on the caller's stream and the chunk items' kernel on the side stream, which
       // leaves the caller's stream before the first and rejoins it after the second: the two run beside each other
@@ -734,14 +775,16 @@ int32_t run_attention(const flexco_layer_cfg& c, const flexco_maps& m, const voi
   if (rc == FLEXCO_EUNSUPPORTED) {
     clear_error();
     direct = false;
+    fold = 1;
     note_fallback(c.dtype, FLEXCO_K_ATTN_FWD);
     KernelTimerScope ts(FLEXCO_K_GENERIC, s);
     rc = launch_attention_generic(c, m, q, ldq, pool, part_ml, part_acc, s);
   }
   if (rc) return rc;
-  if (direct && m.n_parts == m.n_tiles) return FLEXCO_OK;   // every tile had a single key split: nothing left to merge
+  // every tile had a single key range (the folded ones: where all requests have one token): nothing left to merge
+  if (direct && (m.n_parts == m.n_tiles || (m.n_single == m.n_items && m.max_pages <= fold * m.kv_split_pages))) return FLEXCO_OK;
   KernelTimerScope ts(FLEXCO_K_ATTN_MERGE, s);
-  return launch_attention_merge(c, m, part_ml, part_acc, out, ldo, lse, s, direct, keep);
+  return launch_attention_merge(c, m, part_ml, part_acc, out, ldo, lse, s, direct, fold, keep);
 }
 
 }  // namespace

@@ -224,17 +224,20 @@ int32_t launch_attention_mfma(const flexco_layer_cfg& c, const flexco_maps& m, c
                               const flexco_kv_pool& pool, float* part_ml, float* part_acc, void* out, size_t ldo,
                               float* lse, hipStream_t s, const AttnKeep* keep = nullptr, bool skip_chunk = false,
                               bool nothing_to_do = false);
-// the chunk items (everything but single decode tokens) of the same work list, four wavefronts per item, K / V staged in LDS
+// the chunk items (everything but single tokens; alone: those too) of the same work list, four wavefronts per item, K / V staged
+// in LDS; fold: the block of a request of one token takes that many neighbouring key splits as one, the others' partial rows
+// stay unwritten; lag: the reference point of the exponentials may lag the running maximum
 int32_t launch_attention_chunk_mfma(const flexco_layer_cfg& c, const flexco_maps& m, const void* q, size_t ldq,
                                     const flexco_kv_pool& pool, float* part_ml, float* part_acc, void* out, size_t ldo,
-                                    float* lse, hipStream_t s, const AttnKeep* keep = nullptr, bool alone = false);
+                                    float* lse, hipStream_t s, const AttnKeep* keep = nullptr, bool alone = false, int fold = 1,
+                                    bool lag = true);
 // bf16 window backward on the matrix cores; FLEXCO_EUNSUPPORTED (nothing launched) for other shapes
 int32_t launch_attention_bwd_mfma(const flexco_layer_cfg& c, const flexco_kv_pool& pool, const int32_t* seq_pages,
                                   int win_start, int win_len, const void* q, const void* out, const float* lse,
                                   float* delta, const void* dout, void* dq, float* dk_accum, float* dv_accum,
                                   hipStream_t s);
 int32_t launch_attention_merge(const flexco_layer_cfg& c, const flexco_maps& m, const float* part_ml,
-                               const float* part_acc, void* out, size_t ldo, float* lse, hipStream_t s, bool skip_single_split = false,
+                               const float* part_acc, void* out, size_t ldo, float* lse, hipStream_t s, bool direct = false, int fold = 1,
                                const AttnKeep* keep = nullptr);
 int32_t launch_attention_bwd_generic(const flexco_layer_cfg& c, const flexco_kv_pool& pool, const int32_t* seq_pages,
                                      int win_start, int win_len, const void* q, const void* out, const float* lse, float* delta,

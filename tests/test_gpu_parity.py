@@ -186,6 +186,29 @@ def _attention_mixed(name, split):
     assert float(np.max(np.abs(lse - lse_o))) <= (1e-4 if cfg.dtype == "f32" else 2e-2)
 
 
+# the library's own choice of kernel and of key splits taken together (2, 4, .. of the work list's, at most 256 pages; the
+# partial rows in between stay unwritten): work lists cut finely, so that ranges of several splits end inside a split, on its
+# edge and in the last split, with one or with several partial rows left per tile
+@pytest.mark.parametrize("name,split", [("stream", 2), ("stream", 6), ("stream", 34), ("chunks", 2), ("chunks", 6), ("chunks", 8),
+                                        ("both", 2), ("short", 0), ("round", 4)])
+def test_attention_mixed_folded_splits(name, split):
+    say(f"attention_mixed folded {name} split={split}")
+    if name == "stream":                     # the decode tokens carry the time: folded while 400 blocks are left
+        cfg, batch = SMALL_BF16_MHA, gen.mixed_batch(16, 3, decode_ctx=(1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 96, 127, 128, 129, 255, 256, 257, 511, 512, 513)
+                                                     + tuple(range(900, 1500, 9)), prefill=[(40, 33, 73)], finetune=[(130, 17, 147)])
+    elif name == "chunks":                   # the chunks do: ranges of up to 32 pages, the last tile holds one token
+        cfg, batch = SMALL_BF16, gen.mixed_batch(16, 4, decode_ctx=(700,), prefill=[(500, 101, 601), (0, 64, 64)], finetune=[(1000, 77, 1077)])
+    elif name == "both":
+        cfg, batch = SMALL_BF16_G8, gen.mixed_batch(16, 5, decode_ctx=tuple(range(200, 1200, 25)), prefill=[(300, 65, 365)], finetune=[(200, 33, 233)])
+    elif name == "short":                    # nothing but short contexts: the one-wavefront kernel
+        cfg, batch = SMALL_BF16_MHA, gen.mixed_batch(16, 6, decode_ctx=tuple(range(1, 200)))
+    else:                                    # nothing but decode tokens, cut into about one item per wavefront of the chip
+        cfg, batch = SMALL_BF16_MHA, gen.mixed_batch(16, 7, decode_ctx=(150,) * 75)
+    out, a_o, lse, lse_o = attention_case(cfg, batch, split)
+    assert_close("attention out", out, a_o, TOL[cfg.dtype])
+    assert float(np.max(np.abs(lse - lse_o))) <= 2e-2
+
+
 # ------------------------------------------------------------------------------------------
 # attention backward of one token window alone (Sec. 6.1): dQ of the window, dK/dV accumulated
 # into every cached row before the window's end
