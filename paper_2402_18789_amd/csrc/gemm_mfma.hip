@@ -453,16 +453,30 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
       _Pragma("unroll") for (int j = 0; j < NT; ++j)                                                  \
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, bfr_[j]), __builtin_bit_cast(s16x4, af_[i]), acc[i][j], 0, 0, 0); \
   }
-  constexpr bool PF = MT * NT <= 16;
-  int e_first = -1;
-  bf16x4 paf[PF ? MT : 1], pbf[PF ? NT : 1];
-  if constexpr (PF) {
-    if (blockIdx.y == 0) {
-      for (int e = 0; e < ext.n; ++e)
-        if (!FLEXCO_EXT_SKIPS(e)) { e_first = e; break; }
-      if (e_first >= 0) FLEXCO_EXT_LOAD(e_first, 0, paf, pbf)
-    }
+  // The 64-row tile has registers for the operands of eight steps: a decode batch of several adapters has one step per
+  // adapter and target, each a round trip of its own otherwise (48 tokens with four adapters at the 14B shape: gate/up 64.6 -> 60.0
+  // us, down 33.0 -> 31.0, the layer 252 -> 245).
+  constexpr int PF = MT * NT > 16 ? 0 : BM == 64 ? 8 : 1;
+#define FLEXCO_EXT_NEXT(e_, k2_)                                                                      \
+  {                                                                                                   \
+    k2_ += 16;                                                                                        \
+    if (k2_ >= ext.r) {                                                                               \
+      k2_ = 0;                                                                                        \
+      do ++e_; while (e_ < ext.n && FLEXCO_EXT_SKIPS(e_));                                            \
+    }                                                                                                 \
   }
+  const int ext_n = blockIdx.y == 0 ? ext.n : 0;
+  int ext_e = -1, ext_k = ext.r;                    // the first step that was not fetched ahead
+  if (ext_n > 0) FLEXCO_EXT_NEXT(ext_e, ext_k) else ext_e = 0;
+  int n_pf = 0;
+  bf16x4 paf[PF ? PF : 1][MT], pbf[PF ? PF : 1][NT];
+#pragma unroll
+  for (int u = 0; u < PF; ++u)
+    if (ext_e < ext_n) {
+      FLEXCO_EXT_LOAD(ext_e, ext_k, paf[u], pbf[u])
+      ++n_pf;
+      FLEXCO_EXT_NEXT(ext_e, ext_k)
+    }
   // residual and bias in the layout the epilogue stores in: 8 lanes x 8 columns per row, 8 rows per instruction,
   // 32 rows x 64 columns per group of 2 x 4 fragments
   constexpr int NG = (NT + 3) / 4;
@@ -548,23 +562,14 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
   // network (Sec. 4.1) folded into the base projection as extra k-steps of 16, operands read
   // straight from global memory (they are [rows, r] / [r, cols] matrices of a few KB per tile).
   // The first step's operands were fetched before the main loop where the tile leaves registers for them.
-  for (int e = 0; e < (blockIdx.y == 0 ? ext.n : 0); ++e) {
-    if (FLEXCO_EXT_SKIPS(e)) continue;
-    for (int k2 = 0; k2 < ext.r; k2 += 16) {
-      bf16x4 af[MT], bfr[NT];
-      bool have = false;
-      if constexpr (PF) {
-        if (e == e_first && k2 == 0) {
 #pragma unroll
-          for (int i = 0; i < MT; ++i) af[i] = paf[i];
-#pragma unroll
-          for (int j = 0; j < NT; ++j) bfr[j] = pbf[j];
-          have = true;
-        }
-      }
-      if (!have) FLEXCO_EXT_LOAD(e, k2, af, bfr)
-      FLEXCO_EXT_MFMAS(af, bfr)
-    }
+  for (int u = 0; u < PF; ++u)
+    if (u < n_pf) FLEXCO_EXT_MFMAS(paf[u], pbf[u])
+  while (ext_e < ext_n) {
+    bf16x4 af[MT], bfr[NT];
+    FLEXCO_EXT_LOAD(ext_e, ext_k, af, bfr)
+    FLEXCO_EXT_MFMAS(af, bfr)
+    FLEXCO_EXT_NEXT(ext_e, ext_k)
   }
   __syncthreads();   // every wavefront is done with the ring, and (after its own wait above) its loads have landed
   if constexpr (GLU) {
@@ -750,18 +755,10 @@ __global__ __launch_bounds__(256) void gemm_bf16_quad_kernel(const bf16_t* __res
   // The rank-r extension's steps (entry, 16 of its rank) in turn, entries that miss the tile left out.  The operands of the
   // first step are fetched here: their round trip lies open behind the main loop otherwise, every tile (1 % of a 1024-row
   // window's backward; two steps' operands, where there are registers for them, were no faster).
-#define Q_EXT_NEXT(e_, k2_)                                                                           \
-  {                                                                                                   \
-    k2_ += 16;                                                                                        \
-    if (k2_ >= ext.r) {                                                                               \
-      k2_ = 0;                                                                                        \
-      do ++e_; while (e_ < ext.n && FLEXCO_EXT_SKIPS(e_));                                            \
-    }                                                                                                 \
-  }
   const int ext_n = blockIdx.y == 0 ? ext.n : 0;
   int ext_e = -1, ext_k = ext.r;
   bf16x4 xa[MT], xw[NT];
-  if (ext_n > 0) Q_EXT_NEXT(ext_e, ext_k)
+  if (ext_n > 0) FLEXCO_EXT_NEXT(ext_e, ext_k)
   const bool ext_on = ext_n > 0 && ext_e < ext_n;
   if (ext_on) FLEXCO_EXT_LOAD(ext_e, ext_k, xa, xw)
   frag_t fa0[4][2], fa1[4][2], fw0[HN][2], fw1[HN][2];
@@ -789,12 +786,12 @@ __global__ __launch_bounds__(256) void gemm_bf16_quad_kernel(const bf16_t* __res
   // ---- rank-r extension (see the kernel above) ----
   if (ext_on) {
     FLEXCO_EXT_MFMAS(xa, xw)
-    Q_EXT_NEXT(ext_e, ext_k)
+    FLEXCO_EXT_NEXT(ext_e, ext_k)
     while (ext_e < ext_n) {
       bf16x4 af[MT], bfr[NT];
       FLEXCO_EXT_LOAD(ext_e, ext_k, af, bfr)
       FLEXCO_EXT_MFMAS(af, bfr)
-      Q_EXT_NEXT(ext_e, ext_k)
+      FLEXCO_EXT_NEXT(ext_e, ext_k)
     }
   }
   __syncthreads();   // every wavefront is done with the half-tiles, and (after its own wait above) its loads have landed
