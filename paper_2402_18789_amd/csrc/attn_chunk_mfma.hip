@@ -210,13 +210,14 @@ __global__ __launch_bounds__(256, RING == 3 ? 3 : 2) void attn_fwd_chunk_kernel(
     /* lag = LAZY (exponentials then stay below 2^LAZY: no overflow, same relative rounding in bf16), so that the */ \
     /* accumulators are rescaled in few steps - in place, inside a branch the wavefront takes as one - instead */ \
     /* of in every step (32 of a step's 80 vector instructions).                                              */ \
+    float alpha_ = 1.f, l_scaled = l;                                                                 \
     if (__builtin_amdgcn_ballot_w64(mx > m + lag) != 0) {                                             \
       const float m_upd = mx > m + lag ? mx : m;                                                      \
-      const float alpha = __builtin_amdgcn_exp2f(m - m_upd);                                          \
-      l *= alpha;                                                                                     \
+      alpha_ = __builtin_amdgcn_exp2f(m - m_upd);                                                     \
+      l_scaled = l * alpha_;                                                                          \
       m = m_upd;                                                                                      \
       _Pragma("unroll") for (int mt = 0; mt < 8; ++mt)                                                \
-        _Pragma("unroll") for (int j = 0; j < 4; ++j) o[mt][j] *= alpha;                              \
+        _Pragma("unroll") for (int j = 0; j < 4; ++j) o[mt][j] *= alpha_;                             \
     }                                                                                                 \
     const float m_use = (m == -INFINITY) ? 0.f : m;                                                   \
     float p[8], psum = 0.f;                                                                           \
@@ -224,7 +225,7 @@ __global__ __launch_bounds__(256, RING == 3 ? 3 : 2) void attn_fwd_chunk_kernel(
       p[j] = __builtin_amdgcn_exp2f(s[j] - m_use);                                                    \
       psum += p[j];                                                                                   \
     }                                                                                                 \
-    l += psum;                                                                                        \
+    l = lag == 0.f ? __builtin_fmaf(l, alpha_, psum) : l_scaled + psum;   /* (without lag: rounded as in the other kernel) */ \
     bf16x8 pf;                                                                                        \
     _Pragma("unroll") for (int j = 0; j < 8; ++j) pf[j] = (bf16_t)p[j];                               \
     _Pragma("unroll") for (int mt = 0; mt < 8; ++mt)                                                  \
