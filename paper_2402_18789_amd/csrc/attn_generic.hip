@@ -7,6 +7,7 @@
 //   accumulator acc[d] over the keys of the split that the column may see.
 //   part_ml [n_parts, nkv, cols_per_tile, 2], part_acc [n_parts, nkv, cols_per_tile, d]
 // The merge kernel combines the splits of a tile (log-sum-exp weighting).
+#include <algorithm>
 #include "flexco_internal.h"
 #include "device_types.h"
 
@@ -28,14 +29,26 @@ struct AttnArgs {
       *item_split, *item_ntiles;
   int max_pages, nq, nkv, d, ps, split_keys, cols_per_tile;
   float scale;
+  // rows of a tile with a single key split go straight to the output, as the merge kernel would write them
+  void* out;
+  size_t ldo;
+  float* lse;         // or NULL
+  AttnKeep keep;
 };
 
-// One wavefront per column, NW of them per block.  The kernel is a chain of loads (the fp32 configuration's grids do not
+__device__ inline int lane_int(int v, int lane) { return __builtin_amdgcn_readlane(v, lane); }
+__device__ inline float lane_float(float v, int lane) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane)); }
+
+// One wavefront per column, four of a tile's sixteen per block (sixteen kept other CUs idle while they shared one's issue
+// slots: the fp32 configuration's 68-token batch 19 us against 12.6; 40 decode tokens of 500 - 1000 keys 163 against 121).  The kernel is a chain of loads (the fp32 configuration's grids do not
 // fill the chip): K rows and V page rows are read 16 bytes at a time with several loads in flight - a lane per key for the
-// scores, a lane per channel for the output - and a page id is looked up once per page (before: one element and one
-// lookup at a time: 78 us for the fp32 configuration's 68-token batch, 16 now).
-template <typename T, int NW>
-__global__ __launch_bounds__(64 * NW) void attn_fwd_generic_kernel(AttnArgs a, const T* __restrict__ q, size_t ldq,
+// scores, a lane per channel for the output - and a page id is looked up once per page (one element and one
+// lookup at a time: 78 us for the fp32 configuration's 68-token batch).  A column of at most 64 keys has its V
+// on the way beside its K, before the softmax, and takes page ids from the lanes that looked them up; the tables are read in as few
+// dependent steps as there are.
+constexpr int FWD_NW = 4, FWD_COL_BLOCKS = 4;
+template <typename T>
+__global__ __launch_bounds__(64 * FWD_NW) void attn_fwd_generic_kernel(AttnArgs a, const T* __restrict__ q, size_t ldq,
                                                                    const T* __restrict__ kp, const T* __restrict__ vp,
                                                                    float* __restrict__ part_ml,
                                                                    float* __restrict__ part_acc) {
@@ -44,26 +57,41 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_generic_kernel(AttnArgs a, c
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   float* qs = smem + wave * (a.d + a.split_keys);
   float* sc = qs + a.d;
-  // one block per tile of the work item that has this split (blockIdx.z = tile within the item)
-  const int item = blockIdx.x, kvh = blockIdx.y;
-  if ((int)blockIdx.z >= a.item_ntiles[item]) return;
-  const int tile = a.item_tile[item] + blockIdx.z, split = a.item_split[item];
-  if (split >= a.tile_nsplit[tile]) return;
-  const int r = a.tile_req[tile], t0 = a.tile_tok0[tile], ntok = a.tile_ntok[tile];
+  // FWD_COL_BLOCKS blocks per tile of the work item that has this split (blockIdx.z = tile within the item, run of columns)
+  const int item = blockIdx.x, kvh = blockIdx.y, tile_in = blockIdx.z / FWD_COL_BLOCKS, run = blockIdx.z % FWD_COL_BLOCKS;
+  const int ntl = a.item_ntiles[item], tile0 = a.item_tile[item], split = a.item_split[item];
+  if (tile_in >= ntl) return;
+  const int tile = tile0 + tile_in;
+  const int r = a.tile_req[tile], t0 = a.tile_tok0[tile], ntok = a.tile_ntok[tile], nsplit = a.tile_nsplit[tile], part0 = a.tile_part0[tile];
+  if (split >= nsplit) return;
   const int group = a.nq / a.nkv;
-  const int part = a.tile_part0[tile] + split;
-  const int k0 = split * a.split_keys;       // the first key of a page
-  const int32_t* bt = a.block_table + (size_t)r * a.max_pages + k0 / a.ps;
-  for (int c = wave; c < ntok * group; c += NW) {
+  const int part = part0 + split;
+  const int k0 = split * a.split_keys, pg0 = k0 / a.ps;       // the first key of a page
+  const int32_t* bt = a.block_table + (size_t)r * a.max_pages + pg0;
+  const int my_pg = lane / a.ps, my_off = lane % a.ps;        // where the lane's key is in a run of 64
+  const bool whole = nsplit == 1;                             // the whole key range: normalised rows, straight to the output
+  for (int c = run * FWD_NW + wave; c < ntok * group; c += FWD_NW * FWD_COL_BLOCKS) {
     const int t = t0 + c / group, h = kvh * group + c % group;
-    const int kend = min(k0 + a.split_keys, a.tok_pos[t] + 1);
-    const int nk = max(0, kend - k0);
+    const int pos = a.tok_pos[t];
+    const int first_page = bt[min(my_pg, a.max_pages - 1 - pg0)];     // (past the last key: not used)
     for (int dd = lane; dd < a.d; dd += 64) qs[dd] = ld(q + (size_t)t * ldq + h * a.d + dd);
+    const int nk = max(0, min(k0 + a.split_keys, pos + 1) - k0);
+    // a column of one run: V of the lane's first channel, 64 keys
+    const bool short_run = nk <= 64 && a.ps % N == 0;         // (uniform)
+    float v1[64 / N][N];
+    if (short_run) {
+#pragma unroll
+      for (int u = 0; u < 64 / N; ++u) {
+        const int un = min(u * N, max(nk - 1, 0) / N * N);    // past the last key: the last unit again, not used
+        const T* vr = vp + (((size_t)lane_int(first_page, un) * a.nkv + kvh) * (size_t)a.d + min(lane, a.d - 1)) * a.ps + lane_int(my_off, un);
+        Vec<T>::load(vr, v1[u]);
+      }
+    }
     __builtin_amdgcn_wave_barrier();
     float m = -INFINITY;
     for (int jj = lane; jj < nk; jj += 64) {
-      const size_t page = bt[jj / a.ps];
-      const T* kr = kp + ((page * a.nkv + kvh) * a.ps + jj % a.ps) * (size_t)a.d;   // rows are whole 16-byte units
+      const size_t page = jj < 64 ? first_page : bt[jj / a.ps];
+      const T* kr = kp + ((page * a.nkv + kvh) * a.ps + (jj < 64 ? my_off : jj % a.ps)) * (size_t)a.d;   // rows are whole 16-byte units
       float s = 0.f;
 #pragma unroll 8
       for (int dd = 0; dd < a.d; dd += N) {
@@ -86,27 +114,46 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_generic_kernel(AttnArgs a, c
     l = wsum(l);
     __builtin_amdgcn_wave_barrier();
     const size_t idx = ((size_t)part * a.nkv + kvh) * a.cols_per_tile + c;
+    const bool kept = whole && a.keep.lse2 && t >= a.keep.tok0 && t < a.keep.tok0 + a.keep.n;
+    const float inv = 1.0f / l;
     for (int dd = lane; dd < a.d; dd += 64) {
       float acc = 0.f;
-      for (int j0 = 0; j0 < nk; j0 += a.ps) {
-        const T* vr = vp + (((size_t)bt[j0 / a.ps] * a.nkv + kvh) * (size_t)a.d + dd) * a.ps;
-        const int n = min(a.ps, nk - j0);
-        if (a.ps % N == 0) {                 // (a page row is whole 16-byte units; slots past the last key may hold anything)
-#pragma unroll 4
-          for (int p0 = 0; p0 < n; p0 += N) {
-            float v[N];
-            Vec<T>::load(vr + p0, v);
+      if (short_run && dd < 64) {
 #pragma unroll
-            for (int e = 0; e < N; ++e)
-              if (p0 + e < n) acc += sc[j0 + p0 + e] * v[e];
+        for (int u = 0; u < 64 / N; ++u)
+#pragma unroll
+          for (int e = 0; e < N; ++e)
+            if (u * N + e < nk) acc += sc[u * N + e] * v1[u][e];
+      } else {
+        for (int j0 = 0; j0 < nk; j0 += a.ps) {
+          const T* vr = vp + (((size_t)bt[j0 / a.ps] * a.nkv + kvh) * (size_t)a.d + dd) * a.ps;
+          const int n = min(a.ps, nk - j0);
+          if (a.ps % N == 0) {               // (a page row is whole 16-byte units; slots past the last key may hold anything)
+#pragma unroll 4
+            for (int p0 = 0; p0 < n; p0 += N) {
+              float v[N];
+              Vec<T>::load(vr + p0, v);
+#pragma unroll
+              for (int e = 0; e < N; ++e)
+                if (p0 + e < n) acc += sc[j0 + p0 + e] * v[e];
+            }
+          } else {
+            for (int p = 0; p < n; ++p) acc += sc[j0 + p] * ld(vr + p);
           }
-        } else {
-          for (int p = 0; p < n; ++p) acc += sc[j0 + p] * ld(vr + p);
         }
       }
-      part_acc[idx * a.d + dd] = acc;
+      if (!whole) {
+        part_acc[idx * a.d + dd] = acc;
+        continue;
+      }
+      st((T*)a.out + (size_t)t * a.ldo + h * a.d + dd, acc * inv);
+      if (kept) st((T*)a.keep.out2 + ((size_t)(t - a.keep.tok0) * a.nq + h) * a.d + dd, acc * inv);
     }
-    if (lane == 0) { part_ml[idx * 2] = m; part_ml[idx * 2 + 1] = l; }
+    if (lane == 0) {
+      if (!whole) { part_ml[idx * 2] = m; part_ml[idx * 2 + 1] = l; }
+      else if (a.lse) a.lse[(size_t)t * a.nq + h] = m + __logf(l);
+      if (kept) a.keep.lse2[(size_t)(t - a.keep.tok0) * a.nq + h] = m + __logf(l);
+    }
     __builtin_amdgcn_wave_barrier();
   }
 }
@@ -127,7 +174,7 @@ __global__ __launch_bounds__(64) void attn_merge_kernel(const int32_t* __restric
                                                         const float* __restrict__ part_ml,
                                                         const float* __restrict__ part_acc, T* __restrict__ out,
                                                         size_t ldo, float* __restrict__ lse, int nq, int nkv, int d,
-                                                        int cols_per_tile, int direct, int fold_in, const int32_t* __restrict__ req_tok_off,
+                                                        int cols_per_tile, int fold_in, const int32_t* __restrict__ req_tok_off,
                                                         const int32_t* __restrict__ tok_req, AttnKeep keep) {
   const int t = blockIdx.x, h = blockIdx.y;
   const int group = nq / nkv, kvh = h / group;
@@ -135,7 +182,7 @@ __global__ __launch_bounds__(64) void attn_merge_kernel(const int32_t* __restric
   const int c = (t - tile_tok0[tile]) * group + h % group;
   const int nsplit = tile_nsplit[tile], part0 = tile_part0[tile];
   const int fold = token_fold(t, fold_in, tok_req, req_tok_off);
-  if (direct && nsplit <= fold) return;   // the attention kernel has written these rows itself
+  if (nsplit <= fold) return;   // the attention kernel has written these rows itself
   float M = -INFINITY;
   for (int s = 0; s < nsplit; s += fold) {
     const size_t idx = ((size_t)(part0 + s) * nkv + kvh) * cols_per_tile + c;
@@ -184,7 +231,7 @@ __global__ __launch_bounds__(256) void attn_merge128_kernel(const int32_t* __res
                                                             const float* __restrict__ part_ml,
                                                             const float* __restrict__ part_acc, T* __restrict__ out,
                                                             size_t ldo, float* __restrict__ lse, int nq, int nkv,
-                                                            int cols_per_tile, int direct, int fold_in, const int32_t* __restrict__ req_tok_off,
+                                                            int cols_per_tile, int fold_in, const int32_t* __restrict__ req_tok_off,
                                                         const int32_t* __restrict__ tok_req, AttnKeep keep) {
   constexpr int d = 128;
   const int t = blockIdx.x, h = blockIdx.y * 8 + (threadIdx.x >> 5), ln = threadIdx.x & 31;
@@ -193,7 +240,7 @@ __global__ __launch_bounds__(256) void attn_merge128_kernel(const int32_t* __res
   const int tile = tok_tile[t];
   const int fold = token_fold(t, fold_in, tok_req, req_tok_off);
   const int nsplit = (tile_nsplit[tile] + fold - 1) / fold;     // partial rows
-  if (direct && nsplit == 1) return;   // the attention kernel has written these rows itself
+  if (nsplit == 1) return;   // the attention kernel has written these rows itself
   const int c = (t - tile_tok0[tile]) * group + h % group;
   const size_t idx0 = ((size_t)tile_part0[tile] * nkv + kvh) * cols_per_tile + c;
   const size_t step = (size_t)fold * nkv * cols_per_tile;         // from one partial row to the next
@@ -246,7 +293,12 @@ __global__ __launch_bounds__(256) void attn_merge128_kernel(const int32_t* __res
 // = cached rows [0, l).  P is recomputed from Q, K and the stored log-sum-exp.
 // ------------------------------------------------------------------------------------------
 // (delta = rowsum(dO (.) O) of a row is computed here and left for the dK / dV kernel)
-template <typename T>
+//
+// Few of the lane groups' guards and LDS lookups of a 64-key run are needed: a lane owns channels lane + 64 u, u < DU = the least of
+// 1, 2, 4 that covers head_dim, and a key's (row's) factor and address come from the lane that holds them (lane_float,
+// lane_int) instead of from LDS (fp32 configuration 16.1 -> 11.2
+// us for dQ, 9.9 -> 8.2 for dK / dV: most of a run's instructions were guards of channels past head_dim).
+template <typename T, int DU>
 __global__ __launch_bounds__(64) void attn_bwd_dq_generic_kernel(const T* __restrict__ q, const T* __restrict__ dout,
                                                                  const T* __restrict__ out,
                                                                  const float* __restrict__ lse,
@@ -255,18 +307,20 @@ __global__ __launch_bounds__(64) void attn_bwd_dq_generic_kernel(const T* __rest
                                                                  const int32_t* __restrict__ pages,
                                                                  T* __restrict__ dq, int win_start, int nq, int nkv,
                                                                  int d, int ps, float scale) {
-  extern __shared__ float smem[];   // q[d], do[d], ds[64], row of each key of the step [64]
+  extern __shared__ float smem[];   // q[d], do[d]
   constexpr int N = Vec<T>::N;
   float* qs = smem;
   float* dos = smem + d;
-  float* dss = smem + 2 * d;
-  size_t* rows = (size_t*)(dss + 64);   // the key's row of the K pool (d is even: 8-byte aligned)
   const size_t i = blockIdx.x;
   const int h = blockIdx.y, lane = threadIdx.x;
   const int group = nq / nkv, kvh = h / group;
   const int p = win_start + (int)i;
+  const float row_lse = lse[i * nq + h];
   float row_delta = 0.f;
-  for (int dd = lane; dd < d; dd += 64) {
+#pragma unroll
+  for (int u = 0; u < DU; ++u) {
+    const int dd = lane + 64 * u;
+    if (dd >= d) break;
     qs[dd] = ld(q + (i * nq + h) * d + dd);
     const float o = ld(dout + (i * nq + h) * d + dd);
     dos[dd] = o;
@@ -274,58 +328,55 @@ __global__ __launch_bounds__(64) void attn_bwd_dq_generic_kernel(const T* __rest
   }
   row_delta = wsum(row_delta);
   if (lane == 0) delta[i * nq + h] = row_delta;
-  const float row_lse = lse[i * nq + h];
-  float acc[4] = {0.f, 0.f, 0.f, 0.f};   // d <= 256
+  float acc[DU];
+#pragma unroll
+  for (int u = 0; u < DU; ++u) acc[u] = 0.f;
+  __builtin_amdgcn_wave_barrier();
   for (int kc = 0; kc <= p; kc += 64) {
-    __builtin_amdgcn_wave_barrier();
-    const int j = kc + lane;
-    float ds = 0.f;
-    if (j <= p) {
-      const size_t page = pages[j / ps];
-      const size_t row = (page * nkv + kvh) * ps + j % ps;
-      rows[lane] = row;
-      const T* kr = kp + row * (size_t)d;
-      const T* vr = vp + ((page * nkv + kvh) * (size_t)d) * ps + j % ps;
-      float s = 0.f, dp = 0.f;
-      // eight rows of V on their way per lane (a V element is a load of its own; 32 for bf16, 16 for fp32 had too few wavefronts
-      // on a CU: window of 256 rows in 2048, head_dim 256 2524 -> 1819 us of the layer's backward, 64 2466 -> 2303, fp32 of
-      // head_dim 64 2195 -> 2092)
-      constexpr int U = 8 / N;
+    const int j = min(kc + lane, p);
+    const int my_page = pages[j / ps], my_off = j % ps;
+    const size_t page = my_page;
+    const T* kr = kp + ((page * nkv + kvh) * ps + my_off) * (size_t)d;
+    const T* vr = vp + ((page * nkv + kvh) * (size_t)d) * ps + my_off;
+    float s = 0.f, dp = 0.f;
+    // eight rows of V on their way per lane (a V element is a load of its own; 32 for bf16, 16 for fp32 had too few wavefronts
+    // on a CU: window of 256 rows in 2048, head_dim 256 2524 -> 1819 us of the layer's backward, 64 2466 -> 2303, fp32 of
+    // head_dim 64 2195 -> 2092; and 32 with a grid that leaves slots empty 13.8 us against 11.2: code that runs once is
+    // fetched once, and fetching it is what such a launch waits for)
+    constexpr int U = 8 / N;
 #pragma unroll U
-      for (int dd = 0; dd < d; dd += N) {
-        float kv[N], vv[N];
-        Vec<T>::load(kr + dd, kv);
+    for (int dd = 0; dd < d; dd += N) {
+      float kv[N], vv[N];
+      Vec<T>::load(kr + dd, kv);
 #pragma unroll
-        for (int e = 0; e < N; ++e) vv[e] = ld(vr + (size_t)(dd + e) * ps);
+      for (int e = 0; e < N; ++e, vr += ps) vv[e] = ld(vr);
 #pragma unroll
-        for (int e = 0; e < N; ++e) {
-          s += qs[dd + e] * kv[e];
-          dp += dos[dd + e] * vv[e];
-        }
+      for (int e = 0; e < N; ++e) {
+        s += qs[dd + e] * kv[e];
+        dp += dos[dd + e] * vv[e];
       }
-      const float pj = __expf(s * scale - row_lse);
-      ds = pj * (dp - row_delta) * scale;
     }
-    dss[lane] = ds;
-    __builtin_amdgcn_wave_barrier();
+    const float pj = __expf(s * scale - row_lse);
+    const float ds = kc + lane <= p ? pj * (dp - row_delta) * scale : 0.f;
     const int nk = min(64, p + 1 - kc);
 #pragma unroll 8
     for (int jj = 0; jj < nk; ++jj) {
-      const T* kr = kp + rows[jj] * d;
-      const float w = dss[jj];
+      const T* kj = kp + (((size_t)lane_int(my_page, jj) * nkv + kvh) * ps + lane_int(my_off, jj)) * (size_t)d;
+      const float w = lane_float(ds, jj);
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (lane + 64 * u < d) acc[u] += w * ld(kr + lane + 64 * u);
+      for (int u = 0; u < DU; ++u)
+        if (DU == 1 || lane + 64 * u < d) acc[u] += w * ld(kj + (DU == 1 ? min(lane, d - 1) : lane + 64 * u));
     }
   }
 #pragma unroll
-  for (int u = 0; u < 4; ++u)
+  for (int u = 0; u < DU; ++u)
     if (lane + 64 * u < d) st(dq + (i * nq + h) * d + lane + 64 * u, acc[u]);
 }
 
 // one wave per (key j, kv head): sums over every window row that sees key j and every
 // query head of the group; adds into the KV-gradient accumulator rows (Sec. 7).
-template <typename T>
+// VEC: rows of q and dout are read 16 bytes at a time (their alignment is the caller's).
+template <typename T, int DU, bool VEC, bool FEW>
 __global__ __launch_bounds__(64) void attn_bwd_dkv_generic_kernel(const T* __restrict__ q, const T* __restrict__ dout,
                                                                   const float* __restrict__ lse,
                                                                   const float* __restrict__ delta,
@@ -335,11 +386,10 @@ __global__ __launch_bounds__(64) void attn_bwd_dkv_generic_kernel(const T* __res
                                                                   float* __restrict__ dv_accum, int win_start,
                                                                   int win_len, int nq, int nkv, int d, int ps,
                                                                   float scale) {
-  extern __shared__ float smem[];   // k[d], v[d], p[64], ds[64]
+  extern __shared__ float smem[];   // k[d], v[d]
+  constexpr int N = VEC ? Vec<T>::N : 1;
   float* ks = smem;
   float* vs = smem + d;
-  float* pss = smem + 2 * d;
-  float* dss = pss + 64;
   const int j = blockIdx.x, kvh = blockIdx.y, lane = threadIdx.x;
   const int group = nq / nkv;
   const size_t page = pages[j / ps];
@@ -349,44 +399,53 @@ __global__ __launch_bounds__(64) void attn_bwd_dkv_generic_kernel(const T* __res
   }
   const int i_first = max(0, j - win_start);          // first window row that sees key j
   const int n_pairs = (win_len - i_first) * group;
-  float dk[4] = {0.f, 0.f, 0.f, 0.f}, dv[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int pc = 0; pc < n_pairs; pc += 64) {
-    __builtin_amdgcn_wave_barrier();
-    const int pr = pc + lane;
-    float pj = 0.f, ds = 0.f;
-    if (pr < n_pairs) {
-      const size_t i = i_first + pr / group;
-      const int h = kvh * group + pr % group;
-      const T* qr = q + (i * nq + h) * d;
-      const T* dor = dout + (i * nq + h) * d;
-      float s = 0.f, dp = 0.f;
-      for (int dd = 0; dd < d; ++dd) {
-        s += ld(qr + dd) * ks[dd];
-        dp += ld(dor + dd) * vs[dd];
-      }
-      pj = __expf(s * scale - lse[i * nq + h]);
-      ds = pj * (dp - delta[i * nq + h]) * scale;
-    }
-    pss[lane] = pj;
-    dss[lane] = ds;
-    __builtin_amdgcn_wave_barrier();
-    const int np = min(64, n_pairs - pc);
-    for (int pp = 0; pp < np; ++pp) {
-      const size_t i = i_first + (pc + pp) / group;
-      const int h = kvh * group + (pc + pp) % group;
-      const float wp = pss[pp], wd = dss[pp];
+  float dk[DU], dv[DU];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int dd = lane + 64 * u;
-        if (dd < d) {
-          dv[u] += wp * ld(dout + (i * nq + h) * d + dd);
-          dk[u] += wd * ld(q + (i * nq + h) * d + dd);
+  for (int u = 0; u < DU; ++u) dk[u] = dv[u] = 0.f;
+  __builtin_amdgcn_wave_barrier();
+  for (int pc = 0; pc < n_pairs; pc += 64) {
+    const int pr = min(pc + lane, n_pairs - 1);
+    const int my_i = i_first + pr / group, my_h = kvh * group + pr % group;
+    const size_t row = (size_t)my_i * nq + my_h;                // of q and dout
+    const T* qr = q + row * d;
+    const T* dor = dout + row * d;
+    const float row_lse = lse[row], row_delta = delta[row];
+    float s = 0.f, dp = 0.f;
+#pragma unroll VEC ? (FEW ? 8 : 4) : 1
+    for (int dd = 0; dd < d; dd += N) {
+      float qv[N], ov[N];
+      if constexpr (VEC) {
+        Vec<T>::load(qr + dd, qv);
+        Vec<T>::load(dor + dd, ov);
+      } else {
+        qv[0] = ld(qr + dd);
+        ov[0] = ld(dor + dd);
+      }
+#pragma unroll
+      for (int e = 0; e < N; ++e) {
+        s += qv[e] * ks[dd + e];
+        dp += ov[e] * vs[dd + e];
+      }
+    }
+    const float pj = pc + lane < n_pairs ? __expf(s * scale - row_lse) : 0.f;
+    const float ds = pj * (dp - row_delta) * scale;
+    const int np = min(64, n_pairs - pc);
+#pragma unroll FEW ? 16 : 4
+    for (int pp = 0; pp < np; ++pp) {
+      const size_t at = ((size_t)lane_int(my_i, pp) * nq + lane_int(my_h, pp)) * d;
+      const float wp = lane_float(pj, pp), wd = lane_float(ds, pp);
+#pragma unroll
+      for (int u = 0; u < DU; ++u) {
+        const int dd = DU == 1 ? min(lane, d - 1) : lane + 64 * u;
+        if (DU == 1 || dd < d) {
+          dv[u] += wp * ld(dout + at + dd);
+          dk[u] += wd * ld(q + at + dd);
         }
       }
     }
   }
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
+  for (int u = 0; u < DU; ++u) {
     const int dd = lane + 64 * u;
     if (dd < d) {
       dk_accum[((size_t)j * nkv + kvh) * d + dd] += dk[u];
@@ -408,8 +467,11 @@ static int32_t post_launch(const char* what) {
 }
 
 int32_t launch_attention_generic(const flexco_layer_cfg& c, const flexco_maps& m, const void* q, size_t ldq,
-                                 const flexco_kv_pool& pool, float* part_ml, float* part_acc, hipStream_t s) {
+                                 const flexco_kv_pool& pool, float* part_ml, float* part_acc, void* out, size_t ldo, float* lse,
+                                 hipStream_t s, const AttnKeep* keep) {
   AttnArgs a;
+  a.out = out; a.ldo = ldo; a.lse = lse;
+  a.keep = keep ? *keep : AttnKeep{nullptr, nullptr, 0, 0};
   a.tok_pos = m.tok_pos; a.block_table = m.block_table; a.tile_req = m.tile_req; a.tile_tok0 = m.tile_tok0;
   a.tile_ntok = m.tile_ntok; a.tile_nsplit = m.tile_nsplit; a.tile_part0 = m.tile_part0; a.item_tile = m.item_tile;
   a.item_split = m.item_split; a.item_ntiles = m.item_ntiles;
@@ -419,20 +481,15 @@ int32_t launch_attention_generic(const flexco_layer_cfg& c, const flexco_maps& m
   a.scale = 1.0f / sqrtf((float)c.head_dim);
   const size_t shm = 4 * sizeof(float) * (size_t)(a.d + a.split_keys);
   if (shm > 64 * 1024) return fail(FLEXCO_EUNSUPPORTED, "kv_split_pages * page_size = %d keys is too large for the generic attention kernel", a.split_keys);
-  const dim3 grid(m.n_items, c.n_kv_heads, FLEXCO_ATTN_ITEM_TILES);
-  // a tile has up to 16 columns: a wavefront for each while their score rows fit the same LDS
-  if (4 * shm <= 64 * 1024)
-    DISPATCH_T(c.dtype, hipLaunchKernelGGL((attn_fwd_generic_kernel<T, 16>), grid, dim3(1024), 4 * shm, s, a, (const T*)q, ldq,
-                                           (const T*)pool.k_pages, (const T*)pool.v_pages, part_ml, part_acc));
-  else
-    DISPATCH_T(c.dtype, hipLaunchKernelGGL((attn_fwd_generic_kernel<T, 4>), grid, dim3(256), shm, s, a, (const T*)q, ldq,
-                                           (const T*)pool.k_pages, (const T*)pool.v_pages, part_ml, part_acc));
+  const dim3 grid(m.n_items, c.n_kv_heads, FLEXCO_ATTN_ITEM_TILES * FWD_COL_BLOCKS);
+  DISPATCH_T(c.dtype, hipLaunchKernelGGL((attn_fwd_generic_kernel<T>), grid, dim3(64 * FWD_NW), shm, s, a, (const T*)q, ldq,
+                                         (const T*)pool.k_pages, (const T*)pool.v_pages, part_ml, part_acc));
   return post_launch("attn_fwd_generic");
 }
 
 int32_t launch_attention_merge(const flexco_layer_cfg& c, const flexco_maps& m, const float* part_ml,
                                const float* part_acc, void* out, size_t ldo, float* lse, hipStream_t s,
-                               bool direct, int fold, const AttnKeep* keep_in) {
+                               int fold, const AttnKeep* keep_in) {
   AttnKeep keep{nullptr, nullptr, 0, 0};
   if (keep_in) keep = *keep_in;
   const int cpt = m.tile_tokens * (c.n_q_heads / c.n_kv_heads);
@@ -440,12 +497,12 @@ int32_t launch_attention_merge(const flexco_layer_cfg& c, const flexco_maps& m, 
       ((uintptr_t)keep.out2 & 15) == 0) {
     DISPATCH_T(c.dtype, hipLaunchKernelGGL((attn_merge128_kernel<T>), dim3(m.T, (c.n_q_heads + 7) / 8), dim3(256), 0, s,
                                            m.tok_tile, m.tile_tok0, m.tile_nsplit, m.tile_part0, part_ml, part_acc, (T*)out,
-                                           ldo, lse, c.n_q_heads, c.n_kv_heads, cpt, direct ? 1 : 0, fold, m.req_tok_off, m.tok_req, keep));
+                                           ldo, lse, c.n_q_heads, c.n_kv_heads, cpt, fold, m.req_tok_off, m.tok_req, keep));
     return post_launch("attn_merge");
   }
   DISPATCH_T(c.dtype, hipLaunchKernelGGL((attn_merge_kernel<T>), dim3(m.T, c.n_q_heads), dim3(64), 0, s, m.tok_tile,
                                          m.tile_tok0, m.tile_nsplit, m.tile_part0, part_ml, part_acc, (T*)out, ldo,
-                                         lse, c.n_q_heads, c.n_kv_heads, c.head_dim, cpt, direct ? 1 : 0, fold, m.req_tok_off, m.tok_req, keep));
+                                         lse, c.n_q_heads, c.n_kv_heads, c.head_dim, cpt, fold, m.req_tok_off, m.tok_req, keep));
   return post_launch("attn_merge");
 }
 
@@ -454,16 +511,27 @@ int32_t launch_attention_bwd_generic(const flexco_layer_cfg& c, const flexco_kv_
                                      const void* dout, void* dq, float* dk_accum, float* dv_accum, hipStream_t s) {
   const float scale = 1.0f / sqrtf((float)c.head_dim);
   const int l = win_start + win_len;
-  const size_t shm = sizeof(float) * (2 * (size_t)c.head_dim + 64) + sizeof(size_t) * 64;   // (dK/dV: two score rows of 64)
-  DISPATCH_T(c.dtype, {
-    hipLaunchKernelGGL((attn_bwd_dq_generic_kernel<T>), dim3(win_len, c.n_q_heads), dim3(64), shm, s, (const T*)q,
-                       (const T*)dout, (const T*)out, lse, delta, (const T*)pool.k_pages, (const T*)pool.v_pages, seq_pages,
-                       (T*)dq, win_start, c.n_q_heads, c.n_kv_heads, c.head_dim, c.page_size, scale);
-    hipLaunchKernelGGL((attn_bwd_dkv_generic_kernel<T>), dim3(l, c.n_kv_heads), dim3(64), shm, s, (const T*)q,
-                       (const T*)dout, lse, delta, (const T*)pool.k_pages, (const T*)pool.v_pages, seq_pages,
-                       dk_accum, dv_accum, win_start, win_len, c.n_q_heads, c.n_kv_heads, c.head_dim, c.page_size,
-                       scale);
-  });
+  const size_t shm = sizeof(float) * 2 * (size_t)c.head_dim;
+  const bool vec = aligned16(q) && aligned16(dout);      // (head_dim rows are whole 16-byte units)
+#define FLEXCO_BWD_GENERIC(DU_, VEC_, FEW_)                                                                            \
+  DISPATCH_T(c.dtype, {                                                                                               \
+    hipLaunchKernelGGL((attn_bwd_dq_generic_kernel<T, DU_>), dim3(win_len, c.n_q_heads), dim3(64), shm, s, (const T*)q, (const T*)dout, \
+                       (const T*)out, lse, delta, (const T*)pool.k_pages, (const T*)pool.v_pages, seq_pages, (T*)dq, win_start,         \
+                       c.n_q_heads, c.n_kv_heads, c.head_dim, c.page_size, scale);                                    \
+    hipLaunchKernelGGL((attn_bwd_dkv_generic_kernel<T, DU_, VEC_, FEW_>), dim3(l, c.n_kv_heads), dim3(64), shm, s, (const T*)q, (const T*)dout, \
+                       lse, delta, (const T*)pool.k_pages, (const T*)pool.v_pages, seq_pages, dk_accum, dv_accum, win_start, win_len,   \
+                       c.n_q_heads, c.n_kv_heads, c.head_dim, c.page_size, scale);                                    \
+  })
+#define FLEXCO_BWD_GENERIC_D(VEC_, FEW_)                         \
+  if (c.head_dim <= 64) FLEXCO_BWD_GENERIC(1, VEC_, FEW_);       \
+  else if (c.head_dim <= 128) FLEXCO_BWD_GENERIC(2, VEC_, FEW_); \
+  else FLEXCO_BWD_GENERIC(4, VEC_, FEW_);
+  // (at most one wavefront per SIMD: more rows at a time per lane, fp32 configuration 8.2 -> 6.6 us)
+  if (vec && (long)l * c.n_kv_heads <= 1024) { FLEXCO_BWD_GENERIC_D(true, true) }
+  else if (vec) { FLEXCO_BWD_GENERIC_D(true, false) }
+  else { FLEXCO_BWD_GENERIC_D(false, false) }
+#undef FLEXCO_BWD_GENERIC_D
+#undef FLEXCO_BWD_GENERIC
   return post_launch("attn_bwd_generic");
 }
 

@@ -737,7 +737,6 @@ int32_t run_attention(const flexco_layer_cfg& c, const flexco_maps& m, const voi
                       const flexco_kv_pool& pool, void* out, size_t ldo, float* lse, float* part_ml, float* part_acc,
                       hipStream_t s, const AttnKeep* keep = nullptr) {
   int32_t rc;
-  bool direct = true;    // the matrix-core kernel writes the rows of single-split tiles itself
   int fold = 1;          // key splits of the work list taken as one
   {
     KernelTimerScope ts(FLEXCO_K_ATTN_FWD, s);
@@ -774,17 +773,16 @@ int32_t run_attention(const flexco_layer_cfg& c, const flexco_maps& m, const voi
   }
   if (rc == FLEXCO_EUNSUPPORTED) {
     clear_error();
-    direct = false;
     fold = 1;
     note_fallback(c.dtype, FLEXCO_K_ATTN_FWD);
     KernelTimerScope ts(FLEXCO_K_GENERIC, s);
-    rc = launch_attention_generic(c, m, q, ldq, pool, part_ml, part_acc, s);
+    rc = launch_attention_generic(c, m, q, ldq, pool, part_ml, part_acc, out, ldo, lse, s, keep);
   }
   if (rc) return rc;
   // every tile had a single key range (the folded ones: where all requests have one token): nothing left to merge
-  if (direct && (m.n_parts == m.n_tiles || (m.n_single == m.n_items && m.max_pages <= fold * m.kv_split_pages))) return FLEXCO_OK;
+  if (m.n_parts == m.n_tiles || (m.n_single == m.n_items && m.max_pages <= fold * m.kv_split_pages)) return FLEXCO_OK;
   KernelTimerScope ts(FLEXCO_K_ATTN_MERGE, s);
-  return launch_attention_merge(c, m, part_ml, part_acc, out, ldo, lse, s, direct, fold, keep);
+  return launch_attention_merge(c, m, part_ml, part_acc, out, ldo, lse, s, fold, keep);
 }
 
 }  // namespace

@@ -210,9 +210,6 @@ int32_t launch_lora_bwd(const LoraTarget* tg, int count, void* dx, size_t lddx, 
                         hipStream_t s, bool relu = false);
 int32_t launch_relu_mask(float* u, float* t, size_t count, hipStream_t s);
 
-int32_t launch_attention_generic(const flexco_layer_cfg& c, const flexco_maps& m, const void* q, size_t ldq,
-                                 const flexco_kv_pool& pool, float* part_ml, float* part_acc, hipStream_t s);
-// bf16, head_dim 128, page_size 16, group <= 16; otherwise FLEXCO_EUNSUPPORTED without launching
 // The finetune window's rows of the attention output and of the log-sum-exp, written a second time where the
 // backward pass keeps them (row i of the window at out2 + i * nq d / lse2 + i * nq); lse2 = NULL: none.
 struct AttnKeep {
@@ -220,6 +217,10 @@ struct AttnKeep {
   float* lse2;
   int tok0, n;      // the window's token rows [tok0, tok0 + n)
 };
+int32_t launch_attention_generic(const flexco_layer_cfg& c, const flexco_maps& m, const void* q, size_t ldq,
+                                 const flexco_kv_pool& pool, float* part_ml, float* part_acc, void* out, size_t ldo, float* lse,
+                                 hipStream_t s, const AttnKeep* keep);
+// bf16, head_dim 128, page_size 16, group <= 16; otherwise FLEXCO_EUNSUPPORTED without launching
 int32_t launch_attention_mfma(const flexco_layer_cfg& c, const flexco_maps& m, const void* q, size_t ldq,
                               const flexco_kv_pool& pool, float* part_ml, float* part_acc, void* out, size_t ldo,
                               float* lse, hipStream_t s, const AttnKeep* keep = nullptr, bool skip_chunk = false,
@@ -237,7 +238,7 @@ int32_t launch_attention_bwd_mfma(const flexco_layer_cfg& c, const flexco_kv_poo
                                   float* delta, const void* dout, void* dq, float* dk_accum, float* dv_accum,
                                   hipStream_t s);
 int32_t launch_attention_merge(const flexco_layer_cfg& c, const flexco_maps& m, const float* part_ml,
-                               const float* part_acc, void* out, size_t ldo, float* lse, hipStream_t s, bool direct = false, int fold = 1,
+                               const float* part_acc, void* out, size_t ldo, float* lse, hipStream_t s, int fold = 1,
                                const AttnKeep* keep = nullptr);
 int32_t launch_attention_bwd_generic(const flexco_layer_cfg& c, const flexco_kv_pool& pool, const int32_t* seq_pages,
                                      int win_start, int win_len, const void* q, const void* out, const float* lse, float* delta,

@@ -81,3 +81,49 @@ def test_generic_attention_backward(cfg, win_start, win_len):
     assert_close("dq", to_np(dq), dq_o, TOL[cfg.dtype])
     assert_close("dk", to_np(dk) - 1.0, dk_o, TOL[cfg.dtype])
     assert_close("dv", to_np(dv) - 1.0, dv_o, TOL[cfg.dtype])
+
+
+# the forms of the backward kernels: one, two and four channels per lane; accumulator rows x kv heads up to 1024 and above it; Q and dO
+# off their 16-byte alignment (element by element).  Forward: contexts around the 64 keys that are fetched ahead.
+D64_F32, D128_F32, D256_F32 = (C1.with_(name="d%d_f32" % d, n_q_heads=4, n_kv_heads=2, head_dim=d) for d in (64, 128, 256))
+
+
+@pytest.mark.parametrize("cfg,win_start,win_len,shift", [(D64_F32, 0, 64, 0), (D64_F32, 0, 65, 1), (D64_F32, 500, 30, 0), (D128_F32, 3, 50, 0),
+                                                         (D128_F32, 505, 40, 0), (D256_F32, 20, 44, 1), (D256_F32, 490, 40, 0)])
+def test_generic_attention_backward_forms(cfg, win_start, win_len, shift):
+    print(f"attention backward forms {cfg.name} [{win_start}, +{win_len}) shift={shift}", flush=True)
+    l = win_start + win_len
+    n_pages = -(-l // cfg.page_size)
+    g = gen.rng(13, "generic_bwd_forms", cfg.name, win_start, win_len)
+    pages = (g.permutation(n_pages + 3)[:n_pages] + 1).astype(np.int32)
+    rnd = lambda *s: g.standard_normal(s, dtype=np.float32)  # noqa: E731
+    K, V, q, do = rnd(l, cfg.kv_dim), rnd(l, cfg.kv_dim), rnd(win_len, cfg.q_dim), rnd(win_len, cfg.q_dim)
+    pos = np.arange(win_start, l)
+    f64 = lambda a: a.astype(np.float64)  # noqa: E731
+    o, lse = OO.attention(f64(q), pos, f64(K), f64(V), cfg.n_q_heads, cfg.n_kv_heads, cfg.head_dim)
+    dq_o, dk_o, dv_o = OO.attention_bwd(f64(q), pos, f64(K), f64(V), cfg.n_q_heads, cfg.n_kv_heads, cfg.head_dim, f64(do))
+    pool = HH.DevicePool(cfg, n_pages + 4)
+    pool.write_rows(pages, K, V)
+
+    def dev(a, off=0):                       # off elements past an aligned address
+        t = torch.zeros(a.size + off, device="cuda")
+        t[off:] = torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).flatten().cuda()
+        return t[off:].view(a.shape)
+    q_d, o_d, do_d, lse_d = dev(q, shift), dev(o), dev(do, shift), dev(lse)
+    dq, dk, dv = torch.empty_like(q_d), torch.ones(l, cfg.kv_dim, device="cuda"), torch.ones(l, cfg.kv_dim, device="cuda")
+    ws = torch.empty(win_len * cfg.n_q_heads * 4 + 64, dtype=torch.uint8, device="cuda")
+    B.flexco_attention_window_bwd(HH.c_cfg(cfg), pool.c, torch.from_numpy(pages).cuda(), n_pages, win_start, win_len, q_d, o_d, lse_d, do_d,
+                                  dq, dk, dv, ws, ws.numel())
+    torch.cuda.synchronize()
+    for name, got, ref in (("dq", to_np(dq), dq_o), ("dk", to_np(dk) - 1.0, dk_o), ("dv", to_np(dv) - 1.0, dv_o)):
+        assert_close(name, got, ref, TOL["f32"])
+
+
+@pytest.mark.parametrize("cfg", [D64_F32, D128_F32, ODD_F32, WIDE_BF16])
+def test_generic_attention_forward_short_runs(cfg):
+    print(f"attention forward short runs {cfg.name}", flush=True)
+    batch = gen.mixed_batch(cfg.page_size, 6, decode_ctx=(1, 2, 3, 15, 16, 17, 47, 48, 62, 63, 64, 65), prefill=[(0, 64, 64), (30, 35, 65)], finetune=[(1, 63, 64)])
+    for split in (0, 2):
+        out, a_o, lse, lse_o = attention_case(cfg, batch, split)
+        assert_close("attention out", out, a_o, TOL[cfg.dtype])
+        assert float(np.max(np.abs(lse - lse_o))) <= (1e-4 if cfg.dtype == "f32" else 2e-2)
