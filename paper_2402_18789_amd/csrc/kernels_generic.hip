@@ -1008,8 +1008,32 @@ __global__ __launch_bounds__(256) void copy_rows_kernel(const char* __restrict__
 // of a LoRA matrix, addressed as S[i * s_i + j * s_j], so that the same kernels serve
 // A [r, in] (s_i = 1, s_j = in) and B [out, r] (s_i = r, s_j = 1).
 // A launch takes a batch of products (the targets of one projection, u and t, dA and dB): they are small, and a launch
-// costs 4 - 6 us whatever it does (the fp32 configuration's co-served iteration: 51 -> 41 launches, 311 -> 255 us).
+// costs 4 - 6 us whatever it does (the fp32 configuration's co-served iteration: 51 -> 41 launches, 311 -> 255 us; 35 now).
 // --------------------------------------------------------------------------------------
+// acc[j] += sum over this thread's i of X[i] * S(i, j); low ranks: the loads of four passes at once (past the end they repeat
+// the last element, unused)
+template <typename T, int R>
+__device__ inline void lora_row_sums(float (&acc)[R], const T* __restrict__ X, const T* __restrict__ S, size_t s_i, size_t s_j, int n_long,
+                                     int r) {
+  constexpr int P = R <= 8 ? 4 : R <= 16 ? 2 : 1;
+  for (int i0 = threadIdx.x; i0 < n_long; i0 += 256 * P) {
+    float xv[P], sv[P][R];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+      const int i = min(i0 + 256 * p, n_long - 1);
+      xv[p] = ld(X + i);
+#pragma unroll
+      for (int j = 0; j < R; ++j) sv[p][j] = j < r ? ld(S + (size_t)i * s_i + (size_t)j * s_j) : 0.f;
+    }
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+      if (i0 + 256 * p < n_long) {
+#pragma unroll
+        for (int j = 0; j < R; ++j) acc[j] += xv[p] * sv[p][j];
+      }
+  }
+}
+
 // out[m, j] = sum_i X[m, i] * S(i, j)        one block per row m; R = rank bound
 template <typename T, int R>
 __global__ __launch_bounds__(256) void lora_reduce_long_kernel(LoraBatch b, int r, const int32_t* __restrict__ row_idx) {
@@ -1025,12 +1049,7 @@ __global__ __launch_bounds__(256) void lora_reduce_long_kernel(LoraBatch b, int 
   float acc[R];
 #pragma unroll
   for (int j = 0; j < R; ++j) acc[j] = 0.f;
-  for (int i = threadIdx.x; i < n_long; i += 256) {
-    const float xv = ld(X + m * ldx + i);
-#pragma unroll
-    for (int j = 0; j < R; ++j)
-      if (j < r) acc[j] += xv * ld(S + (size_t)i * s_i + (size_t)j * s_j);
-  }
+  lora_row_sums<T, R>(acc, X + m * ldx, S, s_i, s_j, n_long, r);
 #pragma unroll
   for (int j = 0; j < R; ++j) {
     const float v = wave_sum(acc[j]);
@@ -1040,37 +1059,57 @@ __global__ __launch_bounds__(256) void lora_reduce_long_kernel(LoraBatch b, int 
   if (threadIdx.x < r) out[mo * r + threadIdx.x] = red[0][threadIdx.x] + red[1][threadIdx.x] + red[2][threadIdx.x] + red[3][threadIdx.x];
 }
 
-// Y[m, i] += scale * sum_j U[m, j] * S(i, j)     grid (ceil(n_long/256), ceil(n/16), products), or, for products
-// that share their Y, one z block that adds them one after the other
+// Y[m, i] += scale * sum_j U[m, j] * S(i, j) for 16 rows from m0 on and 256 columns from i0 on; products z0 .. z1 - 1, which
+// share their Y, one after the other.  The rows' elements are asked for together.
 template <typename T, int R>
-__global__ __launch_bounds__(256) void lora_expand_kernel(LoraBatch b, int n, int r, float scale,
-                                                          const int32_t* __restrict__ row_idx) {
-  __shared__ float us[16][R];
-  const int m0 = blockIdx.y * 16;
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  const bool shared_y = gridDim.z == 1;
-  for (int z = blockIdx.z; z < (shared_y ? b.count : (int)blockIdx.z + 1); ++z) {
+__device__ inline void lora_expand_block(float (&us)[64][R], const LoraBatch& b, int z0, int z1, int i0, int m0, int n, int r, float scale,
+                                         const int32_t* __restrict__ row_idx) {
+  const int i = i0 + threadIdx.x;
+  const LoraProduct& y0 = b.p[z0];
+  T* yp[16];
+  float yv[16];
+#pragma unroll
+  for (int mm = 0; mm < 16; ++mm) {
+    const int row = min(m0 + mm, n - 1);
+    yp[mm] = (T*)y0.Y + (row_idx ? (size_t)row_idx[row] : (size_t)row) * y0.ldy + min(i, y0.n_long - 1);
+  }
+#pragma unroll
+  for (int mm = 0; mm < 16; ++mm) yv[mm] = ld(yp[mm]);
+  for (int z = z0; z < z1; ++z) {
     const LoraProduct& p = b.p[z];
     const T* __restrict__ S = (const T*)p.S;
+    float sv[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j) sv[j] = (j < r) ? ld(S + (size_t)min(i, p.n_long - 1) * p.s_i + (size_t)j * p.s_j) : 0.f;
     __syncthreads();
     for (int idx = threadIdx.x; idx < 16 * R; idx += 256) {
       const int mm = idx / R, j = idx % R;
       us[mm][j] = (m0 + mm < n && j < r) ? p.U[(size_t)(m0 + mm) * r + j] : 0.f;
     }
     __syncthreads();
-    if (i >= p.n_long) continue;
-    float sv[R];
 #pragma unroll
-    for (int j = 0; j < R; ++j) sv[j] = (j < r) ? ld(S + (size_t)i * p.s_i + (size_t)j * p.s_j) : 0.f;
-    for (int mm = 0; mm < 16 && m0 + mm < n; ++mm) {
+    for (int mm = 0; mm < 16; ++mm) {
       float a = 0.f;
 #pragma unroll
       for (int j = 0; j < R; ++j) a += us[mm][j] * sv[j];
-      const size_t yr = row_idx ? (size_t)row_idx[m0 + mm] : (size_t)(m0 + mm);
-      T* y = (T*)p.Y + yr * p.ldy + i;
-      st(y, ld(y) + scale * a);
+      yv[mm] = (float)(T)(yv[mm] + scale * a);        // (each product is rounded to the storage type by itself)
     }
   }
+  if (i < y0.n_long) {
+#pragma unroll
+    for (int mm = 0; mm < 16; ++mm)
+      if (m0 + mm < n) st(yp[mm], yv[mm]);
+  }
+}
+
+// grid (ceil(n_long/256), ceil(n/16), products), or, for products that share their Y, one z block that adds them one after the other
+template <typename T, int R>
+__global__ __launch_bounds__(256) void lora_expand_kernel(LoraBatch b, int n, int r, float scale,
+                                                          const int32_t* __restrict__ row_idx) {
+  __shared__ float us[64][R];
+  const bool shared_y = gridDim.z == 1;
+  lora_expand_block<T, R>(us, b, blockIdx.z, shared_y ? b.count : (int)blockIdx.z + 1, blockIdx.x * 256, blockIdx.y * 16, n, r, scale,
+                          row_idx);
 }
 
 // Both of a few rows in one launch: u = x A^T, then y += scale u B^T, a block per row and product (down.p[z]: x, A, u;
@@ -1087,12 +1126,7 @@ __global__ __launch_bounds__(256) void lora_rows_kernel(LoraBatch down, LoraBatc
   float acc[R];
 #pragma unroll
   for (int j = 0; j < R; ++j) acc[j] = 0.f;
-  for (int i = threadIdx.x; i < p.n_long; i += 256) {
-    const float xv = ld(X + i);
-#pragma unroll
-    for (int j = 0; j < R; ++j)
-      if (j < r) acc[j] += xv * ld(S + (size_t)i * p.s_i + (size_t)j * p.s_j);
-  }
+  lora_row_sums<T, R>(acc, X, S, p.s_i, p.s_j, p.n_long, r);
 #pragma unroll
   for (int j = 0; j < R; ++j) {
     const float v = wave_sum(acc[j]);
@@ -1119,15 +1153,12 @@ __global__ __launch_bounds__(256) void lora_rows_kernel(LoraBatch down, LoraBatc
 
 // G(i, j) += scale * sum_m X[m, i] * U[m, j]      one thread per long index i, all ranks j
 template <typename T, int R>
-__global__ __launch_bounds__(256) void lora_outer_kernel(LoraBatch b, int n, int r, float scale) {
-  __shared__ float us[64][R];
-  const LoraProduct& p = b.p[blockIdx.y];
+__device__ inline void lora_outer_block(float (&us)[64][R], const LoraProduct& p, int i, int n, int r, float scale) {
   const T* __restrict__ X = (const T*)p.X;
   const float* __restrict__ U = p.U;
   float* __restrict__ G = p.G;
   const size_t ldx = p.ldx, g_i = p.g_i, g_j = p.g_j;
-  const int n_long = p.n_long;
-  const int i = blockIdx.x * 256 + threadIdx.x;
+  const int ic = min(i, p.n_long - 1);
   float acc[R];
 #pragma unroll
   for (int j = 0; j < R; ++j) acc[j] = 0.f;
@@ -1138,19 +1169,34 @@ __global__ __launch_bounds__(256) void lora_outer_kernel(LoraBatch b, int n, int
       us[mm][j] = (m0 + mm < n && j < r) ? U[(size_t)(m0 + mm) * r + j] : 0.f;
     }
     __syncthreads();
-    if (i < n_long) {
-      const int mend = min(64, n - m0);
-      for (int mm = 0; mm < mend; ++mm) {
-        const float xv = ld(X + (size_t)(m0 + mm) * ldx + i);
+    const int mend = min(64, n - m0);
+#pragma unroll 16
+    for (int mm = 0; mm < mend; ++mm) {
+      const float xv = ld(X + (size_t)(m0 + mm) * ldx + ic);
 #pragma unroll
-        for (int j = 0; j < R; ++j) acc[j] += xv * us[mm][j];
-      }
+      for (int j = 0; j < R; ++j) acc[j] += xv * us[mm][j];
     }
   }
-  if (i < n_long) {
+  if (i < p.n_long) {        // all loads of the accumulated gradient first (one round trip, not R in a row)
+    float gv[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j) gv[j] = j < r ? G[(size_t)i * g_i + (size_t)j * g_j] : 0.f;
 #pragma unroll
     for (int j = 0; j < R; ++j)
-      if (j < r) G[(size_t)i * g_i + (size_t)j * g_j] += scale * acc[j];
+      if (j < r) G[(size_t)i * g_i + (size_t)j * g_j] = gv[j] + scale * acc[j];
+  }
+}
+
+// The outer products of a backward window (z = blockIdx.y) and, behind them, dx += scale sum_z t_z A_z by blocks of 16 rows: they
+// read the same t and write nothing the other reads.
+template <typename T, int R>
+__global__ __launch_bounds__(256) void lora_outer_kernel(LoraBatch b, LoraBatch back, int n, int r, float scale) {
+  __shared__ float us[64][R];
+  if ((int)blockIdx.y < b.count) {
+    const LoraProduct& p = b.p[blockIdx.y];
+    if ((int)blockIdx.x * 256 < p.n_long) lora_outer_block<T, R>(us, p, blockIdx.x * 256 + threadIdx.x, n, r, scale);
+  } else if ((int)blockIdx.x * 256 < back.p[0].n_long) {
+    lora_expand_block<T, R>(us, back, 0, back.count, blockIdx.x * 256, (blockIdx.y - b.count) * 16, n, r, scale, nullptr);
   }
 }
 
@@ -1476,9 +1522,10 @@ int32_t launch_copy_rows(const void* src, size_t ld_src_bytes, void* dst, size_t
 
 template <int R>
 static int32_t lora_ops(int op, const LoraBatch& b, bool shared_y, int n, int r, float scale, int dtype, const int32_t* row_idx,
-                        hipStream_t s) {
+                        hipStream_t s, const LoraBatch& back) {
   int wide = 0;
   for (int z = 0; z < b.count; ++z) wide = std::max(wide, (b.p[z].n_long + 255) / 256);
+  for (int z = 0; z < back.count; ++z) wide = std::max(wide, (back.p[z].n_long + 255) / 256);
   DISPATCH_T(dtype, {
     if (op == 0)
       hipLaunchKernelGGL((lora_reduce_long_kernel<T, R>), dim3(n, b.count), dim3(256), 0, s, b, r, row_idx);
@@ -1486,7 +1533,8 @@ static int32_t lora_ops(int op, const LoraBatch& b, bool shared_y, int n, int r,
       hipLaunchKernelGGL((lora_expand_kernel<T, R>), dim3(wide, (n + 15) / 16, shared_y ? 1 : b.count), dim3(256), 0, s, b, n, r,
                          scale, row_idx);
     else
-      hipLaunchKernelGGL((lora_outer_kernel<T, R>), dim3(wide, b.count), dim3(256), 0, s, b, n, r, scale);
+      hipLaunchKernelGGL((lora_outer_kernel<T, R>), dim3(wide, b.count + (back.count ? (n + 15) / 16 : 0)), dim3(256), 0, s, b, back, n, r,
+                         scale);
   });
   return post_launch("lora kernel");
 }
@@ -1516,12 +1564,14 @@ static int32_t lora_rows(const LoraBatch& down, const LoraBatch& up, int n, int 
 }
 
 static int32_t lora_dispatch(int op, const LoraBatch& b, bool shared_y, int n, int r, float scale, int dtype, hipStream_t s,
-                             const int32_t* row_idx = nullptr) {
+                             const int32_t* row_idx = nullptr, const LoraBatch* back_in = nullptr) {
   if (n == 0 || b.count == 0) return FLEXCO_OK;
-  if (r <= 8) return lora_ops<8>(op, b, shared_y, n, r, scale, dtype, row_idx, s);
-  if (r <= 16) return lora_ops<16>(op, b, shared_y, n, r, scale, dtype, row_idx, s);
-  if (r <= 32) return lora_ops<32>(op, b, shared_y, n, r, scale, dtype, row_idx, s);
-  return lora_ops<64>(op, b, shared_y, n, r, scale, dtype, row_idx, s);
+  LoraBatch back = {};
+  if (back_in) back = *back_in;
+  if (r <= 8) return lora_ops<8>(op, b, shared_y, n, r, scale, dtype, row_idx, s, back);
+  if (r <= 16) return lora_ops<16>(op, b, shared_y, n, r, scale, dtype, row_idx, s, back);
+  if (r <= 32) return lora_ops<32>(op, b, shared_y, n, r, scale, dtype, row_idx, s, back);
+  return lora_ops<64>(op, b, shared_y, n, r, scale, dtype, row_idx, s, back);
 }
 
 // u <- relu(u); where u <= 0 the matching element of t (if given) is zeroed: the ReLU's backward mask
@@ -1593,11 +1643,13 @@ int32_t launch_lora_bwd(const LoraTarget* tg, int count, void* dx, size_t lddx, 
   int32_t rc;
   // (u, t and dx of a row in one launch, as the forward pass does: no faster at width 256, rank 8, and everywhere else
   // slower, a window of 64 rows at the 8B shape, rank 8, 895 us against 549.  The outer products read dy and x, which may be dx
-  // itself - the adapter's in-place call.)
+  // itself - the adapter's in-place call: only where dx is neither do they share a launch with it, 15 -> 6.7 us for the fp32
+  // configuration's down projection.)
   if ((rc = lora_dispatch(0, long_sums, false, n, r, 0.f, dtype, s))) return rc;
   if (relu && (rc = launch_relu_mask(tg[0].u, tg[0].t, (size_t)n * r, s))) return rc;
-  if ((rc = lora_dispatch(2, outer, false, n, r, scale, dtype, s))) return rc;
-  return dx ? lora_dispatch(1, back, true, n, r, scale, dtype, s) : FLEXCO_OK;
+  const bool with_dx = dx && !relu && (n + 15) / 16 < 60000;
+  if ((rc = lora_dispatch(2, outer, false, n, r, scale, dtype, s, nullptr, with_dx ? &back : nullptr))) return rc;
+  return dx && !with_dx ? lora_dispatch(1, back, true, n, r, scale, dtype, s) : FLEXCO_OK;
 }
 
 }  // namespace flexco
