@@ -84,13 +84,13 @@ __device__ inline bf16x8 tr_pair(const bf16_t* a, const bf16_t* b) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// kernel A: dQ.  grid (ceil(s / 32), nq), SP = 8 (or 4) wavefronts.  Wavefront w: rows [32 b + 16 (w % 2), + 16), and
-// of the SP pages a step stages, pages 2 (w / 2) and 2 (w / 2) + 1; the SP / 2 key groups are added
+// kernel A: dQ.  grid (ceil(s / (32 NR)), nq), SP = 8 (or 4) wavefronts.  Wavefront w: NR row tiles of 16 from row
+// 32 NR b + 16 NR (w % 2) on, and of the SP pages a step stages, pages 2 (w / 2) and 2 (w / 2) + 1; the SP / 2 key groups are added
 // in a fixed order at the end.  (The grid has one block per CU or fewer and a step is a chain of
 // dependent LDS reads and MFMAs: eight wavefronts halve the number of steps.)
 // ---------------------------------------------------------------------------------------------
-template <int SP>                                                // pages a step stages, one per wavefront
-__global__ __launch_bounds__(64 * SP) void attn_bwd_dq_mfma_kernel(BwdArgs a) {
+template <int SP, int NR>     // pages a step stages, one per wavefront; row tiles of a wavefront
+__global__ __launch_bounds__(64 * SP, SP == 4 ? 2 : 1) void attn_bwd_dq_mfma_kernel(BwdArgs a) {
   __shared__ __attribute__((aligned(1024))) bf16_t kb0[SP * TILE16];
   __shared__ __attribute__((aligned(1024))) bf16_t kb1[SP * TILE16];
   __shared__ __attribute__((aligned(1024))) bf16_t vb0[SP * VPAGE];
@@ -106,47 +106,50 @@ __global__ __launch_bounds__(64 * SP) void attn_bwd_dq_mfma_kernel(BwdArgs a) {
   const int lid = blockIdx.y * gridDim.x + blockIdx.x;
   const int kvh = lid % a.nkv;
   const int h = kvh * group + (lid / a.nkv) % group;
-  const int bx = lid / a.nq;                                     // row block
-  const int i0 = bx * 32 + rt * 16;
-  const int row_c = i0 + c;
-  const bool row_ok = row_c < a.s;
-  const int rcl = row_ok ? row_c : a.s - 1;
-  const int pos_c = row_ok ? a.w0 + row_c : -1;
-  const int wave_last_pos = a.w0 + min(i0 + 15, a.s - 1);      // may be < first key if the tile is empty
-  const int blk_last_row = min(bx * 32 + 31, a.s - 1);
+  const int bx = gridDim.x - 1 - lid / a.nq;                     // row block, the ones that see the most keys first
+  const int i0 = bx * 32 * NR + rt * 16 * NR;                    // the wavefront's rows: NR tiles of 16
+  const int wave_last_pos = a.w0 + min(i0 + 16 * NR - 1, a.s - 1);   // may be < first key if the tiles are empty
+  const int blk_last_row = min(bx * 32 * NR + 32 * NR - 1, a.s - 1);
   const int np = (a.w0 + blk_last_row) / PS + 1;                 // pages visible to the block
   const int nit = (np + SP - 1) / SP;
   const int last_page = (a.l - 1) / PS, last_key = (a.l - 1) % PS;
 
-  bf16x8 qf[4], dof[4];
-  {
+  bf16x8 qf[NR][4], dof[NR][4];
+  int pos_c[NR];
+  float lse2[NR], delta[NR];
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
+    const int row_c = i0 + 16 * r + c;
+    const bool row_ok = row_c < a.s;
+    const int rcl = row_ok ? row_c : a.s - 1;
+    pos_c[r] = row_ok ? a.w0 + row_c : -1;
     const bf16_t* qr = a.q + ((size_t)rcl * a.nq + h) * D + g * 8;
     const bf16_t* dr = a.dout + ((size_t)rcl * a.nq + h) * D + g * 8;
 #pragma unroll
     for (int dc = 0; dc < 4; ++dc) {
-      qf[dc] = *reinterpret_cast<const bf16x8*>(qr + dc * 32);
-      dof[dc] = *reinterpret_cast<const bf16x8*>(dr + dc * 32);
+      qf[r][dc] = *reinterpret_cast<const bf16x8*>(qr + dc * 32);
+      dof[r][dc] = *reinterpret_cast<const bf16x8*>(dr + dc * 32);
     }
-  }
-  const float lse2 = a.lse[(size_t)rcl * a.nq + h] * LOG2E;
-  // delta_i = sum_d dO_id O_id of the wavefront's rows: the four lanes of a row hold 32 of its 128 d each
-  float delta = 0.f;
-  {
+    lse2[r] = a.lse[(size_t)rcl * a.nq + h] * LOG2E;
+    // delta_i = sum_d dO_id O_id of the wavefront's rows: the four lanes of a row hold 32 of its 128 d each
     const bf16_t* orow = a.out + ((size_t)rcl * a.nq + h) * D + g * 8;
+    delta[r] = 0.f;
 #pragma unroll
     for (int dc = 0; dc < 4; ++dc) {
       const bf16x8 of = *reinterpret_cast<const bf16x8*>(orow + dc * 32);
 #pragma unroll
-      for (int q = 0; q < 8; ++q) delta += (float)dof[dc][q] * (float)of[q];
+      for (int q = 0; q < 8; ++q) delta[r] += (float)dof[r][dc][q] * (float)of[q];
     }
-    delta = sum_xor16(delta);
-    delta = sum_xor32(delta);
-    if (kh == 0 && g == 0 && row_ok) a.delta[(size_t)row_c * a.nq + h] = delta;   // for kernel B
+    delta[r] = sum_xor16(delta[r]);
+    delta[r] = sum_xor32(delta[r]);
+    if (kh == 0 && g == 0 && row_ok) a.delta[(size_t)row_c * a.nq + h] = delta[r];   // for kernel B
   }
 
-  f32x4 dq[8];
+  f32x4 dq[NR][8];
 #pragma unroll
-  for (int mt = 0; mt < 8; ++mt) dq[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int r = 0; r < NR; ++r)
+#pragma unroll
+    for (int mt = 0; mt < 8; ++mt) dq[r][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   // ---- loads: wavefront w brings in page slot w of a step, K rows and V ---------------------
   // K: instruction q fills rows 4 q .. + 4 of the slot; lane -> row 4 q + lane / 16, physical chunk
@@ -196,34 +199,37 @@ __global__ __launch_bounds__(64 * SP) void attn_bwd_dq_mfma_kernel(BwdArgs a) {
   // prefix): no comparisons, no per-element branches
 #define FLEXCO_DQ_COMPUTE(kb_, vb_, it_, MASKED_)                                                     \
   if (!(MASKED_) || (SP * (it_) + 2 * kh) * PS <= wave_last_pos) { /* else: nothing visible to these rows (uniform) */ \
-    float ds[8];                                                                                      \
+    bf16x8 dsf[NR];                                                                                   \
     _Pragma("unroll") for (int xx = 0; xx < 2; ++xx) {                                                \
       const bf16_t* kt_ = kb_ + (2 * kh + xx) * TILE16;                                               \
       const bf16_t* vt_ = vb_ + (2 * kh + xx) * VPAGE;                                                \
-      f32x4 sacc = {0.f, 0.f, 0.f, 0.f}, pacc = {0.f, 0.f, 0.f, 0.f};                                 \
+      f32x4 sacc[NR], pacc[NR];                                                                       \
+      _Pragma("unroll") for (int r = 0; r < NR; ++r) sacc[r] = pacc[r] = f32x4{0.f, 0.f, 0.f, 0.f};   \
       _Pragma("unroll") for (int dc = 0; dc < 4; ++dc) {                                              \
         const bf16x8 kf = *reinterpret_cast<const bf16x8*>(kt_ + krow_off + (((dc * 4 + g) ^ krow_sw) * 8)); \
-        sacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[dc], sacc, 0, 0, 0);                    \
         /* rows d + 4: 8 logical chunks on = bit 3 of the chunk index = bit 6 of the element offset */ \
         const bf16x8 vf = tr_pair(vt_ + dc * 512 + v_base, vt_ + dc * 512 + (v_base ^ 64));           \
-        pacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, dof[dc], pacc, 0, 0, 0);                   \
+        _Pragma("unroll") for (int r = 0; r < NR; ++r) {                                              \
+          sacc[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[r][dc], sacc[r], 0, 0, 0);         \
+          pacc[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, dof[r][dc], pacc[r], 0, 0, 0);        \
+        }                                                                                             \
       }                                                                                               \
-      _Pragma("unroll") for (int j = 0; j < 4; ++j) {                                                 \
-        const int kpos = (SP * (it_) + 2 * kh + xx) * PS + 4 * g + j;                                 \
-        const bool ok = !(MASKED_) || kpos <= pos_c;                                                  \
-        /* (the mask goes into the exponent: 2^-inf = 0 without a branch around the exponential) */   \
-        const float e_ = sacc[j] * a.scale_log2 - lse2;                                               \
-        const float p = __builtin_amdgcn_exp2f(ok ? e_ : -INFINITY);                                  \
-        ds[xx * 4 + j] = p * (pacc[j] - delta);                                                       \
-      }                                                                                               \
+      _Pragma("unroll") for (int r = 0; r < NR; ++r)                                                  \
+        _Pragma("unroll") for (int j = 0; j < 4; ++j) {                                               \
+          const int kpos = (SP * (it_) + 2 * kh + xx) * PS + 4 * g + j;                               \
+          const bool ok = !(MASKED_) || kpos <= pos_c[r];                                             \
+          /* (the mask goes into the exponent: 2^-inf = 0 without a branch around the exponential) */ \
+          const float e_ = sacc[r][j] * a.scale_log2 - lse2[r];                                       \
+          const float p = __builtin_amdgcn_exp2f(ok ? e_ : -INFINITY);                                \
+          dsf[r][xx * 4 + j] = (bf16_t)(p * (pacc[r][j] - delta[r]));                                 \
+        }                                                                                             \
     }                                                                                                 \
-    bf16x8 dsf;                                                                                       \
-    _Pragma("unroll") for (int j = 0; j < 8; ++j) dsf[j] = (bf16_t)ds[j];                             \
     /* dQ^T[d, row] += K^T[d, keys] dS^T[keys, row]; lane (d, g): keys 4g..4g+3 of both pages */       \
     _Pragma("unroll") for (int mt = 0; mt < 8; ++mt) {                                                \
       const int off_ = kt_base + (((mt * 2 + kt_hi) ^ kt_sw) * 8);                                    \
       const bf16x8 kt = tr_pair(kb_ + (2 * kh) * TILE16 + off_, kb_ + (2 * kh + 1) * TILE16 + off_);  \
-      dq[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kt, dsf, dq[mt], 0, 0, 0);                     \
+      _Pragma("unroll") for (int r = 0; r < NR; ++r)                                                  \
+        dq[r][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kt, dsf[r], dq[r][mt], 0, 0, 0);          \
     }                                                                                                 \
   }
 
@@ -260,33 +266,44 @@ __global__ __launch_bounds__(64 * SP) void attn_bwd_dq_mfma_kernel(BwdArgs a) {
   }
   if (it < nit) FLEXCO_DQ_STEP(kb0, vb0, kb1, vb1, it, true)
 
-  // ---- add the four key quarters (kh = 0, 1, 2, 3 in this order), scale, store -------------------
-  float* red = reinterpret_cast<float*>(kb0);                    // [2 rt][32][64 lanes] floats = 16 KB
+  // ---- add the SP / 2 key groups (kh = 0, 1, .. in this order), scale, store ---------------------------------
 #pragma unroll 1
   for (int src = 1; src < SP / 2; ++src) {
     __syncthreads();
-    if (kh == src) {
 #pragma unroll
-      for (int mt = 0; mt < 8; ++mt)
+    for (int r = 0; r < NR; ++r) {
+      float* red = reinterpret_cast<float*>(r == 0 ? kb0 : kb1);  // [2 rt][32][64 lanes] floats = 16 KB each
+      if (kh == src) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) red[((rt * 8 + mt) * 4 + j) * 64 + lane] = dq[mt][j];
+        for (int mt = 0; mt < 8; ++mt)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) red[((rt * 8 + mt) * 4 + j) * 64 + lane] = dq[r][mt][j];
+      }
     }
     __syncthreads();
     if (kh == 0) {
 #pragma unroll
-      for (int mt = 0; mt < 8; ++mt)
+      for (int r = 0; r < NR; ++r) {
+        const float* red = reinterpret_cast<const float*>(r == 0 ? kb0 : kb1);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) dq[mt][j] += red[((rt * 8 + mt) * 4 + j) * 64 + lane];
+        for (int mt = 0; mt < 8; ++mt)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) dq[r][mt][j] += red[((rt * 8 + mt) * 4 + j) * 64 + lane];
+      }
     }
   }
-  if (kh == 0 && row_ok) {
-    bf16_t* out = a.dq + ((size_t)row_c * a.nq + h) * D + 4 * g;
+  if (kh == 0) {
 #pragma unroll
-    for (int mt = 0; mt < 8; ++mt) {
-      bf16x4 v;
+    for (int r = 0; r < NR; ++r) {
+      if (i0 + 16 * r + c >= a.s) continue;
+      bf16_t* out = a.dq + ((size_t)(i0 + 16 * r + c) * a.nq + h) * D + 4 * g;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) v[j] = (bf16_t)(dq[mt][j] * a.scale);
-      *reinterpret_cast<bf16x4*>(out + mt * 16) = v;
+      for (int mt = 0; mt < 8; ++mt) {
+        bf16x4 v;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = (bf16_t)(dq[r][mt][j] * a.scale);
+        *reinterpret_cast<bf16x4*>(out + mt * 16) = v;
+      }
     }
   }
 }
@@ -296,18 +313,24 @@ __global__ __launch_bounds__(64 * SP) void attn_bwd_dq_mfma_kernel(BwdArgs a) {
 // 4 b + w % 4 and walks over the window's rows, 32 rows per step, for every second query head of the
 // kv group (w / 4 = 0: heads 0, 2, ..; 1: heads 1, 3, ..): the two halves of a block multiply different
 // heads at the same time and their sums are added in a fixed order at the end.  NH = 1: four wavefronts
-// that walk every head of the group, nothing to add at the end.  (The grid has one
+// that walk every head of the group, nothing to add at the end, two steps from one barrier to the next.  (The grid has one
 // block per CU or fewer, and a step is a chain of dependent LDS reads and MFMAs: the second half's
 // chains fill the first half's waits.)
+// What bounds both kernels: no one pipe - matrix pipes, vector ALU and LDS each busy 35 - 40 % of the time on the 1024-row window of
+// the 14B shape - but the waits between them with two wavefronts per SIMD.  What moved it (both kernels there, 391 us before;
+// 0.49 -> 0.56 PFLOP/s of the definition's five products): two row tiles per wavefront in kernel A 369, steps without masks in a
+// loop of their own in kernel B 357, two steps per barrier 352, its LDS reads ahead of the products 339.  Three buffer sets and the
+// next step's fragments read behind this step's products spilled (21 - 74 registers): 359 - 495.
 // ---------------------------------------------------------------------------------------------
 template <int NH>   // head halves that work side by side: 2 (eight wavefronts) or 1 (four)
 __global__ __launch_bounds__(256 * NH, NH == 1 ? 2 : 1) void attn_bwd_dkv_mfma_kernel(BwdArgs a) {
-  __shared__ __attribute__((aligned(1024))) bf16_t qb0[NH][2 * TILE16];
-  __shared__ __attribute__((aligned(1024))) bf16_t qb1[NH][2 * TILE16];
-  __shared__ __attribute__((aligned(1024))) bf16_t ob0[NH][2 * TILE16];
-  __shared__ __attribute__((aligned(1024))) bf16_t ob1[NH][2 * TILE16];
-  __shared__ __attribute__((aligned(256))) float ld0[NH][64];   // lse[32] | delta[32] of the step's rows
-  __shared__ __attribute__((aligned(256))) float ld1[NH][64];
+  constexpr int SUB = NH == 1 ? 2 : 1;       // steps between two barriers
+  __shared__ __attribute__((aligned(1024))) bf16_t qb0[NH * SUB][2 * TILE16];
+  __shared__ __attribute__((aligned(1024))) bf16_t qb1[NH * SUB][2 * TILE16];
+  __shared__ __attribute__((aligned(1024))) bf16_t ob0[NH * SUB][2 * TILE16];
+  __shared__ __attribute__((aligned(1024))) bf16_t ob1[NH * SUB][2 * TILE16];
+  __shared__ __attribute__((aligned(256))) float ld0[NH * SUB][64];   // lse[32] | delta[32] of the step's rows
+  __shared__ __attribute__((aligned(256))) float ld1[NH * SUB][64];
   __shared__ float red[NH == 2 ? 4 : 1][NH == 2 ? 8 * 4 * 64 : 1];   // sums of the second half, one output at a time
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wavefront-uniform: LDS bases of the loads stay scalar
@@ -343,30 +366,53 @@ __global__ __launch_bounds__(256 * NH, NH == 1 ? 2 : 1) void attn_bwd_dkv_mfma_k
 #pragma unroll
   for (int mt = 0; mt < 8; ++mt) { dk[mt] = f32x4{0.f, 0.f, 0.f, 0.f}; dv[mt] = f32x4{0.f, 0.f, 0.f, 0.f}; }
 
+  // Steps: one per (row block of 32, head NH hh + hg).  First those in which every element counts - rows of the window
+  // at or past the block's last key, a head for every half - in a loop without masks; then the others.
   const int blk_key0 = bx * 64;
   const int first_row = max(0, blk_key0 - a.w0) & ~31;       // first window row that sees the block's keys
-  const int nrb = (a.s - first_row + 31) / 32;               // row blocks per head
-  const int nit = ((group + NH - 1) / NH) * nrb;             // steps: heads NH (it / nrb) + hg
+  const int nrb = (a.s - first_row + 31) / 32;               // row blocks
+  const int heads = group / NH, heads_all = (group + NH - 1) / NH;
+  const bool keys_full = blk_key0 + 64 <= a.l;
+  // visible row blocks [rv0, rv1): rows from the block's last key on, whole blocks
+  const int rv0 = min(max(0, (blk_key0 + 63 - a.w0 - first_row + 31) / 32), nrb);
+  const int rv1 = keys_full ? max(rv0, (a.s - first_row) / 32) : rv0;
+  const int n_vis = ((rv1 - rv0) * heads) & ~(2 * SUB - 1);  // (whole passes over the two buffer sets)
+  const int nit = nrb * heads_all;
+  int rb = rv0, hh = 0;                                      // of the next step to load
+  bool vis = (rv1 - rv0) * heads > 0;
+  auto settle = [&]() {                                      // (of the visible row blocks only an odd last head is left)
+    if (!vis && rb >= rv0 && rb < rv1) {
+      if (heads_all > heads) hh = heads;
+      else { rb = rv1; hh = 0; }
+    }
+  };
+  auto advance = [&]() {
+    if (++hh < (vis ? heads : heads_all)) return;
+    hh = 0;
+    if (++rb == rv1 && vis) { vis = false; rb = 0; }
+    settle();
+  };
+  if (!vis) { rb = 0; settle(); }
 
   // ---- loads: 8 instructions per 32-row tile (4 rows each); wavefront (pw, hg) issues 2 pw, 2 pw + 1
   // of its half's Q tile and dO tile; wavefront pw = 0 also brings in the rows' lse (lanes 0..31) and
   // delta (lanes 32..63), 4 bytes per lane.  Rows past the window repeat its last row, a head past the
   // group repeats the group's last head (both masked later).
   const int t_rin = lane >> 4, t_pc = lane & 15;
-#define FLEXCO_ISSUE_QO(qb_, ob_, ld_, it_)                                                           \
+#define FLEXCO_ISSUE_QO(qb_, ob_, ld_, u_)                                                            \
   {                                                                                                   \
-    const int h_ = kvh * group + min(NH * ((it_) / nrb) + hg, group - 1);                              \
-    const int r0_ = first_row + 32 * ((it_) % nrb);                                                   \
+    const int h_ = kvh * group + min(NH * hh + hg, group - 1);                                        \
+    const int r0_ = first_row + 32 * rb;                                                              \
     _Pragma("unroll") for (int e = 0; e < 2; ++e) {                                                   \
       const int row_ = 4 * (2 * pw + e) + t_rin;                                                      \
       const size_t src_ = ((size_t)min(r0_ + row_, a.s - 1) * a.nq + h_) * D + ((t_pc ^ rsw(row_)) * 8); \
-      __builtin_amdgcn_global_load_lds(FLEXCO_GP(a.q + src_), FLEXCO_LP(qb_[hg] + (2 * pw + e) * 4 * D), 16, 0, 0); \
-      __builtin_amdgcn_global_load_lds(FLEXCO_GP(a.dout + src_), FLEXCO_LP(ob_[hg] + (2 * pw + e) * 4 * D), 16, 0, 0); \
+      __builtin_amdgcn_global_load_lds(FLEXCO_GP(a.q + src_), FLEXCO_LP(qb_[hg * SUB + (u_)] + (2 * pw + e) * 4 * D), 16, 0, 0); \
+      __builtin_amdgcn_global_load_lds(FLEXCO_GP(a.dout + src_), FLEXCO_LP(ob_[hg * SUB + (u_)] + (2 * pw + e) * 4 * D), 16, 0, 0); \
     }                                                                                                 \
     if (pw == 0) {                                                                                    \
       const size_t idx_ = (size_t)min(r0_ + (lane & 31), a.s - 1) * a.nq + h_;                        \
       const float* src_ = (lane < 32 ? a.lse : a.delta) + idx_;                                       \
-      __builtin_amdgcn_global_load_lds(FLEXCO_GP(src_), FLEXCO_LP(ld_[hg]), 4, 0, 0);                 \
+      __builtin_amdgcn_global_load_lds(FLEXCO_GP(src_), FLEXCO_LP(ld_[hg * SUB + (u_)]), 4, 0, 0);                 \
     }                                                                                                 \
   }
 
@@ -376,67 +422,105 @@ __global__ __launch_bounds__(256 * NH, NH == 1 ? 2 : 1) void attn_bwd_dkv_mfma_k
   const int tr_base = tr_row * D + (sc & 1) * 4;
   const int tr_sw = rsw(tr_row), tr_hi = sc >> 1;
 
-  // (an unmasked form of the step for row blocks wholly after the page, chosen per step, cost more in register copies
-  // where the two forms join than the masks do: 200 moves per step; the dQ kernel's steps split into two loops instead)
-#define FLEXCO_DKV_COMPUTE(qb_, ob_, ld_, it_)                                                        \
+  // The order is written down (sched_barrier): left to itself the compiler read the transposed operands of two products right
+  // in front of them, i.e. each pair waited out the LDS.  TRD pairs' operands are on their way or in registers.
+  constexpr int TRD = 3;
+#define FLEXCO_DKV_TR(qt_, ot_, mt_)                                                                  \
   {                                                                                                   \
-    const int r0 = first_row + 32 * ((it_) % nrb);                                                    \
-    const bool head_ok = NH * ((it_) / nrb) + hg < group;                                             \
+    const int off_ = tr_base + ((((mt_) * 2 + tr_hi) ^ tr_sw) * 8);                                   \
+    ot[(mt_) % TRD] = tr_pair(ot_ + off_, ot_ + TILE16 + off_);                                       \
+    qt[(mt_) % TRD] = tr_pair(qt_ + off_, qt_ + TILE16 + off_);                                       \
+  }
+#define FLEXCO_DKV_COMPUTE(qb_, ob_, ld_, u_, r0, head_ok, MASKED_)                                   \
+  {                                                                                                   \
     /* (a step with nothing to add - a head past the group, a page past the sequence, rows before the page - is not */ \
     /* skipped: its elements are all masked and add zeros; a branch around the products cost a copy of all 64      */ \
     /* accumulator registers every second step)                                                                   */ \
     {                                                                                                 \
-      const bf16_t* qt_ = qb_[hg];                                                                    \
-      const bf16_t* ot_ = ob_[hg];                                                                    \
-      const float* lt_ = ld_[hg];                                                                     \
-      float p[8], ds[8];                                                                              \
-      _Pragma("unroll") for (int x = 0; x < 2; ++x) {                                                 \
-        f32x4 sacc = {0.f, 0.f, 0.f, 0.f}, pacc = {0.f, 0.f, 0.f, 0.f};                               \
+      const bf16_t* qt_ = qb_[hg * SUB + (u_)];                                                                    \
+      const bf16_t* ot_ = ob_[hg * SUB + (u_)];                                                                    \
+      const float* lt_ = ld_[hg * SUB + (u_)];                                                                     \
+      bf16x8 qa[2][4], oa[2][4], ot[TRD], qt[TRD];                                                    \
+      f32x4 sacc[2], pacc[2];                                                                         \
+      bf16x8 pf, dsf;                                                                                 \
+      _Pragma("unroll") for (int x = 0; x < 2; ++x)                                                   \
         _Pragma("unroll") for (int dc = 0; dc < 4; ++dc) {                                            \
           const int off_ = x * TILE16 + row_off + (((dc * 4 + g) ^ row_sw) * 8);                      \
-          const bf16x8 qa = *reinterpret_cast<const bf16x8*>(qt_ + off_);                             \
-          const bf16x8 oa = *reinterpret_cast<const bf16x8*>(ot_ + off_);                             \
-          sacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa, kf[dc], sacc, 0, 0, 0);   /* S[row, key] */  \
-          pacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(oa, vf[dc], pacc, 0, 0, 0);   /* dP[row, key] */ \
+          qa[x][dc] = *reinterpret_cast<const bf16x8*>(qt_ + off_);                                   \
+          oa[x][dc] = *reinterpret_cast<const bf16x8*>(ot_ + off_);                                   \
         }                                                                                             \
+      __builtin_amdgcn_sched_barrier(0);                                                              \
+      _Pragma("unroll") for (int x = 0; x < 2; ++x) {                                                 \
+        sacc[x] = pacc[x] = f32x4{0.f, 0.f, 0.f, 0.f};                                                \
+        _Pragma("unroll") for (int dc = 0; dc < 4; ++dc) {                                            \
+          sacc[x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa[x][dc], kf[dc], sacc[x], 0, 0, 0);   /* S[row, key] */  \
+          pacc[x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(oa[x][dc], vf[dc], pacc[x], 0, 0, 0);   /* dP[row, key] */ \
+        }                                                                                             \
+        __builtin_amdgcn_sched_barrier(0);                                                            \
+        if (x == 0) {                                                                                 \
+          _Pragma("unroll") for (int mt = 0; mt < TRD - 1; ++mt) FLEXCO_DKV_TR(qt_, ot_, mt)          \
+          __builtin_amdgcn_sched_barrier(0);                                                          \
+        }                                                                                             \
+      }                                                                                               \
+      _Pragma("unroll") for (int x = 0; x < 2; ++x)                                                   \
         _Pragma("unroll") for (int j = 0; j < 4; ++j) {                                               \
           const int rl = x * 16 + 4 * g + j;            /* lane (key c, g) holds rows 4g..4g+3 of tile x */ \
           const int row = r0 + rl;                                                                    \
-          const bool ok = head_ok && key_ok && row < a.s && kpos <= a.w0 + row;                       \
+          const bool ok = !(MASKED_) || (head_ok && key_ok && row < a.s && kpos <= a.w0 + row);       \
           /* (the mask goes into the exponent: 2^-inf = 0 without a branch around the exponential) */ \
-          const float e_ = sacc[j] * a.scale_log2 - lt_[rl] * LOG2E;   /* (read before the choice: no branch) */ \
+          const float e_ = sacc[x][j] * a.scale_log2 - lt_[rl] * LOG2E;   /* (read before the choice: no branch) */ \
           const float pv = __builtin_amdgcn_exp2f(ok ? e_ : -INFINITY);                               \
-          p[x * 4 + j] = pv;                                                                          \
-          ds[x * 4 + j] = pv * (pacc[j] - lt_[32 + rl]);                                              \
+          pf[x * 4 + j] = (bf16_t)pv;                                                                 \
+          dsf[x * 4 + j] = (bf16_t)(pv * (pacc[x][j] - lt_[32 + rl]));                                \
         }                                                                                             \
-      }                                                                                               \
-      bf16x8 pf, dsf;                                                                                 \
-      _Pragma("unroll") for (int j = 0; j < 8; ++j) { pf[j] = (bf16_t)p[j]; dsf[j] = (bf16_t)ds[j]; } \
       /* dV^T[d, key] += dO^T[d, rows] P[rows, key];  dK^T[d, key] += Q^T[d, rows] dS[rows, key] */    \
       /* lane (d, g): rows 4g..4g+3 of both row tiles at column d */                                   \
       _Pragma("unroll") for (int mt = 0; mt < 8; ++mt) {                                              \
-        const int off_ = tr_base + (((mt * 2 + tr_hi) ^ tr_sw) * 8);                                  \
-        const bf16x8 ot = tr_pair(ot_ + off_, ot_ + TILE16 + off_);                                   \
-        const bf16x8 qt = tr_pair(qt_ + off_, qt_ + TILE16 + off_);                                   \
-        dv[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ot, pf, dv[mt], 0, 0, 0);                    \
-        dk[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qt, dsf, dk[mt], 0, 0, 0);                   \
+        __builtin_amdgcn_sched_barrier(0);                                                            \
+        if (mt + TRD - 1 < 8) FLEXCO_DKV_TR(qt_, ot_, mt + TRD - 1)                                   \
+        __builtin_amdgcn_sched_barrier(0);                                                            \
+        dv[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ot[mt % TRD], pf, dv[mt], 0, 0, 0);          \
+        dk[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qt[mt % TRD], dsf, dk[mt], 0, 0, 0);         \
       }                                                                                               \
+      __builtin_amdgcn_sched_barrier(0);                                                              \
     }                                                                                                 \
   }
-#define FLEXCO_DKV_STEP(qb_, ob_, ld_, qn_, on_, ln_, it_)                                            \
+  // SUB steps from one barrier to the next (a step past the last is all masks)
+  int r0_cur[SUB];
+  bool head_cur[SUB];
+  int n_issued = 0;
+#define FLEXCO_DKV_ISSUE(qb_, ob_, ld_)                                                               \
+  _Pragma("unroll") for (int u = 0; u < SUB; ++u) {                                                   \
+    if (n_issued > 0 && n_issued < nit) advance();                                                    \
+    r0_nxt[u] = first_row + 32 * rb;                                                                  \
+    head_nxt[u] = n_issued < nit && NH * hh + hg < group;                                             \
+    FLEXCO_ISSUE_QO(qb_, ob_, ld_, u)                                                                 \
+    ++n_issued;                                                                                       \
+  }
+  int r0_nxt[SUB];
+  bool head_nxt[SUB];
+#define FLEXCO_DKV_STEP(qb_, ob_, ld_, qn_, on_, ln_, MASKED_)                                        \
   {                                                                                                   \
     FLEXCO_WAIT_ALL_BARRIER                                                                           \
-    if ((it_) + 1 < nit) FLEXCO_ISSUE_QO(qn_, on_, ln_, (it_) + 1)                                    \
-    FLEXCO_DKV_COMPUTE(qb_, ob_, ld_, it_)                                                            \
+    _Pragma("unroll") for (int u = 0; u < SUB; ++u) { r0_cur[u] = r0_nxt[u]; head_cur[u] = head_nxt[u]; } \
+    if (n_issued < nit) {                                                                             \
+      FLEXCO_DKV_ISSUE(qn_, on_, ln_)                                                                 \
+    }                                                                                                 \
+    _Pragma("unroll") for (int u = 0; u < SUB; ++u)                                                   \
+      FLEXCO_DKV_COMPUTE(qb_, ob_, ld_, u, r0_cur[u], head_cur[u], MASKED_)                           \
   }
 
-  FLEXCO_ISSUE_QO(qb0, ob0, ld0, 0)
+  FLEXCO_DKV_ISSUE(qb0, ob0, ld0)
   int it = 0;
-  for (; it + 1 < nit; it += 2) {
-    FLEXCO_DKV_STEP(qb0, ob0, ld0, qb1, ob1, ld1, it)
-    FLEXCO_DKV_STEP(qb1, ob1, ld1, qb0, ob0, ld0, it + 1)
+  for (; it < n_vis; it += 2 * SUB) {
+    FLEXCO_DKV_STEP(qb0, ob0, ld0, qb1, ob1, ld1, false)
+    FLEXCO_DKV_STEP(qb1, ob1, ld1, qb0, ob0, ld0, false)
   }
-  if (it < nit) FLEXCO_DKV_STEP(qb0, ob0, ld0, qb1, ob1, ld1, it)
+  for (; it + SUB < nit; it += 2 * SUB) {
+    FLEXCO_DKV_STEP(qb0, ob0, ld0, qb1, ob1, ld1, true)
+    FLEXCO_DKV_STEP(qb1, ob1, ld1, qb0, ob0, ld0, true)
+  }
+  if (it < nit) FLEXCO_DKV_STEP(qb0, ob0, ld0, qb1, ob1, ld1, true)
   __builtin_amdgcn_s_waitcnt(0x0F70);   // nothing may land in LDS after the block ends
 
   // ---- the second half's sums join the first half's (dK, then dV), which adds them to the accumulator ----
@@ -490,10 +574,14 @@ int32_t launch_attention_bwd_mfma(const flexco_layer_cfg& c, const flexco_kv_poo
   a.scale_log2 = a.scale * LOG2E;
   // kernel A: eight wavefronts and eight pages per step while the grid gives a CU one block; with more blocks than
   // CUs, four wavefronts and four pages (64 KB of LDS, two blocks share a CU, each with its own barrier): 3 - 6 %
-  // faster there, 13 % slower on the one-block grid of a 256-row window
+  // faster there, 13 % slower on the one-block grid of a 256-row window.  Where that still leaves more blocks than CUs, two row
+  // tiles per wavefront (64 rows per block): half the LDS reads per product and two chains to interleave; both kernels of a
+  // 1024-row window in 4096 at the 14B shape 391 -> 369 us, 768 in 4000 at 8B 227 -> 207 (300 rows at 14B, 200 blocks: 114 -> 117)
   const dim3 grid_a((a.s + 31) / 32, a.nq);
-  if ((long)grid_a.x * grid_a.y > 256) hipLaunchKernelGGL(attn_bwd_dq_mfma_kernel<4>, grid_a, dim3(256), 0, s, a);
-  else hipLaunchKernelGGL(attn_bwd_dq_mfma_kernel<8>, grid_a, dim3(512), 0, s, a);
+  const dim3 grid_a2((a.s + 63) / 64, a.nq);
+  if ((long)grid_a2.x * grid_a2.y > 256) hipLaunchKernelGGL((attn_bwd_dq_mfma_kernel<4, 2>), grid_a2, dim3(256), 0, s, a);
+  else if ((long)grid_a.x * grid_a.y > 256) hipLaunchKernelGGL((attn_bwd_dq_mfma_kernel<4, 1>), grid_a, dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((attn_bwd_dq_mfma_kernel<8, 1>), grid_a, dim3(512), 0, s, a);
   // kernel B: the same choice - with more blocks than CUs, four-wavefront blocks that walk all heads of the kv group
   // in turn (33 KB of LDS, two blocks per CU): 7 - 9 % faster on the 4096-key windows
   const dim3 grid_b((a.l + 63) / 64, a.nkv);

@@ -411,7 +411,7 @@ __global__ __launch_bounds__(64) void attn_bwd_dkv_generic_kernel(const T* __res
     const T* dor = dout + row * d;
     const float row_lse = lse[row], row_delta = delta[row];
     float s = 0.f, dp = 0.f;
-#pragma unroll VEC ? (FEW ? 8 : 4) : 1
+#pragma unroll VEC ? (FEW ? 8 : 4) : 2
     for (int dd = 0; dd < d; dd += N) {
       float qv[N], ov[N];
       if constexpr (VEC) {

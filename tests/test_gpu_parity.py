@@ -270,6 +270,14 @@ def test_attention_window_bwd(cfg_name, win_start, win_len):
     assert np.array_equal(to_np(dv_d)[l:], base_v[l:].astype(np.float64))
 
 
+# the forms the backward kernels take by grid: two row tiles per wavefront (more 64-row blocks than CUs), with rows past the window in
+# the second tile or in both; steps without masks beside an odd last head, in both block sizes; a key block that ends past the sequence
+@pytest.mark.parametrize("cfg_name,win_start,win_len", [("c2", 130, 577), ("c2", 0, 625), ("c2", 1000, 640), ("g5", 500, 230), ("g5", 8200, 70),
+                                                        ("mha", 300, 200), ("g8", 64, 160)])
+def test_attention_window_bwd_forms(cfg_name, win_start, win_len):
+    test_attention_window_bwd(cfg_name, win_start, win_len)
+
+
 # ------------------------------------------------------------------------------------------
 # whole layer: forward iterations, then token-window backward
 # ------------------------------------------------------------------------------------------
