@@ -504,7 +504,7 @@ int32_t forward_projection(const flexco_layer_cfg& c, const Adapters& ad, const 
     GemmExt ext;
     memset(&sa, 0, sizeof(sa)); memset(&ext, 0, sizeof(ext));
     // u_{t,a} = scale x A_{t,a}^T for every token row (zero rows where the token is not served by adapter a)
-    sa.row_adapter = m.tok_adapter; sa.rows = T; sa.r = r; sa.scale = c.lora_scale;
+    sa.row_adapter = m.tok_adapter; sa.rows = T; sa.rows_on = m.n_lora; sa.r = r; sa.scale = c.lora_scale;
     sa.part = k.lw.part; sa.part_slots = PART_SLOTS;
     // the finetune window's rows of the unscaled product are kept for the backward pass (dB_t)
     const int ft_ad = ad.any_id ? 0 : m.ft_adapter;

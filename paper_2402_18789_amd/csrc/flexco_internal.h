@@ -24,6 +24,7 @@ struct LoraShrinkArgs {     // out[z][row][rank] = sum_k X[z][row, k] S[z][rank,
   const int32_t* row_adapter;
   int want[LORA_SLOTS];
   int rows, r;
+  int rows_on;              // rows that take part in a product, about; 0: all
   int f32_lo, f32_hi;
   float scale;
   // optional scratch of LORA_SHRINK_SPLITS * part_slots * rows * r floats: long contractions are then cut

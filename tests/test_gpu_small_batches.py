@@ -84,3 +84,15 @@ def test_generic_lora_rows(window, rank):
     cfg = CONFIGS["c1_tiny_f32"].with_(name="tiny_r%d" % rank, lora_rank=rank, lora_targets=("q", "v", "o", "gate", "up", "down"))
     b = gen.mixed_batch(cfg.page_size, 19, decode_ctx=(1, 40), finetune=[(0, window, 2 * window)])
     run_layer_case(cfg, b, ft_window=window, prefill_chunk=32, bwd_windows=[window, window], seed=19)
+
+
+# the matrix-core shrink products x A^T and dy B: blocks of 8 and 16 rows with a remainder, one to four tiles of
+# ranks, fewer groups of 128 columns than wavefronts, and contractions of over 16384 columns cut
+# over blocks in unequal ranges; rows of other adapters and of none beside them
+@pytest.mark.parametrize("rank,ffn,window", [(16, 16512, 23), (16, 1408, 9), (32, 16512, 140), (48, 1408, 23), (64, 1408, 140), (16, 1408, 1100)])
+def test_shrink_products(rank, ffn, window):
+    print(f"LoRA rank {rank}, ffn {ffn}, windows of {window}", flush=True)
+    cfg = WIDE.with_(name="shrink_r%d" % rank, hidden=640, n_q_heads=5, n_kv_heads=1, ffn=ffn, lora_rank=rank,
+                     lora_targets=("q", "k", "v", "o", "gate", "up", "down"))
+    b = gen.mixed_batch(cfg.page_size, 31, decode_ctx=(1, 40, 3), prefill=[(0, 37, 37)], finetune=[(0, window, 2 * window)])
+    run_layer_case(cfg, b, ft_window=window, prefill_chunk=37, bwd_windows=[window, window], seed=31)
