@@ -27,7 +27,7 @@ KERNEL_NAMES = {"gemm_fwd": "gemm_bf16_kernel<BM,BN,false>, gemm_bf16_quad_kerne
                 "gemm_bwd": "gemm_bf16_kernel<128,128,true>, gemm_bf16_quad_kernel<256,true> (input-gradient projections)",
                 "attn_fwd": "attn_fwd_chunk_kernel", "attn_merge": "attn_merge_kernel",
                 "attn_bwd": "attn_delta + attn_bwd_dq_mfma + attn_bwd_dkv_mfma", "elemwise": "norm/rope/swiglu/copy kernels",
-                "lora": "lora_shrink/finalize/transpose/outer kernels", "generic": "type-generic fallbacks"}
+                "lora": "lora_shrink/finalize/outer kernels", "generic": "type-generic fallbacks"}
 
 
 def log(*a):

@@ -201,7 +201,6 @@ constexpr size_t SPLITK_COLS = 32768;   // split-K scratch of the backward GEMMs
 // windows of up to 256 rows twice that (one row of 256 x 256 tiles: K in up to sixteen ranges to fill the chip)
 inline size_t bwd_splitk_cols(int n) { return n <= 256 ? 2 * SPLITK_COLS : SPLITK_COLS; }
 constexpr int FWD_SPLITK_MAX_T = 256;   // forward batches up to this many tokens get split-K scratch too
-constexpr int ROW_T_MAX_ROWS = 256;     // windows up to this many rows take t = dy B inside the row kernels
 
 struct Carver {
   char* base;
@@ -224,7 +223,6 @@ struct LoraWs {
   // backward only
   float* u[LORA_MATS];        // [rows, r]
   float* t[LORA_MATS];        // [rows, r]
-  bf16_t* bt[LORA_MATS];      // transposed B_t, [r, out_t]
 };
 
 void carve_lora(const flexco_layer_cfg& c, int rows, bool backward, Carver& cv, LoraWs& w) {
@@ -239,7 +237,6 @@ void carve_lora(const flexco_layer_cfg& c, int rows, bool backward, Carver& cv, 
     if (!backward) continue;
     w.u[t] = (float*)cv.take(sizeof(float) * (size_t)rows * r);
     w.t[t] = (float*)cv.take(sizeof(float) * (size_t)rows * r);
-    w.bt[t] = (bf16_t*)cv.take(sizeof(bf16_t) * (size_t)out * r);
   }
 }
 
@@ -586,7 +583,6 @@ struct BwdGroup {
   int N_dx;              // width of the projection's input = in_t of every target
   bool fused;            // bf16 matrix-core path: LoRA folded into the GEMM, gradients batched
   int act[3], nact;      // active targets (indices into targets[])
-  bool t_ready;          // fused only: a row kernel writes t_t = dy_t B_t (fp32 and the scaled bf16 copy) before the projection
 };
 
 void plan_group(const flexco_layer_cfg& c, BwdGroup& g) {
@@ -601,27 +597,22 @@ void plan_group(const flexco_layer_cfg& c, BwdGroup& g) {
   }
 }
 
-// Start of a backward window, fused groups only: u_t = x_t A_t^T of every target in one launch,
-// and the transposed B_t the t_t = dy_t B_t products contract against.
+// Start of a backward window, fused groups only: u_t = x_t A_t^T of every target in one launch.
 // Where the forward pass kept u_t (ft->saved_u), its window rows are used as they are.
 int32_t lora_bwd_prepare(const flexco_layer_cfg& c, const flexco_lora* lora, int n, const BwdGroup* groups,
                          int n_groups, BwdWs& k, const flexco_ft_state* ft, int win_start, hipStream_t s) {
   LoraShrinkArgs su;
-  LoraTransposeArgs ta;
-  memset(&su, 0, sizeof(su)); memset(&ta, 0, sizeof(ta));
+  memset(&su, 0, sizeof(su));
   const int r = c.lora_rank;
   su.rows = n; su.r = r; su.scale = 1.f; su.f32_lo = 0; su.f32_hi = n;   // (up to 7 matrices: no split scratch)
-  ta.r = r;
-  int nz = 0, nu = 0;
+  int nu = 0;
   for (int gi = 0; gi < n_groups; ++gi) {
     const BwdGroup& g = groups[gi];
     if (!g.fused) continue;
-    for (int a = 0; a < g.nact; ++a, ++nz) {
+    for (int a = 0; a < g.nact; ++a) {
       const int t = g.targets[g.act[a]];
       int in, out;
       target_dims(c, t, &in, &out);
-      if (g.t_ready) { ta.B[nz] = nullptr; ta.Bt[nz] = nullptr; ta.out[nz] = 0; }   // (no transposed B needed)
-      else { ta.B[nz] = (const bf16_t*)lora->B[t]; ta.Bt[nz] = k.lw.bt[t]; ta.out[nz] = out; }
       if (ft->saved_u[t]) {
         k.lw.u[t] = ft->saved_u[t] + (size_t)win_start * r;
         continue;
@@ -632,7 +623,6 @@ int32_t lora_bwd_prepare(const flexco_layer_cfg& c, const flexco_lora* lora, int
     }
   }
   if (nu > 0) LR(launch_lora_shrink_mfma(su, nu, s));
-  if (nz > 0) LR(launch_lora_transpose(ta, nz, s));
   return FLEXCO_OK;
 }
 
@@ -658,12 +648,13 @@ int32_t backward_projection(const flexco_layer_cfg& c, const flexco_lora* lora, 
     GemmExt ext;
     memset(&st, 0, sizeof(st)); memset(&ext, 0, sizeof(ext));
     st.rows = n; st.r = r; st.scale = c.lora_scale; st.f32_lo = 0; st.f32_hi = n; st.part = k.lw.part; st.part_slots = PART_SLOTS;
+    st.s_kmajor = 1;
     ext.n = g.nact; ext.r = r;
     for (int z = 0; z < g.nact; ++z) {
       const int t = g.targets[g.act[z]];
       int in, out;
       target_dims(c, t, &in, &out);
-      st.X[z] = (const bf16_t*)boff(dy, g.col0[g.act[z]], e); st.ldx[z] = K_dy; st.S[z] = k.lw.bt[t]; st.lds[z] = out;
+      st.X[z] = (const bf16_t*)boff(dy, g.col0[g.act[z]], e); st.ldx[z] = K_dy; st.S[z] = (const bf16_t*)lora->B[t];
       st.K[z] = out; st.out_f32[z] = k.lw.t[t]; st.out_ext[z] = k.lw.ext[t];
       ext.A2[z] = k.lw.ext[t]; ext.W2[z] = (const bf16_t*)lora->A[t]; ext.ldw2[z] = in;
       // dB_t[o, j] += scale sum_m dy_t[m, o] u_t[m, j];   dA_t[j, i] += scale sum_m x_t[m, i] t_t[m, j]
@@ -675,7 +666,7 @@ int32_t backward_projection(const flexco_layer_cfg& c, const flexco_lora* lora, 
       outer.G[q] = lora->dA[t]; outer.g_i[q] = 1; outer.g_j[q] = in; outer.n_long[q] = in;
       outer.count = q + 1;
     }
-    if (!g.t_ready) LR(launch_lora_shrink_mfma(st, g.nact, s));
+    LR(launch_lora_shrink_mfma(st, g.nact, s));
     if (dx)
       return launch_gemm(dy, W, dx, nullptr, nullptr, n, N_dx, K_dy, K_dy, N_dx, N_dx, 0, true, dt, s, &ext,
                          k.gemm_part, k.gemm_part_elems, splits_out);
@@ -1217,32 +1208,6 @@ static int32_t layer_backward_impl(const flexco_layer_cfg* cfg, const flexco_bas
   grp[3].n_targets = 3; grp[3].targets[0] = FLEXCO_T_Q; grp[3].targets[1] = FLEXCO_T_K; grp[3].targets[2] = FLEXCO_T_V;
   grp[3].col0[1] = qd; grp[3].col0[2] = qd + kd; grp[3].xs[0] = grp[3].xs[1] = grp[3].xs[2] = k.hn; grp[3].N_dx = H;
   for (int gi = 0; gi < 4; ++gi) plan_group(c, grp[gi]);
-  // t_t = dy_t B_t of the down, o and q/k/v targets: by the row kernels that hold the rows of dy_t anyway (dY has a
-  // kernel of its own), where rank and type allow; gate / up keep the shrink launch (their dy comes out of a
-  // kernel that does not own whole rows)
-  // (windows of up to ROW_T_MAX_ROWS rows: a row kernel's product costs its row a fixed few microseconds, three shrink launches and the
-  // one that turns the B_t about 24 us whatever the window.  A layer's backward, us, row products / shrink launches:
-  // 8B shape 300 rows 383 / 370, 512 rows 458 / 436; 14B shape 300 rows 481 / 459, 512 rows 585 / 557; level at 256 rows)
-  const bool row_t = row_lora_ok(dt, c.lora_rank) && n <= ROW_T_MAX_ROWS;
-  grp[0].t_ready = grp[0].fused && row_t;
-  grp[2].t_ready = grp[2].fused && row_t;
-  grp[3].t_ready = grp[3].fused && row_t;
-  auto row_lora = [&](const BwdGroup& g) {
-    RowLoraT lt = {};
-    if (!g.t_ready) return lt;
-    lt.r = c.lora_rank; lt.scale = c.lora_scale;
-    for (int i = 0; i < g.n_targets; ++i) {
-      const int t = g.targets[i];
-      if (!has_target(c, t)) continue;
-      // one target: entry 0; the q/k/v group: entry = role (0 q, 1 k, 2 v)
-      const int z = g.n_targets == 1 ? 0 : i;
-      int in, out;
-      target_dims(c, t, &in, &out);
-      lt.col0[z] = g.col0[i]; lt.col1[z] = g.col0[i] + out; lt.B[z] = lora->B[t]; lt.t[z] = k.lw.t[t]; lt.ext[z] = k.lw.ext[t];
-      ++lt.n;
-    }
-    return lt;
-  };
   LoraOuterArgs outer;
   memset(&outer, 0, sizeof(outer));
   outer.n = n; outer.r = c.lora_rank; outer.scale = c.lora_scale;
@@ -1263,7 +1228,6 @@ static int32_t layer_backward_impl(const flexco_layer_cfg* cfg, const flexco_bas
   if (gu_lora && !hn2_late) EW(launch_rmsnorm(x2_w, w->g2, k.hn2, n, H, c.rms_eps, dt, s));
   if (qkv_lora && !hn_late) EW(launch_rmsnorm(x_w, w->g1, k.hn, n, H, c.rms_eps, dt, s));
   FLEXCO_TRY(lora_bwd_prepare(c, lora, n, grp, 4, k, ft, win_start, s));
-  if (grp[0].t_ready) LR(launch_lora_row_t(dY, H, n, H, row_lora(grp[0]), s));
 
   // ---- MLP side: down projection, SwiGLU, gate/up projections, second norm -------------
   // (where an input-gradient product was cut over K, the kernel that reads it next adds the partial sums itself)
@@ -1276,11 +1240,8 @@ static int32_t layer_backward_impl(const flexco_layer_cfg* cfg, const flexco_bas
   EW(launch_swiglu_bwd(gate_w, up_w, k.dact, k.dgu, n, F, dt, s, act_late ? k.act : nullptr,
                        sp_dact > 1 ? k.gemm_part : nullptr, sp_dact));
   FLEXCO_TRY(backward_projection(c, lora, n, k.dgu, 2 * F, w->wgu, k.dh, grp[1], k, outer, s, &sp_dh2));
-  {
-    const RowLoraT lt = row_lora(grp[2]);   // dx2 is the output projection's dy
-    EW(launch_rmsnorm_bwd(x2_w, w->g2, k.dh, dY, k.dx2, n, H, c.rms_eps, dt, s, hn2_late ? k.hn2 : nullptr,
-                          sp_dh2 > 1 ? k.gemm_part : nullptr, sp_dh2, &lt));
-  }
+  EW(launch_rmsnorm_bwd(x2_w, w->g2, k.dh, dY, k.dx2, n, H, c.rms_eps, dt, s, hn2_late ? k.hn2 : nullptr,
+                        sp_dh2 > 1 ? k.gemm_part : nullptr, sp_dh2));
   // ---- output projection ------------------------------------------------------------------
   FLEXCO_TRY(backward_projection(c, lora, n, k.dx2, H, w->wo, k.dattn, grp[2], k, outer, s));
   // ---- attention: dQ of the window, dK/dV of every cached row before its end (Sec. 6.1) ---
@@ -1288,8 +1249,7 @@ static int32_t layer_backward_impl(const flexco_layer_cfg* cfg, const flexco_bas
                                        ft->dk_accum, ft->dv_accum, k.delta, s));
   // ---- q/k/v side: the window's accumulator rows are complete now (Sec. 7) ---------------
   if (dX || qkv_lora || ia3) {
-    const RowLoraT lt_qkv = ia3 ? RowLoraT{} : row_lora(grp[3]);
-    EW(launch_rope_bwd_pack(c, k.dq, ft->dk_accum + w0 * kd, ft->dv_accum + w0 * kd, k.dqkv, win_start, n, s, &lt_qkv));
+    EW(launch_rope_bwd_pack(c, k.dq, ft->dk_accum + w0 * kd, ft->dv_accum + w0 * kd, k.dqkv, win_start, n, s));
     if (ia3) {   // the k and v column ranges of the packed rows: dl += colsum(d (.) unscaled rows), d <- d (.) l
       EW(launch_ia3_colgrad(boff(k.dqkv, qd, e), qkvd, boff(ft->saved_k0, w0 * kd, e), kd, ia3->l_k, k.colsum_part,
                             ia3->dl_k, n, kd, dt, s));
@@ -1339,7 +1299,7 @@ int32_t check_adapter(int32_t dtype, int32_t hidden, const flexco_adapter* ad, b
 }  // namespace
 
 // The adapter's scratch.  Matrix-core path (bf16, b = 64, hidden a multiple of 128): forward = the bf16 ReLU output
-// of every token row; backward = u, t (fp32), t in bf16 and the transposed up-projection.  Otherwise the
+// of every token row; backward = u, t (fp32) and t in bf16.  Otherwise the
 // rank-r fallback kernels: one / two fp32 [rows, b] arrays.
 namespace {
 bool adapter_mfma_ok(int32_t dtype, int32_t hidden, int b) { return dtype == FLEXCO_BF16 && b == 64 && hidden % 128 == 0; }
@@ -1348,7 +1308,7 @@ size_t adapter_fwd_bytes(int32_t dtype, int32_t hidden, int b, size_t T, size_t 
 }
 size_t adapter_bwd_bytes(int32_t dtype, int32_t hidden, int b, size_t n) {
   size_t need = 2 * align_up(sizeof(float) * n * b, 256);
-  if (adapter_mfma_ok(dtype, hidden, b)) need += align_up(sizeof(bf16_t) * n * b, 256) + align_up(sizeof(bf16_t) * (size_t)b * hidden, 256);
+  if (adapter_mfma_ok(dtype, hidden, b)) need += align_up(sizeof(bf16_t) * n * b, 256);
   return need;
 }
 }  // namespace
@@ -1429,19 +1389,15 @@ extern "C" int32_t flexco_adapter_bwd(int32_t dtype, int32_t hidden, const flexc
   const void* x_w = boff(saved_in, (size_t)win_start * hidden, esize(dtype));
   if (adapter_mfma_ok(dtype, hidden, b)) {
     bf16_t* t_ext = (bf16_t*)cv.take(sizeof(bf16_t) * (size_t)n * b);
-    bf16_t* w_up_t = (bf16_t*)cv.take(sizeof(bf16_t) * (size_t)b * hidden);
-    // u = relu(x W_down^T) and t = dY W_up in one launch, t masked by the ReLU
-    LoraTransposeArgs ta;
-    memset(&ta, 0, sizeof(ta));
-    ta.B[0] = (const bf16_t*)ad->w_up; ta.Bt[0] = w_up_t; ta.out[0] = hidden; ta.r = b;
-    LR(launch_lora_transpose(ta, 1, s));
+    // u = relu(x W_down^T), then t = dY W_up, masked by the ReLU
     LoraShrinkArgs sa;
     memset(&sa, 0, sizeof(sa));
     sa.rows = n; sa.r = b; sa.scale = 1.f; sa.f32_lo = 0; sa.f32_hi = n; sa.relu = 1;
     sa.X[0] = (const bf16_t*)x_w; sa.ldx[0] = hidden; sa.S[0] = (const bf16_t*)ad->w_down; sa.lds[0] = hidden; sa.K[0] = hidden;
     sa.out_f32[0] = u;
-    sa.X[1] = (const bf16_t*)dY; sa.ldx[1] = hidden; sa.S[1] = w_up_t; sa.lds[1] = hidden; sa.K[1] = hidden; sa.out_f32[1] = t;
-    LR(launch_lora_shrink_mfma(sa, 2, s));
+    LR(launch_lora_shrink_mfma(sa, 1, s));
+    sa.X[0] = (const bf16_t*)dY; sa.S[0] = (const bf16_t*)ad->w_up; sa.s_kmajor = 1; sa.relu = 0; sa.out_f32[0] = t;
+    LR(launch_lora_shrink_mfma(sa, 1, s));
     LR(launch_relu_bwd_mask(u, t, t_ext, (size_t)n * b, s));
     // dW_up[o, j] += sum_m dY[m, o] u[m, j];  dW_down[j, i] += sum_m x[m, i] t[m, j]   (before dY changes)
     LoraOuterArgs outer;

@@ -24,6 +24,7 @@ struct LoraShrinkArgs {     // out[z][row][rank] = sum_k X[z][row, k] S[z][rank,
   const int32_t* row_adapter;
   int want[LORA_SLOTS];
   int rows, r;
+  int s_kmajor;             // S[z] lies [K][r] (lds unused, r a multiple of 16), not [r][K]
   int rows_on;              // rows that take part in a product, about; 0: all
   int f32_lo, f32_hi;
   float scale;
@@ -37,7 +38,6 @@ struct LoraShrinkArgs {     // out[z][row][rank] = sum_k X[z][row, k] S[z][rank,
 constexpr int LORA_SHRINK_SPLITS = 8;
 // t[i] <- 0 where u[i] <= 0 (the ReLU's backward mask, u = the ReLU's output); t_ext[i] = bf16(t[i])
 int32_t launch_relu_bwd_mask(const float* u, float* t, void* t_ext, size_t count, hipStream_t s);
-struct LoraTransposeArgs { const bf16_t* B[LORA_MATS]; bf16_t* Bt[LORA_MATS]; int out[LORA_MATS]; int r; };
 // batch of rank-r gradient products  G_e(i, j) += scale * sum_m X_e[m, i] U_e[m, j], m < n, i < n_long_e, j < r
 constexpr int LORA_OUTER_MAX = 2 * LORA_MATS;
 struct LoraOuterArgs {
@@ -120,7 +120,6 @@ int32_t launch_gemm_glu_mfma(const void* A, const void* W, void* act, int M, int
                              size_t ld_act, const GemmExt* ext, void* save_gate, void* save_up, int save_row0,
                              int save_rows, size_t ld_save, hipStream_t s, int timer_id);
 int32_t launch_lora_shrink_mfma(const LoraShrinkArgs& a, int n_mats, hipStream_t s);
-int32_t launch_lora_transpose(const LoraTransposeArgs& a, int n_mats, hipStream_t s);
 int32_t launch_lora_outer_batch(const LoraOuterArgs& a, hipStream_t s);
 int32_t launch_lora_outer_bf16(const void* X, size_t ldx, const float* U, float* G, size_t g_i, size_t g_j, int n,
                                int n_long, int r, float scale, hipStream_t s);
@@ -133,31 +132,16 @@ int32_t launch_rmsnorm_sums(const SplitSums& sums, const void* res, void* x, con
                             hipStream_t s, void* save, int save_row0, int save_rows);
 int32_t launch_rmsnorm(const void* x, const void* g, void* h, int T, int H, float eps, int dtype, hipStream_t s,
                        void* save = nullptr, int save_row0 = 0, int save_rows = 0);
-// The LoRA backward's rank-r products t_z = dy_z B_z (Sec. 4.1 bypass form) of up to three targets whose dy_z are
-// column ranges of ONE row that a row kernel has just produced: that kernel multiplies the row by B_z while it
-// holds it (bf16 only, r = 16 or 32), instead of a shrink launch reading the row back.
-struct RowLoraT {
-  int n;                       // targets (0: nothing to do)
-  int col0[3], col1[3];        // target z owns the row's columns [col0, col1)
-  const void* B[3];            // B_z [col1 - col0, r], row-major
-  float* t[3];                 // [rows, r] fp32, unscaled
-  void* ext[3];                // [rows, r] bf16, times scale: operand of the GEMM extension
-  int r;
-  float scale;
-};
-inline bool row_lora_ok(int dtype, int r) { return dtype == FLEXCO_BF16 && (r == 16 || r == 32); }
 int32_t launch_rmsnorm_bwd(const void* x, const void* g, const void* dh, const void* add, void* dx, int T, int H,
                            float eps, int dtype, hipStream_t s, void* hn = nullptr,
-                           const float* dh_part = nullptr, int splits = 1, const RowLoraT* lt = nullptr);
-// t = dy B for one target over n rows of width `width` (the same row product as a kernel of its own)
-int32_t launch_lora_row_t(const void* dy, size_t lddy, int n, int width, const RowLoraT& lt, hipStream_t s);
+                           const float* dh_part = nullptr, int splits = 1);
 int32_t launch_rope_append(const flexco_layer_cfg& c, void* qkv, const int32_t* tok_pos, const int32_t* slot,
                            const flexco_kv_pool& pool, int T, int ft_tok0, int n_ft, int ft_pos0, void* q_cache,
                            hipStream_t s, const SplitSums* sums = nullptr, const void* bias = nullptr);
 // sums: the qkv rows still lie as partial sums (bf16, rope_append_vec); q is then written to qkv, k and v to the pool only
 bool rope_append_vec(const flexco_layer_cfg& c, const void* qkv, const flexco_kv_pool& pool, const void* q_cache);
 int32_t launch_rope_bwd_pack(const flexco_layer_cfg& c, const void* dq, const float* dk_rows, const float* dv_rows,
-                             void* dqkv, int win_start, int n, hipStream_t s, const RowLoraT* lt = nullptr);
+                             void* dqkv, int win_start, int n, hipStream_t s);
 // rows [save_row0, save_row0 + save_rows) of gate and up are also written to save_gate / save_up (NULL: none)
 int32_t launch_swiglu(const void* gu, void* act, int T, int F, int dtype, hipStream_t s, void* save_gate, void* save_up,
                       int save_row0, int save_rows);

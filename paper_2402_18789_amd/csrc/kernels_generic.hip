@@ -21,10 +21,8 @@ namespace flexco {
 // Every lane gets the result.  Within a row of 16 lanes the partner's value comes through the data-parallel
 // primitives, as an operand modifier of the addition itself (lane ^ 1, lane ^ 2, then the other quad of eight lanes
 // and the other half of the row by mirrored reads - the quads, then the halves, are uniform by then); only the two
-// exchanges between rows go through the LDS crossbar (a rank-16 row product ends with sixteen of these sums per
-// wavefront: 4.1 of the norm backward's 17.6 us were the 96 crossbar exchanges of the all-crossbar form; row swaps
-// for the last two steps as well, as the attention kernels use them in their softmax chain, were 3 - 5 % slower
-// here, where sixteen independent sums overlap their crossbar round trips).
+// exchanges between rows go through the LDS crossbar (row swaps for the last two steps as well, as the attention kernels use
+// them in their softmax chain, were 3 - 5 % slower in a kernel of sixteen independent sums, which overlap their crossbar round trips).
 template <int CTRL>
 __device__ inline float dpp_read(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, false));
@@ -55,89 +53,6 @@ __device__ inline float block_sum256(float v, float* red /* >= 4 floats of LDS *
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
   return red[0] + red[1] + red[2] + red[3];
-}
-
-// ---- rank-r products of a row with LoRA B matrices, inside the row kernel that produced the row ------------
-// acc[q] += v * B[col][q]: one 2 R-byte row of B per element
-template <int R>
-__device__ inline void lora_acc_row(float (&acc)[R], float v, const bf16_t* __restrict__ brow) {
-#pragma unroll
-  for (int q8 = 0; q8 < R / 8; ++q8) {
-    const bf16x8 b = *reinterpret_cast<const bf16x8*>(brow + 8 * q8);
-#pragma unroll
-    for (int q = 0; q < 8; ++q) acc[8 * q8 + q] += v * (float)b[q];
-  }
-}
-// the same for N consecutive columns: every load is issued before the first multiply-add
-template <int R, int N>
-__device__ inline void lora_acc_cols(float (&acc)[R], const float (&v)[N], const bf16_t* __restrict__ brow0) {
-  bf16x8 b[N][R / 8];
-#pragma unroll
-  for (int j = 0; j < N; ++j)
-#pragma unroll
-    for (int q8 = 0; q8 < R / 8; ++q8) b[j][q8] = *reinterpret_cast<const bf16x8*>(brow0 + (size_t)j * R + 8 * q8);
-#pragma unroll
-  for (int j = 0; j < N; ++j)
-#pragma unroll
-    for (int q8 = 0; q8 < R / 8; ++q8)
-#pragma unroll
-      for (int q = 0; q < 8; ++q) acc[8 * q8 + q] += v[j] * (float)b[j][q8][q];
-}
-// the two halves of lora_acc_cols apart, for kernels that request the rows of B before they have the values
-template <int R, int N>
-__device__ inline void lora_load_cols(bf16x8 (&b)[N][R / 8], const bf16_t* __restrict__ brow0) {
-#pragma unroll
-  for (int j = 0; j < N; ++j)
-#pragma unroll
-    for (int q8 = 0; q8 < R / 8; ++q8) b[j][q8] = *reinterpret_cast<const bf16x8*>(brow0 + (size_t)j * R + 8 * q8);
-}
-template <int R, int N>
-__device__ inline void lora_fma_cols(float (&acc)[R], const float (&v)[N], const bf16x8 (&b)[N][R / 8]) {
-#pragma unroll
-  for (int j = 0; j < N; ++j)
-#pragma unroll
-    for (int q8 = 0; q8 < R / 8; ++q8)
-#pragma unroll
-      for (int q = 0; q < 8; ++q) acc[8 * q8 + q] += v[j] * (float)b[j][q8][q];
-}
-// sum of acc over the block's 256 threads (the lanes of a wavefront, then the four wavefronts in order) -> t and ext of `row`
-template <int R, int NW = 4>
-__device__ inline void lora_row_finish(float (&acc)[R], float* lds /* NW R floats */, float* t, bf16_t* ext, size_t row,
-                                       float scale) {
-#pragma unroll
-  for (int q = 0; q < R; ++q) acc[q] = wave_sum(acc[q]);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) {
-#pragma unroll
-    for (int q = 0; q < R; ++q) lds[(threadIdx.x >> 6) * R + q] = acc[q];
-  }
-  __syncthreads();
-  if (threadIdx.x < R) {
-    float v = lds[threadIdx.x];
-#pragma unroll
-    for (int w = 1; w < NW; ++w) v += lds[w * R + threadIdx.x];
-    t[row * R + threadIdx.x] = v;
-    ext[row * R + threadIdx.x] = (bf16_t)(v * scale);
-  }
-}
-
-// t = dy B of one target, one block of NW wavefronts per row (see RowLoraT)
-template <int R, int NW>
-__global__ __launch_bounds__(64 * NW) void lora_row_t_kernel(const bf16_t* __restrict__ dy, size_t lddy, int width, RowLoraT lt) {
-  __shared__ float lds[NW * R];
-  const size_t row = blockIdx.x;
-  float acc[R];
-#pragma unroll
-  for (int q = 0; q < R; ++q) acc[q] = 0.f;
-  const bf16_t* B = (const bf16_t*)lt.B[0];
-  for (int i = threadIdx.x * 8; i < width; i += 64 * NW * 8) {
-    const bf16x8 v = *reinterpret_cast<const bf16x8*>(dy + row * lddy + i);
-    float vf[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) vf[j] = (float)v[j];
-    lora_acc_cols<R, 8>(acc, vf, B + (size_t)i * R);
-  }
-  lora_row_finish<R, NW>(acc, lds, lt.t[0], (bf16_t*)lt.ext[0], row, lt.scale);
 }
 
 // --------------------------------------------------------------------------------------
@@ -286,18 +201,11 @@ __device__ inline void load_split_sum(const float* __restrict__ part, int splits
 
 // dx = rstd * (g * dh) - x * rstd^3 * mean(x * g * dh)  (+ add);  hn (optional) = x rstd g, the row
 // the forward norm produced (same arithmetic, same bits), for callers that need it again
-// R > 0 (bf16, VEC): the produced row dx is also multiplied by a LoRA B matrix (see RowLoraT; one target = the whole row)
-template <typename T, bool VEC, int R = 0>
+template <typename T, bool VEC>
 __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(const T* __restrict__ x, const T* __restrict__ g,
                                                           const T* __restrict__ dh, const T* __restrict__ add,
                                                           T* __restrict__ dx, T* __restrict__ hn, int H, float eps,
-                                                          const float* __restrict__ dh_part, int splits, size_t stride,
-                                                          RowLoraT lt) {
-  constexpr int RA = R > 0 ? R : 1;
-  __shared__ float lt_lds[4 * RA];
-  float lt_acc[RA];
-#pragma unroll
-  for (int q = 0; q < RA; ++q) lt_acc[q] = 0.f;
+                                                          const float* __restrict__ dh_part, int splits, size_t stride) {
   // dh_part: dh still lies as split-K partial sums (see load_split_sum); the row's sums are kept in LDS
   // between the two passes (dynamic shared memory of H floats, only then)
   extern __shared__ float dh_row[];
@@ -360,13 +268,7 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(const T* __restrict__ 
         if (add) v[j] += av[j];
       }
       Vec<T>::store(dx + row * H + i, v);
-      if constexpr (R > 0) {   // (the values as they were just stored)
-#pragma unroll
-        for (int j = 0; j < N; ++j) v[j] = (float)(T)v[j];
-        lora_acc_cols<R, N>(lt_acc, v, (const bf16_t*)lt.B[0] + (size_t)i * R);
-      }
     }
-    if constexpr (R > 0) lora_row_finish<R>(lt_acc, lt_lds, lt.t[0], (bf16_t*)lt.ext[0], row, lt.scale);
   } else {
     for (int i = threadIdx.x; i < H; i += 256) {
       if (hn) st(hn + row * H + i, ld(xr + i) * rstd * ld(g + i));
@@ -384,16 +286,14 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(const T* __restrict__ 
 // loads in turn; here the chip holds four times as many wavefronts and each waits once.
 // The sums over the row are taken in another order than above: hn may differ from the forward norm's row in the last
 // bit of an element.
-template <int R, int IT>
+template <int IT>
 __global__ __launch_bounds__(1024) void rmsnorm_bwd_wide_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ g,
                                                                 const bf16_t* __restrict__ dh,
                                                                 const bf16_t* __restrict__ add, bf16_t* __restrict__ dx,
                                                                 bf16_t* __restrict__ hn, int H, float eps,
                                                                 const float* __restrict__ dh_part, int splits,
-                                                                size_t stride, RowLoraT lt) {
-  constexpr int RA = R > 0 ? R : 1;
+                                                                size_t stride) {
   __shared__ float red[2][16];
-  __shared__ float lt_lds[16 * RA];
   const size_t row = blockIdx.x;
   const int wave = threadIdx.x >> 6;
   float v[IT][4], gv[IT][4], dv[IT][4], av[IT][4];
@@ -409,14 +309,12 @@ __global__ __launch_bounds__(1024) void rmsnorm_bwd_wide_kernel(const bf16_t* __
     *reinterpret_cast<bf16x4*>(p) = t;
   };
   float ss = 0.f, sd = 0.f;
-  bf16x8 bfrag[IT][4][R > 0 ? R / 8 : 1];   // the rows of B this thread's elements meet, fetched with the row
 #pragma unroll
   for (int it = 0; it < IT; ++it) {
     const int i = (it * 1024 + (int)threadIdx.x) * 4;
 #pragma unroll
     for (int j = 0; j < 4; ++j) v[it][j] = gv[it][j] = dv[it][j] = av[it][j] = 0.f;
     if (i < H) {
-      if constexpr (R > 0) lora_load_cols<R, 4>(bfrag[it], (const bf16_t*)lt.B[0] + (size_t)i * R);
       ld4(x + row * H + i, v[it]);
       ld4(g + i, gv[it]);
       if (add) ld4(add + row * H + i, av[it]);
@@ -455,9 +353,6 @@ __global__ __launch_bounds__(1024) void rmsnorm_bwd_wide_kernel(const bf16_t* __
   for (int w = 0; w < 16; ++w) { ss += red[0][w]; sd += red[1][w]; }
   const float rstd = 1.0f / sqrtf(ss / H + eps);
   const float coef = rstd * rstd * rstd * sd / H;
-  float lt_acc[RA];
-#pragma unroll
-  for (int q = 0; q < RA; ++q) lt_acc[q] = 0.f;
 #pragma unroll
   for (int it = 0; it < IT; ++it) {
     const int i = (it * 1024 + (int)threadIdx.x) * 4;
@@ -475,14 +370,8 @@ __global__ __launch_bounds__(1024) void rmsnorm_bwd_wide_kernel(const bf16_t* __
         if (add) o[j] += av[it][j];
       }
       st4(dx + row * H + i, o);
-      if constexpr (R > 0) {   // (the values as they were just stored)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) o[j] = (float)(bf16_t)o[j];
-        lora_fma_cols<R, 4>(lt_acc, o, bfrag[it]);
-      }
     }
   }
-  if constexpr (R > 0) lora_row_finish<R, 16>(lt_acc, lt_lds, lt.t[0], (bf16_t*)lt.ext[0], row, lt.scale);
 }
 
 // Rotation angles.  Pair i of a head turns by pos * theta^(-2 i / d).  The host hands over the frequencies in
@@ -701,8 +590,6 @@ __global__ __launch_bounds__(SUMS ? 512 : 256) void rope_append_kernel(T* __rest
 
 // Backward of the q/k/v rotation for a window: dqkv[n, (nq+2nkv)d] = [rope^T(dq) | rope^T(dk) | dv]
 // dq rows are in the storage type, dk/dv rows are the (float) accumulator rows of the window.
-// R > 0 (bf16): the packed row is also multiplied by the LoRA B matrices of q, k, v (see RowLoraT; entry 0 = q,
-// 1 = k, 2 = v, B = NULL where the projection carries no LoRA)
 // N consecutive floats with 16-byte loads
 template <int N>
 __device__ inline void load_f32_run(const float* p, float (&v)[N]) {
@@ -715,17 +602,11 @@ __device__ inline void load_f32_run(const float* p, float (&v)[N]) {
 }
 
 // VEC as in rope_append_kernel
-template <typename T, int R = 0, bool VEC = false>
+template <typename T, bool VEC>
 __global__ __launch_bounds__(256) void rope_bwd_pack_kernel(const T* __restrict__ dq, const float* __restrict__ dk,
                                                             const float* __restrict__ dv, T* __restrict__ dqkv,
-                                                            int nq, int nkv, int d, RopeFreq freq, int win_start,
-                                                            RowLoraT lt) {
+                                                            int nq, int nkv, int d, RopeFreq freq, int win_start) {
   extern __shared__ float cs[];
-  constexpr int RA = R > 0 ? R : 1;
-  __shared__ float lt_lds[4 * RA];
-  float acc_q[RA], acc_k[RA], acc_v[RA];
-#pragma unroll
-  for (int q = 0; q < RA; ++q) acc_q[q] = acc_k[q] = acc_v[q] = 0.f;
   const int r = blockIdx.x;
   const int pos = win_start + r;
   const int half = d >> 1;
@@ -760,36 +641,11 @@ __global__ __launch_bounds__(256) void rope_bwd_pack_kernel(const T* __restrict_
       }
       Vec<T>::store(out + head * d + i, rlo);
       Vec<T>::store(out + head * d + half + i, rhi);
-      if constexpr (R > 0) {   // (the values as they were just stored)
-#pragma unroll
-        for (int j = 0; j < N; ++j) {
-          rlo[j] = (float)(T)rlo[j];
-          rhi[j] = (float)(T)rhi[j];
-        }
-        if (head < nq) {
-          if (lt.B[0]) {
-            const bf16_t* b = (const bf16_t*)lt.B[0] + (size_t)(head * d + i) * R;
-            lora_acc_cols<R, N>(acc_q, rlo, b);
-            lora_acc_cols<R, N>(acc_q, rhi, b + (size_t)half * R);
-          }
-        } else if (lt.B[1]) {
-          const bf16_t* b = (const bf16_t*)lt.B[1] + (size_t)((head - nq) * d + i) * R;
-          lora_acc_cols<R, N>(acc_k, rlo, b);
-          lora_acc_cols<R, N>(acc_k, rhi, b + (size_t)half * R);
-        }
-      }
     }
     for (int idx = threadIdx.x * N; part != 0 && idx < nkv * d; idx += 256 * N) {
       float v[N];
       load_f32_run<N>(dv + (size_t)r * nkv * d + idx, v);
       Vec<T>::store(out + (nq + nkv) * d + idx, v);
-      if constexpr (R > 0) {
-        if (lt.B[2]) {
-#pragma unroll
-          for (int j = 0; j < N; ++j) v[j] = (float)(T)v[j];
-          lora_acc_cols<R, N>(acc_v, v, (const bf16_t*)lt.B[2] + (size_t)idx * R);
-        }
-      }
     }
   } else {
   for (int idx = h_lo * half + threadIdx.x; idx < h_hi * half; idx += 256) {
@@ -807,33 +663,11 @@ __global__ __launch_bounds__(256) void rope_bwd_pack_kernel(const T* __restrict_
     const float rlo = lo * c + hi * sn, rhi = hi * c - lo * sn;
     st(out + head * d + i, rlo);
     st(out + head * d + half + i, rhi);
-    if constexpr (R > 0) {   // (the values as they were just stored)
-      const float vlo = (float)(T)rlo, vhi = (float)(T)rhi;
-      if (head < nq) {
-        if (lt.B[0]) {
-          const bf16_t* b = (const bf16_t*)lt.B[0] + (size_t)(head * d + i) * R;
-          lora_acc_row<R>(acc_q, vlo, b);
-          lora_acc_row<R>(acc_q, vhi, b + (size_t)half * R);
-        }
-      } else if (lt.B[1]) {
-        const bf16_t* b = (const bf16_t*)lt.B[1] + (size_t)((head - nq) * d + i) * R;
-        lora_acc_row<R>(acc_k, vlo, b);
-        lora_acc_row<R>(acc_k, vhi, b + (size_t)half * R);
-      }
-    }
   }
   for (int idx = threadIdx.x; part != 0 && idx < nkv * d; idx += 256) {
     const float v = dv[(size_t)r * nkv * d + idx];
     st(out + (nq + nkv) * d + idx, v);
-    if constexpr (R > 0) {
-      if (lt.B[2]) lora_acc_row<R>(acc_v, (float)(T)v, (const bf16_t*)lt.B[2] + (size_t)idx * R);
-    }
   }
-  }
-  if constexpr (R > 0) {
-    if (lt.B[0] && part != 1) lora_row_finish<R>(acc_q, lt_lds, lt.t[0], (bf16_t*)lt.ext[0], r, lt.scale);
-    if (lt.B[1] && part != 0) lora_row_finish<R>(acc_k, lt_lds, lt.t[1], (bf16_t*)lt.ext[1], r, lt.scale);
-    if (lt.B[2] && part != 0) lora_row_finish<R>(acc_v, lt_lds, lt.t[2], (bf16_t*)lt.ext[2], r, lt.scale);
   }
 }
 
@@ -1322,44 +1156,23 @@ int32_t launch_rmsnorm_sums(const SplitSums& sums, const void* res, void* x, con
 }
 
 int32_t launch_rmsnorm_bwd(const void* x, const void* g, const void* dh, const void* add, void* dx, int T_, int H,
-                           float eps, int dtype, hipStream_t s, void* hn, const float* dh_part, int splits,
-                           const RowLoraT* lt_in) {
+                           float eps, int dtype, hipStream_t s, void* hn, const float* dh_part, int splits) {
   if (T_ == 0) return FLEXCO_OK;
   const bool vec = vec_ok(dtype, H, {x, g, dh, add, dx, hn, dh_part});
   const size_t shm = dh_part ? sizeof(float) * (size_t)H : 0;
-  RowLoraT lt = {};
   // bf16 rows of up to 8192 elements: sixteen wavefronts per row
-  if (dtype == FLEXCO_BF16 && vec && H <= 8192 && (!lt_in || lt_in->n == 0 || (lt_in->n == 1 && row_lora_ok(dtype, lt_in->r)))) {
-    if (lt_in && lt_in->n > 0) lt = *lt_in;
-    const int R = lt_in && lt_in->n > 0 ? lt.r : 0;
-    const size_t stride = (size_t)T_ * H;
-#define FLEXCO_NORM_BWD_WIDE(R_, IT_)                                                                              \
-    hipLaunchKernelGGL((rmsnorm_bwd_wide_kernel<R_, IT_>), dim3(T_), dim3(1024), 0, s, (const bf16_t*)x,            \
+  if (dtype == FLEXCO_BF16 && vec && H <= 8192) {
+#define FLEXCO_NORM_BWD_WIDE(IT_)                                                                                  \
+    hipLaunchKernelGGL((rmsnorm_bwd_wide_kernel<IT_>), dim3(T_), dim3(1024), 0, s, (const bf16_t*)x,                \
                        (const bf16_t*)g, (const bf16_t*)dh, (const bf16_t*)add, (bf16_t*)dx, (bf16_t*)hn, H, eps,   \
-                       dh_part, splits, stride, lt)
-    if (H <= 4096) {
-      if (R == 0) FLEXCO_NORM_BWD_WIDE(0, 1); else if (R == 16) FLEXCO_NORM_BWD_WIDE(16, 1); else FLEXCO_NORM_BWD_WIDE(32, 1);
-    } else {
-      if (R == 0) FLEXCO_NORM_BWD_WIDE(0, 2); else if (R == 16) FLEXCO_NORM_BWD_WIDE(16, 2); else FLEXCO_NORM_BWD_WIDE(32, 2);
-    }
+                       dh_part, splits, (size_t)T_ * H)
+    if (H <= 4096) FLEXCO_NORM_BWD_WIDE(1); else FLEXCO_NORM_BWD_WIDE(2);
 #undef FLEXCO_NORM_BWD_WIDE
-    return post_launch("rmsnorm_bwd");
-  }
-  if (lt_in && lt_in->n > 0) {
-    if (!vec || !row_lora_ok(dtype, lt_in->r) || lt_in->n != 1) return fail(FLEXCO_EUNSUPPORTED, "rmsnorm_bwd: row product not covered");
-    lt = *lt_in;
-    const size_t stride = (size_t)T_ * H;
-#define FLEXCO_NORM_BWD_LT(R_)                                                                                     \
-    hipLaunchKernelGGL((rmsnorm_bwd_kernel<bf16_t, true, R_>), dim3(T_), dim3(256), shm, s, (const bf16_t*)x,       \
-                       (const bf16_t*)g, (const bf16_t*)dh, (const bf16_t*)add, (bf16_t*)dx, (bf16_t*)hn, H, eps,   \
-                       dh_part, splits, stride, lt)
-    if (lt.r == 16) FLEXCO_NORM_BWD_LT(16); else FLEXCO_NORM_BWD_LT(32);
-#undef FLEXCO_NORM_BWD_LT
     return post_launch("rmsnorm_bwd");
   }
   DISPATCH_TV(dtype, vec, hipLaunchKernelGGL((rmsnorm_bwd_kernel<T, VEC>), dim3(T_), dim3(256), shm, s, (const T*)x,
                                              (const T*)g, (const T*)dh, (const T*)add, (T*)dx, (T*)hn, H, eps, dh_part,
-                                             splits, (size_t)T_ * H, lt));
+                                             splits, (size_t)T_ * H));
   return post_launch("rmsnorm_bwd");
 }
 
@@ -1410,7 +1223,7 @@ int32_t launch_rope_append(const flexco_layer_cfg& c, void* qkv, const int32_t* 
 }
 
 int32_t launch_rope_bwd_pack(const flexco_layer_cfg& c, const void* dq, const float* dk_rows, const float* dv_rows,
-                             void* dqkv, int win_start, int n, hipStream_t s, const RowLoraT* lt_in) {
+                             void* dqkv, int win_start, int n, hipStream_t s) {
   const size_t shm = sizeof(float) * c.head_dim;
   if (n == 0) return FLEXCO_OK;
   RopeFreq freq;
@@ -1418,32 +1231,10 @@ int32_t launch_rope_bwd_pack(const flexco_layer_cfg& c, const void* dq, const fl
   const dim3 grid(n, n <= 512 ? 2 : 1);   // few rows: two blocks per row
   // 16-byte accesses: also the float rows of dk / dv (their row pitch nkv d floats is a multiple of 16 bytes then)
   const bool vec = c.head_dim % 2 == 0 && vec_ok(c.dtype, c.head_dim / 2, {dq, dk_rows, dv_rows, dqkv});
-  RowLoraT lt = {};
-  if (lt_in && lt_in->n > 0) {
-    if (!row_lora_ok(c.dtype, lt_in->r)) return fail(FLEXCO_EUNSUPPORTED, "rope_bwd_pack: row product not covered");
-    lt = *lt_in;
-#define FLEXCO_ROPE_BWD_LT(R_, V_)                                                                                      \
-  hipLaunchKernelGGL((rope_bwd_pack_kernel<bf16_t, R_, V_>), grid, dim3(256), shm, s, (const bf16_t*)dq, dk_rows, dv_rows, \
-                     (bf16_t*)dqkv, c.n_q_heads, c.n_kv_heads, c.head_dim, freq, win_start, lt)
-    if (lt.r == 16) { if (vec) FLEXCO_ROPE_BWD_LT(16, true); else FLEXCO_ROPE_BWD_LT(16, false); }
-    else { if (vec) FLEXCO_ROPE_BWD_LT(32, true); else FLEXCO_ROPE_BWD_LT(32, false); }
-#undef FLEXCO_ROPE_BWD_LT
-    return post_launch("rope_bwd_pack");
-  }
-  DISPATCH_TV(c.dtype, vec, hipLaunchKernelGGL((rope_bwd_pack_kernel<T, 0, VEC>), grid, dim3(256), shm, s, (const T*)dq,
+  DISPATCH_TV(c.dtype, vec, hipLaunchKernelGGL((rope_bwd_pack_kernel<T, VEC>), grid, dim3(256), shm, s, (const T*)dq,
                                                dk_rows, dv_rows, (T*)dqkv, c.n_q_heads, c.n_kv_heads, c.head_dim,
-                                               freq, win_start, lt));
+                                               freq, win_start));
   return post_launch("rope_bwd_pack");
-}
-
-int32_t launch_lora_row_t(const void* dy, size_t lddy, int n, int width, const RowLoraT& lt, hipStream_t s) {
-  if (n == 0) return FLEXCO_OK;
-  if (!row_lora_ok(FLEXCO_BF16, lt.r) || width % 8 != 0 || lddy % 8 != 0 || !aligned16(dy) || !aligned16(lt.B[0]))
-    return fail(FLEXCO_EUNSUPPORTED, "lora_row_t: shape not covered");
-  // (sixteen wavefronts per row were measured slower here: the sixteen sums per wavefront at the end grow with them)
-  if (lt.r == 16) hipLaunchKernelGGL((lora_row_t_kernel<16, 4>), dim3(n), dim3(256), 0, s, (const bf16_t*)dy, lddy, width, lt);
-  else hipLaunchKernelGGL((lora_row_t_kernel<32, 4>), dim3(n), dim3(256), 0, s, (const bf16_t*)dy, lddy, width, lt);
-  return post_launch("lora_row_t");
 }
 
 int32_t launch_ia3_scale_rows(void* buf, size_t ld, const int32_t* tok, int n_tok, const Ia3ScaleArgs& a, int dtype,

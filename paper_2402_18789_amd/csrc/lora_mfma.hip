@@ -23,6 +23,16 @@ namespace flexco {
 
 namespace {
 
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+#define FLEXCO_GP(p) ((const __attribute__((address_space(1))) void*)(p))
+#define FLEXCO_LP(p) ((__attribute__((address_space(3))) void*)(p))
+#define FLEXCO_LDS __attribute__((address_space(3)))
+__device__ inline bf16x8 tr_pair(const bf16_t* a, const bf16_t* b) {
+  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((FLEXCO_LDS s16x4*)a);
+  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((FLEXCO_LDS s16x4*)b);
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
 // One block per RB rows and matrix; K is cut, in whole groups of 128 columns, across the block's wavefronts (and over gridDim.z
 // blocks), whose partial sums are added in wavefront order through LDS.
 //
@@ -36,7 +46,9 @@ namespace {
 // Measured, us, operands in fragment order -> turned (same products): 1024 x 4096, three products of rank 16 11.0 -> 6.3, one
 // 10.6 -> 5.6; 2048 x 5120, three 21.0 -> 10.6; 48 x 5120, twelve 12.8 -> 6.5; 1405 x 5120, three of rank 32 31.0 -> 12.9; 1024 x
 // 14336 in one launch 27.6 -> 10.9 (in eight ranges 9.9 -> 7.8, each with a launch of 5 us that adds them).
-template <int RT, int RB>   // rank tiles of 16, rows of a block (8 or 16)
+// KM: S lies [K][r] (a B_t as it is, r a multiple of 16): a load takes 32 of its rows, 16 ranks each, and the operand comes from
+// transposing LDS reads, four k of 16 ranks each.  (Before, a launch of 6 us turned the B_t of a backward window first.)
+template <int RT, int RB, bool KM>   // rank tiles of 16, rows of a block (8 or 16), the low-rank operand's layout
 __global__ __launch_bounds__(512) void lora_shrink_kernel(LoraShrinkArgs a) {
   constexpr int U = RT == 1 ? 2 : 1, NW = 8, XP = RB / 4;
   __shared__ __attribute__((aligned(16))) bf16_t turn[NW][16 * 128];
@@ -72,8 +84,10 @@ __global__ __launch_bounds__(512) void lora_shrink_kernel(LoraShrinkArgs a) {
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
       const int j = rt * 16 + 4 * p + lr;
-      sp[rt][p] = a.S[z] + (size_t)(j < a.r ? j : 0) * a.lds[z] + lc * 8;
+      if (KM) sp[rt][p] = a.S[z] + (size_t)(32 * p + (lane >> 1)) * a.r + rt * 16 + (lane & 1) * 8;
+      else sp[rt][p] = a.S[z] + (size_t)(j < a.r ? j : 0) * a.lds[z] + lc * 8;
     }
+  const size_t s_step = KM ? a.r : 1;             // elements of S per step of k
   f32x4 acc[RT];
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) acc[rt] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -93,6 +107,16 @@ __global__ __launch_bounds__(512) void lora_shrink_kernel(LoraShrinkArgs a) {
     _Pragma("unroll") for (int s = 0; s < 4; ++s)                                                     \
       f_[s] = *reinterpret_cast<const bf16x8*>(buf + m * 128 + (((4 * s + g) ^ m) & 15) * 8);         \
   }
+#define FLEXCO_TURN_KM(v_, f_)                                                                        \
+  {                                                                                                   \
+    asm volatile("" ::: "memory");                                                                    \
+    _Pragma("unroll") for (int p = 0; p < 4; ++p) *reinterpret_cast<bf16x8*>(buf + p * 512 + lane * 8) = v_[p]; \
+    asm volatile("" ::: "memory");                                                                    \
+    _Pragma("unroll") for (int s = 0; s < 4; ++s) {                                                   \
+      const bf16_t* t_ = buf + (32 * s + 8 * g + (m >> 2)) * 16 + 4 * (m & 3);                        \
+      f_[s] = tr_pair(t_, t_ + 4 * 16);                                                               \
+    }                                                                                                 \
+  }
 #define FLEXCO_SHRINK_GROUPS(U_)                                                                      \
   {                                                                                                   \
     bf16x8 x_[U_][XP], s_[U_][RT][4];                                                                 \
@@ -101,15 +125,15 @@ __global__ __launch_bounds__(512) void lora_shrink_kernel(LoraShrinkArgs a) {
         x_[u][p] = *reinterpret_cast<const bf16x8*>(xp[p] + k + 128 * u);                             \
       _Pragma("unroll") for (int rt = 0; rt < RT; ++rt)                                               \
         _Pragma("unroll") for (int p = 0; p < 4; ++p)                                                 \
-          s_[u][rt][p] = *reinterpret_cast<const bf16x8*>(sp[rt][p] + k + 128 * u);                   \
+          s_[u][rt][p] = *reinterpret_cast<const bf16x8*>(sp[rt][p] + (k + 128 * u) * s_step);          \
     }                                                                                                 \
     _Pragma("unroll") for (int u = 0; u < U_; ++u) {                                                  \
       bf16x8 fx_[4], fs_[4];                                                                          \
       FLEXCO_TURN(x_[u], XP, fx_)                                                                     \
       _Pragma("unroll") for (int rt = 0; rt < RT; ++rt) {                                             \
-        FLEXCO_TURN(s_[u][rt], 4, fs_)                                                                \
+        if (KM) FLEXCO_TURN_KM(s_[u][rt], fs_) else FLEXCO_TURN(s_[u][rt], 4, fs_)                    \
         _Pragma("unroll") for (int s = 0; s < 4; ++s)                                                 \
-          acc[rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fx_[s], rt * 16 + m < a.r ? fs_[s] : zero, acc[rt], 0, 0, 0); \
+          acc[rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fx_[s], KM || rt * 16 + m < a.r ? fs_[s] : zero, acc[rt], 0, 0, 0); \
       }                                                                                               \
     }                                                                                                 \
     k += 128 * U_;                                                                                    \
@@ -170,14 +194,6 @@ __global__ __launch_bounds__(256) void relu_bwd_mask_kernel(const float* __restr
   const float v = u[i] > 0.f ? t[i] : 0.f;
   t[i] = v;
   if (t_ext) t_ext[i] = (bf16_t)v;
-}
-
-// Bt[j][o] = B[o][j]
-__global__ __launch_bounds__(256) void lora_transpose_kernel(LoraTransposeArgs a) {
-  const int z = blockIdx.z;
-  const int o = blockIdx.x * 256 + threadIdx.x;
-  if (o >= a.out[z]) return;
-  for (int j = 0; j < a.r; ++j) a.Bt[z][(size_t)j * a.out[z] + o] = a.B[z][(size_t)o * a.r + j];
 }
 
 // G(i, j) += scale * sum_m X[m, i] U[m, j],  G element (i, j) at G[i * g_i + j * g_j]
@@ -252,16 +268,6 @@ __global__ __launch_bounds__(256) void lora_outer_mfma_path_kernel(LoraOuterArgs
 //     comes from two transposing reads (ds_read_b64_tr_b16).  32-byte column pairs are XOR-swizzled
 //     with row % 4 so that the four rows of a read sit on different banks.
 //   * the four wavefronts' sums are added in wavefront order through LDS.
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-#define FLEXCO_GP(p) ((const __attribute__((address_space(1))) void*)(p))
-#define FLEXCO_LP(p) ((__attribute__((address_space(3))) void*)(p))
-#define FLEXCO_LDS __attribute__((address_space(3)))
-__device__ inline bf16x8 tr_pair(const bf16_t* a, const bf16_t* b) {
-  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((FLEXCO_LDS s16x4*)a);
-  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((FLEXCO_LDS s16x4*)b);
-  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-}
-
 template <int RT>   // rank tiles of 16
 __global__ __launch_bounds__(256) void lora_outer_mfma_kernel(LoraOuterArgs a) {
   constexpr int UP = 264;                                                   // row pitch of U^T in elements
@@ -405,6 +411,7 @@ int32_t launch_lora_shrink_mfma(const LoraShrinkArgs& a_in, int n_mats, hipStrea
   if (a.rows == 0 || n_mats == 0) return FLEXCO_OK;
   for (int z = 0; z < n_mats; ++z)
     if (a.K[z] % 128 != 0) return fail(FLEXCO_ESHAPE, "LoRA shrink: K = %d is not a multiple of 128", a.K[z]);
+  if (a.s_kmajor && a.r % 16 != 0) return fail(FLEXCO_ESHAPE, "LoRA shrink: rank %d is not a multiple of 16", a.r);
   // Long contractions of one width, with scratch at hand, are cut over several blocks per row tile where the low-rank operand is
   // over half a MB (rank tiles x K > 16384; a block takes in 64 bytes a cycle): 256 KB to a block, in whole groups of 128 columns.  The
   // launch that adds the partial products costs 5 us.  (48 x 13824, four products of rank 16 10.3 in one launch, 7.2 + 4.7 in two
@@ -422,8 +429,13 @@ int32_t launch_lora_shrink_mfma(const LoraShrinkArgs& a_in, int n_mats, hipStrea
   const dim3 grid((a.rows + rb - 1) / rb, n_mats, a.ksplit), block(512);
 #define FLEXCO_SHRINK(RT_)                                                                            \
   {                                                                                                   \
-    if (rb == 8) hipLaunchKernelGGL((lora_shrink_kernel<RT_, 8>), grid, block, 0, s, a);              \
-    else hipLaunchKernelGGL((lora_shrink_kernel<RT_, 16>), grid, block, 0, s, a);                     \
+    if (a.s_kmajor) {                                                                                 \
+      if (rb == 8) hipLaunchKernelGGL((lora_shrink_kernel<RT_, 8, true>), grid, block, 0, s, a);      \
+      else hipLaunchKernelGGL((lora_shrink_kernel<RT_, 16, true>), grid, block, 0, s, a);             \
+    } else {                                                                                          \
+      if (rb == 8) hipLaunchKernelGGL((lora_shrink_kernel<RT_, 8, false>), grid, block, 0, s, a);     \
+      else hipLaunchKernelGGL((lora_shrink_kernel<RT_, 16, false>), grid, block, 0, s, a);            \
+    }                                                                                                 \
   }
   switch (rt) {
     case 1: FLEXCO_SHRINK(1) break;
@@ -442,14 +454,6 @@ int32_t launch_relu_bwd_mask(const float* u, float* t, void* t_ext, size_t count
   if (count == 0) return FLEXCO_OK;
   hipLaunchKernelGGL(relu_bwd_mask_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, s, u, t, (bf16_t*)t_ext, count);
   return post("relu_bwd_mask");
-}
-
-int32_t launch_lora_transpose(const LoraTransposeArgs& a, int n_mats, hipStream_t s) {
-  int mx = 0;
-  for (int z = 0; z < n_mats; ++z) mx = a.out[z] > mx ? a.out[z] : mx;
-  if (mx == 0) return FLEXCO_OK;
-  hipLaunchKernelGGL(lora_transpose_kernel, dim3((mx + 255) / 256, 1, n_mats), dim3(256), 0, s, a);
-  return post("lora_transpose");
 }
 
 int32_t launch_lora_outer_batch(const LoraOuterArgs& a, hipStream_t s) {
