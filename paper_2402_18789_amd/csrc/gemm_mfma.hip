@@ -196,7 +196,7 @@ __device__ __forceinline__ void store_tile(const f32x4 (&acc)[MT][NT], float* st
   }
 }
 
-template <int BM, int BN, bool TRANS, bool GLU = false, int NSTAGES = 0>
+template <int BM, int BN, bool TRANS, bool GLU = false, int NSTAGES = 0, bool SPREAD = false>
 __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W,
                                                         bf16_t* __restrict__ C, const bf16_t* __restrict__ bias,
                                                         const bf16_t* __restrict__ res, int M, int N, int K,
@@ -307,8 +307,17 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
   const size_t wstep = TRANS ? (size_t)BK * ldw * 2 : (size_t)BK * 2;
 
   // stage index past the end: clamped, the loads repeat the last stage into a free buffer
-#define GEMM_SRC_A(s_) __builtin_amdgcn_make_buffer_rsrc((void*)(pa + (size_t)min((s_), ns - 1) * (BK * 2)), 0, -1, 0x00027000)
-#define GEMM_SRC_W(s_) __builtin_amdgcn_make_buffer_rsrc((void*)(pw + (size_t)min((s_), ns - 1) * wstep), 0, -1, 0x00027000)
+  // SPREAD: a block walks its stages from one of its own on, round to the one before.  Where rows of W lie a multiple of 4 KB apart, the
+  // 128 bytes that all rows' stage s takes sit on the same few memory channels, and blocks that start together stay together; column
+  // tiles spread over the stages use all of them.  (Products of one row tile only: others' weights are shared
+  // between row tiles.)
+  const int first = SPREAD ? (int)((long)tn * ns / tiles_n) : 0;
+  auto stage_at = [&](int s) {
+    const int t = min(s, ns - 1) + first;
+    return (size_t)(SPREAD && t >= ns ? t - ns : t);
+  };
+#define GEMM_SRC_A(s_) __builtin_amdgcn_make_buffer_rsrc((void*)(pa + stage_at(s_) * (BK * 2)), 0, -1, 0x00027000)
+#define GEMM_SRC_W(s_) __builtin_amdgcn_make_buffer_rsrc((void*)(pw + stage_at(s_) * wstep), 0, -1, 0x00027000)
   // The 64-row tile's weights are read by one block and once: non-temporal loads (cache policy bit 1), which leave the
   // caches to what is read again.  8 x 28672 x 4096 with weights in no cache 50.6 -> 47.2 us (5.0 TB/s), calls back to
   // back, a layer of 48 tokens at the 14B shape 253 -> 229, of 8 at the 8B shape 135 -> 128 (among other work 257 -> 252 and 131 -> 122).  Tiles whose weights meet several row tiles lose
@@ -685,6 +694,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_quad_kernel(const bf16_t* __res
   const char* const pw = (const char*)(GLU ? W + (size_t)ac0 * ldw + kbeg : (TRANS ? W + (size_t)kbeg * ldw + n0 : W + (size_t)n0 * ldw + kbeg));
   const size_t wstep = TRANS ? (size_t)BK * ldw * 2 : (size_t)BK * 2;
   // (a stage past the end: clamped, the loads repeat the last stage into a free buffer)
+  auto stage_at = [&](int s) { return (size_t)min(s, ns - 1); };
 #define Q_LOAD(buf_, src_, off_, p_) \
   __builtin_amdgcn_raw_ptr_buffer_load_lds(src_, FLEXCO_LP(buf_ + ((p_) * 4 + wave) * 512), 16, off_[p_], 0, 0, 0);
 #define Q_LOAD_A(buf_, h_, s_) \
@@ -844,7 +854,7 @@ __global__ __launch_bounds__(256) void gemm_splitk_reduce_kernel(const float* __
   *reinterpret_cast<bf16x4*>(C + (size_t)row * ldc + col) = o;
 }
 
-template <int BM, int BN, bool TRANS, bool GLU = false, int NSTAGES = 0>
+template <int BM, int BN, bool TRANS, bool GLU = false, int NSTAGES = 0, bool SPREAD = false>
 int32_t launch_cfg(const void* A, const void* W, void* C, const void* bias, const void* res, int M, int N, int K,
                    size_t lda, size_t ldw, size_t ldc, size_t ldr, const GemmExt& ext, hipStream_t s,
                    int timer_id, float* part = nullptr, int splits = 1, bool first_of_call = true,
@@ -855,7 +865,7 @@ int32_t launch_cfg(const void* A, const void* W, void* C, const void* bias, cons
   void (*kern)(const bf16_t*, const bf16_t*, bf16_t*, const bf16_t*, const bf16_t*, int, int, int, size_t, size_t, size_t, size_t,
                int, int, GemmExt, float*, GemmGlu);
   if constexpr (QUAD) kern = gemm_bf16_quad_kernel<BN, TRANS, GLU>;
-  else kern = gemm_bf16_kernel<BM, BN, TRANS, GLU, NSTAGES>;
+  else kern = gemm_bf16_kernel<BM, BN, TRANS, GLU, NSTAGES, SPREAD>;
   GemmGlu glu;
   if (glu_in) glu = *glu_in; else memset(&glu, 0, sizeof(glu));
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
@@ -998,6 +1008,10 @@ static int thin_splits(int M, int N, int K, size_t part_elems) {
   if (sp > 1) sp = (int)std::min<size_t>(sp, part_elems / ((size_t)M * N));
   return std::max(sp, 1);
 }
+// Whether the column tiles of a product of one row tile start at stages of their own: rows of W a multiple of 4 KB apart.  A layer at the
+// 8B shape (8 and 28 KB), us: 1 token 116 -> 106, 8 tokens 123 -> 114, 30 tokens 143 -> 130, 70 tokens 185 -> 177, 128 tokens
+// 220 -> 210, 160 and 250 tokens (two row tiles) level; at the 14B and 32B shapes (10, 27 and 54 KB) 0.4 % slower with it.
+static bool spread_stages(int M, size_t ldw) { return M <= 128 && ldw % 2048 == 0; }
 
 // Ranges of K in whole stages, equal to within one, to run a product on 256 x 256 tiles with, or 0: the launch plan
 // below is as good.  For products whose 256 x 256 tiles leave CUs idle (or whose last round does), at the price of partial
@@ -1146,14 +1160,14 @@ int32_t launch_gemm_mfma(const void* A, const void* W, void* C, const void* bias
     const int sp = pl.step[0].splits;
     const bool leave = splits_out && sp > 1 && !bias && !residual;
     if (leave) *splits_out = sp;
-    return launch_cfg<THIN_ROWS, 128, false, false, 6>(A, W, C, bias, residual, M, N, K, lda, ldw, ldc, ldr, ext, s, timer_id, part, sp,
-                                                       true, nullptr, leave);
+    const auto thin = spread_stages(M, ldw) ? launch_cfg<THIN_ROWS, 128, false, false, 6, true> : launch_cfg<THIN_ROWS, 128, false, false, 6>;
+    return thin(A, W, C, bias, residual, M, N, K, lda, ldw, ldc, ldr, ext, s, timer_id, part, sp, true, nullptr, leave);
   }
   if (pl.step[0].splits > 1) {
     const bool leave = splits_out && !bias && !residual;
     if (leave) *splits_out = pl.step[0].splits;
-    return launch_cfg<128, 128, false>(A, W, C, bias, residual, M, N, K, lda, ldw, ldc, ldr, ext, s, timer_id, part,
-                                       pl.step[0].splits, true, nullptr, leave);
+    const auto cut = spread_stages(M, ldw) ? launch_cfg<128, 128, false, false, 0, true> : launch_cfg<128, 128, false>;
+    return cut(A, W, C, bias, residual, M, N, K, lda, ldw, ldc, ldr, ext, s, timer_id, part, pl.step[0].splits, true, nullptr, leave);
   }
   int c0 = 0;
   for (int i = 0; i < pl.n; ++i) {
@@ -1198,9 +1212,10 @@ int32_t launch_gemm_glu_mfma(const void* A, const void* W, void* act, int M, int
   glu.save_row0 = save_row0; glu.save_rows = save_gate ? save_rows : 0; glu.ld_save = ld_save;
   const int N = 2 * F;
   const GemmLaunchPlan pl = plan_gemm_mfma(M, N, K, false, 0);
-  if (pl.step[0].bm == THIN_ROWS)
-    return launch_cfg<THIN_ROWS, 128, false, true, 6>(A, W, act, nullptr, nullptr, M, N, K, lda, ldw, ld_act, 0, ext, s, timer_id,
-                                                      nullptr, 1, true, &glu);
+  if (pl.step[0].bm == THIN_ROWS) {
+    const auto thin = spread_stages(M, ldw) ? launch_cfg<THIN_ROWS, 128, false, true, 6, true> : launch_cfg<THIN_ROWS, 128, false, true, 6>;
+    return thin(A, W, act, nullptr, nullptr, M, N, K, lda, ldw, ld_act, 0, ext, s, timer_id, nullptr, 1, true, &glu, false);
+  }
   int c0 = 0;                                       // interleaved columns done = 2 x the act columns done
   for (int i = 0; i < pl.n; ++i) {
     const GemmLaunchStep& st = pl.step[i];
@@ -1219,6 +1234,9 @@ int32_t launch_gemm_glu_mfma(const void* A, const void* W, void* act, int M, int
     else if (st.stages == 2)
       rc = launch_cfg<128, 128, false, true, 2>(A, W, act, nullptr, nullptr, M, st.cols, K, lda, ldw, ld_act, 0, ext, s, timer_id,
                                                 nullptr, 1, first, &glu);
+    else if (spread_stages(M, ldw))
+      rc = launch_cfg<128, 128, false, true, 0, true>(A, W, act, nullptr, nullptr, M, st.cols, K, lda, ldw, ld_act, 0, ext, s, timer_id,
+                                                      nullptr, 1, first, &glu);
     else
       rc = launch_cfg<128, 128, false, true>(A, W, act, nullptr, nullptr, M, st.cols, K, lda, ldw, ld_act, 0, ext, s, timer_id,
                                              nullptr, 1, first, &glu);

@@ -52,6 +52,14 @@ def test_forward_tiles_of_few_rows(M, N, K):
     run_gemm(M, N, K, 0)
 
 
+# rows of W a multiple of 4 KB apart: the column tiles start at stages of their own
+@pytest.mark.parametrize("K", [2048, 6144])
+@pytest.mark.parametrize("M,N", [(1, 8), (63, 136), (64, 6152), (65, 136), (128, 6152)])
+def test_forward_tiles_of_few_rows_from_their_own_stage(M, N, K):
+    print(f"forward, spread stages, M={M} N={N} K={K}", flush=True)
+    run_gemm(M, N, K, 0)
+
+
 @pytest.mark.parametrize("K", [64, 128, 192, 448])
 @pytest.mark.parametrize("M,N", [(1030, 13832), (130, 136), (64, 40)])
 def test_input_gradient_tiles_128(M, N, K):
