@@ -268,10 +268,10 @@ FwdWs carve_fwd(const flexco_layer_cfg& c, int T, int n_parts, void* base) {
   const size_t qd = (size_t)c.n_q_heads * c.head_dim, qkvd = qd + 2 * (size_t)c.n_kv_heads * c.head_dim;
   Carver cv{(char*)base};
   FwdWs w;
-  w.h = cv.take(e * T * c.hidden);
+  w.x2 = cv.take(e * T * c.hidden);
+  w.h = cv.take(e * T * c.hidden);        // (h .. gu side by side: the down product's partial sums may take them all)
   w.qkv = cv.take(e * T * qkvd);
   w.attn = cv.take(e * T * qd);
-  w.x2 = cv.take(e * T * c.hidden);
   w.gu = cv.take(e * T * 2 * c.ffn);
   w.act = cv.take(e * T * c.ffn);
   w.lse = (float*)cv.take(sizeof(float) * T * c.n_q_heads);
@@ -1015,16 +1015,18 @@ static int32_t layer_forward_impl(const flexco_layer_cfg* cfg, const flexco_base
   const size_t e = esize(dt);
   const int qd = c.n_q_heads * c.head_dim, kd = c.n_kv_heads * c.head_dim, qkvd = qd + 2 * kd;
   // Batches of more tokens have no split-K scratch of their own: the [T, 2F] buffer serves while it holds nothing, i.e.
-  // before the gate/up projection and after SwiGLU.
+  // before the gate/up projection and after SwiGLU.  At the down projection nothing reads h, qkv and attn any more either, which lie in
+  // front of it: more ranges of K fit.  (The [T, 2F] buffer alone / all of them, ranges and us of a layer: 500 tokens at the 8B shape 3 / 5,
+  // 309 / 287; 1024 tokens 3 / 4, 885 / 881; 600 tokens at the 14B shape none / 4, 467 / 453; 1024 tokens 2 / 3, 582 / 561.)
   const bool gu_part = dt == FLEXCO_BF16 && T > FWD_SPLITK_MAX_T;
-  auto lend_gu = [&](bool free) {
+  auto lend_gu = [&](bool free, void* from) {
     if (!gu_part) return;
-    k.gemm_part = free ? (float*)k.gu : nullptr;
-    k.gemm_part_elems = free ? (size_t)T * F : 0;
+    k.gemm_part = free ? (float*)from : nullptr;
+    k.gemm_part_elems = free ? (size_t)((char*)k.gu + (size_t)T * F * sizeof(float) - (char*)from) / sizeof(float) : 0;
   };
 
   // attention side
-  lend_gu(true);
+  lend_gu(true, k.gu);
   SplitSums qkv_sums{nullptr, 1}, o_sums{nullptr, 1};
   // (the finetune window's rows of x, x2, the attention output and its log-sum-exp - what graph pruning keeps,
   // Alg. 1 - are written to the sequence's state by the kernels that read or produce them anyway)
@@ -1066,7 +1068,7 @@ static int32_t layer_forward_impl(const flexco_layer_cfg* cfg, const flexco_base
   else
     EW(launch_rmsnorm(k.x2, w->g2, k.h, T, H, c.rms_eps, dt, s, keep_x2, m.ft_tok0, m.n_ft));
   GluOut glu{k.act, (size_t)F, false};
-  lend_gu(false);
+  lend_gu(false, nullptr);
   {
     const int tg[2] = {FLEXCO_T_GATE, FLEXCO_T_UP}, c0[2] = {0, F};
     FLEXCO_TRY(forward_projection(c, ad, m, k.h, H, w->wgu, nullptr, nullptr, 0, k.gu, 2 * F, tg, c0, 2, k, ft, s, &glu));
@@ -1075,7 +1077,7 @@ static int32_t layer_forward_impl(const flexco_layer_cfg* cfg, const flexco_base
   if (!glu.done)
     EW(launch_swiglu(k.gu, k.act, T, F, dt, s, ft ? (void*)boff(ft->saved_gate, p0 * F, e) : nullptr,
                      ft ? (void*)boff(ft->saved_up, p0 * F, e) : nullptr, m.ft_tok0, ft ? m.n_ft : 0));
-  lend_gu(true);
+  lend_gu(true, k.h);
   if (ia3 && m.n_lora > 0) {   // the SwiGLU product of the adapter's rows
     Ia3ScaleArgs sa;
     memset(&sa, 0, sizeof(sa));

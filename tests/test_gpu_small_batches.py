@@ -64,6 +64,19 @@ def test_layer_partial_sums_in_the_lent_buffer(cfg, adapter):
     run_layer_case(cfg, b, ft_window=141, prefill_chunk=131, bwd_windows=[141, 141], seed=29)
 
 
+# the down product's partial sums take h, qkv and attn in front of that buffer as well
+@pytest.mark.parametrize("adapter", [True, False])
+@pytest.mark.parametrize("ffn", [5632, 6016])
+def test_layer_down_partial_sums_past_the_lent_buffer(ffn, adapter):
+    cfg = WIDE.with_(name="down_cut", ffn=ffn, lora_targets=("q", "v", "o", "gate", "down") if adapter else ())
+    b = gen.batch_scaled(29, 5, 3, 90, [(0, 131, 262)], [(0, 141, 282)])
+    T = b.n_tokens
+    ranges = [B.flexco_gemm_k_ranges(T, cfg.hidden, ffn, 0, T * w) for w in (ffn, ffn + cfg.hidden // 2 + cfg.q_dim + cfg.kv_dim)]
+    print(f"layer of {T} tokens, ffn {ffn}, ranges of the down product {ranges}, adapter {adapter}", flush=True)
+    assert T == 277 and ranges[1] > max(1, ranges[0])
+    run_layer_case(cfg, b, ft_window=141, prefill_chunk=131, bwd_windows=[141, 141], seed=29)
+
+
 # (split: pages of 16 keys) contexts of one split, then of up to six, then of 1, 2, 8, 9 and 12
 @pytest.mark.parametrize("split", [24, 4, 2])
 def test_attention_merge_of_many_splits(split):
