@@ -1234,13 +1234,12 @@ static int32_t layer_backward_impl(const flexco_layer_cfg* cfg, const flexco_bas
   // ---- MLP side: down projection, SwiGLU, gate/up projections, second norm -------------
   // (where an input-gradient product was cut over K, the kernel that reads it next adds the partial sums itself)
   int sp_dact = 1, sp_dh2 = 1, sp_dh1 = 1;
-  FLEXCO_TRY(backward_projection(c, lora, n, dY, H, w->wd, k.dact, grp[0], k, outer, s, ia3 ? nullptr : &sp_dact));
-  if (ia3) {   // dl_ff += colsum(dact (.) act0) with the rematerialised SwiGLU product; dact <- dact (.) l_ff
-    EW(launch_swiglu_remat(gate_w, up_w, k.act, n, F, dt, s));
-    EW(launch_ia3_colgrad(k.dact, F, k.act, F, ia3->l_ff, k.colsum_part, ia3->dl_ff, n, F, dt, s));
-  }
-  EW(launch_swiglu_bwd(gate_w, up_w, k.dact, k.dgu, n, F, dt, s, act_late ? k.act : nullptr,
-                       sp_dact > 1 ? k.gemm_part : nullptr, sp_dact));
+  FLEXCO_TRY(backward_projection(c, lora, n, dY, H, w->wd, k.dact, grp[0], k, outer, s, &sp_dact));
+  const float* const dact_part = sp_dact > 1 ? k.gemm_part : nullptr;
+  if (ia3)     // dl_ff += colsum(dact (.) act0) with the rematerialised SwiGLU product; dact (.) l_ff goes on
+    EW(launch_ia3_swiglu_bwd(gate_w, up_w, k.dact, ia3->l_ff, k.dgu, k.colsum_part, ia3->dl_ff, n, F, dt, s, dact_part, sp_dact));
+  else
+    EW(launch_swiglu_bwd(gate_w, up_w, k.dact, k.dgu, n, F, dt, s, act_late ? k.act : nullptr, dact_part, sp_dact));
   FLEXCO_TRY(backward_projection(c, lora, n, k.dgu, 2 * F, w->wgu, k.dh, grp[1], k, outer, s, &sp_dh2));
   EW(launch_rmsnorm_bwd(x2_w, w->g2, k.dh, dY, k.dx2, n, H, c.rms_eps, dt, s, hn2_late ? k.hn2 : nullptr,
                         sp_dh2 > 1 ? k.gemm_part : nullptr, sp_dh2));
@@ -1253,10 +1252,17 @@ static int32_t layer_backward_impl(const flexco_layer_cfg* cfg, const flexco_bas
   if (dX || qkv_lora || ia3) {
     EW(launch_rope_bwd_pack(c, k.dq, ft->dk_accum + w0 * kd, ft->dv_accum + w0 * kd, k.dqkv, win_start, n, s));
     if (ia3) {   // the k and v column ranges of the packed rows: dl += colsum(d (.) unscaled rows), d <- d (.) l
-      EW(launch_ia3_colgrad(boff(k.dqkv, qd, e), qkvd, boff(ft->saved_k0, w0 * kd, e), kd, ia3->l_k, k.colsum_part,
-                            ia3->dl_k, n, kd, dt, s));
-      EW(launch_ia3_colgrad(boff(k.dqkv, qd + kd, e), qkvd, boff(ft->saved_v0, w0 * kd, e), kd, ia3->l_v, k.colsum_part,
-                            ia3->dl_v, n, kd, dt, s));
+      Ia3ColgradArgs ca[2] = {};
+      const int together = 2 * kd <= std::max(F, kd) ? 2 : 1;      // (what the scratch holds)
+      for (int i = 0; i < 2; ++i) {
+        Ia3ColgradArgs& a = ca[together == 2 ? 0 : i];
+        const int z = together == 2 ? i : 0;
+        a.G[z] = boff(k.dqkv, qd + i * kd, e); a.ldg = qkvd; a.ldx = kd;
+        a.X[z] = boff(i ? ft->saved_v0 : ft->saved_k0, w0 * kd, e);
+        a.l[z] = i ? ia3->l_v : ia3->l_k;
+        a.dl[z] = i ? ia3->dl_v : ia3->dl_k;
+      }
+      for (int i = 0; i < 2 / together; ++i) EW(launch_ia3_colgrad(ca[i], together, k.colsum_part, n, kd, dt, s));
     }
     if (dX || qkv_lora)
       FLEXCO_TRY(backward_projection(c, lora, n, k.dqkv, qkvd, w->wqkv, dX ? k.dh : nullptr, grp[3], k, outer, s,

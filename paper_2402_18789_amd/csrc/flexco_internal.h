@@ -160,9 +160,18 @@ struct Ia3ScaleArgs {
 };
 int32_t launch_ia3_scale_rows(void* buf, size_t ld, const int32_t* tok, int n_tok, const Ia3ScaleArgs& a, int dtype,
                               hipStream_t s);
-// dl[c] += sum_r G[r, c] X[r, c];  G[r, c] *= l[c];  part: float [ceil(n / 8)][C] scratch
-int32_t launch_ia3_colgrad(void* G, size_t ldg, const void* X, size_t ldx, const void* l, float* part, float* dl, int n,
-                           int C, int dtype, hipStream_t s);
+// per segment: dl[c] += sum_r G[r, c] X[r, c];  G[r, c] *= l[c];  part: float [segments][ceil(n / 8)][C] scratch
+struct Ia3ColgradArgs {
+  void* G[2]; size_t ldg;
+  const void* X[2]; size_t ldx;
+  const void* l[2];
+  float* dl[2];
+};
+int32_t launch_ia3_colgrad(const Ia3ColgradArgs& a, int n_seg, float* part, int n, int C, int dtype, hipStream_t s);
+// dl[c] += sum_r dact[r, c] act[r, c] with act = silu(gate) (.) up, dgu = the SwiGLU backward of dact (.) l;  part: [ceil(n / 8)][F]
+// scratch;  dact_part, splits: as launch_swiglu_bwd
+int32_t launch_ia3_swiglu_bwd(const void* gate, const void* up, const void* dact, const void* l, void* dgu, float* part, float* dl,
+                              int n, int F, int dtype, hipStream_t s, const float* dact_part, int splits);
 int32_t launch_copy_rows(const void* src, size_t ld_src_bytes, void* dst, size_t ld_dst_bytes, int n_rows,
                          size_t width_bytes, hipStream_t s);
 

@@ -711,10 +711,12 @@ __global__ __launch_bounds__(256) void ia3_scale_rows_kernel(T* __restrict__ buf
 // (= dX) in place.  The second kernel adds the chunks in order into dl: no atomics, a fixed order.
 constexpr int IA3_CHUNK = 8;
 template <typename T, bool VEC>
-__global__ __launch_bounds__(256) void ia3_colgrad_kernel(T* __restrict__ G, size_t ldg, const T* __restrict__ X,
-                                                          size_t ldx, const T* __restrict__ l,
-                                                          float* __restrict__ part, int n, int C) {
+__global__ __launch_bounds__(256) void ia3_colgrad_kernel(Ia3ColgradArgs a, float* __restrict__ part, int n, int C) {
   constexpr int N = VEC ? Vec<T>::N : 1;
+  T* __restrict__ const G = (T*)a.G[blockIdx.z];
+  const T* __restrict__ const X = (const T*)a.X[blockIdx.z];
+  const T* __restrict__ const l = (const T*)a.l[blockIdx.z];
+  const size_t ldg = a.ldg, ldx = a.ldx;
   const int c = (blockIdx.x * 256 + threadIdx.x) * N;
   if (c >= C) return;
   const int r0 = blockIdx.y * IA3_CHUNK;
@@ -736,13 +738,15 @@ __global__ __launch_bounds__(256) void ia3_colgrad_kernel(T* __restrict__ G, siz
     if (VEC) Vec<T>::store(G + (size_t)(r0 + i) * ldg + c, g[i]); else st(G + (size_t)(r0 + i) * ldg + c, g[i][0]);
   }
 #pragma unroll
-  for (int j = 0; j < N; ++j) part[(size_t)blockIdx.y * C + c + j] = acc[j];
+  for (int j = 0; j < N; ++j) part[((size_t)blockIdx.z * gridDim.y + blockIdx.y) * C + c + j] = acc[j];
 }
 
 __global__ __launch_bounds__(256) void ia3_colgrad_finalize_kernel(const float* __restrict__ part, int chunks, int C,
-                                                                   float* __restrict__ dl) {
+                                                                   float* __restrict__ dl0, float* __restrict__ dl1) {
   const int c = blockIdx.x * 256 + threadIdx.x;
   if (c >= C) return;
+  float* const dl = blockIdx.y ? dl1 : dl0;
+  part += (size_t)blockIdx.y * chunks * C;
   float acc = 0.f;
   for (int k0 = 0; k0 < chunks; k0 += 8) {   // eight loads in flight, added in chunk order
     float v[8];
@@ -823,6 +827,100 @@ __global__ __launch_bounds__(256) void swiglu_remat_kernel(const T* __restrict__
 #pragma unroll
   for (int j = 0; j < N; ++j) g[j] = g[j] / (1.0f + __expf(-g[j])) * u[j];
   if (VEC) Vec<T>::store(act + row * F + i, g); else st(act + row * F + i, g[0]);
+}
+
+// N = 4 consecutive elements with one access, or one element
+template <int N>
+__device__ inline void load_run(const float* p, float (&v)[N]) {
+  if constexpr (N == 4) { const f32x4 t = *reinterpret_cast<const f32x4*>(p); v[0] = t[0]; v[1] = t[1]; v[2] = t[2]; v[3] = t[3]; }
+  else v[0] = *p;
+}
+template <int N>
+__device__ inline void load_run(const bf16_t* p, float (&v)[N]) {
+  if constexpr (N == 4) { const bf16x4 t = *reinterpret_cast<const bf16x4*>(p); v[0] = (float)t[0]; v[1] = (float)t[1]; v[2] = (float)t[2]; v[3] = (float)t[3]; }
+  else v[0] = (float)*p;
+}
+template <int N, typename T>
+__device__ inline void store_run(T* p, const float (&v)[N]) {
+  typedef T run_t __attribute__((ext_vector_type(4)));
+  if constexpr (N == 4) *reinterpret_cast<run_t*>(p) = run_t{(T)v[0], (T)v[1], (T)v[2], (T)v[3]};
+  else *p = (T)v[0];
+}
+
+// The SwiGLU backward of a window with an (IA)^3 vector on the product, in one pass over gate, up and dact: per chunk of IA3_CHUNK
+// rows and per column, part[chunk][c] = sum_r dact[r, c] act[r, c] with the rematerialised act, then dact <- dact (.) l and dgu as
+// swiglu_bwd_kernel writes it; act and dact are rounded to the storage type where the separate kernels stored them, so the results
+// are the same bits.  Bound by its bytes; four
+// elements per thread, so that few rows give blocks enough, and four rows' loads in flight together.  205 x 14336 in an (IA)^3 layer: the sum of the
+// product's partial sums, the rematerialisation, the column sums and the backward 9.0 + 5.6 + 6.2 + 6.2 us -> 16.5.
+template <typename T, bool VEC>
+__global__ __launch_bounds__(256) void ia3_swiglu_bwd_kernel(const T* __restrict__ gate, const T* __restrict__ up,
+                                                             const T* __restrict__ dact, const T* __restrict__ l,
+                                                             T* __restrict__ dgu, float* __restrict__ part, int n, int F,
+                                                             const float* __restrict__ dact_part, int splits, size_t stride) {
+  constexpr int N = VEC ? 4 : 1, R = 4, U = 4;
+  static_assert(IA3_CHUNK % R == 0, "whole groups of rows");
+  const int c = (blockIdx.x * 256 + threadIdx.x) * N;
+  if (c >= F) return;
+  const int r0 = blockIdx.y * IA3_CHUNK;
+  float lv[N], acc[N];
+  load_run<N>(l + c, lv);
+#pragma unroll
+  for (int j = 0; j < N; ++j) acc[j] = 0.f;
+  for (int i0 = 0; i0 < IA3_CHUNK && r0 + i0 < n; i0 += R) {
+    float g[R][N], u[R][N], da[R][N];
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const size_t o = (size_t)min(r0 + i0 + i, n - 1) * F + c;
+      load_run<N>(gate + o, g[i]);
+      load_run<N>(up + o, u[i]);
+      if (!dact_part) load_run<N>(dact + o, da[i]);
+    }
+    if (dact_part) {             // added in split order and rounded as load_split_sum does, U splits of all rows on their way at once
+#pragma unroll
+      for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int j = 0; j < N; ++j) da[i][j] = 0.f;
+      for (int sp = 0; sp < splits; sp += U) {
+        float t[U][R][N];
+#pragma unroll
+        for (int q = 0; q < U; ++q)
+#pragma unroll
+          for (int i = 0; i < R; ++i)
+            load_run<N>(dact_part + min(sp + q, splits - 1) * stride + (size_t)min(r0 + i0 + i, n - 1) * F + c, t[q][i]);
+#pragma unroll
+        for (int q = 0; q < U; ++q)
+          if (sp + q < splits)
+#pragma unroll
+            for (int i = 0; i < R; ++i)
+#pragma unroll
+              for (int j = 0; j < N; ++j) da[i][j] += t[q][i][j];
+      }
+#pragma unroll
+      for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int j = 0; j < N; ++j) da[i][j] = (float)(T)da[i][j];
+    }
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const size_t row = r0 + i0 + i;
+      if ((int)row >= n) break;
+      float dg[N], du[N];
+#pragma unroll
+      for (int j = 0; j < N; ++j) {
+        const float gj = g[i][j], uj = u[i][j];
+        acc[j] += da[i][j] * (float)(T)(gj / (1.0f + __expf(-gj)) * uj);
+        const float d = (float)(T)(da[i][j] * lv[j]);
+        const float sg = 1.0f / (1.0f + __expf(-gj));
+        dg[j] = d * uj * (sg + gj * sg * (1.0f - sg));
+        du[j] = d * gj * sg;
+      }
+      store_run<N>(dgu + row * 2 * F + c, dg);
+      store_run<N>(dgu + row * 2 * F + F + c, du);
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < N; ++j) part[(size_t)blockIdx.y * F + c + j] = acc[j];
 }
 
 // --------------------------------------------------------------------------------------
@@ -1250,17 +1348,29 @@ int32_t launch_ia3_scale_rows(void* buf, size_t ld, const int32_t* tok, int n_to
   return post_launch("ia3_scale_rows");
 }
 
-int32_t launch_ia3_colgrad(void* G, size_t ldg, const void* X, size_t ldx, const void* l, float* part, float* dl, int n,
-                           int C, int dtype, hipStream_t s) {
+int32_t launch_ia3_colgrad(const Ia3ColgradArgs& a, int n_seg, float* part, int n, int C, int dtype, hipStream_t s) {
   if (n == 0 || C == 0) return FLEXCO_OK;
   const int chunks = (n + IA3_CHUNK - 1) / IA3_CHUNK;
   const int vn = dtype == FLEXCO_BF16 ? 8 : 4;
-  const bool vec = C % vn == 0 && ldg % vn == 0 && ldx % vn == 0 && aligned16(G) && aligned16(X) && aligned16(l);
+  bool vec = C % vn == 0 && a.ldg % vn == 0 && a.ldx % vn == 0;
+  for (int i = 0; i < n_seg; ++i) vec = vec && aligned16(a.G[i]) && aligned16(a.X[i]) && aligned16(a.l[i]);
   const int per = 256 * (vec ? vn : 1);
-  DISPATCH_TV(dtype, vec, hipLaunchKernelGGL((ia3_colgrad_kernel<T, VEC>), dim3((C + per - 1) / per, chunks), dim3(256), 0,
-                                             s, (T*)G, ldg, (const T*)X, ldx, (const T*)l, part, n, C));
-  hipLaunchKernelGGL(ia3_colgrad_finalize_kernel, dim3((C + 255) / 256), dim3(256), 0, s, part, chunks, C, dl);
+  DISPATCH_TV(dtype, vec, hipLaunchKernelGGL((ia3_colgrad_kernel<T, VEC>), dim3((C + per - 1) / per, chunks, n_seg), dim3(256), 0,
+                                             s, a, part, n, C));
+  hipLaunchKernelGGL(ia3_colgrad_finalize_kernel, dim3((C + 255) / 256, n_seg), dim3(256), 0, s, part, chunks, C, a.dl[0], a.dl[1]);
   return post_launch("ia3_colgrad");
+}
+
+int32_t launch_ia3_swiglu_bwd(const void* gate, const void* up, const void* dact, const void* l, void* dgu, float* part, float* dl,
+                              int n, int F, int dtype, hipStream_t s, const float* dact_part, int splits) {
+  if (n == 0) return FLEXCO_OK;
+  const bool vec = vec_ok(dtype, F, {gate, up, dact, l, dgu, dact_part});
+  const int per = 256 * (vec ? 4 : 1), chunks = (n + IA3_CHUNK - 1) / IA3_CHUNK;
+  DISPATCH_TV(dtype, vec, hipLaunchKernelGGL((ia3_swiglu_bwd_kernel<T, VEC>), dim3((F + per - 1) / per, chunks), dim3(256), 0, s,
+                                             (const T*)gate, (const T*)up, (const T*)dact, (const T*)l, (T*)dgu, part, n, F, dact_part,
+                                             splits, (size_t)n * F));
+  hipLaunchKernelGGL(ia3_colgrad_finalize_kernel, dim3((F + 255) / 256), dim3(256), 0, s, part, chunks, F, dl, (float*)nullptr);
+  return post_launch("ia3_swiglu_bwd");
 }
 
 int32_t launch_swiglu(const void* gu, void* act, int T_, int F, int dtype, hipStream_t s, void* save_gate, void* save_up,

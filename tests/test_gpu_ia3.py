@@ -132,6 +132,16 @@ def test_ia3_small_bf16_group5_bias():
     run_case(SMALL_BF16_G5, b, ft_window=64, prefill_chunk=40, bwd_windows=[33, 131], seed=5)
 
 
+# windows around the eight rows that a block sums and the four it loads together; hidden 1024: dact lies as partial sums of K; a narrow
+# ffn: the column sums of k and v do not fit the scratch side by side
+@pytest.mark.parametrize("hidden,kv,ffn,dtype", [(1024, 2, 1408, "bf16"), (512, 8, 1408, "bf16"), (256, 4, 308, "f32")])
+def test_ia3_backward_in_chunks_of_rows(hidden, kv, ffn, dtype):
+    say(f"(IA)^3 layer, hidden {hidden}, {kv} kv heads, ffn {ffn}, {dtype}")
+    cfg = (C1 if dtype == "f32" else SMALL_BF16).with_(name="ia3_chunks", hidden=hidden, n_kv_heads=kv, ffn=ffn)
+    b = gen.with_adapters(gen.mixed_batch(cfg.page_size, 13, decode_ctx=(5, 16), prefill=[(0, 20, 20)], finetune=[(0, 30, 65)]), [0, -1])
+    run_case(cfg, b, ft_window=35, prefill_chunk=20, bwd_windows=[1, 3, 4, 5, 7, 8, 9, 11, 17], seed=13)
+
+
 def test_ia3_inference_only_batch():
     """No finetune request (ft state = NULL): requests served with the adapter and base-model requests side by side."""
     cfg, seed = SMALL_BF16, 11
