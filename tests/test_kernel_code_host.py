@@ -31,15 +31,20 @@ def barriers_of(code, name):
 # Rings of two stages (the input-gradient form, and the forward form built with two): the buffer freed at a stage's barrier
 # is the stage's own, so no wavefront may have a read on its way there.  Rings of four and six free the stage before:
 # reads issued since the last barrier may be on their way, older ones may not.
+# (template arguments: rows and columns of the tile, transposed, gated, stages, stages walked round from one of the tile's own)
 def test_projection_rings_are_not_overwritten_under_a_read(code):
-    two = 0
-    for (bm, bn, trans, glu, stages), reads in barriers_of(code, "gemm_bf16_kernel").items():
+    two, rotated = 0, set()
+    for args, reads in barriers_of(code, "gemm_bf16_kernel").items():
+        bm, _, trans, glu, stages, spread, *_ = args
         assert len(reads) > 2
-        assert all(old == 0 for _, old in reads), (bm, bn, trans, glu, stages, reads)
+        assert all(old == 0 for _, old in reads), (args, reads)
         if trans or stages == 2:
             two += 1
-            assert all(young == 0 for young, _ in reads), (bm, bn, trans, glu, stages, reads)
+            assert all(young == 0 for young, _ in reads), (args, reads)
+        if spread:
+            rotated.add((bm, glu))
     assert two == 3
+    assert rotated == {(64, 0), (64, 1), (128, 0), (128, 1)}
     for args, reads in barriers_of(code, "gemm_bf16_quad_kernel").items():
         assert all(r == (0, 0) for r in reads), (args, reads)
 
