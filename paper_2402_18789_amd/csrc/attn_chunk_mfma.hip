@@ -13,6 +13,7 @@
 // exponentials may lag its running maximum here (LAZY below), which moves results by rounding only.
 //
 // bf16, head_dim 128, page_size 16, at most 16 query heads per kv head.
+#include "attn_plan.h"
 #include "flexco_internal.h"
 #include "device_types.h"
 
@@ -74,7 +75,9 @@ __global__ __launch_bounds__(256, RING == 3 ? 3 : 2) void attn_fwd_chunk_kernel(
   __shared__ int page_tab[MAXSP];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int item = blockIdx.x / a.nkv, kvh = blockIdx.x % a.nkv;
+  const int turn = blockIdx.x / a.nkv, kvh = blockIdx.x % a.nkv;
+  const int item = a.fold > 1 ? item_of_turn(turn, a.n_items, a.fold) : turn;
+  if (item >= a.n_items) return;
   // (a block's start is a chain of lookups in front of its first load of K: each step asks for all it can)
   const int tile0 = a.item_tile[item], split = a.item_split[item], ntl = a.item_ntiles[item];
   const int tl = tile0 + ntl - 1;
@@ -442,7 +445,7 @@ int32_t launch_attention_chunk_mfma(const flexco_layer_cfg& c, const flexco_maps
   a.req_tok_off = m.req_tok_off;
   a.lag = lag ? LAZY : 0.f;
   const auto kern = m.n_single == 0 ? attn_fwd_chunk_kernel<3> : attn_fwd_chunk_kernel<4>;
-  hipLaunchKernelGGL(kern, dim3((unsigned)m.n_items * c.n_kv_heads), dim3(256), 0, s, a, (const bf16_t*)q, ldq,
+  hipLaunchKernelGGL(kern, dim3((unsigned)turns_of(m.n_items, fold) * c.n_kv_heads), dim3(256), 0, s, a, (const bf16_t*)q, ldq,
                      (const bf16_t*)pool.k_pages, (const bf16_t*)pool.v_pages, part_ml, part_acc);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(FLEXCO_EHIP, "launch of attn_fwd_chunk failed: %s", hipGetErrorString(e));
