@@ -487,10 +487,10 @@ int32_t flexco_bf16_fallbacks(int64_t* counts, int32_t reset);
  * are) launched after the decode tokens' kernel, 2 = that kernel launched beside the decode tokens' kernel, on a side
  * stream of the library's own (default priority; created on the device's first such call, which therefore must not
  * fall inside a stream capture) that leaves the caller's stream before the attention and rejoins it after: to the
- * caller's stream the call behaves as before, also under capture; -1 = chosen by batch, the default: the kernel of
- * four wavefronts for the whole work list, decode tokens included, in one launch, with neighbouring key splits taken together
- * where the list is cut finer than it needs; the one-wavefront kernel for batches of nothing but decode tokens whose contexts
- * are many and short or cut into about as many items as the chip has wavefronts.  Both kernels take the same products per column tile; their results agree to
+ * caller's stream the call behaves as before, also under capture; -1 = chosen by batch, the default: one of
+ * the two for the whole work list, decode tokens included, in one launch - the kernel of four wavefronts, with neighbouring key
+ * splits taken together where the list is cut finer than it needs, or the one-wavefront kernel where the list fills the
+ * chip's rounds of wavefronts better.  Both kernels take the same products per column tile; their results agree to
  * rounding (the kernels scale their running sums at different steps).  Process-wide; returns FLEXCO_EINVAL for other
  * values. */
 int32_t flexco_attention_chunk_path(int32_t mode);

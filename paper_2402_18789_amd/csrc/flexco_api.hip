@@ -8,6 +8,7 @@
 #include <mutex>
 #include <vector>
 
+#include "attn_plan.h"
 #include "flexco_internal.h"
 
 using namespace flexco;
@@ -136,11 +137,9 @@ extern "C" int32_t flexco_kernel_timer_stop(int32_t kernel_id, double* total_ms,
   return rc_out;
 }
 
-// Which kernel takes the chunk items (prefill chunks, finetune windows) of the attention work list: -1 = by batch
-// (the four-wavefront kernel alone when the work list has no single-token item, beside the decode tokens' kernel on a
-// side stream when the chunks' products outweigh the decode stream, else the one-launch kernel: a light chunk load
-// hides in the stream's waits there), 0 = the one-launch kernel, 1 = the four-wavefront kernel after the decode
-// tokens' kernel, 2 = beside it.
+// Which kernel takes the chunk items (prefill chunks, finetune windows) of the attention work list: -1 = by batch, one kernel for the
+// whole list (attn_plan.h), 0 = the one-wavefront kernel, which also takes the single tokens, 1 = the four-wavefront kernel
+// after the single tokens' kernel, 2 = beside it on a side stream.
 static std::atomic<int> g_chunk_path{-1};
 
 // bf16 calls that took a type-generic kernel because the matrix-core kernel of their class does not cover the
@@ -685,43 +684,6 @@ int32_t backward_projection(const flexco_layer_cfg& c, const flexco_lora* lora, 
   }
   if (g.nact > 0) LR(launch_lora_bwd(tg, g.nact, dx, N_dx, n, r, c.lora_scale, dt, s));
   return FLEXCO_OK;
-}
-
-// The default choice of attention kernel and key ranges, from the sums the map builder leaves.
-//
-// alone: the four-wavefront kernel takes the whole work list in one launch: its blocks, two or three per CU, keep as many
-// bytes on their way as the one-wavefront kernel's items did, and share a CU between streaming and multiplying blocks.  Measured
-// against what was done before (one kernel for everything, or the two beside each other on two streams; us): the 14B shape's 512 decode
-// tokens with 512 + 1024 chunk rows 641 -> 608, the 8B shape's 96 decode tokens beside 211 + 205 rows 122 -> 99, 217 decode
-// tokens beside 279 + 40 rows 294 -> 108, 105 beside 74 + 73 166 -> 112, chunks of 713 + 487 + 205 rows without a decode token
-// 144 -> 67 (a last tile of one token had sent them to the pair of kernels), the benchmark batch 428 -> 419.
-// The one-wavefront kernel stays for batches of nothing but decode tokens in two ranges: many short contexts, none of them cut, where
-// a block's fixed chain (tables, first stages) outweighs its few pages (256 requests of 16 - 100 keys 24 against 31 us, of
-// 100 - 600 keys 72 against 76; 128 of 200 - 2000 keys, 70 pages each, 125 against 105), and lists cut into about as many items as
-// the chip has wavefronts of that kernel, 1024 (48 requests of 200 - 2048 keys 49 against 51, 48 of 2000 - 8000 175 against 180; with
-// 1184 items 88 against 81).
-//
-// fold: the work list is cut for one wavefront per item and head, i.e. into more pieces than blocks of four need; the block of a
-// request of one token takes that many neighbouring key splits as one while that leaves 400 blocks, up to the 256 pages of its
-// table (96 requests of 200 - 2000 keys 89 -> 81 from 64 to 128) - 32 where the products of chunks are the work, which a long
-// chain of one wavefront would outlast (24 decode tokens beside 150 and 343 rows 65, with 128 pages 83).
-// 8 pages are too few for a block's fixed chain with 40 items or more (72 items: 22 -> 16; 44: 13.3 against 13.7).
-//
-// Rows of chunks keep their key ranges, and the reference point of their exponentials lags its maximum exactly where
-// the four-wavefront kernel took them before (no single token, or products that outweigh the stream): the probabilities'
-// rounding to bf16 depends on both, and the window's saved rows and gradients with it.
-struct AttnPlan { bool alone; int fold; bool lag; };
-AttnPlan plan_attention(const flexco_maps& m, int nkv) {
-  const int64_t blocks = (int64_t)m.n_items * nkv;
-  const bool lag = m.n_single == 0 || m.chunk_tile_pages >= m.stream_pages;
-  if (m.n_single == m.n_items && blocks >= 768 &&
-      (m.n_parts == m.n_tiles ? m.stream_pages < 24 * (int64_t)m.n_items : blocks <= 1152))
-    return {false, 1, lag};
-  int fold = 1;
-  const int most = 4 * (int64_t)m.stream_pages > m.chunk_tile_pages ? 256 : 32;
-  if (m.req_tok_off && m.kv_split_pages > 0)
-    while (2 * fold * m.kv_split_pages <= most && blocks >= (2 * fold * m.kv_split_pages <= 16 ? 320 : 800) * (int64_t)fold) fold *= 2;
-  return {m.n_single == 0 || m.req_tok_off != nullptr, fold, lag};
 }
 
 int32_t run_attention(const flexco_layer_cfg& c, const flexco_maps& m, const void* q, size_t ldq,
