@@ -27,7 +27,7 @@ __device__ inline float wmax(float v) {
 struct AttnArgs {
   const int32_t *tok_pos, *block_table, *tile_req, *tile_tok0, *tile_ntok, *tile_nsplit, *tile_part0, *item_tile,
       *item_split, *item_ntiles;
-  int max_pages, nq, nkv, d, ps, split_keys, cols_per_tile;
+  int max_pages, nq, nkv, d, ps, split_keys, cols_per_tile, col_blocks;
   float scale;
   // rows of a tile with a single key split go straight to the output, as the merge kernel would write them
   void* out;
@@ -43,11 +43,12 @@ __device__ inline float lane_float(float v, int lane) { return __builtin_bit_cas
 // slots: the fp32 configuration's 68-token batch 19 us against 12.6; 40 decode tokens of 500 - 1000 keys 163 against 121).  The kernel is a chain of loads (the fp32 configuration's grids do not
 // fill the chip): K rows and V page rows are read 16 bytes at a time with several loads in flight - a lane per key for the
 // scores, a lane per channel for the output - and a page id is looked up once per page (one element and one
-// lookup at a time: 78 us for the fp32 configuration's 68-token batch).  A column of at most 64 keys has its V
-// on the way beside its K, before the softmax, and takes page ids from the lanes that looked them up; the tables are read in as few
-// dependent steps as there are.
-constexpr int FWD_NW = 4, FWD_COL_BLOCKS = 4;
-template <typename T>
+// lookup at a time: 78 us for the fp32 configuration's 68-token batch).  SHORT: the form for batches whose columns are all of at
+// most 64 keys and channels: such a column has its V on the way beside its K, before the softmax, and takes page ids from the lanes
+// that looked them up (16.2 -> 12.6 us there); a longer one is still right.  In the kernel of all batches the extra code,
+// which such launches wait for, cost the others 8 - 25 %.  The tables are read in as few dependent steps as there are.
+constexpr int FWD_NW = 4;
+template <typename T, bool SHORT>
 __global__ __launch_bounds__(64 * FWD_NW) void attn_fwd_generic_kernel(AttnArgs a, const T* __restrict__ q, size_t ldq,
                                                                    const T* __restrict__ kp, const T* __restrict__ vp,
                                                                    float* __restrict__ part_ml,
@@ -57,8 +58,8 @@ __global__ __launch_bounds__(64 * FWD_NW) void attn_fwd_generic_kernel(AttnArgs 
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   float* qs = smem + wave * (a.d + a.split_keys);
   float* sc = qs + a.d;
-  // FWD_COL_BLOCKS blocks per tile of the work item that has this split (blockIdx.z = tile within the item, run of columns)
-  const int item = blockIdx.x, kvh = blockIdx.y, tile_in = blockIdx.z / FWD_COL_BLOCKS, run = blockIdx.z % FWD_COL_BLOCKS;
+  // col_blocks blocks per tile of the work item that has this split (blockIdx.z = tile within the item, run of columns)
+  const int item = blockIdx.x, kvh = blockIdx.y, tile_in = blockIdx.z / a.col_blocks, run = blockIdx.z % a.col_blocks;
   const int ntl = a.item_ntiles[item], tile0 = a.item_tile[item], split = a.item_split[item];
   if (tile_in >= ntl) return;
   const int tile = tile0 + tile_in;
@@ -70,18 +71,19 @@ __global__ __launch_bounds__(64 * FWD_NW) void attn_fwd_generic_kernel(AttnArgs 
   const int32_t* bt = a.block_table + (size_t)r * a.max_pages + pg0;
   const int my_pg = lane / a.ps, my_off = lane % a.ps;        // where the lane's key is in a run of 64
   const bool whole = nsplit == 1;                             // the whole key range: normalised rows, straight to the output
-  for (int c = run * FWD_NW + wave; c < ntok * group; c += FWD_NW * FWD_COL_BLOCKS) {
+  for (int c = run * FWD_NW + wave; c < ntok * group; c += FWD_NW * a.col_blocks) {
     const int t = t0 + c / group, h = kvh * group + c % group;
     const int pos = a.tok_pos[t];
-    const int first_page = bt[min(my_pg, a.max_pages - 1 - pg0)];     // (past the last key: not used)
+    int first_page = 0;
+    if (SHORT) first_page = bt[min(my_pg, a.max_pages - 1 - pg0)];     // (past the last key: not used)
     for (int dd = lane; dd < a.d; dd += 64) qs[dd] = ld(q + (size_t)t * ldq + h * a.d + dd);
     const int nk = max(0, min(k0 + a.split_keys, pos + 1) - k0);
     // a column of one run: V of the lane's first channel, 64 keys
-    const bool short_run = nk <= 64 && a.ps % N == 0;         // (uniform)
-    float v1[64 / N][N];
+    const bool short_run = SHORT && nk <= 64 && a.ps % N == 0;         // (uniform)
+    float v1[SHORT ? 64 / N : 1][N];
     if (short_run) {
 #pragma unroll
-      for (int u = 0; u < 64 / N; ++u) {
+      for (int u = 0; u < (SHORT ? 64 / N : 0); ++u) {
         const int un = min(u * N, max(nk - 1, 0) / N * N);    // past the last key: the last unit again, not used
         const T* vr = vp + (((size_t)lane_int(first_page, un) * a.nkv + kvh) * (size_t)a.d + min(lane, a.d - 1)) * a.ps + lane_int(my_off, un);
         Vec<T>::load(vr, v1[u]);
@@ -90,8 +92,8 @@ __global__ __launch_bounds__(64 * FWD_NW) void attn_fwd_generic_kernel(AttnArgs 
     __builtin_amdgcn_wave_barrier();
     float m = -INFINITY;
     for (int jj = lane; jj < nk; jj += 64) {
-      const size_t page = jj < 64 ? first_page : bt[jj / a.ps];
-      const T* kr = kp + ((page * a.nkv + kvh) * a.ps + (jj < 64 ? my_off : jj % a.ps)) * (size_t)a.d;   // rows are whole 16-byte units
+      const size_t page = SHORT && jj < 64 ? first_page : bt[jj / a.ps];
+      const T* kr = kp + ((page * a.nkv + kvh) * a.ps + (SHORT && jj < 64 ? my_off : jj % a.ps)) * (size_t)a.d;   // rows are whole 16-byte units
       float s = 0.f;
 #pragma unroll 8
       for (int dd = 0; dd < a.d; dd += N) {
@@ -120,7 +122,7 @@ __global__ __launch_bounds__(64 * FWD_NW) void attn_fwd_generic_kernel(AttnArgs 
       float acc = 0.f;
       if (short_run && dd < 64) {
 #pragma unroll
-        for (int u = 0; u < 64 / N; ++u)
+        for (int u = 0; u < (SHORT ? 64 / N : 0); ++u)
 #pragma unroll
           for (int e = 0; e < N; ++e)
             if (u * N + e < nk) acc += sc[u * N + e] * v1[u][e];
@@ -481,9 +483,17 @@ int32_t launch_attention_generic(const flexco_layer_cfg& c, const flexco_maps& m
   a.scale = 1.0f / sqrtf((float)c.head_dim);
   const size_t shm = 4 * sizeof(float) * (size_t)(a.d + a.split_keys);
   if (shm > 64 * 1024) return fail(FLEXCO_EUNSUPPORTED, "kv_split_pages * page_size = %d keys is too large for the generic attention kernel", a.split_keys);
-  const dim3 grid(m.n_items, c.n_kv_heads, FLEXCO_ATTN_ITEM_TILES * FWD_COL_BLOCKS);
-  DISPATCH_T(c.dtype, hipLaunchKernelGGL((attn_fwd_generic_kernel<T>), grid, dim3(64 * FWD_NW), shm, s, a, (const T*)q, ldq,
-                                         (const T*)pool.k_pages, (const T*)pool.v_pages, part_ml, part_acc));
+  // a list of nothing but single tokens has one tile per item and a group of columns per tile (8 of them, 10 - 500 keys, with the blocks
+  // of whole items as well 1 - 3 % more)
+  const bool singles = m.n_single == m.n_items;
+  a.col_blocks = singles ? (c.n_q_heads / c.n_kv_heads + FWD_NW - 1) / FWD_NW : 4;
+  const dim3 grid(m.n_items, c.n_kv_heads, (singles ? 1 : FLEXCO_ATTN_ITEM_TILES) * a.col_blocks);
+  DISPATCH_T(c.dtype, {
+    const bool one_run = m.max_kv_len <= 64 && a.d <= 64;
+    const auto kern = one_run ? attn_fwd_generic_kernel<T, true> : attn_fwd_generic_kernel<T, false>;
+    hipLaunchKernelGGL(kern, grid, dim3(64 * FWD_NW), shm, s, a, (const T*)q, ldq, (const T*)pool.k_pages, (const T*)pool.v_pages, part_ml,
+                       part_acc);
+  });
   return post_launch("attn_fwd_generic");
 }
 

@@ -127,3 +127,20 @@ def test_generic_attention_forward_short_runs(cfg):
         out, a_o, lse, lse_o = attention_case(cfg, batch, split)
         assert_close("attention out", out, a_o, TOL[cfg.dtype])
         assert float(np.max(np.abs(lse - lse_o))) <= (1e-4 if cfg.dtype == "f32" else 2e-2)
+
+
+# the forms of the forward kernel: every context of at most 64 keys and 64 channels (V fetched beside K), in one and in several ranges of
+# keys; nothing but single tokens (one tile per item, as many blocks as a group of heads needs)
+GROUP6_F32 = C1.with_(name="g6_f32", n_q_heads=12, n_kv_heads=2, head_dim=64)
+
+
+@pytest.mark.parametrize("split", [0, 2])
+@pytest.mark.parametrize("cfg", [C1, D64_F32, GROUP6_F32, ODD_F32, D128_F32])
+@pytest.mark.parametrize("kind", ["short", "singles", "short singles"])
+def test_generic_attention_forward_forms(cfg, split, kind):
+    print(f"attention forward forms {cfg.name} {kind} split={split}", flush=True)
+    ctx = (1, 2, 15, 16, 17, 31, 33, 48, 62, 63, 64) if "short" in kind else (1, 5, 63, 64, 65, 66, 127, 128, 129, 500)
+    chunks = {} if "singles" in kind else dict(prefill=[(0, 17, 17), (20, 44, 64)], finetune=[(1, 63, 64)])
+    out, a_o, lse, lse_o = attention_case(cfg, gen.mixed_batch(cfg.page_size, 8, decode_ctx=ctx, **chunks), split)
+    assert_close("attention out", out, a_o, TOL[cfg.dtype])
+    assert float(np.max(np.abs(lse - lse_o))) <= 1e-4
