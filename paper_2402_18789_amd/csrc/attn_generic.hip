@@ -360,14 +360,17 @@ __global__ __launch_bounds__(64) void attn_bwd_dq_generic_kernel(const T* __rest
     }
     const float pj = __expf(s * scale - row_lse);
     const float ds = kc + lane <= p ? pj * (dp - row_delta) * scale : 0.f;
+    // (eight keys' rows on their way; past the last key its row again, times zero.  The lane reads are no loop a compiler unrolls.)
     const int nk = min(64, p + 1 - kc);
-#pragma unroll 8
-    for (int jj = 0; jj < nk; ++jj) {
-      const T* kj = kp + (((size_t)lane_int(my_page, jj) * nkv + kvh) * ps + lane_int(my_off, jj)) * (size_t)d;
-      const float w = lane_float(ds, jj);
+    for (int j0 = 0; j0 < nk; j0 += 8) {
 #pragma unroll
-      for (int u = 0; u < DU; ++u)
-        if (DU == 1 || lane + 64 * u < d) acc[u] += w * ld(kj + (DU == 1 ? min(lane, d - 1) : lane + 64 * u));
+      for (int jj = j0; jj < j0 + 8; ++jj) {
+        const T* kj = kp + (((size_t)lane_int(my_page, jj) * nkv + kvh) * ps + lane_int(my_off, jj)) * (size_t)d;
+        const float w = lane_float(ds, jj);
+#pragma unroll
+        for (int u = 0; u < DU; ++u)
+          acc[u] += w * ld(kj + min(lane + 64 * u, d - 1));    // (channels past head_dim: not stored)
+      }
     }
   }
 #pragma unroll
@@ -431,15 +434,16 @@ __global__ __launch_bounds__(64) void attn_bwd_dkv_generic_kernel(const T* __res
     }
     const float pj = pc + lane < n_pairs ? __expf(s * scale - row_lse) : 0.f;
     const float ds = pj * (dp - row_delta) * scale;
+    constexpr int G = FEW ? 16 / DU : 4;      // pairs' rows on their way; past the last pair its rows again, times zero
     const int np = min(64, n_pairs - pc);
-#pragma unroll FEW ? 16 : 4
-    for (int pp = 0; pp < np; ++pp) {
-      const size_t at = ((size_t)lane_int(my_i, pp) * nq + lane_int(my_h, pp)) * d;
-      const float wp = lane_float(pj, pp), wd = lane_float(ds, pp);
+    for (int p0 = 0; p0 < np; p0 += G) {
 #pragma unroll
-      for (int u = 0; u < DU; ++u) {
-        const int dd = DU == 1 ? min(lane, d - 1) : lane + 64 * u;
-        if (DU == 1 || dd < d) {
+      for (int pp = p0; pp < p0 + G; ++pp) {
+        const size_t at = ((size_t)lane_int(my_i, pp) * nq + lane_int(my_h, pp)) * d;
+        const float wp = lane_float(pj, pp), wd = lane_float(ds, pp);
+#pragma unroll
+        for (int u = 0; u < DU; ++u) {
+          const int dd = min(lane + 64 * u, d - 1);
           dv[u] += wp * ld(dout + at + dd);
           dk[u] += wd * ld(q + at + dd);
         }

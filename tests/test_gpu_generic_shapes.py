@@ -129,6 +129,15 @@ def test_generic_attention_forward_short_runs(cfg):
         assert float(np.max(np.abs(lse - lse_o))) <= (1e-4 if cfg.dtype == "f32" else 2e-2)
 
 
+# the rows that the backward kernels fetch together: the last group of them full, of one and of all but one; one, two and four channels per lane, the
+# last of them partly past head_dim
+@pytest.mark.parametrize("win_start,win_len", [(0, 1), (0, 8), (7, 9), (40, 25), (63, 2), (260, 33)])
+@pytest.mark.parametrize("head_dim,dtype", [(40, "f32"), (100, "f32"), (136, "f32"), (200, "bf16"), (256, "bf16")])
+def test_generic_attention_backward_groups(head_dim, dtype, win_start, win_len):
+    test_generic_attention_backward(C1.with_(name="d%d_%s" % (head_dim, dtype), dtype=dtype, n_q_heads=6, n_kv_heads=2, head_dim=head_dim),
+                                    win_start, win_len)
+
+
 # the forms of the forward kernel: every context of at most 64 keys and 64 channels (V fetched beside K), in one and in several ranges of
 # keys; nothing but single tokens (one tile per item, as many blocks as a group of heads needs)
 GROUP6_F32 = C1.with_(name="g6_f32", n_q_heads=12, n_kv_heads=2, head_dim=64)
