@@ -992,21 +992,22 @@ __global__ __launch_bounds__(256) void lora_reduce_long_kernel(LoraBatch b, int 
 }
 
 // Y[m, i] += scale * sum_j U[m, j] * S(i, j) for 16 rows from m0 on and 256 columns from i0 on; products z0 .. z1 - 1, which
-// share their Y, one after the other.  The rows' elements are asked for together.
-template <typename T, int R>
-__device__ inline void lora_expand_block(float (&us)[64][R], const LoraBatch& b, int z0, int z1, int i0, int m0, int n, int r, float scale,
-                                         const int32_t* __restrict__ row_idx) {
+// share their Y, one after the other.  The rows' elements are asked for together, ROWS = 16 or 4 of them: a launch of a few rows
+// waits for its code, and one row of rank 64 takes 11.6 us in the form of sixteen.
+template <typename T, int R, int ROWS>
+__device__ inline void lora_expand_rows(float (&us)[64][R], const LoraBatch& b, int z0, int z1, int i0, int m0, int n, int r, float scale,
+                                        const int32_t* __restrict__ row_idx) {
   const int i = i0 + threadIdx.x;
   const LoraProduct& y0 = b.p[z0];
-  T* yp[16];
-  float yv[16];
+  T* yp[ROWS];
+  float yv[ROWS];
 #pragma unroll
-  for (int mm = 0; mm < 16; ++mm) {
+  for (int mm = 0; mm < ROWS; ++mm) {
     const int row = min(m0 + mm, n - 1);
     yp[mm] = (T*)y0.Y + (row_idx ? (size_t)row_idx[row] : (size_t)row) * y0.ldy + min(i, y0.n_long - 1);
   }
 #pragma unroll
-  for (int mm = 0; mm < 16; ++mm) yv[mm] = ld(yp[mm]);
+  for (int mm = 0; mm < ROWS; ++mm) yv[mm] = ld(yp[mm]);
   for (int z = z0; z < z1; ++z) {
     const LoraProduct& p = b.p[z];
     const T* __restrict__ S = (const T*)p.S;
@@ -1014,13 +1015,13 @@ __device__ inline void lora_expand_block(float (&us)[64][R], const LoraBatch& b,
 #pragma unroll
     for (int j = 0; j < R; ++j) sv[j] = (j < r) ? ld(S + (size_t)min(i, p.n_long - 1) * p.s_i + (size_t)j * p.s_j) : 0.f;
     __syncthreads();
-    for (int idx = threadIdx.x; idx < 16 * R; idx += 256) {
+    for (int idx = threadIdx.x; idx < ROWS * R; idx += 256) {
       const int mm = idx / R, j = idx % R;
       us[mm][j] = (m0 + mm < n && j < r) ? p.U[(size_t)(m0 + mm) * r + j] : 0.f;
     }
     __syncthreads();
 #pragma unroll
-    for (int mm = 0; mm < 16; ++mm) {
+    for (int mm = 0; mm < ROWS; ++mm) {
       float a = 0.f;
 #pragma unroll
       for (int j = 0; j < R; ++j) a += us[mm][j] * sv[j];
@@ -1029,9 +1030,15 @@ __device__ inline void lora_expand_block(float (&us)[64][R], const LoraBatch& b,
   }
   if (i < y0.n_long) {
 #pragma unroll
-    for (int mm = 0; mm < 16; ++mm)
+    for (int mm = 0; mm < ROWS; ++mm)
       if (m0 + mm < n) st(yp[mm], yv[mm]);
   }
+}
+template <typename T, int R>
+__device__ inline void lora_expand_block(float (&us)[64][R], const LoraBatch& b, int z0, int z1, int i0, int m0, int n, int r, float scale,
+                                         const int32_t* __restrict__ row_idx) {
+  if (n - m0 > 4) lora_expand_rows<T, R, 16>(us, b, z0, z1, i0, m0, n, r, scale, row_idx);
+  else lora_expand_rows<T, R, 4>(us, b, z0, z1, i0, m0, n, r, scale, row_idx);
 }
 
 // grid (ceil(n_long/256), ceil(n/16), products), or, for products that share their Y, one z block that adds them one after the other

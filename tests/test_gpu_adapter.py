@@ -228,3 +228,24 @@ def test_adapter_error_paths():
     with pytest.raises(B.FlexcoError) as e:                        # window beyond the sequence
         B.flexco_adapter_bwd(1, cfg.hidden, ad.c, saved, 16, 8, 16, y[:16], ws, ws.numel() * 4)
     assert e.value.code == B.FLEXCO_ESHAPE
+
+
+# windows around the four and the sixteen rows whose elements the type-generic kernels take together, each bound of the rank
+@pytest.mark.parametrize("n", [1, 3, 4, 5, 16, 17, 20, 21, 36])
+@pytest.mark.parametrize("b,hidden", [(8, 256), (12, 300), (24, 256), (64, 520)])
+def test_adapter_backward_of_few_rows(n, b, hidden):
+    say(f"adapter backward of {n} rows, width {hidden}, bottleneck {b}")
+    g = gen.rng(3, "adapter_rows", n, b, hidden)
+    x, dy = (g.standard_normal((n, hidden), dtype=np.float32) for _ in range(2))
+    wd, wu = (g.standard_normal(s, dtype=np.float32) * np.float32(0.05) for s in ((b, hidden), (hidden, b)))
+    dx_o, dwd_o, dwu_o = OA.backward(*(a.astype(np.float64) for a in (x, wd, wu, dy)))
+    ad = DeviceAdapter(C1, wd, wu)
+    code, x_d = HH.DTYPE_CODE["f32"], torch.from_numpy(x).cuda()
+    guard = torch.full((n + 2, hidden), 7.0, device="cuda")
+    guard[:n] = torch.from_numpy(dy).cuda()
+    ws = torch.empty(B.flexco_adapter_workspace_bytes(code, hidden, b, n, n) // 4 + 1, dtype=torch.float32, device="cuda")
+    B.flexco_adapter_bwd(code, hidden, ad.c, x_d, n, 0, n, guard[:n], ws, ws.numel() * 4)
+    torch.cuda.synchronize()
+    for name, got, ref in (("dX", to_np(guard)[:n], dx_o), ("dW_down", to_np(ad.dwd), dwd_o), ("dW_up", to_np(ad.dwu), dwu_o)):
+        assert_close("adapter " + name, got, ref, TOL["f32"])
+    assert np.all(to_np(guard)[n:] == 7.0)
