@@ -15,13 +15,17 @@ namespace flexco {
 
 // The item of the work list that turn `turn` takes where the block of a request of one token takes fold neighbouring key splits as one (turns
 // are dealt to the chip's parts one after the other; turns run to turns_of(n_items, fold), those past the last item have none).
-// Items at a stride of fold: the ones that are left with work are every fold-th of a request, so in the list's own order requests of a
-// multiple of fold splits left all of it to every fold-th part of the chip.  Us, 8 kv heads: 24 requests of 1024 keys in eights 49.9 ->
-// 23.9, 4 of 3072 in fours 33.6 -> 19.2, 24 of 4096 in fours 140 -> 80; odd numbers of splits within 5 %.
+// Within runs of 32 fold items, at a stride of fold: the items that are left with work are every fold-th of a request, so in the list's own
+// order requests of a multiple of fold splits left all of it to every fold-th part of the chip.  Us, 8 kv heads: 24 requests of 1024
+// keys in eights 49.9 -> 23.9, 4 of 3072 in fours 33.6 -> 19.2, 24 of 4096 in fours 140 -> 80; odd numbers of splits within 5 %.  Runs, so
+// that the list's order - the longest first, chunks early - stays what it is (at a stride through the whole list a batch whose chunks are
+// half the work 96 -> 106).
+constexpr int FOLD_RUN = 32;
 FLEXCO_HOST_DEVICE inline int turns_of(int n_items, int fold) { return (n_items + fold - 1) / fold * fold; }
 FLEXCO_HOST_DEVICE inline int item_of_turn(int turn, int n_items, int fold) {
-  const int run = (n_items + fold - 1) / fold;
-  return turn % run * fold + turn / run;
+  const int base = turn / (FOLD_RUN * fold) * (FOLD_RUN * fold), left = n_items - base;
+  const int run = left < FOLD_RUN * fold ? (left + fold - 1) / fold : FOLD_RUN;
+  return base + (turn - base) % run * fold + (turn - base) / run;
 }
 
 // alone: the four-wavefront kernel takes the whole work list in one launch: its blocks, two or three per CU, keep as many

@@ -40,6 +40,13 @@ def test_every_item_has_one_turn(n, fold):
     assert all(0 <= i for i in items)
 
 
+# The list's own order stays what it is but for a few neighbours: it begins with the longest items.
+@pytest.mark.parametrize("fold", [2, 4, 16])
+def test_turns_keep_the_order_of_the_list(fold):
+    items = [lib().item_of_turn(t, 5000, fold) for t in range(lib().turns_of(5000, fold))]
+    assert max(abs(i - t) for t, i in enumerate(items)) < 32 * fold
+
+
 # Requests of an even number of splits: the items that are left with work (the first of every fold) fall to all parts of the chip that the
 # turns are dealt to - 4, 8 or 32 of them - alike.
 @pytest.mark.parametrize("parts", [4, 8, 32])
