@@ -68,7 +68,7 @@ inline int plan_decode(const flexco_maps& m, int nkv) {
   // one fold from 768 on 0.92 / 1.00; fewer or longer ones leave CUs idle (up to 64 pages, 128 - 256 of them up to 1.5)
   if (fold * sp >= m.max_pages) {
     if ((m.max_pages <= 64 && whole >= 384) || (fold == 2 && m.max_pages <= 128 && whole >= 768)) return fold;
-    if (m.max_pages <= 40 && whole >= 160) return full ? 0 : fold;
+    if (m.max_pages <= 40 && whole >= 160 && blocks > 512) return full ? 0 : fold;
   }
   if (sp > 128) return blocks <= 3072 ? 1 : 0;        // 0.68 - 1.00; above 1.00 - 1.03
   // Fine cuts of many blocks (asked for; the default cut leaves 1024 to 2048, or as few as pieces of 8 pages make): down to that first.
@@ -87,11 +87,13 @@ inline int plan_decode(const flexco_maps& m, int nkv) {
     if (left(4 * f) >= 448 && left(4 * f) <= 540) return 4 * f;
     return left(2 * f) >= 620 ? 2 * f : f > 1 ? f : 0;
   }
-  // pieces of 8 pages.  A request of twenty or more: the merge of their sums is what takes the time, by fours 0.58 - 0.90.
+  // pieces of 8 pages.  One round of blocks: as they are 0.76 - 0.93 where a request has up to eight of them, else by pairs 0.65 - 0.87 (as they
+  // are 0.80 - 0.99).
+  if (n <= 512) return m.max_pages <= 8 * p ? f : 2 * f;
+  // A request of twenty or more: the merge of their sums is what takes the time, by fours 0.58 - 0.90.
   if (m.max_pages >= 20 * p) return 4 * f;
-  if (left(4 * f) >= 320) return 4 * f;  // 0.73 - 0.88 / 1.03
-  if (n <= (m.max_pages <= 40 ? 320 : 256)) return f;      // 0.80 / 0.94
-  return left(2 * f) <= 352 ? 2 * f : f > 1 ? f : 0;       // 0.80 - 0.90; two or three hundred pairs more 0.94 - 1.01 / 1.24
+  if (left(4 * f) >= 320) return 4 * f;                    // 0.73 - 0.88 / 1.03
+  return left(2 * f) <= 352 ? 2 * f : f > 1 ? f : 0;       // 0.89 - 1.00; one or two hundred pairs more 0.94 - 1.01 / 1.24
 }
 
 // Lists with chunks.  (Against what was done before them - above - 0.78 on average.)
