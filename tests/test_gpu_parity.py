@@ -8,6 +8,7 @@ import numpy as np
 import pytest
 import torch
 
+from attn_plan import attention_plan
 from workload import gen, CONFIGS
 from workload.configs import KIND_FINETUNE
 
@@ -186,27 +187,73 @@ def _attention_mixed(name, split):
     assert float(np.max(np.abs(lse - lse_o))) <= (1e-4 if cfg.dtype == "f32" else 2e-2)
 
 
-# the library's own choice of kernel and of key splits taken together (2, 4, .. of the work list's, at most 256 pages; the
-# partial rows in between stay unwritten): work lists cut finely, so that ranges of several splits end inside a split, on its
-# edge and in the last split, with one or with several partial rows left per tile
-@pytest.mark.parametrize("name,split", [("stream", 2), ("stream", 6), ("stream", 34), ("chunks", 2), ("chunks", 6), ("chunks", 8),
-                                        ("both", 2), ("short", 0), ("round", 4)])
-def test_attention_mixed_folded_splits(name, split):
-    say(f"attention_mixed folded {name} split={split}")
-    if name == "stream":                     # the decode tokens carry the time: folded while 400 blocks are left
-        cfg, batch = SMALL_BF16_MHA, gen.mixed_batch(16, 3, decode_ctx=(1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 96, 127, 128, 129, 255, 256, 257, 511, 512, 513)
-                                                     + tuple(range(900, 1500, 9)), prefill=[(40, 33, 73)], finetune=[(130, 17, 147)])
-    elif name == "chunks":                   # the chunks do: ranges of up to 32 pages, the last tile holds one token
-        cfg, batch = SMALL_BF16, gen.mixed_batch(16, 4, decode_ctx=(700,), prefill=[(500, 101, 601), (0, 64, 64)], finetune=[(1000, 77, 1077)])
-    elif name == "both":
-        cfg, batch = SMALL_BF16_G8, gen.mixed_batch(16, 5, decode_ctx=tuple(range(200, 1200, 25)), prefill=[(300, 65, 365)], finetune=[(200, 33, 233)])
-    elif name == "short":                    # nothing but short contexts: the one-wavefront kernel
-        cfg, batch = SMALL_BF16_MHA, gen.mixed_batch(16, 6, decode_ctx=tuple(range(1, 200)))
-    else:                                    # nothing but decode tokens, cut into about one item per wavefront of the chip
-        cfg, batch = SMALL_BF16_MHA, gen.mixed_batch(16, 7, decode_ctx=(150,) * 75)
+# The library's own choice of kernel and of key splits taken together (2, 4, .. of the work list's, at most 256 pages; the
+# partial rows in between stay unwritten): ranges of several splits end inside a split, on its edge and in the last split, with one or
+# with several partial rows left per tile.  Expected per case: the splits taken as one (0: the one-wavefront kernel).
+FOLD_EDGES = (1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 96, 127, 128, 129, 255, 256, 257, 511, 512, 513)
+FOLD_BATCHES = {
+    # the decode tokens carry the time, chunks and a window beside them; then alone
+    "stream": (SMALL_BF16_MHA, dict(decode_ctx=FOLD_EDGES + tuple(range(900, 1500, 9)), prefill=[(40, 33, 73)], finetune=[(130, 17, 147)])),
+    "decode": (SMALL_BF16_MHA, dict(decode_ctx=FOLD_EDGES + tuple(range(900, 1500, 9)))),
+    # the chunks do, the last tile holds one token
+    "chunks": (SMALL_BF16, dict(decode_ctx=(700, 1500, 90), prefill=[(500, 101, 601), (0, 64, 64)], finetune=[(1000, 77, 1077)])),
+    "both": (SMALL_BF16_G8, dict(decode_ctx=tuple(range(200, 1200, 25)), prefill=[(300, 65, 365)], finetune=[(200, 33, 233)])),
+    # a request or two of long contexts, most of whose time is the merge
+    "long": (SMALL_BF16, dict(decode_ctx=(5000, 2999, 16, 1))),
+    # every context within one range of the splits taken together: no sums left to merge
+    "whole": (SMALL_BF16_MHA, dict(decode_ctx=tuple(range(20, 1010, 9)) + (1, 16, 17, 1024))),
+    # nothing but short contexts, whole and cut; nothing but equal ones that fill one round of either kernel
+    "short": (SMALL_BF16_MHA, dict(decode_ctx=tuple(range(1, 129)))),
+    "round": (SMALL_BF16_MHA, dict(decode_ctx=(1024,) * 32)),
+}
+
+
+FOLD_CASES = [  # name, pages per split of the list (0: the default), splits as one, sums left to merge
+    ("stream", 0, 2, True), ("stream", 2, 8, True), ("stream", 34, 1, True), ("decode", 0, 4, True), ("decode", 2, 32, True),
+    ("decode", 4, 16, True), ("decode", 6, 4, True), ("decode", 34, 0, True), ("chunks", 0, 1, True), ("chunks", 2, 4, True),
+    ("chunks", 4, 2, True), ("both", 2, 4, True), ("both", 6, 2, True), ("long", 0, 2, True), ("long", 2, 8, True),
+    ("whole", 0, 4, False), ("whole", 2, 32, False), ("whole", 6, 16, False), ("short", 0, 1, False), ("short", 2, 4, False),
+    ("round", 0, 0, True), ("round", 2, 4, True), ("round", 16, 1, True)]
+ONE_TOKEN_CASES = [("few", 0, 2, True), ("few", 2, 8, True), ("long", 4, 4, True), ("whole", 0, 4, False), ("whole", 2, 32, False),
+                   ("short", 0, 0, False), ("short", 2, 4, False)]
+
+
+def expect_plan(cfg, batch, split, fold, merge):
+    db = HH.DeviceBatch(cfg, batch.requests, batch.seq_pages, batch.num_pages, split)
+    maps = db.host_maps
+    assert attention_plan(maps, cfg.n_kv_heads)[0] == fold
+    all_whole = maps.n_single == maps.n_items and maps.max_pages <= max(fold, 1) * maps.kv_split_pages
+    assert merge == (maps.n_parts != maps.n_tiles and not all_whole)
+
+
+@pytest.mark.parametrize("name,split,fold,merge", FOLD_CASES)
+def test_attention_mixed_folded_splits(name, split, fold, merge):
+    say(f"attention_mixed folded {name} split={split}: {fold} as one, {'' if merge else 'not '}merged")
+    cfg, kw = FOLD_BATCHES[name]
+    batch = gen.mixed_batch(16, 3, **kw)
+    expect_plan(cfg, batch, split, fold, merge)
     out, a_o, lse, lse_o = attention_case(cfg, batch, split)
     assert_close("attention out", out, a_o, TOL[cfg.dtype])
     assert float(np.max(np.abs(lse - lse_o))) <= 2e-2
+
+
+# A finetune window of one token: its kept rows of the attention come out of a range of several splits (one partial row left, or none),
+# out of their merge, and out of the one-wavefront kernel
+@pytest.mark.parametrize("name,split,fold,merge", ONE_TOKEN_CASES)
+def test_window_of_one_token_beside_folded_splits(name, split, fold, merge):
+    say(f"window of one token {name} split={split}: {fold} as one, {'' if merge else 'not '}merged")
+    cfg, ctx, pos = {"few": (SMALL_BF16, (700, 90, 33), 1500), "long": (SMALL_BF16, (3000, 90), 4100),
+                     "whole": (SMALL_BF16_MHA, tuple(range(20, 1010, 9)), 700), "short": (SMALL_BF16_MHA, tuple(range(1, 129)), 40)}[name]
+    batch = gen.mixed_batch(16, 3, decode_ctx=ctx, finetune=[(pos, 1, pos + 1)])
+    expect_plan(cfg, batch, split, fold, merge)
+    case = Case(cfg, batch, seed=3, kv_split_pages=split)
+    got, ref, _ = case.forward(batch, gen.layer_input(cfg, 3, batch.n_tokens))
+    assert_close("y", got, ref, TOL["bf16"])
+    (seq, st_d), = case.d_ft.items()
+    st_o = case.o_ft[seq]
+    for kept in ("q_cache", "x", "x2", "gate", "up", "attn"):
+        assert_close("kept " + kept, to_np(getattr(st_d, kept))[pos:], np.asarray(getattr(st_o, kept))[pos:], TOL["bf16"])
+    assert float(np.max(np.abs(to_np(st_d.lse)[pos:] - np.asarray(st_o.lse)[pos:]))) <= 2e-2
 
 
 # ------------------------------------------------------------------------------------------
