@@ -52,11 +52,22 @@ def test_forward_tiles_of_few_rows(M, N, K):
     run_gemm(M, N, K, 0)
 
 
-# rows of W a multiple of 4 KB apart: the column tiles start at stages of their own
+# rows of W a multiple of 4 KB apart: the column tiles of the 64-row form start at stages of their own (its cut form, the cut 128 x 128 one and the
+# gated ones: test_layer_products_from_their_own_stage)
 @pytest.mark.parametrize("K", [2048, 6144])
-@pytest.mark.parametrize("M,N", [(1, 8), (63, 136), (64, 6152), (65, 136), (128, 6152)])
+@pytest.mark.parametrize("M,N", [(1, 136), (30, 1000), (63, 136), (64, 6152)])
 def test_forward_tiles_of_few_rows_from_their_own_stage(M, N, K):
     print(f"forward, spread stages, M={M} N={N} K={K}", flush=True)
+    (bm, bn, _, splits, _), = B.flexco_gemm_plan(M, N, K, 0)
+    assert (bm, bn, splits) == (64, 128, 1) and N > bn        # a second column tile: only it starts elsewhere
+    run_gemm(M, N, K, 0)
+
+
+# ... and the forms that walk them in order at such a pitch too: one column tile, whole 128 x 128 tiles
+@pytest.mark.parametrize("K", [2048, 6144])
+@pytest.mark.parametrize("M,N", [(1, 8), (63, 128), (64, 8), (65, 136), (128, 6152)])
+def test_forward_tiles_of_few_rows_at_a_pitch_of_4_kb(M, N, K):
+    print(f"forward, M={M} N={N} K={K}", flush=True)
     run_gemm(M, N, K, 0)
 
 

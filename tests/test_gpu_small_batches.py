@@ -27,6 +27,26 @@ def test_layer_partial_sums_left_to_the_next_kernel(chunk, window):
     run_layer_case(WIDE, b, ft_window=window, prefill_chunk=chunk, bwd_windows=[window, window], seed=17)
 
 
+# Rows of every weight a multiple of 4 KB apart, at most 128 tokens: the column tiles of the products start at stages of their own - the 64-row
+# form cut over K in unequal ranges, the 128 x 128 form in equal ones, the gated form of either
+@pytest.mark.parametrize("chunk,window", [(12, 14), (30, 30), (31, 30), (47, 46), (62, 62)])
+@pytest.mark.parametrize("hidden,ffn", [(2048, 4096), (2048, 6144)])
+def test_layer_products_from_their_own_stage(hidden, ffn, chunk, window):
+    cfg = WIDE.with_(name="spread", hidden=hidden, ffn=ffn)
+    b = gen.batch_scaled(17, 4, 3, 90, [(0, chunk, 2 * chunk)], [(0, window, 2 * window)])
+    T, bm = b.n_tokens, 64 if b.n_tokens <= 64 else 128
+    print(f"layer of {T} tokens, hidden {hidden}, ffn {ffn}", flush=True)
+    assert T == 4 + chunk + window <= 128
+    unequal = 0
+    for N, K in ((cfg.q_dim + 2 * cfg.kv_dim, hidden), (hidden, cfg.q_dim), (hidden, ffn)):
+        (rows, cols, _, splits, _), = B.flexco_gemm_plan(T, N, K, 0, T * 32768)
+        assert (rows, cols) == (bm, 128) and splits > 1 and K % 2048 == 0 and B.flexco_gemm_k_ranges(T, N, K, 0, T * 32768) == 0
+        unequal += K // 64 % splits != 0
+    assert unequal == (3 if bm == 64 else 0)
+    assert B.flexco_gemm_plan(T, 2 * ffn, hidden, 0) == [(bm, 128, 2 * ffn, 1, 6 if bm == 64 else 4)]
+    run_layer_case(cfg, b, ft_window=window, prefill_chunk=chunk, bwd_windows=[window, window], seed=17)
+
+
 # K that is no multiple of 64 runs on the type-generic kernel, uncut, whatever the planner of the matrix-core path would
 # do with it: the qkv and down products (hidden, ffn), then o (q_dim = 27 x 48); few tokens, no adapter rows, a bias
 @pytest.mark.parametrize("hidden,heads,kv,d", [(2056, 16, 4, 128), (2048, 27, 9, 48), (1352, 11, 11, 128)])
