@@ -281,10 +281,13 @@ def forward_launches(B, cfg, T, use_ia3=False):
     cut over K has a second launch, its sum's, unless the next kernel adds the partial sums itself (the norm behind o,
     the rotation behind qkv unless (IA)^3 scales the rows in between); one that is not may be two tile shapes."""
     H, F, qd, kd = cfg.hidden, cfg.ffn, cfg.q_dim, cfg.kv_dim
-    scratch = T * (32768 if T <= 256 else F)          # what the layer has: its own, or the gate/up buffer while that is free
+    # what the layer has: its own scratch, or the gate/up buffer while that is free and, at the down projection, the bf16
+    # rows of h, qkv and the attention output in front of it
+    scratch = T * (32768 if T <= 256 else F)
+    down = scratch if T <= 256 else T * (F + (H + 2 * qd + 2 * kd) // 2)
     out = []
     for name, N, K, part, left in (("qkv", qd + 2 * kd, H, scratch, not use_ia3), ("o", H, qd, scratch, True),
-                                   ("gate_up", 2 * F, H, 0, False), ("down", H, F, scratch, False)):
+                                   ("gate_up", 2 * F, H, 0, False), ("down", H, F, down, False)):
         plan = B.flexco_gemm_plan(T, N, K, False, part)
         cut = max(plan[0][3], B.flexco_gemm_k_ranges(T, N, K, False, part) if part else 0)
         out.append((name, N * K, len(plan) if cut == 1 else 1 if left else 2))

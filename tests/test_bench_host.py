@@ -28,8 +28,22 @@ def test_sums_left_to_the_next_kernel_are_no_launch():
     assert launches(C2, 16)[:2] == [1, 1] and launches(C2, 16)[3] == 2
 
 
+def down_scratch(cfg, T):
+    """floats: the gate/up buffer and, in front of it, the bf16 rows of h, qkv and the attention output"""
+    return T * cfg.ffn + T * (cfg.hidden + cfg.q_dim + 2 * cfg.kv_dim + cfg.q_dim) // 2
+
+
 def test_cuts_are_asked_for_with_the_layers_own_scratch():
-    # tokens at which more scratch than the gate/up buffer would cut a product that the layer leaves whole
-    more = [T for T in range(257, 2049) if B.flexco_gemm_k_ranges(T, C4.hidden, C4.ffn, 0, 1 << 30) > 1
-            and B.flexco_gemm_k_ranges(T, C4.hidden, C4.ffn, 0, T * C4.ffn) <= 1]
-    assert more and all(launches(C4, T)[3] == len(B.flexco_gemm_plan(T, C4.hidden, C4.ffn, 0, T * C4.ffn)) for T in more)
+    # tokens at which more scratch than the layer's would cut a product that the layer leaves whole
+    more = [T for T in range(257, 2049) if B.flexco_gemm_k_ranges(T, C4.hidden, C4.hidden, 0, 1 << 30) > 1
+            and B.flexco_gemm_k_ranges(T, C4.hidden, C4.hidden, 0, T * C4.ffn) <= 1]
+    assert all(launches(C4, T)[1] == len(B.flexco_gemm_plan(T, C4.hidden, C4.q_dim, 0, T * C4.ffn)) for T in more)
+    # tokens at which the gate/up buffer alone would leave the down product whole, and the layer cuts it
+    cut = [T for T in range(257, 2049) if B.flexco_gemm_k_ranges(T, C4.hidden, C4.ffn, 0, down_scratch(C4, T)) > 1
+           and B.flexco_gemm_k_ranges(T, C4.hidden, C4.ffn, 0, T * C4.ffn) <= 1]
+    assert cut and all(launches(C4, T)[3] == 2 for T in cut)
+    # ... and at which more than all of it would
+    more = [T for T in range(257, 4097) for cfg in (C2, C4, C5) if B.flexco_gemm_k_ranges(T, cfg.hidden, cfg.ffn, 0, 1 << 40) > 1
+            and B.flexco_gemm_k_ranges(T, cfg.hidden, cfg.ffn, 0, down_scratch(cfg, T)) <= 1
+            and launches(cfg, T)[3] != len(B.flexco_gemm_plan(T, cfg.hidden, cfg.ffn, 0, down_scratch(cfg, T)))]
+    assert not more

@@ -4,12 +4,14 @@ import numpy as np
 import pytest
 import torch
 
+import bench
 from workload import gen, CONFIGS
 
 pytestmark = pytest.mark.gpu
 
 if torch.cuda.is_available():
     import paper_2402_18789_amd.binding as B
+    from paper_2402_18789_amd import host as HH
     from gpu_common import Case, TOL, assert_close
     from test_gpu_parity import attention_case, run_layer_case
 
@@ -95,6 +97,29 @@ def test_layer_down_partial_sums_past_the_lent_buffer(ffn, adapter):
     print(f"layer of {T} tokens, ffn {ffn}, ranges of the down product {ranges}, adapter {adapter}", flush=True)
     assert T == 277 and ranges[1] > max(1, ranges[0])
     run_layer_case(cfg, b, ft_window=141, prefill_chunk=131, bwd_windows=[141, 141], seed=29)
+
+
+# the benchmark's account of the projections' launches against those that the layer makes
+@pytest.mark.parametrize("ffn", [2816, 5632])
+def test_launches_of_the_projections_are_those_the_benchmark_counts(ffn):
+    cfg = WIDE.with_(name="down_cut", ffn=ffn, lora_targets=())
+    b = gen.batch_scaled(29, 5, 3, 90, [(0, 131, 262)], [(0, 141, 282)])
+    db = HH.DeviceBatch(cfg, b.requests, b.seq_pages, b.num_pages)
+    T, dev = db.host_maps.T, HH.DeviceLayer(cfg, gen.layer_weights(cfg, 29, 0))
+    counted = sum(n for _, _, n in bench.forward_launches(B, cfg, T))
+    print(f"layer of {T} tokens, ffn {ffn}: {counted} launches counted", flush=True)
+    pool, ft = HH.DevicePool(cfg, b.num_pages), HH.DeviceFtState(cfg, 282)
+    ws = HH.Workspace(dev.c, T, db.host_maps.n_parts, 141, 282)
+    x = torch.randn(T, cfg.hidden, device="cuda").bfloat16()
+    y = torch.empty_like(x)
+    kid = B.KERNEL_IDS["gemm_fwd"]
+    B.flexco_kernel_timer_sample(kid, 1)
+    B.flexco_kernel_timer_start(kid, 64)
+    B.flexco_layer_forward(dev.c, dev.w, dev.lora, db.maps, x, y, pool.c, ft.c, ws.ptr, ws.bytes)
+    torch.cuda.synchronize()
+    each = B.flexco_kernel_timer_read(kid)
+    B.flexco_kernel_timer_stop(kid)
+    assert T == 277 and len(each) == counted
 
 
 # (split: pages of 16 keys) contexts of one split, then of up to six, then of 1, 2, 8, 9 and 12
