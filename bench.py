@@ -435,12 +435,15 @@ def algorithmic_work(cfg, batch, hm, maps_np=None):
 
 
 def measured_traffic(kernel_class):
-    """HBM bytes per launch from the committed rocprofv3 --pmc summary, if there is one."""
+    """HBM bytes per launch from the committed rocprofv3 --pmc summary, if there is one of the kernel named above."""
     path = os.path.join(ROOT, "profiles", "traffic_%s_c2.txt" % kernel_class)
     if not os.path.exists(path):
         return None
-    m = re.search(r"hbm_bytes_per_launch\s*=\s*([0-9.eE+]+)", open(path).read())
-    return float(m.group(1)) if m else None
+    text = open(path).read()
+    m = re.search(r"hbm_bytes_per_launch\s*=\s*([0-9.eE+]+)", text)
+    kernels = re.findall(r"\b\w+_kernel\b", text.split("\n", 1)[0])
+    named = re.findall(r"\b\w+_kernel\b", KERNEL_NAMES.get(kernel_class, ""))
+    return float(m.group(1)) if m and kernels and all(k in named for k in kernels) else None
 
 
 def roofline_entry(name, avg_launch_ms, launches_per_step, work):

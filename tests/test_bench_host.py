@@ -47,3 +47,12 @@ def test_cuts_are_asked_for_with_the_layers_own_scratch():
             and B.flexco_gemm_k_ranges(T, cfg.hidden, cfg.ffn, 0, down_scratch(cfg, T)) <= 1
             and launches(cfg, T)[3] != len(B.flexco_gemm_plan(T, cfg.hidden, cfg.ffn, 0, down_scratch(cfg, T)))]
     assert not more
+
+
+# the counted HBM bytes of a kernel are printed under that kernel's name only
+def test_traffic_is_of_the_kernel_it_is_printed_for(monkeypatch):
+    for name in ("attn_fwd", "gemm_fwd"):
+        assert bench.measured_traffic(name) > 1e6
+        assert bench.roofline_entry(name, 1.0, 1, {})["traffic"] == bench.measured_traffic(name)
+        monkeypatch.setitem(bench.KERNEL_NAMES, name, "another_kernel")
+        assert bench.measured_traffic(name) is None
