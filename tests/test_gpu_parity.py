@@ -121,7 +121,8 @@ def test_lora_fwd_segments(dtype, din, dout, r):
 # ------------------------------------------------------------------------------------------
 # mixed attention alone
 # ------------------------------------------------------------------------------------------
-def attention_case(cfg, batch, split, seed=3):
+def attention_case(cfg, batch, split, seed=3, unseen=0):
+    """unseen: scores of that many leading keys of every request are -inf"""
     case = Case(cfg, batch, seed=seed, kv_split_pages=split)
     om = build_maps(batch.requests, batch.seq_pages, batch.page_size, batch.num_pages)
     T = om["T"]
@@ -134,6 +135,12 @@ def attention_case(cfg, batch, split, seed=3):
         sl = case.o_pool.slots(pages, r.start_pos + r.n_new)[r.start_pos:]
         case.o_pool.k[sl], case.o_pool.v[sl] = k[r.start_pos:], v[r.start_pos:]
         case.d_pool.write_rows(pages, k[r.start_pos:], v[r.start_pos:], start=r.start_pos)
+        if unseen:
+            sl = case.o_pool.slots(pages, unseen)
+            case.o_pool.k[np.ix_(sl, np.arange(0, cfg.kv_dim, cfg.head_dim))] = -np.inf
+            case.d_pool.write_rows(pages, case.o_pool.k[sl], case.o_pool.v[sl])
+    if unseen:
+        q[:, ::cfg.head_dim] = 1.0
     db = HH.DeviceBatch(cfg, batch.requests, batch.seq_pages, batch.num_pages, split)
     ws = HH.Workspace(case.dev.c, T, db.host_maps.n_parts)
     dt = HH.TORCH_DTYPE[cfg.dtype]
@@ -234,6 +241,21 @@ def test_attention_mixed_folded_splits(name, split, fold, merge):
     expect_plan(cfg, batch, split, fold, merge)
     out, a_o, lse, lse_o = attention_case(cfg, batch, split)
     assert_close("attention out", out, a_o, TOL[cfg.dtype])
+    assert float(np.max(np.abs(lse - lse_o))) <= 2e-2
+
+
+# Stages and whole key ranges without a key that counts, in front of those with some: of chunks alone, beside decode tokens, of decode tokens
+# alone and on the one-wavefront kernel
+@pytest.mark.parametrize("split", [0, 4])
+@pytest.mark.parametrize("name", ["chunks", "mixed", "decode", "short"])
+def test_attention_leading_keys_of_no_weight(name, split):
+    say(f"attention, leading keys of no weight: {name} split={split}")
+    kw, unseen = {"chunks": (dict(prefill=[(500, 101, 601)], finetune=[(450, 77, 527)]), 420),
+                  "mixed": (dict(decode_ctx=(700, 1500, 450), prefill=[(500, 101, 601)]), 420),
+                  "decode": (dict(decode_ctx=(700, 1500, 450, 421)), 420), "short": (dict(decode_ctx=(60,) * 300), 40)}[name]
+    batch = gen.mixed_batch(16, 3, **kw)
+    out, a_o, lse, lse_o = attention_case(SMALL_BF16_MHA, batch, split, unseen=unseen)
+    assert_close("attention out", out, a_o, TOL["bf16"])
     assert float(np.max(np.abs(lse - lse_o))) <= 2e-2
 
 

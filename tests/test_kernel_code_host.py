@@ -75,3 +75,19 @@ def test_operands_of_the_products_are_not_written_just_before(code):
 def test_rows_of_the_generic_attention_backward_are_fetched_together(code, name, at_least):
     forms = {n: sum(op.startswith("v_readlane") for _, op, _ in ins) for n, ins in code.items() if name in n and not n.endswith(".kd")}
     assert len(forms) >= 6 and all(k >= at_least for k in forms.values()), forms
+
+
+# The attention's steps over pages that every row sees whole, lists of chunks alone: what a step does for its scores is what bounds it
+# so no select or compare beside those of the running maximum
+def test_attention_steps_of_chunks_alone_select_once(code):
+    (ins,) = [i for n, i in code.items() if "attn_fwd_chunk_kernelILi3E" in n and not n.endswith(".kd")]
+    at = {i[0]: k for k, i in enumerate(ins)}
+    loops = []
+    for k, (addr, op, args) in enumerate(ins):
+        if op.startswith("s_cbranch") or op == "s_branch":
+            off = int(args[0], 0) & 0xffff
+            to = at[addr + 4 + 4 * (off - 0x10000 if off & 0x8000 else off)]
+            body = [o for _, o, _ in ins[to:k + 1]]
+            if to < k and sum(o.startswith("v_mfma") for o in body) == 6 * 16:
+                loops.append((len(body), sum(o.startswith("v_cndmask") for o in body), sum(o.startswith("v_cmp") for o in body)))
+    assert loops and min(loops)[1:] == (6, 6), loops
