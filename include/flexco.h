@@ -433,7 +433,8 @@ int32_t flexco_gemm(const void* A, const void* W, void* C, const void* bias, con
  * but for the products flexco_gemm_k_ranges names.
  * part_elems: floats of split-K scratch the caller has (0 = none: flexco_gemm; the layer calls bring rows x 65536 for
  * windows of at most 256 rows and rows x 32768 for longer ones and for forward batches of at most 256 tokens; larger
- * forward batches bring rows x ffn for all but the gate/up projection).  out (host, 11 ints): out[0] = launches (1 or 2,
+ * forward batches bring rows x ffn for all but the gate/up projection, for the down projection with the memory of their
+ * norm output, qkv and attention output, rows x (hidden + 2 q_dim + 2 kv_dim) / 2, in front of it).  out (host, 11 ints): out[0] = launches (1 or 2,
  * side by side in the output columns), then per launch: tile rows, tile columns, output columns covered, blocks K is
  * cut over (in whole 64-wide stages, equal but for the 64-row tiles, whose ranges differ by one at most), stages of the
  * LDS ring; unused entries 0.  Errors: EINVAL (NULL, non-positive sizes), ESHAPE (K not a

@@ -6,7 +6,7 @@
 // and rematerialises P).  With delta_i = sum_d dO_id O_id:
 //     P_ij = exp(q_i . k_j / sqrt(d) - lse_i)           (j <= position of i)
 //     dP_ij = dO_i . v_j ,   dS_ij = P_ij (dP_ij - delta_i)
-//     dQ_i = sum_j dS_ij k_j / sqrt(d)                   -> kernel A, one block per 32 rows x head
+//     dQ_i = sum_j dS_ij k_j / sqrt(d)                   -> kernel A, one block per 32 or 64 rows x head
 //     dK_j = sum_i dS_ij q_i / sqrt(d),  dV_j = sum_i P_ij dO_i   summed over the window's rows
 //            and over the query heads of the kv group     -> kernel B, one block per 64 keys x kv head
 // Two kernels, each owning its outputs: no atomics, results do not depend on scheduling.  dK/dV are
@@ -16,7 +16,7 @@
 //   * The tiles a block walks over (K and V pages in kernel A; Q and dO rows in kernel B) go from
 //     global memory straight into LDS (global_load_lds_dwordx4, lane l lands at base + 16 l) in two
 //     buffer sets: the loads of step i + 1 are in flight while step i is multiplied, one barrier
-//     per step.
+//     per step (kernel B with four wavefronts: per two steps).
 //   * Operands whose contracted index is contiguous in memory are fetched with ds_read_b128;
 //     operands that must be read "across" rows (V and K^T in kernel A; Q^T, dO^T in kernel B) come
 //     from transposing LDS reads (ds_read_b64_tr_b16: in a group of 16 lanes, lane s hands in the
@@ -583,7 +583,7 @@ int32_t launch_attention_bwd_mfma(const flexco_layer_cfg& c, const flexco_kv_poo
   else if ((long)grid_a.x * grid_a.y > 256) hipLaunchKernelGGL((attn_bwd_dq_mfma_kernel<4, 1>), grid_a, dim3(256), 0, s, a);
   else hipLaunchKernelGGL((attn_bwd_dq_mfma_kernel<8, 1>), grid_a, dim3(512), 0, s, a);
   // kernel B: the same choice - with more blocks than CUs, four-wavefront blocks that walk all heads of the kv group
-  // in turn (33 KB of LDS, two blocks per CU): 7 - 9 % faster on the 4096-key windows
+  // in turn (65 KB of LDS, two blocks per CU): 7 - 9 % faster on the 4096-key windows
   const dim3 grid_b((a.l + 63) / 64, a.nkv);
   if ((long)grid_b.x * grid_b.y > 256) hipLaunchKernelGGL(attn_bwd_dkv_mfma_kernel<1>, grid_b, dim3(256), 0, s, a);
   else hipLaunchKernelGGL(attn_bwd_dkv_mfma_kernel<2>, grid_b, dim3(512), 0, s, a);

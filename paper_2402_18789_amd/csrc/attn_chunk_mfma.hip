@@ -1,16 +1,17 @@
-// Mixed paged attention, the chunk items on their own: prefill chunks and finetune windows whose rows are many
-// (Sec. 6.2: finetuning tokens follow the causal pattern of prefill).
+// Mixed paged attention, a block of four wavefronts per work item: prefill chunks and finetune windows
+// (Sec. 6.2: finetuning tokens follow the causal pattern of prefill) and, unless plan_attention takes the kernel of
+// attn_mfma.hip, decode tokens.
 //
-// The one-launch kernel of attn_mfma.hip gives a work item - up to four column tiles of one request x one key
-// split - to ONE wavefront, which fetches K / V pages from global memory into registers and multiplies them
-// against its tiles one after the other.  That suits the decode stream (one tile per item, the time is HBM's).
-// For long windows the time is the wavefront's own chain of products and exponentials per tile, four tiles deep,
-// with one wavefront per SIMD to run it.  Here the same item goes to a BLOCK of four wavefronts, one tile each:
-// the K / V pages of a step are staged once per block in LDS (straight from global memory, a ring of four stages
-// of two pages) and every wavefront reads its operands from there; 64 KB of LDS and under 256 registers put two
-// blocks on a CU.  The same products per tile and the same form of partial rows and direct outputs as the one-launch
-// kernel, so the merge kernel and everything after see no difference; the reference point of a column's
-// exponentials may lag its running maximum here (LAZY below), which moves results by rounding only.
+// The kernel of attn_mfma.hip gives a work item - up to four column tiles of one request x one key split - to ONE
+// wavefront, which fetches K / V pages from global memory into registers and multiplies them against its tiles one
+// after the other.  For long windows the time is then the wavefront's own chain of products and exponentials per tile,
+// four tiles deep, with one wavefront per SIMD to run it.  Here the same item goes to a BLOCK of four wavefronts, one
+// tile each: the K / V pages of a step are staged once per block in LDS (straight from global memory, a ring of four
+// stages of two pages) and every wavefront reads its operands from there; 65 KB of LDS and under 256 registers put two
+// blocks on a CU.  A decode token's block has a tile for one wavefront only; the others load, and its block may take
+// several key splits of the work list as one.  The same products per tile and the same form of partial rows and direct
+// outputs as the one-wavefront kernel, so the merge kernel and everything after see no difference; the reference point of a
+// column's exponentials may lag its running maximum here (LAZY below), which moves results by rounding only.
 //
 // bf16, head_dim 128, page_size 16, at most 16 query heads per kv head.
 #include "attn_plan.h"
@@ -41,7 +42,7 @@ struct ChunkArgs {
   size_t ldo;
   float* lse;         // or NULL
   AttnKeep keep;
-  int singles;        // single tokens too (else they are the one-launch kernel's)
+  int singles;        // single tokens too (else they are the one-wavefront kernel's)
   int fold;           // key splits of the work list that the block of a request of one token takes as one
   const int32_t* req_tok_off;
   float lag;          // LAZY, or 0: the reference points follow the maxima as in the one-wavefront kernel
@@ -63,7 +64,7 @@ __device__ inline bf16x4 lds_read_8(const bf16_t* p) {
 
 // RING = stages of the K / V ring.  4: 65 KB of LDS, two blocks per CU, two stages of loads in flight - the form for work
 // lists with decode tokens, whose pages stream from HBM (the benchmark batch 420 us, 437 with three stages; a 14B batch 568 and
-// 588), and beside the one-wavefront kernel.  3: 49 KB and at most 168 registers, three blocks per CU, one stage in flight -
+// 588; one form differs by up to 3 % from process to process), and beside the one-wavefront kernel.  3: 49 KB and at most 168 registers, three blocks per CU, one stage in flight -
 // 3 - 10 % faster where only chunks are left (three wavefronts per SIMD fill each other's waits).
 template <int RING>
 __global__ __launch_bounds__(256, RING == 3 ? 3 : 2) void attn_fwd_chunk_kernel(ChunkArgs a, const bf16_t* __restrict__ q, size_t ldq,
@@ -88,7 +89,7 @@ __global__ __launch_bounds__(256, RING == 3 ? 3 : 2) void attn_fwd_chunk_kernel(
   const int tok_first = a.tile_tok0[tile0], ntok_first = a.tile_ntok[tile0];
   const int tok_last = a.tile_tok0[tl] + a.tile_ntok[tl] - 1;
   const bool lone = ntl == 1 && ntok_first == 1;
-  if (!a.singles && lone) return;                          // the one-launch kernel's (whole block, before any barrier)
+  if (!a.singles && lone) return;                          // the one-wavefront kernel's (whole block, before any barrier)
   const int fold = a.fold > 1 && a.req_tok_off[r + 1] - a.req_tok_off[r] == 1 ? a.fold : 1;
   if (split % fold != 0) return;                           // the block of an earlier split takes this one's keys (whole block)
   const int group = a.nq / a.nkv;
@@ -423,7 +424,7 @@ __global__ __launch_bounds__(256, RING == 3 ? 3 : 2) void attn_fwd_chunk_kernel(
 }  // namespace
 
 // The chunk items of the work list (everything but single tokens) on the four-wavefront kernel; the caller
-// has the one-launch kernel skip them.  Same support test as launch_attention_mfma.  alone: the single tokens too.
+// has the one-wavefront kernel skip them.  Same support test as launch_attention_mfma.  alone: the single tokens too.
 int32_t launch_attention_chunk_mfma(const flexco_layer_cfg& c, const flexco_maps& m, const void* q, size_t ldq,
                                     const flexco_kv_pool& pool, float* part_ml, float* part_acc, void* out, size_t ldo,
                                     float* lse, hipStream_t s, const AttnKeep* keep, bool alone, int fold, bool lag) {

@@ -298,8 +298,9 @@ __global__ __launch_bounds__(256) void attn_merge128_kernel(const int32_t* __res
 //
 // Few of the lane groups' guards and LDS lookups of a 64-key run are needed: a lane owns channels lane + 64 u, u < DU = the least of
 // 1, 2, 4 that covers head_dim, and a key's (row's) factor and address come from the lane that holds them (lane_float,
-// lane_int) instead of from LDS (fp32 configuration 16.1 -> 11.2
-// us for dQ, 9.9 -> 8.2 for dK / dV: most of a run's instructions were guards of channels past head_dim).
+// lane_int) instead of from LDS (most of a run's instructions were guards of channels past head_dim), rows of several keys or pairs
+// at a time.  fp32 configuration 15.1 -> 10.3 us for dQ, 9.7 -> 6.0 for dK / dV; layer's backward of a window of 256 rows in 2048, bf16 of
+// head_dim 256 2610 -> 1990 us, 64 2390 -> 1880, fp32 of head_dim 64 2140 -> 1465.
 template <typename T, int DU>
 __global__ __launch_bounds__(64) void attn_bwd_dq_generic_kernel(const T* __restrict__ q, const T* __restrict__ dout,
                                                                  const T* __restrict__ out,
@@ -341,10 +342,9 @@ __global__ __launch_bounds__(64) void attn_bwd_dq_generic_kernel(const T* __rest
     const T* kr = kp + ((page * nkv + kvh) * ps + my_off) * (size_t)d;
     const T* vr = vp + ((page * nkv + kvh) * (size_t)d) * ps + my_off;
     float s = 0.f, dp = 0.f;
-    // eight rows of V on their way per lane (a V element is a load of its own; 32 for bf16, 16 for fp32 had too few wavefronts
-    // on a CU: window of 256 rows in 2048, head_dim 256 2524 -> 1819 us of the layer's backward, 64 2466 -> 2303, fp32 of
-    // head_dim 64 2195 -> 2092; and 32 with a grid that leaves slots empty 13.8 us against 11.2: code that runs once is
-    // fetched once, and fetching it is what such a launch waits for)
+    // eight rows of V on their way per lane (a V element is a load of its own): 32 for bf16 and 16 for fp32 had too few wavefronts
+    // on a CU; and where a grid leaves slots empty code that runs once is fetched once, and fetching it is what such a launch waits
+    // for (fp32 configuration, 32 rows 13.8 us, 8 rows 11.2 before the keys' rows came in groups)
     constexpr int U = 8 / N;
 #pragma unroll U
     for (int dd = 0; dd < d; dd += N) {
@@ -540,7 +540,7 @@ int32_t launch_attention_bwd_generic(const flexco_layer_cfg& c, const flexco_kv_
   if (c.head_dim <= 64) FLEXCO_BWD_GENERIC(1, VEC_, FEW_);       \
   else if (c.head_dim <= 128) FLEXCO_BWD_GENERIC(2, VEC_, FEW_); \
   else FLEXCO_BWD_GENERIC(4, VEC_, FEW_);
-  // (at most one wavefront per SIMD: more rows at a time per lane, fp32 configuration 8.2 -> 6.6 us)
+  // (at most one wavefront per SIMD: more rows at a time per lane, fp32 configuration 8.2 -> 6.6 us before the pairs' rows came in groups)
   if (vec && (long)l * c.n_kv_heads <= 1024) { FLEXCO_BWD_GENERIC_D(true, true) }
   else if (vec) { FLEXCO_BWD_GENERIC_D(true, false) }
   else { FLEXCO_BWD_GENERIC_D(false, false) }

@@ -570,7 +570,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
   // block) or C += sum_e A2_e W2_e (input-gradient form; every entry).  This is the LoRA bypass
   // network (Sec. 4.1) folded into the base projection as extra k-steps of 16, operands read
   // straight from global memory (they are [rows, r] / [r, cols] matrices of a few KB per tile).
-  // The first step's operands were fetched before the main loop where the tile leaves registers for them.
+  // The first PF steps' operands were fetched before the main loop where the tile leaves registers for them.
 #pragma unroll
   for (int u = 0; u < PF; ++u)
     if (u < n_pf) FLEXCO_EXT_MFMAS(paf[u], pbf[u])
@@ -1008,7 +1008,9 @@ static int thin_splits(int M, int N, int K, size_t part_elems) {
   if (sp > 1) sp = (int)std::min<size_t>(sp, part_elems / ((size_t)M * N));
   return std::max(sp, 1);
 }
-// Whether the column tiles of a product of one row tile start at stages of their own: rows of W a multiple of 4 KB apart.  A layer at the
+// Whether the column tiles of a product of one row tile start at stages of their own: rows of W a multiple of 4 KB apart.  Asked for the
+// 64-row tiles, 128 x 128 tiles cut over K and the gated 128 x 128 form on its deep ring; the whole 128 x 128 and 128 x 192 forms of up to
+// 128 rows (the loss head of a short window among them) walk K in order and were not measured with it.  A layer at the
 // 8B shape (8 and 28 KB), us: 1 token 116 -> 106, 8 tokens 123 -> 114, 30 tokens 143 -> 130, 70 tokens 185 -> 177, 128 tokens
 // 220 -> 210, 160 and 250 tokens (two row tiles) level; at the 14B and 32B shapes (10, 27 and 54 KB) 0.4 % slower with it.
 static bool spread_stages(int M, size_t ldw) { return M <= 128 && ldw % 2048 == 0; }
