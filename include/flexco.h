@@ -434,10 +434,10 @@ int32_t flexco_gemm(const void* A, const void* W, void* C, const void* bias, con
  * part_elems: floats of split-K scratch the caller has (0 = none: flexco_gemm; the layer calls bring rows x 65536 for
  * windows of at most 256 rows and rows x 32768 for longer ones and for forward batches of at most 256 tokens; larger
  * forward batches bring rows x ffn for all but the gate/up projection, for the down projection with the memory of their
- * norm output, qkv and attention output, rows x (hidden + 2 q_dim + 2 kv_dim) / 2, in front of it).  out (host, 11 ints): out[0] = launches (1 or 2,
- * side by side in the output columns), then per launch: tile rows, tile columns, output columns covered, blocks K is
- * cut over (in whole 64-wide stages, equal but for the 64-row tiles, whose ranges differ by one at most), stages of the
- * LDS ring; unused entries 0.  Errors: EINVAL (NULL, non-positive sizes), ESHAPE (K not a
+ * norm output, qkv and attention output, rows x (hidden + 2 q_dim + 2 kv_dim) / 2, in front of it).  out (host, 11
+ * ints): out[0] = launches (1 or 2, side by side in the output columns), then per launch: tile rows, tile columns,
+ * output columns covered, blocks K is cut over (in whole 64-wide stages, equal but for the 64-row tiles, whose ranges
+ * differ by one at most), stages of the LDS ring; unused entries 0.  Errors: EINVAL (NULL, non-positive sizes), ESHAPE (K not a
  * multiple of 64 or N not a multiple of 8: such products run on the type-generic kernels). */
 int32_t flexco_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t trans_w, int64_t part_elems, int32_t* out);
 /* Into how many ranges of whole 64-wide stages, equal to within one, the matrix-core path cuts K to run the same product

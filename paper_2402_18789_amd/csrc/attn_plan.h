@@ -31,7 +31,7 @@ FLEXCO_HOST_DEVICE inline int item_of_turn(int turn, int n_items, int fold) {
 // alone: the four-wavefront kernel takes the whole work list in one launch: its blocks, two or three per CU, keep as many
 // bytes on their way as the one-wavefront kernel's items did, and share a CU between streaming and multiplying blocks.  Measured
 // against what was done before (one kernel for everything, or the two beside each other on two streams; us): the 14B shape's 512 decode
-// tokens with 512 + 1024 chunk rows 641 -> 608, the 8B shape's 96 decode tokens beside 211 + 205 rows 122 -> 99, 217 decode
+// tokens with 512 + 1024 chunk rows 612 -> 568, the 8B shape's 96 decode tokens beside 211 + 205 rows 122 -> 99, 217 decode
 // tokens beside 279 + 40 rows 294 -> 108, 105 beside 74 + 73 166 -> 112, chunks of 713 + 487 + 205 rows without a decode token
 // 144 -> 67 (a last tile of one token had sent them to the pair of kernels).
 //
