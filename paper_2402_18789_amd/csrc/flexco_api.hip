@@ -700,7 +700,7 @@ int32_t run_attention(const flexco_layer_cfg& c, const flexco_maps& m, const voi
     const bool beside = mode == 2 && m.n_single > 0 && m.n_single < m.n_items;
     const bool chunk = mode > 0 || alone;
     if (!beside) {
-      // (with no item of its own the one-launch kernel has nothing left to do; its support test still decides)
+      // (with no item of its own the one-wavefront kernel has nothing left to do; its support test still decides)
       rc = launch_attention_mfma(c, m, q, ldq, pool, part_ml, part_acc, out, ldo, lse, s, keep, chunk, chunk && alone);
       if (rc == FLEXCO_OK && chunk)
         rc = launch_attention_chunk_mfma(c, m, q, ldq, pool, part_ml, part_acc, out, ldo, lse, s, keep, alone, fold, plan.lag);
