@@ -24,7 +24,7 @@ import numpy as np  # noqa: E402
 HBM_PEAK_GBS = 8000.0           # MI355X published HBM3E bandwidth
 MFMA_BF16_PEAK_TFLOPS = 2500.0  # MI355X published dense bf16
 KERNEL_NAMES = {"gemm_fwd": "gemm_bf16_kernel<BM,BN,false>, gemm_bf16_quad_kernel<BN,false> (forward projections)",
-                "gemm_bwd": "gemm_bf16_kernel<128,128,true>, gemm_bf16_quad_kernel<256,true> (input-gradient projections)",
+                "gemm_bwd": "gemm_bf16_pair_kernel, gemm_bf16_kernel<128,128,true>, gemm_bf16_quad_kernel<256,true> (input-gradient projections)",
                 "attn_fwd": "attn_fwd_chunk_kernel", "attn_merge": "attn_merge_kernel",
                 "attn_bwd": "attn_delta + attn_bwd_dq_mfma + attn_bwd_dkv_mfma", "elemwise": "norm/rope/swiglu/copy kernels",
                 "lora": "lora_shrink/finalize/outer kernels", "generic": "type-generic fallbacks"}

@@ -430,7 +430,8 @@ int32_t flexco_gemm(const void* A, const void* W, void* C, const void* bias, con
 /* How the bf16 matrix-core path would tile a product of these sizes (host arithmetic only: no GPU is touched, nothing
  * is launched) - the plan flexco_gemm, the frozen base projections over all tokens of the batch (Sec. 6.2; the gated
  * gate/up projection with N = 2 ffn) and the window backward's input-gradient products (Alg. 2; trans_w = 1) follow,
- * but for the products flexco_gemm_k_ranges names.
+ * but for the products flexco_gemm_k_ranges names and, ahead of both, input-gradient products of at most 256 tiles of
+ * 128 x 128 that run on one block of eight wavefronts per tile and range of K, in half the plan's ranges or fewer.
  * part_elems: floats of split-K scratch the caller has (0 = none: flexco_gemm; the layer calls bring rows x 65536 for
  * windows of at most 256 rows and rows x 32768 for longer ones and for forward batches of at most 256 tokens; larger
  * forward batches bring rows x ffn for all but the gate/up projection, for the down projection with the memory of their

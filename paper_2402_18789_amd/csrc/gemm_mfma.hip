@@ -818,6 +818,203 @@ __global__ __launch_bounds__(256) void gemm_bf16_quad_kernel(const bf16_t* __res
 #endif
 }
 
+// Input-gradient products of few row tiles: 128 x 128 tiles by eight wavefronts in two groups of four (2 x 2 of 64 x 64 each, two
+// wavefronts per SIMD).  A group multiplies its half of every stage's 64 of K, and the groups' sums are added through LDS at
+// the end.
+// What bounds these products is the weights' way in (256 rows at the 8B shape: about 50 GB/s per CU of operand tiles, whatever the
+// ring's depth; 0.65 us per stage with weights from HBM, 0.45 from the memory-side cache), and what they pay on top is partial sums: to
+// fill the chip with two blocks of four wavefronts per CU takes twice the ranges of K.  One block of eight has the second
+// wavefront per SIMD without them, and a ring of four stages instead of two.  Products and the launch that adds the ranges, us, M x N x K,
+// two blocks per CU -> this kernel (ranges): 256 x 14336 x 4096 57 -> 47 (2 -> 1), 256 x 4096 x 4096 26.7 -> 22.6 (8 -> 4),
+// 256 x 4096 x 6144 32.4 -> 27.7 (8 -> 4), 128 x 4096 x 28672 65 -> 58, 1024 x 4096 x 4096 54 -> 42 (4 -> 1).  A ring of five
+// stages and rows of A and W 128 or 256 bytes off the multiples of 4 KB: the same to 2 %; the forward form built this way: the
+// same as its four wavefronts.
+__global__ __launch_bounds__(512) void gemm_bf16_pair_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W,
+                                                             bf16_t* __restrict__ C, const bf16_t* __restrict__ bias,
+                                                             const bf16_t* __restrict__ res, int M, int N, int K,
+                                                             size_t lda, size_t ldw, size_t ldc, size_t ldr, int tiles_m,
+                                                             int tiles_n, GemmExt ext, float* __restrict__ part,
+                                                             GemmGlu glu) {
+#ifdef __HIP_DEVICE_COMPILE__
+  constexpr bool TRANS = true, GLU = false;
+  constexpr int BM = 128, BN = 128, NST = 4, NT = 4, NA = 2, NW = 2;       // NA, NW: load instructions of a wavefront and stage
+  constexpr int ST_ELEMS = (BM + BN) * BK;
+  int lid = blockIdx.x;
+  const int nblk = gridDim.x;
+  if ((nblk & 7) == 0) lid = (blockIdx.x & 7) * (nblk >> 3) + (blockIdx.x >> 3);
+  const int tm = lid % tiles_m, tn = lid / tiles_m;
+  const int m0 = tm * BM, n0 = tn * BN;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int grp = wave >> 2;
+  const int fm0 = ((wave >> 1) & 1) * 64, wn0 = (wave & 1) * 64;  // corner of the wavefront's 64 x 64
+  const int wm0 = fm0 + grp * 32;                                 // ... of the 32 x 64 it finishes
+  const int l16 = lane & 15, q4 = lane >> 4;
+  const int st_all = K / BK;
+  const int st_beg = (int)((long)st_all * blockIdx.y / gridDim.y);
+  const int ns = (int)((long)st_all * (blockIdx.y + 1) / gridDim.y) - st_beg;      // stages of this block (at least one)
+  const int kbeg = st_beg * BK;
+
+  __shared__ __attribute__((aligned(1024))) bf16_t ring0[ST_ELEMS];
+  __shared__ __attribute__((aligned(1024))) bf16_t ring1[ST_ELEMS];
+  __shared__ __attribute__((aligned(1024))) bf16_t ring2[ST_ELEMS];
+  __shared__ __attribute__((aligned(1024))) bf16_t ring3[ST_ELEMS];
+  const int d_row = lane >> 3;
+  const int d_c = (lane & 7) ^ FLEXCO_KEY(wave * 8 + d_row);
+  const int t_row = lane >> 4;
+  const int t_k = wave * 4 + t_row;
+  const int t_c = (lane & 15) ^ ((t_k & 3) << 2) ^ (((t_k >> 3) & 1) << 1);
+  unsigned oa[NA], ow[NW];
+#pragma unroll
+  for (int p = 0; p < NA; ++p) oa[p] = (unsigned)((size_t)min((p * 8 + wave) * 8 + d_row, M - 1 - m0) * lda * 2 + d_c * 16);
+#pragma unroll
+  for (int p = 0; p < NW; ++p) {
+    int col = t_c * 8;
+    if (n0 + col >= N) col = 0;   // masked at the store
+    ow[p] = (unsigned)((size_t)(p * 32 + t_k) * ldw * 2 + col * 2);
+  }
+  const char* const pa = (const char*)(A + (size_t)m0 * lda + kbeg);
+  const char* const pw = (const char*)(W + (size_t)kbeg * ldw + n0);
+  const size_t wstep = (size_t)BK * ldw * 2;
+  auto stage_at = [&](int s) { return (size_t)min(s, ns - 1); };
+  // load instruction q of a stage's NA + NW
+#define P_LOAD(ring_, q_)                                                                             \
+  {                                                                                                   \
+    if ((q_) < NA)                                                                                    \
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(sa_, FLEXCO_LP(ring_ + ((q_) * 8 + wave) * 512), 16, oa[(q_) < NA ? (q_) : 0], 0, 0, 0); \
+    else                                                                                              \
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(sw_, FLEXCO_LP(ring_ + BM * BK + (((q_) - NA) * 8 + wave) * 512), 16, ow[(q_) < NA ? 0 : (q_) - NA], 0, 0, 0); \
+  }
+#define P_DMA(ring_, s_)                                                                              \
+  {                                                                                                   \
+    const __amdgpu_buffer_rsrc_t sa_ = GEMM_SRC_A(s_), sw_ = GEMM_SRC_W(s_);                      \
+    _Pragma("unroll") for (int q = 0; q < NA + NW; ++q) P_LOAD(ring_, q)                              \
+  }
+  // element offsets of the wavefront's fragments in a stage, its half of K
+  int a_off[4], w_off[NT];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int r = fm0 + i * 16 + l16;
+    a_off[i] = r * BK + ((grp * 4 + q4) ^ FLEXCO_KEY(r)) * 8;
+  }
+#pragma unroll
+  for (int j = 0; j < NT; ++j) {
+    const int col = wn0 + j * 16 + 4 * (lane & 3);
+    w_off[j] = BM * BK + grp * 32 * BN + (8 * q4 + (l16 >> 2)) * BN + (((col >> 3) ^ ((l16 >> 2) << 2) ^ ((q4 & 1) << 1)) * 8) + (col & 7);
+  }
+#define P_FRAG(ring_, af_, bf_, q_)                                                                   \
+  {                                                                                                   \
+    if ((q_) < 4) {                                                                                   \
+      af_[(q_) & 3] = *reinterpret_cast<const frag_t*>(ring_ + a_off[(q_) & 3]);                      \
+    } else {                                                                                          \
+      const s16x4 lo_ = __builtin_amdgcn_ds_read_tr16_b64_v4i16((FLEXCO_LDS s16x4*)(ring_ + w_off[(q_) & 3]));            \
+      const s16x4 hi_ = __builtin_amdgcn_ds_read_tr16_b64_v4i16((FLEXCO_LDS s16x4*)(ring_ + (w_off[(q_) & 3] + 4 * BN))); \
+      bf_[(q_) & 3] = __builtin_shufflevector(__builtin_bit_cast(u32x2, lo_), __builtin_bit_cast(u32x2, hi_), 0, 1, 2, 3); \
+    }                                                                                                 \
+  }
+  // Before stage s's products: this wavefront's fragments of stage s are in registers and its loads of stage s + 1 have
+  // landed; behind the barrier that holds for all, so stage s's buffer takes the loads of stage s + NST.
+#define P_STAGE(cur_, nxt_, s_, af_, bf_, raf_, rbf_, pad_)                                           \
+  {                                                                                                   \
+    P_BARRIER((NST - 2) * (NA + NW))                                                                  \
+    const __amdgpu_buffer_rsrc_t sa_ = GEMM_SRC_A((s_) + NST), sw_ = GEMM_SRC_W((s_) + NST);      \
+    _Pragma("unroll") for (int n = 0; n < 16; ++n) {                                                  \
+      FLEXCO_MFMA(acc[n / NT][n % NT], bf_[n % NT], af_[n / NT], pad_)                                \
+      if (n < 8) P_FRAG(nxt_, raf_, rbf_, n)                                                          \
+      if (n >= 8 && n < 8 + NA + NW) P_LOAD(cur_, n - 8)                                              \
+      __builtin_amdgcn_sched_barrier(0);                                                              \
+    }                                                                                                 \
+  }
+#define P_BARRIER(vm_)                                                                                \
+  {                                                                                                   \
+    __builtin_amdgcn_sched_barrier(0);                                                                \
+    __builtin_amdgcn_s_waitcnt(Q_WAIT(vm_));                                                          \
+    asm volatile("" ::: "memory");                                                                    \
+    __builtin_amdgcn_s_barrier();                                                                     \
+    asm volatile("" ::: "memory");                                                                    \
+    __builtin_amdgcn_sched_barrier(0);                                                                \
+  }
+  const int ext_n = blockIdx.y == 0 ? ext.n : 0;
+  int ext_e = -1, ext_k = ext.r;
+  bf16x4 xa[2], xw[NT];
+  if (ext_n > 0) FLEXCO_EXT_NEXT(ext_e, ext_k)
+  const bool ext_on = ext_n > 0 && ext_e < ext_n;
+  if (ext_on) {
+    constexpr int MT = 2;
+    FLEXCO_EXT_LOAD(ext_e, ext_k, xa, xw)
+  }
+  f32x4 sum[2][NT];
+  // (a wavefront's piece of the free ring: 9216 bytes, three to a stage)
+  auto piece = [&](int w) { return reinterpret_cast<float*>((w < 3 ? ring0 : w < 6 ? ring1 : ring2) + (w % 3) * 4608); };
+  {
+    constexpr int MT = 4;
+    f32x4 acc[MT][NT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
+    frag_t af0[4], bf0[NT], af1[4], bf1[NT];
+    P_DMA(ring0, 0)
+    P_DMA(ring1, 1)
+    P_DMA(ring2, 2)
+    P_DMA(ring3, 3)
+    FLEXCO_ACC_FENCE
+    P_BARRIER((NST - 1) * (NA + NW))
+#pragma unroll
+    for (int q = 0; q < 8; ++q) P_FRAG(ring0, af0, bf0, q)
+    int st = 0;
+    for (; st + 3 < ns; st += 4) {
+      P_STAGE(ring0, ring1, st, af0, bf0, af1, bf1, "")
+      P_STAGE(ring1, ring2, st + 1, af1, bf1, af0, bf0, "")
+      P_STAGE(ring2, ring3, st + 2, af0, bf0, af1, bf1, "")
+      P_STAGE(ring3, ring0, st + 3, af1, bf1, af0, bf0, "")
+    }
+    if (st < ns) P_STAGE(ring0, ring1, st, af0, bf0, af1, bf1, FLEXCO_PAD)
+    if (st + 1 < ns) P_STAGE(ring1, ring2, st + 1, af1, bf1, af0, bf0, FLEXCO_PAD)
+    if (st + 2 < ns) P_STAGE(ring2, ring3, st + 2, af0, bf0, af1, bf1, FLEXCO_PAD)
+    __builtin_amdgcn_s_waitcnt(Q_WAIT(0));         // nothing may land in LDS after this
+    FLEXCO_ACC_FENCE
+    __syncthreads();                               // every wavefront is done with the ring
+    // each group hands the other the half of its sums that the other finishes
+    float* const out = piece(wave);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j) *reinterpret_cast<f32x4*>(out + (i * NT + j) * 256 + lane * 4) = grp ? acc[i][j] : acc[i + 2][j];
+    __syncthreads();
+    const float* const in = piece(wave ^ 4);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j) {
+        const f32x4 o = *reinterpret_cast<const f32x4*>(in + (i * NT + j) * 256 + lane * 4);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sum[i][j][r] = (grp ? acc[i + 2][j][r] : acc[i][j][r]) + o[r];
+      }
+  }
+  constexpr int MT = 2;
+  f32x4 (&acc)[MT][NT] = sum;
+  if (ext_on) {
+    FLEXCO_EXT_MFMAS(xa, xw)
+    FLEXCO_EXT_NEXT(ext_e, ext_k)
+    while (ext_e < ext_n) {
+      bf16x4 af[MT], bfr[NT];
+      FLEXCO_EXT_LOAD(ext_e, ext_k, af, bfr)
+      FLEXCO_EXT_MFMAS(af, bfr)
+      FLEXCO_EXT_NEXT(ext_e, ext_k)
+    }
+  }
+  // (turned in the piece that only this wavefront has read)
+  float* const stg = piece(wave ^ 4);
+  static_assert(32 * STORE_PITCH32 * 4 <= 9216, "the staged rows of a wavefront fit its piece");
+  const bf16x8 bpre[1] = {}, rpre[1][1][4] = {};
+  store_tile<MT, NT, false>(acc, stg, part ? part + (size_t)blockIdx.y * M * N : nullptr, C, ldc, bias, res, ldr, bpre, rpre, M, N,
+                            m0 + wm0, n0 + wn0, lane);
+#endif
+}
+
 // C[row, col] = sum over splits of part[split][row][col] (+ bias) (+ residual), fixed order
 __global__ __launch_bounds__(256) void gemm_splitk_reduce_kernel(const float* __restrict__ part, int splits,
                                                                  bf16_t* __restrict__ C, const bf16_t* __restrict__ bias,
@@ -854,17 +1051,20 @@ __global__ __launch_bounds__(256) void gemm_splitk_reduce_kernel(const float* __
   *reinterpret_cast<bf16x4*>(C + (size_t)row * ldc + col) = o;
 }
 
-template <int BM, int BN, bool TRANS, bool GLU = false, int NSTAGES = 0, bool SPREAD = false>
+// PAIR: the input-gradient kernel of eight wavefronts (128 x 128)
+template <int BM, int BN, bool TRANS, bool GLU = false, int NSTAGES = 0, bool SPREAD = false, bool PAIR = false>
 int32_t launch_cfg(const void* A, const void* W, void* C, const void* bias, const void* res, int M, int N, int K,
                    size_t lda, size_t ldw, size_t ldc, size_t ldr, const GemmExt& ext, hipStream_t s,
                    int timer_id, float* part = nullptr, int splits = 1, bool first_of_call = true,
                    const GemmGlu* glu_in = nullptr, bool skip_reduce = false) {
   // all LDS is static; the 256-row tiles have a kernel of their own
   constexpr bool QUAD = BM == 256;
-  constexpr int THREADS = 256;
+  constexpr int THREADS = PAIR ? 512 : 256;
+  static_assert(!PAIR || (TRANS && BM == 128 && BN == 128), "the kernel of eight wavefronts has one form");
   void (*kern)(const bf16_t*, const bf16_t*, bf16_t*, const bf16_t*, const bf16_t*, int, int, int, size_t, size_t, size_t, size_t,
                int, int, GemmExt, float*, GemmGlu);
   if constexpr (QUAD) kern = gemm_bf16_quad_kernel<BN, TRANS, GLU>;
+  else if constexpr (PAIR) kern = gemm_bf16_pair_kernel;
   else kern = gemm_bf16_kernel<BM, BN, TRANS, GLU, NSTAGES, SPREAD>;
   GemmGlu glu;
   if (glu_in) glu = *glu_in; else memset(&glu, 0, sizeof(glu));
@@ -1021,7 +1221,7 @@ static bool spread_stages(int M, size_t ldw) { return M <= 128 && ldw % 2048 == 
 // Measured (us, plan -> ranges): forward 1024 x 4096 x 14336 135 -> 99 (4), 2048 x 4096 x 14336 210 -> 172 (2),
 // 1405 x 5120 x 27648 400 -> 312 (2); input gradient 512 x 4096 x 128256 625 -> 419 (8), 512 x 4096 x 28672 152 -> 103 (8),
 // 1024 x 5120 x 7168 126 -> 74 (3), 1024 x 5120 x 5120 100 -> 60 (3), 256 x 4096 x 28672 91 -> 77 (12).
-int plan_gemm_k_ranges(int M, int N, int K, bool trans_w, size_t part_elems) {
+static int k_ranges(int M, int N, int K, bool trans_w, size_t part_elems, double* est_us) {
   if (!trans_w && M <= THIN_ROWS) return 0;         // the plan's 64 x 128 tiles
   const int ns = K / BK;
   const long tiles = (long)((M + 255) / 256) * ((N + 255) / 256);
@@ -1044,7 +1244,33 @@ int plan_gemm_k_ranges(int M, int N, int K, bool trans_w, size_t part_elems) {
     const double t = us_tile256(tiles * r, (double)((ns + r - 1) / r), 256) + us_partial_sums(r, M, N);
     if (t < us) { us = t; best = r; }
   }
+  if (est_us) *est_us = best ? us : us / 0.95;
   return best;
+}
+
+int plan_gemm_k_ranges(int M, int N, int K, bool trans_w, size_t part_elems) { return k_ranges(M, N, K, trans_w, part_elems, nullptr); }
+
+// Ranges of K (1: whole) to run an input-gradient product in on the 128 x 128 kernel of eight wavefronts, or 0: by the choice above
+// and the plan below.  One round of blocks only: more tiles than CUs are shared out better two blocks of four to a CU
+// (512 x 14336 x 4096 83 us on this kernel, 62 on 256 x 256 tiles).  Measured on 130 products of 33 to 1024 rows at the three models'
+// shapes, weights from HBM.  Against the plan's 128 x 128 tiles, two blocks to a CU: up to 256 rows 0.82 - 0.95 of their time (at 33
+// rows up to 1.07), with more rows 0.79 - 0.90 where the blocks fill the chip and 0.95 - 1.27 where they do not (640 x 4096 x 6144, 160
+// blocks: 59 against 46 us).  Against 256 x 256 tiles by the estimates (this one's within 12 %), which see those at few rows too low:
+// 150 x 14336 x 4096 39 us against 44 where they say 46 and 42.
+static int plan_gemm_pair(int M, int N, int K, size_t part_elems) {
+  const int ns = K / BK;
+  const long tiles = (long)((M + 127) / 128) * ((N + 127) / 128);
+  if (tiles > 256) return 0;
+  double us;
+  const bool large = k_ranges(M, N, K, true, part_elems, &us) > 0 || plan_gemm_mfma(M, N, K, true, part_elems).step[0].bm == 256;
+  us = large ? (M <= 192 ? 1.12 : 1.03) * us : 1e30;
+  int best = 0;
+  for (int r = 1; r <= 16 && tiles * r <= 256 && ns / r >= (r > 1 ? 4 : 1); ++r) {
+    if (r > 1 && (size_t)r * M * N > part_elems) break;
+    const double t = 6 + 0.62 * ((ns + r - 1) / r) + us_partial_sums(r, M, N);
+    if (t < us) { us = t; best = r; }
+  }
+  return !large && M > 256 && tiles * best < 250 ? 0 : best;
 }
 
 // What launch_gemm_mfma does for a shape: one or two launches, each a tile shape over a range of output columns,
@@ -1139,6 +1365,13 @@ int32_t launch_gemm_mfma(const void* A, const void* W, void* C, const void* bias
   if (ext_in) ext = *ext_in; else ext.n = 0;
   // splits_out: the caller's next kernel adds the partial sums itself (part[split][M][N], in split order) and
   // the reduction launch is left out; bias and residual are then not applied
+  const int pair = trans_w ? plan_gemm_pair(M, N, K, part ? part_elems : 0) : 0;
+  if (pair) {
+    const bool leave = splits_out && pair > 1 && !bias && !residual;
+    if (leave) *splits_out = pair;
+    return launch_cfg<128, 128, true, false, 0, false, true>(A, W, C, bias, residual, M, N, K, lda, ldw, ldc, ldr, ext, s, timer_id, part,
+                                                             pair, true, nullptr, leave);
+  }
   const int ranges = plan_gemm_k_ranges(M, N, K, trans_w, part ? part_elems : 0);
   if (ranges) {
     const bool leave = splits_out && ranges > 1 && !bias && !residual;

@@ -78,6 +78,22 @@ def test_input_gradient_tiles_128(M, N, K):
     run_gemm(M, N, K, 1, bias=False, res=False)
 
 
+# 128 x 128 tiles by eight wavefronts, two halves of every stage of K: one stage to two rounds of the ring of four, ragged last
+# rows and columns (in ranges of K and with a rank-r extension: the windows of test_gpu_model_iter and the loss head below)
+@pytest.mark.parametrize("K", [64 * n for n in (1, 2, 3, 4, 5, 7, 8, 9)])
+@pytest.mark.parametrize("M,N", [(1, 8), (33, 264), (127, 128), (129, 4104), (256, 1000)])
+def test_input_gradient_tiles_by_eight_wavefronts(M, N, K):
+    print(f"input gradient M={M} N={N} K={K}", flush=True)
+    run_gemm(M, N, K, 1, bias=False, res=False)
+
+
+# ... in ranges that differ by a stage (131 stages in 4, 67 in 8 and more)
+@pytest.mark.parametrize("n,H,V", [(200, 4096, 64 * 131), (100, 520, 64 * 67)])
+def test_input_gradient_by_eight_wavefronts_in_ranges(n, H, V):
+    print(f"loss head n={n} H={H} V={V}", flush=True)
+    run_loss("bf16", n, H, V, seed=5)
+
+
 @pytest.mark.parametrize("M,N,K", [(1023, 13832, 5120), (1000, 13816, 5184)])
 def test_input_gradient_tiles_256(M, N, K):
     print(f"input gradient M={M} N={N} K={K}", flush=True)

@@ -49,6 +49,13 @@ def test_projection_rings_are_not_overwritten_under_a_read(code):
         assert all(r == (0, 0) for r in reads), (args, reads)
 
 
+# The input-gradient kernel of eight wavefronts frees a stage's own buffer at its barrier, too.
+def test_ring_of_the_eight_wavefront_kernel_is_not_overwritten_under_a_read(code):
+    (ins,) = [i for n, i in code.items() if "gemm_bf16_pair_kernel" in n and not n.endswith(".kd")]
+    reads = gfx_code.lds_reads_at_barriers(ins)
+    assert len(reads) > 7 and all(r == (0, 0) for r in reads), reads
+
+
 # Attention: the buffer freed at a step's barrier is the one the step before has read (backward: two buffer sets; chunk
 # items: rings of three and four, whose V is read in the step that ends at the barrier).
 @pytest.mark.parametrize("name", ["attn_bwd_dq_mfma_kernel", "attn_bwd_dkv_mfma_kernel", "attn_fwd_chunk_kernel"])
