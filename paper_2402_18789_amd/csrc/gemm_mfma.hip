@@ -592,8 +592,9 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
 #endif
 }
 
-// The 256-row tiles (256 x 256, and 256 x 192 in the forward form): four wavefronts, one per SIMD, 2 x 2 of 128 x 128 (96) each.
-// (Written below for 256 columns; at 192 a W half-tile has 96 columns and a phase 64 x 48 of the wavefront's tile.)
+// The 256-row tiles (256 x 256, and 256 x 192 and 256 x 128 in the forward form): four wavefronts, one per SIMD, 2 x 2 of 128 x 128
+// (96, 64) each.  (Written below for 256 columns; at 192 (128) a W half-tile has 96 (64) columns and a phase 64 x 48 (32) of the
+// wavefront's tile.)
 //
 // What bounds it: the matrix pipes, if the loads keep up; a block of 64 KB per 64 columns of K needs about 3000 cycles of
 // cover for a load under load, and two whole 64 KB stages give 2048.  So LDS is eight half-tiles of 16 KB (two stages x
@@ -603,7 +604,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
 // load that will be read seven phases on (about 3500 cycles).  Every half-tile is read exactly once:
 //     even stage s:  A0 x W0 (reads W1(s)),  A0 x W1 (reads A1(s)),  A1 x W1 (reads A0(s + 1)),  A1 x W0 (reads W1(s + 1))
 //     odd stage s:   A0 x W1 (reads W0(s)),  A0 x W0 (reads A1(s)),  A1 x W0 (reads A0(s + 1)),  A1 x W1 (reads W0(s + 1))
-// The vmcnt before a phase's barrier: all but the six youngest half-tiles (NA = 4 or NW = 4 (3) instructions each) have landed.
+// The vmcnt before a phase's barrier: all but the six youngest half-tiles (NA = 4 or NW = 4 (3, 2) instructions each) have landed.
 // K is cut over gridDim.y blocks in whole stages, in ranges that differ by a stage at most.
 // Measured against two 64 KB stages of 32 x 32 x 16 products (M x N x K, N(0, 1) x N(0, 0.02) operands): forward
 // 2048 x 24576 x 5120 442 -> 383 us (1.35 PFLOP/s), 512 x 128256 x 4096 535 -> 435, 4096^3 114 -> 97; input gradient
@@ -623,7 +624,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_quad_kernel(const bf16_t* __res
 #ifdef __HIP_DEVICE_COMPILE__
   constexpr int BM = 256, MT = 8, NT = BN / 32, HN = NT / 2;      // HN: 16-column fragments of a phase
   constexpr int NA = 4, NW = BN / 64;                             // load instructions of a half-tile
-  static_assert(BN == 256 || (BN == 192 && !TRANS), "the input-gradient form's W tile swizzle assumes 256-byte rows");
+  static_assert(BN == 256 || ((BN == 192 || BN == 128) && !TRANS), "the input-gradient form's W tile swizzle assumes 256-byte rows");
   int lid = blockIdx.x;
   const int nblk = gridDim.x;
   if ((nblk & 7) == 0) lid = (blockIdx.x & 7) * (nblk >> 3) + (blockIdx.x >> 3);
@@ -723,17 +724,23 @@ __global__ __launch_bounds__(256) void gemm_bf16_quad_kernel(const bf16_t* __res
     }                                                                                                 \
   }
 #define Q_WAIT(n_) (0x0070 | ((n_) & 15) | (((n_) >> 4) << 14))      /* vmcnt(n), lgkmcnt(0) */
-  // a phase: 32 (24) products; behind each second one goes a read for the next phase, then the loads into the buffer the
-  // last phase has read.  At its end this wavefront's reads are in registers and its loads of the half-tile that is read
+  // a phase: 32 (24, 16) products; behind each second one (each of 16) goes a read for the next phase, then the loads into the
+  // buffer the last phase has read.  At its end this wavefront's reads are in registers and its loads of the half-tile that is read
   // next have landed (vm_: instructions of the six younger ones)
 #define Q_PHASE(READ_, rdst_, rbuf_, lbuf_, lsrc_, loff_, nl_, i0_, j0_, a_, w_, vm_, pad_)           \
   {                                                                                                   \
     const __amdgpu_buffer_rsrc_t src_ = lsrc_;                                                        \
     _Pragma("unroll") for (int n = 0; n < 8 * HN; ++n) {                                              \
       FLEXCO_MFMA(acc[i0_ + (n / HN) % 4][j0_ + n % HN], w_[n % HN][n / (4 * HN)], a_[(n / HN) % 4][n / (4 * HN)], pad_) \
-      if ((n & 1) && n < 16) READ_(rdst_, rbuf_, n >> 1)                                              \
-      if ((n & 1) && n >= 16 && n < 16 + 2 * nl_) Q_LOAD(lbuf_, src_, loff_, ((n - 16) >> 1) % nl_)   \
-      if (n & 1) __builtin_amdgcn_sched_barrier(0);                                                   \
+      if (HN > 2) {                                                                                   \
+        if ((n & 1) && n < 16) READ_(rdst_, rbuf_, n >> 1)                                            \
+        if ((n & 1) && n >= 16 && n < 16 + 2 * nl_) Q_LOAD(lbuf_, src_, loff_, ((n - 16) >> 1) % nl_) \
+        if (n & 1) __builtin_amdgcn_sched_barrier(0);                                                 \
+      } else {                                                                                        \
+        if (n < 8) READ_(rdst_, rbuf_, n)                                                             \
+        if (n >= 8 && n < 8 + nl_) Q_LOAD(lbuf_, src_, loff_, (n - 8) % nl_)                          \
+        __builtin_amdgcn_sched_barrier(0);                                                            \
+      }                                                                                               \
     }                                                                                                 \
     Q_END(vm_)                                                                                        \
   }
@@ -1273,6 +1280,27 @@ static int plan_gemm_pair(int M, int N, int K, size_t part_elems) {
   return !large && M > 256 && tiles * best < 250 ? 0 : best;
 }
 
+// Whether a forward product runs on 256 x 128 tiles, one launch over all columns, instead of by the choices above (other_us: their
+// estimated time).  They fill the chip where the others need a second round or leave CUs idle: measured against them, us,
+// 1200 x 6144 x 4096 64 -> 52, 2048 x 4096 x 4096 63 -> 52, 1024 x 7168 x 5120 98 -> 71, 1405 x 5120 x 5120 81 -> 65,
+// gated 256 x 28672 x 4096 83 -> 63.  Time: fitted to 150 products of 129 to 2048 rows.  A round of fewer than 164 blocks
+// has to win by a tenth (1024 x 5120 x 5120, 160 blocks: 68 us where 128 x 192 tiles take 65).
+static bool plan_gemm_256x128(int M, int N, int K, double other_us) {
+  const long blocks = (long)((M + 255) / 256) * ((N + 127) / 128), rounds = (blocks + 255) / 256;
+  const double over = std::max(0.0, (double)blocks / rounds - 128);
+  const double us = rounds * (5 + (double)(K / BK) * (0.70 + 0.0009 * over));
+  return M > 128 && us < (rounds == 1 && blocks >= 164 ? 0.99 : 0.90) * other_us;
+}
+
+// Forward products without a gate: the choice above against ranges of K and the plan.  0: the plan, 1: 256 x 128 tiles, else
+// ranges of K on 256 x 256 tiles.
+static int plan_gemm_forward(int M, int N, int K, size_t part_elems) {
+  if (M <= THIN_ROWS) return 0;
+  double us;
+  const int ranges = k_ranges(M, N, K, false, part_elems, &us);
+  return plan_gemm_256x128(M, N, K, us) ? 1 : ranges;
+}
+
 // What launch_gemm_mfma does for a shape: one or two launches, each a tile shape over a range of output columns,
 // possibly with K cut across blocks.  A pure function of the arguments (host arithmetic only).
 GemmLaunchPlan plan_gemm_mfma(int M, int N, int K, bool trans_w, size_t part_elems) {
@@ -1352,7 +1380,7 @@ static bool takes_product(const void* C, const void* bias, const void* residual,
 
 int gemm_forward_splits(const void* C, int M, int N, int K, size_t lda, size_t ldw, size_t ldc, const GemmExt* ext, size_t part_elems) {
   if (!takes_product(C, nullptr, nullptr, N, K, lda, ldw, ldc, 0, false, ext)) return 1;
-  const int ranges = plan_gemm_k_ranges(M, N, K, false, part_elems);
+  const int ranges = plan_gemm_forward(M, N, K, part_elems);
   return ranges ? ranges : plan_gemm_mfma(M, N, K, false, part_elems).step[0].splits;
 }
 
@@ -1372,7 +1400,9 @@ int32_t launch_gemm_mfma(const void* A, const void* W, void* C, const void* bias
     return launch_cfg<128, 128, true, false, 0, false, true>(A, W, C, bias, residual, M, N, K, lda, ldw, ldc, ldr, ext, s, timer_id, part,
                                                              pair, true, nullptr, leave);
   }
-  const int ranges = plan_gemm_k_ranges(M, N, K, trans_w, part ? part_elems : 0);
+  const int ranges = trans_w ? plan_gemm_k_ranges(M, N, K, true, part ? part_elems : 0) : plan_gemm_forward(M, N, K, part ? part_elems : 0);
+  if (!trans_w && ranges == 1)
+    return launch_cfg<256, 128, false>(A, W, C, bias, residual, M, N, K, lda, ldw, ldc, ldr, ext, s, timer_id);
   if (ranges) {
     const bool leave = splits_out && ranges > 1 && !bias && !residual;
     if (leave) *splits_out = ranges;
@@ -1451,6 +1481,8 @@ int32_t launch_gemm_glu_mfma(const void* A, const void* W, void* act, int M, int
     const auto thin = spread_stages(M, ldw) ? launch_cfg<THIN_ROWS, 128, false, true, 6, true> : launch_cfg<THIN_ROWS, 128, false, true, 6>;
     return thin(A, W, act, nullptr, nullptr, M, N, K, lda, ldw, ld_act, 0, ext, s, timer_id, nullptr, 1, true, &glu, false);
   }
+  if (plan_gemm_256x128(M, N, K, plan_forward(M, N, K).us))
+    return launch_cfg<256, 128, false, true>(A, W, act, nullptr, nullptr, M, N, K, lda, ldw, ld_act, 0, ext, s, timer_id, nullptr, 1, true, &glu);
   int c0 = 0;                                       // interleaved columns done = 2 x the act columns done
   for (int i = 0; i < pl.n; ++i) {
     const GemmLaunchStep& st = pl.step[i];

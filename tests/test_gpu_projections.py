@@ -44,6 +44,15 @@ def test_forward_tiles(tile, M, N, K):
     run_gemm(M, N, K, 0)
 
 
+# 256 x 128 tiles (one launch where the plan has two rounds or leaves CUs idle): odd and even numbers of stages, bias and residual
+# or neither, ragged last rows and columns
+@pytest.mark.parametrize("bias,res", [(True, True), (False, False)])
+@pytest.mark.parametrize("M,N,K", [(1000, 7160, 64 * 25), (1000, 7160, 64 * 20), (1200, 6152, 64 * 25), (769, 8192, 64 * 20)])
+def test_forward_tiles_256_by_128(M, N, K, bias, res):
+    print(f"forward M={M} N={N} K={K} bias {bias} residual {res}", flush=True)
+    run_gemm(M, N, K, 0, bias=bias, res=res)
+
+
 # at most 64 rows: 64 x 128 tiles with a ring of six stages
 @pytest.mark.parametrize("K", [64, 192, 384, 448, 704])
 @pytest.mark.parametrize("M,N", [(1, 8), (63, 136), (64, 1000)])

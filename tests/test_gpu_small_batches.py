@@ -49,6 +49,17 @@ def test_layer_products_from_their_own_stage(hidden, ffn, chunk, window):
     run_layer_case(cfg, b, ft_window=window, prefill_chunk=chunk, bwd_windows=[window, window], seed=17)
 
 
+# 129 to 256 tokens whose gated product covers the chip in one round of 256 x 128 tiles: adapter and finetune rows, a last
+# column tile of eight activations
+@pytest.mark.parametrize("chunk,window", [(60, 66), (141, 96)])
+def test_layer_gated_product_on_256_by_128_tiles(chunk, window):
+    cfg = WIDE.with_(name="gated_256_128", ffn=13832)
+    b = gen.batch_scaled(17, 4, 3, 90, [(0, chunk, 2 * chunk)], [(0, window, 2 * window)])
+    print(f"layer of {b.n_tokens} tokens, ffn {cfg.ffn}", flush=True)
+    assert 128 < b.n_tokens <= 256
+    run_layer_case(cfg, b, ft_window=window, prefill_chunk=chunk, bwd_windows=[window, window], seed=17)
+
+
 # K that is no multiple of 64 runs on the type-generic kernel, uncut, whatever the planner of the matrix-core path would
 # do with it: the qkv and down products (hidden, ffn), then o (q_dim = 27 x 48); few tokens, no adapter rows, a bias
 @pytest.mark.parametrize("hidden,heads,kv,d", [(2056, 16, 4, 128), (2048, 27, 9, 48), (1352, 11, 11, 128)])
