@@ -433,6 +433,7 @@ int32_t flexco_gemm(const void* A, const void* W, void* C, const void* bias, con
  * but for the products flexco_gemm_k_ranges names and, ahead of both, input-gradient products of at most 256 tiles of
  * 128 x 128 that run on one block of eight wavefronts per tile and range of K, in half the plan's ranges or fewer, and
  * forward products of more than 128 rows that run whole on 256 x 128 tiles, in one launch, where those are estimated faster.
+ * 256 tile rows stand for 160, 192, 224 or 256, whichever divides M with the least left over.
  * part_elems: floats of split-K scratch the caller has (0 = none: flexco_gemm; the layer calls bring rows x 65536 for
  * windows of at most 256 rows and rows x 32768 for longer ones and for forward batches of at most 256 tokens; larger
  * forward batches bring rows x ffn for all but the gate/up projection, for the down projection with the memory of their

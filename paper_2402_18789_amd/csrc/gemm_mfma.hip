@@ -23,7 +23,7 @@
 //     the same way, and an MFMA operand (8 consecutive k of one column) comes from two
 //     transposing LDS reads (ds_read_b64_tr_b16).
 // Work-group ids are remapped so that ids that land on the same XCD (id mod 8) work on
-// neighbouring tiles, M fastest: the W tile they share stays in that XCD's L2.
+// neighbouring tiles of the same range of K, M fastest: the W tile they share stays in that XCD's L2.
 #include <algorithm>
 #include <cstring>
 #include "flexco_internal.h"
@@ -90,13 +90,14 @@ __device__ __forceinline__ void store_tile_glu(const f32x4 (&acc)[MT][NT], bf16_
   const bool lane_on = (lane % LPRP) < LPR && ac_w + cl < ac_end;   // F % 8 == 0: a run of 8 is in or out as a whole
 #pragma unroll
   for (int i = 0; i < MT; i += 2) {
+    const int ni = i + 1 < MT ? 2 : 1;             // fragments of 16 rows in this group (compile-time after unrolling)
     const int rb = row0 + i * 16;
     const bool band_saves = glu.save_gate && rb + 32 > glu.save_row0 && rb < glu.save_row0 + glu.save_rows;   // uniform
 #pragma unroll
     for (int what = 0; what < 3; ++what) {         // 0: act, 1: gate, 2: up (the last two for finetune rows only)
       if (what > 0 && !band_saves) break;
 #pragma unroll
-      for (int ii = 0; ii < 2; ++ii)
+      for (int ii = 0; ii < ni; ++ii)
 #pragma unroll
         for (int f = 0; f < NT / 2; ++f) {
           bf16x4 o;
@@ -114,7 +115,7 @@ __device__ __forceinline__ void store_tile_glu(const f32x4 (&acc)[MT][NT], bf16_
       bf16_t* dst = what == 0 ? C : (what == 1 ? glu.save_gate : glu.save_up);
       const size_t ldd = what == 0 ? ldc : glu.ld_save;
 #pragma unroll
-      for (int p = 0; p < 32 / RPI; ++p) {
+      for (int p = 0; p < ni * 16 / RPI; ++p) {
         const int r = p * RPI + rl, row = rb + r;
         const int drow = what == 0 ? row : row - glu.save_row0;
         const bool ok = lane_on && row < M && (what == 0 || (drow >= 0 && drow < glu.save_rows));
@@ -137,12 +138,13 @@ __device__ __forceinline__ void store_tile(const f32x4 (&acc)[MT][NT], float* st
   const int l16 = lane & 15, q4 = lane >> 4;
 #pragma unroll
   for (int i = 0; i < MT; i += 2) {
+    const int ni = i + 1 < MT ? 2 : 1;               // fragments of 16 rows in this group (compile-time after unrolling)
     const int rb = row0 + i * 16;
 #pragma unroll
     for (int j0 = 0; j0 < NT; j0 += 4) {
       const int nj = (j0 + 2 < NT) ? 2 : 1;          // 32-column halves in this group (compile-time after unrolling)
 #pragma unroll
-      for (int ii = 0; ii < 2; ++ii)
+      for (int ii = 0; ii < ni; ++ii)
 #pragma unroll
         for (int jj = 0; jj < 4; ++jj) {
           if (jj >= 2 * nj) break;
@@ -153,7 +155,7 @@ __device__ __forceinline__ void store_tile(const f32x4 (&acc)[MT][NT], float* st
         // 16 lanes x 4 columns per row, 4 rows per instruction
         const int rl = lane >> 4, cl = (lane & 15) * 4;
 #pragma unroll
-        for (int p = 0; p < 8; ++p) {
+        for (int p = 0; p < 4 * ni; ++p) {
           const int r = p * 4 + rl, row = rb + r, col = cb + cl;
           if (cl < nj * 32 && row < M && col < N)    // N % 8 == 0: a run of 4 is inside or outside as a whole
             *reinterpret_cast<f32x4*>(P + (size_t)row * N + col) = *reinterpret_cast<const f32x4*>(stg + r * STORE_PITCH32 + cl);
@@ -162,7 +164,7 @@ __device__ __forceinline__ void store_tile(const f32x4 (&acc)[MT][NT], float* st
         // 8 lanes x 8 columns per row, 8 rows per instruction
         const int rl = lane >> 3, cl = (lane & 7) * 8;
 #pragma unroll
-        for (int p = 0; p < 4; ++p) {
+        for (int p = 0; p < 2 * ni; ++p) {
           const int r = p * 8 + rl, row = rb + r, col = cb + cl;
           if (cl < nj * 32 && row < M && col < N) {  // N % 8 == 0: a run of 8 is inside or outside as a whole
             const f32x4 lo = *reinterpret_cast<const f32x4*>(stg + r * STORE_PITCH32 + cl);
@@ -196,6 +198,25 @@ __device__ __forceinline__ void store_tile(const f32x4 (&acc)[MT][NT], float* st
   }
 }
 
+// Tile (of gridDim.x) and range of K (of gridDim.y) of this block.  Blocks go to the eight XCDs in turn, so the n-th block of an
+// XCD takes the n-th place of its eighth of all places, tile after tile within a range: an XCD works on one range or two, on
+// neighbouring columns, and reads their part of A only (with every range in every XCD, and no order at all for tiles that are no
+// multiple of eight: 1024 x 5120 x 13824 in 3 ranges 115 -> 106 us, input gradient 800 x 5120 x 27648 198 -> 170 (4)).  One row
+// tile shares no weights and keeps an XCD to columns of its own, over all ranges: rows of A a multiple of 4 KB apart put a range's
+// stage on one channel of the L2 (input gradient 256 x 4096 x 28672 82 us the other way, 78 this).
+__device__ __forceinline__ void place_of_block(int tiles_m, int* lid, int* range) {
+  if (tiles_m == 1 && (gridDim.x & 7) == 0) {
+    *range = blockIdx.y;
+    *lid = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    return;
+  }
+  const int at = blockIdx.y * gridDim.x + blockIdx.x, total = gridDim.x * gridDim.y;
+  const int xcd = at & 7, rest = total & 7;
+  const int place = xcd * (total >> 3) + min(xcd, rest) + (at >> 3);      // (the first `rest` XCDs have one more)
+  *range = place / (int)gridDim.x;
+  *lid = place - *range * (int)gridDim.x;
+}
+
 template <int BM, int BN, bool TRANS, bool GLU = false, int NSTAGES = 0, bool SPREAD = false>
 __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W,
                                                         bf16_t* __restrict__ C, const bf16_t* __restrict__ bias,
@@ -207,9 +228,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
   constexpr int WM = BM / 2, WN = BN / 2, MT = WM / 16, NT = WN / 16;
 
   // ---- work-group id -> tile, XCD-aware ------------------------------------------------
-  int lid = blockIdx.x;
-  const int nblk = gridDim.x;
-  if ((nblk & 7) == 0) lid = (blockIdx.x & 7) * (nblk >> 3) + (blockIdx.x >> 3);
+  int lid, range;
+  place_of_block(tiles_m, &lid, &range);
   const int tm = lid % tiles_m, tn = lid / tiles_m;
   const int m0 = tm * BM, n0 = tn * BN;
 
@@ -225,10 +245,10 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
 #pragma unroll
       for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
 
-  // split-K: blockIdx.y owns whole stages of K, in ranges that differ by one at most, and writes fp32 partial sums to `part`
+  // split-K: `range` owns whole stages of K, in ranges that differ by one at most, and writes fp32 partial sums to `part`
   const int st_all = K / BK;
-  const int st_beg = (int)((long)st_all * blockIdx.y / gridDim.y);
-  const int ns = (int)((long)st_all * (blockIdx.y + 1) / gridDim.y) - st_beg;      // stages of this block (at least one)
+  const int st_beg = (int)((long)st_all * range / gridDim.y);
+  const int ns = (int)((long)st_all * (range + 1) / gridDim.y) - st_beg;      // stages of this block (at least one)
   const int kbeg = st_beg * BK;
   const int l16 = lane & 15, q4 = lane >> 4;
 
@@ -474,7 +494,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
       do ++e_; while (e_ < ext.n && FLEXCO_EXT_SKIPS(e_));                                            \
     }                                                                                                 \
   }
-  const int ext_n = blockIdx.y == 0 ? ext.n : 0;
+  const int ext_n = range == 0 ? ext.n : 0;
   int ext_e = -1, ext_k = ext.r;                    // the first step that was not fetched ahead
   if (ext_n > 0) FLEXCO_EXT_NEXT(ext_e, ext_k) else ext_e = 0;
   int n_pf = 0;
@@ -587,7 +607,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
   } else {
     static_assert(2 * 32 * STORE_PITCH32 * 4 <= ST_ELEMS * 2, "the staged rows of two wavefronts fit a stage");
     store_tile<MT, NT, PF_RES>(acc, reinterpret_cast<float*>(wave < 2 ? ring0 : ring1) + (wave & 1) * 32 * STORE_PITCH32,
-                               part ? part + (size_t)blockIdx.y * M * N : nullptr, C, ldc, bias, res, ldr, bpre, rpre, M, N, m0 + wm0, n0 + wn0, lane);
+                               part ? part + (size_t)range * M * N : nullptr, C, ldc, bias, res, ldr, bpre, rpre, M, N, m0 + wm0, n0 + wn0, lane);
   }
 #endif
 }
@@ -612,9 +632,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
 // on zeros: 76 us) and, at K = 4096, the 10 us a tile's first loads and its epilogue take.  Eight wavefronts in two sets
 // that take turns at the matrix pipes and at LDS (64 x 128 each, half as many products per barrier) were as fast with
 // 32 x 32 x 16 products and read half as much again from LDS.
-constexpr int Q_HT = 128 * BK;        // elements of a half-tile: 128 rows x 64 K-columns, or 64 K-rows x 128 columns
-
-template <int BN, bool TRANS, bool GLU>
+template <int BM, int BN, bool TRANS, bool GLU>
 __global__ __launch_bounds__(256) void gemm_bf16_quad_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W,
                                                              bf16_t* __restrict__ C, const bf16_t* __restrict__ bias,
                                                              const bf16_t* __restrict__ res, int M, int N, int K,
@@ -622,22 +640,24 @@ __global__ __launch_bounds__(256) void gemm_bf16_quad_kernel(const bf16_t* __res
                                                              int tiles_n, GemmExt ext, float* __restrict__ part,
                                                              GemmGlu glu) {
 #ifdef __HIP_DEVICE_COMPILE__
-  constexpr int BM = 256, MT = 8, NT = BN / 32, HN = NT / 2;      // HN: 16-column fragments of a phase
-  constexpr int NA = 4, NW = BN / 64;                             // load instructions of a half-tile
+  // HM0, HM1, HN: 16-row fragments of A0 and A1 (one more in A0 where the tile has an odd number), 16-column fragments of a phase
+  constexpr int MT = BM / 32, NT = BN / 32, HM1 = MT / 2, HM0 = MT - HM1, HN = NT / 2;
+  constexpr int NA0 = HM0, NA1 = HM1, NW = HN;                    // load instructions of a half-tile
+  static_assert(BM % 32 == 0 && BM >= 160 && BM <= 256 && 2 * HM0 + NA1 <= 2 * HM1 * HN && 2 * HN + NA0 <= 2 * HM1 * HN,
+                "a half-tile is read and another's loads go out within a phase's products");
   static_assert(BN == 256 || ((BN == 192 || BN == 128) && !TRANS), "the input-gradient form's W tile swizzle assumes 256-byte rows");
-  int lid = blockIdx.x;
-  const int nblk = gridDim.x;
-  if ((nblk & 7) == 0) lid = (blockIdx.x & 7) * (nblk >> 3) + (blockIdx.x >> 3);
+  int lid, range;
+  place_of_block(tiles_m, &lid, &range);
   const int tm = lid % tiles_m, tn = lid / tiles_m;
   const int m0 = tm * BM, n0 = tn * BN;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
-  const int wm0 = wm * 128, wn0 = wn * (BN / 2);
+  const int wm0 = wm * (BM / 2), wn0 = wn * (BN / 2);
   const int l16 = lane & 15, q4 = lane >> 4;
   const int st_all = K / BK;
-  const int st_beg = (int)((long)st_all * blockIdx.y / gridDim.y);
-  const int ns = (int)((long)st_all * (blockIdx.y + 1) / gridDim.y) - st_beg;      // stages of this block (at least one)
+  const int st_beg = (int)((long)st_all * range / gridDim.y);
+  const int ns = (int)((long)st_all * (range + 1) / gridDim.y) - st_beg;      // stages of this block (at least one)
   const int kbeg = st_beg * BK;
 
   f32x4 acc[MT][NT];
@@ -649,10 +669,10 @@ __global__ __launch_bounds__(256) void gemm_bf16_quad_kernel(const bf16_t* __res
       for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
 
   // (separate arrays: the compiler then sees that loads in flight target an array no ds_read of that moment touches)
-  __shared__ __attribute__((aligned(1024))) bf16_t a0e[Q_HT];
-  __shared__ __attribute__((aligned(1024))) bf16_t a0o[Q_HT];
-  __shared__ __attribute__((aligned(1024))) bf16_t a1e[Q_HT];
-  __shared__ __attribute__((aligned(1024))) bf16_t a1o[Q_HT];
+  __shared__ __attribute__((aligned(1024))) bf16_t a0e[HM0 * 32 * BK];
+  __shared__ __attribute__((aligned(1024))) bf16_t a0o[HM0 * 32 * BK];
+  __shared__ __attribute__((aligned(1024))) bf16_t a1e[HM1 * 32 * BK];
+  __shared__ __attribute__((aligned(1024))) bf16_t a1o[HM1 * 32 * BK];
   __shared__ __attribute__((aligned(1024))) bf16_t w0e[HN * 32 * BK];
   __shared__ __attribute__((aligned(1024))) bf16_t w0o[HN * 32 * BK];
   __shared__ __attribute__((aligned(1024))) bf16_t w1e[HN * 32 * BK];
@@ -662,7 +682,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_quad_kernel(const bf16_t* __res
   // rows 4 (4 p + w) .. + 4 of [64][128].  16-byte chunk c of a 128-byte row r is stored at c ^ ((r / 2) % 8), of a
   // 256-byte row at c ^ 4 (r % 4) ^ 2 (r / 8 % 2) (as in the kernel above).  Byte offsets from the tile's own corner fit 32 bits. ----
   const int ac0 = GLU ? glu.col0 + tn * (BN / 2) : 0;
-  unsigned oa[2][NA], ow[2][NW];
+  unsigned oa0[NA0], oa1[NA1], ow[2][NW];
   {
     const int d_row = lane >> 3;
     const int d_c = (lane & 7) ^ (((wave * 8 + d_row) >> 1) & 7);
@@ -671,10 +691,11 @@ __global__ __launch_bounds__(256) void gemm_bf16_quad_kernel(const bf16_t* __res
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
       const int r = (p * 4 + wave) * 8 + d_row;
+      const int ra0 = (BM / 2) * (r / (16 * HM0)) + r % (16 * HM0), ra1 = (BM / 2) * (r / (16 * HM1)) + 16 * HM0 + r % (16 * HM1);
+      if (p < NA0) oa0[p < NA0 ? p : 0] = (unsigned)((size_t)min(ra0, M - 1 - m0) * lda * 2 + d_c * 16);     // tile row of a half-tile's row r
+      if (p < NA1) oa1[p < NA1 ? p : 0] = (unsigned)((size_t)min(ra1, M - 1 - m0) * lda * 2 + d_c * 16);
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const int ra = 128 * (r >> 6) + 64 * h + (r & 63);           // tile row of the half-tile's row r
-        oa[h][p] = (unsigned)((size_t)min(ra, M - 1 - m0) * lda * 2 + d_c * 16);
         if (p >= NW) continue;
         const int rt = (BN / 2) * (r / (BN / 4)) + (BN / 4) * h + r % (BN / 4);      // the same for rows of W
         if (GLU) {
@@ -695,11 +716,18 @@ __global__ __launch_bounds__(256) void gemm_bf16_quad_kernel(const bf16_t* __res
   const char* const pw = (const char*)(GLU ? W + (size_t)ac0 * ldw + kbeg : (TRANS ? W + (size_t)kbeg * ldw + n0 : W + (size_t)n0 * ldw + kbeg));
   const size_t wstep = TRANS ? (size_t)BK * ldw * 2 : (size_t)BK * 2;
   // (a stage past the end: clamped, the loads repeat the last stage into a free buffer)
-  auto stage_at = [&](int s) { return (size_t)min(s, ns - 1); };
+  // (one row tile, which the 128-column form is for, and rows of W a multiple of 4 KB apart: column tiles start at stages of
+  // their own, see the kernel above; gated 256 x 28672 x 4096 69 -> 63 us.  The other forms were 1 % slower for these three instructions a phase)
+  constexpr bool SPREAD = BN == 128;
+  const int first = SPREAD && tiles_m == 1 && (ldw & 2047) == 0 ? (int)((long)tn * ns / tiles_n) : 0;
+  auto stage_at = [&](int s) {
+    const int t = min(s, ns - 1) + first;
+    return (size_t)(SPREAD && t >= ns ? t - ns : t);
+  };
 #define Q_LOAD(buf_, src_, off_, p_) \
   __builtin_amdgcn_raw_ptr_buffer_load_lds(src_, FLEXCO_LP(buf_ + ((p_) * 4 + wave) * 512), 16, off_[p_], 0, 0, 0);
 #define Q_LOAD_A(buf_, h_, s_) \
-  { const __amdgpu_buffer_rsrc_t b_ = GEMM_SRC_A(s_); _Pragma("unroll") for (int p = 0; p < NA; ++p) Q_LOAD(buf_, b_, oa[h_], p) }
+  { const __amdgpu_buffer_rsrc_t b_ = GEMM_SRC_A(s_); _Pragma("unroll") for (int p = 0; p < NA##h_; ++p) Q_LOAD(buf_, b_, oa##h_, p) }
 #define Q_LOAD_W(buf_, g_, s_) \
   { const __amdgpu_buffer_rsrc_t b_ = GEMM_SRC_W(s_); _Pragma("unroll") for (int p = 0; p < NW; ++p) Q_LOAD(buf_, b_, ow[g_], p) }
   const int key = l16 >> 1;
@@ -712,7 +740,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_quad_kernel(const bf16_t* __res
   // fragment q_ (16 rows or columns x 32 of K) of the eight (six) a wavefront reads of a half-tile
 #define Q_READ_ROWS(dst_, buf_, rows_, n_, q_)                                                        \
   dst_[(q_) % n_][(q_) / n_] = *reinterpret_cast<const frag_t*>(buf_ + (rows_ + ((q_) % n_) * 16 + l16) * BK + ((((q_) / n_) * 4 + q4) ^ key) * 8);
-#define Q_READ_A(dst_, buf_, q_) if ((q_) < 8) Q_READ_ROWS(dst_, buf_, wm * 64, 4, (q_) & 7)
+#define Q_READ_A0(dst_, buf_, q_) if ((q_) < 2 * HM0) Q_READ_ROWS(dst_, buf_, wm * (16 * HM0), HM0, (q_) % (2 * HM0))
+#define Q_READ_A1(dst_, buf_, q_) if ((q_) < 2 * HM1) Q_READ_ROWS(dst_, buf_, wm * (16 * HM1), HM1, (q_) % (2 * HM1))
 #define Q_READ_W(dst_, buf_, q_)                                                                      \
   if ((q_) < 2 * HN) {                                                                                \
     if (!TRANS) {                                                                                     \
@@ -727,18 +756,19 @@ __global__ __launch_bounds__(256) void gemm_bf16_quad_kernel(const bf16_t* __res
   // a phase: 32 (24, 16) products; behind each second one (each of 16) goes a read for the next phase, then the loads into the
   // buffer the last phase has read.  At its end this wavefront's reads are in registers and its loads of the half-tile that is read
   // next have landed (vm_: instructions of the six younger ones)
-#define Q_PHASE(READ_, rdst_, rbuf_, lbuf_, lsrc_, loff_, nl_, i0_, j0_, a_, w_, vm_, pad_)           \
+#define Q_PHASE(READ_, nr_, rdst_, rbuf_, lbuf_, lsrc_, loff_, nl_, i0_, hm_, j0_, a_, w_, vm_, pad_)  \
   {                                                                                                   \
+    constexpr int PH = 2 * hm_ * HN;                               /* products of the phase */        \
     const __amdgpu_buffer_rsrc_t src_ = lsrc_;                                                        \
-    _Pragma("unroll") for (int n = 0; n < 8 * HN; ++n) {                                              \
-      FLEXCO_MFMA(acc[i0_ + (n / HN) % 4][j0_ + n % HN], w_[n % HN][n / (4 * HN)], a_[(n / HN) % 4][n / (4 * HN)], pad_) \
-      if (HN > 2) {                                                                                   \
+    _Pragma("unroll") for (int n = 0; n < PH; ++n) {                                                  \
+      FLEXCO_MFMA(acc[i0_ + (n / HN) % hm_][j0_ + n % HN], w_[n % HN][n / (hm_ * HN)], a_[(n / HN) % hm_][n / (hm_ * HN)], pad_) \
+      if (PH >= 24) {                                                                                 \
         if ((n & 1) && n < 16) READ_(rdst_, rbuf_, n >> 1)                                            \
         if ((n & 1) && n >= 16 && n < 16 + 2 * nl_) Q_LOAD(lbuf_, src_, loff_, ((n - 16) >> 1) % nl_) \
         if (n & 1) __builtin_amdgcn_sched_barrier(0);                                                 \
       } else {                                                                                        \
-        if (n < 8) READ_(rdst_, rbuf_, n)                                                             \
-        if (n >= 8 && n < 8 + nl_) Q_LOAD(lbuf_, src_, loff_, (n - 8) % nl_)                          \
+        if (n < nr_) READ_(rdst_, rbuf_, n)                                                           \
+        if (n >= nr_ && n < nr_ + nl_) Q_LOAD(lbuf_, src_, loff_, (n - nr_) % nl_)                    \
         __builtin_amdgcn_sched_barrier(0);                                                            \
       }                                                                                               \
     }                                                                                                 \
@@ -753,41 +783,41 @@ __global__ __launch_bounds__(256) void gemm_bf16_quad_kernel(const bf16_t* __res
     asm volatile("" ::: "memory");                                                                    \
     __builtin_amdgcn_sched_barrier(0);                                                                \
   }
-  // half-tiles in the order they are read: W A A W per stage
-  constexpr int VM0 = 3 * NA + 3 * NW, VM1 = 2 * NA + 4 * NW, VM2 = 3 * NA + 3 * NW, VM3 = 4 * NA + 2 * NW;
+  // (a stage's loads go out in the order W, W, A1, A0)
+  constexpr int VM0 = 2 * NA0 + NA1 + 3 * NW, VM1 = NA0 + NA1 + 4 * NW, VM2 = NA0 + 2 * NA1 + 3 * NW, VM3 = 2 * NA0 + 2 * NA1 + 2 * NW;
 #define Q_EVEN(s_, pad_)                                                                              \
   {                                                                                                   \
-    Q_PHASE(Q_READ_W, fw1, w1e, w0e, GEMM_SRC_W((s_) + 2), ow[0], NW, 0, 0, fa0, fw0, VM0, pad_)          \
-    Q_PHASE(Q_READ_A, fa1, a1e, w1e, GEMM_SRC_W((s_) + 2), ow[1], NW, 0, HN, fa0, fw1, VM1, pad_)         \
-    Q_PHASE(Q_READ_A, fa0, a0o, a1e, GEMM_SRC_A((s_) + 2), oa[1], NA, 4, HN, fa1, fw1, VM2, pad_)         \
-    Q_PHASE(Q_READ_W, fw1, w1o, a0o, GEMM_SRC_A((s_) + 3), oa[0], NA, 4, 0, fa1, fw0, VM3, pad_)          \
+    Q_PHASE(Q_READ_W, 2 * HN, fw1, w1e, w0e, GEMM_SRC_W((s_) + 2), ow[0], NW, 0, HM0, 0, fa0, fw0, VM0, pad_)        \
+    Q_PHASE(Q_READ_A1, 2 * HM1, fa1, a1e, w1e, GEMM_SRC_W((s_) + 2), ow[1], NW, 0, HM0, HN, fa0, fw1, VM1, pad_)     \
+    Q_PHASE(Q_READ_A0, 2 * HM0, fa0, a0o, a1e, GEMM_SRC_A((s_) + 2), oa1, NA1, HM0, HM1, HN, fa1, fw1, VM2, pad_)    \
+    Q_PHASE(Q_READ_W, 2 * HN, fw1, w1o, a0o, GEMM_SRC_A((s_) + 3), oa0, NA0, HM0, HM1, 0, fa1, fw0, VM3, pad_)       \
   }
 #define Q_ODD(s_, pad_)                                                                               \
   {                                                                                                   \
-    Q_PHASE(Q_READ_W, fw0, w0o, w1o, GEMM_SRC_W((s_) + 2), ow[1], NW, 0, HN, fa0, fw1, VM0, pad_)         \
-    Q_PHASE(Q_READ_A, fa1, a1o, w0o, GEMM_SRC_W((s_) + 2), ow[0], NW, 0, 0, fa0, fw0, VM1, pad_)          \
-    Q_PHASE(Q_READ_A, fa0, a0e, a1o, GEMM_SRC_A((s_) + 2), oa[1], NA, 4, 0, fa1, fw0, VM2, pad_)          \
-    Q_PHASE(Q_READ_W, fw0, w0e, a0e, GEMM_SRC_A((s_) + 3), oa[0], NA, 4, HN, fa1, fw1, VM3, pad_)         \
+    Q_PHASE(Q_READ_W, 2 * HN, fw0, w0o, w1o, GEMM_SRC_W((s_) + 2), ow[1], NW, 0, HM0, HN, fa0, fw1, VM0, pad_)       \
+    Q_PHASE(Q_READ_A1, 2 * HM1, fa1, a1o, w0o, GEMM_SRC_W((s_) + 2), ow[0], NW, 0, HM0, 0, fa0, fw0, VM1, pad_)      \
+    Q_PHASE(Q_READ_A0, 2 * HM0, fa0, a0e, a1o, GEMM_SRC_A((s_) + 2), oa1, NA1, HM0, HM1, 0, fa1, fw0, VM2, pad_)     \
+    Q_PHASE(Q_READ_W, 2 * HN, fw0, w0e, a0e, GEMM_SRC_A((s_) + 3), oa0, NA0, HM0, HM1, HN, fa1, fw1, VM3, pad_)      \
   }
   // The rank-r extension's steps (entry, 16 of its rank) in turn, entries that miss the tile left out.  The operands of the
   // first step are fetched here: their round trip lies open behind the main loop otherwise, every tile (1 % of a 1024-row
   // window's backward; two steps' operands, where there are registers for them, were no faster).
-  const int ext_n = blockIdx.y == 0 ? ext.n : 0;
+  const int ext_n = range == 0 ? ext.n : 0;
   int ext_e = -1, ext_k = ext.r;
   bf16x4 xa[MT], xw[NT];
   if (ext_n > 0) FLEXCO_EXT_NEXT(ext_e, ext_k)
   const bool ext_on = ext_n > 0 && ext_e < ext_n;
   if (ext_on) FLEXCO_EXT_LOAD(ext_e, ext_k, xa, xw)
-  frag_t fa0[4][2], fa1[4][2], fw0[HN][2], fw1[HN][2];
+  frag_t fa0[HM0][2], fa1[HM1][2], fw0[HN][2], fw1[HN][2];
   Q_LOAD_A(a0e, 0, 0) Q_LOAD_W(w0e, 0, 0) Q_LOAD_W(w1e, 1, 0) Q_LOAD_A(a1e, 1, 0)
   Q_LOAD_A(a0o, 0, 1) Q_LOAD_W(w1o, 1, 1) Q_LOAD_W(w0o, 0, 1) Q_LOAD_A(a1o, 1, 1)
-  Q_END(VM0)                                     // A0(0), W0(0) have landed
+  Q_END(VM2)                                     // A0(0), W0(0) have landed
 #pragma unroll
   for (int q = 0; q < 8; ++q) {
-    Q_READ_A(fa0, a0e, q)
+    Q_READ_A0(fa0, a0e, q)
     Q_READ_W(fw0, w0e, q)
   }
-  Q_END(VM0)
+  Q_END(VM2)
   Q_LOAD_A(a0e, 0, 2)
   FLEXCO_ACC_FENCE
   Q_END(VM3)                                     // W1(0)
@@ -812,14 +842,15 @@ __global__ __launch_bounds__(256) void gemm_bf16_quad_kernel(const bf16_t* __res
     }
   }
   __syncthreads();   // every wavefront is done with the half-tiles, and (after its own wait above) its loads have landed
-  // (one 16 KB half-tile per wavefront to turn its rows in)
-  bf16_t* const stg = wave == 0 ? a0e : wave == 1 ? a0o : wave == 2 ? a1e : a1o;
-  static_assert(32 * STORE_PITCH32 * 4 <= Q_HT * 2 && 32 * (NT * 8 + 8) <= Q_HT, "the staged rows of a wavefront fit a half-tile");
+  // (a half-tile per wavefront to turn its rows in)
+  bf16_t* const stg = wave == 0 ? a0e : wave == 1 ? a0o : wave == 2 ? (HM1 > 2 ? a1e : w0e) : (HM1 > 2 ? a1o : w0o);
+  constexpr int STG = (HM1 > 2 || HN > HM1 ? 3 : 2) * 32 * BK;     // elements of the smallest of them
+  static_assert(32 * STORE_PITCH32 * 4 <= STG * 2 && 32 * (NT * 8 + 8) <= STG, "the staged rows of a wavefront fit a half-tile");
   if constexpr (GLU) {
     store_tile_glu<MT, NT>(acc, stg, C, ldc, glu, M, N, m0 + wm0, glu.col0 + tn * (BN / 2) + (wn0 >> 1), lane);
   } else {
     bf16x8 bpre[1], rpre[1][1][4];
-    store_tile<MT, NT, false>(acc, reinterpret_cast<float*>(stg), part ? part + (size_t)blockIdx.y * M * N : nullptr, C, ldc,
+    store_tile<MT, NT, false>(acc, reinterpret_cast<float*>(stg), part ? part + (size_t)range * M * N : nullptr, C, ldc,
                               bias, res, ldr, bpre, rpre, M, N, m0 + wm0, n0 + wn0, lane);
   }
 #endif
@@ -846,9 +877,8 @@ __global__ __launch_bounds__(512) void gemm_bf16_pair_kernel(const bf16_t* __res
   constexpr bool TRANS = true, GLU = false;
   constexpr int BM = 128, BN = 128, NST = 4, NT = 4, NA = 2, NW = 2;       // NA, NW: load instructions of a wavefront and stage
   constexpr int ST_ELEMS = (BM + BN) * BK;
-  int lid = blockIdx.x;
-  const int nblk = gridDim.x;
-  if ((nblk & 7) == 0) lid = (blockIdx.x & 7) * (nblk >> 3) + (blockIdx.x >> 3);
+  int lid, range;
+  place_of_block(tiles_m, &lid, &range);
   const int tm = lid % tiles_m, tn = lid / tiles_m;
   const int m0 = tm * BM, n0 = tn * BN;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -858,8 +888,8 @@ __global__ __launch_bounds__(512) void gemm_bf16_pair_kernel(const bf16_t* __res
   const int wm0 = fm0 + grp * 32;                                 // ... of the 32 x 64 it finishes
   const int l16 = lane & 15, q4 = lane >> 4;
   const int st_all = K / BK;
-  const int st_beg = (int)((long)st_all * blockIdx.y / gridDim.y);
-  const int ns = (int)((long)st_all * (blockIdx.y + 1) / gridDim.y) - st_beg;      // stages of this block (at least one)
+  const int st_beg = (int)((long)st_all * range / gridDim.y);
+  const int ns = (int)((long)st_all * (range + 1) / gridDim.y) - st_beg;      // stages of this block (at least one)
   const int kbeg = st_beg * BK;
 
   __shared__ __attribute__((aligned(1024))) bf16_t ring0[ST_ELEMS];
@@ -941,7 +971,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_pair_kernel(const bf16_t* __res
     asm volatile("" ::: "memory");                                                                    \
     __builtin_amdgcn_sched_barrier(0);                                                                \
   }
-  const int ext_n = blockIdx.y == 0 ? ext.n : 0;
+  const int ext_n = range == 0 ? ext.n : 0;
   int ext_e = -1, ext_k = ext.r;
   bf16x4 xa[2], xw[NT];
   if (ext_n > 0) FLEXCO_EXT_NEXT(ext_e, ext_k)
@@ -1017,7 +1047,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_pair_kernel(const bf16_t* __res
   float* const stg = piece(wave ^ 4);
   static_assert(32 * STORE_PITCH32 * 4 <= 9216, "the staged rows of a wavefront fit its piece");
   const bf16x8 bpre[1] = {}, rpre[1][1][4] = {};
-  store_tile<MT, NT, false>(acc, stg, part ? part + (size_t)blockIdx.y * M * N : nullptr, C, ldc, bias, res, ldr, bpre, rpre, M, N,
+  store_tile<MT, NT, false>(acc, stg, part ? part + (size_t)range * M * N : nullptr, C, ldc, bias, res, ldr, bpre, rpre, M, N,
                             m0 + wm0, n0 + wn0, lane);
 #endif
 }
@@ -1058,6 +1088,45 @@ __global__ __launch_bounds__(256) void gemm_splitk_reduce_kernel(const float* __
   *reinterpret_cast<bf16x4*>(C + (size_t)row * ldc + col) = o;
 }
 
+// ---- estimated times, us, of launches of `blocks` blocks over `stages` 64-wide stages of K each.  Fitted to products of
+// 256 to 2048 rows at the 8B, 14B and 32B shapes with N(0, 1) x N(0, 0.02) operands, weights not in a cache; within 10 % of
+// each of some 150 measurements but for windows of 256 rows, which wait for HBM (up to 20 % above the estimate, all shapes
+// alike).  A launch runs in rounds over the CUs; a stage of the 256-row tiles takes longer the more CUs multiply at the
+// same time (the chip's power limit: 256 x 256 tiles 1.03 us at up to 128 blocks, 1.31 at 256).
+// The rows of a "256-row" tile are M's own: tiles of M / n rows in 32s for the fewest row tiles n, or for one more, so that the last
+// tile is not left half empty (gated 300 x 28672 x 4096 95 -> 74 us, 600 rows 161 -> 122, 800 rows 164 -> 151; input gradient
+// 300 x 4096 x 28672 96 -> 86).  cols: column tiles times ranges of K.  Narrow tiles of 160 rows were no faster than of 192.
+static double us_tile256(int M, long cols, double stages, int bn, int* rows = nullptr) {
+  double best = 1e300;
+  const int few = (M + 255) / 256;
+  for (int n = few; n <= few + 1; ++n) {
+    const int bm = std::max(((M + n - 1) / n + 31) / 32 * 32, bn == 256 ? 160 : 192);
+    const long blocks = n * cols, rounds = (blocks + 255) / 256;
+    // (in one round a tile more was as often slower where it is one of few: input gradient 512 x 14336 x 4096 66 -> 72 us)
+    if (n > few && rounds == 1 && few < 4) continue;
+    // (mean over the rounds of the blocks above 128; all rounds but the last are full)
+    const double over = ((rounds - 1) * 128 + std::max(0L, blocks - (rounds - 1) * 256 - 128)) / (double)rounds;
+    const double full = bn == 256 ? 1.03 + 0.0022 * over : bn == 192 ? 0.85 + 0.0013 * over : 0.70 + 0.0009 * over;
+    // a stage of fewer rows against one of 256, measured: 256, 192 and 128 columns wide, 160, 192 and 224 rows; in one round
+    // the weights' way in weighs more
+    static const double PART[2][3][3] = {{{0.82, 0.85, 0.90}, {1, 0.90, 0.96}, {1, 0.85, 0.95}}, {{0.72, 0.80, 0.90}, {1, 0.84, 0.95}, {1, 0.74, 0.92}}};
+    double part = bm == 256 ? 1.0 : PART[rounds > 1][bn == 256 ? 0 : bn == 192 ? 1 : 2][(bm - 160) / 32];
+    if (few == 1) part = std::max(part, 0.95);       // (... and is all there is with one row tile)
+    const double us = rounds * ((bn == 128 ? 5 : 9) + stages * full * part);
+    if (us < best * (n > few ? 0.98 : 1.0)) {
+      best = us;
+      if (rows) *rows = bm;
+    }
+  }
+  return best;
+}
+
+template <int BN, bool TRANS, bool GLU>
+auto quad_kernel(int rows) {
+  if constexpr (BN == 256) if (rows == 160) return gemm_bf16_quad_kernel<160, BN, TRANS, GLU>;
+  return rows == 256 ? gemm_bf16_quad_kernel<256, BN, TRANS, GLU> : rows == 224 ? gemm_bf16_quad_kernel<224, BN, TRANS, GLU> : gemm_bf16_quad_kernel<192, BN, TRANS, GLU>;
+}
+
 // PAIR: the input-gradient kernel of eight wavefronts (128 x 128)
 template <int BM, int BN, bool TRANS, bool GLU = false, int NSTAGES = 0, bool SPREAD = false, bool PAIR = false>
 int32_t launch_cfg(const void* A, const void* W, void* C, const void* bias, const void* res, int M, int N, int K,
@@ -1070,12 +1139,16 @@ int32_t launch_cfg(const void* A, const void* W, void* C, const void* bias, cons
   static_assert(!PAIR || (TRANS && BM == 128 && BN == 128), "the kernel of eight wavefronts has one form");
   void (*kern)(const bf16_t*, const bf16_t*, bf16_t*, const bf16_t*, const bf16_t*, int, int, int, size_t, size_t, size_t, size_t,
                int, int, GemmExt, float*, GemmGlu);
-  if constexpr (QUAD) kern = gemm_bf16_quad_kernel<BN, TRANS, GLU>;
+  int rows = BM;
+  if constexpr (QUAD) {
+    us_tile256(M, (long)((N + BN - 1) / BN) * splits, (double)((K / BK + splits - 1) / splits), BN, &rows);
+    kern = quad_kernel<BN, TRANS, GLU>(rows);
+  }
   else if constexpr (PAIR) kern = gemm_bf16_pair_kernel;
   else kern = gemm_bf16_kernel<BM, BN, TRANS, GLU, NSTAGES, SPREAD>;
   GemmGlu glu;
   if (glu_in) glu = *glu_in; else memset(&glu, 0, sizeof(glu));
-  const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
+  const int tiles_m = (M + rows - 1) / rows, tiles_n = (N + BN - 1) / BN;
   // while the class's timer runs, the kernels carry an event pair of their own (start and end stamps of
   // the dispatch itself)
   hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -1157,16 +1230,6 @@ static int pick_splits(int M, int N, int K, int tiles, size_t part_elems, int wa
 // takes the 256 x 256 tile, at the number of ranges that suits it, where that is estimated 5 % better.
 constexpr double TRANS_RATE_128 = 0.94, TRANS_RATE_256 = 1.05;
 
-// ---- estimated times, us, of launches of `blocks` blocks over `stages` 64-wide stages of K each.  Fitted to products of
-// 256 to 2048 rows at the 8B, 14B and 32B shapes with N(0, 1) x N(0, 0.02) operands, weights not in a cache; within 10 % of
-// each of some 150 measurements but for windows of 256 rows, which wait for HBM (up to 20 % above the estimate, all shapes
-// alike).  A launch runs in rounds over the CUs; a stage of the 256-row tiles takes longer the more CUs multiply at the
-// same time (the chip's power limit: 256 x 256 tiles 1.03 us at up to 128 blocks, 1.31 at 256).
-static double us_tile256(long blocks, double stages, int bn) {
-  const long rounds = (blocks + 255) / 256;
-  const double over = std::max(0.0, (double)blocks / rounds - 128);
-  return rounds * (9 + stages * (bn == 256 ? 1.03 + 0.0022 * over : 0.85 + 0.0013 * over));
-}
 static double us_tile128x192(long blocks, double stages) { return ((blocks + 255) / 256) * (4 + 0.76 * stages); }
 // 128 x 128: one four-stage block per CU, or with more blocks than CUs two two-stage blocks
 static double us_tile128(long blocks, double stages) {
@@ -1188,19 +1251,19 @@ struct GemmPlan {
 };
 static GemmPlan plan_forward(int M, int N, int K) {
   const double ns = K / BK;
-  const long tm256 = (M + 255) / 256, tm128 = (M + 127) / 128;
+  const long tm128 = (M + 127) / 128;
   GemmPlan best{0, 0, 1e300};
   const int n256 = (N + 255) / 256;
   for (int a = n256; a >= 0; --a) {
     const int rest = N - 256 * a;                   // columns left for the narrower tiles
     if (rest < 0 && a != n256) continue;
-    const double t_a = a ? us_tile256(tm256 * a, ns, 256) : 0.0;
+    const double t_a = a ? us_tile256(M, a, ns, 256) : 0.0;
     if (rest <= 0) {
       if (t_a < best.us - 1e-9) best = GemmPlan{a, 0, t_a};
       continue;
     }
     const long c192 = (rest + 191) / 192;
-    const double t_rest[3] = {us_tile128(tm128 * ((rest + 127) / 128), ns), us_tile128x192(tm128 * c192, ns), us_tile256(tm256 * c192, ns, 192)};
+    const double t_rest[3] = {us_tile128(tm128 * ((rest + 127) / 128), ns), us_tile128x192(tm128 * c192, ns), us_tile256(M, c192, ns, 192)};
     for (int sh = 2; sh >= 0; --sh)
       if (t_a + t_rest[sh] < best.us - 1e-9) best = GemmPlan{a, sh, t_a + t_rest[sh]};
   }
@@ -1231,7 +1294,7 @@ static bool spread_stages(int M, size_t ldw) { return M <= 128 && ldw % 2048 == 
 static int k_ranges(int M, int N, int K, bool trans_w, size_t part_elems, double* est_us) {
   if (!trans_w && M <= THIN_ROWS) return 0;         // the plan's 64 x 128 tiles
   const int ns = K / BK;
-  const long tiles = (long)((M + 255) / 256) * ((N + 255) / 256);
+  const long cols = (N + 255) / 256;
   const GemmLaunchPlan pl = plan_gemm_mfma(M, N, K, trans_w, part_elems);
   const GemmLaunchStep& st = pl.step[0];
   double us;
@@ -1241,17 +1304,17 @@ static int k_ranges(int M, int N, int K, bool trans_w, size_t part_elems, double
     const long blocks = (long)((M + st.bm - 1) / st.bm) * ((N + st.bn - 1) / st.bn) * st.splits;
     const double s = (double)ns / st.splits;
     // (the input-gradient form's 128 x 128 blocks have two stages whatever their number)
-    us = (st.bm == 256 ? us_tile256(blocks, s, 256) : !trans_w ? us_tile128(blocks, s)
+    us = (st.bm == 256 ? us_tile256(M, (long)((N + 255) / 256) * st.splits, s, 256) : !trans_w ? us_tile128(blocks, s)
           : blocks <= 256 ? 3 + 0.85 * s : ((blocks + 511) / 512) * (3 + 1.1 * s)) + us_partial_sums(st.splits, M, N);
   }
   int best = 0;
-  us *= 0.95;                                       // (the large tiles have to win clearly)
+  us *= trans_w ? 0.93 : 0.95;                      // (the large tiles have to win clearly)
   for (int r = trans_w ? 1 : 2; r <= 16 && ns / r >= 4; ++r) {
     if (r > 1 && (size_t)r * M * N > part_elems) break;
-    const double t = us_tile256(tiles * r, (double)((ns + r - 1) / r), 256) + us_partial_sums(r, M, N);
+    const double t = us_tile256(M, cols * r, (double)((ns + r - 1) / r), 256) + us_partial_sums(r, M, N);
     if (t < us) { us = t; best = r; }
   }
-  if (est_us) *est_us = best ? us : us / 0.95;
+  if (est_us) *est_us = best ? us : us / (trans_w ? 0.93 : 0.95);
   return best;
 }
 
@@ -1260,9 +1323,9 @@ int plan_gemm_k_ranges(int M, int N, int K, bool trans_w, size_t part_elems) { r
 // Ranges of K (1: whole) to run an input-gradient product in on the 128 x 128 kernel of eight wavefronts, or 0: by the choice above
 // and the plan below.  One round of blocks only: more tiles than CUs are shared out better two blocks of four to a CU
 // (512 x 14336 x 4096 83 us on this kernel, 62 on 256 x 256 tiles).  Measured on 130 products of 33 to 1024 rows at the three models'
-// shapes, weights from HBM.  Against the plan's 128 x 128 tiles, two blocks to a CU: up to 256 rows 0.82 - 0.95 of their time (at 33
-// rows up to 1.07), with more rows 0.79 - 0.90 where the blocks fill the chip and 0.95 - 1.27 where they do not (640 x 4096 x 6144, 160
-// blocks: 59 against 46 us).  Against 256 x 256 tiles by the estimates (this one's within 12 %), which see those at few rows too low:
+// shapes, weights from HBM.  Against the plan's 128 x 128 tiles, two blocks to a CU: 81 to 256 rows 0.82 - 0.95 of their time, with more
+// and with fewer rows 0.79 - 0.95 where the blocks fill the chip and 0.95 - 1.27 where they do not (640 x 4096 x 6144, 160
+// blocks: 59 against 46 us; 33 x 14336 x 4096, 224 blocks: 36 against 31).  Against 256 x 256 tiles by the estimates (this one's within 12 %), which see those at few rows too low:
 // 150 x 14336 x 4096 39 us against 44 where they say 46 and 42.
 static int plan_gemm_pair(int M, int N, int K, size_t part_elems) {
   const int ns = K / BK;
@@ -1277,7 +1340,7 @@ static int plan_gemm_pair(int M, int N, int K, size_t part_elems) {
     const double t = 6 + 0.62 * ((ns + r - 1) / r) + us_partial_sums(r, M, N);
     if (t < us) { us = t; best = r; }
   }
-  return !large && M > 256 && tiles * best < 250 ? 0 : best;
+  return !large && (M > 256 || M <= 80) && tiles * best < 250 ? 0 : best;
 }
 
 // Whether a forward product runs on 256 x 128 tiles, one launch over all columns, instead of by the choices above (other_us: their
@@ -1286,10 +1349,11 @@ static int plan_gemm_pair(int M, int N, int K, size_t part_elems) {
 // gated 256 x 28672 x 4096 83 -> 63.  Time: fitted to 150 products of 129 to 2048 rows.  A round of fewer than 164 blocks
 // has to win by a tenth (1024 x 5120 x 5120, 160 blocks: 68 us where 128 x 192 tiles take 65).
 static bool plan_gemm_256x128(int M, int N, int K, double other_us) {
-  const long blocks = (long)((M + 255) / 256) * ((N + 127) / 128), rounds = (blocks + 255) / 256;
-  const double over = std::max(0.0, (double)blocks / rounds - 128);
-  const double us = rounds * (5 + (double)(K / BK) * (0.70 + 0.0009 * over));
-  return M > 128 && us < (rounds == 1 && blocks >= 164 ? 0.99 : 0.90) * other_us;
+  const long cols = (N + 127) / 128;
+  int rows;
+  const double us = us_tile256(M, cols, K / BK, 128, &rows);
+  const long blocks = (M + rows - 1) / rows * cols;
+  return M > 128 && us < (blocks >= 164 && blocks <= 256 ? 0.99 : 0.90) * other_us;
 }
 
 // Forward products without a gate: the choice above against ranges of K and the plan.  0: the plan, 1: 256 x 128 tiles, else

@@ -53,6 +53,23 @@ def test_forward_tiles_256_by_128(M, N, K, bias, res):
     run_gemm(M, N, K, 0, bias=bias, res=res)
 
 
+# the 256-row kernel's rows are M's own, 160 to 256 in steps of 32: each of them at each width, even and odd numbers of stages
+@pytest.mark.parametrize("M,N,K", [(257, 24592, 512), (257, 24616, 448), (321, 24880, 512), (324, 24736, 448), (387, 24648, 512), (578, 16360, 448),
+                                   (673, 16368, 512), (449, 24656, 448), (131, 32824, 512), (132, 33208, 448), (386, 16544, 512), (194, 32864, 448),
+                                   (899, 8216, 512), (681, 10888, 448), (129, 29552, 512), (258, 11240, 576), (193, 29520, 512), (387, 14752, 448),
+                                   (674, 9840, 512), (900, 7336, 448)])
+def test_forward_tiles_of_the_rows_there_are(M, N, K):
+    print(f"forward M={M} N={N} K={K}", flush=True)
+    run_gemm(M, N, K, 0)
+
+
+@pytest.mark.parametrize("M,N,K", [(129, 33352, 512), (130, 32832, 448), (161, 32928, 512), (163, 32848, 448), (193, 32968, 512), (389, 16400, 448),
+                                   (674, 10984, 512), (675, 10952, 448)])
+def test_input_gradient_tiles_of_the_rows_there_are(M, N, K):
+    print(f"input gradient M={M} N={N} K={K}", flush=True)
+    run_gemm(M, N, K, 1, bias=False, res=False)
+
+
 # at most 64 rows: 64 x 128 tiles with a ring of six stages
 @pytest.mark.parametrize("K", [64, 192, 384, 448, 704])
 @pytest.mark.parametrize("M,N", [(1, 8), (63, 136), (64, 1000)])

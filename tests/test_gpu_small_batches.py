@@ -49,14 +49,14 @@ def test_layer_products_from_their_own_stage(hidden, ffn, chunk, window):
     run_layer_case(cfg, b, ft_window=window, prefill_chunk=chunk, bwd_windows=[window, window], seed=17)
 
 
-# 129 to 256 tokens whose gated product covers the chip in one round of 256 x 128 tiles: adapter and finetune rows, a last
-# column tile of eight activations
-@pytest.mark.parametrize("chunk,window", [(60, 66), (141, 96)])
-def test_layer_gated_product_on_256_by_128_tiles(chunk, window):
-    cfg = WIDE.with_(name="gated_256_128", ffn=13832)
+# A gated product that covers the chip in one round of 128-column tiles (up to 256 tokens) or 256-column ones, of 192, 256, 160, 192
+# and 224 rows; adapter and finetune rows, a last column tile of eight activations
+@pytest.mark.parametrize("chunk,window", [(60, 66), (141, 96), (150, 110), (200, 130), (220, 196)])
+def test_layer_gated_product_on_tiles_of_its_rows(chunk, window):
+    cfg = WIDE.with_(name="gated_rows", ffn=13832)
     b = gen.batch_scaled(17, 4, 3, 90, [(0, chunk, 2 * chunk)], [(0, window, 2 * window)])
     print(f"layer of {b.n_tokens} tokens, ffn {cfg.ffn}", flush=True)
-    assert 128 < b.n_tokens <= 256
+    assert 128 < b.n_tokens <= 448
     run_layer_case(cfg, b, ft_window=window, prefill_chunk=chunk, bwd_windows=[window, window], seed=17)
 
 
