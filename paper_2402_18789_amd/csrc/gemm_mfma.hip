@@ -1108,10 +1108,9 @@ static double us_tile256(int M, long cols, double stages, int bn, int* rows = nu
     const double over = ((rounds - 1) * 128 + std::max(0L, blocks - (rounds - 1) * 256 - 128)) / (double)rounds;
     const double full = bn == 256 ? 1.03 + 0.0022 * over : bn == 192 ? 0.85 + 0.0013 * over : 0.70 + 0.0009 * over;
     // a stage of fewer rows against one of 256, measured: 256, 192 and 128 columns wide, 160, 192 and 224 rows; in one round
-    // the weights' way in weighs more
+    // the weights' way in weighs more, and with one row tile it is all there is
     static const double PART[2][3][3] = {{{0.82, 0.85, 0.90}, {1, 0.90, 0.96}, {1, 0.85, 0.95}}, {{0.72, 0.80, 0.90}, {1, 0.84, 0.95}, {1, 0.74, 0.92}}};
-    double part = bm == 256 ? 1.0 : PART[rounds > 1][bn == 256 ? 0 : bn == 192 ? 1 : 2][(bm - 160) / 32];
-    if (few == 1) part = std::max(part, 0.95);       // (... and is all there is with one row tile)
+    const double part = bm == 256 || few == 1 ? 1.0 : PART[rounds > 1][bn == 256 ? 0 : bn == 192 ? 1 : 2][(bm - 160) / 32];
     const double us = rounds * ((bn == 128 ? 5 : 9) + stages * full * part);
     if (us < best * (n > few ? 0.98 : 1.0)) {
       best = us;
