@@ -302,20 +302,15 @@ __global__ __launch_bounds__(256) void attn_merge128_kernel(const int32_t* __res
 // at a time.  fp32 configuration 15.1 -> 10.3 us for dQ, 9.7 -> 6.0 for dK / dV; layer's backward of a window of 256 rows in 2048, bf16 of
 // head_dim 256 2610 -> 1990 us, 64 2390 -> 1880, fp32 of head_dim 64 2140 -> 1465.
 template <typename T, int DU>
-__global__ __launch_bounds__(64) void attn_bwd_dq_generic_kernel(const T* __restrict__ q, const T* __restrict__ dout,
-                                                                 const T* __restrict__ out,
-                                                                 const float* __restrict__ lse,
-                                                                 float* __restrict__ delta,
-                                                                 const T* __restrict__ kp, const T* __restrict__ vp,
-                                                                 const int32_t* __restrict__ pages,
-                                                                 T* __restrict__ dq, int win_start, int nq, int nkv,
-                                                                 int d, int ps, float scale) {
-  extern __shared__ float smem[];   // q[d], do[d]
+__device__ inline void bwd_dq_row(const size_t i, const int h, const T* __restrict__ q, const T* __restrict__ dout,
+                                  const T* __restrict__ out, const float* __restrict__ lse, float* __restrict__ delta,
+                                  const T* __restrict__ kp, const T* __restrict__ vp, const int32_t* __restrict__ pages,
+                                  T* __restrict__ dq, int win_start, int nq, int nkv, int d, int ps, float scale,
+                                  float* smem) {
   constexpr int N = Vec<T>::N;
-  float* qs = smem;
+  float* qs = smem;                 // smem: q[d], do[d]
   float* dos = smem + d;
-  const size_t i = blockIdx.x;
-  const int h = blockIdx.y, lane = threadIdx.x;
+  const int lane = threadIdx.x;
   const int group = nq / nkv, kvh = h / group;
   const int p = win_start + (int)i;
   const float row_lse = lse[i * nq + h];
@@ -380,22 +375,18 @@ __global__ __launch_bounds__(64) void attn_bwd_dq_generic_kernel(const T* __rest
 
 // one wave per (key j, kv head): sums over every window row that sees key j and every
 // query head of the group; adds into the KV-gradient accumulator rows (Sec. 7).
-// VEC: rows of q and dout are read 16 bytes at a time (their alignment is the caller's).
+// VEC: rows of q and dout are read 16 bytes at a time (their alignment is the caller's).  FEW: for launches that leave slots empty
+// (more rows at a time per lane), delta computed here from the rows of out.
 template <typename T, int DU, bool VEC, bool FEW>
-__global__ __launch_bounds__(64) void attn_bwd_dkv_generic_kernel(const T* __restrict__ q, const T* __restrict__ dout,
-                                                                  const float* __restrict__ lse,
-                                                                  const float* __restrict__ delta,
-                                                                  const T* __restrict__ kp, const T* __restrict__ vp,
-                                                                  const int32_t* __restrict__ pages,
-                                                                  float* __restrict__ dk_accum,
-                                                                  float* __restrict__ dv_accum, int win_start,
-                                                                  int win_len, int nq, int nkv, int d, int ps,
-                                                                  float scale) {
-  extern __shared__ float smem[];   // k[d], v[d]
+__device__ inline void bwd_dkv_key(const int j, const int kvh, const T* __restrict__ q, const T* __restrict__ dout,
+                                   const T* __restrict__ out, const float* __restrict__ lse, const float* __restrict__ delta,
+                                   const T* __restrict__ kp, const T* __restrict__ vp, const int32_t* __restrict__ pages,
+                                   float* __restrict__ dk_accum, float* __restrict__ dv_accum, int win_start, int win_len,
+                                   int nq, int nkv, int d, int ps, float scale, float* smem) {
   constexpr int N = VEC ? Vec<T>::N : 1;
-  float* ks = smem;
+  float* ks = smem;                 // smem: k[d], v[d]
   float* vs = smem + d;
-  const int j = blockIdx.x, kvh = blockIdx.y, lane = threadIdx.x;
+  const int lane = threadIdx.x;
   const int group = nq / nkv;
   const size_t page = pages[j / ps];
   for (int dd = lane; dd < d; dd += 64) {
@@ -414,7 +405,8 @@ __global__ __launch_bounds__(64) void attn_bwd_dkv_generic_kernel(const T* __res
     const size_t row = (size_t)my_i * nq + my_h;                // of q and dout
     const T* qr = q + row * d;
     const T* dor = dout + row * d;
-    const float row_lse = lse[row], row_delta = delta[row];
+    const float row_lse = lse[row];
+    float row_delta = FEW ? 0.f : delta[row];
     float s = 0.f, dp = 0.f;
 #pragma unroll VEC ? (FEW ? 8 : 4) : 2
     for (int dd = 0; dd < d; dd += N) {
@@ -430,6 +422,12 @@ __global__ __launch_bounds__(64) void attn_bwd_dkv_generic_kernel(const T* __res
       for (int e = 0; e < N; ++e) {
         s += qv[e] * ks[dd + e];
         dp += ov[e] * vs[dd + e];
+      }
+      if constexpr (FEW) {
+        float av[N];
+        Vec<T>::load(out + row * d + dd, av);
+#pragma unroll
+        for (int e = 0; e < N; ++e) row_delta += av[e] * ov[e];
       }
     }
     const float pj = pc + lane < n_pairs ? __expf(s * scale - row_lse) : 0.f;
@@ -458,6 +456,49 @@ __global__ __launch_bounds__(64) void attn_bwd_dkv_generic_kernel(const T* __res
       dv_accum[((size_t)j * nkv + kvh) * d + dd] += dv[u];
     }
   }
+}
+
+// dQ of a (window row, query head) per block, delta left for the kernel below
+template <typename T, int DU>
+__global__ __launch_bounds__(64) void attn_bwd_dq_generic_kernel(const T* __restrict__ q, const T* __restrict__ dout,
+                                                                 const T* __restrict__ out, const float* __restrict__ lse,
+                                                                 float* __restrict__ delta, const T* __restrict__ kp,
+                                                                 const T* __restrict__ vp, const int32_t* __restrict__ pages,
+                                                                 T* __restrict__ dq, int win_start, int nq, int nkv, int d,
+                                                                 int ps, float scale) {
+  extern __shared__ float smem[];
+  bwd_dq_row<T, DU>(blockIdx.x, blockIdx.y, q, dout, out, lse, delta, kp, vp, pages, dq, win_start, nq, nkv, d, ps, scale, smem);
+}
+
+template <typename T, int DU, bool VEC>
+__global__ __launch_bounds__(64) void attn_bwd_dkv_generic_kernel(const T* __restrict__ q, const T* __restrict__ dout,
+                                                                  const float* __restrict__ lse, const float* __restrict__ delta,
+                                                                  const T* __restrict__ kp, const T* __restrict__ vp,
+                                                                  const int32_t* __restrict__ pages, float* __restrict__ dk_accum,
+                                                                  float* __restrict__ dv_accum, int win_start, int win_len, int nq,
+                                                                  int nkv, int d, int ps, float scale) {
+  extern __shared__ float smem[];
+  bwd_dkv_key<T, DU, VEC, false>(blockIdx.x, blockIdx.y, q, dout, (const T*)nullptr, lse, delta, kp, vp, pages, dk_accum, dv_accum,
+                                 win_start, win_len, nq, nkv, d, ps, scale, smem);
+}
+
+// Both in one launch, the rows of dQ first (their blocks walk longer): nothing of one is read by the other, as a key's block
+// computes delta itself.
+template <typename T, int DU>
+__global__ __launch_bounds__(64) void attn_bwd_few_generic_kernel(const T* __restrict__ q, const T* __restrict__ dout,
+                                                                  const T* __restrict__ out, const float* __restrict__ lse,
+                                                                  float* __restrict__ delta, const T* __restrict__ kp,
+                                                                  const T* __restrict__ vp, const int32_t* __restrict__ pages,
+                                                                  T* __restrict__ dq, float* __restrict__ dk_accum,
+                                                                  float* __restrict__ dv_accum, int win_start, int win_len, int nq,
+                                                                  int nkv, int d, int ps, float scale) {
+  extern __shared__ float smem[];
+  const int n_dq = win_len * nq, b = blockIdx.x;
+  if (b < n_dq)
+    bwd_dq_row<T, DU>(b / nq, b % nq, q, dout, out, lse, delta, kp, vp, pages, dq, win_start, nq, nkv, d, ps, scale, smem);
+  else
+    bwd_dkv_key<T, DU, true, true>((b - n_dq) / nkv, (b - n_dq) % nkv, q, dout, out, lse, delta, kp, vp, pages, dk_accum, dv_accum,
+                                   win_start, win_len, nq, nkv, d, ps, scale, smem);
 }
 
 #define DISPATCH_T(dtype, ...)                                   \
@@ -527,24 +568,35 @@ int32_t launch_attention_bwd_generic(const flexco_layer_cfg& c, const flexco_kv_
   const int l = win_start + win_len;
   const size_t shm = sizeof(float) * 2 * (size_t)c.head_dim;
   const bool vec = aligned16(q) && aligned16(dout);      // (head_dim rows are whole 16-byte units)
-#define FLEXCO_BWD_GENERIC(DU_, VEC_, FEW_)                                                                            \
+#define FLEXCO_BWD_GENERIC(DU_, VEC_)                                                                                  \
   DISPATCH_T(c.dtype, {                                                                                               \
     hipLaunchKernelGGL((attn_bwd_dq_generic_kernel<T, DU_>), dim3(win_len, c.n_q_heads), dim3(64), shm, s, (const T*)q, (const T*)dout, \
                        (const T*)out, lse, delta, (const T*)pool.k_pages, (const T*)pool.v_pages, seq_pages, (T*)dq, win_start,         \
                        c.n_q_heads, c.n_kv_heads, c.head_dim, c.page_size, scale);                                    \
-    hipLaunchKernelGGL((attn_bwd_dkv_generic_kernel<T, DU_, VEC_, FEW_>), dim3(l, c.n_kv_heads), dim3(64), shm, s, (const T*)q, (const T*)dout, \
+    hipLaunchKernelGGL((attn_bwd_dkv_generic_kernel<T, DU_, VEC_>), dim3(l, c.n_kv_heads), dim3(64), shm, s, (const T*)q, (const T*)dout, \
                        lse, delta, (const T*)pool.k_pages, (const T*)pool.v_pages, seq_pages, dk_accum, dv_accum, win_start, win_len,   \
                        c.n_q_heads, c.n_kv_heads, c.head_dim, c.page_size, scale);                                    \
   })
-#define FLEXCO_BWD_GENERIC_D(VEC_, FEW_)                         \
-  if (c.head_dim <= 64) FLEXCO_BWD_GENERIC(1, VEC_, FEW_);       \
-  else if (c.head_dim <= 128) FLEXCO_BWD_GENERIC(2, VEC_, FEW_); \
-  else FLEXCO_BWD_GENERIC(4, VEC_, FEW_);
-  // (at most one wavefront per SIMD: more rows at a time per lane, fp32 configuration 8.2 -> 6.6 us before the pairs' rows came in groups)
-  if (vec && (long)l * c.n_kv_heads <= 1024) { FLEXCO_BWD_GENERIC_D(true, true) }
-  else if (vec) { FLEXCO_BWD_GENERIC_D(true, false) }
-  else { FLEXCO_BWD_GENERIC_D(false, false) }
-#undef FLEXCO_BWD_GENERIC_D
+#define FLEXCO_BWD_FEW(DU_)                                                                                            \
+  DISPATCH_T(c.dtype, hipLaunchKernelGGL((attn_bwd_few_generic_kernel<T, DU_>), dim3(win_len * c.n_q_heads + l * c.n_kv_heads), dim3(64), \
+                                         shm, s, (const T*)q, (const T*)dout, (const T*)out, lse, delta, (const T*)pool.k_pages, \
+                                         (const T*)pool.v_pages, seq_pages, (T*)dq, dk_accum, dv_accum, win_start, win_len, \
+                                         c.n_q_heads, c.n_kv_heads, c.head_dim, c.page_size, scale))
+#define FLEXCO_BWD_D(MACRO_, ...)                            \
+  if (c.head_dim <= 64) MACRO_(1, ##__VA_ARGS__);            \
+  else if (c.head_dim <= 128) MACRO_(2, ##__VA_ARGS__);      \
+  else MACRO_(4, ##__VA_ARGS__);
+  // Keys' blocks of at most one wavefront per SIMD: both halves in one launch, side by side, more rows at a time per lane (two launches,
+  // the second with as many rows at a time / one; fp32, windows [start, +rows): 4 heads of 64, [0, +8) 9.1 / 4.6 us, [32, +32)
+  // 14.2 / 8.9, [0, +256) 65 / 41, [216, +40) 35 / 30; 16 heads over 2 of 64, [0, +512) 573 / 515; bf16 67 / 35 and 693 / 513).  As every
+  // key's block reads out as well, only while an operand's rows fit an XCD's L2 (16 heads over 2 of 256, [0, +512), bf16 of 4 MB
+  // 1888 / 1630, fp32 of 8 MB 1981 / 2143).
+  const size_t row_bytes = esize(c.dtype) * (size_t)win_len * c.n_q_heads * c.head_dim;
+  if (vec && aligned16(out) && (long)l * c.n_kv_heads <= 1024 && row_bytes <= (4u << 20)) { FLEXCO_BWD_D(FLEXCO_BWD_FEW) }
+  else if (vec) { FLEXCO_BWD_D(FLEXCO_BWD_GENERIC, true) }
+  else { FLEXCO_BWD_D(FLEXCO_BWD_GENERIC, false) }
+#undef FLEXCO_BWD_D
+#undef FLEXCO_BWD_FEW
 #undef FLEXCO_BWD_GENERIC
   return post_launch("attn_bwd_generic");
 }

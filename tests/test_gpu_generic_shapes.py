@@ -89,7 +89,9 @@ D64_F32, D128_F32, D256_F32 = (C1.with_(name="d%d_f32" % d, n_q_heads=4, n_kv_he
 
 
 @pytest.mark.parametrize("cfg,win_start,win_len,shift", [(D64_F32, 0, 64, 0), (D64_F32, 0, 65, 1), (D64_F32, 500, 30, 0), (D128_F32, 3, 50, 0),
-                                                         (D128_F32, 505, 40, 0), (D256_F32, 20, 44, 1), (D256_F32, 490, 40, 0)])
+                                                         (D128_F32, 505, 40, 0), (D256_F32, 20, 44, 1), (D256_F32, 490, 40, 0),
+                                                         (D64_F32, 511, 1, 0), (D128_F32, 473, 40, 0), (D256_F32, 0, 1, 0),
+                                                         (D256_F32, 20, 45, 0), (D256_F32, 472, 40, 0)])
 def test_generic_attention_backward_forms(cfg, win_start, win_len, shift):
     print(f"attention backward forms {cfg.name} [{win_start}, +{win_len}) shift={shift}", flush=True)
     l = win_start + win_len

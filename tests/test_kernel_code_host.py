@@ -78,7 +78,8 @@ def test_operands_of_the_products_are_not_written_just_before(code):
 # The type-generic attention backward: the loops that add a run of keys' (pairs') rows hold several of them, the lane reads of all
 # up front - a loop with lane reads and a remainder is one the compiler leaves as it is, one row's round trip after the other.
 # dQ: 8 keys of three lane reads; dK / dV: 4, 8 or 16 pairs of four.
-@pytest.mark.parametrize("name,at_least", [("attn_bwd_dq_generic_kernel", 8 * 3), ("attn_bwd_dkv_generic_kernel", 4 * 4)])
+@pytest.mark.parametrize("name,at_least", [("attn_bwd_dq_generic_kernel", 8 * 3), ("attn_bwd_dkv_generic_kernel", 4 * 4),
+                                           ("attn_bwd_few_generic_kernel", 8 * 3 + 4 * 4)])
 def test_rows_of_the_generic_attention_backward_are_fetched_together(code, name, at_least):
     forms = {n: sum(op.startswith("v_readlane") for _, op, _ in ins) for n, ins in code.items() if name in n and not n.endswith(".kd")}
     assert len(forms) >= 6 and all(k >= at_least for k in forms.values()), forms
