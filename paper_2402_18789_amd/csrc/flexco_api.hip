@@ -444,10 +444,19 @@ struct GluOut {
   bool done;
 };
 
+inline float* ft_rows(void* saved, const flexco_maps& m, int width) { return (float*)saved + (size_t)m.ft_pos0 * width; }
+
 int32_t gated_gemm(const flexco_layer_cfg& c, const flexco_maps& m, const void* x, int K, const void* W, int F,
-                   const GemmExt* ext, const flexco_ft_state* ft, GluOut& glu, hipStream_t s) {
-  if (c.dtype != FLEXCO_BF16) return FLEXCO_EUNSUPPORTED;
+                   const GemmExt* ext, const flexco_ft_state* ft, GluOut& glu, hipStream_t s, const F32Norm* norm) {
   const size_t e = esize(c.dtype);
+  if (c.dtype == FLEXCO_F32) {
+    if (!gemm_f32_takes_norm(m.T, 2 * F, K, x, W, norm ? *norm : F32Norm{})) return FLEXCO_EUNSUPPORTED;
+    const F32Glu keep{ft ? ft_rows(ft->saved_gate, m, F) : nullptr, ft ? ft_rows(ft->saved_up, m, F) : nullptr, m.ft_tok0, ft ? m.n_ft : 0};
+    KernelTimerScope ts(FLEXCO_K_GENERIC, s);
+    const int32_t rc = launch_gemm_f32_norm_glu(x, W, glu.act, nullptr, m.T, F, K, glu.ld_act, norm, &keep, s);
+    if (rc == FLEXCO_OK) glu.done = true;
+    return rc;
+  }
   const int32_t rc = launch_gemm_glu_mfma(x, W, glu.act, m.T, F, K, K, K, glu.ld_act, ext,
                                           ft ? (void*)boff(ft->saved_gate, (size_t)m.ft_pos0 * F, e) : nullptr,
                                           ft ? (void*)boff(ft->saved_up, (size_t)m.ft_pos0 * F, e) : nullptr, m.ft_tok0,
@@ -471,7 +480,9 @@ struct Adapters {
 int32_t forward_projection(const flexco_layer_cfg& c, const Adapters& ad, const flexco_maps& m, const void* x,
                            int K, const void* W, const void* bias, const void* res, size_t ldr, void* y, int N,
                            const int* targets, const int* col0, int n_targets, FwdWs& k,
-                           const flexco_ft_state* ft, hipStream_t s, GluOut* glu = nullptr, SplitSums* left = nullptr) {
+                           const flexco_ft_state* ft, hipStream_t s, GluOut* glu = nullptr, SplitSums* left = nullptr,
+                           F32Norm* norm = nullptr, const void* raw = nullptr) {
+  // norm (fp32, gemm_f32_takes_norm): the product norms the rows `raw` itself, and writes x only where the bypass reads it
   // left: the caller's next kernel can add the product's partial sums, bias and residual itself; where the product is cut
   // over K (left->splits > 1) they stay in k.gemm_part for it and y is not written
   if (left) *left = SplitSums{nullptr, 1};
@@ -488,6 +499,11 @@ int32_t forward_projection(const flexco_layer_cfg& c, const Adapters& ad, const 
   int act[3], nact = 0;
   for (int i = 0; i < n_targets; ++i)
     if (m.n_lora > 0 && has_target(c, targets[i])) act[nact++] = i;
+  if (norm) norm->h = nact > 0 ? (float*)const_cast<void*>(x) : nullptr;
+  auto normed_product = [&]() -> int32_t {
+    KernelTimerScope ts(FLEXCO_K_GENERIC, s);
+    return launch_gemm_f32_norm_glu(raw, W, y, bias, m.T, N, K, N, norm, nullptr, s);
+  };
   // adapters with rows in this batch
   int used[FLEXCO_MAX_ADAPTERS], nused = 0;
   if (ad.any_id) { if (m.n_lora > 0) used[nused++] = 0; }
@@ -525,7 +541,7 @@ int32_t forward_projection(const flexco_layer_cfg& c, const Adapters& ad, const 
     ext.n = z;
     LR(launch_lora_shrink_mfma(sa, z, s));
     if (glu) {
-      const int32_t rc = gated_gemm(c, m, x, K, W, N / 2, &ext, ft, *glu, s);
+      const int32_t rc = gated_gemm(c, m, x, K, W, N / 2, &ext, ft, *glu, s, nullptr);
       if (rc != FLEXCO_EUNSUPPORTED) return rc;
       clear_error();
     }
@@ -534,12 +550,13 @@ int32_t forward_projection(const flexco_layer_cfg& c, const Adapters& ad, const 
     clear_error();   // e.g. a target boundary inside a 32-column fragment: run the bypass as separate kernels
   }
   if (glu && nact == 0) {
-    const int32_t rc = gated_gemm(c, m, x, K, W, N / 2, nullptr, ft, *glu, s);
+    const int32_t rc = gated_gemm(c, m, norm ? raw : x, K, W, N / 2, nullptr, ft, *glu, s, norm);
     if (rc != FLEXCO_EUNSUPPORTED) return rc;
     clear_error();
   }
-  if (nact == 0) return product(nullptr);
-  FLEXCO_TRY(launch_gemm(x, W, y, bias, res, T, N, K, K, K, N, ldr, false, dt, s, nullptr, k.gemm_part, k.gemm_part_elems));
+  if (nact == 0) return norm ? normed_product() : product(nullptr);
+  if (norm) FLEXCO_TRY(normed_product());
+  else FLEXCO_TRY(launch_gemm(x, W, y, bias, res, T, N, K, K, K, N, ldr, false, dt, s, nullptr, k.gemm_part, k.gemm_part_elems));
   // more adapters than the folded path takes: the backward pass (which folds whenever it can) still
   // expects the finetune rows' rank-r products where the state keeps them
   if (nused > FUSED_ADAPTERS && lora_mfma_ok(c, K) && ft && m.n_ft > 0 && ft->saved_u[targets[act[0]]]) {
@@ -993,14 +1010,21 @@ static int32_t layer_forward_impl(const flexco_layer_cfg* cfg, const flexco_base
   // (the finetune window's rows of x, x2, the attention output and its log-sum-exp - what graph pruning keeps,
   // Alg. 1 - are written to the sequence's state by the kernels that read or produce them anyway)
   const size_t p0 = m.ft_pos0;
-  EW(launch_rmsnorm(x_in, w->g1, k.h, T, H, c.rms_eps, dt, s, ft ? (void*)boff(ft->saved_x, p0 * H, e) : nullptr, m.ft_tok0,
-                    m.n_ft));
+  // fp32, few tiles: the projections that read a norm's rows compute it themselves (its launch is as long as theirs)
+  auto norm_within = [&](const void* x, const void* g, const void* W, int N, void* save, F32Norm* nm) {
+    *nm = F32Norm{(const float*)g, c.rms_eps, nullptr, (float*)save, m.ft_tok0, save ? m.n_ft : 0};
+    return dt == FLEXCO_F32 && gemm_f32_takes_norm(T, N, H, x, W, *nm);
+  };
+  F32Norm norm1, norm2;
+  void* const keep_x = ft ? (void*)boff(ft->saved_x, p0 * H, e) : nullptr;
+  const bool within1 = norm_within(x_in, w->g1, w->wqkv, qkvd, keep_x, &norm1);
+  if (!within1) EW(launch_rmsnorm(x_in, w->g1, k.h, T, H, c.rms_eps, dt, s, keep_x, m.ft_tok0, m.n_ft));
   {
     const int tg[3] = {FLEXCO_T_Q, FLEXCO_T_K, FLEXCO_T_V}, c0[3] = {0, qd, qd + kd};
     // (few tokens: the rotation adds the projection's partial sums; (IA)^3 scales the rows in between)
     const bool sums_ok = dt == FLEXCO_BF16 && !ia3 && aligned16(w->bqkv) && rope_append_vec(c, k.qkv, *pool, ft ? ft->q_cache : nullptr);
     FLEXCO_TRY(forward_projection(c, ad, m, k.h, H, w->wqkv, w->bqkv, nullptr, 0, k.qkv, qkvd, tg, c0, 3, k, ft, s, nullptr,
-                                  sums_ok ? &qkv_sums : nullptr));
+                                  sums_ok ? &qkv_sums : nullptr, within1 ? &norm1 : nullptr, x_in));
   }
   if (ia3 && m.n_lora > 0) {   // keys and values of the adapter's rows, scaled before the rotation and the append
     Ia3ScaleArgs sa;
@@ -1027,13 +1051,14 @@ static int32_t layer_forward_impl(const flexco_layer_cfg* cfg, const flexco_base
   void* const keep_x2 = ft ? (void*)boff(ft->saved_x2, p0 * H, e) : nullptr;
   if (o_sums.splits > 1)
     EW(launch_rmsnorm_sums(o_sums, x_in, k.x2, w->g2, k.h, T, H, c.rms_eps, s, keep_x2, m.ft_tok0, m.n_ft));
-  else
-    EW(launch_rmsnorm(k.x2, w->g2, k.h, T, H, c.rms_eps, dt, s, keep_x2, m.ft_tok0, m.n_ft));
+  const bool within2 = norm_within(k.x2, w->g2, w->wgu, 2 * F, keep_x2, &norm2);      // (never with partial sums, which are bf16's)
+  if (o_sums.splits == 1 && !within2) EW(launch_rmsnorm(k.x2, w->g2, k.h, T, H, c.rms_eps, dt, s, keep_x2, m.ft_tok0, m.n_ft));
   GluOut glu{k.act, (size_t)F, false};
   lend_gu(false, nullptr);
   {
     const int tg[2] = {FLEXCO_T_GATE, FLEXCO_T_UP}, c0[2] = {0, F};
-    FLEXCO_TRY(forward_projection(c, ad, m, k.h, H, w->wgu, nullptr, nullptr, 0, k.gu, 2 * F, tg, c0, 2, k, ft, s, &glu));
+    FLEXCO_TRY(forward_projection(c, ad, m, k.h, H, w->wgu, nullptr, nullptr, 0, k.gu, 2 * F, tg, c0, 2, k, ft, s, &glu, nullptr,
+                                  within2 ? &norm2 : nullptr, k.x2));
   }
   // (the gated projection has written the window's rows of gate and up to the sequence's state)
   if (!glu.done)

@@ -98,6 +98,14 @@ int32_t launch_gemm_generic(const void* A, const void* W, void* C, const void* b
 // fp32 on the matrix cores; FLEXCO_EUNSUPPORTED (nothing launched) where K or a leading dimension is no multiple of four
 int32_t launch_gemm_f32_mfma(const void* A, const void* W, void* C, const void* bias, const void* residual, int M,
                              int N, int K, size_t lda, size_t ldw, size_t ldc, size_t ldr, bool trans_w, hipStream_t s);
+// fp32, few tiles: the rows' RMSNorm (gain g) and / or the gate of [gate | up] within the product.  A, W: rows of K elements.
+// h: the normed rows [M, K], NULL if no one else reads them; save: rows [save_row0, + save_rows) of A, NULL: none.
+struct F32Norm { const float* g; float eps; float* h; float* save; int save_row0, save_rows; };
+// rows [save_row0, + save_rows) of gate and up are kept (N wide), NULL: none
+struct F32Glu { float *save_gate, *save_up; int save_row0, save_rows; };
+bool gemm_f32_takes_norm(int M, int N, int K, const void* x, const void* W, const F32Norm& norm);
+int32_t launch_gemm_f32_norm_glu(const void* A, const void* W, void* C, const void* bias, int M, int N, int K, size_t ldc,
+                                 const F32Norm* norm, const F32Glu* glu, hipStream_t s);
 // How the bf16 MFMA path tiles a product: one or two launches side by side in the output columns, each one tile
 // shape (bm x bn), `cols` output columns, K cut over `splits` blocks, a ring of `stages` stages.  part_elems: floats of
 // split-K scratch at hand (0 = none).  The gated form is the forward plan over its 2F interleaved columns.

@@ -240,8 +240,14 @@ extern "C" int32_t flexco_lm_loss(const flexco_lm_head* head, const void* x, con
   FLEXCO_CHECK(k.bytes <= ws_bytes, FLEXCO_EWORKSPACE, "loss head needs %zu workspace bytes, got %zu", k.bytes, ws_bytes);
   hipStream_t s = (hipStream_t)stream;
   const int H = hd.hidden, V = hd.vocab, dt = hd.dtype;
-  FLEXCO_TRY(launch_rmsnorm(x, hd.g_final, k.h, n, H, hd.rms_eps, dt, s));
-  FLEXCO_TRY(launch_gemm(k.h, hd.w_lm, k.z, nullptr, nullptr, n, V, H, H, H, V, 0, false, dt, s, nullptr, nullptr, 0));
+  const F32Norm norm{(const float*)hd.g_final, hd.rms_eps, nullptr, nullptr, 0, 0};
+  if (dt == FLEXCO_F32 && gemm_f32_takes_norm(n, V, H, x, hd.w_lm, norm)) {
+    KernelTimerScope ts(FLEXCO_K_GENERIC, s);
+    FLEXCO_TRY(launch_gemm_f32_norm_glu(x, hd.w_lm, k.z, nullptr, n, V, H, V, &norm, nullptr, s));
+  } else {
+    FLEXCO_TRY(launch_rmsnorm(x, hd.g_final, k.h, n, H, hd.rms_eps, dt, s));
+    FLEXCO_TRY(launch_gemm(k.h, hd.w_lm, k.z, nullptr, nullptr, n, V, H, H, H, V, 0, false, dt, s, nullptr, nullptr, 0));
+  }
   {
     KernelTimerScope ts(FLEXCO_K_ELEMWISE, s);
     const bool vec = V % (dt == FLEXCO_BF16 ? 8 : 4) == 0;   // rows of z then start 16-byte aligned

@@ -452,6 +452,17 @@ def test_layer_c1_down_only():
     run_layer_case(cfg, gen.batch_c1(3), ft_window=32, prefill_chunk=32, bwd_windows=[20, 44])
 
 
+# fp32 projections that norm their rows and gate their product: K of no whole steps, a ragged column tile of gate and up, rows of the
+# bypass written beside the product; 1024 tiles of gate and up (33 rows in three row tiles) and the sizes past them
+@pytest.mark.parametrize("hidden,ffn,targets", [(260, 100, ("q", "v", "down")), (20, 36, ("k", "gate")), (516, 52, ("o",)),
+                                                (64, 2728, ("q",)), (64, 2736, ("v", "up"))])
+def test_layer_fp32_norm_and_gate_within_the_projections(hidden, ffn, targets):
+    say(f"layer fp32 hidden {hidden} ffn {ffn} {targets}")
+    cfg = C1.with_(name="f32_%d" % hidden, hidden=hidden, ffn=ffn, lora_targets=targets)
+    b = gen.mixed_batch(16, 1, decode_ctx=(1, 17, 64), prefill=[(0, 13, 13)], finetune=[(0, 17, 20)])
+    run_layer_case(cfg, b, ft_window=3, prefill_chunk=13, bwd_windows=[4, 16], seed=hidden)
+
+
 def test_layer_small_bf16():
     say("layer small bf16")
     b = gen.batch_scaled(7, 10, 3, 600, [(0, 130, 130), (256, 64, 400)], [(0, 100, 260)])

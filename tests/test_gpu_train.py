@@ -51,7 +51,8 @@ def run_loss(dtype, n, H, V, seed, ignore=()):
 
 @pytest.mark.parametrize("dtype,n,H,V,ignore", [("f32", 37, 256, 1003, (5,)), ("f32", 4, 64, 50, ()),
                                                 ("bf16", 70, 512, 4104, (0, 69)), ("bf16", 33, 256, 1001, ()),
-                                                ("bf16", 1, 256, 2048, ())])
+                                                ("bf16", 1, 256, 2048, ()), ("f32", 17, 260, 1000, (16,)),
+                                                ("f32", 16, 20, 16384, ()), ("f32", 16, 20, 16385, ())])
 def test_loss_head(dtype, n, H, V, ignore):
     print(f"loss head {dtype} n={n} H={H} V={V}", flush=True)
     run_loss(dtype, n, H, V, seed=1, ignore=ignore)
