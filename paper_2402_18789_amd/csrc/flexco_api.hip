@@ -1213,9 +1213,14 @@ static int32_t layer_backward_impl(const flexco_layer_cfg* cfg, const flexco_bas
   const bool act_late = late_inputs && has_target(c, FLEXCO_T_DOWN);
   const bool hn2_late = late_inputs && gu_lora;
   const bool hn_late = late_inputs && qkv_lora && dX != nullptr;
-  if (has_target(c, FLEXCO_T_DOWN) && !act_late) EW(launch_swiglu_remat(gate_w, up_w, k.act, n, F, dt, s));
-  if (gu_lora && !hn2_late) EW(launch_rmsnorm(x2_w, w->g2, k.hn2, n, H, c.rms_eps, dt, s));
-  if (qkv_lora && !hn_late) EW(launch_rmsnorm(x_w, w->g1, k.hn, n, H, c.rms_eps, dt, s));
+  RematArgs rm;
+  memset(&rm, 0, sizeof(rm));
+  rm.n = n; rm.F = F; rm.H = H; rm.eps = c.rms_eps;
+  if (has_target(c, FLEXCO_T_DOWN) && !act_late) { rm.gate = gate_w; rm.up = up_w; rm.act = k.act; }
+  auto norm_again = [&](const void* x, const void* g, void* h) { rm.x[rm.norms] = x; rm.g[rm.norms] = g; rm.h[rm.norms++] = h; };
+  if (gu_lora && !hn2_late) norm_again(x2_w, w->g2, k.hn2);
+  if (qkv_lora && !hn_late) norm_again(x_w, w->g1, k.hn);
+  if (rm.act || rm.norms > 0) EW(launch_remat(rm, dt, s));
   FLEXCO_TRY(lora_bwd_prepare(c, lora, n, grp, 4, k, ft, win_start, s));
 
   // ---- MLP side: down projection, SwiGLU, gate/up projections, second norm -------------

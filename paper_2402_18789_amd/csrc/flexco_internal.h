@@ -140,9 +140,11 @@ int32_t launch_rmsnorm_sums(const SplitSums& sums, const void* res, void* x, con
                             hipStream_t s, void* save, int save_row0, int save_rows);
 int32_t launch_rmsnorm(const void* x, const void* g, void* h, int T, int H, float eps, int dtype, hipStream_t s,
                        void* save = nullptr, int save_row0 = 0, int save_rows = 0);
+// row losses that are to be added to *accum beside something else (accum = NULL: none)
+struct LossSum { const float* row; int n; float scale; float* accum; };
 int32_t launch_rmsnorm_bwd(const void* x, const void* g, const void* dh, const void* add, void* dx, int T, int H,
                            float eps, int dtype, hipStream_t s, void* hn = nullptr,
-                           const float* dh_part = nullptr, int splits = 1);
+                           const float* dh_part = nullptr, int splits = 1, const LossSum* loss = nullptr);
 int32_t launch_rope_append(const flexco_layer_cfg& c, void* qkv, const int32_t* tok_pos, const int32_t* slot,
                            const flexco_kv_pool& pool, int T, int ft_tok0, int n_ft, int ft_pos0, void* q_cache,
                            hipStream_t s, const SplitSums* sums = nullptr, const void* bias = nullptr);
@@ -156,7 +158,16 @@ int32_t launch_swiglu(const void* gu, void* act, int T, int F, int dtype, hipStr
 int32_t launch_swiglu_bwd(const void* gate, const void* up, const void* dact, void* dgu, int n, int F, int dtype,
                           hipStream_t s, void* act = nullptr,
                           const float* dact_part = nullptr, int splits = 1);
-int32_t launch_swiglu_remat(const void* gate, const void* up, void* act, int n, int F, int dtype, hipStream_t s);
+// n rows of act = silu(gate) * up (F wide; act = NULL: not wanted) and of `norms` RMSNorms h = norm(x) (H wide)
+struct RematArgs {
+  const void *gate, *up;
+  void* act;
+  const void *x[2], *g[2];
+  void* h[2];
+  int n, F, H, norms;
+  float eps;
+};
+int32_t launch_remat(const RematArgs& a, int dtype, hipStream_t s);
 // (IA)^3 forward scale of up to two column ranges of the listed token rows (see ia3_scale_rows_kernel)
 struct Ia3ScaleArgs {
   int n_seg;

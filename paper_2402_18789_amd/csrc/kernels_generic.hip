@@ -61,12 +61,9 @@ __device__ inline float block_sum256(float v, float* red /* >= 4 floats of LDS *
 // VEC: rows are read and written in 16-byte pieces (the host picks it when H is a multiple of the
 // vector width and every pointer and row pitch is 16-byte aligned).
 template <typename T, bool VEC>
-__global__ __launch_bounds__(256) void rmsnorm_kernel(const T* __restrict__ x, const T* __restrict__ g,
-                                                      T* __restrict__ h, int H, float eps, T* __restrict__ save,
-                                                      int save_row0, int save_rows) {
-  __shared__ float red[4];
+__device__ inline void norm_row(const size_t row, const T* __restrict__ x, const T* __restrict__ g, T* __restrict__ h, int H, float eps,
+                                T* __restrict__ save, int save_row0, int save_rows, float* red) {
   constexpr int N = Vec<T>::N;
-  const size_t row = blockIdx.x;
   const T* xr = x + row * H;
   // rows [save_row0, save_row0 + save_rows) also leave a copy of the INPUT row in `save` (the finetune
   // window's rows of an activation graph pruning keeps, written by the kernel that reads them anyway)
@@ -101,6 +98,14 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const T* __restrict__ x, c
   } else {
     for (int i = threadIdx.x; i < H; i += 256) st(h + row * H + i, ld(xr + i) * rstd * ld(g + i));
   }
+}
+
+template <typename T, bool VEC>
+__global__ __launch_bounds__(256) void rmsnorm_kernel(const T* __restrict__ x, const T* __restrict__ g,
+                                                      T* __restrict__ h, int H, float eps, T* __restrict__ save,
+                                                      int save_row0, int save_rows) {
+  __shared__ float red[4];
+  norm_row<T, VEC>(blockIdx.x, x, g, h, H, eps, save, save_row0, save_rows, red);
 }
 
 // x = sums + res, h = rmsnorm(x), bf16: the output projection's partial sums added by the norm that reads the product next
@@ -201,11 +206,33 @@ __device__ inline void load_split_sum(const float* __restrict__ part, int splits
 
 // dx = rstd * (g * dh) - x * rstd^3 * mean(x * g * dh)  (+ add);  hn (optional) = x rstd g, the row
 // the forward norm produced (same arithmetic, same bits), for callers that need it again
+//
+// loss.accum (optional): one block more than rows adds the rows' losses, which are there since an earlier launch:
+// *accum += scale * sum_i row[i], rows added in index order by strided partial sums of 256 threads.  (A launch of its own took
+// 2.5 us of every head: fp32, hidden 256, 32 rows of 1000 logits 21.2 -> 19.5 us, 128 of 32000 178.7 -> 175.0.)
+__device__ inline void loss_sum(const LossSum& l) {
+  __shared__ float part[256];
+  const int t = threadIdx.x;
+  if (t < 256) {
+    float s = 0.f;
+    for (int i = t; i < l.n; i += 256) s += l.row[i];
+    part[t] = s;
+  }
+  __syncthreads();
+  for (int o = 128; o > 0; o >>= 1) {
+    if (t < o) part[t] += part[t + o];
+    __syncthreads();
+  }
+  if (t == 0) l.accum[0] += l.scale * part[0];
+}
+
 template <typename T, bool VEC>
 __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(const T* __restrict__ x, const T* __restrict__ g,
                                                           const T* __restrict__ dh, const T* __restrict__ add,
                                                           T* __restrict__ dx, T* __restrict__ hn, int H, float eps,
-                                                          const float* __restrict__ dh_part, int splits, size_t stride) {
+                                                          const float* __restrict__ dh_part, int splits, size_t stride,
+                                                          LossSum loss) {
+  if (loss.accum && blockIdx.x == gridDim.x - 1) return loss_sum(loss);
   // dh_part: dh still lies as split-K partial sums (see load_split_sum); the row's sums are kept in LDS
   // between the two passes (dynamic shared memory of H floats, only then)
   extern __shared__ float dh_row[];
@@ -292,7 +319,8 @@ __global__ __launch_bounds__(1024) void rmsnorm_bwd_wide_kernel(const bf16_t* __
                                                                 const bf16_t* __restrict__ add, bf16_t* __restrict__ dx,
                                                                 bf16_t* __restrict__ hn, int H, float eps,
                                                                 const float* __restrict__ dh_part, int splits,
-                                                                size_t stride) {
+                                                                size_t stride, LossSum loss) {
+  if (loss.accum && blockIdx.x == gridDim.x - 1) return loss_sum(loss);
   __shared__ float red[2][16];
   const size_t row = blockIdx.x;
   const int wave = threadIdx.x >> 6;
@@ -806,20 +834,32 @@ __global__ __launch_bounds__(256) void swiglu_bwd_kernel(const T* __restrict__ g
   }
   if (VEC) { Vec<T>::store(dgu + row * 2 * F + i, dg); Vec<T>::store(dgu + row * 2 * F + F + i, du); }
   else { st(dgu + row * 2 * F + i, dg[0]); st(dgu + row * 2 * F + F + i, du[0]); }
-  if (act) {   // the rematerialised SwiGLU output (as swiglu_remat_kernel computes it), for callers that need it again
+  if (act) {   // the rematerialised SwiGLU output (as remat_kernel computes it), for callers that need it again
 #pragma unroll
     for (int j = 0; j < N; ++j) g[j] = g[j] / (1.0f + __expf(-g[j])) * u[j];
     if (VEC) Vec<T>::store(act + row * F + i, g); else st(act + row * F + i, g[0]);
   }
 }
 
-// act = silu(gate) * up from the saved gate and up (rematerialisation, Alg. 1)
+// The inputs of a window's adapted projections again (rematerialisation, Alg. 1): act = silu(gate) * up from the saved gate and
+// up in the first n * act_blocks blocks, then the rows of up to two norms.  One launch, as none reads another (fp32
+// configuration: two launches of 2.6 and 2.8 us and the gap between them).
 template <typename T, bool VEC>
-__global__ __launch_bounds__(256) void swiglu_remat_kernel(const T* __restrict__ gate, const T* __restrict__ up,
-                                                           T* __restrict__ act, int F) {
+__global__ __launch_bounds__(256) void remat_kernel(RematArgs a, int act_blocks) {
+  __shared__ float red[4];
   constexpr int N = VEC ? Vec<T>::N : 1;
-  const size_t row = blockIdx.y;
-  const int i = (blockIdx.x * 256 + threadIdx.x) * N;
+  int b = blockIdx.x;
+  if (b >= a.n * act_blocks) {
+    b -= a.n * act_blocks;
+    const int z = b / a.n;
+    norm_row<T, VEC>(b % a.n, (const T*)a.x[z], (const T*)a.g[z], (T*)a.h[z], a.H, a.eps, (T*)nullptr, 0, 0, red);
+    return;
+  }
+  const T *gate = (const T*)a.gate, *up = (const T*)a.up;
+  T* act = (T*)a.act;
+  const int F = a.F;
+  const size_t row = b / act_blocks;
+  const int i = ((b % act_blocks) * 256 + threadIdx.x) * N;
   if (i >= F) return;
   float g[N], u[N];
   if (VEC) { Vec<T>::load(gate + row * F + i, g); Vec<T>::load(up + row * F + i, u); }
@@ -1261,23 +1301,25 @@ int32_t launch_rmsnorm_sums(const SplitSums& sums, const void* res, void* x, con
 }
 
 int32_t launch_rmsnorm_bwd(const void* x, const void* g, const void* dh, const void* add, void* dx, int T_, int H,
-                           float eps, int dtype, hipStream_t s, void* hn, const float* dh_part, int splits) {
+                           float eps, int dtype, hipStream_t s, void* hn, const float* dh_part, int splits, const LossSum* loss) {
   if (T_ == 0) return FLEXCO_OK;
   const bool vec = vec_ok(dtype, H, {x, g, dh, add, dx, hn, dh_part});
   const size_t shm = dh_part ? sizeof(float) * (size_t)H : 0;
+  const LossSum ls = loss ? *loss : LossSum{nullptr, 0, 0.f, nullptr};
+  const dim3 grid(T_ + (ls.accum ? 1 : 0));
   // bf16 rows of up to 8192 elements: sixteen wavefronts per row
   if (dtype == FLEXCO_BF16 && vec && H <= 8192) {
 #define FLEXCO_NORM_BWD_WIDE(IT_)                                                                                  \
-    hipLaunchKernelGGL((rmsnorm_bwd_wide_kernel<IT_>), dim3(T_), dim3(1024), 0, s, (const bf16_t*)x,                \
+    hipLaunchKernelGGL((rmsnorm_bwd_wide_kernel<IT_>), grid, dim3(1024), 0, s, (const bf16_t*)x,                \
                        (const bf16_t*)g, (const bf16_t*)dh, (const bf16_t*)add, (bf16_t*)dx, (bf16_t*)hn, H, eps,   \
-                       dh_part, splits, (size_t)T_ * H)
+                       dh_part, splits, (size_t)T_ * H, ls)
     if (H <= 4096) FLEXCO_NORM_BWD_WIDE(1); else FLEXCO_NORM_BWD_WIDE(2);
 #undef FLEXCO_NORM_BWD_WIDE
     return post_launch("rmsnorm_bwd");
   }
-  DISPATCH_TV(dtype, vec, hipLaunchKernelGGL((rmsnorm_bwd_kernel<T, VEC>), dim3(T_), dim3(256), shm, s, (const T*)x,
+  DISPATCH_TV(dtype, vec, hipLaunchKernelGGL((rmsnorm_bwd_kernel<T, VEC>), grid, dim3(256), shm, s, (const T*)x,
                                              (const T*)g, (const T*)dh, (const T*)add, (T*)dx, (T*)hn, H, eps, dh_part,
-                                             splits, (size_t)T_ * H));
+                                             splits, (size_t)T_ * H, ls));
   return post_launch("rmsnorm_bwd");
 }
 
@@ -1401,13 +1443,21 @@ int32_t launch_swiglu_bwd(const void* gate, const void* up, const void* dact, vo
   return post_launch("swiglu_bwd");
 }
 
-int32_t launch_swiglu_remat(const void* gate, const void* up, void* act, int n, int F, int dtype, hipStream_t s) {
-  if (n == 0) return FLEXCO_OK;
-  const bool vec = vec_ok(dtype, F, {gate, up, act});
-  const int per = 256 * (vec ? (dtype == FLEXCO_BF16 ? 8 : 4) : 1);
-  DISPATCH_TV(dtype, vec, hipLaunchKernelGGL((swiglu_remat_kernel<T, VEC>), dim3((F + per - 1) / per, n), dim3(256), 0,
-                                             s, (const T*)gate, (const T*)up, (T*)act, F));
-  return post_launch("swiglu_remat");
+int32_t launch_remat(const RematArgs& a, int dtype, hipStream_t s) {
+  if (a.n == 0 || (!a.act && a.norms == 0)) return FLEXCO_OK;
+  const bool act_vec = vec_ok(dtype, a.F, {a.gate, a.up, a.act});
+  const bool norm_vec = vec_ok(dtype, a.H, {a.x[0], a.g[0], a.h[0], a.x[1], a.g[1], a.h[1]});
+  if (a.act && a.norms > 0 && act_vec != norm_vec) {       // each in the form its rows allow
+    RematArgs one = a, two = a;
+    one.norms = 0;
+    two.act = nullptr;
+    const int32_t rc = launch_remat(one, dtype, s);
+    return rc ? rc : launch_remat(two, dtype, s);
+  }
+  const bool vec = a.act ? act_vec : norm_vec;
+  const int per = 256 * (vec ? (dtype == FLEXCO_BF16 ? 8 : 4) : 1), act_blocks = a.act ? (a.F + per - 1) / per : 0;
+  DISPATCH_TV(dtype, vec, hipLaunchKernelGGL((remat_kernel<T, VEC>), dim3(a.n * (act_blocks + a.norms)), dim3(256), 0, s, a, act_blocks));
+  return post_launch("remat");
 }
 
 int32_t launch_copy_rows(const void* src, size_t ld_src_bytes, void* dst, size_t ld_dst_bytes, int n_rows,

@@ -143,21 +143,6 @@ __global__ __launch_bounds__(CE_REG_THREADS) void ce_rows_reg_kernel(bf16_t* __r
   }
 }
 
-// *accum += scale * sum_i row_loss[i], rows added in index order by strided partial sums of one block
-__global__ __launch_bounds__(256) void loss_sum_kernel(const float* __restrict__ row_loss, int n, float scale,
-                                                       float* __restrict__ accum) {
-  __shared__ float part[256];
-  float s = 0.f;
-  for (int i = threadIdx.x; i < n; i += 256) s += row_loss[i];
-  part[threadIdx.x] = s;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (threadIdx.x < o) part[threadIdx.x] += part[threadIdx.x + o];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) accum[0] += scale * part[0];
-}
-
 template <typename T>
 __global__ __launch_bounds__(256) void adam_kernel(T* __restrict__ param, float* __restrict__ master,
                                                    const float* __restrict__ grad, float* __restrict__ m,
@@ -269,11 +254,10 @@ extern "C" int32_t flexco_lm_loss(const flexco_lm_head* head, const void* x, con
       else hipLaunchKernelGGL((ce_rows_kernel<float, false>), dim3(n), dim3(CE_THREADS), 0, s, (float*)k.z, targets, k.row_loss, V, scale);
     }
     FLEXCO_TRY(post("ce_rows"));
-    hipLaunchKernelGGL(loss_sum_kernel, dim3(1), dim3(256), 0, s, k.row_loss, n, scale, loss_accum);
-    FLEXCO_TRY(post("loss_sum"));
   }
   FLEXCO_TRY(launch_gemm(k.z, hd.w_lm, k.dh, nullptr, nullptr, n, H, V, V, H, H, 0, true, dt, s, nullptr, k.part, k.part_elems));
-  FLEXCO_TRY(launch_rmsnorm_bwd(x, hd.g_final, k.dh, nullptr, dX, n, H, hd.rms_eps, dt, s));
+  const LossSum loss{k.row_loss, n, scale, loss_accum};
+  FLEXCO_TRY(launch_rmsnorm_bwd(x, hd.g_final, k.dh, nullptr, dX, n, H, hd.rms_eps, dt, s, nullptr, nullptr, 1, &loss));
   return FLEXCO_OK;
 }
 
