@@ -10,7 +10,8 @@
 // dX = dY W remains.
 //
 // Tiling: block tile BM x BN, 256 threads = 4 wavefronts in a 2 x 2 grid, each owning
-// (BM/2) x (BN/2) as 16 x 16 MFMA tiles with fp32 accumulators (the 256 x 256 tile has a kernel of its own, below).
+// (BM/2) x (BN/2) as 16 x 16 MFMA tiles with fp32 accumulators.  Tiles of 160 to 256 rows have a kernel of their own
+// (gemm_bf16_quad_kernel), and so have input gradients of few row tiles (gemm_bf16_pair_kernel: eight wavefronts, 128 x 128).
 //   * Forward form: operand tiles go from global memory straight into LDS
 //     (buffer_load_dwordx4 ... lds: one wavefront instruction fills 1 KB; lane l lands at
 //     base + 16 l), no staging registers and no LDS write instructions.  LDS is a ring of stages
@@ -1226,7 +1227,8 @@ static int pick_splits(int M, int N, int K, int tiles, size_t part_elems, int wa
 // Rates of the input-gradient form's two tile shapes with every block slot taken, PFLOP/s: fitted to twelve products of
 // 512 to 1536 rows at the 8B, 14B and 32B shapes with the 32 x 32 x 16 kernels (the 256 x 256 tile reaches 1.26 now).  What they
 // decide is the plan's tile and equal cut; plan_gemm_k_ranges prices that choice with the present kernels' times and
-// takes the 256 x 256 tile, at the number of ranges that suits it, where that is estimated 5 % better.
+// takes the 256 x 256 tile, at the number of ranges that suits it, where that is estimated 5 % better; plan_gemm_pair then puts
+// the eight-wavefront kernel in the place of 128 x 128 tiles where a window has few row tiles.
 constexpr double TRANS_RATE_128 = 0.94, TRANS_RATE_256 = 1.05;
 
 static double us_tile128x192(long blocks, double stages) { return ((blocks + 255) / 256) * (4 + 0.76 * stages); }
@@ -1324,8 +1326,10 @@ int plan_gemm_k_ranges(int M, int N, int K, bool trans_w, size_t part_elems) { r
 // (512 x 14336 x 4096 83 us on this kernel, 62 on 256 x 256 tiles).  Measured on 130 products of 33 to 1024 rows at the three models'
 // shapes, weights from HBM.  Against the plan's 128 x 128 tiles, two blocks to a CU: 81 to 256 rows 0.82 - 0.95 of their time, with more
 // and with fewer rows 0.79 - 0.95 where the blocks fill the chip and 0.95 - 1.27 where they do not (640 x 4096 x 6144, 160
-// blocks: 59 against 46 us; 33 x 14336 x 4096, 224 blocks: 36 against 31).  Against 256 x 256 tiles by the estimates (this one's within 12 %), which see those at few rows too low:
-// 150 x 14336 x 4096 39 us against 44 where they say 46 and 42.
+// blocks: 59 against 46 us; 33 x 14336 x 4096, 224 blocks: 36 against 31).  What it gains is at a block's ends: over hundreds of
+// stages idle CUs cost more (84 to 128 rows x 5120, 240 blocks: K 55296, 144 stages, 0.96 - 1.00; K 152064, 396 stages, 1.02 - 1.08;
+// 256 blocks of 250 stages, 4096 x 128256, 0.98 - 1.01).  Against 256 x 256 tiles by the estimates (this one's within 12 %), which see
+// those at few rows too low: 150 x 14336 x 4096 39 us against 44 where they say 46 and 42.
 static int plan_gemm_pair(int M, int N, int K, size_t part_elems) {
   const int ns = K / BK;
   const long tiles = (long)((M + 127) / 128) * ((N + 127) / 128);
@@ -1339,7 +1343,8 @@ static int plan_gemm_pair(int M, int N, int K, size_t part_elems) {
     const double t = 6 + 0.62 * ((ns + r - 1) / r) + us_partial_sums(r, M, N);
     if (t < us) { us = t; best = r; }
   }
-  return !large && (M > 256 || M <= 80) && tiles * best < 250 ? 0 : best;
+  const bool idle = tiles * best < 250, long_runs = best && ns / best > 200;
+  return idle && (long_runs || (!large && (M > 256 || M <= 80))) ? 0 : best;
 }
 
 // Whether a forward product runs on 256 x 128 tiles, one launch over all columns, instead of by the choices above (other_us: their
