@@ -204,9 +204,10 @@ __device__ __forceinline__ void store_tile(const f32x4 (&acc)[MT][NT], float* st
 // neighbouring columns, and reads their part of A only (with every range in every XCD, and no order at all for tiles that are no
 // multiple of eight: 1024 x 5120 x 13824 in 3 ranges 115 -> 106 us, input gradient 800 x 5120 x 27648 198 -> 170 (4)).  One row
 // tile shares no weights and keeps an XCD to columns of its own, over all ranges: rows of A a multiple of 4 KB apart put a range's
-// stage on one channel of the L2 (input gradient 256 x 4096 x 28672 82 us the other way, 78 this).
-__device__ __forceinline__ void place_of_block(int tiles_m, int* lid, int* range) {
-  if (tiles_m == 1 && (gridDim.x & 7) == 0) {
+// stage on one channel of the L2 (input gradient 256 x 4096 x 28672 82 us the other way, 78 this); so do the two row tiles of a
+// forward product cut over 128-row tiles (200 x 5120 x 5120 35.4 us the other way, 34.6 this).  apart: this second form.
+__device__ __forceinline__ void place_of_block(bool apart, int* lid, int* range) {
+  if (apart && (gridDim.x & 7) == 0) {
     *range = blockIdx.y;
     *lid = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
     return;
@@ -230,7 +231,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
 
   // ---- work-group id -> tile, XCD-aware ------------------------------------------------
   int lid, range;
-  place_of_block(tiles_m, &lid, &range);
+  place_of_block(!TRANS || tiles_m == 1, &lid, &range);
   const int tm = lid % tiles_m, tn = lid / tiles_m;
   const int m0 = tm * BM, n0 = tn * BN;
 
@@ -648,7 +649,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_quad_kernel(const bf16_t* __res
                 "a half-tile is read and another's loads go out within a phase's products");
   static_assert(BN == 256 || ((BN == 192 || BN == 128) && !TRANS), "the input-gradient form's W tile swizzle assumes 256-byte rows");
   int lid, range;
-  place_of_block(tiles_m, &lid, &range);
+  place_of_block(tiles_m == 1, &lid, &range);
   const int tm = lid % tiles_m, tn = lid / tiles_m;
   const int m0 = tm * BM, n0 = tn * BN;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -879,7 +880,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_pair_kernel(const bf16_t* __res
   constexpr int BM = 128, BN = 128, NST = 4, NT = 4, NA = 2, NW = 2;       // NA, NW: load instructions of a wavefront and stage
   constexpr int ST_ELEMS = (BM + BN) * BK;
   int lid, range;
-  place_of_block(tiles_m, &lid, &range);
+  place_of_block(tiles_m == 1, &lid, &range);
   const int tm = lid % tiles_m, tn = lid / tiles_m;
   const int m0 = tm * BM, n0 = tn * BN;
   const int tid = threadIdx.x, lane = tid & 63;
