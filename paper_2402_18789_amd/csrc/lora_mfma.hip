@@ -12,7 +12,7 @@
 //            k-steps (gemm_mfma.hip), reading the bf16 matrix the shrink kernel writes.
 //   outer    dB += scale dy^T u,  dA += scale t^T x : every output element is a sum over
 //            the window's rows only; on the matrix cores (u, t as bf16, the rows of x / dy through
-//            transposing LDS reads), 64 output columns per block, rows shared out over its 4
+//            transposing LDS reads), 128 output columns per block, rows shared out over 4
 //            wavefronts, fixed-order LDS reduction; a plain FMA kernel covers unaligned shapes.
 #include <algorithm>
 #include <cstring>
@@ -260,30 +260,36 @@ __global__ __launch_bounds__(256) void lora_outer_mfma_path_kernel(LoraOuterArgs
 }
 
 // The same products on the matrix cores: G^T[j, i] += scale sum_m U[m, j] X[m, i] with
-// v_mfma_f32_16x16x32_bf16, D rows = 16 ranks, D columns = 16 of the block's 64 columns i, k = 32 rows m.
-//   * U^T (bf16, row pitch padded) is staged in LDS once per 256-row chunk; a lane reads its 8
+// v_mfma_f32_16x16x32_bf16, D rows = 16 ranks, D columns = 16 of the block's 128 columns i, k = 32 rows m.
+// Eight wavefronts: four for each half of the columns.
+//   * U^T (bf16) is staged in LDS once per 256-row chunk, 16-byte pieces XOR-swizzled with the rank; a lane reads its 8
 //     consecutive m of one rank with one ds_read_b128.
-//   * X: wavefront w owns rows 64 w .. + 64 of the chunk, two [32 rows][64 columns] tiles that go from
+//   * X: wavefront w owns rows 64 (w % 4) .. + 64 of the chunk and the columns of its half, two [32 rows][64 columns] tiles that go from
 //     global memory straight into its own LDS buffers; the operand (8 consecutive rows of one column)
 //     comes from two transposing reads (ds_read_b64_tr_b16).  32-byte column pairs are XOR-swizzled
 //     with row % 4 so that the four rows of a read sit on different banks.
-//   * the four wavefronts' sums are added in wavefront order through LDS.
+//   * a half's four sums are added in wavefront order through LDS, a quarter of its columns by each wavefront.
+// What bounds it: the rows' way in, tile after tile (single buffers; two blocks share a CU up to rank 32), and U, which every block
+// reads whole: hence columns by the 128 (with blocks of 64 columns and four wavefronts, whose sums one wavefront added and wrote, us
+// with nothing cached: a 14B window of 1024 rows, 14 products of rank 16 72 -> 65, of 300 rows 36 -> 29; 32B, rank 32, 1024 rows
+// 139 -> 109, 300 rows 78 -> 48; 8B, 10 products, 256 rows 18.6 -> 16.1; 257 rows x 1000 - 1864, rank 48, 44 -> 18).  Same sums.
 template <int RT>   // rank tiles of 16
-__global__ __launch_bounds__(256) void lora_outer_mfma_kernel(LoraOuterArgs a) {
-  constexpr int UP = 264;                                                   // row pitch of U^T in elements
-  __shared__ __attribute__((aligned(1024))) bf16_t xt[4][2][32 * 64];       // per wavefront: two X tiles
-  __shared__ __attribute__((aligned(16))) bf16_t ut[RT * 16 * UP];          // U^T of the chunk, [rank][row]
-  __shared__ __attribute__((aligned(16))) float red[3][RT][4][64][4];       // sums of wavefronts 1..3
+__global__ __launch_bounds__(512) void lora_outer_mfma_kernel(LoraOuterArgs a) {
+  // element (rank, row) of U^T
+  auto ut_at = [](int j, int m) { return j * 256 + (((m >> 3) ^ (j & 15)) << 3) + (m & 7); };
+  __shared__ __attribute__((aligned(1024))) bf16_t xt[8][2][32 * 64];       // per wavefront: two X tiles; at the end the sums
+  __shared__ __attribute__((aligned(16))) bf16_t ut[RT * 16 * 256];         // U^T of the chunk, [rank][row]
   const int e = blockIdx.y;
   const int n = a.n, r = a.r, n_long = a.n_long[e];
-  const int i0 = blockIdx.x * 64;
-  if (i0 >= n_long) return;   // entries of one launch differ in width
+  if ((int)blockIdx.x * 128 >= n_long) return;   // entries of one launch differ in width
   const bf16_t* __restrict__ X = a.X[e];
   const float* __restrict__ U = a.U[e];
   float* __restrict__ G = a.G[e];
   const size_t ldx = a.ldx[e], g_i = a.g_i[e], g_j = a.g_j[e];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int rows_of = wave & 3;                   // quarter of a chunk's rows
+  const int i0 = blockIdx.x * 128 + 64 * (wave >> 2);
   const int c = lane & 15, g = lane >> 4;
 
   f32x4 acc[RT][4];
@@ -303,7 +309,7 @@ __global__ __launch_bounds__(256) void lora_outer_mfma_kernel(LoraOuterArgs a) {
 
   // a wavefront's two tiles of the chunk that starts at row mb0 (its own LDS buffers: nobody else reads them)
   auto load_tiles = [&](int mb0) {
-    const int mw0 = mb0 + 64 * wave;
+    const int mw0 = mb0 + 64 * rows_of;
 #pragma unroll
     for (int st = 0; st < 2; ++st)
 #pragma unroll
@@ -313,30 +319,39 @@ __global__ __launch_bounds__(256) void lora_outer_mfma_kernel(LoraOuterArgs a) {
       }
   };
   load_tiles(0);
+  // what the sums are added to (nobody else writes it)
+  float gv[RT][4];
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int col = min(i0 + 16 * rows_of + c, n_long - 1), j = min(rt * 16 + 4 * g + q, r - 1);
+      gv[rt][q] = G[(size_t)col * g_i + (size_t)j * g_j];
+    }
   for (int mb = 0; mb < n; mb += 256) {
     __syncthreads();   // the previous chunk's reads of ut are done
     if (r == RT * 16) {
-      // full rank tiles: the chunk of U is one contiguous run of floats; 4 RT 16-byte loads per thread,
+      // full rank tiles: the chunk of U is one contiguous run of floats; 2 RT 16-byte loads per thread,
       // all in flight before the first is converted
-      f32x4 uv[4 * RT];
+      f32x4 uv[2 * RT];
 #pragma unroll
-      for (int k = 0; k < 4 * RT; ++k) {
-        const int idx4 = tid + 256 * k, m = idx4 / (4 * RT);
+      for (int k = 0; k < 2 * RT; ++k) {
+        const int idx4 = tid + 512 * k, m = idx4 / (4 * RT);
         uv[k] = mb + m < n ? *reinterpret_cast<const f32x4*>(U + ((size_t)mb * r + (size_t)idx4 * 4)) : f32x4{0.f, 0.f, 0.f, 0.f};
       }
 #pragma unroll
-      for (int k = 0; k < 4 * RT; ++k) {
-        const int idx4 = tid + 256 * k, m = idx4 / (4 * RT), j = 4 * (idx4 % (4 * RT));
+      for (int k = 0; k < 2 * RT; ++k) {
+        const int idx4 = tid + 512 * k, m = idx4 / (4 * RT), j = 4 * (idx4 % (4 * RT));
 #pragma unroll
-        for (int q = 0; q < 4; ++q) ut[(j + q) * UP + m] = (bf16_t)uv[k][q];
+        for (int q = 0; q < 4; ++q) ut[ut_at(j + q, m)] = (bf16_t)uv[k][q];
       }
     } else {
-      for (int idx = tid; idx < 256 * RT * 16; idx += 256) {
+      for (int idx = tid; idx < 256 * RT * 16; idx += 512) {
         const int m = idx / (RT * 16), j = idx % (RT * 16);
-        ut[j * UP + m] = (bf16_t)((mb + m < n && j < r) ? U[(size_t)(mb + m) * r + j] : 0.f);
+        ut[ut_at(j, m)] = (bf16_t)((mb + m < n && j < r) ? U[(size_t)(mb + m) * r + j] : 0.f);
       }
     }
-    const int mw = mb + 64 * wave;
+    const int mw = mb + 64 * rows_of;
     __syncthreads();   // ut is complete; the barrier's wait also covers this wavefront's tile loads
     if (mw < n) {
 #pragma unroll
@@ -344,7 +359,7 @@ __global__ __launch_bounds__(256) void lora_outer_mfma_kernel(LoraOuterArgs a) {
         bf16x8 af[RT];
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt)
-          af[rt] = *reinterpret_cast<const bf16x8*>(&ut[(rt * 16 + c) * UP + 64 * wave + 32 * st + 8 * g]);
+          af[rt] = *reinterpret_cast<const bf16x8*>(&ut[ut_at(rt * 16 + c, 64 * rows_of + 32 * st + 8 * g)]);
 #pragma unroll
         for (int cg = 0; cg < 4; ++cg) {
           const bf16_t* p = &xt[wave][st][t_row * 64 + ((cg ^ t_k) << 4) + 4 * (c & 3)];
@@ -361,39 +376,27 @@ __global__ __launch_bounds__(256) void lora_outer_mfma_kernel(LoraOuterArgs a) {
       load_tiles(mb + 256);
     }
   }
-  // lane (column c of group cg, g) holds ranks 16 rt + 4 g .. + 4
-  if (wave > 0) {
+  // lane (column c of group cg, g) holds ranks 16 rt + 4 g .. + 4; this wavefront adds up group rows_of of its half
+  const int i = i0 + 16 * rows_of + c;
+  float* const red = reinterpret_cast<float*>(&xt[0][0][0]);      // [wave][cg][lane][4]
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
+  for (int rt = 0; rt < RT; ++rt) {
+    __syncthreads();                                 // every wavefront's reads of the tiles (of the sums before) are done
 #pragma unroll
-      for (int cg = 0; cg < 4; ++cg) *reinterpret_cast<f32x4*>(red[wave - 1][rt][cg][lane]) = acc[rt][cg];
-  }
-  __syncthreads();
-  if (wave == 0) {
+    for (int cg = 0; cg < 4; ++cg) *reinterpret_cast<f32x4*>(red + ((wave * 4 + cg) * 64 + lane) * 4) = acc[rt][cg];
+    __syncthreads();
+    f32x4 v = *reinterpret_cast<const f32x4*>(red + (((wave & 4) * 4 + rows_of) * 64 + lane) * 4);
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
+    for (int w = 1; w < 4; ++w) {
+      const f32x4 o = *reinterpret_cast<const f32x4*>(red + ((((wave & 4) + w) * 4 + rows_of) * 64 + lane) * 4);
 #pragma unroll
-      for (int cg = 0; cg < 4; ++cg) {
-        const int i = i0 + 16 * cg + c;
-        if (i >= n_long) continue;
-        f32x4 v = acc[rt][cg];
+      for (int q = 0; q < 4; ++q) v[q] += o[q];
+    }
+    if (i < n_long)
 #pragma unroll
-        for (int w = 0; w < 3; ++w) {
-          const f32x4 o = *reinterpret_cast<const f32x4*>(red[w][rt][cg][lane]);
-#pragma unroll
-          for (int q = 0; q < 4; ++q) v[q] += o[q];
-        }
-        float gv[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int j = rt * 16 + 4 * g + q;
-          gv[q] = j < r ? G[(size_t)i * g_i + (size_t)j * g_j] : 0.f;
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int j = rt * 16 + 4 * g + q;
-          if (j < r) G[(size_t)i * g_i + (size_t)j * g_j] = gv[q] + a.scale * v[q];
-        }
+      for (int q = 0; q < 4; ++q) {
+        const int j = rt * 16 + 4 * g + q;
+        if (j < r) G[(size_t)i * g_i + (size_t)j * g_j] = gv[rt][q] + a.scale * v[q];
       }
   }
 }
@@ -464,16 +467,17 @@ int32_t launch_lora_outer_batch(const LoraOuterArgs& a, hipStream_t s) {
     mx = a.n_long[e] > mx ? a.n_long[e] : mx;
     tiles_ok = tiles_ok && a.n_long[e] % 8 == 0 && a.n_long[e] >= 8 && a.ldx[e] % 8 == 0 && aligned16(a.X[e]) && aligned16(a.U[e]);
   }
-  const dim3 grid((mx + 63) / 64, a.count);
   if (tiles_ok) {
+    const dim3 grid((mx + 127) / 128, a.count);
     switch ((a.r + 15) / 16) {
-      case 1: hipLaunchKernelGGL(lora_outer_mfma_kernel<1>, grid, dim3(256), 0, s, a); break;
-      case 2: hipLaunchKernelGGL(lora_outer_mfma_kernel<2>, grid, dim3(256), 0, s, a); break;
-      case 3: hipLaunchKernelGGL(lora_outer_mfma_kernel<3>, grid, dim3(256), 0, s, a); break;
-      default: hipLaunchKernelGGL(lora_outer_mfma_kernel<4>, grid, dim3(256), 0, s, a); break;
+      case 1: hipLaunchKernelGGL(lora_outer_mfma_kernel<1>, grid, dim3(512), 0, s, a); break;
+      case 2: hipLaunchKernelGGL(lora_outer_mfma_kernel<2>, grid, dim3(512), 0, s, a); break;
+      case 3: hipLaunchKernelGGL(lora_outer_mfma_kernel<3>, grid, dim3(512), 0, s, a); break;
+      default: hipLaunchKernelGGL(lora_outer_mfma_kernel<4>, grid, dim3(512), 0, s, a); break;
     }
     return post("lora_outer");
   }
+  const dim3 grid((mx + 63) / 64, a.count);
   if (a.r <= 16)
     hipLaunchKernelGGL(lora_outer_mfma_path_kernel<16>, grid, dim3(256), 256 * 16 * sizeof(float), s, a);
   else if (a.r <= 32)
