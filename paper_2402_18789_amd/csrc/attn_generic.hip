@@ -591,8 +591,11 @@ int32_t launch_attention_bwd_generic(const flexco_layer_cfg& c, const flexco_kv_
   // 14.2 / 8.9, [0, +256) 65 / 41, [216, +40) 35 / 30; 16 heads over 2 of 64, [0, +512) 573 / 515; bf16 67 / 35 and 693 / 513).  As every
   // key's block reads out as well, only while an operand's rows fit an XCD's L2 (16 heads over 2 of 256, [0, +512), bf16 of 4 MB
   // 1888 / 1630, fp32 of 8 MB 1981 / 2143).
+  // Two launches also where dQ is written over the rows of out (a row's block reads its own before).
   const size_t row_bytes = esize(c.dtype) * (size_t)win_len * c.n_q_heads * c.head_dim;
-  if (vec && aligned16(out) && (long)l * c.n_kv_heads <= 1024 && row_bytes <= (4u << 20)) { FLEXCO_BWD_D(FLEXCO_BWD_FEW) }
+  const char *o0 = (const char*)out, *q0 = (const char*)dq;
+  const bool over_out = q0 < o0 + row_bytes && o0 < q0 + row_bytes;
+  if (vec && aligned16(out) && !over_out && (long)l * c.n_kv_heads <= 1024 && row_bytes <= (4u << 20)) { FLEXCO_BWD_D(FLEXCO_BWD_FEW) }
   else if (vec) { FLEXCO_BWD_D(FLEXCO_BWD_GENERIC, true) }
   else { FLEXCO_BWD_D(FLEXCO_BWD_GENERIC, false) }
 #undef FLEXCO_BWD_D

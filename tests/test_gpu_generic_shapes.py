@@ -121,6 +121,31 @@ def test_generic_attention_backward_forms(cfg, win_start, win_len, shift):
         assert_close(name, got, ref, TOL["f32"])
 
 
+def test_generic_attention_backward_over_the_output_rows():
+    """dQ written over the rows of out (each block reads its own row before): as into a buffer of its own."""
+    print("attention backward over the output rows", flush=True)
+    cfg, win_start, win_len = D64_F32, 32, 32
+    l = win_start + win_len
+    n_pages = -(-l // cfg.page_size)
+    g = gen.rng(14, "generic_bwd_over_out")
+    dev = lambda *s: torch.from_numpy(g.standard_normal(s, dtype=np.float32)).cuda()  # noqa: E731
+    pool = HH.DevicePool(cfg, n_pages + 1)
+    pool.write_rows(np.arange(n_pages, dtype=np.int32), to_np(dev(l, cfg.kv_dim)), to_np(dev(l, cfg.kv_dim)))
+    q, do, o, lse = dev(win_len, cfg.q_dim), dev(win_len, cfg.q_dim), dev(win_len, cfg.q_dim), 5.0 + dev(win_len, cfg.n_q_heads)
+    got = []
+    for over in (False, True):
+        out = o.clone()
+        dq = out if over else torch.empty_like(q)
+        dk, dv = torch.zeros(l, cfg.kv_dim, device="cuda"), torch.zeros(l, cfg.kv_dim, device="cuda")
+        ws = torch.empty(win_len * cfg.n_q_heads * 4 + 64, dtype=torch.uint8, device="cuda")
+        B.flexco_attention_window_bwd(HH.c_cfg(cfg), pool.c, torch.arange(n_pages, dtype=torch.int32, device="cuda"), n_pages, win_start,
+                                      win_len, q, out, lse, do, dq, dk, dv, ws, ws.numel())
+        torch.cuda.synchronize()
+        got.append((to_np(dq), to_np(dk), to_np(dv)))
+    for a, b in zip(*got):
+        assert np.max(np.abs(a - b)) <= 1e-5 * np.max(np.abs(a))          # (delta's sum in another order: a few roundings of its terms)
+
+
 @pytest.mark.parametrize("cfg", [D64_F32, D128_F32, ODD_F32, WIDE_BF16])
 def test_generic_attention_forward_short_runs(cfg):
     print(f"attention forward short runs {cfg.name}", flush=True)
