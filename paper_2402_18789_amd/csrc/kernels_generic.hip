@@ -980,7 +980,7 @@ __global__ __launch_bounds__(256) void copy_rows_kernel(const char* __restrict__
 // of a LoRA matrix, addressed as S[i * s_i + j * s_j], so that the same kernels serve
 // A [r, in] (s_i = 1, s_j = in) and B [out, r] (s_i = r, s_j = 1).
 // A launch takes a batch of products (the targets of one projection, u and t, dA and dB): they are small, and a launch
-// costs 4 - 6 us whatever it does (the fp32 configuration's co-served iteration: 51 -> 41 launches, 311 -> 255 us; 35 now).
+// costs 4 - 6 us whatever it does (the fp32 configuration's co-served iteration: 51 -> 41 launches, 311 -> 255 us; 28 now).
 // --------------------------------------------------------------------------------------
 // acc[j] += sum over this thread's i of X[i] * S(i, j); low ranks: the loads of four passes at once (past the end they repeat
 // the last element, unused)
