@@ -289,8 +289,7 @@ def forward_launches(B, cfg, T, use_ia3=False):
     for name, N, K, part, left in (("qkv", qd + 2 * kd, H, scratch, not use_ia3), ("o", H, qd, scratch, True),
                                    ("gate_up", 2 * F, H, 0, False), ("down", H, F, down, False)):
         plan = B.flexco_gemm_plan(T, N, K, False, part)
-        cut = max(plan[0][3], B.flexco_gemm_k_ranges(T, N, K, False, part) if part else 0)
-        out.append((name, N * K, len(plan) if cut == 1 else 1 if left else 2))
+        out.append((name, N * K, len(plan) if plan[0][3] == 1 else 1 if left else 2))
     return out
 
 

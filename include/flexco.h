@@ -427,25 +427,24 @@ int32_t flexco_attention_window_bwd(const flexco_layer_cfg* cfg, const flexco_kv
 int32_t flexco_gemm(const void* A, const void* W, void* C, const void* bias, const void* residual,
                     int32_t M, int32_t N, int32_t K, int32_t trans_w, int32_t dtype, void* stream);
 
-/* How the bf16 matrix-core path would tile a product of these sizes (host arithmetic only: no GPU is touched, nothing
- * is launched) - the plan flexco_gemm, the frozen base projections over all tokens of the batch (Sec. 6.2; the gated
- * gate/up projection with N = 2 ffn) and the window backward's input-gradient products (Alg. 2; trans_w = 1) follow,
- * but for the products flexco_gemm_k_ranges names and, ahead of both, input-gradient products of at most 256 tiles of
- * 128 x 128 that run on one block of eight wavefronts per tile and range of K, in half the plan's ranges or fewer, and
- * forward products of more than 128 rows that run whole on 256 x 128 tiles, in one launch, where those are estimated faster.
- * 256 tile rows stand for 160, 192, 224 or 256, whichever divides M with the least left over.
+/* What the bf16 matrix-core path launches for a product of these sizes (host arithmetic only: no GPU is touched, nothing
+ * is launched) - the function flexco_gemm, the frozen base projections over all tokens of the batch (Sec. 6.2; the gated
+ * gate/up projection with N = 2 ffn and no scratch) and the window backward's input-gradient products (Alg. 2; trans_w = 1)
+ * plan with.  Every choice in it goes by estimated time.
  * part_elems: floats of split-K scratch the caller has (0 = none: flexco_gemm; the layer calls bring rows x 65536 for
  * windows of at most 256 rows and rows x 32768 for longer ones and for forward batches of at most 256 tokens; larger
  * forward batches bring rows x ffn for all but the gate/up projection, for the down projection with the memory of their
  * norm output, qkv and attention output, rows x (hidden + 2 q_dim + 2 kv_dim) / 2, in front of it).  out (host, 11
- * ints): out[0] = launches (1 or 2, side by side in the output columns), then per launch: tile rows, tile columns,
- * output columns covered, blocks K is cut over (in whole 64-wide stages, equal but for the 64-row tiles, whose ranges
- * differ by one at most), stages of the LDS ring; unused entries 0.  Errors: EINVAL (NULL, non-positive sizes), ESHAPE (K not a
- * multiple of 64 or N not a multiple of 8: such products run on the type-generic kernels). */
+ * ints): out[0] = launches (1 or 2, side by side in the output columns; the launch that adds the sums of a cut K not
+ * counted), then per launch: tile rows, tile columns, output columns covered, ranges of whole 64-wide stages K is cut into (equal
+ * to within one), stages of the LDS ring; unused entries 0.  Tile rows: 64, 128, or 160, 192, 224 and 256 (160 at 256
+ * columns only).  With trans_w, 128 x 128 and a ring of four is the kernel of eight wavefronts, a ring of two that of four.
+ * Errors: EINVAL (NULL, non-positive sizes), ESHAPE (K not a multiple of 64 or N not a multiple of 8: such products run on
+ * the type-generic kernels). */
 int32_t flexco_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t trans_w, int64_t part_elems, int32_t* out);
-/* Into how many ranges of whole 64-wide stages, equal to within one, the matrix-core path cuts K to run the same product
- * on 256 x 256 tiles instead of by the plan above (out, host, one int); 0: it follows the plan.  Not for the gated form.
- * Arguments and errors as above. */
+/* The ranges of K in that plan (out, host, one int) where the product runs in one launch of tiles of 160 to 256 rows and 256
+ * columns, 1 among them for input gradients only; 0: other tiles, or a forward product that is not cut.  Arguments and errors
+ * as above. */
 int32_t flexco_gemm_k_ranges(int32_t M, int32_t N, int32_t K, int32_t trans_w, int64_t part_elems, int32_t* out);
 
 /* Per-kernel timing with HIP events, for roofline measurement.  While a timer is running the

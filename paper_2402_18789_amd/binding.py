@@ -372,14 +372,14 @@ def flexco_gemm(A, W, Cout, bias, residual, M, N, K, trans_w, dtype, stream=None
 
 
 def flexco_gemm_plan(M, N, K, trans_w, part_elems=0):
-    """-> list of (tile rows, tile columns, output columns, K splits, ring stages), one per launch"""
+    """-> what is launched: list of (tile rows, tile columns, output columns, ranges of K, ring stages)"""
     out = (C.c_int32 * 11)()
     _check(_lib.flexco_gemm_plan(M, N, K, int(trans_w), int(part_elems), out))
     return [tuple(out[1 + 5 * i:6 + 5 * i]) for i in range(out[0])]
 
 
 def flexco_gemm_k_ranges(M, N, K, trans_w, part_elems=0):
-    """-> ranges of K the product runs in on 256 x 256 tiles, 0: it follows flexco_gemm_plan"""
+    """-> ranges of K of a product that runs in one launch on 256-column tiles (input gradients: 1 too), else 0"""
     out = C.c_int32()
     _check(_lib.flexco_gemm_k_ranges(M, N, K, int(trans_w), int(part_elems), C.byref(out)))
     return out.value

@@ -487,14 +487,9 @@ int32_t forward_projection(const flexco_layer_cfg& c, const Adapters& ad, const 
   // over K (left->splits > 1) they stay in k.gemm_part for it and y is not written
   if (left) *left = SplitSums{nullptr, 1};
   auto product = [&](const GemmExt* ext) -> int32_t {
-    if (left && c.dtype == FLEXCO_BF16 && k.gemm_part && gemm_forward_splits(y, m.T, N, K, K, K, N, ext, k.gemm_part_elems) > 1) {
-      const int32_t rc = launch_gemm(x, W, y, nullptr, nullptr, m.T, N, K, K, K, N, 0, false, c.dtype, s, ext, k.gemm_part,
-                                     k.gemm_part_elems, &left->splits);
-      left->part = k.gemm_part;
-      if (rc != FLEXCO_OK || left->splits > 1) return rc;
-      // (came out whole all the same, without bias and residual: once more with them)
-    }
-    return launch_gemm(x, W, y, bias, res, m.T, N, K, K, K, N, ldr, false, c.dtype, s, ext, k.gemm_part, k.gemm_part_elems);
+    if (left) left->part = k.gemm_part;
+    return launch_gemm(x, W, y, bias, res, m.T, N, K, K, K, N, ldr, false, c.dtype, s, ext, k.gemm_part, k.gemm_part_elems,
+                       left ? &left->splits : nullptr);
   };
   int act[3], nact = 0;
   for (int i = 0; i < n_targets; ++i)
@@ -818,7 +813,9 @@ static int32_t check_plan_args(int32_t M, int32_t N, int32_t K, int64_t part_ele
 extern "C" int32_t flexco_gemm_k_ranges(int32_t M, int32_t N, int32_t K, int32_t trans_w, int64_t part_elems, int32_t* out) {
   clear_error();
   FLEXCO_TRY(check_plan_args(M, N, K, part_elems, out));
-  *out = plan_gemm_k_ranges(M, N, K, trans_w != 0, (size_t)part_elems);
+  const GemmLaunchPlan pl = plan_gemm_mfma(M, N, K, trans_w != 0, (size_t)part_elems);
+  const GemmLaunchStep& st = pl.step[0];
+  *out = st.bm > 128 && st.bn == 256 && (trans_w || st.splits > 1) ? st.splits : 0;
   return FLEXCO_OK;
 }
 

@@ -88,7 +88,8 @@ bool kernel_timer_pair(int id, hipEvent_t* start, hipEvent_t* stop, bool first_o
 
 // ---- launchers: no validation, the entry points have done it -------------------------
 // C[M,N] = A[M,K] W[N,K]^T (+bias) (+residual);  trans_w: W is [K,N].  Leading dimensions in elements.
-// part / part_elems: optional fp32 scratch for split-K partial sums (input-gradient form)
+// part / part_elems: optional fp32 scratch for split-K partial sums.  splits_out: the caller adds them itself, and bias and residual
+// with them, where *splits_out > 1 (C is then not written)
 int32_t launch_gemm(const void* A, const void* W, void* C, const void* bias, const void* residual, int M, int N,
                     int K, size_t lda, size_t ldw, size_t ldc, size_t ldr, bool trans_w, int dtype, hipStream_t s,
                     const GemmExt* ext = nullptr, float* part = nullptr, size_t part_elems = 0, int* splits_out = nullptr);
@@ -108,15 +109,12 @@ int32_t launch_gemm_f32_norm_glu(const void* A, const void* W, void* C, const vo
                                  const F32Norm* norm, const F32Glu* glu, hipStream_t s);
 // How the bf16 MFMA path tiles a product: one or two launches side by side in the output columns, each one tile
 // shape (bm x bn), `cols` output columns, K cut over `splits` blocks, a ring of `stages` stages.  part_elems: floats of
-// split-K scratch at hand (0 = none).  The gated form is the forward plan over its 2F interleaved columns.
+// split-K scratch at hand (0 = none).  The gated form is the forward plan over its 2F interleaved columns.  bm: the rows the
+// tiles have, 160 to 256 by gemm_bf16_quad_kernel; 128 x 128 with a ring of four stages is gemm_bf16_pair_kernel in the
+// input-gradient form.
 struct GemmLaunchStep { int bm, bn, cols, splits, stages; };
 struct GemmLaunchPlan { int n; GemmLaunchStep step[2]; };
 GemmLaunchPlan plan_gemm_mfma(int M, int N, int K, bool trans_w, size_t part_elems);
-// ranges K is cut into for a forward product without bias and residual, whatever its tiles; 1 where the MFMA path does not
-// take it
-int gemm_forward_splits(const void* C, int M, int N, int K, size_t lda, size_t ldw, size_t ldc, const GemmExt* ext, size_t part_elems);
-// > 0: the product runs on 256 x 256 tiles with K in that many ranges of whole stages instead of by the plan
-int plan_gemm_k_ranges(int M, int N, int K, bool trans_w, size_t part_elems);
 // bf16 MFMA path; returns FLEXCO_EUNSUPPORTED (without launching) for shapes it does not cover
 int32_t launch_gemm_mfma(const void* A, const void* W, void* C, const void* bias, const void* residual, int M,
                          int N, int K, size_t lda, size_t ldw, size_t ldc, size_t ldr, bool trans_w,

@@ -1128,23 +1128,19 @@ auto quad_kernel(int rows) {
   return rows == 256 ? gemm_bf16_quad_kernel<256, BN, TRANS, GLU> : rows == 224 ? gemm_bf16_quad_kernel<224, BN, TRANS, GLU> : gemm_bf16_quad_kernel<192, BN, TRANS, GLU>;
 }
 
-// PAIR: the input-gradient kernel of eight wavefronts (128 x 128)
+// PAIR: the input-gradient kernel of eight wavefronts (128 x 128); BM = 256: the kernel of 160 to 256 rows, `rows` of them
 template <int BM, int BN, bool TRANS, bool GLU = false, int NSTAGES = 0, bool SPREAD = false, bool PAIR = false>
 int32_t launch_cfg(const void* A, const void* W, void* C, const void* bias, const void* res, int M, int N, int K,
                    size_t lda, size_t ldw, size_t ldc, size_t ldr, const GemmExt& ext, hipStream_t s,
                    int timer_id, float* part = nullptr, int splits = 1, bool first_of_call = true,
-                   const GemmGlu* glu_in = nullptr, bool skip_reduce = false) {
+                   const GemmGlu* glu_in = nullptr, bool skip_reduce = false, int rows = BM) {
   // all LDS is static; the 256-row tiles have a kernel of their own
   constexpr bool QUAD = BM == 256;
   constexpr int THREADS = PAIR ? 512 : 256;
   static_assert(!PAIR || (TRANS && BM == 128 && BN == 128), "the kernel of eight wavefronts has one form");
   void (*kern)(const bf16_t*, const bf16_t*, bf16_t*, const bf16_t*, const bf16_t*, int, int, int, size_t, size_t, size_t, size_t,
                int, int, GemmExt, float*, GemmGlu);
-  int rows = BM;
-  if constexpr (QUAD) {
-    us_tile256(M, (long)((N + BN - 1) / BN) * splits, (double)((K / BK + splits - 1) / splits), BN, &rows);
-    kern = quad_kernel<BN, TRANS, GLU>(rows);
-  }
+  if constexpr (QUAD) kern = quad_kernel<BN, TRANS, GLU>(rows);
   else if constexpr (PAIR) kern = gemm_bf16_pair_kernel;
   else kern = gemm_bf16_kernel<BM, BN, TRANS, GLU, NSTAGES, SPREAD>;
   GemmGlu glu;
@@ -1227,8 +1223,8 @@ static int pick_splits(int M, int N, int K, int tiles, size_t part_elems, int wa
 
 // Rates of the input-gradient form's two tile shapes with every block slot taken, PFLOP/s: fitted to twelve products of
 // 512 to 1536 rows at the 8B, 14B and 32B shapes with the 32 x 32 x 16 kernels (the 256 x 256 tile reaches 1.26 now).  What they
-// decide is the plan's tile and equal cut; plan_gemm_k_ranges prices that choice with the present kernels' times and
-// takes the 256 x 256 tile, at the number of ranges that suits it, where that is estimated 5 % better; plan_gemm_pair then puts
+// decide is a first tile and equal cut; k_ranges prices that choice with the present kernels' times and takes the
+// 256 x 256 tile, at the number of ranges that suits it, where that is estimated 7 % better; pair_ranges then puts
 // the eight-wavefront kernel in the place of 128 x 128 tiles where a window has few row tiles.
 constexpr double TRANS_RATE_128 = 0.94, TRANS_RATE_256 = 1.05;
 
@@ -1287,43 +1283,29 @@ static int thin_splits(int M, int N, int K, size_t part_elems) {
 // 220 -> 210, 160 and 250 tokens (two row tiles) level; at the 14B and 32B shapes (10, 27 and 54 KB) 0.4 % slower with it.
 static bool spread_stages(int M, size_t ldw) { return M <= 128 && ldw % 2048 == 0; }
 
-// Ranges of K in whole stages, equal to within one, to run a product on 256 x 256 tiles with, or 0: the launch plan
-// below is as good.  For products whose 256 x 256 tiles leave CUs idle (or whose last round does), at the price of partial
+// Ranges of K in whole stages, equal to within one, to run a product on 256 x 256 tiles with, or 0: the choice so far, of *us, is as
+// good.  For products whose 256 x 256 tiles leave CUs idle (or whose last round does), at the price of partial
 // sums.  1: the tiles as they are, input-gradient form only (the forward plan has that choice).
-// Measured (us, plan -> ranges): forward 1024 x 4096 x 14336 135 -> 99 (4), 2048 x 4096 x 14336 210 -> 172 (2),
+// Measured (us, the choice so far -> ranges): forward 1024 x 4096 x 14336 135 -> 99 (4), 2048 x 4096 x 14336 210 -> 172 (2),
 // 1405 x 5120 x 27648 400 -> 312 (2); input gradient 512 x 4096 x 128256 625 -> 419 (8), 512 x 4096 x 28672 152 -> 103 (8),
 // 1024 x 5120 x 7168 126 -> 74 (3), 1024 x 5120 x 5120 100 -> 60 (3), 256 x 4096 x 28672 91 -> 77 (12).
-static int k_ranges(int M, int N, int K, bool trans_w, size_t part_elems, double* est_us) {
-  if (!trans_w && M <= THIN_ROWS) return 0;         // the plan's 64 x 128 tiles
+static int k_ranges(int M, int N, int K, bool trans_w, size_t part_elems, double* us) {
   const int ns = K / BK;
   const long cols = (N + 255) / 256;
-  const GemmLaunchPlan pl = plan_gemm_mfma(M, N, K, trans_w, part_elems);
-  const GemmLaunchStep& st = pl.step[0];
-  double us;
-  if (!trans_w && st.splits == 1) {
-    us = plan_forward(M, N, K).us;
-  } else {
-    const long blocks = (long)((M + st.bm - 1) / st.bm) * ((N + st.bn - 1) / st.bn) * st.splits;
-    const double s = (double)ns / st.splits;
-    // (the input-gradient form's 128 x 128 blocks have two stages whatever their number)
-    us = (st.bm == 256 ? us_tile256(M, (long)((N + 255) / 256) * st.splits, s, 256) : !trans_w ? us_tile128(blocks, s)
-          : blocks <= 256 ? 3 + 0.85 * s : ((blocks + 511) / 512) * (3 + 1.1 * s)) + us_partial_sums(st.splits, M, N);
-  }
   int best = 0;
-  us *= trans_w ? 0.93 : 0.95;                      // (the large tiles have to win clearly)
+  double least = (trans_w ? 0.93 : 0.95) * *us;     // (the large tiles have to win clearly)
   for (int r = trans_w ? 1 : 2; r <= 16 && ns / r >= 4; ++r) {
     if (r > 1 && (size_t)r * M * N > part_elems) break;
     const double t = us_tile256(M, cols * r, (double)((ns + r - 1) / r), 256) + us_partial_sums(r, M, N);
-    if (t < us) { us = t; best = r; }
+    if (t < least) { least = t; best = r; }
   }
-  if (est_us) *est_us = best ? us : us / (trans_w ? 0.93 : 0.95);
+  if (best) *us = least;
   return best;
 }
 
-int plan_gemm_k_ranges(int M, int N, int K, bool trans_w, size_t part_elems) { return k_ranges(M, N, K, trans_w, part_elems, nullptr); }
-
-// Ranges of K (1: whole) to run an input-gradient product in on the 128 x 128 kernel of eight wavefronts, or 0: by the choice above
-// and the plan below.  One round of blocks only: more tiles than CUs are shared out better two blocks of four to a CU
+// Ranges of K (1: whole) to run an input-gradient product in on the 128 x 128 kernel of eight wavefronts, or 0: by the choice so
+// far (large: on 256-row tiles, in an estimated us).  One round of blocks only: more tiles than CUs are shared out better two blocks of
+// four to a CU
 // (512 x 14336 x 4096 83 us on this kernel, 62 on 256 x 256 tiles).  Measured on 130 products of 33 to 1024 rows at the three models'
 // shapes, weights from HBM.  Against the plan's 128 x 128 tiles, two blocks to a CU: 81 to 256 rows 0.82 - 0.95 of their time, with more
 // and with fewer rows 0.79 - 0.95 where the blocks fill the chip and 0.95 - 1.27 where they do not (640 x 4096 x 6144, 160
@@ -1331,12 +1313,9 @@ int plan_gemm_k_ranges(int M, int N, int K, bool trans_w, size_t part_elems) { r
 // stages idle CUs cost more (84 to 128 rows x 5120, 240 blocks: K 55296, 144 stages, 0.96 - 1.00; K 152064, 396 stages, 1.02 - 1.08;
 // 256 blocks of 250 stages, 4096 x 128256, 0.98 - 1.01).  Against 256 x 256 tiles by the estimates (this one's within 12 %), which see
 // those at few rows too low: 150 x 14336 x 4096 39 us against 44 where they say 46 and 42.
-static int plan_gemm_pair(int M, int N, int K, size_t part_elems) {
+static int pair_ranges(int M, int N, int K, size_t part_elems, bool large, double us) {
   const int ns = K / BK;
   const long tiles = (long)((M + 127) / 128) * ((N + 127) / 128);
-  if (tiles > 256) return 0;
-  double us;
-  const bool large = k_ranges(M, N, K, true, part_elems, &us) > 0 || plan_gemm_mfma(M, N, K, true, part_elems).step[0].bm == 256;
   us = large ? (M <= 192 ? 1.12 : 1.03) * us : 1e30;
   int best = 0;
   for (int r = 1; r <= 16 && tiles * r <= 256 && ns / r >= (r > 1 ? 4 : 1); ++r) {
@@ -1348,12 +1327,12 @@ static int plan_gemm_pair(int M, int N, int K, size_t part_elems) {
   return idle && (long_runs || (!large && (M > 256 || M <= 80))) ? 0 : best;
 }
 
-// Whether a forward product runs on 256 x 128 tiles, one launch over all columns, instead of by the choices above (other_us: their
-// estimated time).  They fill the chip where the others need a second round or leave CUs idle: measured against them, us,
+// Whether a forward product runs on 256 x 128 tiles, one launch over all columns, instead of by the choice so far (of other_us).
+// They fill the chip where the others need a second round or leave CUs idle: measured against them, us,
 // 1200 x 6144 x 4096 64 -> 52, 2048 x 4096 x 4096 63 -> 52, 1024 x 7168 x 5120 98 -> 71, 1405 x 5120 x 5120 81 -> 65,
 // gated 256 x 28672 x 4096 83 -> 63.  Time: fitted to 150 products of 129 to 2048 rows.  A round of fewer than 164 blocks
 // has to win by a tenth (1024 x 5120 x 5120, 160 blocks: 68 us where 128 x 192 tiles take 65).
-static bool plan_gemm_256x128(int M, int N, int K, double other_us) {
+static bool takes_256x128(int M, int N, int K, double other_us) {
   const long cols = (N + 127) / 128;
   int rows;
   const double us = us_tile256(M, cols, K / BK, 128, &rows);
@@ -1361,21 +1340,15 @@ static bool plan_gemm_256x128(int M, int N, int K, double other_us) {
   return M > 128 && us < (blocks >= 164 && blocks <= 256 ? 0.99 : 0.90) * other_us;
 }
 
-// Forward products without a gate: the choice above against ranges of K and the plan.  0: the plan, 1: 256 x 128 tiles, else
-// ranges of K on 256 x 256 tiles.
-static int plan_gemm_forward(int M, int N, int K, size_t part_elems) {
-  if (M <= THIN_ROWS) return 0;
-  double us;
-  const int ranges = k_ranges(M, N, K, false, part_elems, &us);
-  return plan_gemm_256x128(M, N, K, us) ? 1 : ranges;
-}
-
-// What launch_gemm_mfma does for a shape: one or two launches, each a tile shape over a range of output columns,
-// possibly with K cut across blocks.  A pure function of the arguments (host arithmetic only).
+// What the launchers below launch for a shape, and flexco_gemm_plan returns: one or two launches, each a tile shape over a range
+// of output columns, possibly with K cut across blocks.  A pure function of the arguments (host arithmetic only).  The gated
+// form is a forward product of 2F columns without scratch.
 GemmLaunchPlan plan_gemm_mfma(int M, int N, int K, bool trans_w, size_t part_elems) {
   GemmLaunchPlan pl;
   pl.n = 0;
+  const int ns = K / BK;
   auto add = [&](int bm, int bn, int cols, int splits, int stages) {
+    if (bm == 256) us_tile256(M, (long)((cols + bn - 1) / bn) * splits, (double)((ns + splits - 1) / splits), bn, &bm);     // its own rows
     pl.step[pl.n++] = GemmLaunchStep{bm, bn, cols, splits, stages};
   };
   if (trans_w) {
@@ -1402,7 +1375,16 @@ GemmLaunchPlan plan_gemm_mfma(int M, int N, int K, bool trans_w, size_t part_ele
         if (t < best - 1e-9) { best = t; sp256 = c; }
       }
     }
-    if (sp256) add(256, 256, N, sp256, 2);
+    const int cut = sp256 ? sp256 : sp;
+    const double s = (double)ns / cut;
+    // (this form's 128 x 128 blocks of four wavefronts have two stages whatever their number)
+    const long blocks = (long)tiles * cut;
+    double us = (sp256 ? us_tile256(M, (long)((N + 255) / 256) * cut, s, 256)
+                       : blocks <= 256 ? 3 + 0.85 * s : ((blocks + 511) / 512) * (3 + 1.1 * s)) + us_partial_sums(cut, M, N);
+    const int ranges = k_ranges(M, N, K, true, part_elems, &us);
+    if (const int pair = pair_ranges(M, N, K, part_elems, ranges || sp256, us)) add(128, 128, N, pair, 4);
+    else if (ranges) add(256, 256, N, ranges, 2);
+    else if (sp256) add(256, 256, N, sp256, 2);
     else add(128, 128, N, sp, 2);
     return pl;
   }
@@ -1412,15 +1394,22 @@ GemmLaunchPlan plan_gemm_mfma(int M, int N, int K, bool trans_w, size_t part_ele
   }
   // A batch of few tokens (decode-only iterations) has one or two row tiles and far fewer output tiles
   // than CUs, and its time is the weight stream's: cut K across blocks so that the whole chip pulls on it.
-  if (part_elems && M <= 256) {
-    const int tiles = ((M + 127) / 128) * ((N + 127) / 128);
-    const int sp = tiles < 192 ? pick_splits(M, N, K, tiles, part_elems, 256) : 1;
-    if (sp > 1) {
-      add(128, 128, N, sp, 4);
-      return pl;
-    }
+  int cut = 1;
+  const int tiles = ((M + 127) / 128) * ((N + 127) / 128);
+  if (part_elems && M <= 256 && tiles < 192) cut = pick_splits(M, N, K, tiles, part_elems, 256);
+  GemmPlan fp{0, 0, us_tile128((long)tiles * cut, (double)ns / cut) + us_partial_sums(cut, M, N)};
+  if (cut == 1) fp = plan_forward(M, N, K);
+  double us = fp.us;
+  const int ranges = k_ranges(M, N, K, false, part_elems, &us);
+  if (takes_256x128(M, N, K, us)) {
+    add(256, 128, N, 1, 2);
+    return pl;
   }
-  const GemmPlan fp = plan_forward(M, N, K);
+  if (ranges || cut > 1) {
+    if (ranges) add(256, 256, N, ranges, 2);
+    else add(128, 128, N, cut, 4);
+    return pl;
+  }
   const int n1 = std::min(N, 256 * fp.a256);
   if (n1 > 0) add(256, 256, n1, 1, 2);
   if (n1 < N) {
@@ -1447,89 +1436,49 @@ static bool takes_product(const void* C, const void* bias, const void* residual,
   return offsets_fit(lda, 256) && offsets_fit(ldw, 256) && (!ext || ext_fits(*ext, trans_w, N));
 }
 
-int gemm_forward_splits(const void* C, int M, int N, int K, size_t lda, size_t ldw, size_t ldc, const GemmExt* ext, size_t part_elems) {
-  if (!takes_product(C, nullptr, nullptr, N, K, lda, ldw, ldc, 0, false, ext)) return 1;
-  const int ranges = plan_gemm_forward(M, N, K, part_elems);
-  return ranges ? ranges : plan_gemm_mfma(M, N, K, false, part_elems).step[0].splits;
+// The kernel of a launch of the plan.  spread: the column tiles may start at stages of their own.
+template <bool GLU>
+static auto forward_form(const GemmLaunchStep& st, bool spread) {
+  if (st.bm == THIN_ROWS) return spread ? launch_cfg<THIN_ROWS, 128, false, GLU, 6, true> : launch_cfg<THIN_ROWS, 128, false, GLU, 6>;
+  if (st.bm > 128) return st.bn == 256 ? launch_cfg<256, 256, false, GLU> : st.bn == 192 ? launch_cfg<256, 192, false, GLU> : launch_cfg<256, 128, false, GLU>;
+  if (st.bn == 192) return launch_cfg<128, 192, false, GLU>;
+  if (st.stages == 2) return launch_cfg<128, 128, false, GLU, 2>;
+  return spread && (GLU || st.splits > 1) ? launch_cfg<128, 128, false, GLU, 0, true> : launch_cfg<128, 128, false, GLU>;
+}
+static auto input_gradient_form(const GemmLaunchStep& st) {
+  if (st.bm > 128) return launch_cfg<256, 256, true>;
+  return st.stages == 4 ? launch_cfg<128, 128, true, false, 0, false, true> : launch_cfg<128, 128, true>;
 }
 
 int32_t launch_gemm_mfma(const void* A, const void* W, void* C, const void* bias, const void* residual, int M, int N,
                          int K, size_t lda, size_t ldw, size_t ldc, size_t ldr, bool trans_w, const GemmExt* ext_in,
                          hipStream_t s, float* part, size_t part_elems, int timer_id, int* splits_out) {
   if (splits_out) *splits_out = 1;
+  if (K % BK != 0) return FLEXCO_EUNSUPPORTED;
+  const GemmLaunchPlan pl = plan_gemm_mfma(M, N, K, trans_w, part ? part_elems : 0);
+  // splits_out: the caller's next kernel adds the partial sums itself (part[split][M][N], in split order), and bias and residual
+  // with them; the reduction launch is left out
+  const bool leave = splits_out && pl.step[0].splits > 1;
+  if (leave) bias = residual = nullptr;
   if (!takes_product(C, bias, residual, N, K, lda, ldw, ldc, ldr, trans_w, ext_in)) return FLEXCO_EUNSUPPORTED;
+  if (leave) *splits_out = pl.step[0].splits;
   GemmExt ext;
   if (ext_in) ext = *ext_in; else ext.n = 0;
-  // splits_out: the caller's next kernel adds the partial sums itself (part[split][M][N], in split order) and
-  // the reduction launch is left out; bias and residual are then not applied
-  const int pair = trans_w ? plan_gemm_pair(M, N, K, part ? part_elems : 0) : 0;
-  if (pair) {
-    const bool leave = splits_out && pair > 1 && !bias && !residual;
-    if (leave) *splits_out = pair;
-    return launch_cfg<128, 128, true, false, 0, false, true>(A, W, C, bias, residual, M, N, K, lda, ldw, ldc, ldr, ext, s, timer_id, part,
-                                                             pair, true, nullptr, leave);
-  }
-  const int ranges = trans_w ? plan_gemm_k_ranges(M, N, K, true, part ? part_elems : 0) : plan_gemm_forward(M, N, K, part ? part_elems : 0);
-  if (!trans_w && ranges == 1)
-    return launch_cfg<256, 128, false>(A, W, C, bias, residual, M, N, K, lda, ldw, ldc, ldr, ext, s, timer_id);
-  if (ranges) {
-    const bool leave = splits_out && ranges > 1 && !bias && !residual;
-    if (leave) *splits_out = ranges;
-    if (trans_w)
-      return launch_cfg<256, 256, true>(A, W, C, bias, residual, M, N, K, lda, ldw, ldc, ldr, ext, s, timer_id, part, ranges, true, nullptr, leave);
-    return launch_cfg<256, 256, false>(A, W, C, bias, residual, M, N, K, lda, ldw, ldc, ldr, ext, s, timer_id, part, ranges, true, nullptr, leave);
-  }
-  const GemmLaunchPlan pl = plan_gemm_mfma(M, N, K, trans_w, part ? part_elems : 0);
-  if (trans_w) {
-    const GemmLaunchStep& st = pl.step[0];
-    const bool leave = splits_out && st.splits > 1 && !bias && !residual;
-    if (leave) *splits_out = st.splits;
-    if (st.bm == 256)
-      return launch_cfg<256, 256, true>(A, W, C, bias, residual, M, N, K, lda, ldw, ldc, ldr, ext, s, timer_id, part, st.splits,
-                                        true, nullptr, leave);
-    return launch_cfg<128, 128, true>(A, W, C, bias, residual, M, N, K, lda, ldw, ldc, ldr, ext, s, timer_id, part, st.splits, true,
-                                      nullptr, leave);
-  }
-  if (pl.step[0].bm == THIN_ROWS) {
-    const int sp = pl.step[0].splits;
-    const bool leave = splits_out && sp > 1 && !bias && !residual;
-    if (leave) *splits_out = sp;
-    const auto thin = spread_stages(M, ldw) ? launch_cfg<THIN_ROWS, 128, false, false, 6, true> : launch_cfg<THIN_ROWS, 128, false, false, 6>;
-    return thin(A, W, C, bias, residual, M, N, K, lda, ldw, ldc, ldr, ext, s, timer_id, part, sp, true, nullptr, leave);
-  }
-  if (pl.step[0].splits > 1) {
-    const bool leave = splits_out && !bias && !residual;
-    if (leave) *splits_out = pl.step[0].splits;
-    const auto cut = spread_stages(M, ldw) ? launch_cfg<128, 128, false, false, 0, true> : launch_cfg<128, 128, false>;
-    return cut(A, W, C, bias, residual, M, N, K, lda, ldw, ldc, ldr, ext, s, timer_id, part, pl.step[0].splits, true, nullptr, leave);
-  }
   int c0 = 0;
   for (int i = 0; i < pl.n; ++i) {
     const GemmLaunchStep& st = pl.step[i];
-    const bf16_t* W1 = (const bf16_t*)W + (size_t)c0 * ldw;
-    bf16_t* C1 = (bf16_t*)C + c0;
-    const bf16_t* b1 = bias ? (const bf16_t*)bias + c0 : nullptr;
-    const bf16_t* r1 = residual ? (const bf16_t*)residual + c0 : nullptr;
-    const GemmExt e1 = sub_ext(ext, c0, c0 + st.cols);
-    const bool first = i == 0;
-    int32_t rc;
-    if (st.bm == 256 && st.bn == 256)
-      rc = launch_cfg<256, 256, false>(A, W1, C1, b1, r1, M, st.cols, K, lda, ldw, ldc, ldr, e1, s, timer_id, nullptr, 1, first);
-    else if (st.bm == 256)
-      rc = launch_cfg<256, 192, false>(A, W1, C1, b1, r1, M, st.cols, K, lda, ldw, ldc, ldr, e1, s, timer_id, nullptr, 1, first);
-    else if (st.bn == 192)
-      rc = launch_cfg<128, 192, false>(A, W1, C1, b1, r1, M, st.cols, K, lda, ldw, ldc, ldr, e1, s, timer_id, nullptr, 1, first);
-    else if (st.stages == 2)
-      rc = launch_cfg<128, 128, false, false, 2>(A, W1, C1, b1, r1, M, st.cols, K, lda, ldw, ldc, ldr, e1, s, timer_id, nullptr, 1, first);
-    else
-      rc = launch_cfg<128, 128, false>(A, W1, C1, b1, r1, M, st.cols, K, lda, ldw, ldc, ldr, e1, s, timer_id, nullptr, 1, first);
+    const auto form = trans_w ? input_gradient_form(st) : forward_form<false>(st, spread_stages(M, ldw));
+    const bool all = st.cols == N;
+    const int32_t rc = form(A, (const bf16_t*)W + (size_t)c0 * ldw, (bf16_t*)C + c0, bias ? (const bf16_t*)bias + c0 : nullptr,
+                            residual ? (const bf16_t*)residual + c0 : nullptr, M, st.cols, K, lda, ldw, ldc, ldr,
+                            all ? ext : sub_ext(ext, c0, c0 + st.cols), s, timer_id, part, st.splits, i == 0, nullptr, leave, st.bm);
     if (rc) return rc;
     c0 += st.cols;
   }
   return FLEXCO_OK;
 }
 
-// Gated form: the planner of the forward form over the 2F interleaved columns; a tile of BN W-rows covers
+// Gated form: the plan of a forward product of the 2F interleaved columns; a tile of BN W-rows covers
 // BN / 2 act columns.
 int32_t launch_gemm_glu_mfma(const void* A, const void* W, void* act, int M, int F, int K, size_t lda, size_t ldw,
                              size_t ld_act, const GemmExt* ext_in, void* save_gate, void* save_up, int save_row0,
@@ -1546,36 +1495,12 @@ int32_t launch_gemm_glu_mfma(const void* A, const void* W, void* act, int M, int
   glu.save_row0 = save_row0; glu.save_rows = save_gate ? save_rows : 0; glu.ld_save = ld_save;
   const int N = 2 * F;
   const GemmLaunchPlan pl = plan_gemm_mfma(M, N, K, false, 0);
-  if (pl.step[0].bm == THIN_ROWS) {
-    const auto thin = spread_stages(M, ldw) ? launch_cfg<THIN_ROWS, 128, false, true, 6, true> : launch_cfg<THIN_ROWS, 128, false, true, 6>;
-    return thin(A, W, act, nullptr, nullptr, M, N, K, lda, ldw, ld_act, 0, ext, s, timer_id, nullptr, 1, true, &glu, false);
-  }
-  if (plan_gemm_256x128(M, N, K, plan_forward(M, N, K).us))
-    return launch_cfg<256, 128, false, true>(A, W, act, nullptr, nullptr, M, N, K, lda, ldw, ld_act, 0, ext, s, timer_id, nullptr, 1, true, &glu);
   int c0 = 0;                                       // interleaved columns done = 2 x the act columns done
   for (int i = 0; i < pl.n; ++i) {
     const GemmLaunchStep& st = pl.step[i];
     glu.col0 = c0 / 2;
-    const bool first = i == 0;
-    int32_t rc;
-    if (st.bm == 256 && st.bn == 256)
-      rc = launch_cfg<256, 256, false, true>(A, W, act, nullptr, nullptr, M, st.cols, K, lda, ldw, ld_act, 0, ext, s, timer_id,
-                                             nullptr, 1, first, &glu);
-    else if (st.bm == 256)
-      rc = launch_cfg<256, 192, false, true>(A, W, act, nullptr, nullptr, M, st.cols, K, lda, ldw, ld_act, 0, ext, s, timer_id,
-                                             nullptr, 1, first, &glu);
-    else if (st.bn == 192)
-      rc = launch_cfg<128, 192, false, true>(A, W, act, nullptr, nullptr, M, st.cols, K, lda, ldw, ld_act, 0, ext, s, timer_id,
-                                             nullptr, 1, first, &glu);
-    else if (st.stages == 2)
-      rc = launch_cfg<128, 128, false, true, 2>(A, W, act, nullptr, nullptr, M, st.cols, K, lda, ldw, ld_act, 0, ext, s, timer_id,
-                                                nullptr, 1, first, &glu);
-    else if (spread_stages(M, ldw))
-      rc = launch_cfg<128, 128, false, true, 0, true>(A, W, act, nullptr, nullptr, M, st.cols, K, lda, ldw, ld_act, 0, ext, s, timer_id,
-                                                      nullptr, 1, first, &glu);
-    else
-      rc = launch_cfg<128, 128, false, true>(A, W, act, nullptr, nullptr, M, st.cols, K, lda, ldw, ld_act, 0, ext, s, timer_id,
-                                             nullptr, 1, first, &glu);
+    const int32_t rc = forward_form<true>(st, spread_stages(M, ldw))(A, W, act, nullptr, nullptr, M, st.cols, K, lda, ldw, ld_act, 0, ext, s,
+                                                                     timer_id, nullptr, 1, i == 0, &glu, false, st.bm);
     if (rc) return rc;
     c0 += st.cols;
   }

@@ -1,5 +1,5 @@
-"""flexco_gemm_k_ranges (host arithmetic, no GPU): ranges fit the scratch and hold whole stages, and are taken where the
-256 x 256 tiles of the larger models' products would leave CUs idle."""
+"""flexco_gemm_k_ranges (host arithmetic, no GPU): the ranges of the plan's 256-column tiles, which fit the scratch and hold whole stages,
+and are taken where the 256 x 256 tiles of the larger models' products would leave CUs idle."""
 import numpy as np
 import pytest
 
@@ -17,6 +17,9 @@ def test_ranges_are_well_formed():
         trans = int(g.integers(0, 2))
         r = B.flexco_gemm_k_ranges(M, N, K, trans, pe)
         assert 0 <= r <= 16 and not (M <= 64 and r > 0 and not trans)      # (forward, few rows: the plan's 64-row tiles)
+        plan = B.flexco_gemm_plan(M, N, K, trans, pe)
+        large = len(plan) == 1 and plan[0][0] > 128 and plan[0][1] == 256
+        assert r == (plan[0][3] if large and (trans or plan[0][3] > 1) else 0)
         if r > 1:
             taken += 1
             assert r * M * N <= pe and K // 64 >= 4 * r
