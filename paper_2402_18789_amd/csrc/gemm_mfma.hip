@@ -1090,38 +1090,6 @@ __global__ __launch_bounds__(256) void gemm_splitk_reduce_kernel(const float* __
   *reinterpret_cast<bf16x4*>(C + (size_t)row * ldc + col) = o;
 }
 
-// ---- estimated times, us, of launches of `blocks` blocks over `stages` 64-wide stages of K each.  Fitted to products of
-// 256 to 2048 rows at the 8B, 14B and 32B shapes with N(0, 1) x N(0, 0.02) operands, weights not in a cache; within 10 % of
-// each of some 150 measurements but for windows of 256 rows, which wait for HBM (up to 20 % above the estimate, all shapes
-// alike).  A launch runs in rounds over the CUs; a stage of the 256-row tiles takes longer the more CUs multiply at the
-// same time (the chip's power limit: 256 x 256 tiles 1.03 us at up to 128 blocks, 1.31 at 256).
-// The rows of a "256-row" tile are M's own: tiles of M / n rows in 32s for the fewest row tiles n, or for one more, so that the last
-// tile is not left half empty (gated 300 x 28672 x 4096 95 -> 74 us, 600 rows 161 -> 122, 800 rows 164 -> 151; input gradient
-// 300 x 4096 x 28672 96 -> 86).  cols: column tiles times ranges of K.  Narrow tiles of 160 rows were no faster than of 192.
-static double us_tile256(int M, long cols, double stages, int bn, int* rows = nullptr) {
-  double best = 1e300;
-  const int few = (M + 255) / 256;
-  for (int n = few; n <= few + 1; ++n) {
-    const int bm = std::max(((M + n - 1) / n + 31) / 32 * 32, bn == 256 ? 160 : 192);
-    const long blocks = n * cols, rounds = (blocks + 255) / 256;
-    // (in one round a tile more was as often slower where it is one of few: input gradient 512 x 14336 x 4096 66 -> 72 us)
-    if (n > few && rounds == 1 && few < 4) continue;
-    // (mean over the rounds of the blocks above 128; all rounds but the last are full)
-    const double over = ((rounds - 1) * 128 + std::max(0L, blocks - (rounds - 1) * 256 - 128)) / (double)rounds;
-    const double full = bn == 256 ? 1.03 + 0.0022 * over : bn == 192 ? 0.85 + 0.0013 * over : 0.70 + 0.0009 * over;
-    // a stage of fewer rows against one of 256, measured: 256, 192 and 128 columns wide, 160, 192 and 224 rows; in one round
-    // the weights' way in weighs more, and with one row tile it is all there is
-    static const double PART[2][3][3] = {{{0.82, 0.85, 0.90}, {1, 0.90, 0.96}, {1, 0.85, 0.95}}, {{0.72, 0.80, 0.90}, {1, 0.84, 0.95}, {1, 0.74, 0.92}}};
-    const double part = bm == 256 || few == 1 ? 1.0 : PART[rounds > 1][bn == 256 ? 0 : bn == 192 ? 1 : 2][(bm - 160) / 32];
-    const double us = rounds * ((bn == 128 ? 5 : 9) + stages * full * part);
-    if (us < best * (n > few ? 0.98 : 1.0)) {
-      best = us;
-      if (rows) *rows = bm;
-    }
-  }
-  return best;
-}
-
 template <int BN, bool TRANS, bool GLU>
 auto quad_kernel(int rows) {
   if constexpr (BN == 256) if (rows == 160) return gemm_bf16_quad_kernel<160, BN, TRANS, GLU>;
@@ -1228,12 +1196,59 @@ static int pick_splits(int M, int N, int K, int tiles, size_t part_elems, int wa
 // the eight-wavefront kernel in the place of 128 x 128 tiles where a window has few row tiles.
 constexpr double TRANS_RATE_128 = 0.94, TRANS_RATE_256 = 1.05;
 
+// ---- estimated times, us, of launches of `blocks` blocks over `stages` 64-wide stages of K each.  Fitted to products of
+// 256 to 2048 rows at the 8B, 14B and 32B shapes with N(0, 1) x N(0, 0.02) operands, weights not in a cache; within 10 % of
+// each of some 150 measurements but for windows of 256 rows, which wait for HBM (up to 20 % above the estimate, all shapes
+// alike).  A launch runs in rounds over the CUs; a stage of the 256-row tiles takes longer the more CUs multiply at the
+// same time (the chip's power limit: 256 x 256 tiles 1.03 us at up to 128 blocks, 1.31 at 256).
+// The rows of a "256-row" tile are M's own: tiles of M / n rows in 32s for the fewest row tiles n, or for one more, so that the last
+// tile is not left half empty (gated 300 x 28672 x 4096 95 -> 74 us, 600 rows 161 -> 122, 800 rows 164 -> 151; input gradient
+// 300 x 4096 x 28672 96 -> 86).  cols: column tiles times ranges of K.  Narrow tiles of 160 rows were no faster than of 192.
+// (A class: what M alone decides is taken out of the planner's loops over columns and ranges.)
+class Tile256 {
+ public:
+  Tile256(int M, int bn) : few_((M + 255) / 256), bn_(bn == 256 ? 0 : bn == 192 ? 1 : 2) {
+    // a stage of fewer rows against one of 256, measured: 256, 192 and 128 columns wide, 160, 192 and 224 rows; in one round
+    // the weights' way in weighs more, and with one row tile it is all there is
+    static const double PART[2][3][3] = {{{0.82, 0.85, 0.90}, {1, 0.90, 0.96}, {1, 0.85, 0.95}}, {{0.72, 0.80, 0.90}, {1, 0.84, 0.95}, {1, 0.74, 0.92}}};
+    for (int i = 0; i < 2; ++i) {
+      const int n = few_ + i;
+      rows_[i] = std::max(((M + n - 1) / n + 31) / 32 * 32, bn == 256 ? 160 : 192);
+      for (int more = 0; more < 2; ++more) part_[i][more] = rows_[i] == 256 || few_ == 1 ? 1.0 : PART[more][bn_][(rows_[i] - 160) / 32];
+    }
+  }
+  // cols: column tiles times ranges of K; rows: those of the tiles that take this long
+  double us(long cols, double stages, int* rows = nullptr) const {
+    const double t0 = us_of(0, cols, stages);
+    // (in one round a tile more was as often slower where it is one of few: input gradient 512 x 14336 x 4096 66 -> 72 us)
+    const double t1 = few_ >= 4 || (few_ + 1) * cols > 256 ? us_of(1, cols, stages) : 1e300;
+    const bool more = t1 < t0 * 0.98;
+    if (rows) *rows = rows_[more];
+    return more ? t1 : t0;
+  }
+  // no product of these or of more columns takes less
+  double at_least(long cols, double stages) const { return cols ? std::min(us_of(0, cols, stages), us_of(1, cols, stages)) : 0.0; }
+
+ private:
+  double us_of(int i, long cols, double stages) const {
+    static const double STAGE[3] = {1.03, 0.85, 0.70}, OVER[3] = {0.0022, 0.0013, 0.0009};
+    const long blocks = (few_ + i) * cols, rounds = (blocks + 255) / 256;
+    // (blocks above 128, over the rounds; all rounds but the last are full)
+    const long over = (rounds - 1) * 128 + std::max(0L, blocks - (rounds - 1) * 256 - 128);
+    return rounds * (bn_ == 2 ? 5 : 9) + stages * part_[i][rounds > 1] * (STAGE[bn_] * rounds + OVER[bn_] * over);
+  }
+  int few_, bn_, rows_[2];       // fewest row tiles; rows of a tile with that many, and with one more
+  double part_[2][2];
+};
 static double us_tile128x192(long blocks, double stages) { return ((blocks + 255) / 256) * (4 + 0.76 * stages); }
 // 128 x 128: one four-stage block per CU, or with more blocks than CUs two two-stage blocks
 static double us_tile128(long blocks, double stages) {
   if (blocks <= 256) return 3 + 0.6 * stages;
   const long rounds = (blocks + 511) / 512;
-  return rounds * (3 + (blocks / rounds <= 460 ? 0.95 : 1.1) * stages);
+  return rounds * (3 + (blocks < 461 * rounds ? 0.95 : 1.1) * stages);
+}
+static double at_least_tile128(long blocks, double stages) {      // no more blocks take less
+  return blocks <= 256 ? (blocks ? 3 + 0.6 * stages : 0.0) : ((blocks + 511) / 512) * (3 + 0.95 * stages);
 }
 // partial sums out and back in, and the launch that adds them (also where the next kernel will add them: who comes next is not
 // known here)
@@ -1250,20 +1265,28 @@ struct GemmPlan {
 static GemmPlan plan_forward(int M, int N, int K) {
   const double ns = K / BK;
   const long tm128 = (M + 127) / 128;
+  const Tile256 wide(M, 256), narrow(M, 192);
   GemmPlan best{0, 0, 1e300};
   const int n256 = (N + 255) / 256;
-  for (int a = n256; a >= 0; --a) {
-    const int rest = N - 256 * a;                   // columns left for the narrower tiles
-    if (rest < 0 && a != n256) continue;
-    const double t_a = a ? us_tile256(M, a, ns, 256) : 0.0;
-    if (rest <= 0) {
-      if (t_a < best.us - 1e-9) best = GemmPlan{a, 0, t_a};
-      continue;
+  // (runs of eight a that cannot win, by the run's fewest wide and fewest other columns, are passed over: 512 x 128256 x 4096
+  // 8.3 us on the host without this, 1.0 with; gated 512 x 28672 x 4096 1.6 and 0.35)
+  constexpr int RUN = 8;
+  for (int top = n256; top >= 0; top -= RUN) {
+    const int low = std::max(top - RUN + 1, 0), least = std::max(N - 256 * top, 0);
+    const long c128 = tm128 * ((least + 127) / 128), c192 = (least + 191) / 192;
+    if (wide.at_least(low, ns) + std::min({at_least_tile128(c128, ns), us_tile128x192(tm128 * c192, ns), narrow.at_least(c192, ns)}) >= best.us) continue;
+    for (int a = top; a >= low; --a) {
+      const int rest = N - 256 * a;                 // columns left for the narrower tiles
+      const double t_a = a ? wide.us(a, ns) : 0.0;
+      if (rest <= 0) {
+        if (t_a < best.us - 1e-9) best = GemmPlan{a, 0, t_a};
+        continue;
+      }
+      const long c192 = (rest + 191) / 192;
+      const double t_rest[3] = {us_tile128(tm128 * ((rest + 127) / 128), ns), us_tile128x192(tm128 * c192, ns), narrow.us(c192, ns)};
+      for (int sh = 2; sh >= 0; --sh)
+        if (t_a + t_rest[sh] < best.us - 1e-9) best = GemmPlan{a, sh, t_a + t_rest[sh]};
     }
-    const long c192 = (rest + 191) / 192;
-    const double t_rest[3] = {us_tile128(tm128 * ((rest + 127) / 128), ns), us_tile128x192(tm128 * c192, ns), us_tile256(M, c192, ns, 192)};
-    for (int sh = 2; sh >= 0; --sh)
-      if (t_a + t_rest[sh] < best.us - 1e-9) best = GemmPlan{a, sh, t_a + t_rest[sh]};
   }
   return best;
 }
@@ -1292,11 +1315,12 @@ static bool spread_stages(int M, size_t ldw) { return M <= 128 && ldw % 2048 == 
 static int k_ranges(int M, int N, int K, bool trans_w, size_t part_elems, double* us) {
   const int ns = K / BK;
   const long cols = (N + 255) / 256;
+  const Tile256 tile(M, 256);
   int best = 0;
   double least = (trans_w ? 0.93 : 0.95) * *us;     // (the large tiles have to win clearly)
   for (int r = trans_w ? 1 : 2; r <= 16 && ns / r >= 4; ++r) {
     if (r > 1 && (size_t)r * M * N > part_elems) break;
-    const double t = us_tile256(M, cols * r, (double)((ns + r - 1) / r), 256) + us_partial_sums(r, M, N);
+    const double t = tile.us(cols * r, (double)((ns + r - 1) / r)) + us_partial_sums(r, M, N);
     if (t < least) { least = t; best = r; }
   }
   if (best) *us = least;
@@ -1335,7 +1359,7 @@ static int pair_ranges(int M, int N, int K, size_t part_elems, bool large, doubl
 static bool takes_256x128(int M, int N, int K, double other_us) {
   const long cols = (N + 127) / 128;
   int rows;
-  const double us = us_tile256(M, cols, K / BK, 128, &rows);
+  const double us = Tile256(M, 128).us(cols, K / BK, &rows);
   const long blocks = (M + rows - 1) / rows * cols;
   return M > 128 && us < (blocks >= 164 && blocks <= 256 ? 0.99 : 0.90) * other_us;
 }
@@ -1348,7 +1372,7 @@ GemmLaunchPlan plan_gemm_mfma(int M, int N, int K, bool trans_w, size_t part_ele
   pl.n = 0;
   const int ns = K / BK;
   auto add = [&](int bm, int bn, int cols, int splits, int stages) {
-    if (bm == 256) us_tile256(M, (long)((cols + bn - 1) / bn) * splits, (double)((ns + splits - 1) / splits), bn, &bm);     // its own rows
+    if (bm == 256) Tile256(M, bn).us((long)((cols + bn - 1) / bn) * splits, (double)((ns + splits - 1) / splits), &bm);     // M's own rows
     pl.step[pl.n++] = GemmLaunchStep{bm, bn, cols, splits, stages};
   };
   if (trans_w) {
@@ -1379,7 +1403,7 @@ GemmLaunchPlan plan_gemm_mfma(int M, int N, int K, bool trans_w, size_t part_ele
     const double s = (double)ns / cut;
     // (this form's 128 x 128 blocks of four wavefronts have two stages whatever their number)
     const long blocks = (long)tiles * cut;
-    double us = (sp256 ? us_tile256(M, (long)((N + 255) / 256) * cut, s, 256)
+    double us = (sp256 ? Tile256(M, 256).us((long)((N + 255) / 256) * cut, s)
                        : blocks <= 256 ? 3 + 0.85 * s : ((blocks + 511) / 512) * (3 + 1.1 * s)) + us_partial_sums(cut, M, N);
     const int ranges = k_ranges(M, N, K, true, part_elems, &us);
     if (const int pair = pair_ranges(M, N, K, part_elems, ranges || sp256, us)) add(128, 128, N, pair, 4);

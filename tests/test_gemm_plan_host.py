@@ -1,6 +1,8 @@
 """The projection kernels' launches (flexco_gemm_plan: host arithmetic, no GPU, the function the launchers plan with): those of the
 configurations' own products are what the measurements chose, and any plan is well formed - its launches cover the output
 columns exactly once with tile shapes the kernels are built for, and ranges of K are whole 64-wide stages and fit the scratch."""
+import time
+
 import numpy as np
 import pytest
 
@@ -101,6 +103,21 @@ def test_any_plan_is_well_formed():
             if splits > 1:
                 assert splits * M * N <= pe and len(plan) == 1
                 assert K // 64 // splits >= 4
+
+
+# Planning is host time of every call: the search over the columns does not cost by their number (a loss head's 152064 columns
+# against 1024; every one of 594 column splits priced: 10 to 20 times as long)
+def test_planning_of_many_columns_is_quick():
+    def us(M, N, K):
+        best = 1e9
+        for _ in range(20):
+            t0 = time.perf_counter()
+            for _ in range(50):
+                B.flexco_gemm_plan(M, N, K, 0, 0)
+            best = min(best, time.perf_counter() - t0)
+        return best / 50 * 1e6
+    few, many = us(300, 1024, 5120), us(300, 152064, 5120)
+    assert many < 3 * few, (few, many)
 
 
 def test_rejects_shapes_the_matrix_core_path_does_not_take():
