@@ -1444,19 +1444,22 @@ int32_t launch_swiglu_bwd(const void* gate, const void* up, const void* dact, vo
 }
 
 int32_t launch_remat(const RematArgs& a, int dtype, hipStream_t s) {
-  if (a.n == 0 || (!a.act && a.norms == 0)) return FLEXCO_OK;
-  const bool act_vec = vec_ok(dtype, a.F, {a.gate, a.up, a.act});
-  const bool norm_vec = vec_ok(dtype, a.H, {a.x[0], a.g[0], a.h[0], a.x[1], a.g[1], a.h[1]});
-  if (a.act && a.norms > 0 && act_vec != norm_vec) {       // each in the form its rows allow
-    RematArgs one = a, two = a;
-    one.norms = 0;
-    two.act = nullptr;
-    const int32_t rc = launch_remat(one, dtype, s);
-    return rc ? rc : launch_remat(two, dtype, s);
+  if (a.n == 0) return FLEXCO_OK;
+  // each in the form that its own rows allow: one launch, or two where some are not 16-byte aligned
+  for (const bool vec : {true, false}) {
+    RematArgs p = a;
+    p.norms = 0;
+    if (a.act && vec_ok(dtype, a.F, {a.gate, a.up, a.act}) != vec) p.act = nullptr;
+    for (int z = 0; z < a.norms; ++z)
+      if (vec_ok(dtype, a.H, {a.x[z], a.g[z], a.h[z]}) == vec) {
+        p.x[p.norms] = a.x[z];
+        p.g[p.norms] = a.g[z];
+        p.h[p.norms++] = a.h[z];
+      }
+    if (!p.act && p.norms == 0) continue;
+    const int per = 256 * (vec ? (dtype == FLEXCO_BF16 ? 8 : 4) : 1), act_blocks = p.act ? (p.F + per - 1) / per : 0;
+    DISPATCH_TV(dtype, vec, hipLaunchKernelGGL((remat_kernel<T, VEC>), dim3(p.n * (act_blocks + p.norms)), dim3(256), 0, s, p, act_blocks));
   }
-  const bool vec = a.act ? act_vec : norm_vec;
-  const int per = 256 * (vec ? (dtype == FLEXCO_BF16 ? 8 : 4) : 1), act_blocks = a.act ? (a.F + per - 1) / per : 0;
-  DISPATCH_TV(dtype, vec, hipLaunchKernelGGL((remat_kernel<T, VEC>), dim3(a.n * (act_blocks + a.norms)), dim3(256), 0, s, a, act_blocks));
   return post_launch("remat");
 }
 

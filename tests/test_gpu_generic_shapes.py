@@ -12,7 +12,7 @@ if torch.cuda.is_available():
     import paper_2402_18789_amd.binding as B
     from paper_2402_18789_amd import host as HH
     from oracle import ops as OO
-    from gpu_common import to_np, TOL, assert_close
+    from gpu_common import Case, to_np, TOL, assert_close
     from test_gpu_parity import attention_case
 
 C1 = CONFIGS["c1_tiny_f32"]
@@ -144,6 +144,31 @@ def test_generic_attention_backward_over_the_output_rows():
         got.append((to_np(dq), to_np(dk), to_np(dv)))
     for a, b in zip(*got):
         assert np.max(np.abs(a - b)) <= 1e-5 * np.max(np.abs(a))          # (delta's sum in another order: a few roundings of its terms)
+
+
+# Rows of one kept activation off their 16-byte alignment: the norm that is computed again from them goes element by element, the
+# others as ever - gate's gradient reads the second norm's rows only and keeps its bits, q's the first norm's.
+def test_rematerialised_rows_of_different_alignment():
+    print("layer backward, saved_x off its alignment", flush=True)
+    cfg = C1.with_(name="remat_f32", hidden=1024, lora_targets=("q", "gate", "down"))
+    case = Case(cfg, gen.mixed_batch(cfg.page_size, 3, finetune=[(0, 40, 40)]), seed=3)
+    (r,) = case.batch.requests
+    case.forward(case.batch, gen.layer_input(cfg, 3, 40), oracle=False)
+    st, pages = case.d_ft[r.seq_id], torch.from_numpy(case.dpages(case.batch.seq_pages[r.seq_id])).cuda()
+    dY = torch.from_numpy(gen.layer_input(cfg, 4, 40, tag="dy")).cuda()
+    ws = HH.Workspace(case.dev.c, 0, 0, 40, 40)
+    off = torch.zeros(st.x.numel() + 1, device="cuda")[1:].copy_(st.x.flatten())
+    assert st.x.data_ptr() % 16 == 0 and off.data_ptr() % 16 == 4
+    got = []
+    for rows in (st.x, off):
+        st.c.saved_x = rows.data_ptr()
+        case.dev.zero_grads()
+        st.zero_accum()
+        B.flexco_lora_bwd(case.dev.c, case.dev.w, case.dev.lora, case.d_pool.c, pages, len(pages), st.c, 0, 40, dY, None, ws.ptr, ws.bytes)
+        torch.cuda.synchronize()
+        got.append({t: case.dev.dA[t].clone() for t in cfg.lora_targets})
+    assert torch.equal(got[0]["gate"], got[1]["gate"]) and torch.equal(got[0]["down"], got[1]["down"])
+    assert_close("dA q", to_np(got[1]["q"]), to_np(got[0]["q"]), 1e-5)           # (the row's squares in another order)
 
 
 @pytest.mark.parametrize("cfg", [D64_F32, D128_F32, ODD_F32, WIDE_BF16])
