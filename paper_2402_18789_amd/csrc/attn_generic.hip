@@ -376,8 +376,8 @@ __device__ inline void bwd_dq_row(const size_t i, const int h, const T* __restri
 // one wave per (key j, kv head): sums over every window row that sees key j and every
 // query head of the group; adds into the KV-gradient accumulator rows (Sec. 7).
 // VEC: rows of q and dout are read 16 bytes at a time (their alignment is the caller's).  FEW: for launches that leave slots empty
-// (more rows at a time per lane), delta computed here from the rows of out.
-template <typename T, int DU, bool VEC, bool FEW>
+// (more rows at a time per lane).  DELTA: delta computed here from the rows of out.
+template <typename T, int DU, bool VEC, bool FEW, bool DELTA>
 __device__ inline void bwd_dkv_key(const int j, const int kvh, const T* __restrict__ q, const T* __restrict__ dout,
                                    const T* __restrict__ out, const float* __restrict__ lse, const float* __restrict__ delta,
                                    const T* __restrict__ kp, const T* __restrict__ vp, const int32_t* __restrict__ pages,
@@ -406,7 +406,7 @@ __device__ inline void bwd_dkv_key(const int j, const int kvh, const T* __restri
     const T* qr = q + row * d;
     const T* dor = dout + row * d;
     const float row_lse = lse[row];
-    float row_delta = FEW ? 0.f : delta[row];
+    float row_delta = DELTA ? 0.f : delta[row];
     float s = 0.f, dp = 0.f;
 #pragma unroll VEC ? (FEW ? 8 : 4) : 2
     for (int dd = 0; dd < d; dd += N) {
@@ -423,7 +423,7 @@ __device__ inline void bwd_dkv_key(const int j, const int kvh, const T* __restri
         s += qv[e] * ks[dd + e];
         dp += ov[e] * vs[dd + e];
       }
-      if constexpr (FEW) {
+      if constexpr (DELTA) {
         float av[N];
         Vec<T>::load(out + row * d + dd, av);
 #pragma unroll
@@ -470,7 +470,7 @@ __global__ __launch_bounds__(64) void attn_bwd_dq_generic_kernel(const T* __rest
   bwd_dq_row<T, DU>(blockIdx.x, blockIdx.y, q, dout, out, lse, delta, kp, vp, pages, dq, win_start, nq, nkv, d, ps, scale, smem);
 }
 
-template <typename T, int DU, bool VEC>
+template <typename T, int DU, bool VEC, bool FEW>
 __global__ __launch_bounds__(64) void attn_bwd_dkv_generic_kernel(const T* __restrict__ q, const T* __restrict__ dout,
                                                                   const float* __restrict__ lse, const float* __restrict__ delta,
                                                                   const T* __restrict__ kp, const T* __restrict__ vp,
@@ -478,8 +478,8 @@ __global__ __launch_bounds__(64) void attn_bwd_dkv_generic_kernel(const T* __res
                                                                   float* __restrict__ dv_accum, int win_start, int win_len, int nq,
                                                                   int nkv, int d, int ps, float scale) {
   extern __shared__ float smem[];
-  bwd_dkv_key<T, DU, VEC, false>(blockIdx.x, blockIdx.y, q, dout, (const T*)nullptr, lse, delta, kp, vp, pages, dk_accum, dv_accum,
-                                 win_start, win_len, nq, nkv, d, ps, scale, smem);
+  bwd_dkv_key<T, DU, VEC, FEW, false>(blockIdx.x, blockIdx.y, q, dout, (const T*)nullptr, lse, delta, kp, vp, pages, dk_accum, dv_accum,
+                                      win_start, win_len, nq, nkv, d, ps, scale, smem);
 }
 
 // Both in one launch, the rows of dQ first (their blocks walk longer): nothing of one is read by the other, as a key's block
@@ -497,8 +497,8 @@ __global__ __launch_bounds__(64) void attn_bwd_few_generic_kernel(const T* __res
   if (b < n_dq)
     bwd_dq_row<T, DU>(b / nq, b % nq, q, dout, out, lse, delta, kp, vp, pages, dq, win_start, nq, nkv, d, ps, scale, smem);
   else
-    bwd_dkv_key<T, DU, true, true>((b - n_dq) / nkv, (b - n_dq) % nkv, q, dout, out, lse, delta, kp, vp, pages, dk_accum, dv_accum,
-                                   win_start, win_len, nq, nkv, d, ps, scale, smem);
+    bwd_dkv_key<T, DU, true, true, true>((b - n_dq) / nkv, (b - n_dq) % nkv, q, dout, out, lse, delta, kp, vp, pages, dk_accum, dv_accum,
+                                         win_start, win_len, nq, nkv, d, ps, scale, smem);
 }
 
 #define DISPATCH_T(dtype, ...)                                   \
@@ -568,12 +568,12 @@ int32_t launch_attention_bwd_generic(const flexco_layer_cfg& c, const flexco_kv_
   const int l = win_start + win_len;
   const size_t shm = sizeof(float) * 2 * (size_t)c.head_dim;
   const bool vec = aligned16(q) && aligned16(dout);      // (head_dim rows are whole 16-byte units)
-#define FLEXCO_BWD_GENERIC(DU_, VEC_)                                                                                  \
+#define FLEXCO_BWD_GENERIC(DU_, VEC_, FEW_)                                                                            \
   DISPATCH_T(c.dtype, {                                                                                               \
     hipLaunchKernelGGL((attn_bwd_dq_generic_kernel<T, DU_>), dim3(win_len, c.n_q_heads), dim3(64), shm, s, (const T*)q, (const T*)dout, \
                        (const T*)out, lse, delta, (const T*)pool.k_pages, (const T*)pool.v_pages, seq_pages, (T*)dq, win_start,         \
                        c.n_q_heads, c.n_kv_heads, c.head_dim, c.page_size, scale);                                    \
-    hipLaunchKernelGGL((attn_bwd_dkv_generic_kernel<T, DU_, VEC_>), dim3(l, c.n_kv_heads), dim3(64), shm, s, (const T*)q, (const T*)dout, \
+    hipLaunchKernelGGL((attn_bwd_dkv_generic_kernel<T, DU_, VEC_, FEW_>), dim3(l, c.n_kv_heads), dim3(64), shm, s, (const T*)q, (const T*)dout, \
                        lse, delta, (const T*)pool.k_pages, (const T*)pool.v_pages, seq_pages, dk_accum, dv_accum, win_start, win_len,   \
                        c.n_q_heads, c.n_kv_heads, c.head_dim, c.page_size, scale);                                    \
   })
@@ -591,13 +591,17 @@ int32_t launch_attention_bwd_generic(const flexco_layer_cfg& c, const flexco_kv_
   // 14.2 / 8.9, [0, +256) 65 / 41, [216, +40) 35 / 30; 16 heads over 2 of 64, [0, +512) 573 / 515; bf16 67 / 35 and 693 / 513).  As every
   // key's block reads out as well, only while an operand's rows fit an XCD's L2 (16 heads over 2 of 256, [0, +512), bf16 of 4 MB
   // 1888 / 1630, fp32 of 8 MB 1981 / 2143).
-  // Two launches also where dQ is written over the rows of out (a row's block reads its own before).
+  // Two launches also where dQ is written over the rows of out (a row's block reads its own before).  Their second is then the form
+  // with more rows at a time all the same (fp32, one row at a time / more: 32 heads over 1 of 64, [0, +1024) 5088 / 4092 us, 16 over 2 of
+  // 64, [100, +156), dQ over out 183 / 161; head_dim 256 and bf16 level).
   const size_t row_bytes = esize(c.dtype) * (size_t)win_len * c.n_q_heads * c.head_dim;
   const char *o0 = (const char*)out, *q0 = (const char*)dq;
   const bool over_out = q0 < o0 + row_bytes && o0 < q0 + row_bytes;
-  if (vec && aligned16(out) && !over_out && (long)l * c.n_kv_heads <= 1024 && row_bytes <= (4u << 20)) { FLEXCO_BWD_D(FLEXCO_BWD_FEW) }
-  else if (vec) { FLEXCO_BWD_D(FLEXCO_BWD_GENERIC, true) }
-  else { FLEXCO_BWD_D(FLEXCO_BWD_GENERIC, false) }
+  const bool few = (long)l * c.n_kv_heads <= 1024;
+  if (vec && few && aligned16(out) && !over_out && row_bytes <= (4u << 20)) { FLEXCO_BWD_D(FLEXCO_BWD_FEW) }
+  else if (vec && few) { FLEXCO_BWD_D(FLEXCO_BWD_GENERIC, true, true) }
+  else if (vec) { FLEXCO_BWD_D(FLEXCO_BWD_GENERIC, true, false) }
+  else { FLEXCO_BWD_D(FLEXCO_BWD_GENERIC, false, false) }
 #undef FLEXCO_BWD_D
 #undef FLEXCO_BWD_FEW
 #undef FLEXCO_BWD_GENERIC

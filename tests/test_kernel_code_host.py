@@ -85,6 +85,14 @@ def test_rows_of_the_generic_attention_backward_are_fetched_together(code, name,
     assert len(forms) >= 6 and all(k >= at_least for k in forms.values()), forms
 
 
+# ... and dK / dV of few key blocks has its form with 16 / 8 / 4 pairs at a time whether or not dQ is in the same launch
+@pytest.mark.parametrize("du,pairs", [(1, 16), (2, 8), (4, 4)])
+def test_key_value_gradients_of_few_blocks_fetch_more_rows_at_a_time(code, du, pairs):
+    forms = [sum(op.startswith("v_readlane") for _, op, _ in ins) for n, ins in code.items()
+             if "attn_bwd_dkv_generic_kernel" in n and "Li%dELb1ELb1E" % du in n and not n.endswith(".kd")]
+    assert len(forms) == 2 and all(k >= pairs * 4 for k in forms), forms
+
+
 # The attention's steps over pages that every row sees whole, lists of chunks alone: what a step does for its scores is what bounds it
 # so no select or compare beside those of the running maximum
 def test_attention_steps_of_chunks_alone_select_once(code):
