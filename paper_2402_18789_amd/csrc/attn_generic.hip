@@ -590,7 +590,10 @@ int32_t launch_attention_bwd_generic(const flexco_layer_cfg& c, const flexco_kv_
   // the second with as many rows at a time / one; fp32, windows [start, +rows): 4 heads of 64, [0, +8) 9.1 / 4.6 us, [32, +32)
   // 14.2 / 8.9, [0, +256) 65 / 41, [216, +40) 35 / 30; 16 heads over 2 of 64, [0, +512) 573 / 515; bf16 67 / 35 and 693 / 513).  As every
   // key's block reads out as well, only while an operand's rows fit an XCD's L2 (16 heads over 2 of 256, [0, +512), bf16 of 4 MB
-  // 1888 / 1630, fp32 of 8 MB 1981 / 2143).
+  // 1888 / 1630, fp32 of 8 MB 1981 / 2143), and in fp32 only while the key blocks that see the whole window are few or the rows
+  // short: it is the third operand that bounds them then.  Rows in MB x those blocks, measured over 202 windows (two launches / one):
+  // up to 571 0.48 - 1.02 of the time, 720 to 960 (64 heads over 2 of 64, [448, +64)) 324 / 357, 1024 (32 over 1 of 64, [512, +256))
+  // 1059 / 1264, 2048 (16 over 1 of 256) 1700 / 2285; bf16 0.44 - 0.96 at any.
   // Two launches also where dQ is written over the rows of out (a row's block reads its own before).  Their second is then the form
   // with more rows at a time all the same (fp32, one row at a time / more: 32 heads over 1 of 64, [0, +1024) 5088 / 4092 us, 16 over 2 of
   // 64, [100, +156), dQ over out 183 / 161; head_dim 256 and bf16 level).
@@ -598,7 +601,8 @@ int32_t launch_attention_bwd_generic(const flexco_layer_cfg& c, const flexco_kv_
   const char *o0 = (const char*)out, *q0 = (const char*)dq;
   const bool over_out = q0 < o0 + row_bytes && o0 < q0 + row_bytes;
   const bool few = (long)l * c.n_kv_heads <= 1024;
-  if (vec && few && aligned16(out) && !over_out && row_bytes <= (4u << 20)) { FLEXCO_BWD_D(FLEXCO_BWD_FEW) }
+  const bool third_ok = row_bytes <= (4u << 20) && (c.dtype == FLEXCO_BF16 || row_bytes * win_start * c.n_kv_heads <= (640u << 20));
+  if (vec && few && aligned16(out) && !over_out && third_ok) { FLEXCO_BWD_D(FLEXCO_BWD_FEW) }
   else if (vec && few) { FLEXCO_BWD_D(FLEXCO_BWD_GENERIC, true, true) }
   else if (vec) { FLEXCO_BWD_D(FLEXCO_BWD_GENERIC, true, false) }
   else { FLEXCO_BWD_D(FLEXCO_BWD_GENERIC, false, false) }
