@@ -558,6 +558,35 @@ __global__ __launch_bounds__(SUMS ? 512 : 256) void rope_append_kernel(T* __rest
     const int v_lo = (int)((long)nv * j / len), v_hi = (int)((long)nv * (j + 1) / len);
     const bool whole = len == RUN && ps % N == 0;
     const int v0 = (nq + nkv) * d;
+    // Partial sums: a piece of a row is a round trip per four splits, so a run's rows are not one thread's, one after the other:
+    // each (row, piece) has a thread of its own, and a channel's positions meet in LDS (a chunk's tokens, this kernel: 8B shape
+    // 128 tokens in four ranges 36 -> 10 us, 32B 300 tokens 67 -> 17, 600 tokens 99 -> 23; rows that lie whole take 11 to 14).
+    if constexpr (SUMS) {
+      if (len > 1) {
+        __shared__ __attribute__((aligned(16))) T tile[THREADS * N];      // [channel][position in the run]
+        const int at_once = THREADS / len;                                // pieces
+        for (int p0 = v_lo; p0 < v_hi; p0 += at_once) {
+          const int np = min(at_once, v_hi - p0), k = THREADS - 1 - threadIdx.x;      // (the threads with the least to rotate first)
+          if (p0 > v_lo) __syncthreads();                                 // the tile's readers of the round before are done
+          if (k < np * len) {
+            const int jj = k / np, p = k % np;
+            float v[1][N];
+            load(t0 + jj, v0 + (p0 + p) * N, v, 0);
+#pragma unroll
+            for (int c = 0; c < N; ++c) tile[(p * N + c) * len + jj] = (T)v[0][c];
+          }
+          __syncthreads();
+          const int per = whole ? RUN / N : len, n_out = np * N * per;    // stores per channel: 16 bytes, or one position
+          for (int o = threadIdx.x; o < n_out; o += THREADS) {
+            const int ch = p0 * N + o / per, at = o % per, kh = ch / d, i = ch % d;
+            T* dst = vp + ((page * nkv + kh) * (size_t)d + i) * ps + pip0;
+            if (whole) *reinterpret_cast<f32x4*>(dst + at * N) = *reinterpret_cast<const f32x4*>(tile + o * N);
+            else dst[at] = tile[o];
+          }
+        }
+        return;
+      }
+    }
     for (int vi = v_lo + THREADS - 1 - threadIdx.x; vi < v_hi; vi += THREADS) {      // (the threads with the least to rotate first)
       const int idx = vi * N, kh = idx / d, i = idx % d;
       T* dst = vp + ((page * nkv + kh) * (size_t)d + i) * ps + pip0;

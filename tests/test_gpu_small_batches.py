@@ -29,6 +29,41 @@ def test_layer_partial_sums_left_to_the_next_kernel(chunk, window):
     run_layer_case(WIDE, b, ft_window=window, prefill_chunk=chunk, bwd_windows=[window, window], seed=17)
 
 
+# ... of a run's v rows, added by the blocks that store its positions side by side: pages of 16 (whole runs and pieces of them), of 24 and of
+# 12 (no 16-byte pieces), runs of 2 to 15 tokens, and v rows of more pieces than a block has threads (40 kv heads)
+@pytest.mark.parametrize("kv,page,chunk,window", [(4, 16, 33, 20), (4, 24, 30, 25), (4, 12, 29, 17), (4, 16, 2, 15), (40, 16, 30, 19)])
+def test_layer_partial_sums_of_runs_of_tokens(kv, page, chunk, window):
+    cfg = WIDE.with_(name="runs", n_kv_heads=kv, n_q_heads=max(16, kv), page_size=page, lora_targets=("q", "v"))
+    b = gen.mixed_batch(page, 23, decode_ctx=(1, 5, 40), prefill=[(3, chunk, 3 + chunk)], finetune=[(0, window, 2 * window + 1)])
+    print(f"layer of {b.n_tokens} tokens, {kv} kv heads, pages of {page}", flush=True)
+    assert B.flexco_gemm_plan(b.n_tokens, cfg.q_dim + 2 * cfg.kv_dim, cfg.hidden, 0, b.n_tokens * 32768)[0][3] > 1
+    run_layer_case(cfg, b, ft_window=window, prefill_chunk=chunk, bwd_windows=[window, window + 1], seed=23)
+
+
+# ... in about the time that as many single tokens take (one thread per piece and run: three to four times as long)
+def test_rotation_of_a_chunks_partial_sums_takes_no_longer_than_of_single_tokens():
+    kid, us = B.KERNEL_IDS["elemwise"], {}
+    cfg = WIDE.with_(name="rope_time", n_kv_heads=8, lora_targets=())
+    dev = HH.DeviceLayer(cfg, gen.layer_weights(cfg, 29, 0))
+    for name, b in (("single", gen.mixed_batch(16, 1, decode_ctx=(20,) * 128)), ("chunk", gen.mixed_batch(16, 1, prefill=[(0, 128, 128)]))):
+        db, pool = HH.DeviceBatch(cfg, b.requests, b.seq_pages, b.num_pages), HH.DevicePool(cfg, b.num_pages)
+        ws = HH.Workspace(dev.c, 128, db.host_maps.n_parts)
+        x = torch.randn(128, cfg.hidden, device="cuda").bfloat16()
+        y = torch.empty_like(x)
+        B.flexco_layer_forward(dev.c, dev.w, None, db.maps, x, y, pool.c, None, ws.ptr, ws.bytes)
+        B.flexco_kernel_timer_sample(kid, 1)
+        B.flexco_kernel_timer_start(kid, 64)
+        for _ in range(8):
+            B.flexco_layer_forward(dev.c, dev.w, None, db.maps, x, y, pool.c, None, ws.ptr, ws.bytes)
+        torch.cuda.synchronize()
+        each = B.flexco_kernel_timer_read(kid)
+        B.flexco_kernel_timer_stop(kid)
+        us[name] = 1e3 * min(each[1::len(each) // 8])           # the rotation, between the two norms
+    print(f"rotation: {us}", flush=True)
+    assert B.flexco_gemm_plan(128, cfg.q_dim + 2 * cfg.kv_dim, cfg.hidden, 0, 128 * 32768)[0][3] > 1
+    assert us["chunk"] <= 1.6 * us["single"]
+
+
 # Rows of every weight a multiple of 4 KB apart, at most 128 tokens: the column tiles of the products start at stages of their own - the 64-row
 # form cut over K in unequal ranges, the 128 x 128 form in equal ones, the gated form of either
 @pytest.mark.parametrize("chunk,window", [(12, 14), (30, 30), (31, 30), (47, 46), (62, 62)])
