@@ -450,7 +450,7 @@ int32_t gated_gemm(const flexco_layer_cfg& c, const flexco_maps& m, const void* 
                    const GemmExt* ext, const flexco_ft_state* ft, GluOut& glu, hipStream_t s, const F32Norm* norm) {
   const size_t e = esize(c.dtype);
   if (c.dtype == FLEXCO_F32) {
-    if (!gemm_f32_takes_norm(m.T, 2 * F, K, x, W, norm ? *norm : F32Norm{})) return FLEXCO_EUNSUPPORTED;
+    if (!gemm_f32_takes_gate(m.T, F, K) || !gemm_f32_takes_norm(m.T, 2 * F, K, x, W, norm ? *norm : F32Norm{})) return FLEXCO_EUNSUPPORTED;
     const F32Glu keep{ft ? ft_rows(ft->saved_gate, m, F) : nullptr, ft ? ft_rows(ft->saved_up, m, F) : nullptr, m.ft_tok0, ft ? m.n_ft : 0};
     KernelTimerScope ts(FLEXCO_K_GENERIC, s);
     const int32_t rc = launch_gemm_f32_norm_glu(x, W, glu.act, nullptr, m.T, F, K, glu.ld_act, norm, &keep, s);

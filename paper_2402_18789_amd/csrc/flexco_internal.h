@@ -105,6 +105,7 @@ struct F32Norm { const float* g; float eps; float* h; float* save; int save_row0
 // rows [save_row0, + save_rows) of gate and up are kept (N wide), NULL: none
 struct F32Glu { float *save_gate, *save_up; int save_row0, save_rows; };
 bool gemm_f32_takes_norm(int M, int N, int K, const void* x, const void* W, const F32Norm& norm);
+bool gemm_f32_takes_gate(int M, int F, int K);       // F: columns of gate
 int32_t launch_gemm_f32_norm_glu(const void* A, const void* W, void* C, const void* bias, int M, int N, int K, size_t ldc,
                                  const F32Norm* norm, const F32Glu* glu, hipStream_t s);
 // How the bf16 MFMA path tiles a product: one or two launches side by side in the output columns, each one tile

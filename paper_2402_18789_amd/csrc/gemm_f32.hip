@@ -179,6 +179,14 @@ bool gemm_f32_takes_norm(int M, int N, int K, const void* x, const void* W, cons
   return K % 4 == 0 && small_tiles(M, N) && aligned16(x) && aligned16(W) && aligned16(norm.g) && aligned16(norm.h) && aligned16(norm.save);
 }
 
+// The gate within the product gives a block two fragments, half as many blocks and half as many steps in flight: it takes less where the
+// plain product has more than a block of 16 x 16 per CU, or few steps.  Measured over layers of hidden 512 to 8192 (us, gate and up as
+// one product and SwiGLU -> the gate within): 288 to 1024 tiles -1 to -40 (one token, 768 tiles, from K = 3072 on: +5 to +13), up to
+// 256 tiles K = 512 to 1024 -0.5, 1536 +0.4, 2048 +1.7, 4096 +3.8, 8192 +12.
+bool gemm_f32_takes_gate(int M, int F, int K) {
+  return K <= 1024 || (long)((M + 15) / 16) * ((2 * F + 15) / 16) > 256;
+}
+
 int32_t launch_gemm_f32_norm_glu(const void* A, const void* W, void* C, const void* bias, int M, int N, int K, size_t ldc, const F32Norm* norm,
                                  const F32Glu* glu, hipStream_t s) {
   // (N: columns of C; the gated form's W has 2 N rows)

@@ -455,7 +455,9 @@ def test_layer_c1_down_only():
 # fp32 projections that norm their rows and gate their product: K of no whole steps, a ragged column tile of gate and up, rows of the
 # bypass written beside the product; 1024 tiles of gate and up (33 rows in three row tiles) and the sizes past them
 @pytest.mark.parametrize("hidden,ffn,targets", [(260, 100, ("q", "v", "down")), (20, 36, ("k", "gate")), (516, 52, ("o",)),
-                                                (64, 2728, ("q",)), (64, 2736, ("v", "up"))])
+                                                (64, 2728, ("q",)), (64, 2736, ("v", "up")),
+                                                # more than 1024 columns: the gate within from 257 tiles on (33 rows: three row tiles)
+                                                (1024, 52, ("q",)), (1028, 52, ("q",)), (1028, 672, ("v",)), (1028, 680, ("q",)), (1028, 688, ("up",))])
 def test_layer_fp32_norm_and_gate_within_the_projections(hidden, ffn, targets):
     say(f"layer fp32 hidden {hidden} ffn {ffn} {targets}")
     cfg = C1.with_(name="f32_%d" % hidden, hidden=hidden, ffn=ffn, lora_targets=targets)

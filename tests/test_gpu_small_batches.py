@@ -200,3 +200,32 @@ def test_shrink_products(rank, ffn, window):
                      lora_targets=("q", "k", "v", "o", "gate", "up", "down"))
     b = gen.mixed_batch(cfg.page_size, 31, decode_ctx=(1, 40, 3), prefill=[(0, 37, 37)], finetune=[(0, window, 2 * window)])
     run_layer_case(cfg, b, ft_window=window, prefill_chunk=37, bwd_windows=[window, window], seed=31)
+
+
+# fp32 gate/up product of few tiles and many columns: with the norm within, the gate not - about what the plain product of its size takes
+# (1.5 to 1.7 times that with half the blocks and half the steps in flight)
+def test_fp32_gate_up_product_of_few_tiles_takes_about_the_plain_products_time():
+    kid, T = B.KERNEL_IDS["generic"], 16
+    cfg = CONFIGS["c1_tiny_f32"].with_(name="long_f32", hidden=8192, ffn=512, lora_targets=())
+    dev = HH.DeviceLayer(cfg, gen.layer_weights(cfg, 31, 0))
+    b = gen.mixed_batch(16, 1, decode_ctx=(20,) * T)
+    db, pool = HH.DeviceBatch(cfg, b.requests, b.seq_pages, b.num_pages), HH.DevicePool(cfg, b.num_pages)
+    ws = HH.Workspace(dev.c, T, db.host_maps.n_parts)
+    x = torch.randn(T, cfg.hidden, device="cuda")
+    y, gu = torch.empty_like(x), torch.empty(T, 2 * cfg.ffn, device="cuda")
+
+    def timed(fn):
+        fn()
+        B.flexco_kernel_timer_sample(kid, 1)
+        B.flexco_kernel_timer_start(kid, 256)
+        for _ in range(10):
+            fn()
+        torch.cuda.synchronize()
+        each = B.flexco_kernel_timer_read(kid)
+        B.flexco_kernel_timer_stop(kid)
+        n = len(each) // 10
+        return [1e3 * min(each[i::n]) for i in range(n)]
+    layer = timed(lambda: B.flexco_layer_forward(dev.c, dev.w, None, db.maps, x, y, pool.c, None, ws.ptr, ws.bytes))
+    (plain,) = timed(lambda: B.flexco_gemm(x, dev.t["wgu"], gu, None, None, T, 2 * cfg.ffn, cfg.hidden, 0, B.FLEXCO_F32))
+    print(f"type-generic launches of the layer {layer}, the plain product {plain:.1f} us", flush=True)
+    assert layer[-2] <= 1.35 * plain             # qkv, (attention,) o, gate/up, down
