@@ -16,7 +16,11 @@ if torch.cuda.is_available():
     from test_gpu_train import run_loss
 
 
-def run_gemm(M, N, K, trans, bias=True, res=True):
+def run_gemm(M, N, K, trans, bias=True, res=True, tile=None, stages=None):
+    """tile, stages: the (rows, columns) and LDS ring the product is meant to run on, in one launch over all of K"""
+    if tile:
+        (rows, cols, width, ranges, ring), = B.flexco_gemm_plan(M, N, K, trans, 0)
+        assert (rows, cols) == tile and (width, ranges) == (N, 1) and ring == (stages or ring), (rows, cols, width, ranges, ring)
     g = torch.Generator(device="cuda").manual_seed(M * 7 + N * 3 + K + trans)
     rnd = lambda *s: torch.randn(s, generator=g, device="cuda").to(torch.bfloat16)  # noqa: E731
     A, W = rnd(M, K), rnd(*((K, N) if trans else (N, K)))
@@ -47,27 +51,31 @@ def test_forward_tiles(tile, M, N, K):
 # 256 x 128 tiles (one launch where the plan has two rounds or leaves CUs idle): odd and even numbers of stages, bias and residual
 # or neither, ragged last rows and columns
 @pytest.mark.parametrize("bias,res", [(True, True), (False, False)])
-@pytest.mark.parametrize("M,N,K", [(1000, 7160, 64 * 25), (1000, 7160, 64 * 20), (1200, 6152, 64 * 25), (769, 8192, 64 * 20)])
-def test_forward_tiles_256_by_128(M, N, K, bias, res):
+@pytest.mark.parametrize("M,N,K,rows", [(1000, 7160, 64 * 25, 256), (1000, 7160, 64 * 20, 256), (1200, 6152, 64 * 25, 256), (769, 8192, 64 * 20, 224)])
+def test_forward_tiles_256_by_128(M, N, K, rows, bias, res):
     print(f"forward M={M} N={N} K={K} bias {bias} residual {res}", flush=True)
-    run_gemm(M, N, K, 0, bias=bias, res=res)
+    run_gemm(M, N, K, 0, bias=bias, res=res, tile=(rows, 128))
 
 
 # the 256-row kernel's rows are M's own, 160 to 256 in steps of 32: each of them at each width, even and odd numbers of stages
-@pytest.mark.parametrize("M,N,K", [(257, 24592, 512), (257, 24616, 448), (321, 24880, 512), (324, 24736, 448), (387, 24648, 512), (578, 16360, 448),
-                                   (673, 16368, 512), (449, 24656, 448), (131, 32824, 512), (132, 33208, 448), (386, 16544, 512), (194, 32864, 448),
-                                   (899, 8216, 512), (681, 10888, 448), (129, 29552, 512), (258, 11240, 576), (193, 29520, 512), (387, 14752, 448),
-                                   (674, 9840, 512), (900, 7336, 448)])
-def test_forward_tiles_of_the_rows_there_are(M, N, K):
-    print(f"forward M={M} N={N} K={K}", flush=True)
-    run_gemm(M, N, K, 0)
+ROWS_THERE_ARE = {(160, 256): [(257, 24592, 512), (257, 24616, 448)], (192, 256): [(321, 24880, 512), (324, 24736, 448)],
+                  (224, 256): [(387, 24648, 512), (578, 16360, 448)], (256, 256): [(673, 16368, 512), (449, 24656, 448)],
+                  (192, 192): [(131, 32824, 512), (132, 33208, 448)], (224, 192): [(386, 16544, 512), (194, 32864, 448)],
+                  (256, 192): [(899, 8216, 512), (681, 10888, 448)], (192, 128): [(129, 29552, 512), (258, 11240, 576)],
+                  (224, 128): [(193, 29520, 512), (387, 14752, 448)], (256, 128): [(674, 9840, 512), (900, 7336, 448)]}
 
 
-@pytest.mark.parametrize("M,N,K", [(129, 33352, 512), (130, 32832, 448), (161, 32928, 512), (163, 32848, 448), (193, 32968, 512), (389, 16400, 448),
-                                   (674, 10984, 512), (675, 10952, 448)])
-def test_input_gradient_tiles_of_the_rows_there_are(M, N, K):
-    print(f"input gradient M={M} N={N} K={K}", flush=True)
-    run_gemm(M, N, K, 1, bias=False, res=False)
+@pytest.mark.parametrize("tile,M,N,K", [(tile, *p) for tile, products in ROWS_THERE_ARE.items() for p in products])
+def test_forward_tiles_of_the_rows_there_are(tile, M, N, K):
+    print(f"forward tile {tile} M={M} N={N} K={K}", flush=True)
+    run_gemm(M, N, K, 0, tile=tile)
+
+
+@pytest.mark.parametrize("rows,M,N,K", [(160, 129, 33352, 512), (160, 130, 32832, 448), (192, 161, 32928, 512), (192, 163, 32848, 448),
+                                        (224, 193, 32968, 512), (224, 389, 16400, 448), (256, 674, 10984, 512), (256, 675, 10952, 448)])
+def test_input_gradient_tiles_of_the_rows_there_are(rows, M, N, K):
+    print(f"input gradient of {rows} rows, M={M} N={N} K={K}", flush=True)
+    run_gemm(M, N, K, 1, bias=False, res=False, tile=(rows, 256))
 
 
 # at most 64 rows: 64 x 128 tiles with a ring of six stages
@@ -75,7 +83,7 @@ def test_input_gradient_tiles_of_the_rows_there_are(M, N, K):
 @pytest.mark.parametrize("M,N", [(1, 8), (63, 136), (64, 1000)])
 def test_forward_tiles_of_few_rows(M, N, K):
     print(f"forward M={M} N={N} K={K}", flush=True)
-    run_gemm(M, N, K, 0)
+    run_gemm(M, N, K, 0, tile=(64, 128))
 
 
 # rows of W a multiple of 4 KB apart: the column tiles of the 64-row form start at stages of their own (its cut form, the cut 128 x 128 one and the
@@ -97,26 +105,29 @@ def test_forward_tiles_of_few_rows_at_a_pitch_of_4_kb(M, N, K):
     run_gemm(M, N, K, 0)
 
 
+# (four wavefronts, a ring of two: windows of many rows, and of few where the tiles leave CUs idle)
 @pytest.mark.parametrize("K", [64, 128, 192, 448])
-@pytest.mark.parametrize("M,N", [(1030, 13832), (130, 136), (64, 40)])
+@pytest.mark.parametrize("M,N", [(1030, 13832), (258, 136), (64, 40), (33, 264), (1, 8)])
 def test_input_gradient_tiles_128(M, N, K):
     print(f"input gradient M={M} N={N} K={K}", flush=True)
-    run_gemm(M, N, K, 1, bias=False, res=False)
+    run_gemm(M, N, K, 1, bias=False, res=False, tile=(128, 128), stages=2)
 
 
 # 128 x 128 tiles by eight wavefronts, two halves of every stage of K: one stage to two rounds of the ring of four, ragged last
-# rows and columns (in ranges of K and with a rank-r extension: the windows of test_gpu_model_iter and the loss head below)
+# rows and columns (with a rank-r extension: the windows of test_gpu_small_batches and test_gpu_model_iter)
 @pytest.mark.parametrize("K", [64 * n for n in (1, 2, 3, 4, 5, 7, 8, 9)])
-@pytest.mark.parametrize("M,N", [(1, 8), (33, 264), (127, 128), (129, 4104), (256, 1000)])
+@pytest.mark.parametrize("M,N", [(1, 32008), (33, 32648), (80, 32136), (127, 128), (129, 4104), (130, 136), (256, 1000)])
 def test_input_gradient_tiles_by_eight_wavefronts(M, N, K):
     print(f"input gradient M={M} N={N} K={K}", flush=True)
-    run_gemm(M, N, K, 1, bias=False, res=False)
+    run_gemm(M, N, K, 1, bias=False, res=False, tile=(128, 128), stages=4)
 
 
-# ... in ranges that differ by a stage (131 stages in 4, 67 in 8 and more)
-@pytest.mark.parametrize("n,H,V", [(200, 4096, 64 * 131), (100, 520, 64 * 67)])
+# ... in ranges that differ by a stage (131 stages in 4, 67 in 7 and more), which the loss head's scratch is for
+@pytest.mark.parametrize("n,H,V", [(200, 4096, 64 * 131), (100, 520, 64 * 67), (1, 4096, 64 * 67), (8, 4104, 64 * 67), (33, 264, 64 * 67)])
 def test_input_gradient_by_eight_wavefronts_in_ranges(n, H, V):
-    print(f"loss head n={n} H={H} V={V}", flush=True)
+    (rows, cols, _, ranges, ring), = B.flexco_gemm_plan(n, H, V, 1, 16 * n * H)
+    print(f"loss head n={n} H={H} V={V}: {ranges} ranges", flush=True)
+    assert (rows, cols, ring) == (128, 128, 4) and (V // 64) % ranges != 0
     run_loss("bf16", n, H, V, seed=5)
 
 
@@ -130,9 +141,9 @@ def test_input_gradient_tiles_256(M, N, K):
 # the loss head brings split-K scratch of 16 n H floats: its input gradient contracts over V in V / 64 stages
 @pytest.mark.parametrize("n,H,V", [(385, 4104, 64 * 43), (257, 4096, 64 * 131)])
 def test_input_gradient_in_unequal_ranges(n, H, V):
-    r = B.flexco_gemm_k_ranges(n, H, V, 1, 16 * n * H)
+    (rows, cols, _, r, _), = B.flexco_gemm_plan(n, H, V, 1, 16 * n * H)
     print(f"loss head n={n} H={H} V={V}: {r} ranges", flush=True)
-    assert r > 1 and (V // 64) % r != 0
+    assert rows > 128 and cols == 256 and r > 1 and (V // 64) % r != 0
     run_loss("bf16", n, H, V, seed=3)
 
 

@@ -86,12 +86,13 @@ def test_layer_products_from_their_own_stage(hidden, ffn, chunk, window):
 
 # A gated product that covers the chip in one round of 128-column tiles (up to 256 tokens) or 256-column ones, of 192, 256, 160, 192
 # and 224 rows; adapter and finetune rows, a last column tile of eight activations
-@pytest.mark.parametrize("chunk,window", [(60, 66), (141, 96), (150, 110), (200, 130), (220, 196)])
-def test_layer_gated_product_on_tiles_of_its_rows(chunk, window):
+@pytest.mark.parametrize("chunk,window,tile", [(60, 66, (192, 128)), (141, 96, (256, 128)), (150, 110, (160, 256)), (200, 130, (192, 256)),
+                                               (220, 196, (224, 256))])
+def test_layer_gated_product_on_tiles_of_its_rows(chunk, window, tile):
     cfg = WIDE.with_(name="gated_rows", ffn=13832)
     b = gen.batch_scaled(17, 4, 3, 90, [(0, chunk, 2 * chunk)], [(0, window, 2 * window)])
     print(f"layer of {b.n_tokens} tokens, ffn {cfg.ffn}", flush=True)
-    assert 128 < b.n_tokens <= 448
+    assert B.flexco_gemm_plan(b.n_tokens, 2 * cfg.ffn, cfg.hidden, 0) == [(*tile, 2 * cfg.ffn, 1, 2)]
     run_layer_case(cfg, b, ft_window=window, prefill_chunk=chunk, bwd_windows=[window, window], seed=17)
 
 
