@@ -861,8 +861,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_quad_kernel(const bf16_t* __res
 // Input-gradient products of few row tiles: 128 x 128 tiles by eight wavefronts in two groups of four (2 x 2 of 64 x 64 each, two
 // wavefronts per SIMD).  A group multiplies its half of every stage's 64 of K, and the groups' sums are added through LDS at
 // the end.
-// What bounds these products is the weights' way in (256 rows at the 8B shape: about 50 GB/s per CU of operand tiles, whatever the
-// ring's depth; 0.65 us per stage with weights from HBM, 0.45 from the memory-side cache), and what they pay on top is partial sums: to
+// What bounds these products is the weights' way in (256 x 14336 and 16384, K 1024 to 4096: about 53 GB/s per CU of operand tiles,
+// whatever the ring's depth; 0.60 to 0.63 us per stage with weights from HBM, 0.41 from the memory-side cache), and what they pay on top is partial sums: to
 // fill the chip with two blocks of four wavefronts per CU takes twice the ranges of K.  One block of eight has the second
 // wavefront per SIMD without them, and a ring of four stages instead of two.  Products and the launch that adds the ranges, us, M x N x K,
 // two blocks per CU -> this kernel (ranges): 256 x 14336 x 4096 57 -> 47 (2 -> 1), 256 x 4096 x 4096 26.7 -> 22.6 (8 -> 4),
